@@ -253,8 +253,9 @@ int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void
  *   a_dev: device, fp32 [q];  m_dev: device, fp32 [r];  bits_dev: device, dbf_tiled_bytes(q, r) bytes, the
  *          signs S in the tile layout (as dbf_svid writes them);  U_dev: device, fp32 [q][r].
  *          All four are read as the current iterate and overwritten with the next one.
- *   workspace_dev: device, 256-byte aligned, >= dbf_admm_workspace_bytes(q, r) bytes (two q x r fp32
- *          matrices and the SVID workspace).
+ *   workspace_dev: device, 256-byte aligned, >= dbf_admm_workspace_bytes(q, r) bytes (one q x r fp32 matrix, the
+ *          two operands of the contraction as three bf16 planes each -- 6 bytes per entry of a q x q and a q x r
+ *          matrix -- and the SVID workspace).
  * Asynchronous on hip_stream, allocates nothing; results do not depend on scheduling.  NaNs unsupported.
  * Errors: DBF_EINVAL (null or misaligned pointers, sizes out of range, rho <= 0 or not finite,
  * svid_iters < 1), DBF_EWORKSPACE, DBF_EHIP. */
@@ -271,14 +272,14 @@ int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int r, float r
  * with S (q x p, entries +-1) the packed sign matrix (for the left-factor update of a layer: S = the layer's B
  * signs, q = k, p = n_in, b its input scales, m2 the part of the middle scales that stays with it).  Computes
  *     C = B^T W  (q x r)     and     Minv = (B^T B + rho I)^-1  (q x q)
- * by fp32 matrix-core contractions that read the sign tiles directly (B is never stored densely), a blocked
- * Cholesky factorisation B^T B + rho I = R^T R (blocks of 128), the inverse of the factor and one more
+ * by contractions of fp32 accuracy on the bf16 matrix cores (fp32 operands split into three bf16 parts, signs as one),
+ * a blocked fp32 Cholesky factorisation B^T B + rho I = R^T R (blocks of 128), the inverse of the factor and one more
  * contraction.  The outputs are what dbf_admm_step takes (Minv is symmetric up to rounding).
  *   bits_dev: device, dbf_tiled_bytes(q, p) bytes: S in the tile layout, rows q, columns p (read only).
  *   m2_dev: device fp32 [q];  b_dev: device fp32 [p];  W_dev: device fp32 [p][r] row major (all read only).
  *   rho > 0.   Minv_dev: device fp32 [q][q] out;   C_dev: device fp32 [q][r] out.
- *   workspace_dev: device, 256-byte aligned, >= dbf_admm_prepare_workspace_bytes(p, q, r) bytes (a q x q matrix
- *          and the inverses of the diagonal blocks).
+ *   workspace_dev: device, 256-byte aligned, >= dbf_admm_prepare_workspace_bytes(p, q, r) bytes (a q x q matrix,
+ *          the inverses of the diagonal blocks, S as bf16 and the larger of S, W and the q x q matrix as three bf16 planes).
  *   not_positive_definite_dev: device int (4-byte aligned) or NULL: set to the number of diagonal blocks whose
  *          factorisation met a non-positive pivot (0 = fine; with rho > 0 the matrix is positive definite and
  *          this only happens when rounding swamps rho).  Read it with an ordinary stream-ordered copy.

@@ -3,22 +3,24 @@
 //
 //     Minv = (B^T B + rho I)^-1  (q x q),   C = B^T W  (q x r)
 //
-//     R  = C + rho (a . S . m^T - U)           dbf_admm_rhs_kernel     (A = a . S . m^T never exists densely:
-//                                                                       S is read from the packed tile layout)
-//     Z  = Minv^T R + U   (= W_hat + U)        dbf_admm_gemm_kernel    fp32 matrix cores, U added in the epilogue
+//     R  = C + rho (a . S . m^T - U)           dbf_admm_rhs_kernel     (A = a . S . m^T never exists densely: S is read
+//                                                                       from the packed tile layout; R only as bf16 planes)
+//     Z  = Minv^T R + U   (= W_hat + U)        dbf_split_gemm_kernel   bf16 matrix cores, three-way split operands
+//                                                                       (dbf_split_gemm.h), U added in the epilogue
 //     (S', a', m') = SVID(Z)                   dbf_svid (dbf_svid.hip)
 //     U' = Z - a' . S' . m'^T  (= U + W_hat - A')   dbf_admm_dual_kernel
 //
-// The contraction is q x q x r in fp32 (34 GFLOP at q = 2048, r = 4096) and dominates; the elementwise
-// kernels and the projection are bandwidth bound.  The paper gives no kernel design for this step.
+// The contraction is q x q x r in fp32 accuracy (34 GFLOP at q = 2048, r = 4096) and dominates; the elementwise
+// kernels and the projection are bandwidth bound.  Measured at that size: the contraction 331 us on the fp32 matrix cores,
+// 182 us (0.19 PFLOP/s; 1.13 PFLOP/s of bf16 products) with split operands, whose planes cost 7 (Minv) + 6 us (R); the
+// update 389 -> 302 us; error against 64 bits 8.1e-6 -> 5.1e-6 (fewer roundings: 16 products enter the accumulator at once).
+// The paper gives no kernel design for this step.
 #include "dbf_kernels.h"
+#include "dbf_split_gemm.h"
 
 #include <cmath>
 
 namespace {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 
 // ---------------------------------------------------------------------------------------------
 // Elementwise kernels.  One workgroup per 128 x 64 tile of the sign matrix; thread t takes the four
@@ -38,15 +40,10 @@ __device__ inline TileThread tile_thread(int t) {
     return x;
 }
 
-// MODE 0: out = C + rho (a_i m_j s_ij - U)     (in1 = C, in2 = U)
-// MODE 1: out = Z - a_i m_j s_ij               (in1 = Z; out may be any buffer but Z)
-template <int MODE>
-__global__ __launch_bounds__(256) void dbf_admm_elementwise_kernel(const float* __restrict__ in1,
-                                                                  const float* __restrict__ in2, float rho,
-                                                                  const float* __restrict__ a,
-                                                                  const float* __restrict__ m,
-                                                                  const uint8_t* __restrict__ bits, int rows, int cols,
-                                                                  int n_ct, int vec_ok, float* __restrict__ out) {
+// U' = Z - a_i m_j s_ij
+__global__ __launch_bounds__(256) void dbf_admm_dual_kernel(const float* __restrict__ Z, const float* __restrict__ a,
+                                                           const float* __restrict__ m, const uint8_t* __restrict__ bits,
+                                                           int rows, int cols, int n_ct, int vec_ok, float* __restrict__ out) {
     const TileThread x = tile_thread(threadIdx.x);
     if (x.col >= cols) return;
     const unsigned w =
@@ -61,26 +58,18 @@ __global__ __launch_bounds__(256) void dbf_admm_elementwise_kernel(const float* 
         if (row >= rows) break;
         const float ai = a[row];
         const size_t at = (size_t)row * cols + x.col;
-        float v1[4], v2[4] = {0.f, 0.f, 0.f, 0.f}, res[4];
+        float v[4], res[4];
         if (vec) {
-            const v4f p = *reinterpret_cast<const v4f*>(in1 + at);
-            v1[0] = p.x;  v1[1] = p.y;  v1[2] = p.z;  v1[3] = p.w;
-            if (MODE == 0) {
-                const v4f u = *reinterpret_cast<const v4f*>(in2 + at);
-                v2[0] = u.x;  v2[1] = u.y;  v2[2] = u.z;  v2[3] = u.w;
-            }
+            const v4f p = *reinterpret_cast<const v4f*>(Z + at);
+            v[0] = p.x;  v[1] = p.y;  v[2] = p.z;  v[3] = p.w;
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                v1[e] = x.col + e < cols ? in1[at + e] : 0.f;
-                if (MODE == 0) v2[e] = x.col + e < cols ? in2[at + e] : 0.f;
-            }
+            for (int e = 0; e < 4; ++e) v[e] = x.col + e < cols ? Z[at + e] : 0.f;
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float am = ai * mj[e];
-            const float A = ((w >> (8 * e + s)) & 1u) ? am : -am;
-            res[e] = MODE == 0 ? v1[e] + rho * (A - v2[e]) : v1[e] - A;
+            res[e] = v[e] - (((w >> (8 * e + s)) & 1u) ? am : -am);
         }
         if (vec) {
             *reinterpret_cast<v4f*>(out + at) = (v4f){res[0], res[1], res[2], res[3]};
@@ -92,9 +81,32 @@ __global__ __launch_bounds__(256) void dbf_admm_elementwise_kernel(const float* 
     }
 }
 
+// R = C + rho (a_k m_j s_kj - U) (q x r; k = its row is the summation index of the contraction), written straight into
+// bf16 planes: R exists nowhere in fp32.  The lane's eight rows are one bit of eight bytes 16 apart of one sign tile.
+__global__ __launch_bounds__(256) void dbf_admm_rhs_kernel(const float* __restrict__ C, const float* __restrict__ U, float rho,
+                                                          const float* __restrict__ a, const float* __restrict__ m,
+                                                          const uint8_t* __restrict__ bits, int q, int r, int n_ct,
+                                                          uint8_t* __restrict__ planes) {
+    const SgSite s = sg_site(q, 3);
+    if (!s.live) return;
+    const int j = min(s.i, r - 1), bit = (s.k0 & 127) >> 4;
+    const uint8_t* sb = bits + ((size_t)(s.k0 >> 7) * n_ct + (j >> 6)) * DBF_TILE_BYTES + 256 * ((j >> 4) & 3) + 16 * (s.k0 & 15) + (j & 15);
+    const float mj = m[j];
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int k = min(s.k0 + e, q - 1);   // (clamped, not branched around: the loads of all eight rows in flight)
+        const size_t at = (size_t)k * r + j;
+        const float am = a[k] * mj;
+        const float v = C[at] + rho * (((sb[16 * e] >> bit) & 1 ? am : -am) - U[at]);
+        x[e] = (s.k0 + e < q && s.i < r) ? v : 0.f;
+    }
+    sg_store3(planes, s.off, x);
+}
+
 // ---------------------------------------------------------------------------------------------
-// out = alpha (P^T Q) . rs . cs^T + add + diag I on the fp32 matrix cores:
-//     out[i][j] = alpha * rs[i] * cs[j] * sum_k P[k][i] Q[k][j] + add[i][j] + (i == j ? diag : 0).
+// out = alpha P^T Q + add on the fp32 matrix cores (the short contractions of the factorisation below):
+//     out[i][j] = alpha * sum_k P[k][i] Q[k][j] + add[i][j].
 // Both operands are read by rows of k ("k major"), which is how v_mfma_f32_32x32x2_f32 wants them
 // (lane l supplies A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32]), so tiles go from memory
 // to LDS without a transpose.  Workgroup = 128 x 128 outputs, 4 wavefronts of 64 x 64 (2 x 2 blocks of
@@ -104,14 +116,6 @@ __global__ __launch_bounds__(256) void dbf_admm_elementwise_kernel(const float* 
 // a wavefront (k and k + 1) read different banks.
 // Workgroups are renumbered so that a compute die (linear id modulo 8) works on neighbouring column
 // blocks: the Q tiles it needs stay in its own L2.
-//
-// An operand may also be a packed sign matrix S (rows = the operand's output index, columns = k) in the
-// 128 x 64 tile layout, scaled per k: P[k][i] = kscale[k] * S[i][k] (template arguments PS / QS).  The 16 x 128
-// operand slice of a step is 256 bytes of one tile (the step's 16 columns are one byte group g, byte
-// 16 r + j of it holds in bit s the sign of row 16 s + r, column 16 g + j): 64 threads read one word each and
-// write its 4 x 8 values to LDS.  Padding bits of the tiles are zero bits, i.e. -1, not zero: columns beyond K
-// get a zero scale here, rows beyond M are never stored.  This is how the fixed factor of the ADMM update
-// stays in its packed form: B^T B and B^T W are formed from the sign bits directly.
 // ---------------------------------------------------------------------------------------------
 constexpr int GT = 128;         // outputs per workgroup side
 #ifndef DBF_ADMM_GK
@@ -119,26 +123,17 @@ constexpr int GT = 128;         // outputs per workgroup side
 #endif
 constexpr int GK = DBF_ADMM_GK; // values of k per step
 constexpr int GLD = GT + 32;    // LDS row length in floats
-static_assert(GK == 16, "a step of a sign operand is one 16-column byte group of a tile");
 
 struct GemmArgs {
-    const float* P;        // dense [K][M], leading dimension ldp           (PS == false)
-    const float* Q;        // dense [K][N], leading dimension ldq           (QS == false)
-    const uint8_t* Pbits;  // packed signs, rows = i (M of them), cols = k  (PS == true); first tile of row i = 0
-    const uint8_t* Qbits;  // the same for j                                (QS == true)
-    const float* kscale;   // [K] scale per k of the sign operands
+    const float* P;        // [K][M], leading dimension ldp
+    const float* Q;        // [K][N], leading dimension ldq
     const float* add;      // [M][N] with leading dimension lda, or NULL
-    const float* rs;       // [M] or NULL
-    const float* cs;       // [N] or NULL
     float* out;            // [M][N], leading dimension ldo (may be `add`: every element is read before it is written)
     size_t ldp, ldq, lda, ldo;
-    float alpha, diag;
+    float alpha;
     int M, N, K;
-    int bits_nct;          // column tiles of the sign matrices
     int vec_p, vec_q;      // rows of P / Q can be read in 16-byte pieces
     int upper;             // symmetric output: workgroups whose block lies wholly below the diagonal do nothing
-    int ktri;              // both operands are lower triangular in (k, output index), i.e. zero for k < index: the
-                           // summation starts at the first k that can contribute to the block
 };
 
 __device__ inline v4f load_row4(const float* base, size_t ld, int k, int K, int c, int C, int vec) {
@@ -153,7 +148,6 @@ __device__ inline v4f load_row4(const float* base, size_t ld, int k, int K, int 
     return r;
 }
 
-template <bool PS, bool QS>
 __global__ __launch_bounds__(256) void dbf_admm_gemm_kernel(const GemmArgs g) {
     __shared__ __align__(16) float As[2][GK][GLD];
     __shared__ __align__(16) float Bs[2][GK][GLD];
@@ -168,57 +162,22 @@ __global__ __launch_bounds__(256) void dbf_admm_gemm_kernel(const GemmArgs g) {
     const int wi = (w & 1) * 64, wj = (w >> 1) * 64;  // this wavefront's 64 x 64 corner in the tile
     const int l32 = lane & 31, h = lane >> 5;
 
-    // staging role, dense operand: GK / 8 16-byte pieces of a tile per thread: rows k = tid / 32 (+ 8, ...),
-    // columns 4 (tid % 32).  Sign operand: threads 0..63 take word tid of the step's 256 bytes (wavefront 0 for P,
-    // wavefront 1 for Q, so that the two do not queue behind each other).
+    // staging role: GK / 8 16-byte pieces of a tile per thread: rows k = tid / 32 (+ 8, ...), columns 4 (tid % 32)
     constexpr int NP = GK / 8;
     const int sk = tid >> 5, sc = 4 * (tid & 31);
     v4f ra[NP], rb[NP];
-    unsigned sa = 0, sb = 0;
-    float ka[4] = {0.f, 0.f, 0.f, 0.f}, kb[4] = {0.f, 0.f, 0.f, 0.f};
-    const int st = tid & 63;                       // word of the step
-    const int s_r = st >> 2, s_j = 4 * (st & 3);   // row within the 16-row group, first of its 4 columns
-    const uint8_t* p_tiles = PS ? g.Pbits + (size_t)(i0 / DBF_TILE_ROWS) * g.bits_nct * DBF_TILE_BYTES : nullptr;
-    const uint8_t* q_tiles = QS ? g.Qbits + (size_t)(j0 / DBF_TILE_ROWS) * g.bits_nct * DBF_TILE_BYTES : nullptr;
-    auto fetch_signs = [&](const uint8_t* tiles, int k0, unsigned& word, float (&ks)[4]) {
-        // (k0 is a multiple of 16: tile k0 / 64, byte group (k0 % 64) / 16)
-        const int kk = min(k0, (g.bits_nct * DBF_TILE_COLS) - GK);
-        word = reinterpret_cast<const unsigned*>(tiles + (size_t)(kk >> 6) * DBF_TILE_BYTES + 256 * ((kk >> 4) & 3))[st];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ks[e] = (k0 + s_j + e < g.K) ? g.kscale[k0 + s_j + e] : 0.f;
-    };
     auto fetch = [&](int k0) {
-        if (PS) {
-            if (w == 0) fetch_signs(p_tiles, k0, sa, ka);
-        } else {
 #pragma unroll
-            for (int e = 0; e < NP; ++e) ra[e] = load_row4(g.P, g.ldp, k0 + sk + 8 * e, g.K, i0 + sc, g.M, g.vec_p);
+        for (int e = 0; e < NP; ++e) {
+            ra[e] = load_row4(g.P, g.ldp, k0 + sk + 8 * e, g.K, i0 + sc, g.M, g.vec_p);
+            rb[e] = load_row4(g.Q, g.ldq, k0 + sk + 8 * e, g.K, j0 + sc, g.N, g.vec_q);
         }
-        if (QS) {
-            if (w == 1) fetch_signs(q_tiles, k0, sb, kb);
-        } else {
-#pragma unroll
-            for (int e = 0; e < NP; ++e) rb[e] = load_row4(g.Q, g.ldq, k0 + sk + 8 * e, g.K, j0 + sc, g.N, g.vec_q);
-        }
-    };
-    auto stage_signs = [&](float (*dst)[GLD], unsigned word, const float (&ks)[4]) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int s = 0; s < 8; ++s) dst[s_j + e][16 * s + s_r] = ((word >> (8 * e + s)) & 1u) ? ks[e] : -ks[e];
     };
     auto stage = [&](int buf) {
-        if (PS) {
-            if (w == 0) stage_signs(As[buf], sa, ka);
-        } else {
 #pragma unroll
-            for (int e = 0; e < NP; ++e) *reinterpret_cast<v4f*>(&As[buf][sk + 8 * e][sc]) = ra[e];
-        }
-        if (QS) {
-            if (w == 1) stage_signs(Bs[buf], sb, kb);
-        } else {
-#pragma unroll
-            for (int e = 0; e < NP; ++e) *reinterpret_cast<v4f*>(&Bs[buf][sk + 8 * e][sc]) = rb[e];
+        for (int e = 0; e < NP; ++e) {
+            *reinterpret_cast<v4f*>(&As[buf][sk + 8 * e][sc]) = ra[e];
+            *reinterpret_cast<v4f*>(&Bs[buf][sk + 8 * e][sc]) = rb[e];
         }
     };
 
@@ -230,10 +189,7 @@ __global__ __launch_bounds__(256) void dbf_admm_gemm_kernel(const GemmArgs g) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[bi][bj][v] = 0.f;
 
-    // (lower triangular operands: P[k][i] = 0 for k < i and Q[k][j] = 0 for k < j, so k starts at the larger of
-    //  the block's first row and first column -- a multiple of the step)
-    const int k_first = g.ktri ? max(i0, j0) : 0;
-    const int steps = (g.K - k_first + GK - 1) / GK;
+    const int steps = (g.K + GK - 1) / GK;
     // (the operand values of k pair kk + 1 are read from LDS before the matrix instructions of pair kk are
     // issued, into the other of two register sets: the LDS latency then hides behind 256 cycles of matrix work)
     auto multiply = [&](int buf) {
@@ -260,10 +216,10 @@ __global__ __launch_bounds__(256) void dbf_admm_gemm_kernel(const GemmArgs g) {
     // A workgroup whose dense tiles lie wholly inside both operands (and whose rows can be read in 16-byte pieces)
     // takes a loop without a single branch: guarded loads put a wait for memory between the request and the
     // matrix instructions of every step.  The last step requests its own tiles once more instead of none.
-    const bool inside = !PS && !QS && g.vec_p && g.vec_q && i0 + GT <= g.M && j0 + GT <= g.N && (g.K - k_first) % GK == 0;
+    const bool inside = g.vec_p && g.vec_q && i0 + GT <= g.M && j0 + GT <= g.N && g.K % GK == 0;
     if (inside) {
-        const float* pa = g.P + (size_t)(k_first + sk) * g.ldp + i0 + sc;
-        const float* pb = g.Q + (size_t)(k_first + sk) * g.ldq + j0 + sc;
+        const float* pa = g.P + (size_t)sk * g.ldp + i0 + sc;
+        const float* pb = g.Q + (size_t)sk * g.ldq + j0 + sc;
         auto fetch_inside = [&](int k0) {
 #pragma unroll
             for (int e = 0; e < NP; ++e) {
@@ -281,11 +237,11 @@ __global__ __launch_bounds__(256) void dbf_admm_gemm_kernel(const GemmArgs g) {
             __syncthreads();
         }
     } else {
-        fetch(k_first);
+        fetch(0);
         stage(0);
         __syncthreads();
         for (int s = 0; s < steps; ++s) {
-            if (s + 1 < steps) fetch(k_first + (s + 1) * GK);
+            if (s + 1 < steps) fetch((s + 1) * GK);
             multiply(s & 1);
             if (s + 1 < steps) stage((s & 1) ^ 1);
             __syncthreads();
@@ -299,15 +255,12 @@ __global__ __launch_bounds__(256) void dbf_admm_gemm_kernel(const GemmArgs g) {
         for (int bj = 0; bj < 2; ++bj) {
             const int col = j0 + wj + 32 * bj + l32;
             if (col >= g.N) continue;
-            const float csj = g.cs ? g.cs[col] * g.alpha : g.alpha;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = i0 + wi + 32 * bi + 8 * (v >> 2) + 4 * h + (v & 3);
                 if (row < g.M) {
-                    float val = acc[bi][bj][v] * csj;
-                    if (g.rs) val *= g.rs[row];
+                    float val = acc[bi][bj][v] * g.alpha;
                     if (g.add) val += g.add[(size_t)row * g.lda + col];
-                    if (row == col) val += g.diag;
                     g.out[(size_t)row * g.ldo + col] = val;
                 }
             }
@@ -318,23 +271,20 @@ __global__ __launch_bounds__(256) void dbf_admm_gemm_kernel(const GemmArgs g) {
 inline GemmArgs dense_gemm(const float* P, size_t ldp, const float* Q, size_t ldq, float* out, size_t ldo, int M, int N,
                            int K) {
     GemmArgs g;
-    g.P = P;  g.Q = Q;  g.Pbits = nullptr;  g.Qbits = nullptr;  g.kscale = nullptr;
-    g.add = nullptr;  g.rs = nullptr;  g.cs = nullptr;  g.out = out;
+    g.P = P;  g.Q = Q;
+    g.add = nullptr;  g.out = out;
     g.ldp = ldp;  g.ldq = ldq;  g.lda = 0;  g.ldo = ldo;
-    g.alpha = 1.f;  g.diag = 0.f;
+    g.alpha = 1.f;
     g.M = M;  g.N = N;  g.K = K;
-    g.bits_nct = 0;
     auto vec = [](const float* p, size_t ld) { return (p && (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0) ? 1 : 0; };
     g.vec_p = vec(P, ldp);
     g.vec_q = vec(Q, ldq);
     g.upper = 0;
-    g.ktri = 0;
     return g;
 }
-template <bool PS, bool QS>
 inline void launch_gemm(const GemmArgs& g, hipStream_t st) {
     if (g.M < 1 || g.N < 1 || g.K < 1) return;
-    hipLaunchKernelGGL((dbf_admm_gemm_kernel<PS, QS>), dim3((g.M + GT - 1) / GT, (g.N + GT - 1) / GT), dim3(256), 0, st, g);
+    hipLaunchKernelGGL(dbf_admm_gemm_kernel, dim3((g.M + GT - 1) / GT, (g.N + GT - 1) / GT), dim3(256), 0, st, g);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -496,12 +446,13 @@ __global__ __launch_bounds__(256) void dbf_chol_mirror_kernel(float* __restrict_
 
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 struct AdmmWorkspace {
-    size_t R, Z, svid, total;
+    size_t P, R, Z, svid, total;
 };
 inline AdmmWorkspace admm_workspace(int q, int r) {
     AdmmWorkspace w;
     size_t off = 0;
-    w.R = off;     off = up256(off + 4 * (size_t)q * r);
+    w.P = off;     off = up256(off + sg_plane_bytes(3, q, q));   // planes of Minv
+    w.R = off;     off = up256(off + sg_plane_bytes(3, q, r));   // planes of R
     w.Z = off;     off = up256(off + 4 * (size_t)q * r);
     w.svid = off;  off = up256(off + dbf_svid_workspace_bytes(q, r));
     w.total = off;
@@ -529,26 +480,27 @@ extern "C" int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int
         return DBF_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     uint8_t* base = static_cast<uint8_t*>(workspace_dev);
-    float* R = reinterpret_cast<float*>(base + w.R);
     float* Z = reinterpret_cast<float*>(base + w.Z);
     float* U = static_cast<float*>(U_dev);
     const float* C = static_cast<const float*>(C_dev);
     const int n_rt = dbf_row_tiles(q), n_ct = dbf_col_tiles(r);
-    auto aligned16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-    const int vec_r = ((r & 3) == 0 && aligned16(C) && aligned16(U)) ? 1 : 0;  // (R and Z are 256-byte aligned)
+    const int vec_r = ((r & 3) == 0 && (reinterpret_cast<uintptr_t>(U) & 15) == 0) ? 1 : 0;  // (Z is 256-byte aligned)
 
-    hipLaunchKernelGGL(dbf_admm_elementwise_kernel<0>, dim3(n_ct, n_rt), dim3(256), 0, st, C, U, rho,
-                       static_cast<const float*>(a_dev), static_cast<const float*>(m_dev),
-                       static_cast<const uint8_t*>(bits_dev), q, r, n_ct, vec_r, R);
-    GemmArgs g = dense_gemm(static_cast<const float*>(Minv_dev), q, R, r, Z, r, q, r, q);
-    g.add = U;
-    g.lda = r;
-    launch_gemm<false, false>(g, st);
+    hipLaunchKernelGGL(dbf_split_dense_kernel, sg_plane_grid(q, q), dim3(256), 0, st, static_cast<const float*>(Minv_dev), (size_t)q, q,
+                       q, nullptr, base + w.P);
+    hipLaunchKernelGGL(dbf_admm_rhs_kernel, sg_plane_grid(q, r), dim3(256), 0, st, C, U, rho, static_cast<const float*>(a_dev),
+                       static_cast<const float*>(m_dev), static_cast<const uint8_t*>(bits_dev), q, r, n_ct, base + w.R);
+    SplitGemmArgs g = {};
+    g.P = base + w.P;  g.Q = base + w.R;
+    g.add = U;  g.lda = r;
+    g.out = Z;  g.ldo = r;
+    g.M = q;  g.N = r;  g.K = q;
+    launch_split_gemm<3>(g, st);
     if (hipGetLastError() != hipSuccess) return DBF_EHIP;
     const int rc = dbf_svid(Z, q, r, svid_iters, a_dev, m_dev, bits_dev, base + w.svid, workspace_bytes - w.svid, st);
     if (rc != DBF_OK) return rc;
-    hipLaunchKernelGGL(dbf_admm_elementwise_kernel<1>, dim3(n_ct, n_rt), dim3(256), 0, st, Z, nullptr, 0.f,
-                       static_cast<const float*>(a_dev), static_cast<const float*>(m_dev),
+    hipLaunchKernelGGL(dbf_admm_dual_kernel, dim3(n_ct, n_rt), dim3(256), 0, st, Z, static_cast<const float*>(a_dev),
+                       static_cast<const float*>(m_dev),
                        static_cast<const uint8_t*>(bits_dev), q, r, n_ct, vec_r, U);
     if (hipGetLastError() != hipSuccess) return DBF_EHIP;
     return DBF_OK;
@@ -557,16 +509,22 @@ extern "C" int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int
 // ---- forming the constant matrices of the update on the device ---------------------------------
 namespace {
 struct PrepWorkspace {
-    size_t Y, tinv, fail, total;
+    size_t Y, tinv, fail, S, V, total;
     int nblk;
 };
-inline PrepWorkspace prep_workspace(int q) {
+inline PrepWorkspace prep_workspace(int p, int q, int r) {
     PrepWorkspace w;
     w.nblk = (q + NB - 1) / NB;
     size_t off = 0;
     w.Y = off;     off = up256(off + 4 * (size_t)q * q);
     w.tinv = off;  off = up256(off + 4 * (size_t)w.nblk * NB * NB);
     w.fail = off;  off = up256(off + 256);
+    w.S = off;     off = up256(off + sg_plane_bytes(1, p, q));   // planes of the signs
+    // planes of the other operand of the three large contractions in turn: the scaled signs, b . W, Y
+    size_t v = sg_plane_bytes(3, p, q);
+    v = v < sg_plane_bytes(3, p, r) ? sg_plane_bytes(3, p, r) : v;
+    v = v < sg_plane_bytes(3, q, q) ? sg_plane_bytes(3, q, q) : v;
+    w.V = off;     off = up256(off + v);
     w.total = off;
     return w;
 }
@@ -575,7 +533,7 @@ __global__ void dbf_admm_clear_flag_kernel(int* flag) { *flag = 0; }
 
 extern "C" size_t dbf_admm_prepare_workspace_bytes(int p, int q, int r) {
     if (p < 1 || q < 1 || r < 1 || p > DBF_MAX_DIM || q > DBF_MAX_DIM || r > DBF_MAX_DIM) return 0;
-    return prep_workspace(q).total;
+    return prep_workspace(p, q, r).total;
 }
 
 extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const void* b_dev, const void* W_dev, int p,
@@ -587,7 +545,7 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
     const void* ptrs[7] = {bits_dev, m2_dev, b_dev, W_dev, Minv_dev, C_dev, not_positive_definite_dev};
     for (const void* ptr : ptrs)
         if (reinterpret_cast<uintptr_t>(ptr) & 3) return DBF_EINVAL;
-    const PrepWorkspace w = prep_workspace(q);
+    const PrepWorkspace w = prep_workspace(p, q, r);
     if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < w.total)
         return DBF_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
@@ -602,20 +560,25 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
     const int n_ct = dbf_col_tiles(p);
 
     hipLaunchKernelGGL(dbf_admm_clear_flag_kernel, dim3(1), dim3(1), 0, st, fail);
-    // G = B^T B + rho I with B[l][j] = b_l S[j][l] m2_j: both operands are the sign tiles, scaled by b per summation
-    // index, m2 by output row and column in the epilogue.  Upper blocks only.
+    uint8_t *S = base + w.S, *V = base + w.V;
+    hipLaunchKernelGGL((dbf_split_signs_kernel<false>), sg_plane_grid(p, q), dim3(256), 0, st, bits, n_ct, p, q, nullptr, S);
+    // G = B^T B + rho I with B[l][j] = b_l S[j][l] m2_j: the signs against the signs times b^2, m2 by output row and column in
+    // the epilogue.  Upper blocks only.
     {
-        GemmArgs g = dense_gemm(nullptr, 0, nullptr, 0, G, q, q, q, p);
-        g.Pbits = bits;  g.Qbits = bits;  g.kscale = b;  g.bits_nct = n_ct;
+        hipLaunchKernelGGL((dbf_split_signs_kernel<true>), sg_plane_grid(p, q), dim3(256), 0, st, bits, n_ct, p, q, b, V);
+        SplitGemmArgs g = {};
+        g.P = S;  g.Q = V;  g.out = G;  g.ldo = q;  g.M = q;  g.N = q;  g.K = p;
         g.rs = m2;  g.cs = m2;  g.diag = rho;  g.upper = 1;
-        launch_gemm<true, true>(g, st);
+        launch_split_gemm<1>(g, st);
     }
-    // C = B^T W: the sign tiles against the dense W
+    // C = B^T W: the signs against b . W
     {
-        GemmArgs g = dense_gemm(nullptr, 0, static_cast<const float*>(W_dev), r, static_cast<float*>(C_dev), r, q, r, p);
-        g.Pbits = bits;  g.kscale = b;  g.bits_nct = n_ct;
+        hipLaunchKernelGGL(dbf_split_dense_kernel, sg_plane_grid(p, r), dim3(256), 0, st, static_cast<const float*>(W_dev), (size_t)r, p, r, b,
+                           V);
+        SplitGemmArgs g = {};
+        g.P = S;  g.Q = V;  g.out = static_cast<float*>(C_dev);  g.ldo = r;  g.M = q;  g.N = r;  g.K = p;
         g.rs = m2;
-        launch_gemm<true, false>(g, st);
+        launch_split_gemm<1>(g, st);
     }
     // G = R^T R
     for (int jb = 0; jb < w.nblk; ++jb) {
@@ -627,12 +590,12 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
             // read all of its columns before it writes them)
             float* panel = G + (size_t)j0 * q + j0 + wb;
             GemmArgs g1 = dense_gemm(tj, NB, panel, q, panel, q, wb, rest, wb);
-            launch_gemm<false, false>(g1, st);
+            launch_gemm(g1, st);
             // trailing update: G[i][j] -= sum_k R[j0 + k][i] R[j0 + k][j], upper blocks
             float* trail = G + (size_t)(j0 + wb) * q + j0 + wb;
             GemmArgs g2 = dense_gemm(panel, q, panel, q, trail, q, rest, rest, wb);
             g2.alpha = -1.f;  g2.add = trail;  g2.lda = q;  g2.upper = 1;
-            launch_gemm<false, false>(g2, st);
+            launch_gemm(g2, st);
         }
     }
     // Y = R^-T (lower triangular), right-looking so that every call has many workgroups: Y starts as the identity;
@@ -645,20 +608,22 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
         float* yrow = Y + (size_t)i0 * q;
         // (in place: a workgroup has read all of its columns before it writes them)
         GemmArgs g1 = dense_gemm(ti, NB, yrow, q, yrow, q, wb, ncol, wb);
-        launch_gemm<false, false>(g1, st);
+        launch_gemm(g1, st);
         if (rest > 0) {
             float* ynext = Y + (size_t)(i0 + wb) * q;
             GemmArgs g2 = dense_gemm(G + (size_t)i0 * q + i0 + wb, q, yrow, q, ynext, q, rest, ncol, wb);
             g2.alpha = -1.f;  g2.add = ynext;  g2.lda = q;
-            launch_gemm<false, false>(g2, st);
+            launch_gemm(g2, st);
         }
     }
     // G^-1 = Y^T Y (overwrites the factor): upper blocks, the sums starting where both operands can be non-zero,
     // then the mirror image
     {
-        GemmArgs g = dense_gemm(Y, q, Y, q, G, q, q, q, q);
+        hipLaunchKernelGGL(dbf_split_dense_kernel, sg_plane_grid(q, q), dim3(256), 0, st, Y, (size_t)q, q, q, nullptr, V);
+        SplitGemmArgs g = {};
+        g.P = V;  g.Q = V;  g.out = G;  g.ldo = q;  g.M = q;  g.N = q;  g.K = q;
         g.upper = 1;  g.ktri = 1;
-        launch_gemm<false, false>(g, st);
+        launch_split_gemm<3>(g, st);
         hipLaunchKernelGGL(dbf_chol_mirror_kernel, dim3((q + 31) / 32, (q + 31) / 32), dim3(256), 0, st, G, q);
     }
     if (hipGetLastError() != hipSuccess) return DBF_EHIP;

@@ -104,6 +104,19 @@ def test_admm_step_matches_the_oracle(shape, rho, iters):
     _check_step("step 2", state1, dev.host(), Minv, C, rho, iters)
 
 
+@pytest.mark.parametrize("q,r", [(1, 1), (15, 33), (16, 31), (17, 64), (127, 128), (128, 129), (129, 127), (257, 96)])
+def test_admm_step_at_the_edges_of_the_contraction_tiles(q, r):
+    """The contraction works on fragments of 16 summation indices by 32 outputs and tiles of 128 x 128: one less, equal
+    and one more in each.  The gates are those above (the split operands' error is below fp32's own)."""
+    p, rho = 2 * q + 40, 0.7
+    Bm, W, S, a, m, U = I.make_admm_problem(p, q, r, I.seed_for(9, 300 + q + r))
+    Minv, C = _constants(Bm, W, rho)
+    dev = DeviceState(Minv, C, S, a, m, U)
+    state0 = dev.host()
+    dev.step(rho, 2)
+    _check_step("q=%d r=%d" % (q, r), state0, dev.host(), Minv, C, rho, 2)
+
+
 @pytest.mark.parametrize("q", [2048, 4096])
 def test_admm_step_at_full_size(q):
     """The sizes bench.py times: a 4096 x 4096 weight at 1 and 2 bits per weight, i.e. q = k = 2048 or 4096
