@@ -105,325 +105,236 @@ __global__ __launch_bounds__(256) void dbf_admm_rhs_kernel(const float* __restri
 }
 
 // ---------------------------------------------------------------------------------------------
-// out = alpha P^T Q + add on the fp32 matrix cores (the short contractions of the factorisation below):
-//     out[i][j] = alpha * sum_k P[k][i] Q[k][j] + add[i][j].
-// Both operands are read by rows of k ("k major"), which is how v_mfma_f32_32x32x2_f32 wants them
-// (lane l supplies A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32]), so tiles go from memory
-// to LDS without a transpose.  Workgroup = 128 x 128 outputs, 4 wavefronts of 64 x 64 (2 x 2 blocks of
-// 32 x 32: 64 accumulator registers); 16 values of k per step, double buffered in LDS, the next step's
-// tiles in registers while the current one is multiplied; one barrier per step (32 matrix instructions
-// of 64 cycles per wavefront).  Rows of the LDS tiles are padded by 32 floats so that the two halves of
-// a wavefront (k and k + 1) read different banks.
-// Workgroups are renumbered so that a compute die (linear id modulo 8) works on neighbouring column
-// blocks: the Q tiles it needs stay in its own L2.
+// Inverse of the symmetric positive definite G = B^T B + rho I by a blocked Cholesky factorisation G = R^T R (R upper
+// triangular), blocks of 128: forward elimination of the augmented matrix [G | I] gives [R | Y] with Y = R^-T, and
+// G^-1 = Y^T Y is one more contraction.  Block row jb in two launches:
+//   panel    [R | Y][jb, :] = R_jj^-T [G | Y][jb, :], all columns at once            dbf_chol_panel_kernel
+//   update   [G | Y][i, :] -= R[jb, i]^T [R | Y][jb, :] for the block rows i > jb    dbf_chol_update_kernel
+// and the workgroup of the update that makes diagonal block jb + 1 factors it and inverts its factor right there: that
+// chain of 128 pivots, the longest of the whole, runs beside the other blocks' updates.
+// G and Y share one q x q matrix: block (i, c) is G's for c >= i and Y's for c < i (an update starts it at zero at c = jb), and
+// row jb of R is dead after its own update.  A finished row is written as the bf16 planes that the update and the last
+// contraction read (R's for c > jb, Y's for c <= jb) and nowhere else.
+// What bounds it: the chain.  Per block row 2 launches and 4 x 32 pivots; the update's products take 3 us of it.  Measured at
+// q = 2048 (16 block rows): see dbf_admm_prepare.
 // ---------------------------------------------------------------------------------------------
-constexpr int GT = 128;         // outputs per workgroup side
-#ifndef DBF_ADMM_GK
-#define DBF_ADMM_GK 16
-#endif
-constexpr int GK = DBF_ADMM_GK; // values of k per step
-constexpr int GLD = GT + 32;    // LDS row length in floats
+constexpr int NB = 128;        // block size: the contraction's tile
+constexpr int CH_LD = NB + 1;  // LDS row length of a diagonal block: rows and columns both meet 32 different banks
+constexpr int CH_LDT = 33;
+constexpr int CH_LDS = 4 * (NB * CH_LD + 32 * CH_LDT);
 
-struct GemmArgs {
-    const float* P;        // [K][M], leading dimension ldp
-    const float* Q;        // [K][N], leading dimension ldq
-    const float* add;      // [M][N] with leading dimension lda, or NULL
-    float* out;            // [M][N], leading dimension ldo (may be `add`: every element is read before it is written)
-    size_t ldp, ldq, lda, ldo;
-    float alpha;
-    int M, N, K;
-    int vec_p, vec_q;      // rows of P / Q can be read in 16-byte pieces
-    int upper;             // symmetric output: workgroups whose block lies wholly below the diagonal do nothing
-};
-
-__device__ inline v4f load_row4(const float* base, size_t ld, int k, int K, int c, int C, int vec) {
-    if (k >= K || c >= C) return (v4f){0.f, 0.f, 0.f, 0.f};
-    const float* p = base + (size_t)k * ld + c;
-    if (vec && c + 4 <= C) return *reinterpret_cast<const v4f*>(p);
-    v4f r = {0.f, 0.f, 0.f, 0.f};
-    r.x = p[0];
-    if (c + 1 < C) r.y = p[1];
-    if (c + 2 < C) r.z = p[2];
-    if (c + 3 < C) r.w = p[3];
-    return r;
+// out = P^T Q for 32 x 32 blocks in LDS, 32 values of k: lane l supplies P[k][l % 32] and Q[k][l % 32], k = 2 kk + l / 32.
+__device__ inline v16f chol_mul32(const float* P, int ldp, const float* Q, int ldq, int lane) {
+    const int l32 = lane & 31, h = lane >> 5;
+    float a[16], b[16];
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) {
+        a[kk] = P[(2 * kk + h) * ldp + l32];
+        b[kk] = Q[(2 * kk + h) * ldq + l32];
+    }
+    v16f acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kk], b[kk], acc, 0, 0, 0);
+    return acc;
 }
 
-__global__ __launch_bounds__(256) void dbf_admm_gemm_kernel(const GemmArgs g) {
-    __shared__ __align__(16) float As[2][GK][GLD];
-    __shared__ __align__(16) float Bs[2][GK][GLD];
+// One wavefront: the 32 x 32 diagonal block at H (leading dimension CH_LD, upper triangle read) is replaced by Y = R^-T
+// (lower triangular, zeros above), and T (leading dimension CH_LDT) receives Y^T = R^-1.  Lane l < 32 holds column l of
+// the block, lane 32 + l column l of the identity; a pivot row is scaled by 1 / sqrt(pivot), and its entries R[c][r] reach the
+// other rows through scalar registers: no LDS and no barrier in the chain.  Returns whether a pivot was not positive.
+__device__ inline int chol_factor32(float* H, float* T, int lane) {
+    const int l32 = lane & 31;
+    const bool right = lane >= 32;
+    float x[32];
+    int bad = 0;
+#pragma unroll
+    for (int r = 0; r < 32; ++r) {
+        const float v = H[r * CH_LD + l32];
+        x[r] = right ? (r == l32 ? 1.f : 0.f) : v;
+    }
+#pragma unroll
+    for (int c = 0; c < 32; ++c) {
+        const float piv = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[c]), c));
+        // (1 / sqrt of a pivot below 2^-64 through a scaled copy: the instruction takes no subnormal numbers; one Newton step)
+        const bool tiny = piv < 0x1p-64f;
+        const float ps = tiny ? piv * 0x1p64f : piv;
+        float y = __builtin_amdgcn_rsqf(ps);
+        y = fmaf(0.5f * y, fmaf(-ps * y, y, 1.f), y);
+        y = tiny ? y * 0x1p32f : y;
+        const bool pos = piv > 0.f;
+        bad |= !pos;
+        x[c] *= pos ? y : 0.f;
+#pragma unroll
+        for (int r = c + 1; r < 32; ++r) {
+            const float f = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[c]), r));
+            x[r] = fmaf(-f, x[c], x[r]);
+        }
+    }
+    if (right) {
+#pragma unroll
+        for (int r = 0; r < 32; ++r) {
+            H[r * CH_LD + l32] = x[r];
+            T[l32 * CH_LDT + r] = x[r];
+        }
+    }
+    return bad;
+}
 
+// One workgroup (256 threads): the 128 x 128 block in LDS (upper triangle; identity where it is padded) is factored, and tinv
+// (128 x 128, row major, device memory) receives the inverse of the factor, zeros below the diagonal.  *fail is raised if
+// a pivot is not positive.  The elimination above, once more, with blocks of 32: wavefront 0 brings the next diagonal block
+// up to date and factors it while the others update the rest.
+__device__ inline void chol_block(float* H, float* T, float* __restrict__ tinv, int* __restrict__ fail) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned n_wg = gridDim.x * gridDim.y, lin = blockIdx.x + gridDim.x * blockIdx.y;
-    const unsigned die = lin & 7, slot = lin >> 3, per = n_wg >> 3, extra = n_wg & 7;
-    const unsigned vid = die * per + (die < extra ? die : extra) + slot;
-    const int i0 = (int)(vid % gridDim.x) * GT, j0 = (int)(vid / gridDim.x) * GT;
-    if (g.upper && i0 >= j0 + GT) return;
-    const int wi = (w & 1) * 64, wj = (w >> 1) * 64;  // this wavefront's 64 x 64 corner in the tile
     const int l32 = lane & 31, h = lane >> 5;
-
-    // staging role: GK / 8 16-byte pieces of a tile per thread: rows k = tid / 32 (+ 8, ...), columns 4 (tid % 32)
-    constexpr int NP = GK / 8;
-    const int sk = tid >> 5, sc = 4 * (tid & 31);
-    v4f ra[NP], rb[NP];
-    auto fetch = [&](int k0) {
+    auto blk = [&](int i, int c) { return H + 32 * i * CH_LD + 32 * c; };
+    int bad = 0;
+    if (w == 0) bad = chol_factor32(blk(0, 0), T, lane);
+    __syncthreads();
+    for (int s = 0; s < 4; ++s) {
+        // row s: the three blocks beside the diagonal
+        if (w > 0) {
+            float* d = blk(s, w - 1 + (w - 1 >= s));
+            const v16f o = chol_mul32(T, CH_LDT, d, CH_LD, lane);
 #pragma unroll
-        for (int e = 0; e < NP; ++e) {
-            ra[e] = load_row4(g.P, g.ldp, k0 + sk + 8 * e, g.K, i0 + sc, g.M, g.vec_p);
-            rb[e] = load_row4(g.Q, g.ldq, k0 + sk + 8 * e, g.K, j0 + sc, g.N, g.vec_q);
+            for (int v = 0; v < 16; ++v) d[(8 * (v >> 2) + 4 * h + (v & 3)) * CH_LD + l32] = o[v];
         }
-    };
-    auto stage = [&](int buf) {
+        __syncthreads();
+        if (s == 3) break;
+        // rows i > s: columns c >= i (G) and c <= s (Y; at c = s it starts here)
+        auto update = [&](int i, int c) {
+            float* d = blk(i, c);
+            const v16f o = chol_mul32(blk(s, i), CH_LD, blk(s, c), CH_LD, lane);
 #pragma unroll
-        for (int e = 0; e < NP; ++e) {
-            *reinterpret_cast<v4f*>(&As[buf][sk + 8 * e][sc]) = ra[e];
-            *reinterpret_cast<v4f*>(&Bs[buf][sk + 8 * e][sc]) = rb[e];
+            for (int v = 0; v < 16; ++v) {
+                float* e = d + (8 * (v >> 2) + 4 * h + (v & 3)) * CH_LD + l32;
+                *e = (c == s ? 0.f : *e) - o[v];
+            }
+        };
+        if (w == 0) {
+            update(s + 1, s + 1);
+            bad |= chol_factor32(blk(s + 1, s + 1), T, lane);
+        } else {
+            int n = 0;
+            for (int i = s + 1; i < 4; ++i)
+                for (int c = 0; c < 4; ++c) {
+                    if ((c > s && c < i) || (i == s + 1 && c == s + 1)) continue;
+                    if (++n % 3 == w - 1) update(i, c);
+                }
         }
-    };
+        __syncthreads();
+    }
+    if (bad && tid == 0) atomicAdd(fail, 1);
+    for (int e = tid; e < NB * NB; e += 256) {
+        const int k = e / NB, i = e % NB;
+        tinv[e] = i >= k ? H[i * CH_LD + k] : 0.f;
+    }
+}
 
+// Diagonal block 0.
+__global__ __launch_bounds__(256) void dbf_chol_first_kernel(const float* __restrict__ G, int q, float* __restrict__ tinv,
+                                                           int* __restrict__ fail) {
+    __shared__ __align__(16) uint8_t lds[CH_LDS];
+    float* H = reinterpret_cast<float*>(lds);
+    const int w = min(q, NB);
+    for (int e = threadIdx.x; e < NB * NB; e += 256) {
+        const int i = e / NB, j = e % NB;
+        H[i * CH_LD + j] = (i < w && j < w) ? G[(size_t)min(i, j) * q + max(i, j)] : (i == j ? 1.f : 0.f);
+    }
+    __syncthreads();
+    chol_block(H, H + NB * CH_LD, tinv, fail);
+}
+
+// Row jb, 32 columns per workgroup: the planes of R_jj^-T [G | Y][jb, :].  Wavefront w makes rows 32 w .. + 31; every load is
+// issued before anything waits.  (Columns of the diagonal block itself: Y there is R_jj^-T, the product with the identity.)
+__global__ __launch_bounds__(256) void dbf_chol_panel_kernel(const float* __restrict__ G, int q, int jb, const float* __restrict__ tinv,
+                                                           uint8_t* __restrict__ planes) {
+    __shared__ float Q[NB][33];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j0 = jb * NB, wb = min(NB, q - j0), c0 = 32 * blockIdx.x, n_kb = (q + 15) / 16;
+    const bool diag = (c0 / NB) == jb;
+    const int rk = tid >> 5, cc = c0 + (tid & 31);
+    float qv[16], a[64];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) qv[e] = G[(size_t)(j0 + min(rk + 8 * e, wb - 1)) * q + min(cc, q - 1)];
+#pragma unroll
+    for (int kk = 0; kk < 64; ++kk) a[kk] = tinv[(2 * kk + h) * NB + 32 * w + l32];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const int k = rk + 8 * e;
+        Q[k][tid & 31] = (k >= wb || cc >= q) ? 0.f : diag ? (j0 + k == cc ? 1.f : 0.f) : qv[e];
+    }
+    __syncthreads();
+    v16f acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < 64; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kk], Q[2 * kk + h][l32], acc, 0, 0, 0);
+    // register v of lane (h, l32) is row 8 (v / 4) + 4 h + v % 4; a plane wants rows 8 h .. + 7 of each 16
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float lo = acc[8 * t + e], hi = acc[8 * t + 4 + e];
+            const float got = __shfl_xor(h ? lo : hi, 32, 64);
+            x[e] = h ? got : lo;
+            x[4 + e] = h ? hi : got;
+        }
+        const int kb = j0 / 16 + 2 * w + t;
+        if (kb < n_kb)
+            sg_store3(planes, (((size_t)(c0 / NB) * n_kb + kb) * 12 + ((c0 >> 5) & 3)) * SG_FRAG + lane * 16, x);
+    }
+}
+
+// Rows i > jb: [G | Y][i, :] -= R[jb, i]^T [R | Y][jb, :], a workgroup per 128 x 128 block (the contraction kernel of
+// dbf_split_gemm.h over the 128 summation indices of row jb).  Workgroup (0, 0) has diagonal block jb + 1: it keeps it in LDS
+// and factors it; being the first of the launch it starts with it.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_chol_update_kernel(
+    float* __restrict__ G, int q, int jb, const uint8_t* __restrict__ planes, float* __restrict__ tinv_next, int* __restrict__ fail) {
+    __shared__ __align__(16) uint8_t lds[CH_LDS > 2 * 24 * SG_FRAG ? CH_LDS : 2 * 24 * SG_FRAG];
+    const int nblk = gridDim.x, it = jb + 1 + blockIdx.y, jt = (int)((jb + 1 + blockIdx.x) % nblk);
+    if (jt > jb && jt < it) return;
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), fi = 2 * (w & 1), fj = 2 * (w >> 1);
+    const int n_kb = (q + 15) / 16;
+    const bool factor = blockIdx.x == 0 && blockIdx.y == 0;
     v16f acc[2][2];
+    float old[2][2][16];
+    split_gemm_tile<3>(reinterpret_cast<uint8_t(*)[24 * SG_FRAG]>(lds), planes + ((size_t)it * n_kb + jb * (NB / 16)) * (12 * SG_FRAG),
+                       planes + ((size_t)jt * n_kb + jb * (NB / 16)) * (12 * SG_FRAG), NB / 16, acc, [&]() {
+#pragma unroll
+                           for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                               for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+                                   for (int v = 0; v < 16; ++v) {
+                                       const int row = NB * it + 32 * (fi + bi) + 8 * (v >> 2) + 4 * h + (v & 3);
+                                       const int col = NB * jt + 32 * (fj + bj) + l32;
+                                       old[bi][bj][v] = G[(size_t)min(row, q - 1) * q + min(col, q - 1)];
+                                   }
+                       });
+    float* H = reinterpret_cast<float*>(lds);   // (the tile's last barrier is behind every read of the operands)
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
         for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[bi][bj][v] = 0.f;
-
-    const int steps = (g.K + GK - 1) / GK;
-    // (the operand values of k pair kk + 1 are read from LDS before the matrix instructions of pair kk are
-    // issued, into the other of two register sets: the LDS latency then hides behind 256 cycles of matrix work)
-    auto multiply = [&](int buf) {
-        float fa[2][2], fb[2][2];
-        auto read_pair = [&](int kk, int set) {
-            fa[set][0] = As[buf][2 * kk + h][wi + l32];
-            fa[set][1] = As[buf][2 * kk + h][wi + 32 + l32];
-            fb[set][0] = Bs[buf][2 * kk + h][wj + l32];
-            fb[set][1] = Bs[buf][2 * kk + h][wj + 32 + l32];
-        };
-        read_pair(0, 0);
-#pragma unroll
-        for (int kk = 0; kk < GK / 2; ++kk) {
-            const int set = kk & 1;
-            if (kk + 1 < GK / 2) read_pair(kk + 1, set ^ 1);
-            __builtin_amdgcn_sched_barrier(0);  // (keeps the reads above the matrix instructions)
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][0], fb[set][0], acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][0], fb[set][1], acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][1], fb[set][0], acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[set][1], fb[set][1], acc[1][1], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    // A workgroup whose dense tiles lie wholly inside both operands (and whose rows can be read in 16-byte pieces)
-    // takes a loop without a single branch: guarded loads put a wait for memory between the request and the
-    // matrix instructions of every step.  The last step requests its own tiles once more instead of none.
-    const bool inside = g.vec_p && g.vec_q && i0 + GT <= g.M && j0 + GT <= g.N && g.K % GK == 0;
-    if (inside) {
-        const float* pa = g.P + (size_t)sk * g.ldp + i0 + sc;
-        const float* pb = g.Q + (size_t)sk * g.ldq + j0 + sc;
-        auto fetch_inside = [&](int k0) {
-#pragma unroll
-            for (int e = 0; e < NP; ++e) {
-                ra[e] = *reinterpret_cast<const v4f*>(pa + (size_t)(k0 + 8 * e) * g.ldp);
-                rb[e] = *reinterpret_cast<const v4f*>(pb + (size_t)(k0 + 8 * e) * g.ldq);
-            }
-        };
-        fetch_inside(0);
-        stage(0);
-        __syncthreads();
-        for (int s = 0; s < steps; ++s) {
-            fetch_inside(min(s + 1, steps - 1) * GK);
-            multiply(s & 1);
-            stage((s & 1) ^ 1);
-            __syncthreads();
-        }
-    } else {
-        fetch(0);
-        stage(0);
-        __syncthreads();
-        for (int s = 0; s < steps; ++s) {
-            if (s + 1 < steps) fetch((s + 1) * GK);
-            multiply(s & 1);
-            if (s + 1 < steps) stage((s & 1) ^ 1);
-            __syncthreads();
-        }
-    }
-
-    // epilogue: register v of lane l of a 32 x 32 block is row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            const int col = j0 + wj + 32 * bj + l32;
-            if (col >= g.N) continue;
-#pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int row = i0 + wi + 32 * bi + 8 * (v >> 2) + 4 * h + (v & 3);
-                if (row < g.M) {
-                    float val = acc[bi][bj][v] * g.alpha;
-                    if (g.add) val += g.add[(size_t)row * g.lda + col];
-                    g.out[(size_t)row * g.ldo + col] = val;
-                }
+                const int i = 32 * (fi + bi) + 8 * (v >> 2) + 4 * h + (v & 3), j = 32 * (fj + bj) + l32;
+                const int row = NB * it + i, col = NB * jt + j;
+                const bool in = row < q && col < q;
+                const float val = (jt == jb ? 0.f : old[bi][bj][v]) - acc[bi][bj][v];
+                if (factor) H[i * CH_LD + j] = in ? val : (i == j ? 1.f : 0.f);
+                else if (in) G[(size_t)row * q + col] = val;
             }
-        }
-}
-
-// A dense call: out (M x N, leading dimension ldo) = P^T Q, P [K][M] with leading dimension ldp, Q [K][N] with ldq.
-inline GemmArgs dense_gemm(const float* P, size_t ldp, const float* Q, size_t ldq, float* out, size_t ldo, int M, int N,
-                           int K) {
-    GemmArgs g;
-    g.P = P;  g.Q = Q;
-    g.add = nullptr;  g.out = out;
-    g.ldp = ldp;  g.ldq = ldq;  g.lda = 0;  g.ldo = ldo;
-    g.alpha = 1.f;
-    g.M = M;  g.N = N;  g.K = K;
-    auto vec = [](const float* p, size_t ld) { return (p && (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0) ? 1 : 0; };
-    g.vec_p = vec(P, ldp);
-    g.vec_q = vec(Q, ldq);
-    g.upper = 0;
-    return g;
-}
-inline void launch_gemm(const GemmArgs& g, hipStream_t st) {
-    if (g.M < 1 || g.N < 1 || g.K < 1) return;
-    hipLaunchKernelGGL(dbf_admm_gemm_kernel, dim3((g.M + GT - 1) / GT, (g.N + GT - 1) / GT), dim3(256), 0, st, g);
-}
-
-// ---------------------------------------------------------------------------------------------
-// Cholesky factorisation G = R^T R (R upper triangular) of the symmetric positive definite
-// G = B^T B + rho I and its inverse, blocked by 128 (the contraction kernel's tile):
-//   for every block column:  factor the 128 x 128 diagonal block and invert its factor (one workgroup,
-//   in LDS: below);  R[jb, j>jb] = R_jj^-T G[jb, j>jb]  and  G[i>jb, j>jb] -= R[jb, i]^T R[jb, j]  are calls of
-//   the contraction kernel above (both operands k major as they lie in memory, no transposes).
-//   Y = R^-T (lower triangular) from the identity, right-looking:  Y[i, :] = R_ii^-T Y[i, :], then
-//   Y[i' > i, :] -= R[i, i']^T Y[i, :];   G^-1 = Y^T Y, one more contraction (upper blocks, then mirrored).
-// Only the upper triangle of G is ever read.
-// ---------------------------------------------------------------------------------------------
-constexpr int NB = GT;  // block size of the factorisation
-
-// One workgroup: the w x w diagonal block at (j0, j0) of G (leading dimension ld) is replaced by its upper
-// Cholesky factor (zeros below the diagonal); tinv (NB x NB, row major) receives the inverse of that factor,
-// the identity on the padded part.  *fail is raised if a pivot is not positive (G not positive definite).
-//
-// The factorisation keeps the block in registers: the 256 threads form a 16 x 16 grid, thread (ti, tj) owns
-// the elements (16 a + ti, 16 b + tj), a, b < 8.  A step = one pivot row c: its owners put the row into LDS
-// (two buffers alternate: one barrier per step), everybody reads the pivot and the 8 + 8 row entries that
-// meet its own rows and columns, scales them by 1 / sqrt(pivot), and subtracts their products from its
-// elements of the rows below c.  The row index 16 ca + cr is walked with ca unrolled, so every register index
-// is a constant.  Only the upper triangle is meaningful; what accumulates below it is never used.
-__global__ __launch_bounds__(256) void dbf_chol_diag_kernel(float* __restrict__ G, size_t ld, int j0, int w,
-                                                          float* __restrict__ tinv, int* __restrict__ fail) {
-    constexpr int LDA = NB + 4;  // (rows 16 bytes aligned; neighbouring rows four banks apart)
-    __shared__ __align__(16) float A[NB][LDA];
-    __shared__ __align__(16) float T[NB][LDA];
-    __shared__ __align__(16) float tmp[8][16][16];
-    __shared__ float rowbuf[2][NB];
-    const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
-    float reg[8][8];
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const int i = 16 * a + ti, j = 16 * b + tj;
-            float v = (i == j) ? 1.f : 0.f;                  // padding: identity
-            if (i < w && j < w && j >= i) v = G[(size_t)(j0 + i) * ld + j0 + j];
-            reg[a][b] = v;
-        }
-    int bad = 0;
-#pragma unroll
-    for (int ca = 0; ca < 8; ++ca) {
-        for (int cr = 0; cr < 16; ++cr) {
-            const int c = 16 * ca + cr;
-            float* rb = rowbuf[c & 1];
-            if (ti == cr) {
-#pragma unroll
-                for (int b = ca; b < 8; ++b) rb[16 * b + tj] = reg[ca][b];
-            }
-            __syncthreads();
-            const float piv = rb[c];
-            float inv = 0.f;
-            if (piv > 0.f) inv = 1.f / sqrtf(piv); else bad = 1;
-            float ri[8], rj[8];
-#pragma unroll
-            for (int a = ca; a < 8; ++a) ri[a] = rb[16 * a + ti] * inv;
-#pragma unroll
-            for (int b = ca; b < 8; ++b) rj[b] = rb[16 * b + tj] * inv;
-            if (ti == cr) {                                   // the pivot row itself becomes row c of the factor
-#pragma unroll
-                for (int b = ca; b < 8; ++b) reg[ca][b] = rj[b];
-            }
-#pragma unroll
-            for (int a = ca; a < 8; ++a) {
-                const bool below = a > ca || ti > cr;          // rows after c
-#pragma unroll
-                for (int b = ca; b < 8; ++b)
-                    if (below) reg[a][b] -= ri[a] * rj[b];
-            }
-        }
-    }
-    if (bad && tid == 0) atomicAdd(fail, 1);                  // (every thread saw the same pivots)
-    // the factor to LDS (for the inverse) and to memory, zeros below the diagonal
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const int i = 16 * a + ti, j = 16 * b + tj;
-            const float v = j >= i ? reg[a][b] : 0.f;
-            A[i][j] = v;
-            T[i][j] = 0.f;
-            if (i < w && j < w) G[(size_t)(j0 + i) * ld + j0 + j] = v;
-        }
+    if (!factor) return;
     __syncthreads();
-    // Inverse of the upper triangular factor by 16 x 16 blocks.  The eight diagonal blocks first: thread (I, cc),
-    // 128 of them, solves R_II x = e_cc from the last row upwards with x in registers (entries beyond cc come out
-    // as zeros by themselves, so every index is a constant).
-    if (tid < NB) {
-        const int I = tid >> 4, cc = tid & 15;
-        float x[16];
-#pragma unroll
-        for (int i = 15; i >= 0; --i) {
-            float acc = (i == cc) ? 1.f : 0.f;
-#pragma unroll
-            for (int l = i + 1; l < 16; ++l) acc -= A[16 * I + i][16 * I + l] * x[l];
-            const float di = A[16 * I + i][16 * I + i];
-            x[i] = di != 0.f ? acc / di : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) T[16 * I + i][16 * I + cc] = x[i];
-    }
-    __syncthreads();
-    // Then block diagonal by block diagonal, d = J - I = 1 .. 7 (the blocks of one diagonal are independent):
-    //     T_IJ = -T_II * (sum over I < K <= J of R_IK T_KJ),
-    // thread (r, cc) takes element (r, cc) of every block of the diagonal; the inner sum goes through LDS.
-    {
-        const int r = ti, cc = tj;
-        for (int d = 1; d < 8; ++d) {
-            for (int I = 0; I + d < 8; ++I) {
-                const int J = I + d;
-                float acc = 0.f;
-                for (int K = I + 1; K <= J; ++K) {
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc += A[16 * I + r][16 * K + e] * T[16 * K + e][16 * J + cc];
-                }
-                tmp[I][r][cc] = acc;
-            }
-            __syncthreads();
-            for (int I = 0; I + d < 8; ++I) {
-                const int J = I + d;
-                float acc = 0.f;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc += T[16 * I + r][16 * I + e] * tmp[I][e][cc];
-                T[16 * I + r][16 * J + cc] = -acc;
-            }
-            __syncthreads();
-        }
-    }
-    for (int e = tid; e < NB * NB; e += 256) tinv[e] = T[e / NB][e % NB];
-}
-
-// Y = identity (q x q).
-__global__ __launch_bounds__(256) void dbf_chol_identity_kernel(float* __restrict__ Y, int q) {
-    const int row = blockIdx.y;
-    const int col = blockIdx.x * 256 + threadIdx.x;
-    if (col < q) Y[(size_t)row * q + col] = row == col ? 1.f : 0.f;
+    chol_block(H, H + NB * CH_LD, tinv_next, fail);
 }
 
 // M[j][i] = M[i][j] for i < j: the lower triangle of a symmetric matrix whose upper blocks were computed.
@@ -509,18 +420,17 @@ extern "C" int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int
 // ---- forming the constant matrices of the update on the device ---------------------------------
 namespace {
 struct PrepWorkspace {
-    size_t Y, tinv, fail, S, V, total;
+    size_t tinv, fail, S, V, total;
     int nblk;
 };
 inline PrepWorkspace prep_workspace(int p, int q, int r) {
     PrepWorkspace w;
     w.nblk = (q + NB - 1) / NB;
     size_t off = 0;
-    w.Y = off;     off = up256(off + 4 * (size_t)q * q);
     w.tinv = off;  off = up256(off + 4 * (size_t)w.nblk * NB * NB);
     w.fail = off;  off = up256(off + 256);
     w.S = off;     off = up256(off + sg_plane_bytes(1, p, q));   // planes of the signs
-    // planes of the other operand of the three large contractions in turn: the scaled signs, b . W, Y
+    // planes of the other operand of the three large contractions in turn: the scaled signs, b . W, [R | Y]
     size_t v = sg_plane_bytes(3, p, q);
     v = v < sg_plane_bytes(3, p, r) ? sg_plane_bytes(3, p, r) : v;
     v = v < sg_plane_bytes(3, q, q) ? sg_plane_bytes(3, q, q) : v;
@@ -550,7 +460,6 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
         return DBF_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     uint8_t* base = static_cast<uint8_t*>(workspace_dev);
-    float* Y = reinterpret_cast<float*>(base + w.Y);
     float* tinv = reinterpret_cast<float*>(base + w.tinv);
     int* fail = not_positive_definite_dev ? not_positive_definite_dev : reinterpret_cast<int*>(base + w.fail);
     float* G = static_cast<float*>(Minv_dev);  // G, then its factor, live in the output until the last contraction
@@ -580,46 +489,19 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
         g.rs = m2;
         launch_split_gemm<1>(g, st);
     }
-    // G = R^T R
+    // [G | I] -> [R | Y], the planes of Y (and of R, row by row) in V
+    hipLaunchKernelGGL(dbf_chol_first_kernel, dim3(1), dim3(256), 0, st, G, q, tinv, fail);
     for (int jb = 0; jb < w.nblk; ++jb) {
-        const int j0 = jb * NB, wb = q - j0 < NB ? q - j0 : NB, rest = q - j0 - wb;
+        const bool last = jb + 1 == w.nblk;
         float* tj = tinv + (size_t)jb * NB * NB;
-        hipLaunchKernelGGL(dbf_chol_diag_kernel, dim3(1), dim3(256), 0, st, G, (size_t)q, j0, wb, tj, fail);
-        if (rest > 0) {
-            // panel: R[j0 + i][j0 + wb + j] = sum_k tinv[k][i] G[j0 + k][j0 + wb + j]   (in place: a workgroup has
-            // read all of its columns before it writes them)
-            float* panel = G + (size_t)j0 * q + j0 + wb;
-            GemmArgs g1 = dense_gemm(tj, NB, panel, q, panel, q, wb, rest, wb);
-            launch_gemm(g1, st);
-            // trailing update: G[i][j] -= sum_k R[j0 + k][i] R[j0 + k][j], upper blocks
-            float* trail = G + (size_t)(j0 + wb) * q + j0 + wb;
-            GemmArgs g2 = dense_gemm(panel, q, panel, q, trail, q, rest, rest, wb);
-            g2.alpha = -1.f;  g2.add = trail;  g2.lda = q;  g2.upper = 1;
-            launch_gemm(g2, st);
-        }
+        hipLaunchKernelGGL(dbf_chol_panel_kernel, dim3(4 * w.nblk), dim3(256), 0, st, G, q, jb, tj, V);
+        if (!last)
+            hipLaunchKernelGGL(dbf_chol_update_kernel, dim3(w.nblk, w.nblk - 1 - jb), dim3(256), 0, st, G, q, jb, V, tj + NB * NB,
+                               fail);
     }
-    // Y = R^-T (lower triangular), right-looking so that every call has many workgroups: Y starts as the identity;
-    // block row ib is finished by Y[ib, :] = R_ii^-T Y[ib, :], then every later block row loses its share
-    // Y[i', :] -= R[ib, i']^T Y[ib, :].  Only the columns up to the block's own are non-zero.
-    hipLaunchKernelGGL(dbf_chol_identity_kernel, dim3((q + 255) / 256, q), dim3(256), 0, st, Y, q);
-    for (int ib = 0; ib < w.nblk; ++ib) {
-        const int i0 = ib * NB, wb = q - i0 < NB ? q - i0 : NB, rest = q - i0 - wb, ncol = i0 + wb;
-        const float* ti = tinv + (size_t)ib * NB * NB;
-        float* yrow = Y + (size_t)i0 * q;
-        // (in place: a workgroup has read all of its columns before it writes them)
-        GemmArgs g1 = dense_gemm(ti, NB, yrow, q, yrow, q, wb, ncol, wb);
-        launch_gemm(g1, st);
-        if (rest > 0) {
-            float* ynext = Y + (size_t)(i0 + wb) * q;
-            GemmArgs g2 = dense_gemm(G + (size_t)i0 * q + i0 + wb, q, yrow, q, ynext, q, rest, ncol, wb);
-            g2.alpha = -1.f;  g2.add = ynext;  g2.lda = q;
-            launch_gemm(g2, st);
-        }
-    }
-    // G^-1 = Y^T Y (overwrites the factor): upper blocks, the sums starting where both operands can be non-zero,
+    // G^-1 = Y^T Y (overwrites G): upper blocks, the sums starting where both operands can be non-zero,
     // then the mirror image
     {
-        hipLaunchKernelGGL(dbf_split_dense_kernel, sg_plane_grid(q, q), dim3(256), 0, st, Y, (size_t)q, q, q, nullptr, V);
         SplitGemmArgs g = {};
         g.P = V;  g.Q = V;  g.out = G;  g.ldo = q;  g.M = q;  g.N = q;  g.K = q;
         g.upper = 1;  g.ktri = 1;

@@ -137,24 +137,18 @@ struct SplitGemmArgs {
     int ktri;              // both operands are zero for k < output index: sums start at the first k that can contribute
 };
 
-template <int PA>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_split_gemm_kernel(const SplitGemmArgs g) {
+// The products of a workgroup's 128 x 128 block: acc (2 x 2 blocks of 32 x 32 per wavefront, rows from 64 (w % 2), columns from
+// 64 (w / 2)) = sum over `steps` fragments of 16 k from pp (P's planes) and qp (Q's).  `meanwhile` runs once the first loads
+// are on their way.  Ends with a barrier behind the last read of `lds`.
+template <int PA, class F>
+__device__ inline void split_gemm_tile(uint8_t (*lds)[(4 * PA + 12) * SG_FRAG], const uint8_t* pp, const uint8_t* qp, int steps, v16f (&acc)[2][2],
+                                       F meanwhile) {
     constexpr int PB = 4 * PA * SG_FRAG, QB = 12 * SG_FRAG;   // bytes per step
     constexpr int NF = (PB + QB) / 4096;                      // 16-byte pieces a thread stages per step
-    __shared__ __align__(16) uint8_t lds[2][PB + QB];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned n_wg = gridDim.x * gridDim.y, lin = blockIdx.x + gridDim.x * blockIdx.y;
-    const unsigned die = lin & 7, slot = lin >> 3, per = n_wg >> 3, extra = n_wg & 7;
-    const unsigned vid = die * per + (die < extra ? die : extra) + slot;
-    const int it = (int)(vid % gridDim.x), jt = (int)(vid / gridDim.x);
-    if (g.upper && it > jt) return;
-    const int n_kb = (g.K + 15) / 16;
-    const int kb0 = g.ktri ? min(8 * max(it, jt), n_kb) : 0;
-    const int steps = n_kb - kb0;
-    const uint8_t* pp = g.P + ((size_t)it * n_kb + kb0) * PB + 16 * tid;
-    const uint8_t* qp = g.Q + ((size_t)jt * n_kb + kb0) * QB + 16 * tid;
-
+    pp += 16 * tid;
+    qp += 16 * tid;
     v4f st[NF];
     auto fetch = [&](int s) {
 #pragma unroll
@@ -166,7 +160,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
         for (int f = 0; f < NF; ++f) *reinterpret_cast<v4f*>(&lds[buf][4096 * f + 16 * tid]) = st[f];
     };
-    v16f acc[2][2];
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
@@ -197,18 +190,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                         acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[bi][p], b[bj][q], acc[bi][bj], 0, 0, 0);
             }
     };
-    if (steps > 0) {
-        fetch(0);
-        stage(0);
-        if (steps > 1) fetch(1);
+    if (steps <= 0) return;
+    fetch(0);
+    stage(0);
+    if (steps > 1) fetch(1);
+    meanwhile();
+    __syncthreads();
+    for (int s = 0; s < steps; ++s) {
+        if (s + 1 < steps) stage((s & 1) ^ 1);
+        if (s + 2 < steps) fetch(s + 2);
+        multiply(s & 1);
         __syncthreads();
-        for (int s = 0; s < steps; ++s) {
-            if (s + 1 < steps) stage((s & 1) ^ 1);
-            if (s + 2 < steps) fetch(s + 2);
-            multiply(s & 1);
-            __syncthreads();
-        }
     }
+}
+
+template <int PA>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_split_gemm_kernel(const SplitGemmArgs g) {
+    constexpr int PB = 4 * PA * SG_FRAG, QB = 12 * SG_FRAG;   // bytes per step
+    __shared__ __align__(16) uint8_t lds[2][PB + QB];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned n_wg = gridDim.x * gridDim.y, lin = blockIdx.x + gridDim.x * blockIdx.y;
+    const unsigned die = lin & 7, slot = lin >> 3, per = n_wg >> 3, extra = n_wg & 7;
+    const unsigned vid = die * per + (die < extra ? die : extra) + slot;
+    const int it = (int)(vid % gridDim.x), jt = (int)(vid / gridDim.x);
+    if (g.upper && it > jt) return;
+    const int n_kb = (g.K + 15) / 16;
+    const int kb0 = g.ktri ? min(8 * max(it, jt), n_kb) : 0;
+    const int fi = 2 * (w & 1), fj = 2 * (w >> 1);
+    v16f acc[2][2];
+    split_gemm_tile<PA>(lds, g.P + ((size_t)it * n_kb + kb0) * PB, g.Q + ((size_t)jt * n_kb + kb0) * QB, n_kb - kb0, acc, []() {});
     // register v of lane l of a 32 x 32 block is row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
     const int l32 = lane & 31, h = lane >> 5;
 #pragma unroll
