@@ -124,7 +124,7 @@ constexpr int CH_LDT = 33;
 constexpr int CH_LDS = 4 * (NB * CH_LD + 32 * CH_LDT);
 
 // out = P^T Q for 32 x 32 blocks in LDS, 32 values of k: lane l supplies P[k][l % 32] and Q[k][l % 32], k = 2 kk + l / 32.
-__device__ inline v16f chol_mul32(const float* P, int ldp, const float* Q, int ldq, int lane) {
+__device__ __forceinline__ v16f chol_mul32(const float* P, int ldp, const float* Q, int ldq, int lane) {
     const int l32 = lane & 31, h = lane >> 5;
     float a[16], b[16];
 #pragma unroll
@@ -144,16 +144,18 @@ __device__ inline v16f chol_mul32(const float* P, int ldp, const float* Q, int l
 // (lower triangular, zeros above), and T (leading dimension CH_LDT) receives Y^T = R^-1.  Lane l < 32 holds column l of
 // the block, lane 32 + l column l of the identity; a pivot row is scaled by 1 / sqrt(pivot), and its entries R[c][r] reach the
 // other rows through scalar registers: no LDS and no barrier in the chain.  Returns whether a pivot was not positive.
-__device__ inline int chol_factor32(float* H, float* T, int lane) {
+__device__ __forceinline__ int chol_factor32(float* H, float* T, int lane) {
     const int l32 = lane & 31;
     const bool right = lane >= 32;
     float x[32];
     int bad = 0;
 #pragma unroll
     for (int r = 0; r < 32; ++r) {
-        const float v = H[r * CH_LD + l32];
-        x[r] = right ? (r == l32 ? 1.f : 0.f) : v;
+        x[r] = H[r * CH_LD + l32];
+        asm("" : "+v"(x[r]));  // (loaded by all lanes, not in a branch of its own)
     }
+#pragma unroll
+    for (int r = 0; r < 32; ++r) x[r] = right ? (r == l32 ? 1.f : 0.f) : x[r];
 #pragma unroll
     for (int c = 0; c < 32; ++c) {
         const float piv = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[c]), c));
@@ -166,11 +168,14 @@ __device__ inline int chol_factor32(float* H, float* T, int lane) {
         const bool pos = piv > 0.f;
         bad |= !pos;
         x[c] *= pos ? y : 0.f;
+        // (all entries first, then the products: a scalar register read right after it is written costs idle slots.  The
+        //  next pivot's chain hides among the products)
+        float f[32];
 #pragma unroll
-        for (int r = c + 1; r < 32; ++r) {
-            const float f = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[c]), r));
-            x[r] = fmaf(-f, x[c], x[r]);
-        }
+        for (int r = c + 1; r < 32; ++r) f[r] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[c]), r));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = c + 1; r < 32; ++r) x[r] = fmaf(-f[r], x[c], x[r]);
     }
     if (right) {
 #pragma unroll
@@ -186,7 +191,7 @@ __device__ inline int chol_factor32(float* H, float* T, int lane) {
 // (128 x 128, row major, device memory) receives the inverse of the factor, zeros below the diagonal.  *fail is raised if
 // a pivot is not positive.  The elimination above, once more, with blocks of 32: wavefront 0 brings the next diagonal block
 // up to date and factors it while the others update the rest.
-__device__ inline void chol_block(float* H, float* T, float* __restrict__ tinv, int* __restrict__ fail) {
+__device__ __forceinline__ void chol_block(float* H, float* T, float* __restrict__ tinv, int* __restrict__ fail) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
@@ -228,6 +233,7 @@ __device__ inline void chol_block(float* H, float* T, float* __restrict__ tinv, 
         __syncthreads();
     }
     if (bad && tid == 0) atomicAdd(fail, 1);
+#pragma unroll 16
     for (int e = tid; e < NB * NB; e += 256) {
         const int k = e / NB, i = e % NB;
         tinv[e] = i >= k ? H[i * CH_LD + k] : 0.f;
@@ -240,9 +246,11 @@ __global__ __launch_bounds__(256) void dbf_chol_first_kernel(const float* __rest
     __shared__ __align__(16) uint8_t lds[CH_LDS];
     float* H = reinterpret_cast<float*>(lds);
     const int w = min(q, NB);
+#pragma unroll 16
     for (int e = threadIdx.x; e < NB * NB; e += 256) {
         const int i = e / NB, j = e % NB;
-        H[i * CH_LD + j] = (i < w && j < w) ? G[(size_t)min(i, j) * q + max(i, j)] : (i == j ? 1.f : 0.f);
+        const float v = G[(size_t)min(min(i, j), w - 1) * q + min(max(i, j), w - 1)];
+        H[i * CH_LD + j] = (i < w && j < w) ? v : (i == j ? 1.f : 0.f);
     }
     __syncthreads();
     chol_block(H, H + NB * CH_LD, tinv, fail);
