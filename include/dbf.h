@@ -27,8 +27,8 @@
  *   - Launching entry points (dbf_gemv*, dbf_gemm, dbf_stack_gemv) are
  *     asynchronous on the caller's HIP stream (a hipStream_t passed as void*,
  *     NULL = the default stream), allocate nothing and do not synchronise.  A
- *     layer holds scratch for its middle activations and, for batches of 2 and
- *     more, for its quantised stage inputs, so one layer must not run on two
+ *     layer holds scratch for its middle activations, its quantised stage inputs
+ *     and the sums of column pieces, so one layer must not run on two
  *     streams at the same time, be it directly or through stacks that hold it.
  *   - Non-finite activations give unspecified (but memory-safe) results.
  *
@@ -63,15 +63,17 @@ enum {
 
 /* Which decode kernel dbf_gemv_kind runs. */
 enum {
-    DBF_GEMV_AUTO = 0, /* what dbf_gemv uses.  Batch 1: DBF_GEMV_MFMA for a group of layers whose B stage
-                          alone fills the chip (1024 workgroups: 64 layers of 4096 x 4096,
-                          k = 2048), DBF_GEMV_MFMA_SPLIT for a single layer and shorter groups (measured
-                          faster there: in one launch their A-stage workgroups would all sit waiting
-                          next to the B stage), long rows of short launches cut into column pieces.
-                          Batches of 2 and more -- and groups of layers with long stage inputs at
-                          batch 1 too, see DBF_TUNE_LONG_ROWS -- quantise each stage input once per
-                          call: four launches (quantise x, B stage, quantise t, A stage).  Every
-                          choice gives the same bits as DBF_GEMV_MFMA and DBF_GEMV_MFMA_SPLIT     */
+    DBF_GEMV_AUTO = 0, /* what dbf_gemv uses.  A layer or a group whose stages have at most 256 workgroups (row tiles
+                          of 128 rows times groups of up to 8 batch rows): two launches at any batch, every
+                          workgroup rounding the stage input it needs, long rows cut into column pieces.
+                          Else, batch 1: DBF_GEMV_MFMA for a group of layers whose B stage alone fills the
+                          chip (1024 workgroups: 64 layers of 4096 x 4096, k = 2048), DBF_GEMV_MFMA_SPLIT for
+                          shorter groups (measured faster there: in one launch their A-stage workgroups
+                          would all sit waiting next to the B stage).  Batches of 2 and more -- and groups
+                          of layers with long stage inputs at batch 1 too, see DBF_TUNE_LONG_ROWS -- quantise
+                          each stage input once per call: four launches (quantise x, B stage, quantise t,
+                          A stage).  Every choice gives the same bits as DBF_GEMV_MFMA and
+                          DBF_GEMV_MFMA_SPLIT                                                      */
     DBF_GEMV_VALU = 1, /* fp32 add/subtract per sign bit on the vector ALU (exact fp32 sums) */
     DBF_GEMV_MFMA = 2, /* sign bytes fed to the int8 matrix cores as the adder; the input
                           vector of each stage is rounded once to 16-bit fixed point.  Both

@@ -22,6 +22,7 @@ SOURCES = [
     "dbf_api.hip",
     "dbf_gemv_valu.hip",
     "dbf_gemv_mfma.hip",
+    "dbf_gemv_few.hip",
     "dbf_gemm_i8.hip",
     "dbf_gemm_static.hip",
     "dbf_probe.hip",

@@ -215,6 +215,11 @@ int shared_span(const DbfStage& st, long long stage_tiles) {
     return (int)(span > DBF_MAX_SPAN ? DBF_MAX_SPAN : span);
 }
 
+// Bytes of the sums and counters of column pieces (DbfPlan::d_few_acc) for stages of at most n_rt row tiles; 0: the plan has none.
+size_t few_acc_bytes(int n_rt) {
+    return n_rt <= DBF_FEW_MAX_ROW_TILES ? sizeof(int) * (size_t)n_rt * (DBF_MAX_BATCH * DBF_TILE_ROWS + DBF_PIECE_CNT_STRIDE) : 0;
+}
+
 void free_plan(DbfPlan& p) {
     if (p.dev_block) (void)hipFree(p.dev_block);
     p.dev_block = nullptr;
@@ -222,8 +227,9 @@ void free_plan(DbfPlan& p) {
 
 // Builds and uploads the launch tables for `n` layers whose stages (with their x/y offsets
 // already set) are given in sB / sA.
+// few_acc: zeroed device memory for DbfPlan::d_few_acc (few_acc_bytes of it), or NULL: the plan then holds its own.
 int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA, const std::vector<int>& span_b,
-               const std::vector<int>& span_a, DbfPlan* p) {
+               const std::vector<int>& span_a, int* few_acc, DbfPlan* p) {
     const int n = (int)sB.size();
     std::vector<DbfWorkItem> wB1, wA1;
     std::vector<DbfItem> items_n, items_1;
@@ -418,7 +424,11 @@ int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA,
     std::memcpy(image.data() + o_is, items_s.data(), sizeof(DbfItem) * items_s.size());
     void* dev = nullptr;
     hipError_t e = dbf_mfma_prepare();
-    if (e == hipSuccess) e = hipMalloc(&dev, off);
+    if (e == hipSuccess) e = dbf_few_prepare();
+    // (the sums of the column pieces of small launches, cleared on the device: they are no part of the image)
+    const size_t few_bytes = few_acc_bytes((int)(rtB > rtA ? rtB : rtA)), few_own = few_acc ? 0 : few_bytes;
+    if (e == hipSuccess) e = hipMalloc(&dev, off + few_own);
+    if (e == hipSuccess && few_own) e = hipMemset(static_cast<uint8_t*>(dev) + off, 0, few_own);
     if (e == hipSuccess) {
         for (DbfItem& it : items_p) {  // rebase the accumulator and counter addresses
             it.acc = reinterpret_cast<int*>(static_cast<uint8_t*>(dev) + reinterpret_cast<size_t>(it.acc));
@@ -456,13 +466,16 @@ int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA,
     p->d_items_p = cut ? reinterpret_cast<DbfItem*>(d + o_ip) : nullptr;
     p->nBp = nBp;
     p->nAp = (int)items_p.size() - nBp;
+    p->h_stage_B = sB[0];
+    p->h_stage_A = sA[0];
+    p->d_few_acc = !few_bytes ? nullptr : few_acc ? few_acc : reinterpret_cast<int*>(d + off);
     p->span = max_span;
     return DBF_OK;
 }
 
 // Section offsets of a layer's single device block (256-byte aligned sections).
 struct LayerOffsets {
-    size_t A, B, a, m, b, image_bytes, t, qB, qA, total;
+    size_t A, B, a, m, b, image_bytes, t, qB, qA, few, total;
     int a_len, m_len, b_len, t_stride;
 };
 LayerOffsets layer_offsets(int n_in, int n_out, int k) {
@@ -481,6 +494,8 @@ LayerOffsets layer_offsets(int n_in, int n_out, int k) {
     o.t = off;  off = align_up(off + 4 * (size_t)DBF_MAX_BATCH * o.t_stride, 256);
     o.qB = off;  off = align_up(off + DBF_QIN_HEADER + 2 * (size_t)DBF_MAX_BATCH * o.b_len, 256);
     o.qA = off;  off = align_up(off + DBF_QIN_HEADER + 2 * (size_t)DBF_MAX_BATCH * dbf_col_tiles(k) * DBF_TILE_COLS, 256);
+    const int rt_k = dbf_row_tiles(k), rt_out = dbf_row_tiles(n_out);
+    o.few = off;  off = align_up(off + few_acc_bytes(rt_k > rt_out ? rt_k : rt_out), 256);
     o.total = off;
     return o;
 }
@@ -514,6 +529,7 @@ int create_layer(int n_in, int n_out, int k, const LayerOffsets& o, dbf_layer** 
     L->t_stride = o.t_stride;
     L->dqB = d + o.qB;
     L->dqA = d + o.qA;
+    L->d_few_acc = reinterpret_cast<int*>(d + o.few);
 
     DbfStage& sb = L->h_stages[0];
     sb.bits = L->dB;  sb.in_scale = L->db;  sb.row_scale = L->dm;  sb.t = L->dt;
@@ -532,7 +548,7 @@ int create_layer(int n_in, int n_out, int k, const LayerOffsets& o, dbf_layer** 
 // The launch plan of a layer alone: one row tile per workgroup gives the most parallelism.
 int finish_layer(dbf_layer* L) {
     std::vector<DbfStage> vB(1, L->h_stages[0]), vA(1, L->h_stages[1]);
-    return build_plan(vB, vA, std::vector<int>(1, 1), std::vector<int>(1, 1), &L->plan);
+    return build_plan(vB, vA, std::vector<int>(1, 1), std::vector<int>(1, 1), L->d_few_acc, &L->plan);
 }
 
 void destroy_layer(dbf_layer* L) {
@@ -580,6 +596,14 @@ inline bool kind_ok(int kind) {
     return kind == DBF_GEMV_AUTO || kind == DBF_GEMV_VALU || kind == DBF_GEMV_MFMA || kind == DBF_GEMV_MFMA_SPLIT;
 }
 
+// Both stages of a plan in launches of few workgroups (dbf_gemv_few.hip), where each has at most one workgroup per compute unit.
+int launch_few(const DbfPlan& p, const void* x, void* y, int batch, hipStream_t stream, hipEvent_t mid) {
+    DBF_HIP_TRY(dbf_launch_few(p, false, x, y, nullptr, batch, stream));
+    if (mid) DBF_HIP_TRY(hipEventRecord(mid, stream));
+    DBF_HIP_TRY(dbf_launch_few(p, true, x, y, nullptr, batch, stream));
+    return DBF_OK;
+}
+
 // Launches one decode pass of a plan on `stream`.  `mid`, if not NULL, is recorded between the
 // B-stage launch and the A-stage launch of the two-launch kinds (timed entry point only).
 int launch_plan(int kind, const DbfPlan& p, const void* x, void* y, int batch, hipStream_t stream,
@@ -601,6 +625,11 @@ int launch_plan(int kind, const DbfPlan& p, const void* x, void* y, int batch, h
         kind = DBF_GEMV_VALU;
     }
     const int FUSED_MIN_B_ITEMS = dbf_tune(DBF_TUNE_FUSED_MIN_B_ITEMS);
+    // Few row tiles: workgroups that round their own input, at any batch.  Not where a knob names one of the other forms, nor
+    // for plans that quantise every input once per call (long_rows) or that the knob sends through the one launch.
+    if (kind == DBF_GEMV_AUTO && !p.long_rows && dbf_tune(DBF_TUNE_SHARED_Q) < 0 && dbf_tune(DBF_TUNE_SHARED_MIN_BATCH) <= (batch > 2 ? batch : 2) &&
+        !(p.n_layers > 1 && p.nB1 >= FUSED_MIN_B_ITEMS) && dbf_few_takes(p, false, batch) && dbf_few_takes(p, true, batch))
+        return launch_few(p, x, y, batch, stream, mid);
     const bool pieces_ok = kind == DBF_GEMV_AUTO;  // the named kinds keep their one-workgroup-per-row-tile lists
     if (kind == DBF_GEMV_AUTO) kind = DBF_GEMV_MFMA_SPLIT;  // (until the list is known, below)
     const int wait_us = dbf_tune(DBF_TUNE_WAIT_LIMIT_US);
@@ -896,7 +925,7 @@ int dbf_stack_create_grouped(const dbf_layer* const* layers, int n_layers, const
         S->h_y_prefix[i + 1] = S->h_y_prefix[i] + L->n_out;
     }
     S->h_x_prefix[n_layers] = x_end;
-    const int rc = build_plan(sB, sA, stack_spans(DBF_TUNE_STACK_SPAN_B), stack_spans(DBF_TUNE_STACK_SPAN_A), &S->plan);
+    const int rc = build_plan(sB, sA, stack_spans(DBF_TUNE_STACK_SPAN_B), stack_spans(DBF_TUNE_STACK_SPAN_A), nullptr, &S->plan);
     if (rc != DBF_OK) {
         dbf_stack_free(S);
         return rc;

@@ -1,0 +1,523 @@
+// Decode launches of few workgroups: a layer alone or a handful of them at a batch of 2 and more, rows long enough to be
+// cut into column pieces, prompts of a few dozen tokens, and layers so small that one workgroup does both stages.
+//
+// The arithmetic is that of dbf_gemv_mfma.hip (16-bit fixed-point stage inputs as two int8 planes, masked sign bytes as the
+// other operand of v_mfma_i32_16x16x64_i8, exact integer sums), and so are the bits.  The split is another one, because such
+// a launch is not bound by memory or by the matrix cores but by its chain of latencies:
+//   * every workgroup rounds the rows of the stage input it needs itself.  A launch of its own for that costs 3.4-4.3 us,
+//     as much as half of the stage; here it is 5 vector instructions per value beside the sign tiles' way from memory;
+//   * a workgroup has eight wavefronts, each with eight tiles in flight from its first instructions on (64 KiB per workgroup;
+//     four wavefronts with four tiles each held a compute unit that has one workgroup to 11 GB/s);
+//   * where compute units would idle, the tokens of a call are dealt to several workgroups per row tile (`group` tokens each:
+//     less rounding per workgroup, the sign bytes come from L2), and long rows are cut into column pieces.
+// Measured figures are at the dispatch rules (dbf_api.hip).
+#include "dbf_kernels.h"
+#include "dbf_wave.h"
+
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+
+constexpr int FEW_WAVES = 8;
+constexpr int FEW_THREADS = 64 * FEW_WAVES;
+constexpr int FEW_PF = 8;            // tiles in flight per wavefront
+constexpr int FEW_RB = DBF_TILE_ROWS + 1;  // LDS row of a reduction buffer (see RB_STRIDE in dbf_gemv_mfma.hip)
+constexpr float QMAX = 32512.f;
+constexpr unsigned OOB = 0x80000000u;
+
+struct FewMisc {
+    float scale[DBF_MAX_BATCH];
+    int sigma[DBF_MAX_BATCH];
+    float wmax[DBF_MAX_BATCH][FEW_WAVES];
+    int last, pad_[3];
+};
+static_assert(sizeof(FewMisc) % 16 == 0, "the planes behind it are read in 16-byte pieces");
+
+// LDS: FewMisc, the quantised planes tile by tile -- per column tile 64 bytes of plane 0 (row 0's high bytes), of plane 1
+// (its low bytes), ..., 64 bytes of padding that spread the writes over the banks --, then the sums.
+__host__ __device__ inline int few_tile_block(int ncols) { return (ncols + 1) * DBF_TILE_COLS; }
+
+// How the eight wavefronts share the input rows: P rows at a time (a power of two), 8 / P wavefronts each.
+struct FewShare {
+    int P, parts, row, part;
+};
+__host__ __device__ inline int few_parts(int nb) { return nb <= 1 ? 8 : nb <= 2 ? 4 : nb <= 4 ? 2 : 1; }
+__device__ inline FewShare few_share(int nb, int w) {
+    FewShare s;
+    s.parts = few_parts(nb);
+    s.P = FEW_WAVES / s.parts;
+    s.row = w & (s.P - 1);
+    s.part = w / s.P;
+    return s;
+}
+
+// The rows of a stage's input: fp16 x times b (B stage), or the fp32 middle activations, which are padded with zeros.  load()
+// requests the eight values of vector v of a row, get() turns what has arrived into numbers.
+struct FewRaw {
+    v4u a, b;
+};
+struct InputX {
+    const uint16_t* x;   // first row of the group
+    const uint16_t* b;   // zero padded to whole column tiles
+    int cols;
+    bool fast;           // rows can be read in 16-byte pieces
+    __device__ __forceinline__ void load(int bi, int v, FewRaw& r) const {
+        const uint16_t* row = x + (size_t)bi * cols;
+        r.b = *reinterpret_cast<const v4u*>(b + 8 * v);
+        if (fast) {
+            r.a = *reinterpret_cast<const v4u*>(row + (8 * v < cols ? 8 * v : 0));
+        } else {
+            uint16_t h[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) h[e] = row[min(8 * v + e, cols - 1)];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r.a[e] = h[2 * e] | (unsigned)h[2 * e + 1] << 16;
+        }
+    }
+    __device__ __forceinline__ void get(int v, const FewRaw& r, float (&u)[8]) const {
+        const h8 xv = __builtin_bit_cast(h8, r.a), bv = __builtin_bit_cast(h8, r.b);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u[e] = fmaf((float)xv[e], (float)bv[e], -0.f);  // (exact)
+        if (fast) {   // (then cols is a multiple of 8)
+            const bool in = 8 * v < cols;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) u[e] = in ? u[e] : 0.f;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) u[e] = 8 * v + e < cols ? u[e] : 0.f;
+        }
+    }
+};
+struct InputT {
+    const float* t;
+    int stride;
+    __device__ __forceinline__ void load(int bi, int v, FewRaw& r) const {
+        const v4u* p = reinterpret_cast<const v4u*>(t + (size_t)bi * stride + 8 * v);
+        r.a = p[0];
+        r.b = p[1];
+    }
+    __device__ __forceinline__ void get(int, const FewRaw& r, float (&u)[8]) const {
+        const v4f a = __builtin_bit_cast(v4f, r.a), b = __builtin_bit_cast(v4f, r.b);
+        u[0] = a.x;  u[1] = a.y;  u[2] = a.z;  u[3] = a.w;
+        u[4] = b.x;  u[5] = b.y;  u[6] = b.z;  u[7] = b.w;
+    }
+};
+
+// Largest |u| of every row: wmax[row][part].  held: every wavefront has one row and at most H vectors per lane, which have been
+// requested into raw and stay there.
+template <class IN, int H>
+__device__ __forceinline__ void few_max(const IN& in, const FewShare s, int nb, int nvec, bool held, const FewRaw (&raw)[H],
+                                        float (&u)[H][8], FewMisc* m, int lane) {
+    if (held) {
+        float mx = 0.f;
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            in.get(min(lane + 64 * (s.part + s.parts * i), nvec - 1), raw[i], u[i]);   // (a vector past the row repeats its last)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(u[i][e]));
+        }
+        mx = dbf_wave_max(mx);
+        if (lane == 0 && s.row < nb) m->wmax[s.row][s.part] = mx;
+        return;
+    }
+    for (int bi = s.row; bi < nb; bi += s.P) {
+        float mx = 0.f;
+        for (int v0 = lane + 64 * s.part; v0 < nvec; v0 += 64 * s.parts * 4) {
+            FewRaw r[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) in.load(bi, min(v0 + 64 * s.parts * i, nvec - 1), r[i]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float u[8];
+                in.get(min(v0 + 64 * s.parts * i, nvec - 1), r[i], u);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(u[e]));
+            }
+        }
+        mx = dbf_wave_max(mx);
+        if (lane == 0) m->wmax[bi][s.part] = mx;
+    }
+}
+
+// q = rint(u * inv) of eight values as high and low bytes; returns the sum of the q.  Adding 1.5 * 2^23 + 128 rounds to the
+// integer q + 128 (ties to even: 128 is even) and leaves it in the low bits of the word, where byte 1 is the high byte of
+// q and byte 0 the low one with its top bit flipped.
+__device__ __forceinline__ int few_round8(const float (&u)[8], float inv, uint2& hi, uint2& lo) {
+#pragma clang fp contract(off)
+    unsigned p[4], h[2], l[2];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float t0 = u[2 * e] * inv, t1 = u[2 * e + 1] * inv;
+        const unsigned b0 = __builtin_bit_cast(unsigned, t0 + 12583040.f), b1 = __builtin_bit_cast(unsigned, t1 + 12583040.f);
+        p[e] = __builtin_amdgcn_perm(b1, b0, 0x05010400u);  // (b0.0, b1.0, b0.1, b1.1)
+    }
+    int sh = 0, sl = 0;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        l[e] = __builtin_amdgcn_perm(p[2 * e + 1], p[2 * e], 0x05040100u) ^ 0x80808080u;
+        h[e] = __builtin_amdgcn_perm(p[2 * e + 1], p[2 * e], 0x07060302u);
+        sh = __builtin_amdgcn_sdot4((int)h[e], 0x01010101, sh, false);
+        sl = __builtin_amdgcn_sdot4((int)l[e], 0x01010101, sl, false);
+    }
+    hi = make_uint2(h[0], h[1]);
+    lo = make_uint2(l[0], l[1]);
+    return 256 * sh + sl;
+}
+
+// Rounds the vectors [v0, v1) of every row into the planes (whose first column tile is v0's) and adds up the sums of the q.
+template <class IN, int H>
+__device__ __forceinline__ void few_round(const IN& in, const FewShare s, int nb, int nvec, int v0, int v1, bool held,
+                                          const float (&held_u)[H][8], FewMisc* m, unsigned char* planes, int tile_block, int lane) {
+    auto inv_of = [&](int bi) {
+        float mx = 0.f;
+        for (int p = 0; p < s.parts; ++p) mx = fmaxf(mx, m->wmax[bi][p]);
+        if (s.part == 0 && lane == 0) m->scale[bi] = mx / QMAX;
+        return mx > 0.f ? QMAX / mx : 0.f;
+    };
+    auto put = [&](int bi, int v, const float (&u)[8], float inv) {
+        uint2 hi, lo;
+        const int sum = few_round8(u, inv, hi, lo);
+        unsigned char* d = planes + ((v - v0) >> 3) * tile_block + 2 * bi * DBF_TILE_COLS + 8 * (v & 7);
+        *reinterpret_cast<uint2*>(d) = hi;
+        *reinterpret_cast<uint2*>(d + DBF_TILE_COLS) = lo;
+        return sum;
+    };
+    if (held) {
+        if (s.row >= nb) return;
+        const float inv = inv_of(s.row);
+        int sum = 0;
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const int v = lane + 64 * (s.part + s.parts * i);
+            if (v >= v0 && v < v1) sum += put(s.row, v, held_u[i], inv);
+        }
+        sum = dbf_wave_sum(sum);
+        if (lane == 0) atomicAdd(&m->sigma[s.row], sum);
+        return;
+    }
+    for (int bi = s.row; bi < nb; bi += s.P) {
+        const float inv = inv_of(bi);
+        int sum = 0;
+        for (int b = v0 + lane + 64 * s.part; b < v1; b += 64 * s.parts * 4) {
+            FewRaw r[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) in.load(bi, min(b + 64 * s.parts * i, nvec - 1), r[i]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (b + 64 * s.parts * i < v1) {
+                    float u[8];
+                    in.get(b + 64 * s.parts * i, r[i], u);
+                    sum += put(bi, b + 64 * s.parts * i, u, inv);
+                }
+        }
+        sum = dbf_wave_sum(sum);
+        if (lane == 0) atomicAdd(&m->sigma[bi], sum);
+    }
+}
+
+// One wavefront's tiles [lo, hi) of a span of tiles of one row tile.
+struct FewStream {
+    __amdgpu_buffer_rsrc_t rsrc;
+    v4u tl[FEW_PF];
+    int lo, hi, lane;
+
+    __device__ __forceinline__ void fetch(int j, int unit) {
+        const unsigned off = (unit < hi ? (unsigned)unit * DBF_TILE_BYTES : OOB) + 16u * lane;
+        tl[j] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
+    }
+    __device__ __forceinline__ void start(const uint8_t* bits, int n_units, int lo_, int hi_, int lane_) {
+        rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(bits), 0, n_units * DBF_TILE_BYTES, 0x00020000);
+        lo = lo_;  hi = hi_;  lane = lane_;
+#pragma unroll
+        for (int j = 0; j < FEW_PF; ++j) {
+            fetch(j, lo + j);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // planes: LDS planes whose tile 0 is the span's first tile.
+    __device__ __forceinline__ void run(const unsigned char* planes, int tile_block, int ncols, v4i (&acc)[8]) {
+        const int g = lane >> 4, c = lane & 15;
+        // (unused operand columns alias a valid one)
+        const unsigned char* xp = planes + (c < ncols ? c : c % ncols) * DBF_TILE_COLS + 16 * g + lo * tile_block;
+        auto multiply = [&](int j) {
+            const v4i xv = *reinterpret_cast<const v4i*>(xp);
+            xp += tile_block;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const unsigned msk = 0x01010101u << s;
+                const v4i a = {(int)(tl[j].x & msk), (int)(tl[j].y & msk), (int)(tl[j].z & msk), (int)(tl[j].w & msk)};
+                acc[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, xv, acc[s], 0, 0, 0);
+            }
+        };
+        // (whole rounds of the ring, then the rest without new requests: with a way out in the middle of a round the compiler
+        //  cannot tell which loads are still under way at its start, and waits for all of them)
+        int i0 = lo;
+        for (; i0 + FEW_PF <= hi; i0 += FEW_PF) {
+#pragma unroll
+            for (int j = 0; j < FEW_PF; ++j) {
+                multiply(j);
+                fetch(j, i0 + j + FEW_PF);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < FEW_PF - 1; ++j) {
+            if (i0 + j >= hi) break;
+            multiply(j);
+        }
+    }
+};
+
+// The signed sum of row rho of a row tile and batch row bi: 2 * (sum over the set bits) - sigma, exact (modulo 2^32 on the way).
+__device__ inline int few_total(const int* red, int bi, int rho, int sigma) {
+    const int s = rho >> 4;
+    int vh = red[2 * bi * FEW_RB + rho] >> s, vl = red[(2 * bi + 1) * FEW_RB + rho] >> s;
+    if (s == 7) {  // the mask 0x80 is -128 as an int8
+        vh = -vh;
+        vl = -vl;
+    }
+    return (int)(2u * (unsigned)(vh * 256 + vl) - (unsigned)sigma);
+}
+
+// Rounded to fp32, then to fp16, as in every other kernel (left to itself the compiler rounds the last product to fp16 at once:
+// one output in ten thousand in its last bit).
+__device__ __forceinline__ uint16_t few_half(float v) {
+    asm("" : "+v"(v));
+    return __builtin_bit_cast(uint16_t, (_Float16)v);
+}
+
+// One stage, workgroup (row tile, token group, column piece).  `first`: LIST: the items (one row tile each); else the layer's
+// sign tiles, everything a workgroup needs being kernel arguments that arrive in scalar registers (a layer alone: no memory round
+// trip before its loads).  io: x or y.  acc: zeroed integers, [row tile][DBF_MAX_BATCH][128], then an arrival counter per
+// (row tile, token group).
+template <bool STAGE_A, bool LIST, int H>
+__global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_few_kernel(
+    const void* __restrict__ first, const uint16_t* __restrict__ in_scale, const uint16_t* __restrict__ row_scale, float* __restrict__ t_base,
+    uint16_t* __restrict__ io, int* __restrict__ acc_base, int cols_, int rows_, unsigned tokens, unsigned cut) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T = tokens & 0xFFFF, group = tokens >> 16, chunk_tiles = cut & 0xFFFF, pieces = cut >> 16;
+    const int t0 = blockIdx.y * group, nb = min(group, T - t0), ncols = 2 * nb;
+    const int tile_block = few_tile_block(ncols);
+    const uint8_t* bits;
+    int cols, rows, row0, stride, n_items;
+    if (LIST) {
+        const DbfItem& it = static_cast<const DbfItem*>(first)[blockIdx.x];
+        bits = it.bits;
+        cols = it.cols;  rows = it.rows;  row0 = it.row0;  stride = it.t_stride;
+        in_scale = it.in_scale;  row_scale = it.row_scale;
+        if (!t_base) t_base = it.t;
+        io += it.io_off * T;
+        n_items = rows_;
+    } else {
+        cols = cols_;  rows = rows_;  row0 = blockIdx.x * DBF_TILE_ROWS;
+        stride = ((STAGE_A ? cols : rows) + DBF_TILE_ROWS - 1) & ~(DBF_TILE_ROWS - 1);
+        bits = static_cast<const uint8_t*>(first) + (size_t)blockIdx.x * ((cols + DBF_TILE_COLS - 1) / DBF_TILE_COLS) * DBF_TILE_BYTES;
+        row_scale += row0;
+        n_items = (rows + DBF_TILE_ROWS - 1) / DBF_TILE_ROWS;
+    }
+    const int n_ct = (cols + DBF_TILE_COLS - 1) / DBF_TILE_COLS, nvec = 8 * n_ct;
+    const int ct0 = n_ct * blockIdx.z / pieces, ct1 = n_ct * (blockIdx.z + 1) / pieces;
+    FewMisc* m = reinterpret_cast<FewMisc*>(smem);
+    unsigned char* planes = smem + sizeof(FewMisc);
+    int* red = reinterpret_cast<int*>(planes + chunk_tiles * tile_block);
+    float* t = t_base + (size_t)t0 * stride;
+    const FewShare sh = few_share(nb, w);
+
+    InputX inx;
+    inx.x = io + (size_t)t0 * cols;  inx.b = in_scale;  inx.cols = cols;
+    inx.fast = (cols & 7) == 0 && (reinterpret_cast<uintptr_t>(inx.x) & 15) == 0;
+    const InputT inp = {t, stride};
+    const int mine = (nvec + 64 * sh.parts - 1) / (64 * sh.parts);
+    const bool held = mine <= H && ct1 - ct0 <= chunk_tiles && (STAGE_A || inx.fast);
+    const float rscale = (float)__builtin_bit_cast(_Float16, row_scale[tid & 127]);
+    // The input is requested before the first tiles: loads complete in order, and the tiles come from farther away.
+    FewRaw raw[H];
+    FewStream st;
+    int c0 = ct0, c1 = min(ct1, c0 + chunk_tiles);
+    auto start = [&]() {
+        const int n = c1 - c0;
+        st.start(bits + (size_t)c0 * DBF_TILE_BYTES, n, n * w / FEW_WAVES, n * (w + 1) / FEW_WAVES, lane);
+    };
+    if (held) {
+        const int bi = min(sh.row, nb - 1);
+#pragma unroll
+        for (int i = 0; i < H; ++i) {
+            const int v = min(lane + 64 * (sh.part + sh.parts * i), nvec - 1);
+            if (STAGE_A) inp.load(bi, v, raw[i]); else inx.load(bi, v, raw[i]);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    start();
+    __builtin_amdgcn_sched_barrier(0);
+    for (int i = tid; i < ncols * FEW_RB; i += FEW_THREADS) red[i] = 0;
+    if (tid < DBF_MAX_BATCH) m->sigma[tid] = 0;
+    float u[H][8];
+    if (STAGE_A) few_max(inp, sh, nb, nvec, held, raw, u, m, lane); else few_max(inx, sh, nb, nvec, held, raw, u, m, lane);
+    __syncthreads();
+    v4i acc[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) acc[s] = (v4i){0, 0, 0, 0};
+    for (;;) {
+        if (STAGE_A) few_round(inp, sh, nb, nvec, 8 * c0, 8 * c1, held, u, m, planes, tile_block, lane);
+        else few_round(inx, sh, nb, nvec, 8 * c0, 8 * c1, held, u, m, planes, tile_block, lane);
+        __syncthreads();
+        st.run(planes, tile_block, ncols, acc);
+        if (c1 >= ct1) break;
+        __syncthreads();   // every wavefront is done with the chunk's planes
+        c0 = c1;
+        c1 = min(ct1, c0 + chunk_tiles);
+        start();
+    }
+    // the wavefronts' sums: register i of acc[s] of lane (g, c) is row 16 s + 4 g + i, operand column c
+    if ((lane & 15) < ncols) {
+#pragma unroll
+        for (int s = 0; s < 8; ++s)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) atomicAdd(&red[(lane & 15) * FEW_RB + 4 * (lane >> 4) + 16 * s + i], acc[s][i]);
+    }
+    __syncthreads();
+
+    const int rho = tid & 127, row = row0 + rho;
+    auto store = [&](int bi, int total) {
+        const float val = (float)total * m->scale[bi] * rscale;
+        if (STAGE_A) {
+            if (row < rows) io[(size_t)(t0 + bi) * rows + row] = few_half(val);
+        } else {
+            t[(size_t)bi * stride + row] = val;   // (padded rows have scale 0)
+        }
+    };
+    if (pieces == 1) {
+        for (int bi = tid >> 7; bi < nb; bi += FEW_THREADS / 128) store(bi, few_total(red, bi, rho, m->sigma[bi]));
+        return;
+    }
+    // A column piece: exact integer sums are added up in memory; the last piece of the row tile to arrive takes them out
+    // (leaving zeros), scales and stores.
+    int* a = acc_base + ((size_t)blockIdx.x * DBF_MAX_BATCH + t0) * DBF_TILE_ROWS + rho;
+    for (int bi = tid >> 7; bi < nb; bi += FEW_THREADS / 128)
+        __hip_atomic_fetch_add(a + bi * DBF_TILE_ROWS, few_total(red, bi, rho, m->sigma[bi]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's adds have been performed ...
+    __syncthreads();                                  // ... and so have the workgroup's
+    if (tid == 0) {
+        int* cnt = acc_base + (size_t)n_items * DBF_MAX_BATCH * DBF_TILE_ROWS + (size_t)blockIdx.x * DBF_PIECE_CNT_STRIDE + blockIdx.y;
+        m->last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == pieces - 1;
+        if (m->last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!m->last) return;
+    for (int bi = tid >> 7; bi < nb; bi += FEW_THREADS / 128)
+        store(bi, __hip_atomic_exchange(a + bi * DBF_TILE_ROWS, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+constexpr int FEW_MAX_WGS = 256;     // compute units
+constexpr int FEW_LDS = 156 * 1024;  // (its registers give a workgroup the compute unit to itself)
+
+template <bool STAGE_A, bool LIST, int H>
+hipError_t raise_lds() {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(&dbf_few_kernel<STAGE_A, LIST, H>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                               FEW_LDS);
+}
+
+// Tokens per workgroup and column pieces of a stage of n_items row tiles.  As many workgroups as there are compute units, and no
+// more: a second one on a compute unit costs a whole round (its registers allow one).  Fewer tokens per workgroup first -- less
+// rounding in each, no combination --, then, for rows of 80 column tiles and more, pieces of at least 24 tiles.  Microseconds per call:
+//   4096 x 4096, k = 3072, batch 8, tokens per workgroup 8 / 4 / 2                 14.6 / 13.7 / 13.4 (96 workgroups a stage at most)
+//   three of them, batch 8, 8 / 4 / 2                                              15.0 / 14.1 / 24.8 (288 workgroups)
+//   28672 -> 8192, k = 12743, batch 1, pieces of the two stages 1, 1 / 2, 4 / 3, 4 27.1 / 22.5 / 29.6 (100 row tiles: 300 workgroups)
+//   11008 -> 4096, k = 4477, batch 1, pieces 1 / 2 / 4 / 7                         16.7 / 15.7 / 14.5 / 14.1
+//   4096 -> 11008, k = 4477 (70 column tiles), batch 1, pieces 1 / 2               13.5 / 13.8
+struct FewCut {
+    int group, pieces;
+    long long wgs;
+};
+FewCut few_cut(int n_items, int n_ct, int T, bool pieces_ok) {
+    FewCut c = {2, 1, 0};
+    auto groups = [&]() { return (T + c.group - 1) / c.group; };
+    while (c.group < 8 && (long long)n_items * groups() > FEW_MAX_WGS) c.group *= 2;
+    c.wgs = (long long)n_items * groups();
+    if (pieces_ok && n_ct >= 80 && 2 * c.wgs <= FEW_MAX_WGS) {
+        c.pieces = (int)(FEW_MAX_WGS / c.wgs);
+        if (c.pieces > n_ct / 24) c.pieces = n_ct / 24;
+    }
+    return c;
+}
+inline int few_cols(const DbfPlan& p, bool stage_a) { return dbf_col_tiles(stage_a ? p.max_cols_A : p.max_cols_B); }
+
+}  // namespace
+
+// More than 64 KiB of LDS per workgroup has to be asked for, once per process (see dbf_mfma_prepare).
+hipError_t dbf_few_prepare() {
+    static const hipError_t raised = [] {
+        const hipError_t e[] = {raise_lds<false, false, 2>(), raise_lds<false, true, 2>(), raise_lds<true, false, 2>(), raise_lds<true, true, 2>(),
+                                raise_lds<false, false, 4>(), raise_lds<false, true, 4>(), raise_lds<true, false, 4>(), raise_lds<true, true, 4>(),
+                                raise_lds<false, false, 8>(), raise_lds<false, true, 8>(), raise_lds<true, false, 8>(), raise_lds<true, true, 8>()};
+        for (hipError_t x : e)
+            if (x != hipSuccess) {
+                (void)hipGetLastError();
+                return x;
+            }
+        return hipSuccess;
+    }();
+    return raised;
+}
+
+// A stage is taken if it makes at most one workgroup per compute unit, and a workgroup has no more than 2560 column tiles to round
+// (tokens x column tiles).  Against the launches it stands in for, microseconds per call of both stages:
+//   4096 x 4096, k = 3072         batch 1 / 2 / 8 / 16   11.1 / 15.2 / 16.8 / 21.0 -> 10.9 / 11.5 / 11.6 / 11.9
+//   three of them                                        11.3 / 15.3 / 17.0 / 21.4 -> 11.0 / 11.6 / 13.0 / 16.1
+//   11008 -> 4096, k = 4477                              16.3 / 24.7 / 24.9 / 30.5 -> 12.0 / 13.8 / 17.1 / 21.9
+//   28672 -> 8192, k = 12743                             36.5 / 58.0 / 60.3 / 68.9 -> 21.0 / 26.8 / 47.3 / (71.0: 8 x 448 column tiles)
+//   512 x 512, k = 256                                    8.3 / 12.3 / 13.4 / 16.4 ->  7.6 /  8.0 /  8.1 /  8.3
+//   two of 4096 -> 11008, k = 4477 at batch 16           23.1 -> (29.0: 344 workgroups)
+bool dbf_few_takes(const DbfPlan& p, bool stage_a, int T) {
+    const int longest = p.max_cols_B > p.max_cols_A ? p.max_cols_B : p.max_cols_A;
+    if (longest > DBF_INT_PATH_MAX_COLS) return false;
+    const FewCut c = few_cut(stage_a ? p.nA1 : p.nB1, few_cols(p, stage_a), T, false);
+    return c.wgs <= FEW_MAX_WGS && (c.group < T ? c.group : T) * few_cols(p, stage_a) <= 2560;
+}
+
+hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y, float* t_over, int T, hipStream_t stream) {
+    const hipError_t raised = dbf_few_prepare();
+    if (raised != hipSuccess) return raised;
+    const FewCut cut_ = few_cut(stage_a ? p.nA1 : p.nB1, few_cols(p, stage_a), T, p.d_few_acc && T <= DBF_MAX_BATCH);
+    const int group = cut_.group, pieces = cut_.pieces;
+    const int nb = group < T ? group : T, tile_block = few_tile_block(2 * nb), red = 2 * nb * FEW_RB * 4;
+    const int n_ct = dbf_col_tiles(stage_a ? p.max_cols_A : p.max_cols_B), want = (n_ct + pieces - 1) / pieces;
+    const int fit = (FEW_LDS - (int)sizeof(FewMisc) - red) / tile_block;
+    const int chunk = want < fit ? want : fit;
+    const size_t lds = sizeof(FewMisc) + (size_t)chunk * tile_block + red;
+    const int n_items = stage_a ? p.nA1 : p.nB1;
+    const dim3 grid(n_items, (T + group - 1) / group, pieces);
+    uint16_t* io = static_cast<uint16_t*>(stage_a ? y : const_cast<void*>(x));
+    const unsigned tokens = (unsigned)T | (unsigned)group << 16, cut = (unsigned)chunk | (unsigned)pieces << 16;
+    const DbfStage& s = stage_a ? p.h_stage_A : p.h_stage_B;   // (a layer alone)
+    const bool list = p.n_layers > 1;
+    const void* first = list ? static_cast<const void*>(p.d_items_1 + (stage_a ? p.nB1 : 0)) : s.bits;
+    float* t = t_over ? t_over : list ? nullptr : s.t;
+    const int held = (8 * n_ct + 64 * few_parts(nb) - 1) / (64 * few_parts(nb));   // vectors of eight values per lane
+#define DBF_FEW(A, L)                                                                                                                          \
+    if (held <= 2)                                                                                                                             \
+        hipLaunchKernelGGL((dbf_few_kernel<A, L, 2>), grid, dim3(FEW_THREADS), lds, stream, first, s.in_scale, s.row_scale, t, io, p.d_few_acc, \
+                           s.cols, list ? n_items : s.rows, tokens, cut);                                                                      \
+    else if (held <= 4)                                                                                                                        \
+        hipLaunchKernelGGL((dbf_few_kernel<A, L, 4>), grid, dim3(FEW_THREADS), lds, stream, first, s.in_scale, s.row_scale, t, io, p.d_few_acc, \
+                           s.cols, list ? n_items : s.rows, tokens, cut);                                                                      \
+    else                                                                                                                                       \
+        hipLaunchKernelGGL((dbf_few_kernel<A, L, 8>), grid, dim3(FEW_THREADS), lds, stream, first, s.in_scale, s.row_scale, t, io, p.d_few_acc, \
+                           s.cols, list ? n_items : s.rows, tokens, cut)
+    if (stage_a && list) {
+        DBF_FEW(true, true);
+    } else if (stage_a) {
+        DBF_FEW(true, false);
+    } else if (list) {
+        DBF_FEW(false, true);
+    } else {
+        DBF_FEW(false, false);
+    }
+#undef DBF_FEW
+    return hipGetLastError();
+}

@@ -43,6 +43,14 @@ int dbf_mfma_one_pass_cols();
 // One-time, per-process set-up of the matrix-core decode kernels (LDS limits); cheap to call again.
 hipError_t dbf_mfma_prepare();
 
+// Launches of few workgroups (dbf_gemv_few.hip): one stage of the plan's layers for T (below 65536) tokens or batch rows, every workgroup
+// rounding the stage input it needs.  dbf_few_takes: whether the stage is one for it.
+// t_over: the middle activations [T][t_stride], or NULL for the layers' own (T <= DBF_MAX_BATCH).
+bool dbf_few_takes(const DbfPlan& p, bool stage_a, int T);
+hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y, float* t_over, int T, hipStream_t stream);
+// One-time, per-process set-up of those kernels (LDS limits); cheap to call again.
+hipError_t dbf_few_prepare();
+
 // Prefill (T tokens): two stages with the middle activations in the caller's workspace; arguments are
 // validated by dbf_gemm before this is called.  int8 matrix cores as the adder (masked sign bytes as one
 // operand, the activations rounded per token to 16-bit fixed point and split into two int8 planes), exact

@@ -815,3 +815,42 @@ def test_one_launch_calls_may_switch_between_the_lists_of_a_plan():
         stack.close()
         for l in layers:
             l.close()
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (64, 128, 64), (65, 129, 63), (520, 1000, 300), (1023, 257, 511), (4104, 300, 4160),
+                                   (5184, 130, 5120), (12296, 260, 900), (900, 200, 12300)])
+def test_launches_of_few_workgroups_equal_the_two_launch_kind_bit_for_bit(shape):
+    """The default kind on a layer alone and on a group of three: workgroups that round their own input, with the values held in
+    registers (2, 4 or 8 vectors per lane) or read twice, one row tile whole or in column pieces (80 column tiles and more), in one
+    chunk of LDS or several, 2 to 8 batch rows per workgroup.  Every batch, an x that can be read in 16-byte pieces
+    and one that cannot, two calls in a row (the pieces' sums must be left at zero).  Integer sums: no tolerance."""
+    n_in, n_out, k = shape
+    Ls = [I.make_layer(n_in, n_out, k, seed=I.seed_for(6, 700 + i + k)) for i in range(3)]
+    layers = [G.pack(L) for L in Ls]
+    stack = B.dbf_stack_create_grouped(layers, [3])
+    try:
+        for batch in (1, 2, 3, 4, 7, 8, 9, 16):
+            X = I.make_activations(batch, n_in, I.seed_for(6, 750 + batch))
+            for off in (0, 1):
+                buf = torch.zeros(batch * n_in + 8, dtype=torch.float16, device="cuda")
+                buf[off:off + batch * n_in] = G.f16_to_dev(X).reshape(-1)
+                ptr = buf.data_ptr() + 2 * off
+
+                def run(call, n, kind):
+                    y = torch.full((n, batch, n_out), float("nan"), dtype=torch.float16, device="cuda")
+                    call(ptr, y.data_ptr(), batch, G.stream_handle(), kind)
+                    torch.cuda.synchronize()
+                    return y.cpu().view(torch.int16).numpy()
+
+                what = "few n_in=%d n_out=%d k=%d batch=%d offset=%d" % (n_in, n_out, k, batch, off)
+                G.say("start " + what)
+                alone = lambda *a: B.dbf_gemv(layers[0], *a)   # noqa: E731
+                group = lambda *a: B.dbf_stack_gemv(stack, *a)  # noqa: E731
+                for call, n in ((alone, 1), (group, 3)):
+                    want = run(call, n, B.GEMV_MFMA_SPLIT)
+                    for rep in range(2):
+                        assert np.array_equal(run(call, n, B.GEMV_AUTO), want), (what, n, rep)
+    finally:
+        stack.close()
+        for l in layers:
+            l.close()
