@@ -169,13 +169,11 @@ int dbf_sync_timeouts(const dbf_layer* layer, int* timeouts);
  *                per token to 16-bit fixed point (q = rint(u * 32512 / max|u|)) and split into two int8
  *                planes; the masked sign bytes are the other operand; the sums are exact integers; the
  *                middle activations stay in fp32.
- *   DBF_GEMM_AUTO (dbf_gemm): DBF_GEMM_I8; calls of up to 2 * DBF_MAX_BATCH tokens are run as one or two
- *                decode batches (dbf_gemv), which give the same bits at a third to two thirds of the latency.
+ *   DBF_GEMM_AUTO (dbf_gemm): DBF_GEMM_I8; calls of up to DBF_MAX_BATCH tokens (2 * DBF_MAX_BATCH where n_in or k is
+ *                above DBF_INT_PATH_MAX_COLS) are run as decode batches (dbf_gemv), which give the same bits.
  *
  * X_dev: device fp16 [T][n_in]; Y_dev: device fp16 [T][n_out]; T >= 1 (at most 65535 * 64).
- * workspace_dev: device scratch of at least dbf_gemm_workspace_bytes(layer, T) bytes (up to 512 tokens that
- * includes room for the integer sums of stages whose columns are cut into shares over more workgroups: calls of
- * few tokens would otherwise leave most of the chip idle; same bits), 256-byte aligned, contents need not be
+ * workspace_dev: device scratch of at least dbf_gemm_workspace_bytes(layer, T) bytes, 256-byte aligned, contents need not be
  * anything on entry and are undefined on return.  Asynchronous on the
  * stream; allocates nothing.  Errors: DBF_EINVAL (NULL pointer, T < 1 or too large, unknown
  * kind), DBF_EWORKSPACE (NULL, misaligned or short workspace), DBF_ESHAPE (more than 2 * DBF_MAX_BATCH tokens
@@ -194,9 +192,8 @@ int dbf_gemm_kind(const dbf_layer* layer, const void* X_dev, void* Y_dev, int T,
  * dbf_gemm_kind(..., DBF_GEMM_I8, ...), for every T >= 1, with the scratch (quantised activations, fp32 middle
  * activations) in a static device array of DBF_GEMM_STATIC_BYTES that each GPU the library runs on holds
  * until the process ends.  Calls no hipMalloc / hipFree or any allocating routine.
- *   Limit: every call with dbf_gemm_workspace_bytes(layer, T) <= DBF_GEMM_STATIC_BYTES is taken, and so is a
- *   call of up to 512 tokens that fits without the room for the sums of column shares (it then runs unsplit);
- *   else DBF_EWORKSPACE and nothing is launched (T = 512 at 11008 -> 4096, k = 5970 needs 28.4 MiB unsplit; 1024
+ *   Limit: every call with dbf_gemm_workspace_bytes(layer, T) <= DBF_GEMM_STATIC_BYTES is taken,
+ *   else DBF_EWORKSPACE and nothing is launched (T = 512 at 11008 -> 4096, k = 5970 needs 28.4 MiB; 1024
  *   tokens of a 4096 x 4096, k = 2048 layer 20 MiB).  The current device must be the layer's (DBF_EINVAL).
  *   The first call on a device looks up the array's address (hipGetSymbolAddress); make it outside graph capture.
  *   Every call on a GPU uses that GPU's one array: calls that may overlap in time on one GPU (two streams,
@@ -389,10 +386,10 @@ enum {
                                          quantise every stage input once per call at batch 1 too (four launches per
                                          call instead of one); 0: no plan does; 1: every plan does                  */
     /* LAUNCH knob */
-    DBF_TUNE_GEMM_SPLITS = 12,        /* dbf_gemm / dbf_gemm_static of up to 512 tokens: -1 (default): a stage that
-                                         would start at most 64 workgroups (256 rows x 64 tokens each; 128 if it
-                                         has 8192 columns or more) cuts its columns into 4 shares; 1: never; N in
-                                         2..1024: N shares (at most one per 64 columns)                            */
+    DBF_TUNE_GEMM_SPLITS = 12,        /* dbf_gemm / dbf_gemm_static: -1 (default): the kernel of a stage is chosen by its size;
+                                         1: always the one whose workgroups (256 rows x 64 tokens) walk all columns;
+                                         2..1024: always the one whose wavefronts (128 rows x 32 tokens each) take a share
+                                         of the columns, a fourth (below 8) or an eighth                            */
     DBF_TUNE_FUSED_MIN_B_ITEMS = 13,  /* DBF_GEMV_AUTO at batch 1 runs both stages of a group of layers in one launch
                                          only if the B stage has at least this many workgroups, else in a launch per
                                          stage; 0..2^20 (default 1024: what the chip holds at once)                  */

@@ -425,6 +425,7 @@ int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA,
     void* dev = nullptr;
     hipError_t e = dbf_mfma_prepare();
     if (e == hipSuccess) e = dbf_few_prepare();
+    if (e == hipSuccess) e = dbf_gemm_i8_prepare();
     // (the sums of the column pieces of small launches, cleared on the device: they are no part of the image)
     const size_t few_bytes = few_acc_bytes((int)(rtB > rtA ? rtB : rtA)), few_own = few_acc ? 0 : few_bytes;
     if (e == hipSuccess) e = hipMalloc(&dev, off + few_own);
@@ -731,12 +732,11 @@ int dbf_gemm_kind(const dbf_layer* L, const void* X_dev, void* Y_dev, int T, voi
         return DBF_EWORKSPACE;
     if ((T + 63) / 64 > 65535) return DBF_EINVAL;  // token blocks are the grid's y dimension
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    // Up to 16 tokens are a decode batch: the same fixed-point arithmetic (the int8 prefill gives the decode
-    // kernel's bits), at a third of the latency (a prefill workgroup walks all column steps of its rows
-    // whatever the token count: 67 us against 24 us at 4096 x 4096, k = 4096).
-    // Up to 32 tokens are two such batches, one after the other (4096 x 4096, k = 4096: 35-46 us for 17-32 tokens
-    // against 64-65; 11008 -> 4096, k = 5970: 53-67 against 119-120; at 48 tokens three batches lose on the first).
-    if (kind == DBF_GEMM_AUTO && T <= 2 * DBF_MAX_BATCH) {
+    // Up to 16 tokens are a decode batch: the same fixed-point arithmetic (prefill gives the decode kernels' bits), without
+    // the launches that quantise a prompt (4096 x 4096, k = 4096 at 16 tokens: 13.7 us against 22).
+    // (... and up to 32 tokens two of them on layers beyond the integer paths, which decode with fp32 sums)
+    const bool long_rows = L->n_in > DBF_INT_PATH_MAX_COLS || L->k > DBF_INT_PATH_MAX_COLS;
+    if (kind == DBF_GEMM_AUTO && T <= (long_rows ? 2 : 1) * DBF_MAX_BATCH) {
         for (int t0 = 0; t0 < T; t0 += DBF_MAX_BATCH) {
             const int nb = T - t0 < DBF_MAX_BATCH ? T - t0 : DBF_MAX_BATCH;
             const int rc = launch_plan(DBF_GEMV_AUTO, L->plan, static_cast<const uint16_t*>(X_dev) + (size_t)t0 * L->n_in,
@@ -745,8 +745,8 @@ int dbf_gemm_kind(const dbf_layer* L, const void* X_dev, void* Y_dev, int T, voi
         }
         return DBF_OK;
     }
-    if (L->n_in > DBF_INT_PATH_MAX_COLS || L->k > DBF_INT_PATH_MAX_COLS) return DBF_ESHAPE;  // (int32 sums: see dbf.h)
-    const hipError_t e = dbf_gemm_i8_launch(L, X_dev, Y_dev, T, workspace_dev, workspace_bytes, stream);
+    if (long_rows) return DBF_ESHAPE;  // (int32 sums: see dbf.h)
+    const hipError_t e = dbf_gemm_i8_launch(L, X_dev, Y_dev, T, workspace_dev, stream);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return DBF_EHIP;

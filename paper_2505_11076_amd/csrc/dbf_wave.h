@@ -11,11 +11,20 @@ template <int CTRL>
 __device__ inline int dbf_dpp_move(int v) {
     return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
 }
-__device__ inline float dbf_wave_max(float v) {
+__device__ inline float dbf_row16_max(float v) {  // of the row's 16 lanes, in every one of them
     v = fmaxf(v, __builtin_bit_cast(float, dbf_dpp_move<0xB1>(__builtin_bit_cast(int, v))));   // quad_perm [1,0,3,2]
     v = fmaxf(v, __builtin_bit_cast(float, dbf_dpp_move<0x4E>(__builtin_bit_cast(int, v))));   // quad_perm [2,3,0,1]
     v = fmaxf(v, __builtin_bit_cast(float, dbf_dpp_move<0x124>(__builtin_bit_cast(int, v))));  // row_ror:4
-    v = fmaxf(v, __builtin_bit_cast(float, dbf_dpp_move<0x128>(__builtin_bit_cast(int, v))));  // row_ror:8
+    return fmaxf(v, __builtin_bit_cast(float, dbf_dpp_move<0x128>(__builtin_bit_cast(int, v))));  // row_ror:8
+}
+__device__ inline int dbf_row16_sum(int v) {
+    v += dbf_dpp_move<0xB1>(v);
+    v += dbf_dpp_move<0x4E>(v);
+    v += dbf_dpp_move<0x124>(v);
+    return v + dbf_dpp_move<0x128>(v);
+}
+__device__ inline float dbf_wave_max(float v) {
+    v = dbf_row16_max(v);
     const int b = __builtin_bit_cast(int, v);
     const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 0));
     const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 16));
@@ -24,10 +33,7 @@ __device__ inline float dbf_wave_max(float v) {
     return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
 }
 __device__ inline int dbf_wave_sum(int v) {
-    v += dbf_dpp_move<0xB1>(v);
-    v += dbf_dpp_move<0x4E>(v);
-    v += dbf_dpp_move<0x124>(v);
-    v += dbf_dpp_move<0x128>(v);
+    v = dbf_row16_sum(v);
     return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) +
            __builtin_amdgcn_readlane(v, 48);
 }

@@ -200,3 +200,25 @@ def test_gemm_argument_errors():
         assert lib.dbf_gemm_kind(h, x.data_ptr(), y.data_ptr(), T, ws.data_ptr(), need, 1, None) == B.DBF_EINVAL  # withdrawn
     finally:
         layer.close()
+
+
+@pytest.mark.parametrize("shape", [(40, 10, 9), (64, 128, 64), (700, 300, 129), (4096, 900, 1000), (4104, 130, 5000), (12304, 260, 600)])
+def test_prefill_kernels_by_size_equal_the_decode_kernels_bit_for_bit(shape):
+    """Around the sizes where the kernel of a stage changes -- workgroups that round their own input (up to 8 tokens each), 128 rows x 32
+    tokens with the columns shared by eight or four wavefronts, 256 rows x 64 tokens, rows quantised from registers, by a wavefront
+    or by a workgroup -- and with the kernels named by the knob (1: the last; 2, 8: shares of a fourth, an eighth).  Integer
+    sums: no tolerance."""
+    n_in, n_out, k = shape
+    L = I.make_layer(n_in, n_out, k, seed=I.seed_for(4, 130 + k))
+    X = I.make_activations(577, n_in, I.seed_for(4, 131 + k))
+    layer = G.pack(L)
+    try:
+        want = _decode_in_batches(layer, X)
+        for T in (17, 31, 32, 33, 63, 65, 129, 256, 257, 577):
+            for knob in (-1, 1, 2, 8):
+                B.dbf_tuning_set(B.TUNE_GEMM_SPLITS, knob)
+                G.say("start prefill n_in=%d n_out=%d k=%d T=%d knob %d" % (n_in, n_out, k, T, knob))
+                assert np.array_equal(G.run_gemm(layer, X[:T], B.GEMM_AUTO), want[:T]), (T, knob)
+    finally:
+        B.dbf_tuning_reset()
+        layer.close()
