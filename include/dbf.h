@@ -65,7 +65,8 @@ enum {
 enum {
     DBF_GEMV_AUTO = 0, /* what dbf_gemv uses.  A layer or a group whose stages have at most 256 workgroups (row tiles
                           of 128 rows times groups of up to 8 batch rows): two launches at any batch, every
-                          workgroup rounding the stage input it needs, long rows cut into column pieces.
+                          workgroup rounding the stage input it needs, long rows cut into column pieces; one
+                          launch for layers of at most 32 tiles (of 128 rows x 64 columns) a stage.
                           Else, batch 1: DBF_GEMV_MFMA for a group of layers whose B stage alone fills the
                           chip (1024 workgroups: 64 layers of 4096 x 4096, k = 2048), DBF_GEMV_MFMA_SPLIT for
                           shorter groups (measured faster there: in one launch their A-stage workgroups

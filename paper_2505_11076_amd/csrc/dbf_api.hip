@@ -240,6 +240,11 @@ int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA,
         for (int rt = 0; rt < sA[i].n_rt; ++rt) wA1.push_back(DbfWorkItem{i, rt, 1, 0});
         if (sB[i].cols > p->max_cols_B) p->max_cols_B = sB[i].cols;
         if (sA[i].cols > p->max_cols_A) p->max_cols_A = sA[i].cols;
+        if (sA[i].n_rt > p->max_rt_A) p->max_rt_A = sA[i].n_rt;
+        for (const DbfStage* st : {&sB[i], &sA[i]}) {
+            const long long tiles = (long long)st->n_rt * st->n_ct;
+            if (tiles > p->max_stage_tiles) p->max_stage_tiles = tiles;
+        }
     }
     // Several layers most of whose sign bytes sit in layers with long stage inputs -- one longer than the one-pass
     // prologue holds, so that every workgroup would read it twice (for the scale, then for the rounding: as many
@@ -599,6 +604,10 @@ inline bool kind_ok(int kind) {
 
 // Both stages of a plan in launches of few workgroups (dbf_gemv_few.hip), where each has at most one workgroup per compute unit.
 int launch_few(const DbfPlan& p, const void* x, void* y, int batch, hipStream_t stream, hipEvent_t mid) {
+    if (!mid && dbf_small_layer_takes(p, batch)) {   // (one launch; the timed entry point keeps the two it reports)
+        DBF_HIP_TRY(dbf_launch_small_layers(p, x, y, batch, stream));
+        return DBF_OK;
+    }
     DBF_HIP_TRY(dbf_launch_few(p, false, x, y, nullptr, batch, stream));
     if (mid) DBF_HIP_TRY(hipEventRecord(mid, stream));
     DBF_HIP_TRY(dbf_launch_few(p, true, x, y, nullptr, batch, stream));

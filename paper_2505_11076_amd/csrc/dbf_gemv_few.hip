@@ -413,6 +413,126 @@ __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
         store(bi, __hip_atomic_exchange(a + bi * DBF_TILE_ROWS, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
+// ---------------------------------------------------------------------------------------------
+// A small layer in one launch: a workgroup per layer and pair of tokens runs both stages, the middle activations stay in LDS.  For layers
+// of at most SMALL_TILES tiles a stage, i.e. four per wavefront: the signs of BOTH stages are requested at the start and have
+// arrived when they are needed.  Such a call is bound by its launches -- the host takes 3.2 us for each, the device 2 --,
+// not by the one compute unit that does the work.  Device, us per call at batch 1 / 8, two launches / one: 512 x 512, k = 256 (16 tiles)
+// 7.6, 8.1 / 6.4, 7.2;  k = 512 (32) 7.8, 8.3 / 7.3, 8.2;  768 x 768, k = 384 (36) 8.1, 8.6 / 8.8, 9.0;  1024 x 1024, k = 512 (64) 8.3, 8.8 /
+// 9.2, 10.4: hence the limit.  From Python, where a launch costs more, 512 x 512 went from 10.0 to 6.7.
+// ---------------------------------------------------------------------------------------------
+constexpr int SMALL_PER_WAVE = 4, SMALL_TILES = FEW_WAVES * SMALL_PER_WAVE;
+
+// The sums of a wavefront's tiles (tiles[0 .. hi - lo) of the span, row tile major) into red[row tile].
+__device__ __forceinline__ void small_stage(const FewStream& st, const unsigned char* planes, int tile_block, int ncols, int n_ct, int* red) {
+    const int g = st.lane >> 4, c = st.lane & 15;
+    const unsigned char* xp = planes + (c < ncols ? c : c % ncols) * DBF_TILE_COLS + 16 * g;
+    int rt = st.lo / n_ct, ct = st.lo - rt * n_ct;
+    v4i acc[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) acc[s] = (v4i){0, 0, 0, 0};
+    auto flush = [&]() {
+        if (c < ncols) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) atomicAdd(&red[(rt * ncols + c) * FEW_RB + 4 * g + 16 * s + i], acc[s][i]);
+        }
+#pragma unroll
+        for (int s = 0; s < 8; ++s) acc[s] = (v4i){0, 0, 0, 0};
+    };
+#pragma unroll
+    for (int j = 0; j < SMALL_PER_WAVE; ++j) {
+        if (st.lo + j >= st.hi) break;
+        const v4i xv = *reinterpret_cast<const v4i*>(xp + ct * tile_block);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const unsigned msk = 0x01010101u << s;
+            const v4i a = {(int)(st.tl[j].x & msk), (int)(st.tl[j].y & msk), (int)(st.tl[j].z & msk), (int)(st.tl[j].w & msk)};
+            acc[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, xv, acc[s], 0, 0, 0);
+        }
+        if (++ct == n_ct) {
+            flush();
+            ct = 0;
+            ++rt;
+        }
+    }
+    if (ct != 0 && st.hi > st.lo) flush();
+}
+
+__global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_small_layer_kernel(
+    const DbfStage* __restrict__ stages_b, const DbfStage* __restrict__ stages_a, const uint16_t* __restrict__ x_base,
+    uint16_t* __restrict__ y_base, int T, int group, int planes_bytes, int red_ints) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const DbfStage sb = stages_b[blockIdx.x], sa = stages_a[blockIdx.x];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t0 = blockIdx.y * group, nb = min(group, T - t0), ncols = 2 * nb;
+    const int tile_block = few_tile_block(ncols);
+    FewMisc* m = reinterpret_cast<FewMisc*>(smem);                 // one per stage
+    unsigned char* planes = smem + 2 * sizeof(FewMisc);
+    int* red_b = reinterpret_cast<int*>(planes + planes_bytes);    // [row tiles of both stages][ncols][FEW_RB]
+    int* red_a = red_b + sb.n_rt * ncols * FEW_RB;
+    float* t = reinterpret_cast<float*>(red_b + red_ints);         // [nb][rows of B, whole row tiles]
+    const int t_len = sb.n_rt * DBF_TILE_ROWS;
+    const FewShare sh = few_share(nb, w);
+    constexpr int H = 2;
+
+    InputX inx;
+    inx.x = x_base + sb.x_off * T + (size_t)t0 * sb.cols;  inx.b = sb.in_scale;  inx.cols = sb.cols;
+    inx.fast = (sb.cols & 7) == 0 && (reinterpret_cast<uintptr_t>(inx.x) & 15) == 0;
+    FewRaw raw[H];
+    const int nvec_b = 8 * sb.n_ct, nvec_a = 8 * sa.n_ct;
+    {
+        const int bi = min(sh.row, nb - 1);
+#pragma unroll
+        for (int i = 0; i < H; ++i) inx.load(bi, min(lane + 64 * (sh.part + sh.parts * i), nvec_b - 1), raw[i]);
+    }
+    FewStream st, st2;
+    const int n = sb.n_rt * sb.n_ct, n2 = sa.n_rt * sa.n_ct;
+    __builtin_amdgcn_sched_barrier(0);
+    st.start(sb.bits, n, n * w / FEW_WAVES, n * (w + 1) / FEW_WAVES, lane);
+    st2.start(sa.bits, n2, n2 * w / FEW_WAVES, n2 * (w + 1) / FEW_WAVES, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int i = tid; i < red_ints; i += FEW_THREADS) red_b[i] = 0;
+    if (tid < 2 * DBF_MAX_BATCH) m[tid / DBF_MAX_BATCH].sigma[tid % DBF_MAX_BATCH] = 0;
+    float u[H][8];
+    few_max(inx, sh, nb, nvec_b, true, raw, u, m, lane);
+    __syncthreads();
+    few_round(inx, sh, nb, nvec_b, 0, nvec_b, true, u, m, planes, tile_block, lane);
+    __syncthreads();
+    small_stage(st, planes, tile_block, ncols, sb.n_ct, red_b);
+    __syncthreads();
+    for (int e = tid; e < nb * t_len; e += FEW_THREADS) {
+        const int bi = e / t_len, row = e - bi * t_len;
+        t[e] = (float)few_total(red_b + (row >> 7) * ncols * FEW_RB, bi, row & 127, m->sigma[bi]) * m->scale[bi] *
+               (float)__builtin_bit_cast(_Float16, sb.row_scale[row]);
+    }
+    __syncthreads();
+    const InputT inp = {t, t_len};
+    {
+        const int bi = min(sh.row, nb - 1);
+#pragma unroll
+        for (int i = 0; i < H; ++i) inp.load(bi, min(lane + 64 * (sh.part + sh.parts * i), nvec_a - 1), raw[i]);
+    }
+    ++m;
+    few_max(inp, sh, nb, nvec_a, true, raw, u, m, lane);
+    __syncthreads();
+    few_round(inp, sh, nb, nvec_a, 0, nvec_a, true, u, m, planes, tile_block, lane);
+    __syncthreads();
+    small_stage(st2, planes, tile_block, ncols, sa.n_ct, red_a);
+    __syncthreads();
+    const int rows = sa.rows, all = sa.n_rt * DBF_TILE_ROWS;
+    uint16_t* y = y_base + sa.y_off * T + (size_t)t0 * rows;
+    for (int e = tid; e < nb * all; e += FEW_THREADS) {
+        const int bi = e / all, row = e - bi * all;
+        if (row >= rows) continue;
+        const float val = (float)few_total(red_a + (row >> 7) * ncols * FEW_RB, bi, row & 127, m->sigma[bi]) * m->scale[bi] *
+                          (float)__builtin_bit_cast(_Float16, sa.row_scale[row]);
+        y[(size_t)bi * rows + row] = few_half(val);
+    }
+}
+
 constexpr int FEW_MAX_WGS = 256;     // compute units
 constexpr int FEW_LDS = 156 * 1024;  // (its registers give a workgroup the compute unit to itself)
 
@@ -452,7 +572,8 @@ inline int few_cols(const DbfPlan& p, bool stage_a) { return dbf_col_tiles(stage
 // More than 64 KiB of LDS per workgroup has to be asked for, once per process (see dbf_mfma_prepare).
 hipError_t dbf_few_prepare() {
     static const hipError_t raised = [] {
-        const hipError_t e[] = {raise_lds<false, false, 2>(), raise_lds<false, true, 2>(), raise_lds<true, false, 2>(), raise_lds<true, true, 2>(),
+        const hipError_t e[] = {hipFuncSetAttribute(reinterpret_cast<const void*>(&dbf_small_layer_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, FEW_LDS),
+                                raise_lds<false, false, 2>(), raise_lds<false, true, 2>(), raise_lds<true, false, 2>(), raise_lds<true, true, 2>(),
                                 raise_lds<false, false, 4>(), raise_lds<false, true, 4>(), raise_lds<true, false, 4>(), raise_lds<true, true, 4>(),
                                 raise_lds<false, false, 8>(), raise_lds<false, true, 8>(), raise_lds<true, false, 8>(), raise_lds<true, true, 8>()};
         for (hipError_t x : e)
@@ -519,5 +640,33 @@ hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y
         DBF_FEW(false, false);
     }
 #undef DBF_FEW
+    return hipGetLastError();
+}
+
+// LDS of a workgroup of the small-layer kernel for nb tokens.
+static size_t small_lds(const DbfPlan& p, int nb, int* planes, int* red_ints) {
+    const int ct_b = dbf_col_tiles(p.max_cols_B), ct_a = dbf_col_tiles(p.max_cols_A), rt_b = dbf_row_tiles(p.max_cols_A);  // (rows of B: columns of A)
+    *planes = (ct_b > ct_a ? ct_b : ct_a) * few_tile_block(2 * nb);
+    *red_ints = (rt_b + p.max_rt_A) * 2 * nb * FEW_RB;
+    return 2 * sizeof(FewMisc) + (size_t)*planes + 4 * (size_t)*red_ints + 4 * (size_t)nb * rt_b * DBF_TILE_ROWS;
+}
+static int small_group(int T) { return T < 2 ? 1 : 2; }
+
+bool dbf_small_layer_takes(const DbfPlan& p, int T) {
+    const int nb = small_group(T);
+    if (p.max_stage_tiles > SMALL_TILES || (long long)p.n_layers * ((T + nb - 1) / nb) > FEW_MAX_WGS) return false;
+    int planes, red;
+    const int longest = p.max_cols_B > p.max_cols_A ? p.max_cols_B : p.max_cols_A;
+    return dbf_col_tiles(longest) * 8 <= 2 * 64 * few_parts(nb) && small_lds(p, nb, &planes, &red) <= (size_t)FEW_LDS;
+}
+
+hipError_t dbf_launch_small_layers(const DbfPlan& p, const void* x, void* y, int T, hipStream_t stream) {
+    const hipError_t raised = dbf_few_prepare();
+    if (raised != hipSuccess) return raised;
+    const int group = small_group(T);
+    int planes, red;
+    const size_t lds = small_lds(p, group, &planes, &red);
+    hipLaunchKernelGGL(dbf_small_layer_kernel, dim3(p.n_layers, (T + group - 1) / group), dim3(FEW_THREADS), lds, stream, p.d_stagesB, p.d_stagesA,
+                       static_cast<const uint16_t*>(x), static_cast<uint16_t*>(y), T, group, planes, red);
     return hipGetLastError();
 }

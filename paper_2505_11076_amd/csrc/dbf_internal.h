@@ -115,6 +115,8 @@ struct DbfPlan {
     unsigned long long* d_sync;
     int span;                   // row tiles per item in d_items_n
     int max_cols_B, max_cols_A;
+    int max_rt_A;               // row tiles of the largest A stage
+    long long max_stage_tiles;  // sign tiles of the largest stage of a layer
     DbfStage h_stage_B, h_stage_A;  // the stages of the first layer (launches of a layer alone take them as arguments)
     int* d_few_acc;             // plans of at most DBF_FEW_MAX_ROW_TILES row tiles per stage: zeroed sums and counters of column pieces
                                 // (dbf_gemv_few.hip), returned to zero by every launch; NULL otherwise

@@ -48,6 +48,9 @@ hipError_t dbf_mfma_prepare();
 // t_over: the middle activations [T][t_stride], or NULL for the layers' own (T <= DBF_MAX_BATCH).
 bool dbf_few_takes(const DbfPlan& p, bool stage_a, int T);
 hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y, float* t_over, int T, hipStream_t stream);
+// Both stages of small layers in one launch, a workgroup per layer and pair of tokens; dbf_small_layer_takes: whether the plan's layers are.
+bool dbf_small_layer_takes(const DbfPlan& p, int T);
+hipError_t dbf_launch_small_layers(const DbfPlan& p, const void* x, void* y, int T, hipStream_t stream);
 // One-time, per-process set-up of those kernels (LDS limits); cheap to call again.
 hipError_t dbf_few_prepare();
 

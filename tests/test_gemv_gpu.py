@@ -817,12 +817,12 @@ def test_one_launch_calls_may_switch_between_the_lists_of_a_plan():
             l.close()
 
 
-@pytest.mark.parametrize("shape", [(1, 1, 1), (64, 128, 64), (65, 129, 63), (520, 1000, 300), (1023, 257, 511), (4104, 300, 4160),
+@pytest.mark.parametrize("shape", [(1, 1, 1), (64, 128, 64), (65, 129, 63), (513, 500, 500), (1024, 256, 256), (129, 1024, 250), (520, 1000, 300), (1023, 257, 511), (4104, 300, 4160),
                                    (5184, 130, 5120), (12296, 260, 900), (900, 200, 12300)])
 def test_launches_of_few_workgroups_equal_the_two_launch_kind_bit_for_bit(shape):
     """The default kind on a layer alone and on a group of three: workgroups that round their own input, with the values held in
     registers (2, 4 or 8 vectors per lane) or read twice, one row tile whole or in column pieces (80 column tiles and more), in one
-    chunk of LDS or several, 2 to 8 batch rows per workgroup.  Every batch, an x that can be read in 16-byte pieces
+    chunk of LDS or several, 2 to 8 batch rows per workgroup; layers of up to 32 tiles a stage in one launch.  Every batch, an x that can be read in 16-byte pieces
     and one that cannot, two calls in a row (the pieces' sums must be left at zero).  Integer sums: no tolerance."""
     n_in, n_out, k = shape
     Ls = [I.make_layer(n_in, n_out, k, seed=I.seed_for(6, 700 + i + k)) for i in range(3)]
