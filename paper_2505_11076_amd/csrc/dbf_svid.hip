@@ -9,13 +9,14 @@
 //
 // Everything is bound by reading Z (fp32, rows x cols, row major).  A round needs u = |Z| v before any of
 // v' = |Z|^T u -- but only row by row: the term of row i in v' needs u_i alone, and u_i needs row i alone.  So
-// ONE pass over Z does a whole round (dbf_svid_round_kernel): a workgroup of 16 wavefronts holds a batch of whole
-// rows in registers, forms their dots with v, and adds the rows, weighted by those dots, into its partial column
-// sums; a second, small launch sums the partial sums over the workgroups.  Rows too long for that (more than
-// 24576 columns) or not readable in 16-byte pieces, and matrices of fewer than 24 Mi entries (where it is slower),
-// take two passes per round (row dots, column dots) and a reduce launch.  In both forms the normalisations are not passes of their own.  The iterate is kept unnormalised (u_raw = |Z| v, v_raw = |Z|^T u_raw; the length of u
-// cancels in v / ||v||), the column reduction leaves the squared length of v_raw as one partial sum per
-// workgroup, and the next row pass scales by 1 / ||v_raw|| on the fly; the last kernel forms
+// ONE pass over Z does a whole round (dbf_svid_round_kernel): a workgroup holds batches of whole rows in registers,
+// forms their dots with v, and adds the rows, weighted by those dots, into its partial column sums; a second, small
+// launch sums the partial sums over the workgroups.  Rows of up to 4096 columns are dealt to workgroups in groups of the
+// eight that share a byte of the sign tiles, so that the first pass writes the signs as well.  Rows too long for one pass (more than
+// 24576 columns, 12288 where they cannot be read in 16-byte pieces) take two passes per round (row dots, column dots) and the same
+// reduce launch.  In both forms the normalisations are not passes of their own.  The iterate is kept unnormalised (u_raw =
+// |Z| v, v_raw = |Z|^T u_raw; the length of u cancels in v / ||v||), the column reduction leaves the squared length of v_raw
+// as one partial sum per workgroup, and the next row pass scales by 1 / ||v_raw|| on the fly; the last kernel forms
 // m = v_raw / ||v_raw|| and a = sigma u = u_raw ||v_raw|| / ||u_raw||^2.  All reductions have a fixed
 // order, so the result does not depend on scheduling:
 //   row dots     one wavefront per row, 16-byte loads, butterfly reduction;
@@ -32,12 +33,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int COL_CHUNK_ROWS = 64;   // rows per partial sum of the column pass
 constexpr int COL_BLOCK = 256;       // columns per workgroup of the column pass
-constexpr int ROUND_THREADS = 1024;  // workgroup of the one-pass round
-// Matrices below this many entries take the two-pass round: a workgroup of the one-pass round then holds too few
-// rows to keep its loads ahead of its barriers.  Measured, 8 rounds, two passes / one pass in ms: 4096 x 4096 0.254 /
-// 0.299, 2048 x 4096 0.183 / 0.221, 6144 x 4096 0.361 / 0.336, 11008 x 4096 0.587 / 0.452, 4096 x 11008 0.507 / 0.410,
-// 16384 x 4096 0.866 / 0.578, 8192 x 8192 0.933 / 0.551.
-constexpr size_t ROUND_MIN_ENTRIES = (size_t)24 << 20;
+constexpr int ROUND_WGS = 256;       // workgroups of the one-pass round: one per compute unit
 
 __device__ inline float wave_sum_f(float v) {
 #pragma unroll
@@ -88,37 +84,72 @@ __global__ __launch_bounds__(256) void dbf_svid_row_dots_kernel(const float* __r
     if (lane == 0) u[row] = s * inv;
 }
 
-// One round in one pass.  Workgroup = 1024 threads = 16 wavefronts, one per compute unit (512-thread workgroups,
-// two or three per compute unit, were slower); it takes `rows_per_wg` consecutive rows, RB at a time.  Thread t
-// holds, of every row of the batch, the CPL float4s at columns 4 t + 4096 k (k < CPL), so a wavefront's load of a
-// row segment is 1 KiB contiguous.  Per batch: the next batch's loads are issued first (register double buffer:
-// the barrier below puts all 16 wavefronts in step, so nothing else hides the latency), then every wavefront
-// forms its part of the RB row dots (register-to-register reduction), leaves it in LDS, and after ONE barrier
-// (two LDS buffers alternate) every thread sums the 16 parts in wavefront order, scales by 1 / ||v_raw|| -> u_raw
-// of the RB rows (threads 0 .. RB-1 store them), and adds |z| u_raw of its columns into its CPL float4
-// accumulators.  At the end the accumulators are the workgroup's partial column sums: partial[workgroup][column].
-// FIRST: v = 1 / sqrt(cols) everywhere, v_raw is not read.  All sums have a fixed order.
-template <int CPL, bool FIRST>
-__global__ __launch_bounds__(ROUND_THREADS) void dbf_svid_round_kernel(const float* __restrict__ Z, int rows, int cols,
+// One round in one pass, a workgroup of W wavefronts per compute unit.  Rows come in groups of eight, group 16 q + r being the rows
+// 128 q + 16 s + r, s = 0 .. 7 (one byte column of a sign tile); a workgroup has `groups_per_wg` consecutive groups and takes RB rows
+// of one at a time.  Thread t holds, of every row of the batch, the CPL float4s at columns 4 t + 256 W k (k < CPL), so a
+// wavefront's load of a row segment is 1 KiB contiguous.  Per batch: the next batch's loads are issued first (register double
+// buffer), then every wavefront forms its part of the RB row dots (register-to-register reduction) and leaves it in LDS; the
+// parts are summed by RB rows of 16 lanes, scaled by 1 / ||v_raw|| -> u_raw, and every thread adds |z| u_raw of its columns
+// into its CPL float4 accumulators.  At the end the accumulators are the workgroup's partial column sums: partial[workgroup][column].
+// FIRST: v = 1 / sqrt(cols) everywhere, v_raw is not read; and with CPL == 1 the signs are written.  All sums have a fixed order.
+// What bounds it: at 4096 x 4096 reading Z from the last-level cache, 67 MB in two batches per workgroup.
+template <int W, int CPL, bool FIRST, bool VEC>
+__global__ __launch_bounds__(64 * W) void dbf_svid_round_kernel(const float* __restrict__ Z, int rows, int cols,
                                                               const float* __restrict__ v,
                                                               const float* __restrict__ ss_part, int n_ss,
                                                               float* __restrict__ u, float* __restrict__ partial,
-                                                              int rows_per_wg) {
-    constexpr int RB = CPL == 1 ? 8 : CPL == 2 ? 4 : CPL <= 4 ? 2 : 1;  // rows per batch: about 32 registers per buffer
-    __shared__ float dots[2][ROUND_THREADS / 64][RB];
+                                                              int groups_per_wg, int n_groups, uint8_t* __restrict__ bits, int n_ct) {
+    constexpr int RB = CPL == 1 ? 8 : CPL == 2 ? 4 : CPL == 3 ? 2 : 1;  // rows per batch: about 32 registers per buffer
+    constexpr int NB = 8 / RB;                                         // batches per group
+    constexpr bool SIGNS = FIRST && CPL == 1 && VEC;
+    __shared__ float dots[2][RB][16];
+    __shared__ __align__(16) float us[2][RB];
     __shared__ float inv_s;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int row0 = blockIdx.x * rows_per_wg;
-    const int row_end = min(rows, row0 + rows_per_wg);
+    const int b_lo = blockIdx.x * groups_per_wg * NB, b_hi = min(n_groups, (int)(blockIdx.x + 1) * groups_per_wg) * NB;
     v4f vv[CPL], acc[CPL];
-    bool live[CPL];
+    // element e of the thread's k-th float4: column 4 tid + 256 W k + e, or, where rows cannot be read in 16-byte pieces, tid + 64 W (4 k + e)
+    auto col_of = [&](int k, int e) { return VEC ? 4 * tid + 256 * W * k + e : tid + 64 * W * (4 * k + e); };
+    auto live = [&](int k, int e) { return col_of(k, VEC ? 0 : e) < cols; };   // (VEC: cols is a multiple of 4)
 #pragma unroll
     for (int k = 0; k < CPL; ++k) {
-        const int col = 4 * tid + 4 * ROUND_THREADS * k;
-        live[k] = col < cols;  // (cols is a multiple of 4)
-        vv[k] = (!FIRST && live[k]) ? *reinterpret_cast<const v4f*>(v + col) : (v4f){0.f, 0.f, 0.f, 0.f};
+        vv[k] = (v4f){0.f, 0.f, 0.f, 0.f};
+        if (!FIRST && VEC && live(k, 0)) vv[k] = *reinterpret_cast<const v4f*>(v + col_of(k, 0));
+        if (!FIRST && !VEC) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) vv[k][e] = live(k, e) ? v[col_of(k, e)] : 0.f;
+        }
         acc[k] = (v4f){0.f, 0.f, 0.f, 0.f};
     }
+    // row i of batch b
+    auto row_of = [&](int b, int i) {
+        const int g = b / NB;
+        return 128 * (g >> 4) + 16 * (RB * (b % NB) + i) + (g & 15);
+    };
+    // (no branch around a load: rows beyond the matrix are read as its last row and get weight zero below,
+    //  columns beyond the matrix are read as the row's first and get v = 0 / are masked, so that all loads of a
+    //  batch are in flight together)
+    auto load_batch = [&](v4f (&z)[RB][CPL], int b) {
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const int row = min(row_of(b, r), rows - 1);
+#pragma unroll
+            for (int k = 0; k < CPL; ++k) {
+                const float* zr = Z + (size_t)row * cols;
+                if (VEC) {
+                    z[r][k] = *reinterpret_cast<const v4f*>(zr + (live(k, 0) ? col_of(k, 0) : 0));
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) z[r][k][e] = zr[live(k, e) ? col_of(k, e) : 0];
+                }
+            }
+        }
+    };
+    auto abs4 = [](v4f a) { return (v4f){fabsf(a.x), fabsf(a.y), fabsf(a.z), fabsf(a.w)}; };
+    v4f za[RB][CPL], zb[RB][CPL];
+    load_batch(za, b_lo);
+    load_batch(zb, min(b_lo + 1, b_hi - 1));
+    if (tid < 2 * RB * 16) (&dots[0][0][0])[tid] = 0.f;   // (the parts of wavefronts that a narrower workgroup does not have)
     if (w == 0) {
         float inv;
         if (FIRST) {
@@ -129,24 +160,10 @@ __global__ __launch_bounds__(ROUND_THREADS) void dbf_svid_round_kernel(const flo
         }
         if (lane == 0) inv_s = inv;
     }
-    // (no branch around a load: rows beyond the workgroup's are read as its last row and get weight zero below,
-    //  columns beyond the matrix are read as the row's first and get v = 0 / are masked, so that all loads of a
-    //  batch are in flight together)
-    auto load_batch = [&](v4f (&z)[RB][CPL], int r0) {
-#pragma unroll
-        for (int r = 0; r < RB; ++r) {
-            const int row = min(r0 + r, row_end - 1);
-#pragma unroll
-            for (int k = 0; k < CPL; ++k)
-                z[r][k] = *reinterpret_cast<const v4f*>(Z + (size_t)row * cols + (live[k] ? 4 * tid + 4 * ROUND_THREADS * k : 0));
-        }
-    };
-    auto abs4 = [](v4f a) { return (v4f){fabsf(a.x), fabsf(a.y), fabsf(a.z), fabsf(a.w)}; };
-    v4f za[RB][CPL], zb[RB][CPL];
-    load_batch(za, row0);
+    __syncthreads();
     int buf = 0;
     // (two batches per trip, so that the two register buffers keep their names)
-    auto process = [&](v4f (&z)[RB][CPL], int r0) {
+    auto process = [&](v4f (&z)[RB][CPL], int b) {
         float part[RB];
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
@@ -154,24 +171,42 @@ __global__ __launch_bounds__(ROUND_THREADS) void dbf_svid_round_kernel(const flo
 #pragma unroll
             for (int k = 0; k < CPL; ++k) {
                 const v4f a = abs4(z[r][k]);
-                if (FIRST) sdot += live[k] ? (a.x + a.y) + (a.z + a.w) : 0.f;
+                if (FIRST) sdot += ((live(k, 0) ? a.x : 0.f) + (live(k, 1) ? a.y : 0.f)) + ((live(k, 2) ? a.z : 0.f) + (live(k, 3) ? a.w : 0.f));
                 else sdot += a.x * vv[k].x + a.y * vv[k].y + a.z * vv[k].z + a.w * vv[k].w;
             }
             part[r] = dbf_wave_sum_f(sdot);
         }
         if (lane == 0) {
 #pragma unroll
-            for (int r = 0; r < RB; ++r) dots[buf][w][r] = part[r];
+            for (int r = 0; r < RB; ++r) dots[buf][r][w] = part[r];
+        }
+        if (SIGNS) {
+            const int g = b, col = 4 * tid;
+            unsigned out = 0;
+#pragma unroll
+            for (int s = 0; s < RB; ++s) {
+                const v4f a = z[s][0];
+                const unsigned four = (unsigned)(a.x >= 0.f) | (unsigned)(a.y >= 0.f) << 8 | (unsigned)(a.z >= 0.f) << 16 | (unsigned)(a.w >= 0.f) << 24;
+                out |= (live(0, 0) && row_of(b, s) < rows) ? four << s : 0u;
+            }
+            if (col < n_ct * DBF_TILE_COLS)
+                *reinterpret_cast<unsigned*>(bits + ((size_t)(g >> 4) * n_ct + (col >> 6)) * DBF_TILE_BYTES + 256 * ((col >> 4) & 3) +
+                                             16 * (g & 15) + (col & 15)) = out;
         }
         __syncthreads();
-        const float inv = inv_s;
+        if (tid < 16 * RB) {
+            const float tot = dbf_row16_sum_f((&dots[buf][0][0])[tid]);
+            if ((tid & 15) == 0) {
+                const int row = row_of(b, tid >> 4);
+                const float ur = row < rows ? tot * inv_s : 0.f;
+                us[buf][tid >> 4] = ur;
+                if (row < rows) u[row] = ur;
+            }
+        }
+        __syncthreads();
 #pragma unroll
         for (int r = 0; r < RB; ++r) {
-            float tot = 0.f;
-#pragma unroll
-            for (int q = 0; q < ROUND_THREADS / 64; ++q) tot += dots[buf][q][r];
-            const float ur = r0 + r < row_end ? tot * inv : 0.f;
-            if (tid == r && r0 + r < row_end) u[r0 + r] = ur;
+            const float ur = us[buf][r];
 #pragma unroll
             for (int k = 0; k < CPL; ++k) {
                 const v4f a = abs4(z[r][k]);
@@ -180,17 +215,25 @@ __global__ __launch_bounds__(ROUND_THREADS) void dbf_svid_round_kernel(const flo
         }
         buf ^= 1;
     };
-    for (int r0 = row0; r0 < row_end; r0 += 2 * RB) {
-        load_batch(zb, r0 + RB);       // (rows beyond the workgroup's read as zeros without touching memory)
-        process(za, r0);
-        if (r0 + RB < row_end) {
-            load_batch(za, r0 + 2 * RB);
-            process(zb, r0 + RB);
+    for (int b = b_lo; b < b_hi; b += 2) {
+        process(za, b);
+        if (b + 2 < b_hi) load_batch(za, b + 2);
+        if (b + 1 < b_hi) {
+            process(zb, b + 1);
+            if (b + 3 < b_hi) load_batch(zb, b + 3);
         }
     }
 #pragma unroll
-    for (int k = 0; k < CPL; ++k)
-        if (live[k]) *reinterpret_cast<v4f*>(partial + (size_t)blockIdx.x * cols + 4 * tid + 4 * ROUND_THREADS * k) = acc[k];
+    for (int k = 0; k < CPL; ++k) {
+        float* out = partial + (size_t)blockIdx.x * cols;
+        if (VEC) {
+            if (live(k, 0)) *reinterpret_cast<v4f*>(out + col_of(k, 0)) = acc[k];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (live(k, e)) out[col_of(k, e)] = acc[k][e];
+        }
+    }
 }
 
 // partial[chunk][j] = sum over the chunk's rows i of |Z[i][j]| u[i]
@@ -234,24 +277,32 @@ __global__ __launch_bounds__(256) void dbf_svid_col_dots_kernel(const float* __r
         partial[(size_t)blockIdx.y * cols + blockIdx.x * COL_BLOCK + c] = ((part[0][c] + part[1][c]) + part[2][c]) + part[3][c];
 }
 
-// v_raw[j] = sum over chunks of partial[chunk][j]: four interleaved running sums (chunks c = 0, 4, 8, ... in the
-// first, and so on), combined as ((s0 + s1) + s2) + s3; and ss_part[workgroup] = sum of v_raw[j]^2 over the
-// workgroup's 64 columns (butterfly order).  Workgroup = 64 columns x the 4 running sums (one wavefront each: a
-// thread's chain of dependent loads is a quarter of the chunks), combined through LDS in that fixed order.
-__global__ __launch_bounds__(256) void dbf_svid_col_reduce_kernel(const float* __restrict__ partial, int chunks, int cols,
+// v_raw[j] = sum over chunks of partial[chunk][j]: sixteen interleaved running sums (chunks c = 0, 16, 32, ... in the
+// first, and so on), added up in order; and ss_part[workgroup] = sum of v_raw[j]^2 over the workgroup's 64 columns (butterfly
+// order).  Workgroup = 64 columns x the 16 running sums (one wavefront each, sixteen loads in flight: up to 256 chunks are one memory
+// round trip; with four sums and a load at a time 64 chunks took 6.6 us).
+constexpr int REDUCE_SUMS = 16;
+__global__ __launch_bounds__(64 * REDUCE_SUMS) void dbf_svid_col_reduce_kernel(const float* __restrict__ partial, int chunks, int cols,
                                                                float* __restrict__ v, float* __restrict__ ss_part) {
-    __shared__ float part[4][64];
+    __shared__ float part[REDUCE_SUMS][64];
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int j = blockIdx.x * 64 + lane;
+    const int j = blockIdx.x * 64 + lane, jc = min(j, cols - 1);
     float s = 0.f;
-    if (j < cols)
-        for (int c = q; c < chunks; c += 4) s += partial[(size_t)c * cols + j];
+    for (int c0 = q; c0 < chunks; c0 += 16 * REDUCE_SUMS) {
+        float p[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) p[i] = partial[(size_t)min(c0 + REDUCE_SUMS * i, chunks - 1) * cols + jc];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s += c0 + REDUCE_SUMS * i < chunks ? p[i] : 0.f;
+    }
     part[q][lane] = s;
     __syncthreads();
     if (q == 0) {
-        const float vj = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
+        float vj = part[0][lane];
+#pragma unroll
+        for (int i = 1; i < REDUCE_SUMS; ++i) vj += part[i][lane];
         if (j < cols) v[j] = vj;
-        const float ss = wave_sum_f(vj * vj);
+        const float ss = wave_sum_f(j < cols ? vj * vj : 0.f);
         if (lane == 0) ss_part[blockIdx.x] = ss;
     }
 }
@@ -308,20 +359,24 @@ __global__ __launch_bounds__(256) void dbf_svid_signs_kernel(const float* __rest
 }
 
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
-// Rows per workgroup of the one-pass round: one workgroup per compute unit (256 in all), at least 8 rows each.
-inline int round_rows_per_wg(int rows) {
-    const int per = (rows + 255) / 256;
-    return per < 8 ? 8 : per;
-}
-template <int CPL>
-void launch_round(bool first, int n_wg, hipStream_t st, const float* Z, int rows, int cols, const float* v,
-                  const float* ss_part, int n_ss, float* u, float* partial, int rows_per_wg) {
+// Groups of eight rows per workgroup of the one-pass round.
+inline int round_groups_per_wg(int rows) { return (16 * dbf_row_tiles(rows) + ROUND_WGS - 1) / ROUND_WGS; }
+struct RoundArgs {
+    const float *Z, *v, *ss_part;
+    float *u, *partial;
+    uint8_t* bits;
+    int rows, cols, n_ss, n_ct;
+};
+template <int W, int CPL, bool VEC>
+int launch_round(bool first, hipStream_t st, const RoundArgs& a) {
+    const int per = round_groups_per_wg(a.rows), n_groups = 16 * dbf_row_tiles(a.rows), n_wg = (n_groups + per - 1) / per;
     if (first)
-        hipLaunchKernelGGL((dbf_svid_round_kernel<CPL, true>), dim3(n_wg), dim3(ROUND_THREADS), 0, st, Z, rows, cols, v, ss_part, n_ss,
-                           u, partial, rows_per_wg);
+        hipLaunchKernelGGL((dbf_svid_round_kernel<W, CPL, true, VEC>), dim3(n_wg), dim3(64 * W), 0, st, a.Z, a.rows, a.cols, a.v, a.ss_part,
+                           a.n_ss, a.u, a.partial, per, n_groups, a.bits, a.n_ct);
     else
-        hipLaunchKernelGGL((dbf_svid_round_kernel<CPL, false>), dim3(n_wg), dim3(ROUND_THREADS), 0, st, Z, rows, cols, v, ss_part, n_ss,
-                           u, partial, rows_per_wg);
+        hipLaunchKernelGGL((dbf_svid_round_kernel<W, CPL, false, VEC>), dim3(n_wg), dim3(64 * W), 0, st, a.Z, a.rows, a.cols, a.v, a.ss_part,
+                           a.n_ss, a.u, a.partial, per, n_groups, a.bits, a.n_ct);
+    return n_wg;
 }
 struct SvidWorkspace {
     size_t u, v, partial, scalars, total;
@@ -329,7 +384,7 @@ struct SvidWorkspace {
 inline SvidWorkspace svid_workspace(int rows, int cols) {
     SvidWorkspace w;
     size_t chunks = ((size_t)rows + COL_CHUNK_ROWS - 1) / COL_CHUNK_ROWS;
-    const size_t n_wg = ((size_t)rows + round_rows_per_wg(rows) - 1) / round_rows_per_wg(rows);
+    const size_t per = round_groups_per_wg(rows), n_wg = (16 * (size_t)dbf_row_tiles(rows) + per - 1) / per;
     if (n_wg > chunks) chunks = n_wg;  // partial sums: one row per 64-row chunk or per workgroup of the one-pass round
     size_t off = 0;
     w.u = off;        off = up256(off + 4 * (size_t)rows);
@@ -370,21 +425,37 @@ extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* 
     const int n_rt = dbf_row_tiles(rows), n_ct = dbf_col_tiles(cols);
     const int n_ss = (cols + 63) / 64;
 
-    hipLaunchKernelGGL(dbf_svid_signs_kernel, dim3(n_ct, n_rt), dim3(256), 0, st, Z, rows, cols, n_ct,
-                       static_cast<uint8_t*>(bits_dev));
-    const int cpl = (cols + 4 * ROUND_THREADS - 1) / (4 * ROUND_THREADS);  // float4s per thread and row in the one-pass round
-    const int rpw = round_rows_per_wg(rows), n_wg = (rows + rpw - 1) / rpw;
+    // One pass per round wherever rows can be held: up to 24576 columns in 16-byte pieces, 12288 in single values.  8 rounds, us, two
+    // passes / one: 4096 x 4096 247 / 154, 2048 x 4096 161 / 93, 8192 x 8192 (one pass before: 548) 472.
+    const int cpl = (cols + 4095) / 4096;  // float4s per thread and row of a workgroup of 1024
+    const bool one_pass = cpl <= (vec_ok ? 6 : 3);
+    if (!(one_pass && cpl == 1 && vec_ok))   // (else the first pass writes the signs)
+        hipLaunchKernelGGL(dbf_svid_signs_kernel, dim3(n_ct, n_rt), dim3(256), 0, st, Z, rows, cols, n_ct,
+                           static_cast<uint8_t*>(bits_dev));
+    const RoundArgs ra = {Z, v, ss_part, u, partial, static_cast<uint8_t*>(bits_dev), rows, cols, n_ss, n_ct};
     for (int it = 0; it < iters; ++it) {
-        if (vec_ok && cpl <= 6 && (size_t)rows * cols >= ROUND_MIN_ENTRIES) {  // (7 float4s per thread and row spill)
-            switch (cpl) {
-                case 1: launch_round<1>(it == 0, n_wg, st, Z, rows, cols, v, ss_part, n_ss, u, partial, rpw); break;
-                case 2: launch_round<2>(it == 0, n_wg, st, Z, rows, cols, v, ss_part, n_ss, u, partial, rpw); break;
-                case 3: launch_round<3>(it == 0, n_wg, st, Z, rows, cols, v, ss_part, n_ss, u, partial, rpw); break;
-                case 4: launch_round<4>(it == 0, n_wg, st, Z, rows, cols, v, ss_part, n_ss, u, partial, rpw); break;
-                case 5: launch_round<5>(it == 0, n_wg, st, Z, rows, cols, v, ss_part, n_ss, u, partial, rpw); break;
-                default: launch_round<6>(it == 0, n_wg, st, Z, rows, cols, v, ss_part, n_ss, u, partial, rpw); break;
+        if (one_pass) {
+            int n_wg;
+            const bool first = it == 0;
+            if (vec_ok) {
+                switch (cpl) {
+                    case 1: n_wg = cols <= 1024 ? launch_round<4, 1, true>(first, st, ra) : cols <= 2048 ? launch_round<8, 1, true>(first, st, ra)
+                                                                                          : launch_round<16, 1, true>(first, st, ra); break;
+                    case 2: n_wg = launch_round<16, 2, true>(first, st, ra); break;
+                    case 3: n_wg = launch_round<16, 3, true>(first, st, ra); break;
+                    case 4: n_wg = launch_round<16, 4, true>(first, st, ra); break;
+                    case 5: n_wg = launch_round<16, 5, true>(first, st, ra); break;
+                    default: n_wg = launch_round<16, 6, true>(first, st, ra); break;
+                }
+            } else {
+                switch (cpl) {
+                    case 1: n_wg = cols <= 1024 ? launch_round<4, 1, false>(first, st, ra) : cols <= 2048 ? launch_round<8, 1, false>(first, st, ra)
+                                                                                           : launch_round<16, 1, false>(first, st, ra); break;
+                    case 2: n_wg = launch_round<16, 2, false>(first, st, ra); break;
+                    default: n_wg = launch_round<16, 3, false>(first, st, ra); break;
+                }
             }
-            hipLaunchKernelGGL(dbf_svid_col_reduce_kernel, dim3(n_ss), dim3(256), 0, st, partial, n_wg, cols, v, ss_part);
+            hipLaunchKernelGGL(dbf_svid_col_reduce_kernel, dim3(n_ss), dim3(64 * REDUCE_SUMS), 0, st, partial, n_wg, cols, v, ss_part);
             continue;
         }
         if (it == 0)
@@ -395,7 +466,7 @@ extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* 
                                ss_part, n_ss, u, vec_ok);
         hipLaunchKernelGGL(dbf_svid_col_dots_kernel, dim3((cols + COL_BLOCK - 1) / COL_BLOCK, chunks), dim3(256), 0, st,
                            Z, rows, cols, u, partial);
-        hipLaunchKernelGGL(dbf_svid_col_reduce_kernel, dim3(n_ss), dim3(256), 0, st, partial, chunks, cols, v, ss_part);
+        hipLaunchKernelGGL(dbf_svid_col_reduce_kernel, dim3(n_ss), dim3(64 * REDUCE_SUMS), 0, st, partial, chunks, cols, v, ss_part);
     }
     const int longest = rows > cols ? rows : cols;
     hipLaunchKernelGGL(dbf_svid_finish_kernel, dim3((longest + 255) / 256), dim3(256), 0, st, u, rows, ss_part, n_ss, v,

@@ -83,3 +83,19 @@ def test_svid_argument_errors():
         bad[pos] = val
         with pytest.raises(B.DbfError):
             B.dbf_svid(*bad)
+
+
+@pytest.mark.parametrize("rows,cols", [(5, 7), (17, 1020), (129, 1023), (128, 1028), (255, 2047), (4200, 2052), (2049, 4095), (257, 4097), (130, 8188),
+                                       (131, 8194), (70, 12285), (66, 12290), (40, 16380), (33, 20484)])
+def test_svid_one_pass_rounds_at_the_edges_of_their_row_lengths(rows, cols):
+    """A round in one pass over the matrix: 4, 8 and 16 wavefronts per workgroup, 1 to 6 float4s per thread and row, rows that can be read in
+    16-byte pieces and rows that cannot (12285 columns are the last few of those), groups of rows that hang over the end, several
+    groups per workgroup.  Tolerance: as above."""
+    Z = I.make_svid_matrix(rows, cols, I.seed_for(8, 40 + rows + cols))
+    for iters in (1, 3):
+        G.say("start svid %dx%d iters=%d" % (rows, cols, iters))
+        S, a_ref, m_ref = O.svid(Z.astype(np.float64), iters)
+        a, m, words = _run(Z, iters)
+        assert np.array_equal(words, O.pack_signs(S)), "sign bits differ"
+        assert np.max(np.abs(a - a_ref)) <= TOL * np.max(np.abs(a_ref))
+        assert np.max(np.abs(m - m_ref)) <= TOL * np.max(np.abs(m_ref))
