@@ -6,6 +6,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "dbf_kernels.h"
@@ -225,14 +226,25 @@ void free_plan(DbfPlan& p) {
     p.dev_block = nullptr;
 }
 
-// Builds and uploads the launch tables for `n` layers whose stages (with their x/y offsets
-// already set) are given in sB / sA.
-// few_acc: zeroed device memory for DbfPlan::d_few_acc (few_acc_bytes of it), or NULL: the plan then holds its own.
-int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA, const std::vector<int>& span_b,
-               const std::vector<int>& span_a, int* few_acc, DbfPlan* p) {
-    const int n = (int)sB.size();
+// A launch plan before its memory is known: the tables as they will be uploaded, and how much zeroed memory goes with them.  Stage pointers
+// may still name a place in a block that is allocated together with the plan (a layer's own); place_plan moves them there.
+struct PlanDraft {
+    DbfPlan p;
+    std::vector<DbfStage> sB, sA;
     std::vector<DbfWorkItem> wB1, wA1;
-    std::vector<DbfItem> items_n, items_1;
+    std::vector<DbfItem> items_n, items_1, items_s, items_p;
+    size_t o_sA, o_wB, o_wA, o_in, o_i1, o_is, o_ip, tables_bytes;   // offsets in the tables (stages of B first)
+    size_t o_ac, o_cn, o_few, zero_bytes;                            // offsets in the zeroed memory (d_sync first)
+};
+
+void draft_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA, const std::vector<int>& span_b, const std::vector<int>& span_a,
+                PlanDraft* draft) {
+    DbfPlan* p = &draft->p;
+    draft->sB = sB;
+    draft->sA = sA;
+    std::vector<DbfWorkItem>&wB1 = draft->wB1, &wA1 = draft->wA1;
+    std::vector<DbfItem>&items_n = draft->items_n, &items_1 = draft->items_1, &items_s = draft->items_s, &items_p = draft->items_p;
+    const int n = (int)sB.size();
     int nBn = 0, nB1 = 0;
     std::memset(p, 0, sizeof(*p));
     for (int i = 0; i < n; ++i) {
@@ -299,7 +311,6 @@ int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA,
         for (int x : v) max_span = x > max_span ? x : max_span;
         return v;
     };
-    std::vector<DbfItem> items_s;
     phase = 0;
     for (int i = 0; i < n; ++i) append_items(items_s, sB[i], i, false, 0, shared_pattern_for(span_b, sB[i], tiles_B), &phase);
     const int nBs = (int)items_s.size();
@@ -378,23 +389,15 @@ int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA,
     const size_t cnt_ints = cut ? (size_t)(rtB + rtA) * DBF_PIECE_CNT_STRIDE : 0;
 
     size_t off = 0;
-    const size_t o_sB = off;  off = align_up(off + sizeof(DbfStage) * n, 256);
-    const size_t o_sA = off;  off = align_up(off + sizeof(DbfStage) * n, 256);
-    const size_t o_wB = off;  off = align_up(off + sizeof(DbfWorkItem) * wB1.size(), 256);
-    const size_t o_wA = off;  off = align_up(off + sizeof(DbfWorkItem) * wA1.size(), 256);
-    const size_t o_in = off;  off = align_up(off + sizeof(DbfItem) * items_n.size(), 256);
-    const size_t o_i1 = off;  off = align_up(off + sizeof(DbfItem) * items_1.size(), 256);
-    const size_t o_is = off;  off = align_up(off + sizeof(DbfItem) * items_s.size(), 256);
-    const size_t o_sy = off;  off = align_up(off + sizeof(unsigned long long) * (2 * (size_t)n + 1) * DBF_SYNC_STRIDE, 256);
-    const size_t o_ac = off;  off = align_up(off + sizeof(int) * acc_ints, 256);
-    const size_t o_cn = off;  off = align_up(off + sizeof(int) * cnt_ints, 256);
-    std::vector<DbfItem> items_p;
+    draft->o_ac = off = align_up(off + sizeof(unsigned long long) * (2 * (size_t)n + 1) * DBF_SYNC_STRIDE, 256);
+    draft->o_cn = off = align_up(off + sizeof(int) * acc_ints, 256);
+    draft->o_few = off = align_up(off + sizeof(int) * cnt_ints, 256);
+    draft->zero_bytes = align_up(off + few_acc_bytes((int)(rtB > rtA ? rtB : rtA)), 256);
     int nBp = 0;
     if (cut) {
-        // device addresses are offsets from the block's base, known only after the allocation:
-        // build with a null base here and rebase below
-        int* acc0 = reinterpret_cast<int*>(o_ac);
-        int* cnt0 = reinterpret_cast<int*>(o_cn);
+        // (accumulators and counters as offsets in the zeroed memory, like everything else that is placed later)
+        int* acc0 = reinterpret_cast<int*>(draft->o_ac);
+        int* cnt0 = reinterpret_cast<int*>(draft->o_cn);
         size_t row_tiles_before = 0;
         for (int i = 0; i < n; ++i) {
             const int stride = sB[i].n_rt * DBF_TILE_ROWS;
@@ -418,70 +421,119 @@ int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA,
             it.need = sB[it.layer].n_rt;
             it.peers = sA[it.layer].n_rt;
         }
-    const size_t o_ip = off;  off = align_up(off + sizeof(DbfItem) * items_p.size(), 256);
-    std::vector<uint8_t> image(off, 0);
-    std::memcpy(image.data() + o_sB, sB.data(), sizeof(DbfStage) * n);
-    std::memcpy(image.data() + o_sA, sA.data(), sizeof(DbfStage) * n);
-    std::memcpy(image.data() + o_wB, wB1.data(), sizeof(DbfWorkItem) * wB1.size());
-    std::memcpy(image.data() + o_wA, wA1.data(), sizeof(DbfWorkItem) * wA1.size());
-    std::memcpy(image.data() + o_in, items_n.data(), sizeof(DbfItem) * items_n.size());
-    std::memcpy(image.data() + o_i1, items_1.data(), sizeof(DbfItem) * items_1.size());
-    std::memcpy(image.data() + o_is, items_s.data(), sizeof(DbfItem) * items_s.size());
-    void* dev = nullptr;
-    hipError_t e = dbf_mfma_prepare();
-    if (e == hipSuccess) e = dbf_few_prepare();
-    if (e == hipSuccess) e = dbf_gemm_i8_prepare();
-    // (the sums of the column pieces of small launches, cleared on the device: they are no part of the image)
-    const size_t few_bytes = few_acc_bytes((int)(rtB > rtA ? rtB : rtA)), few_own = few_acc ? 0 : few_bytes;
-    if (e == hipSuccess) e = hipMalloc(&dev, off + few_own);
-    if (e == hipSuccess && few_own) e = hipMemset(static_cast<uint8_t*>(dev) + off, 0, few_own);
-    if (e == hipSuccess) {
-        for (DbfItem& it : items_p) {  // rebase the accumulator and counter addresses
-            it.acc = reinterpret_cast<int*>(static_cast<uint8_t*>(dev) + reinterpret_cast<size_t>(it.acc));
-            it.cnt = reinterpret_cast<int*>(static_cast<uint8_t*>(dev) + reinterpret_cast<size_t>(it.cnt));
-        }
-        std::memcpy(image.data() + o_ip, items_p.data(), sizeof(DbfItem) * items_p.size());
-    }
-    if (e == hipSuccess) e = hipMemcpy(dev, image.data(), off, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        if (dev) (void)hipFree(dev);
-        return DBF_EHIP;
-    }
-    uint8_t* d = static_cast<uint8_t*>(dev);
-    p->dev_block = dev;
+    off = 0;
+    draft->o_sA = off = align_up(off + sizeof(DbfStage) * n, 256);
+    draft->o_wB = off = align_up(off + sizeof(DbfStage) * n, 256);
+    draft->o_wA = off = align_up(off + sizeof(DbfWorkItem) * wB1.size(), 256);
+    draft->o_in = off = align_up(off + sizeof(DbfWorkItem) * wA1.size(), 256);
+    draft->o_i1 = off = align_up(off + sizeof(DbfItem) * items_n.size(), 256);
+    draft->o_is = off = align_up(off + sizeof(DbfItem) * items_1.size(), 256);
+    draft->o_ip = off = align_up(off + sizeof(DbfItem) * items_s.size(), 256);
+    draft->tables_bytes = align_up(off + sizeof(DbfItem) * items_p.size(), 256);
     p->n_layers = n;
-    p->d_stagesB = reinterpret_cast<DbfStage*>(d + o_sB);
-    p->d_stagesA = reinterpret_cast<DbfStage*>(d + o_sA);
-    p->d_workB1 = reinterpret_cast<DbfWorkItem*>(d + o_wB);
-    p->d_workA1 = reinterpret_cast<DbfWorkItem*>(d + o_wA);
     p->blocksB1 = (int)wB1.size();
     p->blocksA1 = (int)wA1.size();
-    p->d_items_n = reinterpret_cast<DbfItem*>(d + o_in);
     p->nBn = nBn;
     p->nAn = (int)items_n.size() - nBn;
-    p->d_items_1 = reinterpret_cast<DbfItem*>(d + o_i1);
     p->nB1 = nB1;
     p->nA1 = (int)items_1.size() - nB1;
-    p->d_items_s = reinterpret_cast<DbfItem*>(d + o_is);
     p->nBs = nBs;
     p->nAs = (int)items_s.size() - nBs;
     p->rows_ok = 2 * (rtB + rtA) >= 7 * (long long)items_s.size();  // at least 3.5 row tiles per item on average
-    p->d_sync = reinterpret_cast<unsigned long long*>(d + o_sy);
-    p->d_items_p = cut ? reinterpret_cast<DbfItem*>(d + o_ip) : nullptr;
     p->nBp = nBp;
     p->nAp = (int)items_p.size() - nBp;
-    p->h_stage_B = sB[0];
-    p->h_stage_A = sA[0];
-    p->d_few_acc = !few_bytes ? nullptr : few_acc ? few_acc : reinterpret_cast<int*>(d + off);
     p->span = max_span;
+}
+
+// Gives a draft its memory: `tables` (tables_bytes, filled by the caller with the returned image), `zero` (zero_bytes, zeroed by the
+// caller), both 256-byte aligned; stage_shift is added to the stages' addresses.
+std::vector<uint8_t> place_plan(PlanDraft& d, uint8_t* tables, uint8_t* zero, uintptr_t stage_shift, DbfPlan* p) {
+    auto moved = [](auto*& ptr, uintptr_t by) {
+        using T = typename std::remove_reference<decltype(ptr)>::type;
+        if (ptr) ptr = reinterpret_cast<T>(reinterpret_cast<uintptr_t>(ptr) + by);
+    };
+    for (std::vector<DbfStage>* stages : {&d.sB, &d.sA})
+        for (DbfStage& st : *stages) {
+            moved(st.bits, stage_shift);
+            moved(st.in_scale, stage_shift);
+            moved(st.row_scale, stage_shift);
+            moved(st.t, stage_shift);
+            moved(st.q_in, stage_shift);
+        }
+    for (std::vector<DbfItem>* list : {&d.items_n, &d.items_1, &d.items_s, &d.items_p})
+        for (DbfItem& it : *list) {
+            moved(it.bits, stage_shift);
+            moved(it.in_scale, stage_shift);
+            moved(it.row_scale, stage_shift);
+            moved(it.t, stage_shift);
+            moved(it.q_in, stage_shift);
+            moved(it.acc, reinterpret_cast<uintptr_t>(zero));   // (NULL outside items_p; there never at offset 0)
+            moved(it.cnt, reinterpret_cast<uintptr_t>(zero));
+        }
+    std::vector<uint8_t> image(d.tables_bytes, 0);
+    auto put = [&](size_t at, const auto& v) {
+        if (!v.empty()) std::memcpy(image.data() + at, v.data(), sizeof(v[0]) * v.size());
+    };
+    put(0, d.sB);
+    put(d.o_sA, d.sA);
+    put(d.o_wB, d.wB1);
+    put(d.o_wA, d.wA1);
+    put(d.o_in, d.items_n);
+    put(d.o_i1, d.items_1);
+    put(d.o_is, d.items_s);
+    put(d.o_ip, d.items_p);
+    *p = d.p;
+    p->d_stagesB = reinterpret_cast<DbfStage*>(tables);
+    p->d_stagesA = reinterpret_cast<DbfStage*>(tables + d.o_sA);
+    p->d_workB1 = reinterpret_cast<DbfWorkItem*>(tables + d.o_wB);
+    p->d_workA1 = reinterpret_cast<DbfWorkItem*>(tables + d.o_wA);
+    p->d_items_n = reinterpret_cast<DbfItem*>(tables + d.o_in);
+    p->d_items_1 = reinterpret_cast<DbfItem*>(tables + d.o_i1);
+    p->d_items_s = reinterpret_cast<DbfItem*>(tables + d.o_is);
+    p->d_items_p = d.items_p.empty() ? nullptr : reinterpret_cast<DbfItem*>(tables + d.o_ip);
+    p->d_sync = reinterpret_cast<unsigned long long*>(zero);
+    p->d_few_acc = d.zero_bytes > d.o_few ? reinterpret_cast<int*>(zero + d.o_few) : nullptr;
+    p->h_stage_B = d.sB[0];
+    p->h_stage_A = d.sA[0];
+    return image;
+}
+
+// One-time set-up of every kernel a plan may launch (LDS limits): not at the first launch, which may sit inside a stream capture.
+hipError_t prepare_kernels() {
+    hipError_t e = dbf_mfma_prepare();
+    if (e == hipSuccess) e = dbf_few_prepare();
+    if (e == hipSuccess) e = dbf_gemm_i8_prepare();
+    return e;
+}
+
+// Builds and uploads the launch tables for layers whose stages (with their addresses and x/y offsets already set) are given.
+int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA, const std::vector<int>& span_b,
+               const std::vector<int>& span_a, DbfPlan* p) {
+    PlanDraft draft;
+    draft_plan(sB, sA, span_b, span_a, &draft);
+    void* dev = nullptr;
+    hipError_t e = prepare_kernels();
+    if (e == hipSuccess) e = hipMalloc(&dev, draft.tables_bytes + draft.zero_bytes);
+    if (e == hipSuccess) {
+        uint8_t* d = static_cast<uint8_t*>(dev);
+        const std::vector<uint8_t> image = place_plan(draft, d, d + draft.tables_bytes, 0, p);
+        e = hipMemset(d + draft.tables_bytes, 0, draft.zero_bytes);
+        if (e == hipSuccess) e = hipMemcpy(dev, image.data(), image.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipDeviceSynchronize();
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        if (dev) (void)hipFree(dev);
+        std::memset(p, 0, sizeof(*p));
+        return DBF_EHIP;
+    }
+    p->dev_block = dev;
     return DBF_OK;
 }
 
 // Section offsets of a layer's single device block (256-byte aligned sections).
 struct LayerOffsets {
-    size_t A, B, a, m, b, image_bytes, t, qB, qA, few, total;
+    size_t A, B, a, m, b, image_bytes, t, qB, qA, total;
     int a_len, m_len, b_len, t_stride;
 };
 LayerOffsets layer_offsets(int n_in, int n_out, int k) {
@@ -500,67 +552,72 @@ LayerOffsets layer_offsets(int n_in, int n_out, int k) {
     o.t = off;  off = align_up(off + 4 * (size_t)DBF_MAX_BATCH * o.t_stride, 256);
     o.qB = off;  off = align_up(off + DBF_QIN_HEADER + 2 * (size_t)DBF_MAX_BATCH * o.b_len, 256);
     o.qA = off;  off = align_up(off + DBF_QIN_HEADER + 2 * (size_t)DBF_MAX_BATCH * dbf_col_tiles(k) * DBF_TILE_COLS, 256);
-    const int rt_k = dbf_row_tiles(k), rt_out = dbf_row_tiles(n_out);
-    o.few = off;  off = align_up(off + few_acc_bytes(rt_k > rt_out ? rt_k : rt_out), 256);
     o.total = off;
     return o;
 }
 
-// Allocates the device block of a layer of the given shape on the current device and describes it
-// (pointers, stages); the contents are left to the caller except the scratch, which is zeroed.
-int create_layer(int n_in, int n_out, int k, const LayerOffsets& o, dbf_layer** out) {
+// Makes a layer of the given shape on the current device: ONE allocation that holds its signs and vectors (left to the caller to fill),
+// its scratch and the zeroed memory of its launch plan, the plan's tables, and `extra_bytes` from `extra` (at *extra_dev).
+// Everything is queued on the null stream; the scratch is zeroed there.
+int create_layer(int n_in, int n_out, int k, const LayerOffsets& o, const void* extra, size_t extra_bytes, void** extra_dev, dbf_layer** out) {
     dbf_layer* L = new (std::nothrow) dbf_layer();
     if (!L) return DBF_ENOMEM;
+    DbfStage& sb = L->h_stages[0];
+    DbfStage& sa = L->h_stages[1];
+    auto place = [&](uint8_t* d) {
+        L->dA = d + o.A;  L->dB = d + o.B;
+        L->da = reinterpret_cast<uint16_t*>(d + o.a);
+        L->dm = reinterpret_cast<uint16_t*>(d + o.m);
+        L->db = reinterpret_cast<uint16_t*>(d + o.b);
+        L->dt = reinterpret_cast<float*>(d + o.t);
+        L->dqB = d + o.qB;
+        L->dqA = d + o.qA;
+        sb.bits = L->dB;  sb.in_scale = L->db;  sb.row_scale = L->dm;  sb.t = L->dt;  sb.q_in = L->dqB;
+        sa.bits = L->dA;  sa.in_scale = nullptr;  sa.row_scale = L->da;  sa.t = L->dt;  sa.q_in = L->dqA;
+    };
+    L->t_stride = o.t_stride;
+    sb.x_off = sb.y_off = sa.x_off = sa.y_off = 0;
+    sb.n_rt = dbf_row_tiles(k);  sb.n_ct = dbf_col_tiles(n_in);
+    sb.rows = k;  sb.cols = n_in;  sb.t_stride = o.t_stride;  sb.pad_ = 0;
+    sa.n_rt = dbf_row_tiles(n_out);  sa.n_ct = dbf_col_tiles(k);
+    sa.rows = n_out;  sa.cols = k;  sa.t_stride = o.t_stride;  sa.pad_ = 0;
+    // (drafted as if the block lay at DRAFT_BASE)
+    constexpr uintptr_t DRAFT_BASE = 1 << 20;
+    place(reinterpret_cast<uint8_t*>(DRAFT_BASE));
+    // (the launch plan of a layer alone: one row tile per workgroup gives the most parallelism)
+    PlanDraft draft;
+    draft_plan(std::vector<DbfStage>(1, sb), std::vector<DbfStage>(1, sa), std::vector<int>(1, 1), std::vector<int>(1, 1), &draft);
+    const size_t o_zero = o.total, o_tables = o_zero + draft.zero_bytes, o_extra = o_tables + draft.tables_bytes, total = o_extra + extra_bytes;
     void* dev = nullptr;
     int device = 0;
-    if (hipGetDevice(&device) != hipSuccess || hipMalloc(&dev, o.total) != hipSuccess) {
+    hipError_t e = prepare_kernels();
+    if (e == hipSuccess) e = hipGetDevice(&device);
+    if (e == hipSuccess) e = hipMalloc(&dev, total);
+    if (e == hipSuccess) {
+        uint8_t* d = static_cast<uint8_t*>(dev);
+        place(d);
+        std::vector<uint8_t> image = place_plan(draft, d + o_tables, d + o_zero, reinterpret_cast<uintptr_t>(d) - DRAFT_BASE, &L->plan);
+        image.resize(draft.tables_bytes + extra_bytes);
+        if (extra_bytes) std::memcpy(image.data() + draft.tables_bytes, extra, extra_bytes);
+        if (extra_dev) *extra_dev = d + o_extra;
+        e = hipMemsetAsync(d + o.t, 0, o_tables - o.t, nullptr);
+        if (e == hipSuccess) e = hipMemcpy(d + o_tables, image.data(), image.size(), hipMemcpyHostToDevice);
+    }
+    if (e != hipSuccess) {
         (void)hipGetLastError();
+        if (dev) (void)hipFree(dev);
         delete L;
         return DBF_EHIP;
     }
-    if (hipMemset(static_cast<uint8_t*>(dev) + o.t, 0, o.total - o.t) != hipSuccess) {
-        (void)hipGetLastError();
-        (void)hipFree(dev);
-        delete L;
-        return DBF_EHIP;
-    }
-    uint8_t* d = static_cast<uint8_t*>(dev);
     L->n_in = n_in;  L->n_out = n_out;  L->k = k;  L->device = device;
     L->dev_block = dev;  L->device_bytes = o.total;
-    L->dA = d + o.A;  L->dB = d + o.B;
-    L->da = reinterpret_cast<uint16_t*>(d + o.a);
-    L->dm = reinterpret_cast<uint16_t*>(d + o.m);
-    L->db = reinterpret_cast<uint16_t*>(d + o.b);
-    L->dt = reinterpret_cast<float*>(d + o.t);
-    L->t_stride = o.t_stride;
-    L->dqB = d + o.qB;
-    L->dqA = d + o.qA;
-    L->d_few_acc = reinterpret_cast<int*>(d + o.few);
-
-    DbfStage& sb = L->h_stages[0];
-    sb.bits = L->dB;  sb.in_scale = L->db;  sb.row_scale = L->dm;  sb.t = L->dt;
-    sb.x_off = 0;  sb.y_off = 0;
-    sb.n_rt = dbf_row_tiles(k);  sb.n_ct = dbf_col_tiles(n_in);
-    sb.rows = k;  sb.cols = n_in;  sb.t_stride = o.t_stride;  sb.pad_ = 0;  sb.q_in = L->dqB;
-    DbfStage& sa = L->h_stages[1];
-    sa.bits = L->dA;  sa.in_scale = nullptr;  sa.row_scale = L->da;  sa.t = L->dt;
-    sa.x_off = 0;  sa.y_off = 0;
-    sa.n_rt = dbf_row_tiles(n_out);  sa.n_ct = dbf_col_tiles(k);
-    sa.rows = n_out;  sa.cols = k;  sa.t_stride = o.t_stride;  sa.pad_ = 0;  sa.q_in = L->dqA;
     *out = L;
     return DBF_OK;
 }
 
-// The launch plan of a layer alone: one row tile per workgroup gives the most parallelism.
-int finish_layer(dbf_layer* L) {
-    std::vector<DbfStage> vB(1, L->h_stages[0]), vA(1, L->h_stages[1]);
-    return build_plan(vB, vA, std::vector<int>(1, 1), std::vector<int>(1, 1), L->d_few_acc, &L->plan);
-}
-
 void destroy_layer(dbf_layer* L) {
     if (!L) return;
-    free_plan(L->plan);
-    if (L->dev_block) (void)hipFree(L->dev_block);
+    if (L->dev_block) (void)hipFree(L->dev_block);   // (its plan lives there too)
     delete L;
 }
 
@@ -581,7 +638,7 @@ int build_layer(int n_in, int n_out, int k, const uint32_t* A_bits, const uint32
     std::memcpy(image + o.b, b, 2 * (size_t)n_in);
 
     dbf_layer* L = nullptr;
-    rc = create_layer(n_in, n_out, k, o, &L);
+    rc = create_layer(n_in, n_out, k, o, nullptr, 0, nullptr, &L);
     if (rc != DBF_OK) {
         std::free(image);
         return rc;
@@ -589,7 +646,7 @@ int build_layer(int n_in, int n_out, int k, const uint32_t* A_bits, const uint32
     hipError_t e = hipMemcpy(L->dev_block, image, o.image_bytes, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     std::free(image);
-    if (e != hipSuccess || finish_layer(L) != DBF_OK) {
+    if (e != hipSuccess) {
         (void)hipGetLastError();
         destroy_layer(L);
         return DBF_EHIP;
@@ -840,15 +897,12 @@ int dbf_prune_middle(const dbf_layer* L, const int32_t* keep, int n_keep, dbf_la
 
     dbf_layer* N = nullptr;
     const LayerOffsets o = layer_offsets(L->n_in, L->n_out, n_keep);
-    int rc = create_layer(L->n_in, L->n_out, n_keep, o, &N);
+    void* keep_dev = nullptr;
+    const int rc = create_layer(L->n_in, L->n_out, n_keep, o, keep, sizeof(int) * (size_t)n_keep, &keep_dev, &N);
     if (rc != DBF_OK) return rc;
-    int* keep_dev = nullptr;
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(&keep_dev), sizeof(int) * (size_t)n_keep);
-    if (e == hipSuccess) e = hipMemcpy(keep_dev, keep, sizeof(int) * (size_t)n_keep, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = dbf_prune_launch(L, N, keep_dev, n_keep, nullptr);
+    hipError_t e = dbf_prune_launch(L, N, static_cast<const int*>(keep_dev), n_keep, nullptr);
     if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (keep_dev) (void)hipFree(keep_dev);
-    if (e != hipSuccess || finish_layer(N) != DBF_OK) {
+    if (e != hipSuccess) {
         (void)hipGetLastError();
         destroy_layer(N);
         return DBF_EHIP;
@@ -934,7 +988,7 @@ int dbf_stack_create_grouped(const dbf_layer* const* layers, int n_layers, const
         S->h_y_prefix[i + 1] = S->h_y_prefix[i] + L->n_out;
     }
     S->h_x_prefix[n_layers] = x_end;
-    const int rc = build_plan(sB, sA, stack_spans(DBF_TUNE_STACK_SPAN_B), stack_spans(DBF_TUNE_STACK_SPAN_A), nullptr, &S->plan);
+    const int rc = build_plan(sB, sA, stack_spans(DBF_TUNE_STACK_SPAN_B), stack_spans(DBF_TUNE_STACK_SPAN_A), &S->plan);
     if (rc != DBF_OK) {
         dbf_stack_free(S);
         return rc;

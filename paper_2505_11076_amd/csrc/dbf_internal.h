@@ -85,7 +85,7 @@ struct DbfItem {
 
 // Device-side state of one launch plan: everything a decode call of a layer or a stack needs.
 struct DbfPlan {
-    void* dev_block;            // single allocation holding all tables below
+    void* dev_block;            // single allocation holding all tables below (NULL: a layer's own plan, which lives in the layer's block)
     int n_layers;
     DbfStage* d_stagesB;        // [n_layers]
     DbfStage* d_stagesA;        // [n_layers]
@@ -136,7 +136,6 @@ struct dbf_layer {
     int t_stride;
     unsigned char* dqB;     // quantised input of the B stage (DbfStage::q_in)
     unsigned char* dqA;     // quantised input of the A stage
-    int* d_few_acc;         // what the layer's own plan has as DbfPlan::d_few_acc (zeroed with the scratch)
     DbfStage h_stages[2];   // {B stage, A stage} with offsets 0
     DbfPlan plan;           // launch plan of this layer alone
 };

@@ -75,11 +75,14 @@ __global__ __launch_bounds__(256) void dbf_prune_rows_kernel(const uint8_t* __re
     reinterpret_cast<unsigned*>(new_bits + ((size_t)rtn * n_ct + ct) * DBF_TILE_BYTES)[tid] = tile[tid];
 }
 
-// m'[i] = m[keep[i]], zero beyond the kept channels (the vector is padded to whole row tiles).
-__global__ void dbf_prune_scale_kernel(const uint16_t* __restrict__ old_m, uint16_t* __restrict__ new_m,
-                                       const int* __restrict__ keep, int n_keep, int padded) {
+// The vectors: m'[i] = m[keep[i]], zero beyond the kept channels (padded to whole row tiles); a and b as they are.
+__global__ void dbf_prune_vectors_kernel(const uint16_t* __restrict__ old_m, uint16_t* __restrict__ new_m, const int* __restrict__ keep, int n_keep,
+                                         int m_len, const uint16_t* __restrict__ old_a, uint16_t* __restrict__ new_a, int a_len,
+                                         const uint16_t* __restrict__ old_b, uint16_t* __restrict__ new_b, int b_len) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < padded) new_m[i] = i < n_keep ? old_m[keep[i]] : (uint16_t)0;
+    if (i < m_len) new_m[i] = i < n_keep ? old_m[keep[i]] : (uint16_t)0;
+    if (i < a_len) new_a[i] = old_a[i];
+    if (i < b_len) new_b[i] = old_b[i];
 }
 
 }  // namespace
@@ -93,12 +96,9 @@ hipError_t dbf_prune_launch(const dbf_layer* src, dbf_layer* dst, const int* kee
                        ctA_new, keep_dev, n_keep);
     hipLaunchKernelGGL(dbf_prune_rows_kernel, dim3(ctB, rtB_new), dim3(256), 0, stream, src->dB, dst->dB, ctB, keep_dev,
                        n_keep);
-    const int padded = rtB_new * DBF_TILE_ROWS;
-    hipLaunchKernelGGL(dbf_prune_scale_kernel, dim3((padded + 255) / 256), dim3(256), 0, stream, src->dm, dst->dm,
-                       keep_dev, n_keep, padded);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = hipMemcpyAsync(dst->da, src->da, 2 * (size_t)rtA * DBF_TILE_ROWS, hipMemcpyDeviceToDevice, stream);
-    if (e != hipSuccess) return e;
-    return hipMemcpyAsync(dst->db, src->db, 2 * (size_t)ctB * DBF_TILE_COLS, hipMemcpyDeviceToDevice, stream);
+    const int m_len = rtB_new * DBF_TILE_ROWS, a_len = rtA * DBF_TILE_ROWS, b_len = ctB * DBF_TILE_COLS;
+    const int most = m_len > a_len ? (m_len > b_len ? m_len : b_len) : (a_len > b_len ? a_len : b_len);
+    hipLaunchKernelGGL(dbf_prune_vectors_kernel, dim3((most + 255) / 256), dim3(256), 0, stream, src->dm, dst->dm, keep_dev, n_keep, m_len, src->da,
+                       dst->da, a_len, src->db, dst->db, b_len);
+    return hipGetLastError();
 }
