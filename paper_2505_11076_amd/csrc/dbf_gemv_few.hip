@@ -11,6 +11,8 @@
 //   * where compute units would idle, the tokens of a call are dealt to several workgroups per row tile (`group` tokens each:
 //     less rounding per workgroup, the sign bytes come from L2), and long rows are cut into column pieces.
 // Measured figures are at the dispatch rules (dbf_api.hip).
+#include <type_traits>
+
 #include "dbf_kernels.h"
 #include "dbf_wave.h"
 
@@ -536,10 +538,14 @@ __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
 constexpr int FEW_MAX_WGS = 256;     // compute units
 constexpr int FEW_LDS = 156 * 1024;  // (its registers give a workgroup the compute unit to itself)
 
-template <bool STAGE_A, bool LIST, int H>
-hipError_t raise_lds() {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&dbf_few_kernel<STAGE_A, LIST, H>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               FEW_LDS);
+hipError_t raise_lds(const void* kernel) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FEW_LDS); }
+template <int H>
+hipError_t raise_lds_few() {
+    hipError_t e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, false, H>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, true, H>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<true, false, H>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<true, true, H>));
+    return e;
 }
 
 // Tokens per workgroup and column pieces of a stage of n_items row tiles.  As many workgroups as there are compute units, and no
@@ -572,10 +578,8 @@ inline int few_cols(const DbfPlan& p, bool stage_a) { return dbf_col_tiles(stage
 // More than 64 KiB of LDS per workgroup has to be asked for, once per process (see dbf_mfma_prepare).
 hipError_t dbf_few_prepare() {
     static const hipError_t raised = [] {
-        const hipError_t e[] = {hipFuncSetAttribute(reinterpret_cast<const void*>(&dbf_small_layer_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, FEW_LDS),
-                                raise_lds<false, false, 2>(), raise_lds<false, true, 2>(), raise_lds<true, false, 2>(), raise_lds<true, true, 2>(),
-                                raise_lds<false, false, 4>(), raise_lds<false, true, 4>(), raise_lds<true, false, 4>(), raise_lds<true, true, 4>(),
-                                raise_lds<false, false, 8>(), raise_lds<false, true, 8>(), raise_lds<true, false, 8>(), raise_lds<true, true, 8>()};
+        const hipError_t e[] = {raise_lds(reinterpret_cast<const void*>(&dbf_small_layer_kernel)), raise_lds_few<2>(), raise_lds_few<4>(),
+                                raise_lds_few<6>(), raise_lds_few<8>(), raise_lds_few<10>()};
         for (hipError_t x : e)
             if (x != hipSuccess) {
                 (void)hipGetLastError();
@@ -620,26 +624,19 @@ hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y
     const void* first = list ? static_cast<const void*>(p.d_items_1 + (stage_a ? p.nB1 : 0)) : s.bits;
     float* t = t_over ? t_over : list ? nullptr : s.t;
     const int held = (8 * n_ct + 64 * few_parts(nb) - 1) / (64 * few_parts(nb));   // vectors of eight values per lane
-#define DBF_FEW(A, L)                                                                                                                          \
-    if (held <= 2)                                                                                                                             \
-        hipLaunchKernelGGL((dbf_few_kernel<A, L, 2>), grid, dim3(FEW_THREADS), lds, stream, first, s.in_scale, s.row_scale, t, io, p.d_few_acc, \
-                           s.cols, list ? n_items : s.rows, tokens, cut);                                                                      \
-    else if (held <= 4)                                                                                                                        \
-        hipLaunchKernelGGL((dbf_few_kernel<A, L, 4>), grid, dim3(FEW_THREADS), lds, stream, first, s.in_scale, s.row_scale, t, io, p.d_few_acc, \
-                           s.cols, list ? n_items : s.rows, tokens, cut);                                                                      \
-    else                                                                                                                                       \
-        hipLaunchKernelGGL((dbf_few_kernel<A, L, 8>), grid, dim3(FEW_THREADS), lds, stream, first, s.in_scale, s.row_scale, t, io, p.d_few_acc, \
-                           s.cols, list ? n_items : s.rows, tokens, cut)
-    if (stage_a && list) {
-        DBF_FEW(true, true);
-    } else if (stage_a) {
-        DBF_FEW(true, false);
-    } else if (list) {
-        DBF_FEW(false, true);
-    } else {
-        DBF_FEW(false, false);
-    }
-#undef DBF_FEW
+    auto launch = [&](auto h) {
+        constexpr int H = decltype(h)::value;
+        void (*kernel)(const void*, const uint16_t*, const uint16_t*, float*, uint16_t*, int*, int, int, unsigned, unsigned) =
+            stage_a ? (list ? dbf_few_kernel<true, true, H> : dbf_few_kernel<true, false, H>)
+                    : (list ? dbf_few_kernel<false, true, H> : dbf_few_kernel<false, false, H>);
+        hipLaunchKernelGGL(kernel, grid, dim3(FEW_THREADS), lds, stream, first, s.in_scale, s.row_scale, t, io, p.d_few_acc, s.cols,
+                           list ? n_items : s.rows, tokens, cut);
+    };
+    if (held <= 2) launch(std::integral_constant<int, 2>{});
+    else if (held <= 4) launch(std::integral_constant<int, 4>{});
+    else if (held <= 6) launch(std::integral_constant<int, 6>{});
+    else if (held <= 8) launch(std::integral_constant<int, 8>{});
+    else launch(std::integral_constant<int, 10>{});
     return hipGetLastError();
 }
 
