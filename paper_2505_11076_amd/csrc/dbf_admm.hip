@@ -313,8 +313,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const bool factor = blockIdx.x == 0 && blockIdx.y == 0;
     v16f acc[2][2];
     float old[2][2][16];
-    split_gemm_tile<3>(reinterpret_cast<uint8_t(*)[24 * SG_FRAG]>(lds), planes + ((size_t)it * n_kb + jb * (NB / 16)) * (12 * SG_FRAG),
-                       planes + ((size_t)jt * n_kb + jb * (NB / 16)) * (12 * SG_FRAG), NB / 16, acc, [&]() {
+    split_gemm_tile<3, 2, 1>(reinterpret_cast<uint8_t(*)[24 * SG_FRAG]>(lds), planes + ((size_t)it * n_kb + jb * (NB / 16)) * (12 * SG_FRAG),
+                          planes + ((size_t)jt * n_kb + jb * (NB / 16)) * (12 * SG_FRAG), 0, NB / 16, acc, [&]() {
 #pragma unroll
                            for (int bi = 0; bi < 2; ++bi)
 #pragma unroll

@@ -137,93 +137,130 @@ struct SplitGemmArgs {
     int ktri;              // both operands are zero for k < output index: sums start at the first k that can contribute
 };
 
-// The products of a workgroup's 128 x 128 block: acc (2 x 2 blocks of 32 x 32 per wavefront, rows from 64 (w % 2), columns from
-// 64 (w / 2)) = sum over `steps` fragments of 16 k from pp (P's planes) and qp (Q's).  `meanwhile` runs once the first loads
-// are on their way.  Ends with a barrier behind the last read of `lds`.
-template <int PA, class F>
-__device__ inline void split_gemm_tile(uint8_t (*lds)[(4 * PA + 12) * SG_FRAG], const uint8_t* pp, const uint8_t* qp, int steps, v16f (&acc)[2][2],
-                                       F meanwhile) {
-    constexpr int PB = 4 * PA * SG_FRAG, QB = 12 * SG_FRAG;   // bytes per step
-    constexpr int NF = (PB + QB) / 4096;                      // 16-byte pieces a thread stages per step
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    pp += 16 * tid;
-    qp += 16 * tid;
-    v4f st[NF];
-    auto fetch = [&](int s) {
+// The products of a workgroup's block of 64 BI x 128: acc (BI x 2 blocks of 32 x 32 per wavefront, rows from 32 BI (w % 2), columns from
+// 64 (w / 2)) = sum over `steps` fragments of 16 k from pp (P's planes; BI = 1: of rows 64 `half` .. of the 128) and qp (Q's).
+// KS = 2: a workgroup of 512 threads, wavefronts 4-7 take every second step with LDS buffers of their own (lds: [KS][2][..]); their sums
+// are added at the end, and only threads 0-255 have the result.
+// `meanwhile` runs once the first loads are on their way.  Ends with a barrier behind the last read of `lds`.
+template <int PA, int BI, int KS, class F>
+__device__ inline void split_gemm_tile(uint8_t (*lds)[(2 * BI * PA + 12) * SG_FRAG], const uint8_t* pp, const uint8_t* qp, int half, int all_steps,
+                                       v16f (&acc)[BI][2], F meanwhile) {
+    constexpr int PB = 4 * PA * SG_FRAG, QB = 12 * SG_FRAG;   // bytes per step in memory
+    constexpr int NP = 2 * BI * PA, NF = NP + 12, PER = (NF + 3) / 4;   // fragments per step; of a wavefront's to stage
+    const int tid = threadIdx.x & 255, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+    const int steps = (all_steps - kg + KS - 1) / KS, rounds = (all_steps + KS - 1) / KS;   // this half's steps; barriers are everybody's
+    uint8_t(*const first_lds)[(2 * BI * PA + 12) * SG_FRAG] = lds;
+    lds += 2 * kg;
+    v4f st[PER];
+    auto fetch = [&](int i) {
+        const int s = KS * i + kg;
 #pragma unroll
-        for (int f = 0; f < NF; ++f)
-            st[f] = f < PA ? *reinterpret_cast<const v4f*>(pp + (size_t)s * PB + 4096 * f)
-                           : *reinterpret_cast<const v4f*>(qp + (size_t)s * QB + 4096 * (f - PA));
+        for (int n = 0; n < PER; ++n) {
+            const int f = w + 4 * n;
+            const uint8_t* src = f < NP ? pp + (size_t)s * PB + (4 * (f / (2 * BI)) + 2 * half + f % (2 * BI)) * SG_FRAG
+                                        : qp + (size_t)s * QB + (min(f, NF - 1) - NP) * SG_FRAG;
+            st[n] = *reinterpret_cast<const v4f*>(src + 16 * lane);
+        }
     };
     auto stage = [&](int buf) {
 #pragma unroll
-        for (int f = 0; f < NF; ++f) *reinterpret_cast<v4f*>(&lds[buf][4096 * f + 16 * tid]) = st[f];
+        for (int n = 0; n < PER; ++n)
+            if (NF % 4 == 0 || w + 4 * n < NF) *reinterpret_cast<v4f*>(&lds[buf][(w + 4 * n) * SG_FRAG + 16 * lane]) = st[n];
     };
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
         for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[bi][bj][v] = 0.f;
-    const int fi = 2 * (w & 1), fj = 2 * (w >> 1);            // this wavefront's first 32-blocks
+    const int fi = BI * (w & 1), fj = 2 * (w >> 1);           // this wavefront's first 32-blocks
     auto multiply = [&](int buf) {
         const uint8_t* base = &lds[buf][16 * lane];
-        v8bf a[2][PA], b[2][3];
+        v8bf a[BI][PA], b[2][3];
 #pragma unroll
-        for (int x = 0; x < 2; ++x) {
+        for (int p = 0; p < PA; ++p)
 #pragma unroll
-            for (int p = 0; p < PA; ++p) a[x][p] = *reinterpret_cast<const v8bf*>(base + (4 * p + fi + x) * SG_FRAG);
+            for (int x = 0; x < BI; ++x) a[x][p] = *reinterpret_cast<const v8bf*>(base + (2 * BI * p + fi + x) * SG_FRAG);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) b[x][p] = *reinterpret_cast<const v8bf*>(base + PB + (4 * p + fj + x) * SG_FRAG);
-        }
-        // (piece pairs outermost: an accumulator is used again only after the three others)
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) b[x][p] = *reinterpret_cast<const v8bf*>(base + (NP + 4 * p + fj + x) * SG_FRAG);
+        // (piece pairs outermost: an accumulator is used again only after the others)
 #pragma unroll
         for (int p = PA - 1; p >= 0; --p)
 #pragma unroll
             for (int q = 2; q >= 0; --q) {
                 if (p + q > 2) continue;
 #pragma unroll
-                for (int bi = 0; bi < 2; ++bi)
+                for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
                     for (int bj = 0; bj < 2; ++bj)
                         acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[bi][p], b[bj][q], acc[bi][bj], 0, 0, 0);
             }
     };
-    if (steps <= 0) return;
-    fetch(0);
-    stage(0);
+    if (all_steps <= 0) return;
+    if (steps > 0) {
+        fetch(0);
+        stage(0);
+    }
     if (steps > 1) fetch(1);
     meanwhile();
     __syncthreads();
-    for (int s = 0; s < steps; ++s) {
+    for (int s = 0; s < rounds; ++s) {
         if (s + 1 < steps) stage((s & 1) ^ 1);
         if (s + 2 < steps) fetch(s + 2);
-        multiply(s & 1);
+        if (KS == 1 || s < steps) multiply(s & 1);
         __syncthreads();
+    }
+    if (KS == 2) {
+        v16f* sums = reinterpret_cast<v16f*>(first_lds);      // [BI][2][256]
+        static_assert(KS == 1 || BI * 2 * 256 * sizeof(v16f) <= 4 * (2 * BI * PA + 12) * SG_FRAG, "the sums fit the buffers");
+#pragma unroll
+        for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+            for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {                 // (16-byte pieces, thread by thread: no bank conflicts)
+                    v4f* at = reinterpret_cast<v4f*>(sums) + ((bi * 2 + bj) * 4 + c) * 256 + tid;
+                    if (kg == 1) *at = (v4f){acc[bi][bj][4 * c], acc[bi][bj][4 * c + 1], acc[bi][bj][4 * c + 2], acc[bi][bj][4 * c + 3]};
+                }
+        __syncthreads();
+#pragma unroll
+        for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+            for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const v4f o = reinterpret_cast<const v4f*>(sums)[((bi * 2 + bj) * 4 + c) * 256 + tid];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[bi][bj][4 * c + e] += o[e];
+                }
     }
 }
 
-template <int PA>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_split_gemm_kernel(const SplitGemmArgs g) {
+template <int PA, int BI, int KS>
+__global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_split_gemm_kernel(const SplitGemmArgs g) {
     constexpr int PB = 4 * PA * SG_FRAG, QB = 12 * SG_FRAG;   // bytes per step
-    __shared__ __align__(16) uint8_t lds[2][PB + QB];
-    const int tid = threadIdx.x, lane = tid & 63;
+    __shared__ __align__(16) uint8_t lds[2 * KS][(2 * BI * PA + 12) * SG_FRAG];
+    const int tid = threadIdx.x & 255, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned n_wg = gridDim.x * gridDim.y, lin = blockIdx.x + gridDim.x * blockIdx.y;
     const unsigned die = lin & 7, slot = lin >> 3, per = n_wg >> 3, extra = n_wg & 7;
     const unsigned vid = die * per + (die < extra ? die : extra) + slot;
-    const int it = (int)(vid % gridDim.x), jt = (int)(vid / gridDim.x);
-    if (g.upper && it > jt) return;
+    const int it = (int)(vid % gridDim.x), jt = (int)(vid / gridDim.x), row0 = 64 * BI * it;
+    if (g.upper && row0 >= 128 * (jt + 1)) return;
     const int n_kb = (g.K + 15) / 16;
-    const int kb0 = g.ktri ? min(8 * max(it, jt), n_kb) : 0;
-    const int fi = 2 * (w & 1), fj = 2 * (w >> 1);
-    v16f acc[2][2];
-    split_gemm_tile<PA>(lds, g.P + ((size_t)it * n_kb + kb0) * PB, g.Q + ((size_t)jt * n_kb + kb0) * QB, n_kb - kb0, acc, []() {});
+    const int kb0 = g.ktri ? min(max(row0, 128 * jt) / 16, n_kb) : 0;
+    const int fi = BI * (w & 1), fj = 2 * (w >> 1);
+    v16f acc[BI][2];
+    split_gemm_tile<PA, BI, KS>(lds, g.P + ((size_t)(row0 >> 7) * n_kb + kb0) * PB, g.Q + ((size_t)jt * n_kb + kb0) * QB, (row0 >> 6) & (2 - BI),
+                                n_kb - kb0, acc, []() {});
+    if (KS == 2 && threadIdx.x >= 256) return;
     // register v of lane l of a 32 x 32 block is row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
     const int l32 = lane & 31, h = lane >> 5;
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
         for (int bj = 0; bj < 2; ++bj) {
             const int col = 128 * jt + 32 * (fj + bj) + l32;
@@ -231,7 +268,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const float csj = g.cs ? g.cs[col] : 1.f;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int row = 128 * it + 32 * (fi + bi) + 8 * (v >> 2) + 4 * h + (v & 3);
+                const int row = row0 + 32 * (fi + bi) + 8 * (v >> 2) + 4 * h + (v & 3);
                 if (row < g.M) {
                     float val = acc[bi][bj][v] * csj;
                     if (g.rs) val *= g.rs[row];
@@ -243,9 +280,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         }
 }
 
+// Where blocks of 128 x 128 would not put two workgroups on every compute unit, a lone one waits out its barriers and LDS latencies:
+// the steps are shared by two halves of a workgroup of 512; and the blocks are 64 x 128 where those of 128 x 128 would leave half of
+// the compute units idle.  Whole calls, us, 128 x 128 with 256 threads / with 512 / 64 x 128 with 512: an update of q = 512, r = 768 (24 blocks)
+// 87.6 / 88.4 / 68.4, 1024 x 1024 (64) 112.9 / 111.4 / 84.9, 1408 x 1269 (110) 147.3 / 144.0 / 112.1, 1536 x 2048 (192) 143.5 / 139.5 / 157.5,
+// 2048 x 4096 (512) 272 / 312 / 357; the constants at p = 4096, q = 700, r = 1000 531 / 488 / 424.
 template <int PA>
 inline void launch_split_gemm(const SplitGemmArgs& g, hipStream_t st) {
-    hipLaunchKernelGGL((dbf_split_gemm_kernel<PA>), dim3((g.M + 127) / 128, (g.N + 127) / 128), dim3(256), 0, st, g);
+    const int mt = (g.M + 127) / 128, nt = (g.N + 127) / 128;
+    const long long blocks = g.upper ? (long long)mt * (mt + 1) / 2 : (long long)mt * nt;
+    if (blocks <= 128)
+        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 1, 2>), dim3((g.M + 63) / 64, nt), dim3(512), 0, st, g);
+    else if (blocks <= 256)
+        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 2, 2>), dim3(mt, nt), dim3(512), 0, st, g);
+    else
+        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 2, 1>), dim3(mt, nt), dim3(256), 0, st, g);
 }
 
 }  // namespace

@@ -306,3 +306,19 @@ def test_admm_iterations_on_the_device_approach_a_factorisable_target():
     res = residual(dev.host())
     G.say("  residual %.3e -> %.3e" % (res0, res))
     assert res < 1e-2 * res0
+
+
+@pytest.mark.parametrize("p,q,r", [(33, 1, 1), (48, 17, 130), (300, 129, 64), (64, 191, 257), (900, 193, 1500), (260, 1536, 1400), (100, 2048, 2100)])
+def test_admm_contractions_with_their_steps_and_blocks_cut_by_size(p, q, r):
+    """The contraction's three forms -- 64 x 128 blocks and 128 x 128 blocks with the steps in two halves (up to 128 and up to 256 blocks of 128 x
+    128), 128 x 128 blocks whole -- at ragged sizes, with one step, an odd number and an even number of them; the factorisation with one, two
+    and sixteen block rows, the last of them short.  Gates: as above."""
+    rho = 0.8
+    prob = PackedProblem(p, q, r, I.seed_for(9, 500 + p + q + r))
+    Minv, Cm = prob.prepare_on_device(rho)
+    _check_constants("constants p=%d q=%d r=%d" % (p, q, r), prob, rho, Minv, Cm)
+    dev = DeviceState(np.ascontiguousarray(Minv.T), Cm, prob.S, prob.a, prob.m, prob.U)
+    state0 = dev.host()
+    dev.step(rho, 1)
+    Minv64, C64 = O.admm_constants(prob.B_dense, prob.W, rho)
+    _check_step("update q=%d r=%d" % (q, r), state0, dev.host(), Minv64, C64, rho, 1, z_gate=2 * Z_GATE)
