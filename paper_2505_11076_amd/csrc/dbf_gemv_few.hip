@@ -10,7 +10,7 @@
 //     four wavefronts with four tiles each held a compute unit that has one workgroup to 11 GB/s);
 //   * where compute units would idle, the tokens of a call are dealt to several workgroups per row tile (`group` tokens each:
 //     less rounding per workgroup, the sign bytes come from L2), and long rows are cut into column pieces.
-// Measured figures are at the dispatch rules (dbf_api.hip).
+// Measured figures are at the rules that cut and choose such launches (few_cut, dbf_few_takes, dbf_small_layer_kernel).
 #include <type_traits>
 
 #include "dbf_kernels.h"
@@ -608,7 +608,8 @@ bool dbf_few_takes(const DbfPlan& p, bool stage_a, int T) {
 hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y, float* t_over, int T, hipStream_t stream) {
     const hipError_t raised = dbf_few_prepare();
     if (raised != hipSuccess) return raised;
-    const FewCut cut_ = few_cut(stage_a ? p.nA1 : p.nB1, few_cols(p, stage_a), T, p.d_few_acc && T <= DBF_MAX_BATCH);
+    // (a prompt, which brings its own middle activations, is never cut: its calls may overlap on one layer and share nothing of it)
+    const FewCut cut_ = few_cut(stage_a ? p.nA1 : p.nB1, few_cols(p, stage_a), T, !t_over && p.d_few_acc && T <= DBF_MAX_BATCH);
     const int group = cut_.group, pieces = cut_.pieces;
     const int nb = group < T ? group : T, tile_block = few_tile_block(2 * nb), red = 2 * nb * FEW_RB * 4;
     const int n_ct = dbf_col_tiles(stage_a ? p.max_cols_A : p.max_cols_B), want = (n_ct + pieces - 1) / pieces;
