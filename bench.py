@@ -754,10 +754,10 @@ def svid_bench(B, I, torch, np, stream, proto, iters=8):
         from oracle import dbf_oracle as O
         O.svid(Z.astype(np.float64), iters)
         cpu_s = time.time() - t0
-        # (the library makes both products of a round in ONE pass over Z for matrices of 24 Mi entries and more with rows of
-        #  at most 24576 values; the algorithmic bytes above keep the two-pass count, so the rate on them can pass the peak)
-        one_pass = rows * cols >= (24 << 20) and cols <= 24576 and cols % 4 == 0
-        passes = (iters + 1) if one_pass else (2 * iters + 1)
+        # (the library makes both products of a round in ONE pass over Z for rows of at most 24576 values, and up to 4096 the
+        #  signs in the first of them; the algorithmic bytes above keep the two-pass count, so the rate on them can pass the peak)
+        one_pass = cols <= 24576 and cols % 4 == 0
+        passes = (iters if cols <= 4096 else iters + 1) if one_pass else (2 * iters + 1)
         res["%dx%d_iters%d" % (rows, cols, iters)] = {
             "ms_per_call": round(ms, 4), "algorithmic_bytes": nbytes, "GBps": round(nbytes / (ms * 1e-3) / 1e9, 1),
             "frac_of_hbm_peak": round(nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
@@ -884,7 +884,7 @@ def prefill_bench(B, I, torch, np, stream, proto):
         res["%dx%d_k%d_T%d" % (n_in, n_out, k, T)] = {
             "ms": round(ms, 4), "tflops": round(tf, 2), "frac_of_f16_mfma_peak": round(tf / MFMA_F16_PEAK_TFLOPS, 4),
             "variant": "int8 matrix cores, 16-bit fixed-point activations", "protocol": protocol}
-        # few tokens (latency bound): up to 32 run as decode batches, up to 512 with the columns of a stage cut into shares
+        # few tokens (latency bound): up to 16 run as a decode batch, then kernels by size
         few = {}
         for Tf in (16, 32, 64, 256):
             ms_f, _ = proto.run(lambda: B.dbf_gemm(layer, x.data_ptr(), y.data_ptr(), Tf, ws.data_ptr(), ws_bytes, stream))

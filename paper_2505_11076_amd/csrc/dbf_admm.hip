@@ -12,8 +12,9 @@
 //
 // The contraction is q x q x r in fp32 accuracy (34 GFLOP at q = 2048, r = 4096) and dominates; the elementwise
 // kernels and the projection are bandwidth bound.  Measured at that size: the contraction 331 us on the fp32 matrix cores,
-// 182 us (0.19 PFLOP/s; 1.13 PFLOP/s of bf16 products) with split operands, whose planes cost 7 (Minv) + 6 us (R); the
-// update 389 -> 302 us; error against 64 bits 8.1e-6 -> 5.1e-6 (fewer roundings: 16 products enter the accumulator at once).
+// 182-223 us by the card's clock (0.15-0.19 PFLOP/s; 0.92-1.13 PFLOP/s of bf16 products, where a plain bf16 product of 8192^3
+// reaches 1.22) with split operands, whose planes cost 7 (Minv) + 6 us (R); the update with two rounds of SVID 388 -> 285 us; error
+// against 64 bits 8.1e-6 -> 5.2e-6 (fewer roundings: 16 products enter the accumulator at once).
 // The paper gives no kernel design for this step.
 #include "dbf_kernels.h"
 #include "dbf_split_gemm.h"
@@ -116,7 +117,9 @@ __global__ __launch_bounds__(256) void dbf_admm_rhs_kernel(const float* __restri
 // row jb of R is dead after its own update.  A finished row is written as the bf16 planes that the update and the last
 // contraction read (R's for c > jb, Y's for c <= jb) and nowhere else.
 // What bounds it: the chain.  Per block row 2 launches and 4 x 32 pivots; the update's products take 3 us of it.  Measured at
-// q = 2048 (16 block rows): see dbf_admm_prepare.
+// q = 2048 (16 block rows): panel 5.5 us, update 31.6 us of which the pivots 25, first block 30.  With p = r = 4096 the constants
+// took 4392 us in contractions per block on the fp32 matrix cores (84 us per diagonal block, on its own); now 1037: 590 us here,
+// 200 + 106 + 89 us in the contractions C, G and Y^T Y.
 // ---------------------------------------------------------------------------------------------
 constexpr int NB = 128;        // block size: the contraction's tile
 constexpr int CH_LD = NB + 1;  // LDS row length of a diagonal block: rows and columns both meet 32 different banks

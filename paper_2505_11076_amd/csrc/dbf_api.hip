@@ -692,7 +692,8 @@ int launch_plan(int kind, const DbfPlan& p, const void* x, void* y, int batch, h
         kind = DBF_GEMV_VALU;
     }
     const int FUSED_MIN_B_ITEMS = dbf_tune(DBF_TUNE_FUSED_MIN_B_ITEMS);
-    // Few row tiles: workgroups that round their own input, at any batch.  Not where a knob names one of the other forms, nor
+    // Few row tiles: workgroups that round their own input, at any batch (measured: dbf_few_takes).  What is left to the forms below
+    // are launches of more than 256 of them, longer inputs, named kinds and knobs.  Not where a knob names one of the other forms, nor
     // for plans that quantise every input once per call (long_rows) or that the knob sends through the one launch.
     if (kind == DBF_GEMV_AUTO && !p.long_rows && dbf_tune(DBF_TUNE_SHARED_Q) < 0 && dbf_tune(DBF_TUNE_SHARED_MIN_BATCH) <= (batch > 2 ? batch : 2) &&
         !(p.n_layers > 1 && p.nB1 >= FUSED_MIN_B_ITEMS) && dbf_few_takes(p, false, batch) && dbf_few_takes(p, true, batch))
@@ -708,7 +709,7 @@ int launch_plan(int kind, const DbfPlan& p, const void* x, void* y, int batch, h
     }
     // several row tiles per workgroup only if all columns of both stages fit one LDS chunk
     const int max_cols = p.max_cols_B > p.max_cols_A ? p.max_cols_B : p.max_cols_A;
-    // (column pieces at batch 2 only for a layer or three.  Wide rows, us per call with / without pieces at
+    // (column pieces: beyond 256 row tiles, or where a knob keeps a call from the above; at batch 2 only for a layer or three.  Wide rows, us per call with / without pieces at
     //  batch 2: 1 layer of 11008 -> 4096 23.5 / 26.8, 3 layers 26.9 / 27.0, 4 layers 27.8 / 24.6, 8: 31.3 / 26.0,
     //  16: 51.0 / 30.9, 32: 113.8 / 48.8)
     const bool use_pieces = pieces_ok && p.d_items_p && !p.long_rows &&

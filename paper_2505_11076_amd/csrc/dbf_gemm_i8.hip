@@ -6,7 +6,7 @@
 //   stage 2:   Y   = (mid A^T) . a          (T x n_out, fp16) contraction over k
 //
 // (forward-pass expression of the paper, section 3; the paper times batch 1 only, so this design
-// is not taken from it).  Compared with the fp16 path (dbf_gemm_mfma.hip):
+// is not taken from it).  Compared with a path on the fp16 matrix cores:
 //   * the A operand of v_mfma_i32_16x16x64_i8 is the masked sign bytes, one AND per register
 //     (0.25 vector-ALU operations per sign instead of 1), and one instruction covers 64 columns;
 //   * the sums are exact integers: acc_s = 2^s * sum over set bits of q, so
@@ -15,7 +15,11 @@
 //   * hi and lo planes are separate instructions with separate accumulators: twice the
 //     instructions at twice the int8 rate.
 //
-// Work split of a stage: workgroup = 256 rows x 64 tokens, 4 wavefronts; wavefront w owns row tile
+// Three kernels by size, all with the same bits: up to a few dozen tokens those of dbf_gemv_few.hip (no quantising launch), then
+// 128 rows x 32 tokens per workgroup (dbf_gemm_i8_mid_kernel), then the one that this describes (the rules: dbf_gemm_i8_launch,
+// mid_waves).
+//
+// Work split of a stage of many tokens: workgroup = 256 rows x 64 tokens, 4 wavefronts; wavefront w owns row tile
 // (w & 1) and the token half (w >> 1): 128 rows x 32 tokens = 8 planes x 2 token blocks x
 // {hi, lo} = 32 accumulator tiles (128 registers).  Twice as many workgroups as compute units at
 // 4096 rows x 2048 tokens, i.e. two wavefronts per SIMD.  The 64-token slice of the quantised
@@ -507,7 +511,7 @@ void dbf_gemm_i8_stage_kernel(const StageArgs a) {
 }
 
 // The same stage for calls of a few hundred tokens, where workgroups of 256 rows x 64 tokens leave compute units idle or alone with
-// one wavefront per SIMD: a workgroup of 128 rows x 32 tokens whose eight wavefronts take an eighth of the column steps each.
+// one wavefront per SIMD: a workgroup of 128 rows x 32 tokens whose WAVES wavefronts take an equal share of the column steps each.
 // Every wavefront has 128 rows x 32 tokens of its own (the accumulators of the kernel above), loads its sign tiles and operand
 // bytes straight into registers, MID_DEPTH steps ahead, and meets the others only at the end: exact integer sums through LDS.
 // No barrier and no LDS traffic per step; what bounds it is the matrix pipe with its ANDs, then L2 (5 KiB per wavefront and step).

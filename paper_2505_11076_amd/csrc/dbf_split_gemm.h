@@ -117,10 +117,11 @@ __global__ __launch_bounds__(256) void dbf_split_signs_kernel(const uint8_t* __r
 
 // ---------------------------------------------------------------------------------------------
 // out[i][j] = rs[i] * cs[j] * sum_k P[k][i] Q[k][j] + add[i][j] + (i == j ? diag : 0)
-// from the planes of P (PA = 3 pieces, or 1: signs) and Q (3 pieces).  Workgroup = 128 x 128 outputs, 4 wavefronts of 64 x 64
-// (2 x 2 blocks of 32 x 32: 64 accumulator registers), 16 values of k per step: 24 matrix instructions of 32 cycles per wavefront
-// (12 with PA = 1) against 12 (8) LDS reads of 1 KiB, a step's 24 (16) KiB double buffered in LDS and requested two steps ahead into
-// registers, one barrier per step; two workgroups per compute unit cover each other's barriers.  Workgroups are renumbered so that a
+// from the planes of P (PA = 3 pieces, or 1: signs) and Q (3 pieces).  Workgroup = 128 x 128 outputs (BI = 2; BI = 1: 64 x 128), 4
+// wavefronts of 64 x 64 (2 x 2 blocks of 32 x 32: 64 accumulator registers; BI = 1: 32 x 64), 16 values of k per step: 24 matrix
+// instructions of 32 cycles per wavefront (12 with PA = 1) against 12 (8) LDS reads of 1 KiB, a step's 24 (16) KiB double buffered in
+// LDS and requested two steps ahead into registers, one barrier per step; two workgroups per compute unit cover each other's barriers.
+// KS = 2: eight wavefronts, two such halves that take every other step and add up through LDS at the end.  Workgroups are renumbered so that a
 // compute die (linear id modulo 8) works on neighbouring column blocks: the Q planes it needs stay in its own L2.
 // ---------------------------------------------------------------------------------------------
 struct SplitGemmArgs {
