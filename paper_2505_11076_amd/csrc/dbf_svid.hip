@@ -280,27 +280,30 @@ __global__ __launch_bounds__(256) void dbf_svid_col_dots_kernel(const float* __r
 // v_raw[j] = sum over chunks of partial[chunk][j]: sixteen interleaved running sums (chunks c = 0, 16, 32, ... in the
 // first, and so on), added up in order; and ss_part[workgroup] = sum of v_raw[j]^2 over the workgroup's 64 columns (butterfly
 // order).  Workgroup = 64 columns x the 16 running sums (one wavefront each, sixteen loads in flight: up to 256 chunks are one memory
-// round trip; with four sums and a load at a time 64 chunks took 6.6 us).
+// round trip; with four sums and a load at a time 64 chunks took 6.6 us).  Summed in 64 bits: up to 256 partial sums in 32 bits, against
+// 64 of the two passes, left m 20 % further from the exact factor (7.7e-8 against 6.5e-8 at 4096 x 4096, means of 12 inputs; 4.7e-8 with
+// these sums, 3.9e-8 with those of the last kernel too).  The 64-bit sums of both cost a call of 8 rounds 2.5 us of 154.
 constexpr int REDUCE_SUMS = 16;
 __global__ __launch_bounds__(64 * REDUCE_SUMS) void dbf_svid_col_reduce_kernel(const float* __restrict__ partial, int chunks, int cols,
                                                                float* __restrict__ v, float* __restrict__ ss_part) {
-    __shared__ float part[REDUCE_SUMS][64];
+    __shared__ double part[REDUCE_SUMS][64];
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int j = blockIdx.x * 64 + lane, jc = min(j, cols - 1);
-    float s = 0.f;
+    double s = 0.;
     for (int c0 = q; c0 < chunks; c0 += 16 * REDUCE_SUMS) {
         float p[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) p[i] = partial[(size_t)min(c0 + REDUCE_SUMS * i, chunks - 1) * cols + jc];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s += c0 + REDUCE_SUMS * i < chunks ? p[i] : 0.f;
+        for (int i = 0; i < 16; ++i) s += (double)(c0 + REDUCE_SUMS * i < chunks ? p[i] : 0.f);
     }
     part[q][lane] = s;
     __syncthreads();
     if (q == 0) {
-        float vj = part[0][lane];
+        double sum = part[0][lane];
 #pragma unroll
-        for (int i = 1; i < REDUCE_SUMS; ++i) vj += part[i][lane];
+        for (int i = 1; i < REDUCE_SUMS; ++i) sum += part[i][lane];
+        const float vj = (float)sum;
         if (j < cols) v[j] = vj;
         const float ss = wave_sum_f(j < cols ? vj * vj : 0.f);
         if (lane == 0) ss_part[blockIdx.x] = ss;
@@ -309,24 +312,33 @@ __global__ __launch_bounds__(64 * REDUCE_SUMS) void dbf_svid_col_reduce_kernel(c
 
 // The two factors from the unnormalised iterate: m = v_raw / ||v_raw|| (in place) and
 // a = sigma u = u_raw ||v_raw|| / ||u_raw||^2 (sigma = ||v_raw|| / ||u_raw||, u = u_raw / ||u_raw||).
-// Every workgroup forms both lengths itself, in the same fixed order, and then writes its 256 entries of each.
+// Every workgroup forms both lengths itself, in 64 bits and the same fixed order, and then writes its 256 entries of each.
 __global__ __launch_bounds__(256) void dbf_svid_finish_kernel(const float* __restrict__ u_raw, int rows,
                                                              const float* __restrict__ ss_part, int n_ss,
                                                              float* __restrict__ m, int cols, float* __restrict__ a) {
-    __shared__ float part[256];
-    float s = 0.f;
-    for (int i = threadIdx.x; i < rows; i += 256) s += u_raw[i] * u_raw[i];
+    __shared__ double part[256];
+    double s = 0.;
+    for (int i = threadIdx.x; i < rows; i += 256) s += (double)u_raw[i] * (double)u_raw[i];
     part[threadIdx.x] = s;
     __syncthreads();
     for (int w = 128; w >= 1; w >>= 1) {
         if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
         __syncthreads();
     }
-    const float ssu = part[0];
-    const float nv = sqrtf(wave_total(ss_part, n_ss, threadIdx.x & 63));
+    const double ssu = part[0];
+    __syncthreads();
+    s = 0.;
+    for (int i = threadIdx.x; i < n_ss; i += 256) s += (double)ss_part[i];
+    part[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = 128; w >= 1; w >>= 1) {
+        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+        __syncthreads();
+    }
+    const double nv = sqrt(part[0]);
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < rows) a[i] = ssu > 0.f ? u_raw[i] * (nv / ssu) : 0.f;
-    if (i < cols && nv > 0.f) m[i] = m[i] / nv;
+    if (i < rows) a[i] = ssu > 0. ? (float)(u_raw[i] * (nv / ssu)) : 0.f;
+    if (i < cols && nv > 0.) m[i] = (float)(m[i] / nv);
 }
 
 // Sign(Z) into the tile layout: tile = 128 rows x 64 columns, byte 256 g + 16 r + j, bit s = sign of
@@ -426,7 +438,7 @@ extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* 
     const int n_ss = (cols + 63) / 64;
 
     // One pass per round wherever rows can be held: up to 24576 columns in 16-byte pieces, 12288 in single values.  8 rounds, us, two
-    // passes / one: 4096 x 4096 247 / 154, 2048 x 4096 161 / 93, 8192 x 8192 (one pass before: 548) 472.
+    // passes / one: 4096 x 4096 247 / 157; before the 64-bit column sums 154, and 2048 x 4096 161 / 93, 8192 x 8192 (one pass before: 548) 472.
     const int cpl = (cols + 4095) / 4096;  // float4s per thread and row of a workgroup of 1024
     const bool one_pass = cpl <= (vec_ok ? 6 : 3);
     if (!(one_pass && cpl == 1 && vec_ok))   // (else the first pass writes the signs)
