@@ -64,7 +64,8 @@ enum {
 /* Which decode kernel dbf_gemv_kind runs. */
 enum {
     DBF_GEMV_AUTO = 0, /* what dbf_gemv uses.  A layer or a group whose stages have at most 256 workgroups (row tiles
-                          of 128 rows times groups of up to 8 batch rows): two launches at any batch, every
+                          of 128 rows times groups of up to 8 batch rows), no knob that steers the forms below
+                          having been set: two launches at any batch, every
                           workgroup rounding the stage input it needs, long rows cut into column pieces; one
                           launch for layers of at most 32 tiles (of 128 rows x 64 columns) a stage.
                           Else, batch 1: DBF_GEMV_MFMA for a group of layers whose B stage alone fills the
@@ -357,6 +358,9 @@ int dbf_probe_mfma(int wide, int with_ands, int wavefronts_per_simd, int iters, 
  * can be re-tuned on other shapes.  The library reads no environment variables.
  * A knob is read when a plan is built (dbf_pack*, dbf_prune_middle, dbf_stack_create*: the PLAN knobs)
  * or when a launch is issued (the LAUNCH knobs); changing one never affects plans that already exist.
+ * The knobs of the decode cuts and forms (all but DBF_TUNE_WAIT_LIMIT_US and DBF_TUNE_GEMM_SPLITS) steer work item
+ * lists that DBF_GEMV_AUTO uses where launches have more than 256 workgroups; a call of fewer takes those lists too
+ * if its plan was built under a PLAN knob off its default, or a LAUNCH knob is off its default when it is issued.
  * Not thread safe against concurrent pack / create / launch calls.
  *   dbf_tuning_set:   DBF_EINVAL for an unknown knob or a value outside the stated range.
  *   dbf_tuning_get:   the current value, or INT_MIN for an unknown knob.

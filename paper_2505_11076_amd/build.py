@@ -175,6 +175,25 @@ def build_sanitize_check(driver_cpp: str) -> str:
     return exe
 
 
+def build_route_recorder(runtime_cpp: str) -> str:
+    """Links the library's objects with `runtime_cpp`, a HIP runtime that records launches instead of making them, into a
+    shared library whose entry points can be called on a machine without a GPU (-Bsymbolic: its HIP calls are bound to
+    that runtime, whatever else is loaded).  Returns the path of the library."""
+    out_dir = os.path.join(OBJ, "routes")
+    os.makedirs(out_dir, exist_ok=True)
+    objs = [os.path.join(OBJ, os.path.splitext(s)[0] + ".o") for s in SOURCES]
+    newest = max(os.path.getmtime(os.path.join(d, f)) for d in (CSRC, os.path.join(HERE, "..", "include")) for f in os.listdir(d))
+    if not all(os.path.exists(o) and os.path.getmtime(o) >= newest for o in objs):
+        build(verbose=False)
+    lib = os.path.join(out_dir, "libdbf_routes.so")
+    cmd = ["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-Wl,-Bsymbolic", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+           "-Wno-deprecated-declarations", runtime_cpp, *objs, "-o", lib]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("route recorder:\n%s\n%s" % (res.stdout, res.stderr))
+    return lib
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as pool:

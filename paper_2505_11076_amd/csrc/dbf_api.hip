@@ -5,6 +5,7 @@
 #include <climits>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <new>
 #include <type_traits>
 #include <vector>
@@ -81,6 +82,13 @@ Knob g_knobs[DBF_TUNE_COUNT_] = {
     {256, 256, 0, 1 << 20},       // DBF_TUNE_WIDE_WG_MAX_ITEMS
     {256, 256, 0, 1 << 20},       // DBF_TUNE_FP4_MAX_ITEMS
 };
+
+// Whether all of these knobs have their defaults.
+bool at_default(std::initializer_list<int> knobs) {
+    for (int k : knobs)
+        if (g_knobs[k].value != g_knobs[k].def) return false;
+    return true;
+}
 
 // Column pieces.  Cutting pays only for long rows: every piece pays the workgroup's prologue (it reads
 // the whole input row for the quantisation scale) and the last piece an extra epilogue, which at 4096
@@ -276,6 +284,8 @@ void draft_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA
         }
         p->long_rows = lr == 1 || (lr < 0 && n > 1 && 2 * bytes_long > bytes_all);
     }
+    p->built_in_cuts = at_default({DBF_TUNE_COL_PIECES, DBF_TUNE_PIECE_TARGET, DBF_TUNE_PIECE_MIN_TILES, DBF_TUNE_PIECE_NEVER_TILES,
+                                   DBF_TUNE_PIECE_MAX_ROW_TILES, DBF_TUNE_STACK_SPAN_B, DBF_TUNE_STACK_SPAN_A, DBF_TUNE_LONG_ROWS});
     p->x_vec_ok = 1;
     for (int i = 0; i < n; ++i)
         if ((sB[i].cols & 7) != 0 || (sB[i].x_off & 7) != 0) p->x_vec_ok = 0;
@@ -693,10 +703,12 @@ int launch_plan(int kind, const DbfPlan& p, const void* x, void* y, int batch, h
     }
     const int FUSED_MIN_B_ITEMS = dbf_tune(DBF_TUNE_FUSED_MIN_B_ITEMS);
     // Few row tiles: workgroups that round their own input, at any batch (measured: dbf_few_takes).  What is left to the forms below
-    // are launches of more than 256 of them, longer inputs, named kinds and knobs.  Not where a knob names one of the other forms, nor
-    // for plans that quantise every input once per call (long_rows) or that the knob sends through the one launch.
-    if (kind == DBF_GEMV_AUTO && !p.long_rows && dbf_tune(DBF_TUNE_SHARED_Q) < 0 && dbf_tune(DBF_TUNE_SHARED_MIN_BATCH) <= (batch > 2 ? batch : 2) &&
-        !(p.n_layers > 1 && p.nB1 >= FUSED_MIN_B_ITEMS) && dbf_few_takes(p, false, batch) && dbf_few_takes(p, true, batch))
+    // are launches of more than 256 of them, longer inputs, plans that quantise every input once per call (long_rows), named
+    // kinds, and calls where a knob that steers those forms has been set: it would have nothing to steer here.
+    if (kind == DBF_GEMV_AUTO && !p.long_rows && p.built_in_cuts &&
+        at_default({DBF_TUNE_SHARED_Q, DBF_TUNE_SHARED_MIN_BATCH, DBF_TUNE_SHARED_LDS_KB, DBF_TUNE_FUSED_MIN_B_ITEMS, DBF_TUNE_WIDE_WG_MAX_ITEMS,
+                    DBF_TUNE_FP4_MAX_ITEMS}) &&
+        dbf_few_takes(p, false, batch) && dbf_few_takes(p, true, batch))
         return launch_few(p, x, y, batch, stream, mid);
     const bool pieces_ok = kind == DBF_GEMV_AUTO;  // the named kinds keep their one-workgroup-per-row-tile lists
     if (kind == DBF_GEMV_AUTO) kind = DBF_GEMV_MFMA_SPLIT;  // (until the list is known, below)

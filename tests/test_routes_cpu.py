@@ -1,0 +1,136 @@
+"""Which kernels a public call launches, and what device memory it takes, without a GPU: the library's objects linked with
+a HIP runtime that records (tests/route_recorder.cpp)."""
+import ctypes as C
+import os
+
+import numpy as np
+import pytest
+
+from paper_2505_11076_amd import binding as B
+from paper_2505_11076_amd import build as _build
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+class Recorder:
+    """The recording library; layers and stacks are plain handles."""
+
+    def __init__(self):
+        self.lib = C.CDLL(_build.build_route_recorder(os.path.join(ROOT, "tests", "route_recorder.cpp")))
+        for name in ("rec_take", "rec_last_block", "rec_held", "rec_memset_bytes", "dbf_gemm_workspace_bytes", "dbf_tiled_bytes"):
+            getattr(self.lib, name).restype = C.c_size_t
+        self.lib.rec_take.argtypes = [C.c_void_p, C.c_size_t]
+        self.lib.dbf_free.restype = self.lib.dbf_stack_free.restype = self.lib.dbf_tuning_reset.restype = None
+
+    def launches(self):
+        """[(kernel, grid, threads, dynamic LDS bytes)] since the last call."""
+        buf = C.create_string_buffer(self.lib.rec_take(None, 0) + 1)
+        self.lib.rec_take(buf, len(buf))
+        out = []
+        for line in buf.value.decode().splitlines():
+            name, gx, gy, gz, threads, lds = line.split()
+            name = name[name.index("dbf_"):]
+            out.append((name[:name.index("_kernel")], (int(gx), int(gy), int(gz)), int(threads), int(lds)))
+        return out
+
+    def layer(self, n_in, n_out, k):
+        """A layer with all signs -1 and zero scales: only its shape matters here."""
+        A = np.zeros((n_out, (k + 31) // 32), np.uint32)
+        Bw = np.zeros((k, (n_in + 31) // 32), np.uint32)
+        v = [np.zeros(n, np.uint16) for n in (n_out, k, n_in)]
+        h = C.c_void_p()
+        assert self.lib.dbf_pack_bits(n_in, n_out, k, *[C.c_void_p(a.ctypes.data) for a in (A, Bw, *v)], C.byref(h)) == 0
+        return h
+
+    def stack(self, layers):
+        h = C.c_void_p()
+        assert self.lib.dbf_stack_create((C.c_void_p * len(layers))(*[l.value for l in layers]), len(layers), C.byref(h)) == 0
+        return h
+
+    def gemv(self, layer, batch, offset=0, kind=B.GEMV_AUTO):
+        self.launches()
+        assert self.lib.dbf_gemv_kind(layer, C.c_void_p(4096 + offset), C.c_void_p(1 << 20), batch, kind, None) == 0
+        return self.launches()
+
+    def stack_gemv(self, stack, batch, kind=B.GEMV_AUTO):
+        self.launches()
+        assert self.lib.dbf_stack_gemv(stack, C.c_void_p(4096), C.c_void_p(1 << 20), batch, kind, None) == 0
+        return self.launches()
+
+
+@pytest.fixture(scope="module")
+def rec():
+    r = Recorder()
+    yield r
+    r.lib.dbf_tuning_reset()
+
+
+def _names(launches):
+    return [l[0] for l in launches]
+
+
+FEW = {"dbf_few", "dbf_small_layer"}
+
+
+@pytest.mark.parametrize("when,knob,value", [
+    ("plan", B.TUNE_COL_PIECES, 0), ("plan", B.TUNE_COL_PIECES, 3), ("plan", B.TUNE_PIECE_TARGET, 4096), ("plan", B.TUNE_PIECE_MIN_TILES, 2),
+    ("plan", B.TUNE_PIECE_NEVER_TILES, 0), ("plan", B.TUNE_PIECE_MAX_ROW_TILES, 16), ("plan", B.TUNE_STACK_SPAN_B, 3), ("plan", B.TUNE_STACK_SPAN_A, 2),
+    ("plan", B.TUNE_LONG_ROWS, 0),
+    ("launch", B.TUNE_SHARED_Q, 2), ("launch", B.TUNE_SHARED_MIN_BATCH, 1), ("launch", B.TUNE_SHARED_MIN_BATCH, 17), ("launch", B.TUNE_SHARED_LDS_KB, 40),
+    ("launch", B.TUNE_FUSED_MIN_B_ITEMS, 0), ("launch", B.TUNE_WIDE_WG_MAX_ITEMS, 0), ("launch", B.TUNE_FP4_MAX_ITEMS, 0)])
+def test_a_decode_knob_off_its_default_takes_the_forms_that_the_knobs_steer(rec, when, knob, value):
+    """Every knob of the decode cuts and forms is one of the item lists' (dbf.h): where one of them is set, a default call of
+    few workgroups -- a layer alone, a group, at any batch -- goes through those lists, and PLAN knobs stay with the plan that
+    was built under them."""
+    shapes = [(6000, 300, 520), (520, 700, 6000), (300, 200, 100)]
+    lib = rec.lib
+    lib.dbf_tuning_reset()
+    before = [rec.layer(*s) for s in shapes]
+    assert lib.dbf_tuning_set(knob, value) == 0
+    layers = [rec.layer(*s) for s in shapes]
+    stack = rec.stack(layers)
+    if when == "plan":
+        lib.dbf_tuning_reset()
+    try:
+        for batch in (1, 2, 7, 16):
+            for call, h in [(rec.gemv, l) for l in layers] + [(rec.stack_gemv, stack)]:
+                assert not FEW & set(_names(call(h, batch))), (batch, _names(call(h, batch)))
+        lib.dbf_tuning_reset()
+        for l in before:                       # (plans built at the defaults are not affected)
+            assert set(_names(rec.gemv(l, 1))) <= FEW
+        if when == "launch":
+            for l in layers:
+                assert set(_names(rec.gemv(l, 1))) <= FEW
+    finally:
+        lib.dbf_tuning_reset()
+        lib.dbf_stack_free(stack)
+        for l in layers + before:
+            lib.dbf_free(l)
+
+
+def test_knobs_steer_what_the_header_says(rec):
+    """Of the forms behind the knobs: no column piece with COL_PIECES = 0 (one workgroup per row tile), N pieces with N, once-per-call
+    quantisation from SHARED_MIN_BATCH on, eight wavefronts and the fp4 form by their item limits."""
+    lib = rec.lib
+    lib.dbf_tuning_reset()
+
+    def routes(plan, launch, batch, shape=(6000, 300, 520)):
+        for knob, value in plan + launch:
+            assert lib.dbf_tuning_set(knob, value) == 0
+        l = rec.layer(*shape)
+        try:
+            return rec.gemv(l, batch)
+        finally:
+            lib.dbf_tuning_reset()
+            lib.dbf_free(l)
+
+    k_tiles, out_tiles = 5, 3          # row tiles of the two stages
+    assert [l[1][0] for l in routes([(B.TUNE_COL_PIECES, 0)], [], 1)] == [k_tiles, out_tiles]
+    assert [l[1][0] for l in routes([(B.TUNE_COL_PIECES, 3)], [], 1)] == [3 * k_tiles, out_tiles]   # (8 tiles a piece: the short rows stay whole)
+    assert _names(routes([(B.TUNE_COL_PIECES, 0)], [(B.TUNE_SHARED_MIN_BATCH, 1)], 1)) == ["dbf_quantise_inputs", "dbf_items_mfma"] * 2
+    assert _names(routes([(B.TUNE_COL_PIECES, 0)], [(B.TUNE_SHARED_MIN_BATCH, 17)], 16)) == ["dbf_items_mfma"] * 2
+    square = (4096, 4096, 2048)
+    threads = lambda **kw: [l[2] for l in routes([], [(getattr(B, n), v) for n, v in kw.items()], 1, square)]   # noqa: E731
+    assert threads(TUNE_FP4_MAX_ITEMS=0) == [512, 512] and threads(TUNE_FP4_MAX_ITEMS=0, TUNE_WIDE_WG_MAX_ITEMS=0) == [256, 256]
+    lds = lambda **kw: [l[3] for l in routes([], [(getattr(B, n), v) for n, v in kw.items()], 1, square)]       # noqa: E731
+    assert lds(TUNE_WIDE_WG_MAX_ITEMS=1) != lds(TUNE_WIDE_WG_MAX_ITEMS=1, TUNE_FP4_MAX_ITEMS=0)                 # (its operand rows are the larger)
