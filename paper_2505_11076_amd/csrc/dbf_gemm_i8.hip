@@ -321,6 +321,86 @@ __global__ __launch_bounds__(256) void dbf_quantise_rows_block_kernel(const Quan
     }
 }
 
+// Rows of eight values and more that start anywhere, read twice (the second read hits in L2 or the last-level cache): a workgroup of 1024
+// threads has eight tokens, a wavefront every 16th column step of theirs, a token eight of its lanes.  So a wavefront's load is
+// whole cache lines of eight rows (128 bytes of fp16 each) and its store of a plane whole lines too (eight tokens x 16 bytes, four
+// times): what bounds the kernels above at many tokens is writing a line in eight pieces.  (Of a FROM_F32 row every column is there.)
+template <bool FROM_F32>
+__global__ __launch_bounds__(1024) void dbf_quantise_rows_twice_kernel(const QuantArgs a) {
+    constexpr int UN = 4;   // steps of a wavefront whose loads are in flight together
+    __shared__ __align__(16) float wmax[8][16];
+    __shared__ __align__(16) int wsum[8][16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, tau = lane >> 3;
+    const int token = 8 * blockIdx.x + tau, n_steps = a.kp >> 6;
+    const bool live = token < a.T;
+    const char* row = static_cast<const char*>(a.src) + (size_t)min(token, a.T - 1) * a.ld * (FROM_F32 ? 4 : 2);
+    // eight values of every step kt0 + 16 i (steps past the row: its last one again)
+    auto load = [&](int kt0, float (&u)[UN][8]) {
+        v4u r0[UN], r1[UN];
+#pragma unroll
+        for (int i = 0; i < UN; ++i) {
+            const int v = 8 * min(kt0 + 16 * i, n_steps - 1) + (lane & 7);
+            if (FROM_F32) {
+                r0[i] = *reinterpret_cast<const v4u*>(row + 32 * (size_t)v);
+                r1[i] = *reinterpret_cast<const v4u*>(row + 32 * (size_t)v + 16);
+            } else {
+                r0[i] = dbf_half8_load(reinterpret_cast<const uint16_t*>(row), v, a.cols);
+                r1[i] = *reinterpret_cast<const v4u*>(a.col_scale + 8 * (size_t)v);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < UN; ++i) {
+            const int v = 8 * min(kt0 + 16 * i, n_steps - 1) + (lane & 7);
+            if (FROM_F32) {
+                const v4f f0 = __builtin_bit_cast(v4f, r0[i]), f1 = __builtin_bit_cast(v4f, r1[i]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    u[i][e] = f0[e];
+                    u[i][4 + e] = f1[e];
+                }
+            } else {
+                const h8 xv = __builtin_bit_cast(h8, dbf_half8_place(r0[i], v, a.cols)), bv = __builtin_bit_cast(h8, r1[i]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) u[i][e] = (float)xv[e] * (float)bv[e];
+            }
+        }
+    };
+    float mx = 0.f;
+    for (int kt0 = w; kt0 < n_steps; kt0 += 16 * UN) {
+        float u[UN][8];
+        load(kt0, u);
+#pragma unroll
+        for (int i = 0; i < UN; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(u[i][e]));
+    }
+    mx = dbf_row8_max(mx);
+    if ((lane & 7) == 0) wmax[tau][w] = mx;
+    __syncthreads();
+    mx = 0.f;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) mx = fmaxf(mx, wmax[tau][q]);
+    const float inv = mx > 0.f ? QMAX / mx : 0.f;
+    int local = 0;
+    for (int kt0 = w; kt0 < n_steps; kt0 += 16 * UN) {
+        float u[UN][8];
+        load(kt0, u);
+#pragma unroll
+        for (int i = 0; i < UN; ++i)
+            if (live && kt0 + 16 * i < n_steps) local += quantise_store(a, token, 8 * (kt0 + 16 * i) + (lane & 7), u[i], inv);
+    }
+    local = dbf_row8_sum(local);
+    if ((lane & 7) == 0) wsum[tau][w] = local;
+    __syncthreads();
+    if (w == 0 && (lane & 7) == 0 && live) {
+        int sum = 0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) sum += wsum[tau][q];
+        a.scale[token] = mx / QMAX;
+        a.sigma[token] = sum;
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
 // One stage: out[token][row] = rscale[row] * scale[token] * sum_col sign(row, col) * q[token][col]
 // ---------------------------------------------------------------------------------------------
@@ -628,8 +708,13 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
     }
 }
 
-// The quantiser for a row length: rows held in registers where they can be read in 16-byte pieces (up to 4096 and up
-// to 12288 padded columns), else a wavefront or a workgroup per token that reads value by value / twice.
+// The quantiser for a row length: rows held in registers where they can be read in 16-byte pieces (up to 4096 and up to 12288 padded
+// columns); longer ones by a workgroup per token, or by eight tokens a workgroup where that gives 160 workgroups and the planes (48 MB
+// and more) are beyond the L2s, so that pieces of a line no longer meet there; and those that cannot be read in 16-byte pieces by the
+// latter too from 2049 columns on, below by a wavefront per token.
+// Launches, us, a workgroup per token / eight tokens: 28672 columns  1024 tokens 34 / 47   1280: 48 / 47   1536: 88 / 58   4096: 269 / 137;
+// 14336  1024: 17.7 / 26.2   1536: 26.1 / 28.4   2048: 39 / 31   4096: 95 / 64;   11007  777: 45 / 22   4096: 179 / 50;   a wavefront per token /
+// eight tokens: 4095  777: 14.3 / 12.0   4096: 59 / 21;   1001  777: 5.2 / 8.4   4096: 14.8 / 16.0.
 template <bool FROM_F32>
 void launch_quantise(const QuantArgs& q, size_t kp, int T, hipStream_t stream) {
     const bool straight = q.vec_ok && (q.cols & 7) == 0 && q.cols >= 8;
@@ -637,6 +722,8 @@ void launch_quantise(const QuantArgs& q, size_t kp, int T, hipStream_t stream) {
         hipLaunchKernelGGL((dbf_quantise_rows_held_kernel<FROM_F32, 2>), dim3(q.Tp / 4), dim3(1024), 0, stream, q);
     else if (straight && kp <= 12288)
         hipLaunchKernelGGL((dbf_quantise_rows_held_kernel<FROM_F32, 6>), dim3(q.Tp / 4), dim3(1024), 0, stream, q);
+    else if (straight ? T >= 1280 && T * kp >= 24u << 20 : kp > 2048)
+        hipLaunchKernelGGL(dbf_quantise_rows_twice_kernel<FROM_F32>, dim3(q.Tp / 8), dim3(1024), 0, stream, q);
     else if (kp <= 4096)
         hipLaunchKernelGGL(dbf_quantise_rows_kernel<FROM_F32>, dim3((T + 3) / 4), dim3(256), 0, stream, q);
     else

@@ -23,6 +23,17 @@ __device__ inline int dbf_row16_sum(int v) {
     v += dbf_dpp_move<0x124>(v);
     return v + dbf_dpp_move<0x128>(v);
 }
+// ... and of eight neighbouring lanes
+__device__ inline float dbf_row8_max(float v) {
+    v = fmaxf(v, __builtin_bit_cast(float, dbf_dpp_move<0xB1>(__builtin_bit_cast(int, v))));
+    v = fmaxf(v, __builtin_bit_cast(float, dbf_dpp_move<0x4E>(__builtin_bit_cast(int, v))));
+    return fmaxf(v, __builtin_bit_cast(float, dbf_dpp_move<0x141>(__builtin_bit_cast(int, v))));  // row_half_mirror
+}
+__device__ inline int dbf_row8_sum(int v) {
+    v += dbf_dpp_move<0xB1>(v);
+    v += dbf_dpp_move<0x4E>(v);
+    return v + dbf_dpp_move<0x141>(v);
+}
 __device__ inline float dbf_wave_max(float v) {
     v = dbf_row16_max(v);
     const int b = __builtin_bit_cast(int, v);
@@ -54,6 +65,24 @@ __device__ inline float dbf_wave_sum_f(float v) {
     const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 32));
     const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(b, 48));
     return (r0 + r1) + (r2 + r3);
+}
+
+// Eight fp16 values, columns 8 v .. + 7 of a row of `cols` values (8 at least) that starts at any even address, in one load: a vector
+// that reaches past the row's end is read as the row's last eight values.  dbf_half8_place moves what has arrived where it belongs,
+// zeros from column `cols` on (apart, so that a load has no use of its data right behind it).
+typedef unsigned int dbf_v4u __attribute__((ext_vector_type(4)));
+typedef unsigned int dbf_v4u_any __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ dbf_v4u dbf_half8_load(const uint16_t* row, int v, int cols) {
+    return *reinterpret_cast<const dbf_v4u_any*>(row + min(8 * v, cols - 8));
+}
+__device__ __forceinline__ dbf_v4u dbf_half8_place(dbf_v4u r, int v, int cols) {
+    const int past = 8 * v + 8 - cols;   // values of the vector that lie past the row
+    if ((cols & 7) != 0) {   // (a row of whole vectors has no part of one)
+        unsigned __int128 b = __builtin_bit_cast(unsigned __int128, r);
+        b >>= 16 * min(max(past, 0), 7);
+        r = __builtin_bit_cast(dbf_v4u, b);
+    }
+    return past < 8 ? r : (dbf_v4u){0, 0, 0, 0};
 }
 
 #endif  // DBF_WAVE_H

@@ -222,3 +222,30 @@ def test_prefill_kernels_by_size_equal_the_decode_kernels_bit_for_bit(shape):
     finally:
         B.dbf_tuning_reset()
         layer.close()
+
+
+@pytest.mark.parametrize("shape,T,offset", [((2049, 130, 70), 33, 0), ((2055, 130, 70), 70, 1), ((4104, 129, 65), 129, 1), ((12301, 200, 130), 65, 3),
+                                            ((12296, 130, 70), 1537, 0), ((16384, 64, 64), 1540, 0), ((100, 130, 12300), 1536, 0)])
+def test_rows_quantised_eight_tokens_a_workgroup(shape, T, offset):
+    """Long rows of many tokens, and rows that cannot be read in 16-byte pieces (x `offset` values off, columns no multiple of 8),
+    are rounded by workgroups of eight tokens: every remainder of the last vector of a row, token counts that end in the
+    middle of a workgroup, rows of fp16 and of the middle activations.  Integer sums: no tolerance."""
+    n_in, n_out, k = shape
+    L = I.make_layer(n_in, n_out, k, seed=I.seed_for(4, 170 + T))
+    X = I.make_activations(T, n_in, I.seed_for(4, 171 + T))
+    layer = G.pack(L)
+    try:
+        want = _decode_in_batches(layer, X)
+        G.say("start rounding n_in=%d n_out=%d k=%d T=%d offset %d" % (n_in, n_out, k, T, offset))
+        buf = torch.full((T * n_in + 8,), float("inf"), dtype=torch.float16, device="cuda")   # (what lies beside the rows must not count)
+        buf[offset:offset + T * n_in] = G.f16_to_dev(X).reshape(-1)
+        wsb = B.dbf_gemm_workspace_bytes(layer, T)
+        ws = torch.full((wsb,), 0x5A, dtype=torch.uint8, device="cuda")
+        y = torch.full((T, n_out), float("nan"), dtype=torch.float16, device="cuda")
+        B.dbf_tuning_set(B.TUNE_GEMM_SPLITS, 1)   # (always the kernels that take a quantised input)
+        B.dbf_gemm(layer, buf.data_ptr() + 2 * offset, y.data_ptr(), T, ws.data_ptr(), wsb, G.stream_handle(), B.GEMM_I8)
+        torch.cuda.synchronize()
+        assert np.array_equal(G.dev_to_f64(y), want)
+    finally:
+        B.dbf_tuning_reset()
+        layer.close()
