@@ -224,11 +224,6 @@ int shared_span(const DbfStage& st, long long stage_tiles) {
     return (int)(span > DBF_MAX_SPAN ? DBF_MAX_SPAN : span);
 }
 
-// Bytes of the sums and counters of column pieces (DbfPlan::d_few_acc) for stages of at most n_rt row tiles; 0: the plan has none.
-size_t few_acc_bytes(int n_rt) {
-    return n_rt <= DBF_FEW_MAX_ROW_TILES ? sizeof(int) * (size_t)n_rt * (DBF_MAX_BATCH * DBF_TILE_ROWS + DBF_PIECE_CNT_STRIDE) : 0;
-}
-
 void free_plan(DbfPlan& p) {
     if (p.dev_block) (void)hipFree(p.dev_block);
     p.dev_block = nullptr;
@@ -402,7 +397,9 @@ void draft_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA
     draft->o_ac = off = align_up(off + sizeof(unsigned long long) * (2 * (size_t)n + 1) * DBF_SYNC_STRIDE, 256);
     draft->o_cn = off = align_up(off + sizeof(int) * acc_ints, 256);
     draft->o_few = off = align_up(off + sizeof(int) * cnt_ints, 256);
-    draft->zero_bytes = align_up(off + few_acc_bytes((int)(rtB > rtA ? rtB : rtA)), 256);
+    // (sums and counters of the column pieces of dbf_gemv_few.hip, for plans that go there and have a stage that can be cut)
+    const size_t few_B = dbf_few_acc_bytes((int)rtB, p->max_cols_B), few_A = dbf_few_acc_bytes((int)rtA, p->max_cols_A);
+    draft->zero_bytes = align_up(off + (p->built_in_cuts && !p->long_rows ? (few_B > few_A ? few_B : few_A) : 0), 256);
     int nBp = 0;
     if (cut) {
         // (accumulators and counters as offsets in the zeroed memory, like everything else that is placed later)

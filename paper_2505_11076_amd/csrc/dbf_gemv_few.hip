@@ -605,6 +605,12 @@ bool dbf_few_takes(const DbfPlan& p, bool stage_a, int T) {
     return c.wgs <= FEW_MAX_WGS && (c.group < T ? c.group : T) * few_cols(p, stage_a) <= 2560;
 }
 
+size_t dbf_few_acc_bytes(int n_items, int max_cols) {
+    // (one token makes the fewest workgroups, so the rule cuts there if it cuts at all)
+    const bool cut = max_cols <= DBF_INT_PATH_MAX_COLS && few_cut(n_items, dbf_col_tiles(max_cols), 1, true).pieces > 1;
+    return cut ? sizeof(int) * (size_t)n_items * (DBF_MAX_BATCH * DBF_TILE_ROWS + DBF_PIECE_CNT_STRIDE) : 0;
+}
+
 hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y, float* t_over, int T, hipStream_t stream) {
     const hipError_t raised = dbf_few_prepare();
     if (raised != hipSuccess) return raised;

@@ -11,7 +11,6 @@
 #define DBF_SYNC_STRIDE 64  /* 64-bit words between the per-layer counters of a plan (DbfPlan::d_sync): 512 bytes, so
                               that polls of different counters spread over the memory channels */
 #define DBF_PIECES_MAX_BATCH 2  /* largest batch for which row tiles may be cut into column pieces */
-#define DBF_FEW_MAX_ROW_TILES 256 /* row tiles per stage up to which a plan holds DbfPlan::d_few_acc: 8.1 KiB each */
 #define DBF_PIECE_CNT_STRIDE 32 /* ints between the arrival counters of two row tiles: 128 bytes, a cache line each (side by side
                                    the finishing atomics of a launch's workgroups queued at one line: a 4096 x 11008 layer
                                    alone 18.1 -> 17.0 us, 4096 x 14336 19.2 -> 18.0) */
@@ -119,8 +118,8 @@ struct DbfPlan {
     int max_rt_A;               // row tiles of the largest A stage
     long long max_stage_tiles;  // sign tiles of the largest stage of a layer
     DbfStage h_stage_B, h_stage_A;  // the stages of the first layer (launches of a layer alone take them as arguments)
-    int* d_few_acc;             // plans of at most DBF_FEW_MAX_ROW_TILES row tiles per stage: zeroed sums and counters of column pieces
-                                // (dbf_gemv_few.hip), returned to zero by every launch; NULL otherwise
+    int* d_few_acc;             // plans with a stage that dbf_gemv_few.hip may cut: zeroed sums and counters of its column pieces, returned
+                                // to zero by every launch; NULL otherwise
 };
 
 struct dbf_layer {

@@ -47,6 +47,8 @@ hipError_t dbf_mfma_prepare();
 // rounding the stage input it needs.  dbf_few_takes: whether the stage is one for it.
 // t_over: the middle activations [T][t_stride], or NULL for the layers' own (T <= DBF_MAX_BATCH).
 bool dbf_few_takes(const DbfPlan& p, bool stage_a, int T);
+// Bytes of DbfPlan::d_few_acc for a stage of n_items row tiles: 8.1 KiB each, 0 if no call cuts its rows.
+size_t dbf_few_acc_bytes(int n_items, int max_cols);
 hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y, float* t_over, int T, hipStream_t stream);
 // Both stages of small layers in one launch, a workgroup per layer and pair of tokens; dbf_small_layer_takes: whether the plan's layers are.
 bool dbf_small_layer_takes(const DbfPlan& p, int T);

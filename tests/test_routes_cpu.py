@@ -156,3 +156,52 @@ def test_long_and_ragged_rows_of_many_tokens_are_not_written_in_pieces_of_cache_
         assert _names(rec.gemm(l, T, offset))[0] == "dbf_quantise_" + quantiser
     finally:
         rec.lib.dbf_free(l)
+
+
+def _layer_bytes(n_in, n_out, k):
+    """Signs, vectors and scratch of a layer, each section a multiple of 256 bytes: what its calls read and write."""
+    up = lambda v, a: (v + a - 1) // a * a   # noqa: E731
+    rows = lambda v: up(v, 128)              # noqa: E731
+    cols = lambda v: up(v, 64)               # noqa: E731
+    parts = [rows(n_out) * cols(k) // 8, rows(k) * cols(n_in) // 8, 2 * rows(n_out), 2 * rows(k), 2 * cols(n_in),
+             4 * 16 * rows(k), 128 + 32 * cols(n_in), 128 + 32 * cols(k)]
+    return sum(up(v, 256) for v in parts)
+
+
+def _tables_bound(n_in, n_out, k):
+    # counters, and per row tile the records of the item lists and two rows of sums of their column pieces
+    return 8192 + 3072 * ((n_out + 127) // 128 + (k + 127) // 128)
+
+
+@pytest.mark.parametrize("shape", [(64, 64, 32), (512, 512, 256), (4096, 4096, 2048), (4096, 11008, 4477), (5056, 4096, 3000), (4096, 28672, 2730)])
+def test_layers_and_stacks_whose_rows_are_never_cut_hold_no_sums_of_column_pieces(rec, shape):
+    """Sums of column pieces take 8.1 KiB per row tile (260 KiB beside the 2 MiB of a 4096 x 4096 layer of k = 2048): only a plan with
+    a stage that a call can cut -- 80 column tiles and more, 128 row tiles at most -- holds and clears them."""
+    rec.lib.dbf_tuning_reset()
+    cleared = rec.lib.rec_memset_bytes()
+    layers = [rec.layer(*shape) for _ in range(2)]
+    held, cleared = rec.lib.rec_last_block(), rec.lib.rec_memset_bytes() - cleared
+    stack = rec.stack(layers)
+    in_stack = rec.lib.rec_last_block()
+    try:
+        assert held <= _layer_bytes(*shape) + _tables_bound(*shape)
+        assert cleared <= 2 * (held - rec.lib.dbf_tiled_bytes(shape[1], shape[2]) - rec.lib.dbf_tiled_bytes(shape[2], shape[0]))
+        assert in_stack <= 2 * _tables_bound(*shape)
+        for batch in (1, 2, 16):
+            assert all(l[1][2] == 1 for l in rec.gemv(layers[0], batch) + rec.stack_gemv(stack, batch) if l[0] == "dbf_few")
+    finally:
+        rec.lib.dbf_stack_free(stack)
+        for l in layers:
+            rec.lib.dbf_free(l)
+
+
+@pytest.mark.parametrize("shape,cut", [((11008, 4096, 4477), (True, False)), ((28672, 8192, 12743), (True, True)), ((5120, 300, 100), (True, False)),
+                                       ((100, 300, 5120), (False, True))])
+def test_layers_whose_rows_can_be_cut_hold_the_sums(rec, shape, cut):
+    l = rec.layer(*shape)
+    try:
+        tiles = max(((v + 127) // 128) for v, c in zip((shape[2], shape[1]), cut) if c)
+        assert rec.lib.rec_last_block() >= _layer_bytes(*shape) + 8320 * tiles
+        assert tuple(x[1][2] > 1 for x in rec.gemv(l, 1)) == cut
+    finally:
+        rec.lib.dbf_free(l)
