@@ -453,8 +453,9 @@ void draft_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA
 }
 
 // Gives a draft its memory: `tables` (tables_bytes, filled by the caller with the returned image), `zero` (zero_bytes, zeroed by the
-// caller), both 256-byte aligned; stage_shift is added to the stages' addresses.
-std::vector<uint8_t> place_plan(PlanDraft& d, uint8_t* tables, uint8_t* zero, uintptr_t stage_shift, DbfPlan* p) {
+// caller), both 256-byte aligned; stage_shift is added to the addresses of the stages' signs and vectors, scratch_shift to those of
+// their scratch.
+std::vector<uint8_t> place_plan(PlanDraft& d, uint8_t* tables, uint8_t* zero, uintptr_t stage_shift, uintptr_t scratch_shift, DbfPlan* p) {
     auto moved = [](auto*& ptr, uintptr_t by) {
         using T = typename std::remove_reference<decltype(ptr)>::type;
         if (ptr) ptr = reinterpret_cast<T>(reinterpret_cast<uintptr_t>(ptr) + by);
@@ -464,16 +465,16 @@ std::vector<uint8_t> place_plan(PlanDraft& d, uint8_t* tables, uint8_t* zero, ui
             moved(st.bits, stage_shift);
             moved(st.in_scale, stage_shift);
             moved(st.row_scale, stage_shift);
-            moved(st.t, stage_shift);
-            moved(st.q_in, stage_shift);
+            moved(st.t, scratch_shift);
+            moved(st.q_in, scratch_shift);
         }
     for (std::vector<DbfItem>* list : {&d.items_n, &d.items_1, &d.items_s, &d.items_p})
         for (DbfItem& it : *list) {
             moved(it.bits, stage_shift);
             moved(it.in_scale, stage_shift);
             moved(it.row_scale, stage_shift);
-            moved(it.t, stage_shift);
-            moved(it.q_in, stage_shift);
+            moved(it.t, scratch_shift);
+            moved(it.q_in, scratch_shift);
             moved(it.acc, reinterpret_cast<uintptr_t>(zero));   // (NULL outside items_p; there never at offset 0)
             moved(it.cnt, reinterpret_cast<uintptr_t>(zero));
         }
@@ -523,7 +524,7 @@ int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA,
     if (e == hipSuccess) e = hipMalloc(&dev, draft.tables_bytes + draft.zero_bytes);
     if (e == hipSuccess) {
         uint8_t* d = static_cast<uint8_t*>(dev);
-        const std::vector<uint8_t> image = place_plan(draft, d, d + draft.tables_bytes, 0, p);
+        const std::vector<uint8_t> image = place_plan(draft, d, d + draft.tables_bytes, 0, 0, p);
         e = hipMemset(d + draft.tables_bytes, 0, draft.zero_bytes);
         if (e == hipSuccess) e = hipMemcpy(dev, image.data(), image.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -564,21 +565,22 @@ LayerOffsets layer_offsets(int n_in, int n_out, int k) {
 }
 
 // Makes a layer of the given shape on the current device: ONE allocation that holds its signs and vectors (left to the caller to fill),
-// its scratch and the zeroed memory of its launch plan, the plan's tables, and `extra_bytes` from `extra` (at *extra_dev).
-// Everything is queued on the null stream; the scratch is zeroed there.
+// the zeroed memory of its launch plan, its scratch, and the plan's tables.  `extra_bytes` from `extra` (4 k at most) go up with the
+// tables, to *extra_dev in the end of the scratch: there until the layer's first call.
+// Everything is queued on the null stream; the rest of the scratch is zeroed there.
 int create_layer(int n_in, int n_out, int k, const LayerOffsets& o, const void* extra, size_t extra_bytes, void** extra_dev, dbf_layer** out) {
     dbf_layer* L = new (std::nothrow) dbf_layer();
     if (!L) return DBF_ENOMEM;
     DbfStage& sb = L->h_stages[0];
     DbfStage& sa = L->h_stages[1];
-    auto place = [&](uint8_t* d) {
+    auto place = [&](uint8_t* d, uint8_t* scratch) {   // (scratch: where offset 0 would be if the block had nothing before it)
         L->dA = d + o.A;  L->dB = d + o.B;
         L->da = reinterpret_cast<uint16_t*>(d + o.a);
         L->dm = reinterpret_cast<uint16_t*>(d + o.m);
         L->db = reinterpret_cast<uint16_t*>(d + o.b);
-        L->dt = reinterpret_cast<float*>(d + o.t);
-        L->dqB = d + o.qB;
-        L->dqA = d + o.qA;
+        L->dt = reinterpret_cast<float*>(scratch + o.t);
+        L->dqB = scratch + o.qB;
+        L->dqA = scratch + o.qA;
         sb.bits = L->dB;  sb.in_scale = L->db;  sb.row_scale = L->dm;  sb.t = L->dt;  sb.q_in = L->dqB;
         sa.bits = L->dA;  sa.in_scale = nullptr;  sa.row_scale = L->da;  sa.t = L->dt;  sa.q_in = L->dqA;
     };
@@ -590,11 +592,12 @@ int create_layer(int n_in, int n_out, int k, const LayerOffsets& o, const void* 
     sa.rows = n_out;  sa.cols = k;  sa.t_stride = o.t_stride;  sa.pad_ = 0;
     // (drafted as if the block lay at DRAFT_BASE)
     constexpr uintptr_t DRAFT_BASE = 1 << 20;
-    place(reinterpret_cast<uint8_t*>(DRAFT_BASE));
+    place(reinterpret_cast<uint8_t*>(DRAFT_BASE), reinterpret_cast<uint8_t*>(DRAFT_BASE));
     // (the launch plan of a layer alone: one row tile per workgroup gives the most parallelism)
     PlanDraft draft;
     draft_plan(std::vector<DbfStage>(1, sb), std::vector<DbfStage>(1, sa), std::vector<int>(1, 1), std::vector<int>(1, 1), &draft);
-    const size_t o_zero = o.total, o_tables = o_zero + draft.zero_bytes, o_extra = o_tables + draft.tables_bytes, total = o_extra + extra_bytes;
+    const size_t o_zero = o.image_bytes, o_tables = o.total + draft.zero_bytes, total = o_tables + draft.tables_bytes;
+    const size_t upload = align_up(extra_bytes, 256);   // (the quantised input of the A stage, the scratch's last part, is 32 k and more)
     void* dev = nullptr;
     int device = 0;
     hipError_t e = prepare_kernels();
@@ -602,13 +605,15 @@ int create_layer(int n_in, int n_out, int k, const LayerOffsets& o, const void* 
     if (e == hipSuccess) e = hipMalloc(&dev, total);
     if (e == hipSuccess) {
         uint8_t* d = static_cast<uint8_t*>(dev);
-        place(d);
-        std::vector<uint8_t> image = place_plan(draft, d + o_tables, d + o_zero, reinterpret_cast<uintptr_t>(d) - DRAFT_BASE, &L->plan);
-        image.resize(draft.tables_bytes + extra_bytes);
-        if (extra_bytes) std::memcpy(image.data() + draft.tables_bytes, extra, extra_bytes);
-        if (extra_dev) *extra_dev = d + o_extra;
-        e = hipMemsetAsync(d + o.t, 0, o_tables - o.t, nullptr);
-        if (e == hipSuccess) e = hipMemcpy(d + o_tables, image.data(), image.size(), hipMemcpyHostToDevice);
+        place(d, d + draft.zero_bytes);
+        const uintptr_t shift = reinterpret_cast<uintptr_t>(d) - DRAFT_BASE;
+        std::vector<uint8_t> image(upload, 0);
+        if (extra_bytes) std::memcpy(image.data(), extra, extra_bytes);
+        const std::vector<uint8_t> tables = place_plan(draft, d + o_tables, d + o_zero, shift, shift + draft.zero_bytes, &L->plan);
+        image.insert(image.end(), tables.begin(), tables.end());
+        if (extra_dev) *extra_dev = d + o_tables - upload;
+        e = hipMemsetAsync(d + o_zero, 0, o_tables - upload - o_zero, nullptr);
+        if (e == hipSuccess) e = hipMemcpy(d + o_tables - upload, image.data(), image.size(), hipMemcpyHostToDevice);
     }
     if (e != hipSuccess) {
         (void)hipGetLastError();

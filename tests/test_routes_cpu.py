@@ -205,3 +205,20 @@ def test_layers_whose_rows_can_be_cut_hold_the_sums(rec, shape, cut):
         assert tuple(x[1][2] > 1 for x in rec.gemv(l, 1)) == cut
     finally:
         rec.lib.dbf_free(l)
+
+
+@pytest.mark.parametrize("shape,kept", [((64, 64, 32), 1), ((512, 300, 256), 200), ((4096, 4096, 2048), 1536), ((100, 300, 5120), 5119)])
+def test_a_pruned_layer_holds_what_a_packed_one_of_its_shape_holds(rec, shape, kept):
+    """The kept indices are there while the layer is made, not for its life."""
+    n_in, n_out, k = shape
+    rec.lib.dbf_tuning_reset()
+    l, same = rec.layer(*shape), rec.layer(n_in, n_out, kept)
+    want, held = rec.lib.rec_last_block(), rec.lib.rec_held()
+    keep = np.sort(np.random.default_rng(1).choice(k, kept, replace=False)).astype(np.int32)
+    pruned = C.c_void_p()
+    try:
+        assert rec.lib.dbf_prune_middle(l, C.c_void_p(keep.ctypes.data), kept, C.byref(pruned)) == 0
+        assert rec.lib.rec_held() - held == want
+    finally:
+        for h in (l, same, pruned):
+            rec.lib.dbf_free(h)
