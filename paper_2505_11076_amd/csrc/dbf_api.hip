@@ -622,7 +622,7 @@ int create_layer(int n_in, int n_out, int k, const LayerOffsets& o, const void* 
         return DBF_EHIP;
     }
     L->n_in = n_in;  L->n_out = n_out;  L->k = k;  L->device = device;
-    L->dev_block = dev;  L->device_bytes = o.total;
+    L->dev_block = dev;  L->device_bytes = total;
     *out = L;
     return DBF_OK;
 }

@@ -222,3 +222,16 @@ def test_a_pruned_layer_holds_what_a_packed_one_of_its_shape_holds(rec, shape, k
     finally:
         for h in (l, same, pruned):
             rec.lib.dbf_free(h)
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1), (512, 512, 256), (4096, 4096, 2048), (11008, 4096, 4477)])
+def test_dims_reports_all_the_device_memory_a_layer_holds(rec, shape):
+    """Launch plan and sums of column pieces included: they live in the layer's block."""
+    rec.lib.dbf_tuning_reset()
+    l = rec.layer(*shape)
+    try:
+        n = C.c_size_t()
+        assert rec.lib.dbf_dims(l, None, None, None, C.byref(n)) == 0
+        assert n.value == rec.lib.rec_last_block()
+    finally:
+        rec.lib.dbf_free(l)
