@@ -452,6 +452,9 @@ void draft_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA
     p->span = max_span;
 }
 
+// Zeroed memory of a plan that goes up with the tables: a memset costs as much as the upload of a few hundred KiB.
+constexpr size_t ZEROES_UPLOADED = 256 << 10;
+
 // Gives a draft its memory: `tables` (tables_bytes, filled by the caller with the returned image), `zero` (zero_bytes, zeroed by the
 // caller), both 256-byte aligned; stage_shift is added to the addresses of the stages' signs and vectors, scratch_shift to those of
 // their scratch.
@@ -460,25 +463,31 @@ std::vector<uint8_t> place_plan(PlanDraft& d, uint8_t* tables, uint8_t* zero, ui
         using T = typename std::remove_reference<decltype(ptr)>::type;
         if (ptr) ptr = reinterpret_cast<T>(reinterpret_cast<uintptr_t>(ptr) + by);
     };
-    for (std::vector<DbfStage>* stages : {&d.sB, &d.sA})
-        for (DbfStage& st : *stages) {
-            moved(st.bits, stage_shift);
-            moved(st.in_scale, stage_shift);
-            moved(st.row_scale, stage_shift);
-            moved(st.t, scratch_shift);
-            moved(st.q_in, scratch_shift);
-        }
-    for (std::vector<DbfItem>* list : {&d.items_n, &d.items_1, &d.items_s, &d.items_p})
-        for (DbfItem& it : *list) {
-            moved(it.bits, stage_shift);
-            moved(it.in_scale, stage_shift);
-            moved(it.row_scale, stage_shift);
-            moved(it.t, scratch_shift);
-            moved(it.q_in, scratch_shift);
-            moved(it.acc, reinterpret_cast<uintptr_t>(zero));   // (NULL outside items_p; there never at offset 0)
-            moved(it.cnt, reinterpret_cast<uintptr_t>(zero));
-        }
-    std::vector<uint8_t> image(d.tables_bytes, 0);
+    if (stage_shift || scratch_shift) {
+        for (std::vector<DbfStage>* stages : {&d.sB, &d.sA})
+            for (DbfStage& st : *stages) {
+                moved(st.bits, stage_shift);
+                moved(st.in_scale, stage_shift);
+                moved(st.row_scale, stage_shift);
+                moved(st.t, scratch_shift);
+                moved(st.q_in, scratch_shift);
+            }
+        for (std::vector<DbfItem>* list : {&d.items_n, &d.items_1, &d.items_s, &d.items_p})
+            for (DbfItem& it : *list) {
+                moved(it.bits, stage_shift);
+                moved(it.in_scale, stage_shift);
+                moved(it.row_scale, stage_shift);
+                moved(it.t, scratch_shift);
+                moved(it.q_in, scratch_shift);
+            }
+    }
+    for (DbfItem& it : d.items_p) {   // (never at offset 0, where NULL would be)
+        moved(it.acc, reinterpret_cast<uintptr_t>(zero));
+        moved(it.cnt, reinterpret_cast<uintptr_t>(zero));
+    }
+    std::vector<uint8_t> image;
+    image.reserve(d.tables_bytes + ZEROES_UPLOADED);
+    image.resize(d.tables_bytes, 0);
     auto put = [&](size_t at, const auto& v) {
         if (!v.empty()) std::memcpy(image.data() + at, v.data(), sizeof(v[0]) * v.size());
     };
@@ -524,8 +533,9 @@ int build_plan(const std::vector<DbfStage>& sB, const std::vector<DbfStage>& sA,
     if (e == hipSuccess) e = hipMalloc(&dev, draft.tables_bytes + draft.zero_bytes);
     if (e == hipSuccess) {
         uint8_t* d = static_cast<uint8_t*>(dev);
-        const std::vector<uint8_t> image = place_plan(draft, d, d + draft.tables_bytes, 0, 0, p);
-        e = hipMemset(d + draft.tables_bytes, 0, draft.zero_bytes);
+        std::vector<uint8_t> image = place_plan(draft, d, d + draft.tables_bytes, 0, 0, p);
+        if (draft.zero_bytes <= ZEROES_UPLOADED) image.resize(draft.tables_bytes + draft.zero_bytes, 0);
+        else e = hipMemsetAsync(d + draft.tables_bytes, 0, draft.zero_bytes, nullptr);
         if (e == hipSuccess) e = hipMemcpy(dev, image.data(), image.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipDeviceSynchronize();
     }
