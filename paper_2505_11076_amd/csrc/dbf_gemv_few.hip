@@ -651,7 +651,7 @@ hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y
 static size_t small_lds(const DbfPlan& p, int nb, int* planes, int* red_ints) {
     const int ct_b = dbf_col_tiles(p.max_cols_B), ct_a = dbf_col_tiles(p.max_cols_A), rt_b = dbf_row_tiles(p.max_cols_A);  // (rows of B: columns of A)
     *planes = (ct_b > ct_a ? ct_b : ct_a) * few_tile_block(2 * nb);
-    *red_ints = (rt_b + p.max_rt_A) * 2 * nb * FEW_RB;
+    *red_ints = ((rt_b + p.max_rt_A) * 2 * nb * FEW_RB + 3) & ~3;   // (the activations behind them are read in 16-byte pieces)
     return 2 * sizeof(FewMisc) + (size_t)*planes + 4 * (size_t)*red_ints + 4 * (size_t)nb * rt_b * DBF_TILE_ROWS;
 }
 static int small_group(int T) { return T < 2 ? 1 : 2; }

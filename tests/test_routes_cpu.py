@@ -253,3 +253,18 @@ def test_a_short_stack_is_made_by_one_upload(rec, n, shape):
         rec.lib.dbf_stack_free(stack)
         for l in layers:
             rec.lib.dbf_free(l)
+
+
+@pytest.mark.parametrize("shape", [(64, 64, 32), (65, 129, 63), (300, 100, 200), (128, 640, 64), (512, 512, 256)])
+def test_sections_of_a_small_layers_lds_are_read_where_they_are_aligned(rec, shape):
+    """The middle activations are the last section of the small-layer kernel's LDS and are read in 16-byte pieces; they and what lies
+    before the sums are multiples of 16 bytes, so they start on one if the whole is one (sums of an odd number of row tiles
+    for one token are not)."""
+    rec.lib.dbf_tuning_reset()
+    l = rec.layer(*shape)
+    try:
+        for batch in (1, 2, 3, 16):
+            (name, _, _, lds), = rec.gemv(l, batch)
+            assert name == "dbf_small_layer" and lds % 16 == 0, (batch, lds)
+    finally:
+        rec.lib.dbf_free(l)
