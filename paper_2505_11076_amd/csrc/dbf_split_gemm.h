@@ -92,12 +92,13 @@ __global__ __launch_bounds__(256) void dbf_split_signs_kernel(const uint8_t* __r
     const SgSite s = sg_site(K, SCALED ? 3 : 1);
     if (!s.live) return;
     const int i = min(s.i, (M + 127) / 128 * 128 - 1), ir = i & 127;
-    const uint2 b = *reinterpret_cast<const uint2*>(bits + ((size_t)(i >> 7) * n_ct + (s.k0 >> 6)) * DBF_TILE_BYTES +
-                                                    256 * ((s.k0 >> 4) & 3) + 16 * (ir & 15) + (s.k0 & 15));
+    const unsigned* b = reinterpret_cast<const unsigned*>(bits + ((size_t)(i >> 7) * n_ct + (s.k0 >> 6)) * DBF_TILE_BYTES +
+                                                          256 * ((s.k0 >> 4) & 3) + 16 * (ir & 15) + (s.k0 & 15));   // (a caller's: 4-byte aligned)
+    const unsigned b0 = b[0], b1 = b[1];
     float x[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const unsigned bit = ((e < 4 ? b.x : b.y) >> (8 * (e & 3) + (ir >> 4))) & 1u;
+        const unsigned bit = ((e < 4 ? b0 : b1) >> (8 * (e & 3) + (ir >> 4))) & 1u;
         float v = 1.f;
         if (SCALED) {
             const float c = kscale[min(s.k0 + e, K - 1)];

@@ -322,3 +322,36 @@ def test_admm_contractions_with_their_steps_and_blocks_cut_by_size(p, q, r):
     dev.step(rho, 1)
     Minv64, C64 = O.admm_constants(prob.B_dense, prob.W, rho)
     _check_step("update q=%d r=%d" % (q, r), state0, dev.host(), Minv64, C64, rho, 1, z_gate=2 * Z_GATE)
+
+
+@pytest.mark.parametrize("p,q,r", [(100, 70, 90), (520, 300, 260)])
+def test_sign_tiles_may_start_at_any_multiple_of_four_bytes(p, q, r):
+    """The packed signs of the constants and of an update are documented as 4-byte aligned: the same tiles 4, 8 and 12 bytes further on
+    give the same bits."""
+    rng = np.random.default_rng(I.seed_for(6, 900 + p))
+    S = np.where(rng.random((q, p)) < 0.5, -1.0, 1.0)
+    tiles = torch.from_numpy(B.dbf_tile_host(q, p, O.pack_signs(S)).copy()).cuda()
+    step = torch.from_numpy(B.dbf_tile_host(q, r, O.pack_signs(np.where(rng.random((q, r)) < 0.5, -1.0, 1.0))).copy()).cuda()
+    f = lambda *s: torch.from_numpy(rng.uniform(0.5, 1.5, s).astype(np.float32)).cuda()   # noqa: E731
+    m2, b, W, a, m, U = f(q), f(p), f(p, r), f(q), f(r), f(q, r)
+    wsb = max(B.dbf_admm_prepare_workspace_bytes(p, q, r), B.dbf_admm_workspace_bytes(q, r))
+    want = None
+    for off in (0, 4, 8, 12):
+        G.say("sign tiles %d bytes on, p=%d q=%d r=%d" % (off, p, q, r))
+        ws = torch.full((wsb,), 0xA5, dtype=torch.uint8, device="cuda")
+        moved = torch.zeros(tiles.numel() + 16, dtype=torch.uint8, device="cuda")
+        moved[off:off + tiles.numel()] = tiles
+        st = torch.zeros(step.numel() + 16, dtype=torch.uint8, device="cuda")
+        st[off:off + step.numel()] = step
+        Minv, C = torch.empty((q, q), device="cuda"), torch.empty((q, r), device="cuda")
+        a1, m1, U1 = a.clone(), m.clone(), U.clone()
+        B.dbf_admm_prepare(moved.data_ptr() + off, m2.data_ptr(), b.data_ptr(), W.data_ptr(), p, q, r, 1.0, Minv.data_ptr(), C.data_ptr(),
+                           ws.data_ptr(), wsb, 0, G.stream_handle())
+        B.dbf_admm_step(Minv.data_ptr(), C.data_ptr(), q, r, 1.0, 2, a1.data_ptr(), m1.data_ptr(), st.data_ptr() + off, U1.data_ptr(),
+                        ws.data_ptr(), wsb, G.stream_handle())
+        torch.cuda.synchronize()
+        got = [t.cpu().numpy().copy() for t in (Minv, C, a1, m1, U1, st[off:off + step.numel()])]
+        if want is None:
+            want = got
+        for g, w in zip(got, want):
+            assert np.array_equal(g.view(np.uint8), w.view(np.uint8)), off
