@@ -58,39 +58,38 @@ __device__ inline FewShare few_share(int nb, int w) {
 
 // The rows of a stage's input: fp16 x times b (B stage), or the fp32 middle activations, which are padded with zeros.  load()
 // requests the eight values of vector v of a row, get() turns what has arrived into numbers.
+// ANY: rows start at any even address and have any number of columns (in a kernel of its own: the code for it cost calls that do not
+// need it 3 %).  1024 x 1024, k = 512, batch 1, x two bytes off: 10.4 us read value by value and twice, 8.4 so; 4095 -> 4097 14.2 / 10.6.
 struct FewRaw {
     v4u a, b;
 };
+template <bool ANY>
 struct InputX {
     const uint16_t* x;   // first row of the group
     const uint16_t* b;   // zero padded to whole column tiles
     int cols;
-    bool fast;           // rows can be read in 16-byte pieces
     __device__ __forceinline__ void load(int bi, int v, FewRaw& r) const {
         const uint16_t* row = x + (size_t)bi * cols;
         r.b = *reinterpret_cast<const v4u*>(b + 8 * v);
-        if (fast) {
+        if (!ANY) {
             r.a = *reinterpret_cast<const v4u*>(row + (8 * v < cols ? 8 * v : 0));
-        } else {
-            uint16_t h[8];
+        } else if (cols >= 8) {
+            r.a = dbf_half8_load(row, v, cols);
+        } else {   // (the row's end in the vector's end, as dbf_half8_load has it)
+            unsigned h[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) h[e] = row[min(8 * v + e, cols - 1)];
+            for (int e = 0; e < 8; ++e) h[e] = row[max(e + cols - 8, 0)];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) r.a[e] = h[2 * e] | (unsigned)h[2 * e + 1] << 16;
+            for (int e = 0; e < 4; ++e) r.a[e] = h[2 * e] | h[2 * e + 1] << 16;
         }
     }
     __device__ __forceinline__ void get(int v, const FewRaw& r, float (&u)[8]) const {
-        const h8 xv = __builtin_bit_cast(h8, r.a), bv = __builtin_bit_cast(h8, r.b);
+        const h8 xv = __builtin_bit_cast(h8, ANY ? dbf_half8_place(r.a, v, cols) : r.a), bv = __builtin_bit_cast(h8, r.b);
+        const bool in = 8 * v < cols;   // (what lies past the row in its last vector is zero by now)
 #pragma unroll
         for (int e = 0; e < 8; ++e) u[e] = fmaf((float)xv[e], (float)bv[e], -0.f);  // (exact)
-        if (fast) {   // (then cols is a multiple of 8)
-            const bool in = 8 * v < cols;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) u[e] = in ? u[e] : 0.f;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) u[e] = 8 * v + e < cols ? u[e] : 0.f;
-        }
+        for (int e = 0; e < 8; ++e) u[e] = in ? u[e] : 0.f;
     }
 };
 struct InputT {
@@ -295,7 +294,7 @@ __device__ __forceinline__ uint16_t few_half(float v) {
 // sign tiles, everything a workgroup needs being kernel arguments that arrive in scalar registers (a layer alone: no memory round
 // trip before its loads).  io: x or y.  acc: zeroed integers, [row tile][DBF_MAX_BATCH][128], then an arrival counter per
 // (row tile, token group).
-template <bool STAGE_A, bool LIST, int H>
+template <bool STAGE_A, bool LIST, int H, bool ANY>
 __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_few_kernel(
     const void* __restrict__ first, const uint16_t* __restrict__ in_scale, const uint16_t* __restrict__ row_scale, float* __restrict__ t_base,
     uint16_t* __restrict__ io, int* __restrict__ acc_base, int cols_, int rows_, unsigned tokens, unsigned cut) {
@@ -330,12 +329,11 @@ __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     float* t = t_base + (size_t)t0 * stride;
     const FewShare sh = few_share(nb, w);
 
-    InputX inx;
+    InputX<ANY> inx;
     inx.x = io + (size_t)t0 * cols;  inx.b = in_scale;  inx.cols = cols;
-    inx.fast = (cols & 7) == 0 && (reinterpret_cast<uintptr_t>(inx.x) & 15) == 0;
     const InputT inp = {t, stride};
     const int mine = (nvec + 64 * sh.parts - 1) / (64 * sh.parts);
-    const bool held = mine <= H && ct1 - ct0 <= chunk_tiles && (STAGE_A || inx.fast);
+    const bool held = mine <= H && ct1 - ct0 <= chunk_tiles;
     const float rscale = (float)__builtin_bit_cast(_Float16, row_scale[tid & 127]);
     // The input is requested before the first tiles: loads complete in order, and the tiles come from farther away.
     FewRaw raw[H];
@@ -462,6 +460,7 @@ __device__ __forceinline__ void small_stage(const FewStream& st, const unsigned 
     if (ct != 0 && st.hi > st.lo) flush();
 }
 
+template <bool ANY>
 __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_small_layer_kernel(
     const DbfStage* __restrict__ stages_b, const DbfStage* __restrict__ stages_a, const uint16_t* __restrict__ x_base,
     uint16_t* __restrict__ y_base, int T, int group, int planes_bytes, int red_ints) {
@@ -480,9 +479,8 @@ __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     const FewShare sh = few_share(nb, w);
     constexpr int H = 2;
 
-    InputX inx;
+    InputX<ANY> inx;
     inx.x = x_base + sb.x_off * T + (size_t)t0 * sb.cols;  inx.b = sb.in_scale;  inx.cols = sb.cols;
-    inx.fast = (sb.cols & 7) == 0 && (reinterpret_cast<uintptr_t>(inx.x) & 15) == 0;
     FewRaw raw[H];
     const int nvec_b = 8 * sb.n_ct, nvec_a = 8 * sa.n_ct;
     {
@@ -541,12 +539,16 @@ constexpr int FEW_LDS = 156 * 1024;  // (its registers give a workgroup the comp
 hipError_t raise_lds(const void* kernel) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FEW_LDS); }
 template <int H>
 hipError_t raise_lds_few() {
-    hipError_t e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, false, H>));
-    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, true, H>));
-    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<true, false, H>));
-    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<true, true, H>));
+    hipError_t e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, false, H, false>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, true, H, false>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, false, H, true>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, true, H, true>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<true, false, H, false>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<true, true, H, false>));
     return e;
 }
+// Whether every x row of a call can be read in 16-byte pieces.
+bool rows_aligned(const DbfPlan& p, const void* x) { return p.x_vec_ok && (reinterpret_cast<uintptr_t>(x) & 15) == 0; }
 
 // Tokens per workgroup and column pieces of a stage of n_items row tiles.  As many workgroups as there are compute units, and no
 // more: a second one on a compute unit costs a whole round (its registers allow one).  Fewer tokens per workgroup first -- less
@@ -578,7 +580,8 @@ inline int few_cols(const DbfPlan& p, bool stage_a) { return dbf_col_tiles(stage
 // More than 64 KiB of LDS per workgroup has to be asked for, once per process (see dbf_mfma_prepare).
 hipError_t dbf_few_prepare() {
     static const hipError_t raised = [] {
-        const hipError_t e[] = {raise_lds(reinterpret_cast<const void*>(&dbf_small_layer_kernel)), raise_lds_few<2>(), raise_lds_few<4>(),
+        const hipError_t e[] = {raise_lds(reinterpret_cast<const void*>(&dbf_small_layer_kernel<false>)),
+                                raise_lds(reinterpret_cast<const void*>(&dbf_small_layer_kernel<true>)), raise_lds_few<2>(), raise_lds_few<4>(),
                                 raise_lds_few<6>(), raise_lds_few<8>(), raise_lds_few<10>()};
         for (hipError_t x : e)
             if (x != hipSuccess) {
@@ -634,8 +637,9 @@ hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y
     auto launch = [&](auto h) {
         constexpr int H = decltype(h)::value;
         void (*kernel)(const void*, const uint16_t*, const uint16_t*, float*, uint16_t*, int*, int, int, unsigned, unsigned) =
-            stage_a ? (list ? dbf_few_kernel<true, true, H> : dbf_few_kernel<true, false, H>)
-                    : (list ? dbf_few_kernel<false, true, H> : dbf_few_kernel<false, false, H>);
+            stage_a ? (list ? dbf_few_kernel<true, true, H, false> : dbf_few_kernel<true, false, H, false>)
+            : rows_aligned(p, x) ? (list ? dbf_few_kernel<false, true, H, false> : dbf_few_kernel<false, false, H, false>)
+                                 : (list ? dbf_few_kernel<false, true, H, true> : dbf_few_kernel<false, false, H, true>);
         hipLaunchKernelGGL(kernel, grid, dim3(FEW_THREADS), lds, stream, first, s.in_scale, s.row_scale, t, io, p.d_few_acc, s.cols,
                            list ? n_items : s.rows, tokens, cut);
     };
@@ -670,7 +674,7 @@ hipError_t dbf_launch_small_layers(const DbfPlan& p, const void* x, void* y, int
     const int group = small_group(T);
     int planes, red;
     const size_t lds = small_lds(p, group, &planes, &red);
-    hipLaunchKernelGGL(dbf_small_layer_kernel, dim3(p.n_layers, (T + group - 1) / group), dim3(FEW_THREADS), lds, stream, p.d_stagesB, p.d_stagesA,
+    hipLaunchKernelGGL(rows_aligned(p, x) ? dbf_small_layer_kernel<false> : dbf_small_layer_kernel<true>, dim3(p.n_layers, (T + group - 1) / group), dim3(FEW_THREADS), lds, stream, p.d_stagesB, p.d_stagesA,
                        static_cast<const uint16_t*>(x), static_cast<uint16_t*>(y), T, group, planes, red);
     return hipGetLastError();
 }

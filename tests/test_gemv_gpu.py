@@ -817,7 +817,7 @@ def test_one_launch_calls_may_switch_between_the_lists_of_a_plan():
             l.close()
 
 
-@pytest.mark.parametrize("shape", [(1, 1, 1), (64, 128, 64), (65, 129, 63), (513, 500, 500), (1024, 256, 256), (129, 1024, 250), (520, 1000, 300), (1023, 257, 511), (4104, 300, 4160),
+@pytest.mark.parametrize("shape", [(1, 1, 1), (5, 300, 40), (7, 1200, 130), (9, 20, 8), (64, 128, 64), (65, 129, 63), (513, 500, 500), (1024, 256, 256), (129, 1024, 250), (520, 1000, 300), (1023, 257, 511), (4104, 300, 4160),
                                    (5184, 130, 5120), (12296, 260, 900), (900, 200, 12300)])
 def test_launches_of_few_workgroups_equal_the_two_launch_kind_bit_for_bit(shape):
     """The default kind on a layer alone and on a group of three: workgroups that round their own input, with the values held in

@@ -25,12 +25,14 @@ class Recorder:
 
     def launches(self):
         """[(kernel, grid, threads, dynamic LDS bytes)] since the last call."""
+        self.full_names = []
         buf = C.create_string_buffer(self.lib.rec_take(None, 0) + 1)
         self.lib.rec_take(buf, len(buf))
         out = []
         for line in buf.value.decode().splitlines():
             name, gx, gy, gz, threads, lds = line.split()
             name = name[name.index("dbf_"):]
+            self.full_names.append(name)
             out.append((name[:name.index("_kernel")], (int(gx), int(gy), int(gz)), int(threads), int(lds)))
         return out
 
@@ -266,5 +268,20 @@ def test_sections_of_a_small_layers_lds_are_read_where_they_are_aligned(rec, sha
         for batch in (1, 2, 3, 16):
             (name, _, _, lds), = rec.gemv(l, batch)
             assert name == "dbf_small_layer" and lds % 16 == 0, (batch, lds)
+    finally:
+        rec.lib.dbf_free(l)
+
+
+@pytest.mark.parametrize("shape,offset,any_rows", [((4096, 4096, 2048), 0, False), ((4096, 4096, 2048), 2, True), ((4095, 4097, 2047), 0, True),
+                                                   ((512, 512, 256), 0, False), ((512, 512, 256), 2, True), ((5, 40, 9), 0, True)])
+def test_rows_that_cannot_be_read_in_16_byte_pieces_have_kernels_of_their_own(rec, shape, offset, any_rows):
+    """... which read them in as few loads and hold them as the others do (calls of 768-1024 columns with a misaligned x had become 8 %
+    slower than the launches before them), and the others do without the code for it."""
+    rec.lib.dbf_tuning_reset()
+    l = rec.layer(*shape)
+    try:
+        for batch in (1, 8):
+            first = rec.gemv(l, batch, offset)[0][0]
+            assert first in FEW and rec.full_names[0].split("EEv")[0].rstrip("E").endswith("Lb1" if any_rows else "Lb0"), rec.full_names
     finally:
         rec.lib.dbf_free(l)
