@@ -601,11 +601,19 @@ hipError_t dbf_few_prepare() {
 //   28672 -> 8192, k = 12743                             36.5 / 58.0 / 60.3 / 68.9 -> 21.0 / 26.8 / 47.3 / (71.0: 8 x 448 column tiles)
 //   512 x 512, k = 256                                    8.3 / 12.3 / 13.4 / 16.4 ->  7.6 /  8.0 /  8.1 /  8.3
 //   two of 4096 -> 11008, k = 4477 at batch 16           23.1 -> (29.0: 344 workgroups)
+// Nor is a group of layers taken whose workgroups would have more than four tokens of whole rows that are longer than the registers hold
+// (80 column tiles; 128 where two groups of tokens share a call): every workgroup reads them twice by one wavefront a row, which
+// the launches that round each layer's input once for all of its row tiles do in less.  Means over groups of 3-6 layers, against those
+// launches: up to 8 tokens  80 column tiles 0.85 (26 calls)   96: 1.02 (12)   128: 1.07 (6)   172: 1.12 (6);   9-16 tokens  128: 0.91 (14)
+// 144: 1.00 (17)   172: 1.02 (10)   224: 1.07 (4)   313: 1.12 (4).  Layers alone win throughout (0.67-0.92: few rows to round in those launches).
 bool dbf_few_takes(const DbfPlan& p, bool stage_a, int T) {
     const int longest = p.max_cols_B > p.max_cols_A ? p.max_cols_B : p.max_cols_A;
     if (longest > DBF_INT_PATH_MAX_COLS) return false;
-    const FewCut c = few_cut(stage_a ? p.nA1 : p.nB1, few_cols(p, stage_a), T, false);
-    return c.wgs <= FEW_MAX_WGS && (c.group < T ? c.group : T) * few_cols(p, stage_a) <= 2560;
+    const int n_items = stage_a ? p.nA1 : p.nB1, n_ct = few_cols(p, stage_a);
+    const FewCut c = few_cut(n_items, n_ct, T, p.d_few_acc && T <= DBF_MAX_BATCH);
+    const int nb = c.group < T ? c.group : T;
+    if (c.wgs > FEW_MAX_WGS || nb * n_ct > 2560) return false;
+    return !(p.n_layers > 1 && nb > 4 && c.pieces == 1 && n_ct > (T > 8 ? 128 : 80));
 }
 
 size_t dbf_few_acc_bytes(int n_items, int max_cols) {
