@@ -344,7 +344,7 @@ def main():
 
     # ---- practical HBM read ceiling: a plain streaming read of 1 GiB ---------------------------
     if not args.stream_only:
-        ceiling = read_ceiling(B, torch, stream)
+        ceiling = read_ceiling(B, torch, stream, proto)
         out["hbm_read_ceiling_GBps"] = round(ceiling, 1)
         out["frac_of_read_ceiling"] = round(value / ceiling, 4)
         out["roofline"]["frac_of_read_ceiling"] = round(achieved / ceiling, 4)
@@ -845,20 +845,15 @@ def isolated_latency(B, torch, np, layer, xs, ys, batch, stream, kind):
             "note": "one layer, cache warm, launch bound"}
 
 
-def read_ceiling(B, torch, stream):
+def read_ceiling(B, torch, stream, proto):
+    """GB/s of a plain read of 1 GiB: the best of three measurements after a settle phase each, like every other rate here
+    (five reads right after the fill once fell into the clock's transient after idle: 80 GB/s, and 75 times that as the stream's
+    share of it)."""
     probe = torch.empty(1 << 30, dtype=torch.uint8, device="cuda")
     probe.random_(0, 255)
     sink = torch.zeros(1, dtype=torch.int32, device="cuda")
-    for _ in range(2):
-        B.dbf_probe_read(probe.data_ptr(), probe.numel(), sink.data_ptr(), stream)
-    torch.cuda.synchronize()
-    p0, p1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    p0.record()
-    for _ in range(5):
-        B.dbf_probe_read(probe.data_ptr(), probe.numel(), sink.data_ptr(), stream)
-    p1.record()
-    torch.cuda.synchronize()
-    return probe.numel() * 5 / (p0.elapsed_time(p1) * 1e-3) / 1e9
+    ms = min(proto.run(lambda: B.dbf_probe_read(probe.data_ptr(), probe.numel(), sink.data_ptr(), stream))[0] for _ in range(3))
+    return probe.numel() / (ms * 1e-3) / 1e9
 
 
 def prefill_bench(B, I, torch, np, stream, proto):
