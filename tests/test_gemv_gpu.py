@@ -361,9 +361,10 @@ def test_stack_call_replayed_from_a_captured_graph(batch):
 def test_column_pieces_equal_whole_rows_bit_for_bit(batch):
     """Launches with few row tiles cut long rows into column pieces that add exact integer sums into
     per-row accumulators; the last piece scales and stores.  Every piece quantises with the scale of
-    the whole row, so the result must equal the uncut launch bit for bit -- for a layer alone (two
-    launches), for a short stack (one launch, the finishing piece publishes the row tile), with
-    pieces forced onto short rows, and on repeated calls (accumulators and counters are left at zero)."""
+    the whole row, so the result must equal the uncut launch bit for bit -- for a layer alone and for a
+    short stack, with pieces forced onto short rows, and on repeated calls (accumulators and counters are left at zero).
+    The knobs send the calls to the item lists, whole or in pieces; the default rule sends them to the workgroups that
+    round their own input, which cut by a rule of their own (tests/test_routes_cpu.py holds which call goes where)."""
     shapes = [(6000, 300, 520), (520, 700, 6000), (4100, 260, 4500)]
     Ls = [I.make_layer(n_in, n_out, k, seed=I.seed_for(5, 970 + i)) for i, (n_in, n_out, k) in enumerate(shapes)]
     Xs = [I.make_activations(batch, L.n_in, I.seed_for(5, 980 + i)) for i, L in enumerate(Ls)]
@@ -410,6 +411,25 @@ def test_column_pieces_equal_whole_rows_bit_for_bit(batch):
     for L, X, y_bits in zip(Ls, Xs, whole[:3]):
         G.check(O.f16_bits_to_f64(y_bits.view(np.uint16)).reshape(batch, L.n_out), O.forward_from_packed(X, L, "staged"),
                 "whole rows %dx%d" % (L.n_out, L.n_in))
+
+
+@pytest.mark.parametrize("shape,batch", [((256, 33000, 4200), 1), ((9000, 200, 33100), 1), ((4200, 40000, 5000), 1)])
+def test_column_pieces_by_the_default_rule_equal_whole_rows_bit_for_bit(shape, batch):
+    """Plans of 257 to 768 row tiles a stage keep the item lists by default, at batch 1 with their long rows in pieces: two launches, the
+    pieces of the A stage, of the B stage (k = 33100: 259 row tiles) and of both, against the kind that cuts no rows; twice, so
+    that sums and counters left over would show."""
+    n_in, n_out, k = shape
+    L = I.make_layer(n_in, n_out, k, seed=I.seed_for(5, 1350 + k))
+    X = I.make_activations(batch, n_in, I.seed_for(5, 1351))
+    layer = G.pack(L)
+    try:
+        G.say("default pieces n_in=%d n_out=%d k=%d" % shape)
+        want = G.run_gemv(layer, X, B.GEMV_MFMA_SPLIT)
+        for rep in range(2):
+            assert np.array_equal(G.run_gemv(layer, X, B.GEMV_AUTO), want), rep
+        assert B.dbf_sync_timeouts(layer) == 0
+    finally:
+        layer.close()
 
 
 @pytest.mark.parametrize("batch", [1, 3, 4])
@@ -468,7 +488,8 @@ def test_fp4_sign_operands_equal_the_int8_form_bit_for_bit():
     and the stage input as four signed hexadecimal digits in bf6; the sums are integers below 2^24 in fp32, so the
     result must be the int8 form's bit for bit: a layer alone, stacks in one launch and in two, launches larger than
     the rule would give this form (by the knob), repeated calls, and an x that cannot be read in 16-byte pieces
-    (which takes the int8 form whatever the knob says)."""
+    (which takes the int8 form whatever the knob says).  (Off its default the knob keeps calls of few workgroups on these
+    lists.)"""
     shapes = [(4096, 600, 2100), (2304, 520, 4096), (4096, 300, 2056), (2048, 1000, 3000)]
     Ls = [I.make_layer(n_in, n_out, k, seed=I.seed_for(5, 1300 + i)) for i, (n_in, n_out, k) in enumerate(shapes)]
     Xs = [I.make_activations(1, L.n_in, I.seed_for(5, 1310 + i)) for i, L in enumerate(Ls)]
@@ -821,9 +842,9 @@ def test_one_launch_calls_may_switch_between_the_lists_of_a_plan():
                                    (5184, 130, 5120), (12296, 260, 900), (900, 200, 12300)])
 def test_launches_of_few_workgroups_equal_the_two_launch_kind_bit_for_bit(shape):
     """The default kind on a layer alone and on a group of three: workgroups that round their own input, with the values held in
-    registers (2, 4 or 8 vectors per lane) or read twice, one row tile whole or in column pieces (80 column tiles and more), in one
-    chunk of LDS or several, 2 to 8 batch rows per workgroup; layers of up to 32 tiles a stage in one launch.  Every batch, an x that can be read in 16-byte pieces
-    and one that cannot, two calls in a row (the pieces' sums must be left at zero).  Integer sums: no tolerance."""
+    registers (2 to 10 vectors per lane) or read twice, one row tile whole or in column pieces (80 column tiles and more),
+    2 to 8 batch rows per workgroup; layers of up to 32 tiles a stage in one launch.  Every batch, an x that can be read in
+    16-byte pieces and one that cannot, two calls in a row (the pieces' sums must be left at zero).  Integer sums: no tolerance."""
     n_in, n_out, k = shape
     Ls = [I.make_layer(n_in, n_out, k, seed=I.seed_for(6, 700 + i + k)) for i in range(3)]
     layers = [G.pack(L) for L in Ls]
@@ -850,6 +871,35 @@ def test_launches_of_few_workgroups_equal_the_two_launch_kind_bit_for_bit(shape)
                     want = run(call, n, B.GEMV_MFMA_SPLIT)
                     for rep in range(2):
                         assert np.array_equal(run(call, n, B.GEMV_AUTO), want), (what, n, rep)
+    finally:
+        stack.close()
+        for l in layers:
+            l.close()
+
+
+@pytest.mark.parametrize("shapes,batch", [([(9000, 300, 16700)], 8), ([(12000, 300, 16520)], 6), ([(300, 16700, 14100)], 5), ([(10301, 256, 16520)], 7),
+                                          ([(18000, 64, 3000)] * 3, 8), ([(64, 16500, 17300), (64, 64, 64)], 4)])
+def test_few_workgroups_with_rows_of_several_lds_chunks(shapes, batch):
+    """Rows that the LDS of a workgroup does not hold for its tokens (138 column tiles for eight of them, 268 for four) are rounded and
+    multiplied chunk by chunk: of the B stage and of the A stage, of a layer alone and of a list, whose other layers' rows may fit.
+    That these calls take those kernels is checked on the CPU (tests/test_routes_cpu.py)."""
+    Ls = [I.make_layer(*s, seed=I.seed_for(6, 880 + i + s[2])) for i, s in enumerate(shapes)]
+    layers = [G.pack(L) for L in Ls]
+    stack = B.dbf_stack_create(layers)
+    try:
+        Xs = [I.make_activations(batch, L.n_in, I.seed_for(6, 890 + batch + i)) for i, L in enumerate(Ls)]
+        x_all = torch.cat([G.f16_to_dev(X).reshape(-1) for X in Xs])
+        outs = []
+        for kind in (B.GEMV_MFMA_SPLIT, B.GEMV_AUTO, B.GEMV_AUTO):
+            G.say("several chunks %s batch %d kind %d" % (shapes[0], batch, kind))
+            y = torch.full((batch * sum(L.n_out for L in Ls),), float("nan"), dtype=torch.float16, device="cuda")
+            if len(layers) == 1:
+                B.dbf_gemv(layers[0], x_all.data_ptr(), y.data_ptr(), batch, G.stream_handle(), kind)
+            else:
+                B.dbf_stack_gemv(stack, x_all.data_ptr(), y.data_ptr(), batch, G.stream_handle(), kind)
+            torch.cuda.synchronize()
+            outs.append(y.cpu().view(torch.int16).numpy())
+        assert np.array_equal(outs[1], outs[0]) and np.array_equal(outs[2], outs[0])
     finally:
         stack.close()
         for l in layers:

@@ -302,3 +302,35 @@ def test_groups_of_layers_with_many_tokens_of_long_rows_round_them_once(rec, n, 
         rec.lib.dbf_stack_free(stack)
         for l in layers:
             rec.lib.dbf_free(l)
+
+
+@pytest.mark.parametrize("shapes,batch,stage", [([(9000, 300, 16700)], 8, 0), ([(12000, 300, 16520)], 6, 0), ([(300, 16700, 14100)], 5, 1),
+                                                ([(10301, 256, 16520)], 7, 0), ([(18000, 64, 3000)] * 3, 8, 0), ([(64, 16500, 17300), (64, 64, 64)], 4, 1)])
+def test_rows_of_several_lds_chunks_go_to_the_few_workgroup_kernels(rec, shapes, batch, stage):
+    """The calls of test_few_workgroups_with_rows_of_several_lds_chunks: with less LDS than the whole rows of their tokens would take."""
+    rec.lib.dbf_tuning_reset()
+    layers = [rec.layer(*s) for s in shapes]
+    stack = rec.stack(layers)
+    try:
+        launches = rec.gemv(layers[0], batch) if len(layers) == 1 else rec.stack_gemv(stack, batch)
+        assert _names(launches) == ["dbf_few"] * 2
+        _, (_, groups, pieces), _, lds = launches[stage]
+        tokens = -(-batch // groups)
+        planes = lds - 656 - 2 * tokens * 129 * 4          # (LDS before and behind the operand planes)
+        assert pieces == 1 and planes < (shapes[0][0 if stage == 0 else 2] + 63) // 64 * (2 * tokens + 1) * 64
+    finally:
+        rec.lib.dbf_stack_free(stack)
+        for l in layers:
+            rec.lib.dbf_free(l)
+
+
+@pytest.mark.parametrize("shape", [(256, 33000, 4200), (9000, 200, 33100), (4200, 40000, 5000)])
+def test_plans_of_257_to_768_row_tiles_keep_their_column_pieces(rec, shape):
+    rec.lib.dbf_tuning_reset()
+    l = rec.layer(*shape)
+    try:
+        launches = rec.gemv(l, 1)
+        assert _names(launches) == ["dbf_items_mfma"] * 2
+        assert sum(x[1][0] for x in launches) > (shape[1] + 127) // 128 + (shape[2] + 127) // 128
+    finally:
+        rec.lib.dbf_free(l)
