@@ -733,9 +733,10 @@ int launch_plan(int kind, const DbfPlan& p, const void* x, void* y, int batch, h
     }
     // several row tiles per workgroup only if all columns of both stages fit one LDS chunk
     const int max_cols = p.max_cols_B > p.max_cols_A ? p.max_cols_B : p.max_cols_A;
-    // (column pieces: beyond 256 row tiles, or where a knob keeps a call from the above; at batch 2 only for a layer or three.  Wide rows, us per call with / without pieces at
-    //  batch 2: 1 layer of 11008 -> 4096 23.5 / 26.8, 3 layers 26.9 / 27.0, 4 layers 27.8 / 24.6, 8: 31.3 / 26.0,
-    //  16: 51.0 / 30.9, 32: 113.8 / 48.8)
+    // (column pieces: beyond 256 row tiles, or where a knob keeps a call from the above; at batch 2 only for a layer or three.  Wide
+    //  rows, us per call with / without pieces at batch 2: 1 layer of 11008 -> 4096 23.5 / 26.8, 3 layers 26.9 / 27.0, 4 layers
+    //  27.8 / 24.6, 8: 31.3 / 26.0, 16: 51.0 / 30.9, 32: 113.8 / 48.8.  Batch 1 beyond 256 row tiles, with / without: 256 -> 33000, k = 4200
+    //  16.2 / 14.1, k = 8192 38.8 / 30.3, five of 8192 x 8192, k = 4096 22.0 / 28.6, eight 29.1 / 29.4, twelve 40.7 / 31.8)
     const bool use_pieces = pieces_ok && p.d_items_p && !p.long_rows &&
                             (batch == 1 || (batch <= DBF_PIECES_MAX_BATCH && p.piece_row_tiles <= 96));
     // Batches of 2 and more: every stage input is quantised once per call; the items read it from memory tile by tile,

@@ -682,7 +682,8 @@ hipError_t dbf_launch_small_layers(const DbfPlan& p, const void* x, void* y, int
     const int group = small_group(T);
     int planes, red;
     const size_t lds = small_lds(p, group, &planes, &red);
-    hipLaunchKernelGGL(rows_aligned(p, x) ? dbf_small_layer_kernel<false> : dbf_small_layer_kernel<true>, dim3(p.n_layers, (T + group - 1) / group), dim3(FEW_THREADS), lds, stream, p.d_stagesB, p.d_stagesA,
+    hipLaunchKernelGGL(rows_aligned(p, x) ? dbf_small_layer_kernel<false> : dbf_small_layer_kernel<true>,
+                       dim3(p.n_layers, (T + group - 1) / group), dim3(FEW_THREADS), lds, stream, p.d_stagesB, p.d_stagesA,
                        static_cast<const uint16_t*>(x), static_cast<uint16_t*>(y), T, group, planes, red);
     return hipGetLastError();
 }

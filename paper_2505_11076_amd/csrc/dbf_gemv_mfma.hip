@@ -1202,7 +1202,9 @@ hipError_t dbf_launch_items_mfma(const DbfItem* items, int n_items, unsigned lon
         //  11.0 / 10.8 us, k = 2048 10.5 / 10.1 / 9.8, 2048 columns 9.3 / 9.0 / 8.7, 4096 -> 11008 11.2 / 11.2 / 10.9; 1024 columns
         //  8.4 / 8.4 / 8.6, hence the column limit.  Streams lose with it -- 512 layers of 4096 x 4096 5.9 against 6.1 TB/s, 256 layers
         //  5.5 / 5.9, 1024 x 4096 at 1 bit 3.3 / 4.3 -- its operand rows fill LDS at two workgroups per compute unit, and
-        //  its prologue is the longer one)
+        //  its prologue is the longer one.  The default kind comes here with launches whose other stage has more than 256
+        //  workgroups: this form / eight wavefronts / four there, nine of 4096 x 4096, k = 2048 11.8 / 11.9 / 12.4, sixteen 13.1 / 13.1 / 13.3,
+        //  2048 -> 40000 11.2 / 11.5 / 11.5, 4096 -> 40000, k = 4096 14.9 / 14.9 / 15.4)
         const hipError_t raised = dbf_mfma_prepare();  // (done when the plan was built; repeated calls cost nothing)
         if (raised != hipSuccess) return raised;
         const int tiles4 = (dbf_col_tiles(max_cols) + 3) & ~3;

@@ -1,10 +1,12 @@
 // fp32 contractions on the bf16 matrix cores, for the ADMM kernels (dbf_admm.hip): out = P^T Q in fp32 accuracy.
 //
 // An fp32 value is the sum of three bf16 values, x = h + m + l, each the rounded rest of the ones before it (8 + 8 + 8
-// significant bits: the sum is exact unless l falls below the smallest bf16).  A product of two such sums is taken as the
-// six partial products h h, h m, m h, m m, h l, l h; what is left out (m l, l m, l l) is below 2^-26 of the product, a
-// quarter of fp32's own rounding.  Products of two bf16 are exact in the matrix cores, sums are kept in fp32.  An operand that
-// is a matrix of signs is one bf16 plane of +-1, and three products suffice.
+// significant bits: the sum is exact unless l falls below the smallest bf16, for |x| below about 1e-33).  A product of two such
+// sums is taken as the six partial products h h, h m, m h, m m, h l, l h; what is left out (m l, l m, l l) is at most about 2^-24
+// of the product, fp32's own unit roundoff (|m| reaches 2^-8 and |l| 2^-17 of x; 2^-28 on average), of either sign.  Products of two
+// bf16 are exact in the matrix cores, sums are kept in fp32, 16 products entering a sum at once: measured against 64 bits the
+// contractions are closer than on the fp32 matrix instructions (dbf_admm.hip).  An operand that is a matrix of signs is one bf16
+// plane of +-1, and three products suffice.
 //
 // Why: v_mfma_f32_32x32x16_bf16 does 16 k in 8 passes where v_mfma_f32_32x32x2_f32 does 2 k in 16: six of the former per
 // 16 k are 2.7 times as fast, three 5.3 times.
