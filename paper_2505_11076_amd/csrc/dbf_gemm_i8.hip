@@ -712,11 +712,12 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2
 
 // The quantiser for a row length: rows held in registers where they can be read in 16-byte pieces (up to 4096 and up to 12288 padded
 // columns); longer ones by a workgroup per token, or by eight tokens a workgroup where that gives 160 workgroups and the planes (48 MB
-// and more) are beyond the L2s, so that pieces of a line no longer meet there; and those that cannot be read in 16-byte pieces by the
-// latter too from 2049 columns on, below by a wavefront per token.
+// and more) are beyond the L2s, so that pieces of a line no longer meet there.  Rows that cannot be read in 16-byte pieces: up to 2048
+// columns by a wavefront per token, up to 4096 by eight tokens a workgroup, beyond by the latter from 384 tokens on.
 // Launches, us, a workgroup per token / eight tokens: 28672 columns  1024 tokens 34 / 47   1280: 48 / 47   1536: 88 / 58   4096: 269 / 137;
-// 14336  1024: 17.7 / 26.2   1536: 26.1 / 28.4   2048: 39 / 31   4096: 95 / 64;   11007  777: 45 / 22   4096: 179 / 50;   a wavefront per token /
-// eight tokens: 4095  777: 14.3 / 12.0   4096: 59 / 21;   1001  777: 5.2 / 8.4   4096: 14.8 / 16.0.
+// 14336  1024: 17.7 / 26.2   1536: 26.1 / 28.4   2048: 39 / 31   4096: 95 / 64;   11007  777: 45 / 22   4096: 179 / 50 (calls of
+// 11007 -> 4096 at 64 / 256 / 384 tokens 41.1, 64.0, 80.4 / 44.3, 66.6, 78.3);   a wavefront per token / eight tokens: 4095  256: 16.4 / 9.8
+// 777: 14.3 / 12.0   4096: 59 / 21;   1001  777: 5.2 / 8.4   4096: 14.8 / 16.0.
 template <bool FROM_F32>
 void launch_quantise(const QuantArgs& q, size_t kp, int T, hipStream_t stream) {
     const bool straight = q.vec_ok && (q.cols & 7) == 0 && q.cols >= 8;
@@ -724,7 +725,7 @@ void launch_quantise(const QuantArgs& q, size_t kp, int T, hipStream_t stream) {
         hipLaunchKernelGGL((dbf_quantise_rows_held_kernel<FROM_F32, 2>), dim3(q.Tp / 4), dim3(1024), 0, stream, q);
     else if (straight && kp <= 12288)
         hipLaunchKernelGGL((dbf_quantise_rows_held_kernel<FROM_F32, 6>), dim3(q.Tp / 4), dim3(1024), 0, stream, q);
-    else if (straight ? T >= 1280 && T * kp >= 24u << 20 : kp > 2048)
+    else if (straight ? T >= 1280 && T * kp >= 24u << 20 : kp > 4096 ? T >= 384 : kp > 2048)
         hipLaunchKernelGGL(dbf_quantise_rows_twice_kernel<FROM_F32>, dim3(q.Tp / 8), dim3(1024), 0, stream, q);
     else if (kp <= 4096)
         hipLaunchKernelGGL(dbf_quantise_rows_kernel<FROM_F32>, dim3((T + 3) / 4), dim3(256), 0, stream, q);

@@ -222,7 +222,8 @@ def test_prefill_kernels_by_size_equal_the_decode_kernels_bit_for_bit(shape):
         layer.close()
 
 
-@pytest.mark.parametrize("shape,T,offset", [((2049, 130, 70), 33, 0), ((2055, 130, 70), 70, 1), ((4104, 129, 65), 129, 1), ((12301, 200, 130), 65, 3),
+@pytest.mark.parametrize("shape,T,offset", [((2049, 130, 70), 33, 0), ((2055, 130, 70), 70, 1), ((4104, 129, 65), 129, 1), ((4104, 129, 65), 390, 1), ((12301, 200, 130), 65, 3),
+                                                            ((12301, 200, 130), 385, 3),
                                             ((12296, 130, 70), 1537, 0), ((16384, 64, 64), 1540, 0), ((100, 130, 12300), 1536, 0)])
 def test_rows_quantised_eight_tokens_a_workgroup(shape, T, offset):
     """Long rows of many tokens, and rows that cannot be read in 16-byte pieces (x `offset` values off, columns no multiple of 8),

@@ -149,7 +149,8 @@ def test_knobs_steer_what_the_header_says(rec):
     ((4096, 4096, 3072), 2048, 0, "rows_held"), ((11008, 4096, 4477), 2048, 0, "rows_held"), ((16384, 128, 300), 1500, 0, "rows_block"),
     ((16384, 128, 300), 1536, 0, "rows_twice"), ((28672, 128, 300), 1279, 0, "rows_block"),
     ((28672, 128, 300), 4096, 0, "rows_twice"), ((4095, 4097, 3071), 4096, 0, "rows_twice"),
-    ((4096, 4096, 3072), 2048, 2, "rows_twice"), ((11007, 4096, 4477), 1500, 0, "rows_twice"), ((1001, 2000, 700), 4096, 0, "rows")])
+    ((4096, 4096, 3072), 2048, 2, "rows_twice"), ((11007, 4096, 4477), 1500, 0, "rows_twice"), ((11007, 4096, 4477), 384, 0, "rows_twice"),
+    ((11007, 4096, 4477), 200, 0, "rows_block"), ((1001, 2000, 700), 4096, 0, "rows")])
 def test_long_and_ragged_rows_of_many_tokens_are_not_written_in_pieces_of_cache_lines(rec, shape, T, offset, quantiser):
     """A prompt's rows go to the quantiser whose stores fit the operand layout: with a workgroup per token a cache line of it is
     written in eight pieces, which took up to 2.4 times as long (178 us against 73 for 4096 tokens of 16384 columns)."""
