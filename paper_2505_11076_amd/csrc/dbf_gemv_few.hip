@@ -85,11 +85,8 @@ struct InputX {
     }
     __device__ __forceinline__ void get(int v, const FewRaw& r, float (&u)[8]) const {
         const h8 xv = __builtin_bit_cast(h8, ANY ? dbf_half8_place(r.a, v, cols) : r.a), bv = __builtin_bit_cast(h8, r.b);
-        const bool in = 8 * v < cols;   // (what lies past the row in its last vector is zero by now)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] = fmaf((float)xv[e], (float)bv[e], -0.f);  // (exact)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] = in ? u[e] : 0.f;
+        for (int e = 0; e < 8; ++e) u[e] = fmaf((float)xv[e], (float)bv[e], -0.f);  // (exact; past the row b is zero)
     }
 };
 struct InputT {

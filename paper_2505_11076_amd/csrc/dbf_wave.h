@@ -68,21 +68,19 @@ __device__ inline float dbf_wave_sum_f(float v) {
 }
 
 // Eight fp16 values, columns 8 v .. + 7 of a row of `cols` values (8 at least) that starts at any even address, in one load: a vector
-// that reaches past the row's end is read as the row's last eight values.  dbf_half8_place moves what has arrived where it belongs,
-// zeros from column `cols` on (apart, so that a load has no use of its data right behind it).
+// that reaches past the row's end is read as the row's last eight values.  dbf_half8_place moves what has arrived where it belongs
+// (apart, so that a load has no use of its data right behind it); from column `cols` on it leaves zeros or values of the row:
+// callers multiply by a vector that is zero there.
 typedef unsigned int dbf_v4u __attribute__((ext_vector_type(4)));
 typedef unsigned int dbf_v4u_any __attribute__((ext_vector_type(4), aligned(2)));
 __device__ __forceinline__ dbf_v4u dbf_half8_load(const uint16_t* row, int v, int cols) {
     return *reinterpret_cast<const dbf_v4u_any*>(row + min(8 * v, cols - 8));
 }
 __device__ __forceinline__ dbf_v4u dbf_half8_place(dbf_v4u r, int v, int cols) {
-    const int past = 8 * v + 8 - cols;   // values of the vector that lie past the row
-    if ((cols & 7) != 0) {   // (a row of whole vectors has no part of one)
-        unsigned __int128 b = __builtin_bit_cast(unsigned __int128, r);
-        b >>= 16 * min(max(past, 0), 7);
-        r = __builtin_bit_cast(dbf_v4u, b);
-    }
-    return past < 8 ? r : (dbf_v4u){0, 0, 0, 0};
+    if ((cols & 7) == 0) return r;   // (a row of whole vectors has no part of one)
+    unsigned __int128 b = __builtin_bit_cast(unsigned __int128, r);
+    b >>= 16 * min(max(8 * v + 8 - cols, 0), 7);
+    return __builtin_bit_cast(dbf_v4u, b);
 }
 
 #endif  // DBF_WAVE_H
