@@ -594,9 +594,9 @@ void dbf_gemm_i8_stage_kernel(const StageArgs a) {
 // one wavefront per SIMD: a workgroup of 128 rows x 32 tokens whose WAVES wavefronts take an equal share of the column steps each.
 // Every wavefront has 128 rows x 32 tokens of its own (the accumulators of the kernel above), loads its sign tiles and operand
 // bytes straight into registers, MID_DEPTH steps ahead, and meets the others only at the end: exact integer sums through LDS.
-// No barrier and no LDS traffic per step; what bounds it is the loads: at 411 tokens of 4096 -> 11008, k = 4477, the A stage (1118
-// workgroups, 52 us) keeps the matrix pipe 47 % busy while its wavefronts wait half of their time for 400 MB (5 KiB per wavefront and
-// step) at 7.7 TB/s, of which 79 % come from L2; the B stage (611 workgroups, 24 us) 38 %.  The kernel above: 57-64 % busy.
+// No barrier and no LDS traffic per step; the matrix pipe with its ANDs and the loads bound it together: at 411 tokens of 4096 -> 11008,
+// k = 4477, the A stage (1118 workgroups, 52 us) keeps the matrix pipes 48 % busy and brings 400 MB (5 KiB per wavefront and step) to
+// registers, 7.7 TB/s, 79 % of the requests hitting L2; the B stage (611 workgroups, 24 us) 38 %.  The kernel above: 62-65 % busy.
 constexpr int MID_TOKENS = 32, MID_DEPTH = 3;
 constexpr int MID_LDS = 16 * 64 * 16;   // per wavefront
 template <bool OUT_F32, int WAVES>
