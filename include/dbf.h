@@ -65,9 +65,10 @@ enum {
 enum {
     DBF_GEMV_AUTO = 0, /* what dbf_gemv uses.  A layer or a group whose stages have at most 256 workgroups (row tiles
                           of 128 rows times groups of up to 8 batch rows), no knob that steers the forms below
-                          having been set: two launches at any batch, every
-                          workgroup rounding the stage input it needs, long rows cut into column pieces; one
-                          launch for layers of at most 32 tiles (of 128 rows x 64 columns) a stage.
+                          having been set: two launches at any batch, every workgroup rounding the stage input
+                          it needs, long rows cut into column pieces; one launch for layers of at most 32 tiles
+                          (of 128 rows x 64 columns) a stage.  (Not groups of layers whose workgroups would round
+                          more than four batch rows of more than 80 column tiles, 128 beyond batch 8.)
                           Else, batch 1: DBF_GEMV_MFMA for a group of layers whose B stage alone fills the
                           chip (1024 workgroups: 64 layers of 4096 x 4096, k = 2048), DBF_GEMV_MFMA_SPLIT for
                           shorter groups (measured faster there: in one launch their A-stage workgroups

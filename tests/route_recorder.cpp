@@ -23,12 +23,9 @@ std::map<const void*, std::string>& kernels() {
     static std::map<const void*, std::string> m;
     return m;
 }
-std::map<const void*, int>& lds_limits() {
-    static std::map<const void*, int> m;
-    return m;
-}
 std::map<void*, size_t> g_blocks;
 size_t g_last_block = 0, g_memset_bytes = 0;
+hipError_t g_error = hipSuccess;   // of a launch, until it is asked for
 std::string g_log;
 
 }  // namespace
@@ -77,13 +74,11 @@ hipError_t hipLaunchKernel(const void* fn, dim3 grid, dim3 block, void**, size_t
     char line[512];
     std::snprintf(line, sizeof(line), "%s %u %u %u %u %zu\n", it == kernels().end() ? "?" : it->second.c_str(), grid.x, grid.y, grid.z, block.x, lds);
     g_log += line;
-    const auto lim = lds_limits().find(fn);
-    return lds > 65536 && (lim == lds_limits().end() || (size_t)lim->second < lds) ? hipErrorInvalidValue : hipSuccess;
+    // (what no launch may ask for)
+    if (lds > 163840 || !grid.x || !grid.y || !grid.z || block.x * block.y * block.z > 1024) g_error = hipErrorInvalidConfiguration;
+    return g_error;
 }
-hipError_t hipFuncSetAttribute(const void* fn, hipFuncAttribute what, int value) {
-    if (what == hipFuncAttributeMaxDynamicSharedMemorySize) lds_limits()[fn] = value;
-    return hipSuccess;
-}
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipMalloc(void** p, size_t n) {
     *p = std::aligned_alloc(4096, (n + 4095) & ~(size_t)4095);
     if (!*p) return hipErrorOutOfMemory;
@@ -122,7 +117,11 @@ hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) {
     return hipSuccess;
 }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() {
+    const hipError_t e = g_error;
+    g_error = hipSuccess;
+    return e;
+}
 hipError_t hipEventCreate(hipEvent_t* e) {
     *e = reinterpret_cast<hipEvent_t>(1);
     return hipSuccess;
