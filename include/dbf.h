@@ -256,10 +256,10 @@ int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void
  *          signs S in the tile layout (as dbf_svid writes them);  U_dev: device, fp32 [q][r].
  *          All four are read as the current iterate and overwritten with the next one.
  *   workspace_dev: device, 256-byte aligned, >= dbf_admm_workspace_bytes(q, r) bytes (one q x r fp32 matrix, the
- *          two operands of the contraction as three bf16 planes each -- 6 bytes per entry of a q x q and a q x r
- *          matrix -- and the SVID workspace).
- * The contraction has fp32 accuracy for operands whose entries are not all below about 1e-33 (it splits them into parts of
- * fp32's own range); below, the relative error grows, to 1e-6 at 1e-35.
+ *          two operands of the contraction as two fp16 planes each -- 4 bytes per entry of a q x q and a q x r
+ *          matrix, rounded up to 128 each way, and their scales -- and the SVID workspace).
+ * The contraction has fp32 accuracy: its operands are split into two fp16 parts relative to the largest of 128 entries along the
+ * summation.  An entry is met to 2^-23 of itself down to 2^-28 of that largest one, and to 2^-51 of the largest below.
  * Asynchronous on hip_stream, allocates nothing; results do not depend on scheduling.  NaNs unsupported.
  * Errors: DBF_EINVAL (null or misaligned pointers, sizes out of range, rho <= 0 or not finite,
  * svid_iters < 1), DBF_EWORKSPACE, DBF_EHIP. */
@@ -276,14 +276,14 @@ int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int r, float r
  * with S (q x p, entries +-1) the packed sign matrix (for the left-factor update of a layer: S = the layer's B
  * signs, q = k, p = n_in, b its input scales, m2 the part of the middle scales that stays with it).  Computes
  *     C = B^T W  (q x r)     and     Minv = (B^T B + rho I)^-1  (q x q)
- * by contractions of fp32 accuracy (as dbf_admm_step's) on the bf16 matrix cores (fp32 operands in three bf16 parts, signs as one),
+ * by contractions of fp32 accuracy (as dbf_admm_step's) on the fp16 matrix cores (fp32 operands in two fp16 parts, signs as one),
  * a blocked fp32 Cholesky factorisation B^T B + rho I = R^T R (blocks of 128), the inverse of the factor and one more
  * contraction.  The outputs are what dbf_admm_step takes (Minv is symmetric up to rounding).
  *   bits_dev: device, dbf_tiled_bytes(q, p) bytes: S in the tile layout, rows q, columns p (read only).
  *   m2_dev: device fp32 [q];  b_dev: device fp32 [p];  W_dev: device fp32 [p][r] row major (all read only).
  *   rho > 0.   Minv_dev: device fp32 [q][q] out;   C_dev: device fp32 [q][r] out.
  *   workspace_dev: device, 256-byte aligned, >= dbf_admm_prepare_workspace_bytes(p, q, r) bytes (a q x q matrix,
- *          the inverses of the diagonal blocks, S as bf16 and the larger of S, W and the q x q matrix as three bf16 planes).
+ *          the inverses of the diagonal blocks, S as fp16 and the largest of S, W and the q x q matrix as two fp16 planes).
  *   not_positive_definite_dev: device int (4-byte aligned) or NULL: set to the number of diagonal blocks whose
  *          factorisation met a non-positive pivot (0 = fine; with rho > 0 the matrix is positive definite and
  *          this only happens when rounding swamps rho).  Read it with an ordinary stream-ordered copy.

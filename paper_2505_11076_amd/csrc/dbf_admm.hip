@@ -4,17 +4,17 @@
 //     Minv = (B^T B + rho I)^-1  (q x q),   C = B^T W  (q x r)
 //
 //     R  = C + rho (a . S . m^T - U)           dbf_admm_rhs_kernel     (A = a . S . m^T never exists densely: S is read
-//                                                                       from the packed tile layout; R only as bf16 planes)
-//     Z  = Minv^T R + U   (= W_hat + U)        dbf_split_gemm_kernel   bf16 matrix cores, three-way split operands
+//                                                                       from the packed tile layout; R only as fp16 planes)
+//     Z  = Minv^T R + U   (= W_hat + U)        dbf_split_gemm_kernel   fp16 matrix cores, operands split in two
 //                                                                       (dbf_split_gemm.h), U added in the epilogue
 //     (S', a', m') = SVID(Z)                   dbf_svid (dbf_svid.hip)
 //     U' = Z - a' . S' . m'^T  (= U + W_hat - A')   dbf_admm_dual_kernel
 //
 // The contraction is q x q x r in fp32 accuracy (34 GFLOP at q = 2048, r = 4096) and dominates; the elementwise
-// kernels and the projection are bandwidth bound.  Measured at that size: the contraction 331 us on the fp32 matrix cores,
-// 182-223 us by the card's clock (0.15-0.19 PFLOP/s; 0.92-1.13 PFLOP/s of bf16 products, where a plain bf16 product of 8192^3
-// reaches 1.22) with split operands, whose planes cost 7 (Minv) + 6 us (R); the update with two rounds of SVID 388 -> 285 us; error
-// against 64 bits 8.1e-6 -> 5.2e-6 (fewer roundings: 16 products enter the accumulator at once).
+// kernels and the projection are bandwidth bound.  Measured at that size: the contraction 331 us on the fp32 matrix cores, 219 on the bf16
+// ones with operands in three parts, 106 on the fp16 ones with operands in two, whose planes cost 7 (Minv) and 16 us (R, with its making); the update with two
+// rounds of SVID 388, 288, 190 us; error against 64 bits 8.1e-6, 5.1e-6, 1.8e-6 (fewer roundings: 16 products enter the accumulator at
+// once, and half as many of them).
 // The paper gives no kernel design for this step.
 #include "dbf_kernels.h"
 #include "dbf_split_gemm.h"
@@ -83,26 +83,29 @@ __global__ __launch_bounds__(256) void dbf_admm_dual_kernel(const float* __restr
 }
 
 // R = C + rho (a_k m_j s_kj - U) (q x r; k = its row is the summation index of the contraction), written straight into
-// bf16 planes: R exists nowhere in fp32.  The lane's eight rows are one bit of eight bytes 16 apart of one sign tile.
+// fp16 planes: R exists nowhere in fp32.  The lane's eight rows are one bit of eight bytes 16 apart of one sign tile.
 __global__ __launch_bounds__(256) void dbf_admm_rhs_kernel(const float* __restrict__ C, const float* __restrict__ U, float rho,
                                                           const float* __restrict__ a, const float* __restrict__ m,
                                                           const uint8_t* __restrict__ bits, int q, int r, int n_ct,
                                                           uint8_t* __restrict__ planes) {
-    const SgSite s = sg_site(q, 3);
-    if (!s.live) return;
-    const int j = min(s.i, r - 1), bit = (s.k0 & 127) >> 4;
-    const uint8_t* sb = bits + ((size_t)(s.k0 >> 7) * n_ct + (j >> 6)) * DBF_TILE_BYTES + 256 * ((j >> 4) & 3) + 16 * (s.k0 & 15) + (j & 15);
+    const SgSite s = sg_site(q, 2);
+    const int j = min(s.i, r - 1);
     const float mj = m[j];
-    float x[8];
+    float x[2][8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int k = min(s.k0 + e, q - 1);   // (clamped, not branched around: the loads of all eight rows in flight)
-        const size_t at = (size_t)k * r + j;
-        const float am = a[k] * mj;
-        const float v = C[at] + rho * (((sb[16 * e] >> bit) & 1 ? am : -am) - U[at]);
-        x[e] = (s.k0 + e < q && s.i < r) ? v : 0.f;
+    for (int n = 0; n < 2; ++n) {
+        const int bit = (s.k0[n] & 127) >> 4;   // (a chunk is a row tile)
+        const uint8_t* sb = bits + ((size_t)blockIdx.x * n_ct + (j >> 6)) * DBF_TILE_BYTES + 256 * ((j >> 4) & 3) + 16 * (s.k0[n] & 15) + (j & 15);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int k = min(s.k0[n] + e, q - 1);   // (clamped, not branched around: the loads of all sixteen rows in flight)
+            const size_t at = (size_t)k * r + j;
+            const float am = a[k] * mj;
+            const float v = C[at] + rho * (((sb[16 * e] >> bit) & 1 ? am : -am) - U[at]);
+            x[n][e] = (s.k0[n] + e < q && s.i < r) ? v : 0.f;
+        }
     }
-    sg_store3(planes, s.off, x);
+    sg_split_chunk(planes, q, r, s, x);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -114,7 +117,7 @@ __global__ __launch_bounds__(256) void dbf_admm_rhs_kernel(const float* __restri
 // and the workgroup of the update that makes diagonal block jb + 1 factors it and inverts its factor right there: that
 // chain of 128 pivots, the longest of the whole, runs beside the other blocks' updates.
 // G and Y share one q x q matrix: block (i, c) is G's for c >= i and Y's for c < i (an update starts it at zero at c = jb), and
-// row jb of R is dead after its own update.  A finished row is written as the bf16 planes that the update and the last
+// row jb of R is dead after its own update.  A finished row is written as the fp16 planes that the update and the last
 // contraction read (R's for c > jb, Y's for c <= jb) and nowhere else.
 // What bounds it: the chain.  Per block row 2 launches and 4 x 32 pivots; the update's products take 3 us of it.  Measured at
 // q = 2048 (16 block rows): panel 5.5 us, update 31.6 us of which the pivots 25, first block 30.  With p = r = 4096 the constants
@@ -263,10 +266,10 @@ __global__ __launch_bounds__(256) void dbf_chol_first_kernel(const float* __rest
 // issued before anything waits.  (Columns of the diagonal block itself: Y there is R_jj^-T, the product with the identity.)
 __global__ __launch_bounds__(256) void dbf_chol_panel_kernel(const float* __restrict__ G, int q, int jb, const float* __restrict__ tinv,
                                                            uint8_t* __restrict__ planes) {
-    __shared__ float Q[NB][33];
+    __shared__ float Q[NB][33], part[4][32];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int j0 = jb * NB, wb = min(NB, q - j0), c0 = 32 * blockIdx.x, n_kb = (q + 15) / 16;
+    const int j0 = jb * NB, wb = min(NB, q - j0), c0 = 32 * blockIdx.x, n_kb = sg_kblocks(q);
     const bool diag = (c0 / NB) == jb;
     const int rk = tid >> 5, cc = c0 + (tid & 31);
     float qv[16], a[64];
@@ -285,6 +288,16 @@ __global__ __launch_bounds__(256) void dbf_chol_panel_kernel(const float* __rest
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
     for (int kk = 0; kk < 64; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kk], Q[2 * kk + h][l32], acc, 0, 0, 0);
+    // the largest magnitude of each column: its scale
+    float mx = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) mx = fmaxf(mx, fabsf(acc[v]));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if (lane < 32) part[w][lane] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(part[0][l32], part[1][l32]), fmaxf(part[2][l32], part[3][l32]));
+    const SgScale scale = sg_scale(mx);
+    if (tid < 32) reinterpret_cast<float*>(planes + sg_scales_at(2, q, q))[(size_t)jb * sg_lines(q) + c0 + tid] = scale.up;
     // register v of lane (h, l32) is row 8 (v / 4) + 4 h + v % 4; a plane wants rows 8 h .. + 7 of each 16
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -297,27 +310,105 @@ __global__ __launch_bounds__(256) void dbf_chol_panel_kernel(const float* __rest
             x[4 + e] = h ? hi : got;
         }
         const int kb = j0 / 16 + 2 * w + t;
-        if (kb < n_kb)
-            sg_store3(planes, (((size_t)(c0 / NB) * n_kb + kb) * 12 + ((c0 >> 5) & 3)) * SG_FRAG + lane * 16, x);
+        sg_store2(planes + (((size_t)(c0 / NB) * n_kb + kb) * 8 + ((c0 >> 5) & 3)) * SG_FRAG + lane * 16, x, scale.down);
     }
 }
 
-// Rows i > jb: [G | Y][i, :] -= R[jb, i]^T [R | Y][jb, :], a workgroup per 128 x 128 block (the contraction kernel of
-// dbf_split_gemm.h over the 128 summation indices of row jb).  Workgroup (0, 0) has diagonal block jb + 1: it keeps it in LDS
+// The products of one chunk for a workgroup of 128 x 128 outputs (dbf_split_gemm.h has the layout of the operands): acc = their sums, scaled.
+// 32 k per step, through registers into two LDS buffers.  `meanwhile` runs beside the last step's products.  Ends with a barrier behind the last read of `lds`.
+struct CholTile {
+    uint8_t frags[2][32 * SG_FRAG];
+    float up[256];
+};
+template <class F>
+__device__ __forceinline__ void chol_tile(CholTile& lds, const SgOperand P, const SgOperand Q, v16f (&acc)[2][2], F meanwhile) {
+    constexpr int STEPS = NB / 32;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), fi = 2 * (w & 1), fj = 2 * (w >> 1);
+    v4f st[8];
+    v16f low[2][2];   // the products with a low piece (dbf_split_gemm.h)
+    // (an operand's 32 k are 16 KiB in one run: [k / 16][piece][32-block])
+    auto fetch = [&](int s) {
+#pragma unroll
+        for (int n = 0; n < 8; ++n) st[n] = *reinterpret_cast<const v4f*>((n < 4 ? P.frags : Q.frags) + (size_t)s * 16 * SG_FRAG + 4096 * (n & 3) + 16 * tid);
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int n = 0; n < 8; ++n) *reinterpret_cast<v4f*>(&lds.frags[buf][4096 * n + 16 * tid]) = st[n];
+    };
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[bi][bj][v] = low[bi][bj][v] = 0.f;
+    fetch(0);
+    const float up = tid < 128 ? P.up[tid] : Q.up[tid - 128];
+    stage(0);
+    lds.up[tid] = up;
+    fetch(1);
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        if (s + 1 < STEPS) stage((s + 1) & 1);
+        if (s + 2 < STEPS) fetch(s + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        if (s + 1 == STEPS) meanwhile();
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub) {
+            const uint8_t* base = &lds.frags[s & 1][8 * sub * SG_FRAG + 16 * lane];
+            v8h a[2][2], b[2][2];
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    a[x][p] = *reinterpret_cast<const v8h*>(base + (4 * p + fi + x) * SG_FRAG);
+                    b[x][p] = *reinterpret_cast<const v8h*>(base + (16 + 4 * p + fj + x) * SG_FRAG);
+                }
+#pragma unroll
+            for (int p = 1; p >= 0; --p)
+#pragma unroll
+                for (int q = 1 - p; q >= 0; --q)
+#pragma unroll
+                    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+                        for (int bj = 0; bj < 2; ++bj) {
+                            v16f& sum = p + q == 0 ? acc[bi][bj] : low[bi][bj];
+                            sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][p], b[bj][q], sum, 0, 0, 0);
+                        }
+        }
+        __syncthreads();
+    }
+    // (scaled by one operand after the other: see dbf_split_gemm.h)
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj) {
+            const float uq = lds.up[128 + 32 * (fj + bj) + (lane & 31)];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const v4f ur = *reinterpret_cast<const v4f*>(&lds.up[32 * (fi + bi) + 8 * c + 4 * (lane >> 5)]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[bi][bj][4 * c + e] = fmaf(low[bi][bj][4 * c + e], 1.f / SG_LOW, acc[bi][bj][4 * c + e]) * ur[e] * uq;
+            }
+        }
+    __syncthreads();
+}
+
+// Rows i > jb: [G | Y][i, :] -= R[jb, i]^T [R | Y][jb, :], a workgroup per 128 x 128 block.  Workgroup (0, 0) has diagonal block jb + 1: it keeps it in LDS
 // and factors it; being the first of the launch it starts with it.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_chol_update_kernel(
     float* __restrict__ G, int q, int jb, const uint8_t* __restrict__ planes, float* __restrict__ tinv_next, int* __restrict__ fail) {
-    __shared__ __align__(16) uint8_t lds[CH_LDS > 2 * 24 * SG_FRAG ? CH_LDS : 2 * 24 * SG_FRAG];
+    __shared__ __align__(16) uint8_t lds[CH_LDS > sizeof(CholTile) ? CH_LDS : sizeof(CholTile)];
     const int nblk = gridDim.x, it = jb + 1 + blockIdx.y, jt = (int)((jb + 1 + blockIdx.x) % nblk);
     if (jt > jb && jt < it) return;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), fi = 2 * (w & 1), fj = 2 * (w >> 1);
-    const int n_kb = (q + 15) / 16;
     const bool factor = blockIdx.x == 0 && blockIdx.y == 0;
     v16f acc[2][2];
     float old[2][2][16];
-    split_gemm_tile<3, 2, 1>(reinterpret_cast<uint8_t(*)[24 * SG_FRAG]>(lds), planes + ((size_t)it * n_kb + jb * (NB / 16)) * (12 * SG_FRAG),
-                          planes + ((size_t)jt * n_kb + jb * (NB / 16)) * (12 * SG_FRAG), 0, NB / 16, acc, [&]() {
+    // (block row jb is whole: only the last can be short, and it has nothing to update)
+    chol_tile(*reinterpret_cast<CholTile*>(lds), sg_operand(planes, 2, q, q, it, jb), sg_operand(planes, 2, q, q, jt, jb), acc, [&]() {
 #pragma unroll
                            for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
@@ -373,8 +464,8 @@ struct AdmmWorkspace {
 inline AdmmWorkspace admm_workspace(int q, int r) {
     AdmmWorkspace w;
     size_t off = 0;
-    w.P = off;     off = up256(off + sg_plane_bytes(3, q, q));   // planes of Minv
-    w.R = off;     off = up256(off + sg_plane_bytes(3, q, r));   // planes of R
+    w.P = off;     off = up256(off + sg_plane_bytes(2, q, q));   // planes of Minv
+    w.R = off;     off = up256(off + sg_plane_bytes(2, q, r));   // planes of R
     w.Z = off;     off = up256(off + 4 * (size_t)q * r);
     w.svid = off;  off = up256(off + dbf_svid_workspace_bytes(q, r));
     w.total = off;
@@ -417,7 +508,7 @@ extern "C" int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int
     g.add = U;  g.lda = r;
     g.out = Z;  g.ldo = r;
     g.M = q;  g.N = r;  g.K = q;
-    launch_split_gemm<3>(g, st);
+    launch_split_gemm<2>(g, st);
     if (hipGetLastError() != hipSuccess) return DBF_EHIP;
     const int rc = dbf_svid(Z, q, r, svid_iters, a_dev, m_dev, bits_dev, base + w.svid, workspace_bytes - w.svid, st);
     if (rc != DBF_OK) return rc;
@@ -442,9 +533,9 @@ inline PrepWorkspace prep_workspace(int p, int q, int r) {
     w.fail = off;  off = up256(off + 256);
     w.S = off;     off = up256(off + sg_plane_bytes(1, p, q));   // planes of the signs
     // planes of the other operand of the three large contractions in turn: the scaled signs, b . W, [R | Y]
-    size_t v = sg_plane_bytes(3, p, q);
-    v = v < sg_plane_bytes(3, p, r) ? sg_plane_bytes(3, p, r) : v;
-    v = v < sg_plane_bytes(3, q, q) ? sg_plane_bytes(3, q, q) : v;
+    size_t v = sg_plane_bytes(2, p, q);
+    v = v < sg_plane_bytes(2, p, r) ? sg_plane_bytes(2, p, r) : v;
+    v = v < sg_plane_bytes(2, q, q) ? sg_plane_bytes(2, q, q) : v;
     w.V = off;     off = up256(off + v);
     w.total = off;
     return w;
@@ -516,7 +607,7 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
         SplitGemmArgs g = {};
         g.P = V;  g.Q = V;  g.out = G;  g.ldo = q;  g.M = q;  g.N = q;  g.K = q;
         g.upper = 1;  g.ktri = 1;
-        launch_split_gemm<3>(g, st);
+        launch_split_gemm<2>(g, st);
         hipLaunchKernelGGL(dbf_chol_mirror_kernel, dim3((q + 31) / 32, (q + 31) / 32), dim3(256), 0, st, G, q);
     }
     if (hipGetLastError() != hipSuccess) return DBF_EHIP;

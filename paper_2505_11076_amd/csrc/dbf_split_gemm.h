@@ -1,15 +1,15 @@
-// fp32 contractions on the bf16 matrix cores, for the ADMM kernels (dbf_admm.hip): out = P^T Q in fp32 accuracy.
+// fp32 contractions on the fp16 matrix cores, for the ADMM kernels (dbf_admm.hip): out = P^T Q in fp32 accuracy.
 //
-// An fp32 value is the sum of three bf16 values, x = h + m + l, each the rounded rest of the ones before it (8 + 8 + 8
-// significant bits: the sum is exact unless l falls below the smallest bf16, for |x| below about 1e-33).  A product of two such
-// sums is taken as the six partial products h h, h m, m h, m m, h l, l h; what is left out (m l, l m, l l) is at most about 2^-24
-// of the product, fp32's own unit roundoff (|m| reaches 2^-8 and |l| 2^-17 of x; 2^-28 on average), of either sign.  Products of two
-// bf16 are exact in the matrix cores, sums are kept in fp32, 16 products entering a sum at once: measured against 64 bits the
-// contractions are closer than on the fp32 matrix instructions (dbf_admm.hip).  An operand that is a matrix of signs is one bf16
-// plane of +-1, and three products suffice.
+// An fp32 value is taken as (h + l / 2048) 2^e: h the fp16 value nearest to x 2^-e, l the fp16 value nearest to 2048 times the rest.  e belongs
+// to an output line of an operand and a chunk of 128 summation indices: it puts the largest magnitude of those 128 values into
+// [2^14, 2^15).  h and l have 22 significant bits and a sign between them: x is met to 2^-23 of itself, 2^-24.5 on average, and values below 2^-28 of
+// the chunk's largest to 2^-51 of that one.  A product of two such values is taken as h h + (h l + l h) / 2048, the two in sums of their own;
+// l l, left out, is at most 2^-22 of the product (2^-24.5 on average), of either sign.  Products of two fp16 are exact in the matrix cores, the
+// sums of a chunk are kept in fp32, 16 products entering a sum at once, and are scaled and added to the total chunk by chunk.
+// An operand that is a matrix of signs is one fp16 plane of +-1, and two products suffice.
 //
-// Why: v_mfma_f32_32x32x16_bf16 does 16 k in 8 passes where v_mfma_f32_32x32x2_f32 does 2 k in 16: six of the former per
-// 16 k are 2.7 times as fast, three 5.3 times.
+// Why: v_mfma_f32_32x32x16_f16 does 16 k in 8 passes where v_mfma_f32_32x32x2_f32 does 2 k in 16; three of the former per 16 k
+// are half of what three bf16 parts per value need (six products, of 8 significant bits a part).
 #ifndef DBF_SPLIT_GEMM_H
 #define DBF_SPLIT_GEMM_H
 
@@ -19,113 +19,160 @@ namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
 // ---------------------------------------------------------------------------------------------
 // Operand planes.  The operand element (k, i) -- summation index k, output index i -- lives in a fragment of 16 k by 32 i, the
 // operand of one matrix instruction: lane l of a wavefront holds i = l % 32, k = 8 (l / 32) .. + 7, 16 bytes, 1 KiB in all.
 // Order in memory: [i / 128][k / 16][piece][(i / 32) % 4][lane][8], so that what a workgroup of 128 outputs stages per step is
 // one contiguous run, every load and LDS access of it is 16 bytes per lane in lane order, and no operand is transposed
-// anywhere but in the kernels below, which make the planes.  Zeros beyond K and beyond M.
+// anywhere but in the kernels below, which make the planes.  Zeros beyond K (up to whole chunks) and beyond M.  Behind the planes of a
+// two-piece operand the 2^e: [k / 128][M rounded up to 128].
 // ---------------------------------------------------------------------------------------------
 constexpr int SG_FRAG = 1024;                 // bytes of a fragment
-inline size_t sg_plane_bytes(int pieces, size_t K, size_t M) {
-    return ((M + 127) / 128) * ((K + 15) / 16) * (size_t)pieces * 4 * SG_FRAG;
+constexpr float SG_LOW = 2048.f;              // what l is scaled by
+constexpr int SG_STEP = 16;                   // summation indices per step of the contraction
+constexpr int SG_CHUNK = 128;                 // summation indices that share a line's scale
+constexpr int SG_CHUNK_STEPS = SG_CHUNK / SG_STEP;
+__host__ __device__ inline int sg_kblocks(int K) { return (K + SG_CHUNK - 1) / SG_CHUNK * (SG_CHUNK / 16); }
+__host__ __device__ inline int sg_lines(int M) { return (M + 127) & ~127; }
+__host__ __device__ inline size_t sg_scales_at(int pieces, int K, int M) { return (size_t)(sg_lines(M) >> 7) * sg_kblocks(K) * pieces * 4 * SG_FRAG; }
+inline size_t sg_plane_bytes(int pieces, int K, int M) {
+    return sg_scales_at(pieces, K, M) + (pieces == 1 ? 0 : sizeof(float) * (size_t)((K + SG_CHUNK - 1) / SG_CHUNK) * sg_lines(M));
 }
 
-// h, m, l of eight values
-__device__ inline void sg_split8(const float (&x)[8], v8bf& h, v8bf& m, v8bf& l) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        h[e] = (__bf16)x[e];
-        const float r1 = x[e] - (float)h[e];
-        m[e] = (__bf16)r1;
-        l[e] = (__bf16)(r1 - (float)m[e]);
-    }
-}
-
-// Where a wavefront of the plane kernels works: fragment (ib, kb) of a grid of (ceil(K / 16) / 4) x 4 ceil(M / 128) workgroups.
-struct SgSite {
-    int i, k0;       // this lane's output index and first k
-    bool live;       // the wavefront has a fragment
-    size_t off;      // byte offset of the lane's 16 bytes in piece 0 (pieces are 4 fragments apart)
+// 2^-e and 2^e for a line's chunk whose largest magnitude is mx.  (Chunks of tiny values are not brought all the way up, so that both are
+// normal numbers: h + l is then exact below 2^-126.  Infinities: any scale does, their products are not numbers.)
+struct SgScale {
+    float down, up;
 };
-__device__ inline SgSite sg_site(int K, int pieces) {
-    const int lane = threadIdx.x & 63, n_kb = (K + 15) / 16;
-    const int kb = blockIdx.x * 4 + (threadIdx.x >> 6), ib = blockIdx.y;
-    SgSite s;
-    s.live = kb < n_kb;
-    s.i = 32 * ib + (lane & 31);
-    s.k0 = 16 * kb + 8 * (lane >> 5);
-    s.off = (((size_t)(ib >> 2) * n_kb + kb) * (4 * pieces) + (ib & 3)) * SG_FRAG + lane * 16;
+__device__ __forceinline__ SgScale sg_scale(float mx) {
+    const int e = (int)(__builtin_bit_cast(unsigned, mx) >> 23);              // (mx >= 0: its biased exponent)
+    const int b = min(max(e, 15), 254) - 14;                                  // biased exponent of `up`: 1 .. 240
+    SgScale s;
+    s.up = __builtin_bit_cast(float, (unsigned)b << 23);
+    s.down = __builtin_bit_cast(float, (unsigned)(254 - b) << 23);
     return s;
 }
-inline dim3 sg_plane_grid(int K, int M) { return dim3(((K + 15) / 16 + 3) / 4, 4 * ((M + 127) / 128)); }
 
-__device__ inline void sg_store3(uint8_t* planes, size_t off, const float (&x)[8]) {
-    v8bf h, m, l;
-    sg_split8(x, h, m, l);
-    *reinterpret_cast<v8bf*>(planes + off) = h;
-    *reinterpret_cast<v8bf*>(planes + off + 4 * SG_FRAG) = m;
-    *reinterpret_cast<v8bf*>(planes + off + 8 * SG_FRAG) = l;
+// The two pieces of eight values to a fragment of piece 0 (`at`) and of piece 1.
+__device__ __forceinline__ void sg_store2(uint8_t* at, const float (&x)[8], float down) {
+    v8h h, l;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float v = x[e] * down;
+        h[e] = (_Float16)v;
+        l[e] = (_Float16)((v - (float)h[e]) * SG_LOW);
+    }
+    *reinterpret_cast<v8h*>(at) = h;
+    *reinterpret_cast<v8h*>(at + 4 * SG_FRAG) = l;
+}
+
+// The plane kernels: a workgroup of 256 threads has a chunk of 128 k and 32 lines, a wavefront two fragments of it.
+struct SgSite {
+    int i, k0[2];    // this lane's output index and the first k of its two fragments
+    size_t off[2];   // byte offset of the lane's 16 bytes in piece 0 (pieces are 4 fragments apart)
+};
+__device__ inline SgSite sg_site(int K, int pieces) {
+    const int lane = threadIdx.x & 63, n_kb = sg_kblocks(K), ib = blockIdx.y;
+    SgSite s;
+    s.i = 32 * ib + (lane & 31);
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const int kb = blockIdx.x * (SG_CHUNK / 16) + 2 * (threadIdx.x >> 6) + n;
+        s.k0[n] = 16 * kb + 8 * (lane >> 5);
+        s.off[n] = (((size_t)(ib >> 2) * n_kb + kb) * (4 * pieces) + (ib & 3)) * SG_FRAG + lane * 16;
+    }
+    return s;
+}
+inline dim3 sg_plane_grid(int K, int M) { return dim3((K + SG_CHUNK - 1) / SG_CHUNK, sg_lines(M) / 32); }
+
+// Scales the values of a workgroup's chunk and lines and stores their pieces and scales.  x: zero where k or i is out of range.
+__device__ __forceinline__ void sg_split_chunk(uint8_t* planes, int K, int M, const SgSite& s, const float (&x)[2][8]) {
+    __shared__ float part[4][32];
+    const int lane = threadIdx.x & 63, l32 = lane & 31, w = threadIdx.x >> 6;
+    float mx = 0.f;
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(x[n][e]));
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    if (lane < 32) part[w][lane] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(part[0][l32], part[1][l32]), fmaxf(part[2][l32], part[3][l32]));
+    const SgScale c = sg_scale(mx);
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+        sg_store2(planes + s.off[n], x[n], c.down);
+    if (threadIdx.x < 32) reinterpret_cast<float*>(planes + sg_scales_at(2, K, M))[(size_t)blockIdx.x * sg_lines(M) + s.i] = c.up;
 }
 
 // Planes of a dense k-major matrix src [K][ld >= M], its rows scaled by kscale (or NULL).  A wavefront's load of one k is two
-// runs of 128 bytes.  Bound by memory: 4 bytes read and 6 written per element.
+// runs of 128 bytes.  Bound by memory: 4 bytes read and 4 written per element.
 __global__ __launch_bounds__(256) void dbf_split_dense_kernel(const float* __restrict__ src, size_t ld, int K, int M,
                                                              const float* __restrict__ kscale, uint8_t* __restrict__ planes) {
-    const SgSite s = sg_site(K, 3);
-    if (!s.live) return;
-    float x[8];
+    const SgSite s = sg_site(K, 2);
+    float x[2][8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int k = min(s.k0 + e, K - 1), i = min(s.i, M - 1);   // (clamped, not branched around: eight loads in flight)
-        const float v = src[(size_t)k * ld + i] * (kscale ? kscale[k] : 1.f);
-        x[e] = (s.k0 + e < K && s.i < M) ? v : 0.f;
-    }
-    sg_store3(planes, s.off, x);
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int k = min(s.k0[n] + e, K - 1), i = min(s.i, M - 1);   // (clamped, not branched around: sixteen loads in flight)
+            const float v = src[(size_t)k * ld + i] * (kscale ? kscale[k] : 1.f);
+            x[n][e] = (s.k0[n] + e < K && s.i < M) ? v : 0.f;
+        }
+    sg_split_chunk(planes, K, M, s, x);
 }
 
-// Planes of a packed sign matrix S (rows = output index i, columns = k) in the 128 x 64 tile layout.  SCALED: three planes of
+// Planes of a packed sign matrix S (rows = output index i, columns = k) in the 128 x 64 tile layout.  SCALED: two planes of
 // +-kscale[k]^2; else one plane of +-1.  A lane's eight signs are bit (i % 128) / 16 of eight consecutive bytes.
 template <bool SCALED>
 __global__ __launch_bounds__(256) void dbf_split_signs_kernel(const uint8_t* __restrict__ bits, int n_ct, int K, int M,
                                                              const float* __restrict__ kscale, uint8_t* __restrict__ planes) {
-    const SgSite s = sg_site(K, SCALED ? 3 : 1);
-    if (!s.live) return;
-    const int i = min(s.i, (M + 127) / 128 * 128 - 1), ir = i & 127;
-    const unsigned* b = reinterpret_cast<const unsigned*>(bits + ((size_t)(i >> 7) * n_ct + (s.k0 >> 6)) * DBF_TILE_BYTES +
-                                                          256 * ((s.k0 >> 4) & 3) + 16 * (ir & 15) + (s.k0 & 15));   // (a caller's: 4-byte aligned)
-    const unsigned b0 = b[0], b1 = b[1];
-    float x[8];
+    const SgSite s = sg_site(K, SCALED ? 2 : 1);
+    const int i = min(s.i, sg_lines(M) - 1), ir = i & 127;
+    float x[2][8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const unsigned bit = ((e < 4 ? b0 : b1) >> (8 * (e & 3) + (ir >> 4))) & 1u;
-        float v = 1.f;
-        if (SCALED) {
-            const float c = kscale[min(s.k0 + e, K - 1)];
-            v = c * c;
+    for (int n = 0; n < 2; ++n) {
+        const int k0 = min(s.k0[n], 64 * n_ct - 8);   // (a fragment that does not exist reads the row's last columns)
+        const unsigned* b = reinterpret_cast<const unsigned*>(bits + ((size_t)(i >> 7) * n_ct + (k0 >> 6)) * DBF_TILE_BYTES +
+                                                              256 * ((k0 >> 4) & 3) + 16 * (ir & 15) + (k0 & 15));   // (a caller's: 4-byte aligned)
+        const unsigned b0 = b[0], b1 = b[1];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const unsigned bit = ((e < 4 ? b0 : b1) >> (8 * (e & 3) + (ir >> 4))) & 1u;
+            float v = 1.f;
+            if (SCALED) {
+                const float c = kscale[min(s.k0[n] + e, K - 1)];
+                v = c * c;
+            }
+            x[n][e] = (s.k0[n] + e < K && s.i < M) ? (bit ? v : -v) : 0.f;
         }
-        x[e] = (s.k0 + e < K && s.i < M) ? (bit ? v : -v) : 0.f;
     }
     if (SCALED) {
-        sg_store3(planes, s.off, x);
+        sg_split_chunk(planes, K, M, s, x);
     } else {
-        v8bf h;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) h[e] = (__bf16)x[e];
-        *reinterpret_cast<v8bf*>(planes + s.off) = h;
+        for (int n = 0; n < 2; ++n) {
+            v8h h;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) h[e] = (_Float16)x[n][e];
+            *reinterpret_cast<v8h*>(planes + s.off[n]) = h;
+        }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
 // out[i][j] = rs[i] * cs[j] * sum_k P[k][i] Q[k][j] + add[i][j] + (i == j ? diag : 0)
-// from the planes of P (PA = 3 pieces, or 1: signs) and Q (3 pieces).  Workgroup = 128 x 128 outputs (BI = 2; BI = 1: 64 x 128), 4
-// wavefronts of 64 x 64 (2 x 2 blocks of 32 x 32: 64 accumulator registers; BI = 1: 32 x 64), 16 values of k per step: 24 matrix
-// instructions of 32 cycles per wavefront (12 with PA = 1) against 12 (8) LDS reads of 1 KiB, a step's 24 (16) KiB double buffered in
-// LDS and requested two steps ahead into registers, one barrier per step; two workgroups per compute unit cover each other's barriers.
-// KS = 2: eight wavefronts, two such halves that take every other step and add up through LDS at the end.  Workgroups are renumbered so that a
-// compute die (linear id modulo 8) works on neighbouring column blocks: the Q planes it needs stay in its own L2.
+// from the planes of P (PA = 2 pieces, or 1: signs) and Q (2 pieces).  Workgroup = 128 x 128 outputs (BI = 2; BI = 1: 64 x 128), 4
+// wavefronts of 64 x 64 (2 x 2 blocks of 32 x 32: 64 registers for each of the three sums; BI = 1: 32 x 64), 16 values of k per step:
+// 12 matrix instructions of 32 cycles per wavefront (8 with PA = 1) against 8 (6) LDS reads of 1 KiB.  A step's 16 (12) KiB come straight
+// from memory into one of four LDS buffers, three steps ahead, one barrier per step; two workgroups per compute unit cover each
+// other's barriers.  A chunk's last products are made block by block, each block being scaled and added to the total while the next is multiplied.
+// KS = 2: eight wavefronts, two such halves that take every other chunk and add up through LDS at the end.
+// What bounds it: the matrix pipes, at the rate that a plain bf16 product of 8192^3 reaches on the same card (1.24 PFLOP/s).  2048 x 4096
+// outputs, K = 2048 (PA = 2): through registers into two LDS buffers of 32 k 130 us, so 96 (1.07 PFLOP/s; without the LDS traffic and
+// the loads 89); a workgroup of four wavefronts with 64 x 128 outputs each, 12 LDS reads per 24 instructions, 132.
 // ---------------------------------------------------------------------------------------------
 struct SplitGemmArgs {
     const uint8_t* P;
@@ -138,157 +185,230 @@ struct SplitGemmArgs {
     float diag;
     int M, N, K;
     int upper;             // symmetric output: workgroups whose block lies wholly below the diagonal do nothing
-    int ktri;              // both operands are zero for k < output index: sums start at the first k that can contribute
+    int ktri;              // both operands are zero for k < output index: sums start at the first chunk that can contribute
 };
 
-// The products of a workgroup's block of 64 BI x 128: acc (BI x 2 blocks of 32 x 32 per wavefront, rows from 32 BI (w % 2), columns from
-// 64 (w / 2)) = sum over `steps` fragments of 16 k from pp (P's planes; BI = 1: of rows 64 `half` .. of the 128) and qp (Q's).
-// KS = 2: a workgroup of 512 threads, wavefronts 4-7 take every second step with LDS buffers of their own (lds: [KS][2][..]); their sums
-// are added at the end, and only threads 0-255 have the result.
-// `meanwhile` runs once the first loads are on their way.  Ends with a barrier behind the last read of `lds`.
-template <int PA, int BI, int KS, class F>
-__device__ inline void split_gemm_tile(uint8_t (*lds)[(2 * BI * PA + 12) * SG_FRAG], const uint8_t* pp, const uint8_t* qp, int half, int all_steps,
-                                       v16f (&acc)[BI][2], F meanwhile) {
-    constexpr int PB = 4 * PA * SG_FRAG, QB = 12 * SG_FRAG;   // bytes per step in memory
-    constexpr int NP = 2 * BI * PA, NF = NP + 12, PER = (NF + 3) / 4;   // fragments per step; of a wavefront's to stage
-    const int tid = threadIdx.x & 255, lane = tid & 63;
+// One operand of a workgroup's block: its fragments from a chunk on, its lines' scales from that chunk on (two pieces).
+struct SgOperand {
+    const uint8_t* frags;
+    const float* up;
+    int lines;       // scales from one chunk to the next
+};
+__device__ inline SgOperand sg_operand(const uint8_t* planes, int pieces, int K, int M, int block, int chunk) {
+    SgOperand o;
+    o.frags = planes + ((size_t)block * sg_kblocks(K) + chunk * SG_CHUNK_STEPS) * (4 * pieces) * SG_FRAG;
+    o.lines = sg_lines(M);
+    o.up = reinterpret_cast<const float*>(planes + sg_scales_at(pieces, K, M)) + (size_t)chunk * o.lines + 128 * block;
+    return o;
+}
+
+// 1 KiB of a wavefront, 16 bytes (or 256 bytes, 4) per lane in lane order, from memory into LDS.
+typedef const __attribute__((address_space(1))) unsigned* SgGlobal;
+typedef __attribute__((address_space(3))) unsigned* SgShared;
+__device__ __forceinline__ void sg_load16_lds(const void* src, void* dst) { __builtin_amdgcn_global_load_lds((SgGlobal)src, (SgShared)dst, 16, 0, 0); }
+__device__ __forceinline__ void sg_load4_lds(const void* src, void* dst) { __builtin_amdgcn_global_load_lds((SgGlobal)src, (SgShared)dst, 4, 0, 0); }
+// Waits until at most LEFT of this wavefront's loads are under way and its LDS reads have arrived, then for the workgroup's other wavefronts.
+// (The wait is the builtin one: the compiler counts with it and adds none of its own before the LDS reads of a buffer.)
+template <int LEFT>
+__device__ __forceinline__ void sg_barrier() {
+    static_assert(LEFT < 16, "the low four bits of the count");
+    __builtin_amdgcn_s_waitcnt(0x0070 | LEFT);   // vmcnt <= LEFT, lgkmcnt = 0
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+template <int PA, int BI, int KS>
+__global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_split_gemm_kernel(const SplitGemmArgs g) {
+    // slots of P and of Q in a buffer; P's loads per wavefront and step (BI = 1, PA = 1: two of its four slots are copies), all of them
+    constexpr int NP = BI * PA < 2 ? 4 : 2 * BI * PA, NF = NP + 8, PL = NP / 4, PER = PL + 2;
+    constexpr int BUF = NF * SG_FRAG, SUMS = KS == 2 ? 2 * 256 * (int)sizeof(v16f) : 0;
+    // (four objects: the compiler then knows that a load into one is not read from another)
+    __shared__ __align__(16) uint8_t r0[KS * BUF > SUMS ? KS * BUF : SUMS], r1[KS * BUF], r2[KS * BUF], r3[KS * BUF];
+    __shared__ __align__(16) float ups[KS][256];   // the scales of a chunk: P's 128 lines, then Q's
+    const int tid = threadIdx.x & 255, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
-    const int steps = (all_steps - kg + KS - 1) / KS, rounds = (all_steps + KS - 1) / KS;   // this half's steps; barriers are everybody's
-    uint8_t(*const first_lds)[(2 * BI * PA + 12) * SG_FRAG] = lds;
-    lds += 2 * kg;
-    v4f st[PER];
-    auto fetch = [&](int i) {
-        const int s = KS * i + kg;
+    // A compute die (linear id modulo 8) works on neighbouring blocks, eight rows of them at a time: what it reads of both operands stays
+    // in its own L2.  (2048 x 4096 outputs: whole columns of blocks to a die 97 us, 8 x 8 blocks 92.)
+    const int mt = gridDim.x, nt = gridDim.y;
+    const unsigned n_wg = mt * nt, lin = blockIdx.x + mt * blockIdx.y;
+    const unsigned die = lin & 7, slot = lin >> 3, per = n_wg >> 3, extra = n_wg & 7;
+    const int vid = (int)(die * per + (die < extra ? die : extra) + slot), band = vid / (8 * nt), in_band = vid - band * 8 * nt, rows = min(8, mt - 8 * band);
+    const int it = 8 * band + in_band % rows, jt = in_band / rows, row0 = 64 * BI * it;
+    if (g.upper && row0 >= 128 * (jt + 1)) return;
+    const int chunk0 = g.ktri ? min(max(row0, 128 * jt), g.K - 1) / SG_CHUNK : 0, chunks = (g.K + SG_CHUNK - 1) / SG_CHUNK - chunk0;
+    const int half = (row0 >> 6) & (2 - BI);       // BI = 1: which 64 of P's 128 lines
+    const SgOperand P = sg_operand(g.P, PA, g.K, g.M, row0 >> 7, chunk0), Q = sg_operand(g.Q, 2, g.K, g.N, jt, chunk0);
+
+    // this half's i-th chunk is KS i + kg; past the last: that one again, not added to the total
+    auto fetch = [&](uint8_t* buf, int i, int sub) {
+        const int s = SG_CHUNK_STEPS * min(KS * i + kg, chunks - 1) + sub;
+        const uint8_t *p = P.frags + (size_t)s * (4 * PA * SG_FRAG) + 16 * lane, *q = Q.frags + (size_t)s * (8 * SG_FRAG) + 16 * lane;
 #pragma unroll
         for (int n = 0; n < PER; ++n) {
             const int f = w + 4 * n;
-            const uint8_t* src = f < NP ? pp + (size_t)s * PB + (4 * (f / (2 * BI)) + 2 * half + f % (2 * BI)) * SG_FRAG
-                                        : qp + (size_t)s * QB + (min(f, NF - 1) - NP) * SG_FRAG;
-            st[n] = *reinterpret_cast<const v4f*>(src + 16 * lane);
+            const uint8_t* src = n >= PL ? q + (f - NP) * SG_FRAG : BI == 2 ? p + f * SG_FRAG : p + (4 * (PA == 2 ? f >> 1 : 0) + 2 * half + (f & 1)) * SG_FRAG;
+            sg_load16_lds(src, buf + kg * BUF + f * SG_FRAG);
         }
     };
-    auto stage = [&](int buf) {
-#pragma unroll
-        for (int n = 0; n < PER; ++n)
-            if (NF % 4 == 0 || w + 4 * n < NF) *reinterpret_cast<v4f*>(&lds[buf][(w + 4 * n) * SG_FRAG + 16 * lane]) = st[n];
+    auto fetch_ups = [&](int i) {
+        const int c = min(KS * i + kg, chunks - 1);
+        sg_load4_lds((w < 2 && PA == 2 ? P.up + (size_t)c * P.lines : Q.up + (size_t)c * Q.lines) + (tid & 127), &ups[kg][64 * w]);
     };
+    v16f acc[BI][2], low[BI][2], tot[BI][2];   // h h; h l and l h, times SG_LOW; all of the chunks before
 #pragma unroll
     for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
         for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[bi][bj][v] = 0.f;
+            for (int v = 0; v < 16; ++v) {
+                tot[bi][bj][v] = 0.f;
+                acc[bi][bj][v] = 0.f;
+                low[bi][bj][v] = 0.f;
+            }
     const int fi = BI * (w & 1), fj = 2 * (w >> 1);           // this wavefront's first 32-blocks
-    auto multiply = [&](int buf) {
-        const uint8_t* base = &lds[buf][16 * lane];
-        v8bf a[BI][PA], b[2][3];
+    v8h a[BI][PA], b[2][2];
+    auto read = [&](const uint8_t* buf) {
+        const uint8_t* base = buf + kg * BUF + 16 * lane;
 #pragma unroll
         for (int p = 0; p < PA; ++p)
 #pragma unroll
-            for (int x = 0; x < BI; ++x) a[x][p] = *reinterpret_cast<const v8bf*>(base + (2 * BI * p + fi + x) * SG_FRAG);
+            for (int x = 0; x < BI; ++x) a[x][p] = *reinterpret_cast<const v8h*>(base + (2 * BI * p + fi + x) * SG_FRAG);
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
-            for (int x = 0; x < 2; ++x) b[x][p] = *reinterpret_cast<const v8bf*>(base + (NP + 4 * p + fj + x) * SG_FRAG);
-        // (piece pairs outermost: an accumulator is used again only after the others)
+            for (int x = 0; x < 2; ++x) b[x][p] = *reinterpret_cast<const v8h*>(base + (NP + 4 * p + fj + x) * SG_FRAG);
+    };
+    auto product = [&](int bi, int bj, int p, int q) {
+        v16f& sum = p + q == 0 ? acc[bi][bj] : low[bi][bj];
+        sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][p], b[bj][q], sum, 0, 0, 0);
+    };
+    // (piece pairs outermost: an accumulator is used again only after the others)
+    auto multiply = [&]() {
 #pragma unroll
         for (int p = PA - 1; p >= 0; --p)
 #pragma unroll
-            for (int q = 2; q >= 0; --q) {
-                if (p + q > 2) continue;
+            for (int q = 1 - p; q >= 0; --q)
 #pragma unroll
                 for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
-                    for (int bj = 0; bj < 2; ++bj)
-                        acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[bi][p], b[bj][q], acc[bi][bj], 0, 0, 0);
-            }
+                    for (int bj = 0; bj < 2; ++bj) product(bi, bj, p, q);
     };
-    if (all_steps <= 0) return;
-    if (steps > 0) {
-        fetch(0);
-        stage(0);
-    }
-    if (steps > 1) fetch(1);
-    meanwhile();
-    __syncthreads();
-    for (int s = 0; s < rounds; ++s) {
-        if (s + 1 < steps) stage((s & 1) ^ 1);
-        if (s + 2 < steps) fetch(s + 2);
-        if (KS == 1 || s < steps) multiply(s & 1);
-        __syncthreads();
-    }
-    if (KS == 2) {
-        v16f* sums = reinterpret_cast<v16f*>(first_lds);      // [BI][2][256]
-        static_assert(KS == 1 || BI * 2 * 256 * sizeof(v16f) <= 4 * (2 * BI * PA + 12) * SG_FRAG, "the sums fit the buffers");
+    // A chunk's sums, scaled, to the total.  Register v of lane l of a 32 x 32 block is row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.
+    // (scaled by one operand after the other: the product of the scales may be out of range where the result is not)
+    auto fold = [&](int bi, int bj) {
+        const float* u = ups[kg];
+        const float uq = u[128 + 32 * (fj + bj) + l32];
 #pragma unroll
-        for (int bi = 0; bi < BI; ++bi)
+        for (int c = 0; c < 4; ++c) {
+            const v4f ur = PA == 1 ? (v4f){1.f, 1.f, 1.f, 1.f} : *reinterpret_cast<const v4f*>(u + 64 * half + 32 * (fi + bi) + 8 * c + 4 * h);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float sum = fmaf(low[bi][bj][4 * c + e], 1.f / SG_LOW, acc[bi][bj][4 * c + e]);
+                tot[bi][bj][4 * c + e] = fmaf(PA == 1 ? sum : sum * ur[e], uq, tot[bi][bj][4 * c + e]);
+                acc[bi][bj][4 * c + e] = 0.f;
+                low[bi][bj][4 * c + e] = 0.f;
+            }
+        }
+    };
+    auto multiply_last = [&](bool live) {
+#pragma unroll
+        for (int n = 0; n <= 2 * BI; ++n) {
+            if (n < 2 * BI) {
+#pragma unroll
+                for (int p = PA - 1; p >= 0; --p)
+#pragma unroll
+                    for (int q = 1 - p; q >= 0; --q) product(n >> 1, n & 1, p, q);
+            }
+            if (n > 0 && live) fold((n - 1) >> 1, (n - 1) & 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    static_assert(SG_CHUNK_STEPS == 8, "the buffers of a chunk's steps are written out below");
+    uint8_t* const ring[4] = {r0, r1, r2, r3};
+    fetch(r0, 0, 0);
+    fetch(r1, 0, 1);
+    fetch(r2, 0, 2);
+    const int rounds = (chunks + KS - 1) / KS;
+    for (int i = 0; i < rounds; ++i) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            // the loads of this step have arrived, those of the two after it (and, of steps 0 and 1, the scales) may not have; every
+            // wavefront is done with the step before, whose buffer the next loads take
+            if (j == 1 || j == 2) sg_barrier<2 * PER + 1>(); else sg_barrier<2 * PER>();
+            fetch(ring[(j + 3) & 3], i + (j + 3) / 8, (j + 3) & 7);
+            if (j == 0) fetch_ups(i);
+            read(ring[j & 3]);
+            if (j < 7) multiply(); else multiply_last(KS == 1 || KS * i + kg < chunks);
+        }
+    }
+    sg_barrier<0>();
+    if (KS == 2) {
+        v4f* sums = reinterpret_cast<v4f*>(r0);   // [2][4][256]: 16-byte pieces, thread by thread: no bank conflicts
+#pragma unroll
+        for (int bi = 0; bi < BI; ++bi) {
+            if (bi > 0) __syncthreads();
 #pragma unroll
             for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {                 // (16-byte pieces, thread by thread: no bank conflicts)
-                    v4f* at = reinterpret_cast<v4f*>(sums) + ((bi * 2 + bj) * 4 + c) * 256 + tid;
-                    if (kg == 1) *at = (v4f){acc[bi][bj][4 * c], acc[bi][bj][4 * c + 1], acc[bi][bj][4 * c + 2], acc[bi][bj][4 * c + 3]};
-                }
-        __syncthreads();
-#pragma unroll
-        for (int bi = 0; bi < BI; ++bi)
+                for (int c = 0; c < 4; ++c)
+                    if (kg == 1)
+                        sums[(bj * 4 + c) * 256 + tid] = (v4f){tot[bi][bj][4 * c], tot[bi][bj][4 * c + 1], tot[bi][bj][4 * c + 2], tot[bi][bj][4 * c + 3]};
+            __syncthreads();
 #pragma unroll
             for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const v4f o = reinterpret_cast<const v4f*>(sums)[((bi * 2 + bj) * 4 + c) * 256 + tid];
+                    const v4f o = sums[(bj * 4 + c) * 256 + tid];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[bi][bj][4 * c + e] += o[e];
+                    for (int e = 0; e < 4; ++e) tot[bi][bj][4 * c + e] += o[e];
                 }
+        }
+        if (kg == 1) return;
+    }
+    // (what is added is loaded for all of the block at once, clamped, not branched around)
+    auto row_of = [&](int bi, int v) { return row0 + 32 * (fi + bi) + 8 * (v >> 2) + 4 * h + (v & 3); };
+    if (g.rs) {
+#pragma unroll
+        for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float rs = g.rs[min(row_of(bi, v), g.M - 1)];
+#pragma unroll
+                for (int bj = 0; bj < 2; ++bj) tot[bi][bj][v] *= rs;
+            }
+    }
+#pragma unroll
+    for (int bj = 0; bj < 2; ++bj) {
+        const int col = 128 * jt + 32 * (fj + bj) + l32, cc = min(col, g.N - 1);
+        const float cs = g.cs ? g.cs[cc] : 1.f;
+        float add[BI][16];
+#pragma unroll
+        for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) add[bi][v] = 0.f;
+        if (g.add) {
+#pragma unroll
+            for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) add[bi][v] = g.add[(size_t)min(row_of(bi, v), g.M - 1) * g.lda + cc];
+        }
+#pragma unroll
+        for (int bi = 0; bi < BI; ++bi)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = row_of(bi, v);
+                const float val = tot[bi][bj][v] * cs + add[bi][v] + (row == col ? g.diag : 0.f);
+                if (row < g.M && col < g.N) g.out[(size_t)row * g.ldo + col] = val;
+            }
     }
 }
 
-template <int PA, int BI, int KS>
-__global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_split_gemm_kernel(const SplitGemmArgs g) {
-    constexpr int PB = 4 * PA * SG_FRAG, QB = 12 * SG_FRAG;   // bytes per step
-    __shared__ __align__(16) uint8_t lds[2 * KS][(2 * BI * PA + 12) * SG_FRAG];
-    const int tid = threadIdx.x & 255, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const unsigned n_wg = gridDim.x * gridDim.y, lin = blockIdx.x + gridDim.x * blockIdx.y;
-    const unsigned die = lin & 7, slot = lin >> 3, per = n_wg >> 3, extra = n_wg & 7;
-    const unsigned vid = die * per + (die < extra ? die : extra) + slot;
-    const int it = (int)(vid % gridDim.x), jt = (int)(vid / gridDim.x), row0 = 64 * BI * it;
-    if (g.upper && row0 >= 128 * (jt + 1)) return;
-    const int n_kb = (g.K + 15) / 16;
-    const int kb0 = g.ktri ? min(max(row0, 128 * jt) / 16, n_kb) : 0;
-    const int fi = BI * (w & 1), fj = 2 * (w >> 1);
-    v16f acc[BI][2];
-    split_gemm_tile<PA, BI, KS>(lds, g.P + ((size_t)(row0 >> 7) * n_kb + kb0) * PB, g.Q + ((size_t)jt * n_kb + kb0) * QB, (row0 >> 6) & (2 - BI),
-                                n_kb - kb0, acc, []() {});
-    if (KS == 2 && threadIdx.x >= 256) return;
-    // register v of lane l of a 32 x 32 block is row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
-    const int l32 = lane & 31, h = lane >> 5;
-#pragma unroll
-    for (int bi = 0; bi < BI; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            const int col = 128 * jt + 32 * (fj + bj) + l32;
-            if (col >= g.N) continue;
-            const float csj = g.cs ? g.cs[col] : 1.f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = row0 + 32 * (fi + bi) + 8 * (v >> 2) + 4 * h + (v & 3);
-                if (row < g.M) {
-                    float val = acc[bi][bj][v] * csj;
-                    if (g.rs) val *= g.rs[row];
-                    if (g.add) val += g.add[(size_t)row * g.lda + col];
-                    if (row == col) val += g.diag;
-                    g.out[(size_t)row * g.ldo + col] = val;
-                }
-            }
-        }
-}
-
 // Where blocks of 128 x 128 would not put two workgroups on every compute unit, a lone one waits out its barriers and LDS latencies:
-// the steps are shared by two halves of a workgroup of 512; and the blocks are 64 x 128 where those of 128 x 128 would leave half of
-// the compute units idle.  Whole calls, us, 128 x 128 with 256 threads / with 512 / 64 x 128 with 512: an update of q = 512, r = 768 (24 blocks)
-// 87.6 / 88.4 / 68.4, 1024 x 1024 (64) 112.9 / 111.4 / 84.9, 1408 x 1269 (110) 147.3 / 144.0 / 112.1, 1536 x 2048 (192) 143.5 / 139.5 / 157.5,
-// 2048 x 4096 (512) 272 / 312 / 357; the constants at p = 4096, q = 700, r = 1000 531 / 488 / 424.
+// the chunks are shared by two halves of a workgroup of 512; and the blocks are 64 x 128 where those of 128 x 128 would leave half of
+// the compute units idle.  us, 64 x 128 with 512 threads / 128 x 128 with 512 / with 256 (K = M):  512 x 768 outputs (24 blocks) 12.2 / 17.9 / 19.2,
+// 1024 x 2048 (128) 20.2 / 27.5 / 30.1, 1536 x 1536 (144) 44.7 / 36.2 / 40.7, 2048 x 2048 (256) 62.1 / 55.2 / 57.8, 1792 x 2560 (280) 77.6 / 84.1 / 67.6,
+// 2415 x 2816 (418) 137 / 115 / 102.
 template <int PA>
 inline void launch_split_gemm(const SplitGemmArgs& g, hipStream_t st) {
     const int mt = (g.M + 127) / 128, nt = (g.N + 127) / 128;

@@ -356,3 +356,29 @@ def test_sign_tiles_may_start_at_any_multiple_of_four_bytes(p, q, r):
             want = got
         for g, w in zip(got, want):
             assert np.array_equal(g.view(np.uint8), w.view(np.uint8)), off
+
+
+@pytest.mark.parametrize("q,r", [(130, 70), (300, 200), (513, 129)])
+def test_admm_contraction_with_operands_of_many_magnitudes(q, r):
+    """Minv = D M D and C = C0 / D with D from 2^-12 to 2^12: along a line of either operand entries differ by 2^24 and more, while all terms of
+    a sum count alike.  The operands are split relative to the largest of 128 entries of a line, exactly to 2^-23 down to 2^-28 of it, so that a sum is met
+    to a few 2^-22 of the sum of its terms' magnitudes; 2^-19 leaves room for the fp32 additions (as many roundings as 16-term steps)."""
+    rng = np.random.default_rng(I.seed_for(6, 970 + q))
+    D = np.exp2(rng.uniform(-12, 12, q))
+    M = rng.uniform(0.2, 1.0, (q, q)) * np.where(rng.random((q, q)) < 0.5, -1.0, 1.0)
+    Minv = ((M + M.T) * D[:, None] * D[None, :]).astype(np.float32)
+    C = (rng.standard_normal((q, r)) / D[:, None]).astype(np.float32)
+    S = np.where(rng.random((q, r)) < 0.5, 1, -1).astype(np.int8)
+    a, m = (0.3 / D).astype(np.float32), rng.uniform(0.5, 1.5, r).astype(np.float32)
+    U = (0.1 * rng.standard_normal((q, r)) / D[:, None]).astype(np.float32)
+    dev = DeviceState(Minv, C, S, a, m, U)
+    dev.step(1.0, 2)
+    S1, a1, m1, U1 = dev.host()
+    R = C.astype(np.float64) + a.astype(np.float64)[:, None] * S * m - U
+    Z = Minv.astype(np.float64) @ R + U
+    terms = np.abs(Minv.astype(np.float64)) @ (np.abs(C).astype(np.float64) + np.abs(a.astype(np.float64)[:, None] * m) + np.abs(U)) + np.abs(U)
+    got = U1 + a1[:, None] * S1 * m1[None, :]
+    err = np.abs(got - Z)
+    gate = 2.0 ** -19 * terms + 2.0 ** -22 * np.abs(a1[:, None] * m1[None, :])
+    G.say("  magnitudes q=%d r=%d: largest error %.2g of the gate" % (q, r, np.max(err / gate)))
+    assert np.all(err <= gate)
