@@ -20,6 +20,7 @@
 #include "dbf_split_gemm.h"
 
 #include <cmath>
+#include <utility>
 
 namespace {
 
@@ -120,41 +121,127 @@ __global__ __launch_bounds__(256) void dbf_admm_rhs_kernel(const float* __restri
 // row jb of R is dead after its own update.  A finished row is written as the fp16 planes that the update and the last
 // contraction read (R's for c > jb, Y's for c <= jb) and nowhere else.
 // What bounds it: the chain.  Per block row 2 launches and 4 x 32 pivots; the update's products take 3 us of it.  Measured at
-// q = 2048 (16 block rows): panel 5.5 us, update 31.6 us of which the pivots 25, first block 30.  With p = r = 4096 the constants
-// took 4392 us in contractions per block on the fp32 matrix cores (84 us per diagonal block, on its own); now 1037: 590 us here,
-// 200 + 106 + 89 us in the contractions C, G and Y^T Y.
+// q = 2048 (16 block rows): panel 5.6 us, update 31.6 us of which the pivots 25 while every entry of a pivot row went through a scalar register and
+// the pivot's root stood in the chain; now 6.1 and 23.7.  With p = r = 4096 the constants took 890 us so, now 756.
 // ---------------------------------------------------------------------------------------------
 constexpr int NB = 128;        // block size: the contraction's tile
-constexpr int CH_LD = NB + 1;  // LDS row length of a diagonal block: rows and columns both meet 32 different banks
-constexpr int CH_LDT = 33;
+constexpr int CH_LD = NB + 4;  // LDS row length of a diagonal block: rows start on 16 bytes
+constexpr int CH_LDT = 36;
 constexpr int CH_LDS = 4 * (NB * CH_LD + 32 * CH_LDT);
 
-// out = P^T Q for 32 x 32 blocks in LDS, 32 values of k: lane l supplies P[k][l % 32] and Q[k][l % 32], k = 2 kk + l / 32.
-__device__ __forceinline__ v16f chol_mul32(const float* P, int ldp, const float* Q, int ldq, int lane) {
+// d -= P^T Q (or d = -P^T Q) for 32 x 32 blocks in LDS, 32 values of k: lane l supplies P[k][l % 32] and Q[k][l % 32], k = 2 kk + l / 32.
+// (What is there is read with the operands, but subtracted from at the end: starting the sums from it rounds it 32 times.)
+__device__ __forceinline__ void chol_update32(float* d, const float* P, const float* Q, bool fresh, int lane) {
     const int l32 = lane & 31, h = lane >> 5;
     float a[16], b[16];
+    v16f acc, old;
 #pragma unroll
     for (int kk = 0; kk < 16; ++kk) {
-        a[kk] = P[(2 * kk + h) * ldp + l32];
-        b[kk] = Q[(2 * kk + h) * ldq + l32];
+        a[kk] = P[(2 * kk + h) * CH_LD + l32];
+        b[kk] = Q[(2 * kk + h) * CH_LD + l32];
     }
-    v16f acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) old[v] = d[(8 * (v >> 2) + 4 * h + (v & 3)) * CH_LD + l32];
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
     for (int kk = 0; kk < 16; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kk], b[kk], acc, 0, 0, 0);
-    return acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) d[(8 * (v >> 2) + 4 * h + (v & 3)) * CH_LD + l32] = (fresh ? 0.f : old[v]) - acc[v];
+}
+
+// The operand of 16 x 16 outputs for 32 values of k: lane l supplies P[k][l % 16], k = 16 (kk / 4) + 4 (l / 16) + kk % 4 (rows four apart start 16 banks
+// apart); register v of the result is row 4 (l / 16) + v, column l % 16.
+__device__ __forceinline__ void chol_load16(const float* P, int ld, int lane, float (&x)[8]) {
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) x[kk] = P[(16 * (kk >> 2) + 4 * (lane >> 4) + (kk & 3)) * ld + (lane & 15)];
+}
+
+// x -= (lane N of each 16 of v) * t.  (Written out: the compiler makes two instructions of it.)
+template <int N>
+__device__ __forceinline__ void chol_sub(float& x, float v, float t) {
+    asm("v_fmac_f32_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(x) : "v"(v), "v"(t), "n"(N));
+}
+template <int C, int... R>
+__device__ __forceinline__ void chol_rows(float (&x)[32], float v0, float v1, float t, std::integer_sequence<int, R...>) {
+    (chol_sub<(C + 1 + R) & 15>(x[C + 1 + R], C + 1 + R < 16 ? v0 : v1, t), ...);
+}
+// Pivot C, its value to lane C of piv: the rows below lose their multiples of row C.  t = x[C] / pivot (reciprocal and one Newton step), and lanes 0-15
+// of x[C] in every 16 lanes of v0, lanes 16-31 in every 16 of v1.  (One block, so that what the instructions want between a write and a
+// use -- two others before a lane swap of a fresh register and before a lane broadcast of one, one behind the reciprocal -- is the work itself.)
+template <int C>
+__device__ __forceinline__ void chol_pivot(float (&x)[32], float& piv) {
+    float v0, v1, t, r, p;
+    asm("v_mov_b32 %0, %6\n\t"
+        "v_mov_b32 %1, %6\n\t"
+        "v_readlane_b32 %4, %6, %7\n\t"
+        "v_rcp_f32 %3, %4\n\t"
+        "v_permlane32_swap_b32 %0, %1\n\t"
+        "v_mov_b32 %1, %0\n\t"
+        "v_fma_f32 %2, -%4, %3, 1.0\n\t"
+        "v_fma_f32 %3, %2, %3, %3\n\t"
+        "v_permlane16_swap_b32 %0, %1\n\t"
+        "v_mul_f32 %2, %6, %3\n\t"
+        "v_writelane_b32 %5, %4, %7"
+        : "=&v"(v0), "=&v"(v1), "=&v"(t), "=&v"(r), "=&s"(p), "+v"(piv)
+        : "v"(x[C]), "n"(C));
+    chol_rows<C>(x, v0, v1, t, std::make_integer_sequence<int, 31 - C>());
+}
+template <int... C>
+__device__ __forceinline__ void chol_pivots(float (&x)[32], float& piv, std::integer_sequence<int, C...>) {
+    (chol_pivot<C>(x, piv), ...);
+}
+
+// The same for any pivots, in LDS and at leisure: pivots down to subnormal numbers (the instructions take none: a scaled copy), rows of pivots that are not
+// positive set to zero.  Returns whether there was one of the latter.
+__device__ __forceinline__ int chol_factor32_any(float* H, float* T, int lane) {
+    const int l32 = lane & 31;
+    volatile float* X = lane < 32 ? H + l32 : T + l32;   // column l of the block or of the identity
+    const int ld = lane < 32 ? CH_LD : CH_LDT;
+    volatile float* G = H;
+    int bad = 0;
+    if (lane >= 32)
+        for (int r = 0; r < 32; ++r) X[r * ld] = r == l32 ? 1.f : 0.f;
+#pragma unroll 1
+    for (int c = 0; c < 32; ++c) {
+        const float piv = G[c * CH_LD + c];
+        const bool tiny = piv < 0x1p-64f, pos = piv > 0.f;
+        const float ps = tiny ? piv * 0x1p64f : piv;
+        float y = __builtin_amdgcn_rsqf(ps);
+        y = fmaf(0.5f * y, fmaf(-ps * y, y, 1.f), y);
+        y = tiny ? y * 0x1p32f : y;
+        bad |= !pos;
+        const float xc = X[c * ld] * (pos ? y : 0.f);
+        X[c * ld] = xc;
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int r = c + 1; r < 32; ++r) X[r * ld] = fmaf(-G[c * CH_LD + r], xc, X[r * ld]);
+        __builtin_amdgcn_wave_barrier();
+    }
+    float x[32];
+#pragma unroll
+    for (int r = 0; r < 32; ++r) x[r] = X[r * ld];
+    __builtin_amdgcn_wave_barrier();
+    if (lane >= 32) {
+#pragma unroll
+        for (int r = 0; r < 32; ++r) {
+            G[r * CH_LD + l32] = x[r];
+            T[l32 * CH_LDT + r] = x[r];
+        }
+    }
+    return bad;
 }
 
 // One wavefront: the 32 x 32 diagonal block at H (leading dimension CH_LD, upper triangle read) is replaced by Y = R^-T
 // (lower triangular, zeros above), and T (leading dimension CH_LDT) receives Y^T = R^-1.  Lane l < 32 holds column l of
-// the block, lane 32 + l column l of the identity; a pivot row is scaled by 1 / sqrt(pivot), and its entries R[c][r] reach the
-// other rows through scalar registers: no LDS and no barrier in the chain.  Returns whether a pivot was not positive.
+// the block, lane 32 + l column l of the identity.  A pivot row's entries reach the other rows through lane broadcasts that are part
+// of the multiplication; the rows are scaled by 1 / sqrt(pivot) at the end, all roots at once.  What bounds it: a wavefront on its own issues one
+// instruction in four cycles, here 11 and one per row below for a pivot.  (With every entry through a scalar register, two
+// instructions a row, and the root in the chain from pivot to pivot 8300 cycles, so 4400.)  Returns whether a pivot was not positive.
 __device__ __forceinline__ int chol_factor32(float* H, float* T, int lane) {
     const int l32 = lane & 31;
     const bool right = lane >= 32;
-    float x[32];
-    int bad = 0;
+    float x[32], piv = 1.f;
 #pragma unroll
     for (int r = 0; r < 32; ++r) {
         x[r] = H[r * CH_LD + l32];
@@ -162,27 +249,12 @@ __device__ __forceinline__ int chol_factor32(float* H, float* T, int lane) {
     }
 #pragma unroll
     for (int r = 0; r < 32; ++r) x[r] = right ? (r == l32 ? 1.f : 0.f) : x[r];
+    chol_pivots(x, piv, std::make_integer_sequence<int, 32>());
+    if (__any(__builtin_bit_cast(unsigned, piv) - 0x00800000u >= 0x7f000000u)) return chol_factor32_any(H, T, lane);   // (not a positive normal number)
+    float y = __builtin_amdgcn_rsqf(piv);
+    y = fmaf(0.5f * y, fmaf(-piv * y, y, 1.f), y);
 #pragma unroll
-    for (int c = 0; c < 32; ++c) {
-        const float piv = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[c]), c));
-        // (1 / sqrt of a pivot below 2^-64 through a scaled copy: the instruction takes no subnormal numbers; one Newton step)
-        const bool tiny = piv < 0x1p-64f;
-        const float ps = tiny ? piv * 0x1p64f : piv;
-        float y = __builtin_amdgcn_rsqf(ps);
-        y = fmaf(0.5f * y, fmaf(-ps * y, y, 1.f), y);
-        y = tiny ? y * 0x1p32f : y;
-        const bool pos = piv > 0.f;
-        bad |= !pos;
-        x[c] *= pos ? y : 0.f;
-        // (all entries first, then the products: a scalar register read right after it is written costs idle slots.  The
-        //  next pivot's chain hides among the products)
-        float f[32];
-#pragma unroll
-        for (int r = c + 1; r < 32; ++r) f[r] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[c]), r));
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int r = c + 1; r < 32; ++r) x[r] = fmaf(-f[r], x[c], x[r]);
-    }
+    for (int r = 0; r < 32; ++r) x[r] *= __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, y), r));
     if (right) {
 #pragma unroll
         for (int r = 0; r < 32; ++r) {
@@ -190,59 +262,76 @@ __device__ __forceinline__ int chol_factor32(float* H, float* T, int lane) {
             T[l32 * CH_LDT + r] = x[r];
         }
     }
-    return bad;
+    return 0;
 }
 
 // One workgroup (256 threads): the 128 x 128 block in LDS (upper triangle; identity where it is padded) is factored, and tinv
-// (128 x 128, row major, device memory) receives the inverse of the factor, zeros below the diagonal.  *fail is raised if
-// a pivot is not positive.  The elimination above, once more, with blocks of 32: wavefront 0 brings the next diagonal block
-// up to date and factors it while the others update the rest.
+// (128 x 128, row major, device memory) receives Y = R^-T, the inverse of the transposed factor: its 32 x 32 blocks on and below the diagonal.  *fail is raised if
+// a pivot is not positive.  The elimination above, once more, with blocks of 32: all wavefronts bring the
+// next diagonal block up to date, wavefront 0 factors it while the others update the rest.
 __device__ __forceinline__ void chol_block(float* H, float* T, float* __restrict__ tinv, int* __restrict__ fail) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, h = lane >> 5;
     auto blk = [&](int i, int c) { return H + 32 * i * CH_LD + 32 * c; };
+    const int r16 = w & 1, c16 = w >> 1, at16 = (16 * r16 + 4 * (lane >> 4)) * CH_LD + 16 * c16 + (lane & 15);   // a wavefront's 16 x 16 of a block
     int bad = 0;
-    if (w == 0) bad = chol_factor32(blk(0, 0), T, lane);
-    __syncthreads();
+#pragma unroll 1
     for (int s = 0; s < 4; ++s) {
-        // row s: the three blocks beside the diagonal
-        if (w > 0) {
-            float* d = blk(s, w - 1 + (w - 1 >= s));
-            const v16f o = chol_mul32(T, CH_LDT, d, CH_LD, lane);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) d[(8 * (v >> 2) + 4 * h + (v & 3)) * CH_LD + l32] = o[v];
-        }
-        __syncthreads();
-        if (s == 3) break;
-        // rows i > s: columns c >= i (G) and c <= s (Y; at c = s it starts here)
-        auto update = [&](int i, int c) {
-            float* d = blk(i, c);
-            const v16f o = chol_mul32(blk(s, i), CH_LD, blk(s, c), CH_LD, lane);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                float* e = d + (8 * (v >> 2) + 4 * h + (v & 3)) * CH_LD + l32;
-                *e = (c == s ? 0.f : *e) - o[v];
-            }
-        };
+        // beside the pivots of block (s, s): what else row s - 1 takes from the rows i >= s, columns c >= i (G) and c < s (Y)
         if (w == 0) {
-            update(s + 1, s + 1);
-            bad |= chol_factor32(blk(s + 1, s + 1), T, lane);
-        } else {
+            bad |= chol_factor32(blk(s, s), T, lane);
+        } else if (s > 0) {
             int n = 0;
-            for (int i = s + 1; i < 4; ++i)
+            for (int i = s; i < 4; ++i)
                 for (int c = 0; c < 4; ++c) {
-                    if ((c > s && c < i) || (i == s + 1 && c == s + 1)) continue;
-                    if (++n % 3 == w - 1) update(i, c);
+                    if ((c >= s && c < i) || (i == s && c == s)) continue;
+                    if (++n % 3 == w - 1) chol_update32(blk(i, c), blk(s - 1, i), blk(s - 1, c), c == s - 1, lane);   // (Y starts at c = s - 1)
                 }
         }
         __syncthreads();
+        // row s, the three blocks beside the diagonal, 16 x 16 of each to a wavefront
+        {
+            float t[8], d[3][8];
+            chol_load16(T + 16 * r16, CH_LDT, lane, t);
+#pragma unroll
+            for (int n = 0; n < 3; ++n) chol_load16(blk(s, n + (n >= s)) + 16 * c16, CH_LD, lane, d[n]);
+            __syncthreads();   // (in place)
+            v4f o[3];
+#pragma unroll
+            for (int n = 0; n < 3; ++n) o[n] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk)
+#pragma unroll
+                for (int n = 0; n < 3; ++n) o[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(t[kk], d[n][kk], o[n], 0, 0, 0);
+#pragma unroll
+            for (int n = 0; n < 3; ++n)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) blk(s, n + (n >= s))[at16 + v * CH_LD] = o[n][v];
+        }
+        __syncthreads();
+        // the next diagonal block, 16 x 16 to a wavefront
+        if (s < 3) {
+            float a[8], b[8];
+            chol_load16(blk(s, s + 1) + 16 * r16, CH_LD, lane, a);
+            chol_load16(blk(s, s + 1) + 16 * c16, CH_LD, lane, b);
+            float* d = blk(s + 1, s + 1) + at16;
+            v4f old, o[2];   // (two sums: half the chain)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) old[v] = d[v * CH_LD];
+            o[0] = o[1] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk) o[kk & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], b[kk], o[kk & 1], 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) d[v * CH_LD] = old[v] - (o[0][v] + o[1][v]);
+            __syncthreads();
+        }
     }
     if (bad && tid == 0) atomicAdd(fail, 1);
-#pragma unroll 16
-    for (int e = tid; e < NB * NB; e += 256) {
-        const int k = e / NB, i = e % NB;
-        tinv[e] = i >= k ? H[i * CH_LD + k] : 0.f;
+    // (32 x 32 blocks above the diagonal are not read)
+#pragma unroll
+    for (int n = 0; n < NB * NB / 4 / 256; ++n) {
+        const int e = tid + 256 * n, i = e / (NB / 4), k = 4 * (e % (NB / 4));
+        if (k / 32 <= i / 32) *reinterpret_cast<v4f*>(tinv + NB * i + k) = *reinterpret_cast<const v4f*>(H + i * CH_LD + k);
     }
 }
 
@@ -272,11 +361,13 @@ __global__ __launch_bounds__(256) void dbf_chol_panel_kernel(const float* __rest
     const int j0 = jb * NB, wb = min(NB, q - j0), c0 = 32 * blockIdx.x, n_kb = sg_kblocks(q);
     const bool diag = (c0 / NB) == jb;
     const int rk = tid >> 5, cc = c0 + (tid & 31);
-    float qv[16], a[64];
+    float qv[16];
+    v4f a[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) qv[e] = G[(size_t)(j0 + min(rk + 8 * e, wb - 1)) * q + min(cc, q - 1)];
+    // (register e of a[m] is k = 8 m + 4 h + e of row 32 w + l32; k >= 32 (w + 1) is not used)
 #pragma unroll
-    for (int kk = 0; kk < 64; ++kk) a[kk] = tinv[(2 * kk + h) * NB + 32 * w + l32];
+    for (int m = 0; m < 16; ++m) a[m] = *reinterpret_cast<const v4f*>(tinv + (32 * w + l32) * NB + 8 * m + 4 * h);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         const int k = rk + 8 * e;
@@ -287,7 +378,13 @@ __global__ __launch_bounds__(256) void dbf_chol_panel_kernel(const float* __rest
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
-    for (int kk = 0; kk < 64; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kk], Q[2 * kk + h][l32], acc, 0, 0, 0);
+    for (int b = 0; b < 4; ++b) {
+        if (b > w) break;
+#pragma unroll
+        for (int m = 4 * b; m < 4 * b + 4; ++m)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m][e], Q[8 * m + 4 * h + e][l32], acc, 0, 0, 0);
+    }
     // the largest magnitude of each column: its scale
     float mx = 0.f;
 #pragma unroll

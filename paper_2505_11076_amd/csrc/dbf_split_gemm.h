@@ -184,7 +184,7 @@ struct SplitGemmArgs {
     size_t lda, ldo;
     float diag;
     int M, N, K;
-    int upper;             // symmetric output: workgroups whose block lies wholly below the diagonal do nothing
+    int upper;             // symmetric output (M = N): only the blocks that meet the upper triangle are made, a workgroup in x for each
     int ktri;              // both operands are zero for k < output index: sums start at the first chunk that can contribute
 };
 
@@ -230,12 +230,24 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
     // A compute die (linear id modulo 8) works on neighbouring blocks, eight rows of them at a time: what it reads of both operands stays
     // in its own L2.  (2048 x 4096 outputs: whole columns of blocks to a die 97 us, 8 x 8 blocks 92.)
-    const int mt = gridDim.x, nt = gridDim.y;
-    const unsigned n_wg = mt * nt, lin = blockIdx.x + mt * blockIdx.y;
-    const unsigned die = lin & 7, slot = lin >> 3, per = n_wg >> 3, extra = n_wg & 7;
-    const int vid = (int)(die * per + (die < extra ? die : extra) + slot), band = vid / (8 * nt), in_band = vid - band * 8 * nt, rows = min(8, mt - 8 * band);
-    const int it = 8 * band + in_band % rows, jt = in_band / rows, row0 = 64 * BI * it;
-    if (g.upper && row0 >= 128 * (jt + 1)) return;
+    int it, jt;
+    if (g.upper) {
+        // column by column of the blocks that meet the upper triangle: (2 / BI) (jt + 1) of column jt
+        const int v = blockIdx.x;
+        auto before = [](int c) { return (2 / BI) * (c * (c + 1) / 2); };
+        jt = (int)((sqrtf(1.f + (float)(4 * BI) * (float)v) - 1.f) * 0.5f);
+        while (before(jt) > v) --jt;
+        while (before(jt + 1) <= v) ++jt;
+        it = v - before(jt);
+    } else {
+        const int mt = gridDim.x, nt = gridDim.y;
+        const unsigned n_wg = mt * nt, lin = blockIdx.x + mt * blockIdx.y;
+        const unsigned die = lin & 7, slot = lin >> 3, per = n_wg >> 3, extra = n_wg & 7;
+        const int vid = (int)(die * per + (die < extra ? die : extra) + slot), band = vid / (8 * nt), in_band = vid - band * 8 * nt, rows = min(8, mt - 8 * band);
+        it = 8 * band + in_band % rows;
+        jt = in_band / rows;
+    }
+    const int row0 = 64 * BI * it;
     const int chunk0 = g.ktri ? min(max(row0, 128 * jt), g.K - 1) / SG_CHUNK : 0, chunks = (g.K + SG_CHUNK - 1) / SG_CHUNK - chunk0;
     const int half = (row0 >> 6) & (2 - BI);       // BI = 1: which 64 of P's 128 lines
     const SgOperand P = sg_operand(g.P, PA, g.K, g.M, row0 >> 7, chunk0), Q = sg_operand(g.Q, 2, g.K, g.N, jt, chunk0);
@@ -408,17 +420,21 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
 // the chunks are shared by two halves of a workgroup of 512; and the blocks are 64 x 128 where those of 128 x 128 would leave half of
 // the compute units idle.  us, 64 x 128 with 512 threads / 128 x 128 with 512 / with 256 (K = M):  512 x 768 outputs (24 blocks) 12.2 / 17.9 / 19.2,
 // 1024 x 2048 (128) 20.2 / 27.5 / 30.1, 1536 x 1536 (144) 44.7 / 36.2 / 40.7, 2048 x 2048 (256) 62.1 / 55.2 / 57.8, 1792 x 2560 (280) 77.6 / 84.1 / 67.6,
-// 2415 x 2816 (418) 137 / 115 / 102.
+// 2415 x 2816 (418) 137 / 115 / 102.  Sums of unequal lengths (ktri) in 64 x 128 with 256 threads, so that short ones end early: the upper 136 blocks of
+// Y^T Y, q = 2048, 35 us, in 128 x 128 with 512 threads 45 (B^T B, of equal lengths: 69 and 64).
 template <int PA>
 inline void launch_split_gemm(const SplitGemmArgs& g, hipStream_t st) {
     const int mt = (g.M + 127) / 128, nt = (g.N + 127) / 128;
     const long long blocks = g.upper ? (long long)mt * (mt + 1) / 2 : (long long)mt * nt;
+    auto grid = [&](int bi) { return g.upper ? dim3((unsigned)(blocks * (2 / bi))) : dim3(bi == 2 ? mt : (g.M + 63) / 64, nt); };
     if (blocks <= 128)
-        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 1, 2>), dim3((g.M + 63) / 64, nt), dim3(512), 0, st, g);
+        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 1, 2>), grid(1), dim3(512), 0, st, g);
+    else if (g.ktri && blocks <= 256)
+        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 1, 1>), grid(1), dim3(256), 0, st, g);
     else if (blocks <= 256)
-        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 2, 2>), dim3(mt, nt), dim3(512), 0, st, g);
+        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 2, 2>), grid(2), dim3(512), 0, st, g);
     else
-        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 2, 1>), dim3(mt, nt), dim3(256), 0, st, g);
+        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 2, 1>), grid(2), dim3(256), 0, st, g);
 }
 
 }  // namespace

@@ -382,3 +382,30 @@ def test_admm_contraction_with_operands_of_many_magnitudes(q, r):
     gate = 2.0 ** -19 * terms + 2.0 ** -22 * np.abs(a1[:, None] * m1[None, :])
     G.say("  magnitudes q=%d r=%d: largest error %.2g of the gate" % (q, r, np.max(err / gate)))
     assert np.all(err <= gate)
+
+
+@pytest.mark.parametrize("q", [40, 200])
+def test_admm_prepare_with_subnormal_pivots(q):
+    """Pivots below 2^-126, where the reciprocal and root instructions take none: G = B^T B + rho I with rho = 9e-39 and B^T B a
+    hundredth of it, so that Minv is near the top of the range (1.1e38).  Against 64 bits; G itself has a spacing of 2^-149, 1.6e-7 of rho."""
+    p, r, rho = 64, 16, np.float32(9e-39)
+    rng = np.random.default_rng(I.seed_for(6, 950 + q))
+    S = np.where(rng.random((q, p)) < 0.5, -1.0, 1.0)
+    m2 = np.full(q, 1.2e-21, dtype=np.float32)
+    b, W = np.ones(p, dtype=np.float32), rng.standard_normal((p, r)).astype(np.float32)
+    bits = torch.from_numpy(B.dbf_tile_host(q, p, O.pack_signs(S)).copy()).cuda()
+    dev = [torch.from_numpy(x.copy()).cuda() for x in (m2, b, W)]
+    Minv, Cm = torch.empty((q, q), device="cuda"), torch.empty((q, r), device="cuda")
+    flag = torch.full((1,), 77, dtype=torch.int32, device="cuda")
+    wsb = B.dbf_admm_prepare_workspace_bytes(p, q, r)
+    ws = torch.full((wsb,), 0xA5, dtype=torch.uint8, device="cuda")
+    B.dbf_admm_prepare(bits.data_ptr(), dev[0].data_ptr(), dev[1].data_ptr(), dev[2].data_ptr(), p, q, r, float(rho), Minv.data_ptr(),
+                       Cm.data_ptr(), ws.data_ptr(), wsb, flag.data_ptr(), G.stream_handle())
+    torch.cuda.synchronize()
+    assert int(flag.item()) == 0
+    Bt = m2.astype(np.float64)[:, None] * S
+    want = np.linalg.inv((Bt @ Bt.T + float(rho) * np.eye(q)) * 1e38) * 1e38
+    got = Minv.cpu().numpy().astype(np.float64)
+    err = np.max(np.abs(got - want)) / np.max(np.abs(want))
+    G.say("  subnormal pivots q=%d: Minv err %.2e of max" % (q, err))
+    assert np.all(np.isfinite(got)) and err <= 2e-5
