@@ -8,9 +8,9 @@
 //     as much as half of the stage; here it is 5 vector instructions per value beside the sign tiles' way from memory;
 //   * a workgroup has eight wavefronts, each with eight tiles in flight from its first instructions on (64 KiB per workgroup;
 //     four wavefronts with four tiles each held a compute unit that has one workgroup to 11 GB/s);
-//   * where compute units would idle, the tokens of a call are dealt to several workgroups per row tile (`group` tokens each:
-//     less rounding per workgroup, the sign bytes come from L2), and long rows are cut into column pieces.
-// Measured figures are at the rules that cut and choose such launches (few_cut, dbf_few_takes, dbf_small_layer_kernel).
+//   * where compute units would idle, the tokens of a call and the bit planes of a row tile are dealt to several workgroups (less
+//     rounding and fewer matrix instructions in each, the sign bytes come from L2), and long rows are cut into column pieces.
+// Measured figures are at the rules that cut and choose such launches (few_cut, few_split, dbf_few_takes, dbf_small_layer_kernel).
 #include <type_traits>
 
 #include "dbf_kernels.h"
@@ -26,6 +26,7 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 constexpr int FEW_WAVES = 8;
 constexpr int FEW_THREADS = 64 * FEW_WAVES;
 constexpr int FEW_PF = 8;            // tiles in flight per wavefront
+constexpr int FEW_HELD = 10;         // vectors of eight input values a lane can hold
 constexpr int FEW_RB = DBF_TILE_ROWS + 1;  // LDS row of a reduction buffer (see RB_STRIDE in dbf_gemv_mfma.hip)
 constexpr float QMAX = 32512.f;
 constexpr unsigned OOB = 0x80000000u;
@@ -44,17 +45,20 @@ __host__ __device__ inline int few_tile_block(int ncols) { return (ncols + 1) * 
 
 // How the eight wavefronts share the input rows: P rows at a time (a power of two), 8 / P wavefronts each.
 struct FewShare {
-    int P, parts, row, part;
+    int P, parts, log_parts, row, part;
 };
-__host__ __device__ inline int few_parts(int nb) { return nb <= 1 ? 8 : nb <= 2 ? 4 : nb <= 4 ? 2 : 1; }
+__host__ __device__ inline int few_log_parts(int nb) { return nb <= 1 ? 3 : nb <= 2 ? 2 : nb <= 4 ? 1 : 0; }
+__host__ __device__ inline int few_parts(int nb) { return 1 << few_log_parts(nb); }
 __device__ inline FewShare few_share(int nb, int w) {
     FewShare s;
-    s.parts = few_parts(nb);
-    s.P = FEW_WAVES / s.parts;
+    s.log_parts = few_log_parts(nb);
+    s.parts = 1 << s.log_parts;
+    s.P = FEW_WAVES >> s.log_parts;
     s.row = w & (s.P - 1);
-    s.part = w / s.P;
+    s.part = w >> (3 - s.log_parts);
     return s;
 }
+static_assert(FEW_WAVES == 8, "the shift by 3");
 
 // The rows of a stage's input: fp16 x times b (B stage), or the fp32 middle activations, which are padded with zeros.  load()
 // requests the eight values of vector v of a row, get() turns what has arrived into numbers.
@@ -86,7 +90,7 @@ struct InputX {
     __device__ __forceinline__ void get(int v, const FewRaw& r, float (&u)[8]) const {
         const h8 xv = __builtin_bit_cast(h8, ANY ? dbf_half8_place(r.a, v, cols) : r.a), bv = __builtin_bit_cast(h8, r.b);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) u[e] = fmaf((float)xv[e], (float)bv[e], -0.f);  // (exact; past the row b is zero)
+        for (int e = 0; e < 8; ++e) u[e] = fmaf((float)xv[e], (float)bv[e], 0.f);  // (exact; past the row b is zero; one instruction with its conversions, v_fma_mix_f32)
     }
 };
 struct InputT {
@@ -104,7 +108,17 @@ struct InputT {
     }
 };
 
-// Largest |u| of every row: wmax[row][part].  held: every wavefront has one row and at most H vectors per lane, which have been
+// Largest |u| of a wavefront's part of a row, to every entry e of wmax[row] with e % parts == part: the eight of a row are read at once.
+__device__ __forceinline__ void few_put_max(FewMisc* m, int bi, const FewShare s, float mx, int lane) {
+    if (lane < FEW_WAVES && (lane & (s.parts - 1)) == s.part) m->wmax[bi][lane] = mx;
+}
+__device__ __forceinline__ float few_row_max(const FewMisc* m, int bi) {
+    const v4f* p = reinterpret_cast<const v4f*>(m->wmax[bi]);
+    const v4f a = p[0], b = p[1];
+    return fmaxf(fmaxf(fmaxf(a.x, a.y), fmaxf(a.z, a.w)), fmaxf(fmaxf(b.x, b.y), fmaxf(b.z, b.w)));
+}
+
+// Largest |u| of every row (few_put_max).  held: every wavefront has one row and at most H vectors per lane, which have been
 // requested into raw and stay there.
 template <class IN, int H>
 __device__ __forceinline__ void few_max(const IN& in, const FewShare s, int nb, int nvec, bool held, const FewRaw (&raw)[H],
@@ -118,7 +132,7 @@ __device__ __forceinline__ void few_max(const IN& in, const FewShare s, int nb, 
             for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(u[i][e]));
         }
         mx = dbf_wave_max(mx);
-        if (lane == 0 && s.row < nb) m->wmax[s.row][s.part] = mx;
+        if (s.row < nb) few_put_max(m, s.row, s, mx, lane);
         return;
     }
     for (int bi = s.row; bi < nb; bi += s.P) {
@@ -136,7 +150,7 @@ __device__ __forceinline__ void few_max(const IN& in, const FewShare s, int nb, 
             }
         }
         mx = dbf_wave_max(mx);
-        if (lane == 0) m->wmax[bi][s.part] = mx;
+        few_put_max(m, bi, s, mx, lane);
     }
 }
 
@@ -165,36 +179,36 @@ __device__ __forceinline__ int few_round8(const float (&u)[8], float inv, uint2&
     return 256 * sh + sl;
 }
 
-// Rounds the vectors [v0, v1) of every row into the planes (whose first column tile is v0's) and adds up the sums of the q.
+// Rounds the vectors [v0, v1) of every row into the planes (whose first column tile is v0's) and adds up the sums of the q; of held rows
+// the lane's sum is returned, for few_sigma once the barrier behind the planes has been passed.
 template <class IN, int H>
-__device__ __forceinline__ void few_round(const IN& in, const FewShare s, int nb, int nvec, int v0, int v1, bool held,
+__device__ __forceinline__ int few_round(const IN& in, const FewShare s, int nb, int nvec, int v0, int v1, bool held,
                                           const float (&held_u)[H][8], FewMisc* m, unsigned char* planes, int tile_block, int lane) {
     auto inv_of = [&](int bi) {
-        float mx = 0.f;
-        for (int p = 0; p < s.parts; ++p) mx = fmaxf(mx, m->wmax[bi][p]);
-        if (s.part == 0 && lane == 0) m->scale[bi] = mx / QMAX;
+        const float mx = few_row_max(m, bi);
         return mx > 0.f ? QMAX / mx : 0.f;
     };
-    auto put = [&](int bi, int v, const float (&u)[8], float inv) {
+    auto place = [&](int bi, int v) { return planes + ((v - v0) >> 3) * tile_block + 2 * bi * DBF_TILE_COLS + 8 * (v & 7); };
+    auto put = [&](unsigned char* d, const float (&u)[8], float inv) {
         uint2 hi, lo;
         const int sum = few_round8(u, inv, hi, lo);
-        unsigned char* d = planes + ((v - v0) >> 3) * tile_block + 2 * bi * DBF_TILE_COLS + 8 * (v & 7);
         *reinterpret_cast<uint2*>(d) = hi;
         *reinterpret_cast<uint2*>(d + DBF_TILE_COLS) = lo;
         return sum;
     };
     if (held) {
-        if (s.row >= nb) return;
+        if (s.row >= nb) return 0;
         const float inv = inv_of(s.row);
         int sum = 0;
+        const int va = lane + 64 * s.part;
+        unsigned char* d = place(s.row, va);
 #pragma unroll
-        for (int i = 0; i < H; ++i) {
-            const int v = lane + 64 * (s.part + s.parts * i);
-            if (v >= v0 && v < v1) sum += put(s.row, v, held_u[i], inv);
+        for (int i = 0; i < H; ++i) {   // vector va + 64 parts i
+            const int v = va + 64 * s.parts * i;
+            if (v >= v0 && v < v1) sum += put(d, held_u[i], inv);
+            d += 8 * s.parts * tile_block;
         }
-        sum = dbf_wave_sum(sum);
-        if (lane == 0) atomicAdd(&m->sigma[s.row], sum);
-        return;
+        return sum;
     }
     for (int bi = s.row; bi < nb; bi += s.P) {
         const float inv = inv_of(bi);
@@ -208,12 +222,22 @@ __device__ __forceinline__ void few_round(const IN& in, const FewShare s, int nb
                 if (b + 64 * s.parts * i < v1) {
                     float u[8];
                     in.get(b + 64 * s.parts * i, r[i], u);
-                    sum += put(bi, b + 64 * s.parts * i, u, inv);
+                    sum += put(place(bi, b + 64 * s.parts * i), u, inv);
                 }
         }
         sum = dbf_wave_sum(sum);
         if (lane == 0) atomicAdd(&m->sigma[bi], sum);
     }
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // (vectors past the row were requested and not used: nothing may be left for the loop over the tiles to wait for)
+    return 0;
+}
+// What nobody needs before the sums are taken: the held rows' sums of the q, and the scales.
+__device__ __forceinline__ void few_sigma(FewMisc* m, const FewShare s, int nb, bool held, int sum, int tid) {
+    if (held && s.row < nb) {
+        sum = dbf_wave_sum(sum);
+        if ((tid & 63) == 0) atomicAdd(&m->sigma[s.row], sum);
+    }
+    if (tid < nb) m->scale[tid] = few_row_max(m, tid) / QMAX;
 }
 
 // One wavefront's tiles [lo, hi) of a span of tiles of one row tile.
@@ -235,17 +259,22 @@ struct FewStream {
             __builtin_amdgcn_sched_barrier(0);
         }
     }
-    // planes: LDS planes whose tile 0 is the span's first tile.
-    __device__ __forceinline__ void run(const unsigned char* planes, int tile_block, int ncols, v4i (&acc)[8]) {
+    // planes: LDS planes whose tile 0 is the span's first tile.  The sign tiles' bit planes s0 .. s0 + NP - 1 are multiplied.
+    template <int NP>
+    __device__ __forceinline__ void run(const unsigned char* planes, int tile_block, int ncols, int s0, v4i (&acc)[NP]) {
         const int g = lane >> 4, c = lane & 15;
-        // (unused operand columns alias a valid one)
-        const unsigned char* xp = planes + (c < ncols ? c : c % ncols) * DBF_TILE_COLS + 16 * g + lo * tile_block;
+        // (unused operand columns read the last valid one)
+        const unsigned char* xp = planes + min(c, ncols - 1) * DBF_TILE_COLS + 16 * g + lo * tile_block;
+        // A tile's operand is read while the one before is multiplied (the last read, of a tile behind the span, lands in the LDS that the
+        // launch keeps behind the planes and is not used).
+        v4i next = *reinterpret_cast<const v4i*>(xp);
         auto multiply = [&](int j) {
-            const v4i xv = *reinterpret_cast<const v4i*>(xp);
+            const v4i xv = next;
             xp += tile_block;
+            next = *reinterpret_cast<const v4i*>(xp);
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                const unsigned msk = 0x01010101u << s;
+            for (int s = 0; s < NP; ++s) {
+                const unsigned msk = 0x01010101u << (NP == 8 ? s : s0 + s);
                 const v4i a = {(int)(tl[j].x & msk), (int)(tl[j].y & msk), (int)(tl[j].z & msk), (int)(tl[j].w & msk)};
                 acc[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, xv, acc[s], 0, 0, 0);
             }
@@ -269,15 +298,19 @@ struct FewStream {
     }
 };
 
-// The signed sum of row rho of a row tile and batch row bi: 2 * (sum over the set bits) - sigma, exact (modulo 2^32 on the way).
-__device__ inline int few_total(const int* red, int bi, int rho, int sigma) {
-    const int s = rho >> 4;
-    int vh = red[2 * bi * FEW_RB + rho] >> s, vl = red[(2 * bi + 1) * FEW_RB + rho] >> s;
+// The signed sum of a row of bit plane s from its sums over the high and the low bytes of the q: 2 * (sum over the set bits) - sigma, exact
+// (modulo 2^32 on the way).
+__device__ inline int few_total(int high, int low, int s, int sigma) {
+    int vh = high >> s, vl = low >> s;
     if (s == 7) {  // the mask 0x80 is -128 as an int8
         vh = -vh;
         vl = -vl;
     }
     return (int)(2u * (unsigned)(vh * 256 + vl) - (unsigned)sigma);
+}
+// ... of row rho of a row tile and batch row bi of the small-layer kernel
+__device__ inline int small_total(const int* red, int bi, int rho, int sigma) {
+    return few_total(red[2 * bi * FEW_RB + rho], red[(2 * bi + 1) * FEW_RB + rho], rho >> 4, sigma);
 }
 
 // Rounded to fp32, then to fp16, as in every other kernel (left to itself the compiler rounds the last product to fp16 at once:
@@ -287,21 +320,34 @@ __device__ __forceinline__ uint16_t few_half(float v) {
     return __builtin_bit_cast(uint16_t, (_Float16)v);
 }
 
-// One stage, workgroup (row tile, token group, column piece).  `first`: LIST: the items (one row tile each); else the layer's
-// sign tiles, everything a workgroup needs being kernel arguments that arrive in scalar registers (a layer alone: no memory round
-// trip before its loads).  io: x or y.  acc: zeroed integers, [row tile][DBF_MAX_BATCH][128], then an arrival counter per
-// (row tile, token group).
-template <bool STAGE_A, bool LIST, int H, bool ANY>
+// Operand columns of `nb` tokens, rounded up to a power of two (its logarithm): 1 .. 4.
+__host__ __device__ inline int few_log_cols(int nb) { return nb <= 1 ? 1 : nb <= 2 ? 2 : nb <= 4 ? 3 : 4; }
+__host__ __device__ inline int few_slot_bytes(int nb, int np) { return FEW_WAVES * 4 * np * 16 << few_log_cols(nb); }
+
+// One stage, workgroup (row tile, group of tokens and of bit planes, column piece).  `first`: LIST: the items (one row tile each); else the layer's
+// sign tiles, behind which its vectors lie in_off and row_off times 16 bytes.  All arguments fit the 14 scalar registers that are loaded before
+// the wavefronts start (a layer alone: no memory round trip before its loads).
+// NP: bit planes of a workgroup (blockIdx.y: group of tokens, then of bit planes), 8 where rows are cut.  tokens: T | group << 16 | aliased << 20; cut: tiles of an LDS chunk | pieces << 10 | (ceil(2^16 / pieces) - 1) << 16.
+// io: x or y.  acc: zeroed integers, [row tile][DBF_MAX_BATCH][128], then an arrival counter per (row tile, token group).
+// Where the time of a workgroup goes (three layers of 4096 x 4096, k = 3072, batch 8: 64 tiles, four tokens; cycles of 13000 on the compute
+// unit): arguments, item and requests 2400, the input's arrival and maximum 1900, rounding 2900, tiles 3800, sums 1400, outputs 700.  The
+// matrix instructions with their ANDs take 29 cycles each for 16 of work; nothing overlaps the rounding but the tiles' way from memory.
+// The wavefronts' sums: every wavefront leaves its own in LDS in 16-byte pieces, a thread adds up the eight of two rows.  They lie behind the
+// planes, or where the planes were (`aliased`), if both do not fit.
+template <bool STAGE_A, bool LIST, int H, int NP, bool ANY>
 __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_few_kernel(
-    const void* __restrict__ first, const uint16_t* __restrict__ in_scale, const uint16_t* __restrict__ row_scale, float* __restrict__ t_base,
-    uint16_t* __restrict__ io, int* __restrict__ acc_base, int cols_, int rows_, unsigned tokens, unsigned cut) {
+    const void* __restrict__ first, float* __restrict__ t_base, uint16_t* __restrict__ io, int* __restrict__ acc_base, int in_off, int row_off,
+    int cols_, int rows_, unsigned tokens, unsigned cut) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int T = tokens & 0xFFFF, group = tokens >> 16, chunk_tiles = cut & 0xFFFF, pieces = cut >> 16;
-    const int t0 = blockIdx.y * group, nb = min(group, T - t0), ncols = 2 * nb;
+    const int T = tokens & 0xFFFF, group = (tokens >> 16) & 15, aliased = tokens >> 20;
+    const int s0 = NP * (blockIdx.y % (8 / NP)), piece = blockIdx.z;
+    const int chunk_tiles = cut & 1023, pieces = (cut >> 10) & 63;
+    const int t0 = blockIdx.y / (8 / NP) * group, nb = min(group, T - t0), ncols = 2 * nb;
     const int tile_block = few_tile_block(ncols);
     const uint8_t* bits;
+    const uint16_t *in_scale, *row_scale;
     int cols, rows, row0, stride, n_items;
     if (LIST) {
         const DbfItem& it = static_cast<const DbfItem*>(first)[blockIdx.x];
@@ -314,24 +360,27 @@ __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     } else {
         cols = cols_;  rows = rows_;  row0 = blockIdx.x * DBF_TILE_ROWS;
         stride = ((STAGE_A ? cols : rows) + DBF_TILE_ROWS - 1) & ~(DBF_TILE_ROWS - 1);
-        bits = static_cast<const uint8_t*>(first) + (size_t)blockIdx.x * ((cols + DBF_TILE_COLS - 1) / DBF_TILE_COLS) * DBF_TILE_BYTES;
-        row_scale += row0;
+        const uint8_t* tiles = static_cast<const uint8_t*>(first);
+        bits = tiles + (size_t)blockIdx.x * ((cols + DBF_TILE_COLS - 1) / DBF_TILE_COLS) * DBF_TILE_BYTES;
+        in_scale = reinterpret_cast<const uint16_t*>(tiles + 16ll * in_off);
+        row_scale = reinterpret_cast<const uint16_t*>(tiles + 16ll * row_off) + row0;
         n_items = (rows + DBF_TILE_ROWS - 1) / DBF_TILE_ROWS;
     }
     const int n_ct = (cols + DBF_TILE_COLS - 1) / DBF_TILE_COLS, nvec = 8 * n_ct;
-    const int ct0 = n_ct * blockIdx.z / pieces, ct1 = n_ct * (blockIdx.z + 1) / pieces;
+    // (pieces of ceil(n_ct / pieces) tiles, or one more; the last takes what is left)
+    const int piece_tiles = (int)(((unsigned)n_ct * (cut >> 16) + n_ct + 65535u) >> 16);
+    const int ct0 = min(n_ct, piece * piece_tiles), ct1 = min(n_ct, ct0 + piece_tiles);
     FewMisc* m = reinterpret_cast<FewMisc*>(smem);
     unsigned char* planes = smem + sizeof(FewMisc);
-    int* red = reinterpret_cast<int*>(planes + chunk_tiles * tile_block);
+    v4i* slots = reinterpret_cast<v4i*>(planes + (aliased ? 0 : chunk_tiles * tile_block));   // [wavefront][plane][g][column]
     float* t = t_base + (size_t)t0 * stride;
     const FewShare sh = few_share(nb, w);
 
     InputX<ANY> inx;
     inx.x = io + (size_t)t0 * cols;  inx.b = in_scale;  inx.cols = cols;
     const InputT inp = {t, stride};
-    const int mine = (nvec + 64 * sh.parts - 1) / (64 * sh.parts);
+    const int mine = (nvec + 64 * sh.parts - 1) >> (6 + sh.log_parts);
     const bool held = mine <= H && ct1 - ct0 <= chunk_tiles;
-    const float rscale = (float)__builtin_bit_cast(_Float16, row_scale[tid & 127]);
     // The input is requested before the first tiles: loads complete in order, and the tiles come from farther away.
     FewRaw raw[H];
     FewStream st;
@@ -348,55 +397,76 @@ __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
             if (STAGE_A) inp.load(bi, v, raw[i]); else inx.load(bi, v, raw[i]);
         }
     }
+    // this thread's outputs: of token bi the rows rho and rho + 1 of the row tile, from the sums of columns c (high bytes even, low odd)
+    const int lc = few_log_cols(nb), c = tid & ((1 << lc) - 1), plane = s0 + (tid >> (lc + 2)), bi = c >> 1, odd = c & 1;
+    const int rho = 16 * plane + 4 * ((tid >> lc) & 3) + 2 * odd, row = row0 + rho;
+    const bool mine_out = tid < (4 * NP << lc) && c < ncols;
+    const unsigned rscale2 = *reinterpret_cast<const unsigned*>(row_scale + (rho & 127));
     __builtin_amdgcn_sched_barrier(0);
     start();
     __builtin_amdgcn_sched_barrier(0);
-    for (int i = tid; i < ncols * FEW_RB; i += FEW_THREADS) red[i] = 0;
     if (tid < DBF_MAX_BATCH) m->sigma[tid] = 0;
     float u[H][8];
     if (STAGE_A) few_max(inp, sh, nb, nvec, held, raw, u, m, lane); else few_max(inx, sh, nb, nvec, held, raw, u, m, lane);
     __syncthreads();
-    v4i acc[8];
+    v4i acc[NP];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) acc[s] = (v4i){0, 0, 0, 0};
+    for (int s = 0; s < NP; ++s) acc[s] = (v4i){0, 0, 0, 0};
     for (;;) {
-        if (STAGE_A) few_round(inp, sh, nb, nvec, 8 * c0, 8 * c1, held, u, m, planes, tile_block, lane);
-        else few_round(inx, sh, nb, nvec, 8 * c0, 8 * c1, held, u, m, planes, tile_block, lane);
+        const int sum = STAGE_A ? few_round(inp, sh, nb, nvec, 8 * c0, 8 * c1, held, u, m, planes, tile_block, lane)
+                                : few_round(inx, sh, nb, nvec, 8 * c0, 8 * c1, held, u, m, planes, tile_block, lane);
         __syncthreads();
-        st.run(planes, tile_block, ncols, acc);
-        if (c1 >= ct1) break;
+        if (NP < 8 || c0 == ct0) few_sigma(m, sh, nb, held, sum, tid);
+        st.run<NP>(planes, tile_block, ncols, s0, acc);
+        if (NP < 8 || c1 >= ct1) break;   // (a part of the bit planes: of pieces that are one chunk)
         __syncthreads();   // every wavefront is done with the chunk's planes
         c0 = c1;
         c1 = min(ct1, c0 + chunk_tiles);
         start();
     }
-    // the wavefronts' sums: register i of acc[s] of lane (g, c) is row 16 s + 4 g + i, operand column c
+    // register i of acc[s] of lane (g, c) is row 16 (s0 + s) + 4 g + i, operand column c
+    if (aliased) __syncthreads();
     if ((lane & 15) < ncols) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) atomicAdd(&red[(lane & 15) * FEW_RB + 4 * (lane >> 4) + 16 * s + i], acc[s][i]);
+        for (int s = 0; s < NP; ++s) slots[((4 * (w * NP + s) + (lane >> 4)) << lc) + (lane & 15)] = acc[s];
     }
     __syncthreads();
 
-    const int rho = tid & 127, row = row0 + rho;
-    auto store = [&](int bi, int total) {
-        const float val = (float)total * m->scale[bi] * rscale;
+    int total[2];
+    if (mine_out) {
+        v4i sum = slots[tid];
+#pragma unroll
+        for (int q = 1; q < FEW_WAVES; ++q) sum += slots[((4 * q * NP) << lc) + tid];
+        // (rows 0 and 1 are finished by the even column's lane, 2 and 3 by the odd one's: each hands the other what it lacks)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int own = odd ? sum[2 + i] : sum[i], other = dbf_dpp_move<0xB1>(odd ? sum[i] : sum[2 + i]);   // quad_perm [1,0,3,2]
+            total[i] = few_total(odd ? other : own, odd ? own : other, plane, m->sigma[bi]);
+        }
+    }
+    auto store = [&]() {
+        const float scale = m->scale[bi];
+        const float v0 = (float)total[0] * scale * (float)__builtin_bit_cast(_Float16, (uint16_t)rscale2);
+        const float v1 = (float)total[1] * scale * (float)__builtin_bit_cast(_Float16, (uint16_t)(rscale2 >> 16));
         if (STAGE_A) {
-            if (row < rows) io[(size_t)(t0 + bi) * rows + row] = few_half(val);
+            uint16_t* out = io + (size_t)(t0 + bi) * rows + row;
+            if (row < rows) out[0] = few_half(v0);
+            if (row + 1 < rows) out[1] = few_half(v1);
         } else {
-            t[(size_t)bi * stride + row] = val;   // (padded rows have scale 0)
+            *reinterpret_cast<float2*>(t + (size_t)bi * stride + row) = make_float2(v0, v1);   // (padded rows have scale 0)
         }
     };
     if (pieces == 1) {
-        for (int bi = tid >> 7; bi < nb; bi += FEW_THREADS / 128) store(bi, few_total(red, bi, rho, m->sigma[bi]));
+        if (mine_out) store();
         return;
     }
     // A column piece: exact integer sums are added up in memory; the last piece of the row tile to arrive takes them out
     // (leaving zeros), scales and stores.
-    int* a = acc_base + ((size_t)blockIdx.x * DBF_MAX_BATCH + t0) * DBF_TILE_ROWS + rho;
-    for (int bi = tid >> 7; bi < nb; bi += FEW_THREADS / 128)
-        __hip_atomic_fetch_add(a + bi * DBF_TILE_ROWS, few_total(red, bi, rho, m->sigma[bi]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int* a = acc_base + ((size_t)blockIdx.x * DBF_MAX_BATCH + t0 + bi) * DBF_TILE_ROWS + rho;
+    if (mine_out) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) __hip_atomic_fetch_add(a + i, total[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's adds have been performed ...
     __syncthreads();                                  // ... and so have the workgroup's
     if (tid == 0) {
@@ -405,9 +475,10 @@ __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
         if (m->last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (!m->last) return;
-    for (int bi = tid >> 7; bi < nb; bi += FEW_THREADS / 128)
-        store(bi, __hip_atomic_exchange(a + bi * DBF_TILE_ROWS, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    if (!m->last || !mine_out) return;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) total[i] = __hip_atomic_exchange(a + i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    store();
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -423,7 +494,7 @@ constexpr int SMALL_PER_WAVE = 4, SMALL_TILES = FEW_WAVES * SMALL_PER_WAVE;
 // The sums of a wavefront's tiles (tiles[0 .. hi - lo) of the span, row tile major) into red[row tile].
 __device__ __forceinline__ void small_stage(const FewStream& st, const unsigned char* planes, int tile_block, int ncols, int n_ct, int* red) {
     const int g = st.lane >> 4, c = st.lane & 15;
-    const unsigned char* xp = planes + (c < ncols ? c : c % ncols) * DBF_TILE_COLS + 16 * g;
+    const unsigned char* xp = planes + min(c, ncols - 1) * DBF_TILE_COLS + 16 * g;
     int rt = st.lo / n_ct, ct = st.lo - rt * n_ct;
     v4i acc[8];
 #pragma unroll
@@ -496,13 +567,14 @@ __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     float u[H][8];
     few_max(inx, sh, nb, nvec_b, true, raw, u, m, lane);
     __syncthreads();
-    few_round(inx, sh, nb, nvec_b, 0, nvec_b, true, u, m, planes, tile_block, lane);
+    const int sum_b = few_round(inx, sh, nb, nvec_b, 0, nvec_b, true, u, m, planes, tile_block, lane);
     __syncthreads();
+    few_sigma(m, sh, nb, true, sum_b, tid);
     small_stage(st, planes, tile_block, ncols, sb.n_ct, red_b);
     __syncthreads();
     for (int e = tid; e < nb * t_len; e += FEW_THREADS) {
         const int bi = e / t_len, row = e - bi * t_len;
-        t[e] = (float)few_total(red_b + (row >> 7) * ncols * FEW_RB, bi, row & 127, m->sigma[bi]) * m->scale[bi] *
+        t[e] = (float)small_total(red_b + (row >> 7) * ncols * FEW_RB, bi, row & 127, m->sigma[bi]) * m->scale[bi] *
                (float)__builtin_bit_cast(_Float16, sb.row_scale[row]);
     }
     __syncthreads();
@@ -515,8 +587,9 @@ __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     ++m;
     few_max(inp, sh, nb, nvec_a, true, raw, u, m, lane);
     __syncthreads();
-    few_round(inp, sh, nb, nvec_a, 0, nvec_a, true, u, m, planes, tile_block, lane);
+    const int sum_a = few_round(inp, sh, nb, nvec_a, 0, nvec_a, true, u, m, planes, tile_block, lane);
     __syncthreads();
+    few_sigma(m, sh, nb, true, sum_a, tid);
     small_stage(st2, planes, tile_block, ncols, sa.n_ct, red_a);
     __syncthreads();
     const int rows = sa.rows, all = sa.n_rt * DBF_TILE_ROWS;
@@ -524,7 +597,7 @@ __global__ __launch_bounds__(FEW_THREADS) __attribute__((amdgpu_waves_per_eu(2, 
     for (int e = tid; e < nb * all; e += FEW_THREADS) {
         const int bi = e / all, row = e - bi * all;
         if (row >= rows) continue;
-        const float val = (float)few_total(red_a + (row >> 7) * ncols * FEW_RB, bi, row & 127, m->sigma[bi]) * m->scale[bi] *
+        const float val = (float)small_total(red_a + (row >> 7) * ncols * FEW_RB, bi, row & 127, m->sigma[bi]) * m->scale[bi] *
                           (float)__builtin_bit_cast(_Float16, sa.row_scale[row]);
         y[(size_t)bi * rows + row] = few_half(val);
     }
@@ -534,15 +607,21 @@ constexpr int FEW_MAX_WGS = 256;     // compute units
 constexpr int FEW_LDS = 156 * 1024;  // (its registers give a workgroup the compute unit to itself)
 
 hipError_t raise_lds(const void* kernel) { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, FEW_LDS); }
-template <int H>
+template <int H, int NP>
 hipError_t raise_lds_few() {
-    hipError_t e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, false, H, false>));
-    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, true, H, false>));
-    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, false, H, true>));
-    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, true, H, true>));
-    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<true, false, H, false>));
-    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<true, true, H, false>));
+    hipError_t e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, false, H, NP, false>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, true, H, NP, false>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, false, H, NP, true>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<false, true, H, NP, true>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<true, false, H, NP, false>));
+    if (e == hipSuccess) e = raise_lds(reinterpret_cast<const void*>(&dbf_few_kernel<true, true, H, NP, false>));
     return e;
+}
+template <int NP>
+hipError_t raise_lds_planes() {
+    for (hipError_t e : {raise_lds_few<2, NP>(), raise_lds_few<4, NP>(), raise_lds_few<6, NP>(), raise_lds_few<8, NP>(), raise_lds_few<FEW_HELD, NP>()})
+        if (e != hipSuccess) return e;
+    return hipSuccess;
 }
 // Whether every x row of a call can be read in 16-byte pieces.
 bool rows_aligned(const DbfPlan& p, const void* x) { return p.x_vec_ok && (reinterpret_cast<uintptr_t>(x) & 15) == 0; }
@@ -570,6 +649,42 @@ FewCut few_cut(int n_items, int n_ct, int T, bool pieces_ok) {
     }
     return c;
 }
+// How a stage that is not cut into column pieces is shared out: `group` tokens and `planes` bit planes of the row tile (16 rows each) to a
+// workgroup, at most one workgroup per compute unit as in few_cut.  Per column tile a workgroup takes about 10 cycles to round a token (18 where
+// it reads the row twice) and 8 to multiply a bit plane; the sign tiles come from L2 for all but one of those that read them.  The least of
+// that sum.  us per call of both stages, (tokens, planes) the same for both:
+//   4096 x 4096, k = 2048 (16 and 32 row tiles), batch 1       2, 8: 9.84   2, 4: 8.57   2, 2: 7.91   (2, 1: 8.1)
+//   three of 4096 x 4096, k = 3072 (72 and 96), batch 1        2, 8: 10.83  2, 4: 9.37
+//   one of those (24 and 32), batch 4                          2, 8: 10.66  2, 4: 9.22   2, 2: 8.61   4, 8: 11.74  4, 2: 9.39
+//   batch 8                                                    2, 8: 10.77  2, 4: 9.41   4, 4: 10.31  4, 2: 9.62   8, 8: 13.81  8, 2: 11.08
+//   batch 16                                                   2, 8: 11.08  4, 8: 12.04  4, 4: 10.62  8, 8: 13.89  8, 2: 11.37
+// Column pieces stay as they are: 28672 -> 8192, k = 12743, batch 1, pieces 20.4, whole rows by planes 23.0.
+struct FewSplit {
+    int group, pieces, planes;
+};
+FewSplit few_split(const FewCut& base, int n_items, int n_ct, int T) {
+    FewSplit best = {base.group, base.pieces, 8};
+    if (base.pieces > 1) return best;
+    int least = 1 << 30;
+    for (int group = 2; group <= 8; group *= 2) {
+        const int nb = group < T ? group : T;
+        if (group > 2 && 2 * nb <= group) continue;   // (the smaller group is the same)
+        if (nb * n_ct > 2560 && group > base.group) continue;
+        const bool fits = (n_ct + 1) * few_tile_block(2 * nb) + (int)sizeof(FewMisc) <= FEW_LDS;   // (rows in one LDS chunk)
+        const bool held = fits && (8 * n_ct + 64 * few_parts(nb) - 1) / (64 * few_parts(nb)) <= FEW_HELD;
+        for (int planes : {8, 4, 2}) {
+            if (planes < 8 && !fits) continue;
+            if ((long long)n_items * ((T + group - 1) / group) * (8 / planes) > FEW_MAX_WGS) continue;
+            const int cost = nb * (held ? 10 : 18) + 8 * planes;
+            if (cost < least) {
+                least = cost;
+                best.group = group;
+                best.planes = planes;
+            }
+        }
+    }
+    return best;
+}
 inline int few_cols(const DbfPlan& p, bool stage_a) { return dbf_col_tiles(stage_a ? p.max_cols_A : p.max_cols_B); }
 
 }  // namespace
@@ -578,8 +693,8 @@ inline int few_cols(const DbfPlan& p, bool stage_a) { return dbf_col_tiles(stage
 hipError_t dbf_few_prepare() {
     static const hipError_t raised = [] {
         const hipError_t e[] = {raise_lds(reinterpret_cast<const void*>(&dbf_small_layer_kernel<false>)),
-                                raise_lds(reinterpret_cast<const void*>(&dbf_small_layer_kernel<true>)), raise_lds_few<2>(), raise_lds_few<4>(),
-                                raise_lds_few<6>(), raise_lds_few<8>(), raise_lds_few<10>()};
+                                raise_lds(reinterpret_cast<const void*>(&dbf_small_layer_kernel<true>)), raise_lds_planes<8>(),
+                                raise_lds_planes<4>(), raise_lds_planes<2>()};
         for (hipError_t x : e)
             if (x != hipSuccess) {
                 (void)hipGetLastError();
@@ -623,36 +738,50 @@ hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y
     const hipError_t raised = dbf_few_prepare();
     if (raised != hipSuccess) return raised;
     // (a prompt, which brings its own middle activations, is never cut: its calls may overlap on one layer and share nothing of it)
-    const FewCut cut_ = few_cut(stage_a ? p.nA1 : p.nB1, few_cols(p, stage_a), T, !t_over && p.d_few_acc && T <= DBF_MAX_BATCH);
-    const int group = cut_.group, pieces = cut_.pieces;
-    const int nb = group < T ? group : T, tile_block = few_tile_block(2 * nb), red = 2 * nb * FEW_RB * 4;
-    const int n_ct = dbf_col_tiles(stage_a ? p.max_cols_A : p.max_cols_B), want = (n_ct + pieces - 1) / pieces;
-    const int fit = (FEW_LDS - (int)sizeof(FewMisc) - red) / tile_block;
-    const int chunk = want < fit ? want : fit;
-    const size_t lds = sizeof(FewMisc) + (size_t)chunk * tile_block + red;
+    const FewSplit split = few_split(few_cut(stage_a ? p.nA1 : p.nB1, few_cols(p, stage_a), T, !t_over && p.d_few_acc && T <= DBF_MAX_BATCH),
+                                     stage_a ? p.nA1 : p.nB1, few_cols(p, stage_a), T);
+    const int group = split.group, pieces = split.pieces, np = split.planes;
+    const int nb = group < T ? group : T, tile_block = few_tile_block(2 * nb), slots = few_slot_bytes(nb, np);
+    const int n_ct = few_cols(p, stage_a), reciprocal = (65536 + pieces - 1) / pieces - 1;
+    const int want = (int)(((unsigned)n_ct * reciprocal + n_ct + 65535u) >> 16);   // tiles of a piece
+    // The wavefronts' sums behind the planes of a whole piece, or in their place where that does not fit (an idle tile behind the planes: see
+    // FewStream::run).
+    const bool aliased = (size_t)want * tile_block + slots + sizeof(FewMisc) > (size_t)FEW_LDS;
+    const int fit = (FEW_LDS - (int)sizeof(FewMisc)) / tile_block - 1, chunk = aliased && want > fit ? fit : want;
+    const int behind = aliased ? (slots > (chunk + 1) * tile_block ? slots : (chunk + 1) * tile_block) : chunk * tile_block + slots;
+    const size_t lds = sizeof(FewMisc) + (size_t)behind;
     const int n_items = stage_a ? p.nA1 : p.nB1;
-    const dim3 grid(n_items, (T + group - 1) / group, pieces);
+    const dim3 grid(n_items, (T + group - 1) / group * (8 / np), pieces);
     uint16_t* io = static_cast<uint16_t*>(stage_a ? y : const_cast<void*>(x));
-    const unsigned tokens = (unsigned)T | (unsigned)group << 16, cut = (unsigned)chunk | (unsigned)pieces << 16;
+    const unsigned tokens = (unsigned)T | (unsigned)group << 16 | (unsigned)aliased << 20;
+    const unsigned cut = (unsigned)chunk | (unsigned)pieces << 10 | (unsigned)reciprocal << 16;
     const DbfStage& s = stage_a ? p.h_stage_A : p.h_stage_B;   // (a layer alone)
     const bool list = p.n_layers > 1;
     const void* first = list ? static_cast<const void*>(p.d_items_1 + (stage_a ? p.nB1 : 0)) : s.bits;
     float* t = t_over ? t_over : list ? nullptr : s.t;
+    // (a layer's tiles and vectors lie in one block, every section on a multiple of 256 bytes)
+    auto from_tiles = [&](const uint16_t* v) { return list || !v ? 0 : (int)((reinterpret_cast<const uint8_t*>(v) - s.bits) / 16); };
+    const int in_off = from_tiles(s.in_scale), row_off = from_tiles(s.row_scale);
     const int held = (8 * n_ct + 64 * few_parts(nb) - 1) / (64 * few_parts(nb));   // vectors of eight values per lane
-    auto launch = [&](auto h) {
-        constexpr int H = decltype(h)::value;
-        void (*kernel)(const void*, const uint16_t*, const uint16_t*, float*, uint16_t*, int*, int, int, unsigned, unsigned) =
-            stage_a ? (list ? dbf_few_kernel<true, true, H, false> : dbf_few_kernel<true, false, H, false>)
-            : rows_aligned(p, x) ? (list ? dbf_few_kernel<false, true, H, false> : dbf_few_kernel<false, false, H, false>)
-                                 : (list ? dbf_few_kernel<false, true, H, true> : dbf_few_kernel<false, false, H, true>);
-        hipLaunchKernelGGL(kernel, grid, dim3(FEW_THREADS), lds, stream, first, s.in_scale, s.row_scale, t, io, p.d_few_acc, s.cols,
+    auto launch = [&](auto h, auto planes) {
+        constexpr int H = decltype(h)::value, NP = decltype(planes)::value;
+        void (*kernel)(const void*, float*, uint16_t*, int*, int, int, int, int, unsigned, unsigned) =
+            stage_a ? (list ? dbf_few_kernel<true, true, H, NP, false> : dbf_few_kernel<true, false, H, NP, false>)
+            : rows_aligned(p, x) ? (list ? dbf_few_kernel<false, true, H, NP, false> : dbf_few_kernel<false, false, H, NP, false>)
+                                 : (list ? dbf_few_kernel<false, true, H, NP, true> : dbf_few_kernel<false, false, H, NP, true>);
+        hipLaunchKernelGGL(kernel, grid, dim3(FEW_THREADS), lds, stream, first, t, io, p.d_few_acc, in_off, row_off, s.cols,
                            list ? n_items : s.rows, tokens, cut);
     };
-    if (held <= 2) launch(std::integral_constant<int, 2>{});
-    else if (held <= 4) launch(std::integral_constant<int, 4>{});
-    else if (held <= 6) launch(std::integral_constant<int, 6>{});
-    else if (held <= 8) launch(std::integral_constant<int, 8>{});
-    else launch(std::integral_constant<int, 10>{});
+    auto launch_planes = [&](auto planes) {
+        if (held <= 2) launch(std::integral_constant<int, 2>{}, planes);
+        else if (held <= 4) launch(std::integral_constant<int, 4>{}, planes);
+        else if (held <= 6) launch(std::integral_constant<int, 6>{}, planes);
+        else if (held <= 8) launch(std::integral_constant<int, 8>{}, planes);
+        else launch(std::integral_constant<int, FEW_HELD>{}, planes);
+    };
+    if (np == 2) launch_planes(std::integral_constant<int, 2>{});
+    else if (np == 4) launch_planes(std::integral_constant<int, 4>{});
+    else launch_planes(std::integral_constant<int, 8>{});
     return hipGetLastError();
 }
 

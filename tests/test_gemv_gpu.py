@@ -904,3 +904,28 @@ def test_few_workgroups_with_rows_of_several_lds_chunks(shapes, batch):
         stack.close()
         for l in layers:
             l.close()
+
+
+@pytest.mark.parametrize("shape,n", [((260, 3000, 3000), 3), ((300, 4000, 1100), 2), ((700, 130, 4033), 1), ((1000, 9001, 200), 1)])
+def test_row_tiles_whose_bit_planes_are_shared_by_workgroups(shape, n):
+    """Two, four or all of the eight bit planes of a row tile to a workgroup, with one to eight tokens (tests/test_routes_cpu.py has the rule), also
+    of the last row tile, whose planes may hold no row: a layer alone and groups, every batch up to 16, against the kind that
+    cuts nothing.  Integer sums: no tolerance."""
+    n_in, n_out, k = shape
+    layers = [G.pack(I.make_layer(n_in, n_out, k, seed=I.seed_for(6, 900 + i + k))) for i in range(n)]
+    stack = B.dbf_stack_create_grouped(layers, [n])
+    try:
+        for batch in range(1, 17):
+            X = G.f16_to_dev(I.make_activations(batch, n_in, I.seed_for(6, 920 + batch)))
+            outs = []
+            for kind in (B.GEMV_MFMA_SPLIT, B.GEMV_AUTO, B.GEMV_AUTO):
+                G.say("bit planes %s x %d batch %d kind %d" % (shape, n, batch, kind))
+                y = torch.full((n, batch, n_out), float("nan"), dtype=torch.float16, device="cuda")
+                B.dbf_stack_gemv(stack, X.data_ptr(), y.data_ptr(), batch, G.stream_handle(), kind)
+                torch.cuda.synchronize()
+                outs.append(y.cpu().view(torch.int16).numpy())
+            assert np.array_equal(outs[1], outs[0]) and np.array_equal(outs[2], outs[0]), batch
+    finally:
+        stack.close()
+        for l in layers:
+            l.close()

@@ -335,3 +335,24 @@ def test_plans_of_257_to_768_row_tiles_keep_their_column_pieces(rec, shape):
         assert sum(x[1][0] for x in launches) > (shape[1] + 127) // 128 + (shape[2] + 127) // 128
     finally:
         rec.lib.dbf_free(l)
+
+
+@pytest.mark.parametrize("n,shape,batch,grids", [
+    (1, (4096, 4096, 2048), 1, [(16, 4, 1), (32, 4, 1)]), (3, (4096, 4096, 3072), 1, [(72, 2, 1), (96, 2, 1)]),
+    (1, (4096, 4096, 3072), 8, [(24, 8, 1), (32, 8, 1)]), (1, (4096, 4096, 3072), 16, [(24, 8, 1), (32, 8, 1)]),
+    (3, (4096, 4096, 3072), 8, [(72, 2, 1), (96, 2, 1)]), (1, (28672, 8192, 12743), 1, [(100, 1, 2), (64, 1, 4)]),
+    (3, (18000, 64, 3000), 8, [(72, 2, 1), (3, 16, 1)])])
+def test_bit_planes_of_a_row_tile_are_dealt_to_idle_compute_units(rec, n, shape, batch, grids):
+    """Grids (row tiles, groups of tokens times groups of bit planes, column pieces): at most one workgroup per compute unit; rows of several
+    LDS chunks keep all eight bit planes in one workgroup."""
+    rec.lib.dbf_tuning_reset()
+    layers = [rec.layer(*shape) for _ in range(n)]
+    stack = rec.stack(layers)
+    try:
+        launches = rec.gemv(layers[0], batch) if n == 1 else rec.stack_gemv(stack, batch)
+        assert _names(launches) == ["dbf_few"] * 2
+        assert [l[1] for l in launches] == grids
+    finally:
+        rec.lib.dbf_stack_free(stack)
+        for l in layers:
+            rec.lib.dbf_free(l)
