@@ -22,7 +22,7 @@
 //   row dots     one wavefront per row, 16-byte loads, butterfly reduction;
 //   column dots  workgroup = 256 columns x 64 rows (4 row lanes x 16 rows, combined in LDS in lane
 //                order), partial sums per 64-row chunk, then summed over the chunks in a fixed order;
-//   norms        partial sums of squares per 64 columns (v) or per thread stride (u), combined in a fixed tree;
+//   norms        partial sums of squares per 32 or 64 columns (v) or per thread stride (u), combined in a fixed tree;
 //   signs        one workgroup per 128 x 64 tile, a thread per four bytes of the tile.
 #include "dbf_kernels.h"
 #include "dbf_wave.h"
@@ -82,6 +82,24 @@ __global__ __launch_bounds__(256) void dbf_svid_row_dots_kernel(const float* __r
         inv = nrm > 0.f ? 1.0f / nrm : 0.f;
     }
     if (lane == 0) u[row] = s * inv;
+}
+
+// The sums of N values (8 or 4) over the wavefront, N / 4 to a lane: entry i of the result, in every lane of the row rho of 16 lanes, is the
+// sum of value i + N / 4 (2 (rho / 2) + rho % 2).  Halves and rows of lanes change places, so that every addition serves two values:
+// 28 instructions for eight values, where a reduction each takes 150.
+template <int N>
+__device__ __forceinline__ void wave_sums(const float (&x)[N], float (&sum)[N / 4]) {
+    float s[N / 2];
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) {
+        const auto p = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x[i]), __builtin_bit_cast(unsigned, x[i + N / 2]), false, false);
+        s[i] = __builtin_bit_cast(float, (unsigned)p[0]) + __builtin_bit_cast(float, (unsigned)p[1]);   // (lanes 0-31: value i, 32-63: i + N / 2)
+    }
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) {
+        const auto p = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, s[i]), __builtin_bit_cast(unsigned, s[i + N / 4]), false, false);
+        sum[i] = dbf_row16_sum_f(__builtin_bit_cast(float, (unsigned)p[0]) + __builtin_bit_cast(float, (unsigned)p[1]));
+    }
 }
 
 // One round in one pass, a workgroup of W wavefronts per compute unit.  Rows come in groups of eight, group 16 q + r being the rows
@@ -174,9 +192,16 @@ __global__ __launch_bounds__(64 * W) void dbf_svid_round_kernel(const float* __r
                 if (FIRST) sdot += ((live(k, 0) ? a.x : 0.f) + (live(k, 1) ? a.y : 0.f)) + ((live(k, 2) ? a.z : 0.f) + (live(k, 3) ? a.w : 0.f));
                 else sdot += a.x * vv[k].x + a.y * vv[k].y + a.z * vv[k].z + a.w * vv[k].w;
             }
-            part[r] = dbf_wave_sum_f(sdot);
+            part[r] = RB >= 4 ? sdot : dbf_wave_sum_f(sdot);
         }
-        if (lane == 0) {
+        if constexpr (RB >= 4) {
+            float sum[RB / 4];
+            wave_sums<RB>(part, sum);
+            if ((lane & 15) == 0) {
+#pragma unroll
+                for (int i = 0; i < RB / 4; ++i) dots[buf][i + RB / 4 * (lane >> 4)][w] = sum[i];
+            }
+        } else if (lane == 0) {
 #pragma unroll
             for (int r = 0; r < RB; ++r) dots[buf][r][w] = part[r];
         }
@@ -277,68 +302,86 @@ __global__ __launch_bounds__(256) void dbf_svid_col_dots_kernel(const float* __r
         partial[(size_t)blockIdx.y * cols + blockIdx.x * COL_BLOCK + c] = ((part[0][c] + part[1][c]) + part[2][c]) + part[3][c];
 }
 
-// v_raw[j] = sum over chunks of partial[chunk][j]: sixteen interleaved running sums (chunks c = 0, 16, 32, ... in the
-// first, and so on), added up in order; and ss_part[workgroup] = sum of v_raw[j]^2 over the workgroup's 64 columns (butterfly
-// order).  Workgroup = 64 columns x the 16 running sums (one wavefront each, sixteen loads in flight: up to 256 chunks are one memory
-// round trip; with four sums and a load at a time 64 chunks took 6.6 us).  Summed in 64 bits: up to 256 partial sums in 32 bits, against
+// v_raw[j] = sum over chunks of partial[chunk][j]: S interleaved running sums (chunks c = 0, S, 2 S, ... in the first, and so on), added up in
+// order; and ss_part[workgroup] = sum of v_raw[j]^2 over the workgroup's COLS columns (butterfly order).  Workgroup = COLS columns x S running
+// sums, 256 chunks in one memory round trip (with four sums and a load at a time 64 chunks took 6.6 us, so 4).  32 columns a workgroup while that is
+// one workgroup per compute unit: calls of 8 rounds, 64 / 32 columns, 1024 x 1024 54.0 / 49.9 us, 4096 x 4096 136.1 / 134.4; 4 rounds of
+// 4096 x 11008 163.5 / 167.8.  Summed in 64 bits: up to 256 partial sums in 32 bits, against
 // 64 of the two passes, left m 20 % further from the exact factor (7.7e-8 against 6.5e-8 at 4096 x 4096, means of 12 inputs; 4.7e-8 with
 // these sums, 3.9e-8 with those of the last kernel too).  The 64-bit sums of both cost a call of 8 rounds 2.5 us of 154.
-constexpr int REDUCE_SUMS = 16;
-__global__ __launch_bounds__(64 * REDUCE_SUMS) void dbf_svid_col_reduce_kernel(const float* __restrict__ partial, int chunks, int cols,
+constexpr int REDUCE_THREADS = 1024;
+inline int reduce_cols(int cols) { return cols <= 8192 ? 32 : 64; }
+template <int COLS>
+__global__ __launch_bounds__(REDUCE_THREADS) void dbf_svid_col_reduce_kernel(const float* __restrict__ partial, int chunks, int cols,
                                                                float* __restrict__ v, float* __restrict__ ss_part) {
-    __shared__ double part[REDUCE_SUMS][64];
-    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int j = blockIdx.x * 64 + lane, jc = min(j, cols - 1);
+    constexpr int S = REDUCE_THREADS / COLS, LOADS = 256 / S, H = 64 / COLS;
+    __shared__ double part[S][COLS];
+    const int c = threadIdx.x % COLS, q = threadIdx.x / COLS;
+    const int j = blockIdx.x * COLS + c, jc = min(j, cols - 1);
     double s = 0.;
-    for (int c0 = q; c0 < chunks; c0 += 16 * REDUCE_SUMS) {
-        float p[16];
+    for (int c0 = q; c0 < chunks; c0 += LOADS * S) {
+        float p[LOADS];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) p[i] = partial[(size_t)min(c0 + REDUCE_SUMS * i, chunks - 1) * cols + jc];
+        for (int i = 0; i < LOADS; ++i) p[i] = partial[(size_t)min(c0 + S * i, chunks - 1) * cols + jc];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s += (double)(c0 + REDUCE_SUMS * i < chunks ? p[i] : 0.f);
+        for (int i = 0; i < LOADS; ++i) s += (double)(c0 + S * i < chunks ? p[i] : 0.f);
     }
-    part[q][lane] = s;
+    part[q][c] = s;
     __syncthreads();
-    if (q == 0) {
-        double sum = part[0][lane];
+    if (threadIdx.x < 64) {   // (COLS = 32: half of the running sums to each half of the wavefront)
+        double sum = part[q][c];
 #pragma unroll
-        for (int i = 1; i < REDUCE_SUMS; ++i) sum += part[i][lane];
+        for (int i = 1; i < S / H; ++i) sum += part[q + H * i][c];
+        if (H == 2) sum += __shfl_xor(sum, 32, 64);
         const float vj = (float)sum;
-        if (j < cols) v[j] = vj;
-        const float ss = wave_sum_f(j < cols ? vj * vj : 0.f);
-        if (lane == 0) ss_part[blockIdx.x] = ss;
+        if (j < cols && q == 0) v[j] = vj;
+        const float ss = wave_sum_f(j < cols && q == 0 ? vj * vj : 0.f);
+        if (threadIdx.x == 0) ss_part[blockIdx.x] = ss;
     }
+}
+template <class... A>
+void launch_reduce(int cols, hipStream_t st, A... a) {
+    const int per = reduce_cols(cols);
+    hipLaunchKernelGGL(per == 32 ? dbf_svid_col_reduce_kernel<32> : dbf_svid_col_reduce_kernel<64>, dim3((cols + per - 1) / per), dim3(REDUCE_THREADS),
+                       0, st, a...);
 }
 
 // The two factors from the unnormalised iterate: m = v_raw / ||v_raw|| (in place) and
 // a = sigma u = u_raw ||v_raw|| / ||u_raw||^2 (sigma = ||v_raw|| / ||u_raw||, u = u_raw / ||u_raw||).
-// Every workgroup forms both lengths itself, in 64 bits and the same fixed order, and then writes its 256 entries of each.
-__global__ __launch_bounds__(256) void dbf_svid_finish_kernel(const float* __restrict__ u_raw, int rows,
+// Every workgroup forms both lengths itself, in 64 bits and the same fixed order, and then writes its 1024 entries of each.  Bound by its chain of
+// latencies: one memory round trip for both lengths, then sixteen partial sums of each from LDS.
+constexpr int FINISH = 1024;
+__global__ __launch_bounds__(FINISH) void dbf_svid_finish_kernel(const float* __restrict__ u_raw, int rows,
                                                              const float* __restrict__ ss_part, int n_ss,
                                                              float* __restrict__ m, int cols, float* __restrict__ a) {
-    __shared__ double part[256];
-    double s = 0.;
-    for (int i = threadIdx.x; i < rows; i += 256) s += (double)u_raw[i] * (double)u_raw[i];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
+    __shared__ double part[2][FINISH / 64];
+    const int tid = threadIdx.x, lane = tid & 63, i = blockIdx.x * FINISH + tid;
+    const float ui = u_raw[min(i, rows - 1)], mi = m[min(i, cols - 1)];
+    double s[2] = {0., 0.};
+    for (int j0 = tid; j0 < rows; j0 += 4 * FINISH) {
+        float p[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) p[e] = u_raw[min(j0 + FINISH * e, rows - 1)];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[0] += j0 + FINISH * e < rows ? (double)p[e] * (double)p[e] : 0.;
     }
-    const double ssu = part[0];
-    __syncthreads();
-    s = 0.;
-    for (int i = threadIdx.x; i < n_ss; i += 256) s += (double)ss_part[i];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
+    for (int j = tid; j < n_ss; j += FINISH) s[1] += (double)ss_part[j];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) s[k] += __shfl_xor(s[k], off, 64);
+        if (lane == 0) part[k][tid >> 6] = s[k];
     }
-    const double nv = sqrt(part[0]);
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < rows) a[i] = ssu > 0. ? (float)(u_raw[i] * (nv / ssu)) : 0.f;
-    if (i < cols && nv > 0.) m[i] = (float)(m[i] / nv);
+    __syncthreads();
+    double ssu = part[0][0], ssv = part[1][0];
+#pragma unroll
+    for (int w = 1; w < FINISH / 64; ++w) {
+        ssu += part[0][w];
+        ssv += part[1][w];
+    }
+    const double nv = sqrt(ssv);
+    if (i < rows) a[i] = ssu > 0. ? (float)(ui * (nv / ssu)) : 0.f;
+    if (i < cols && nv > 0.) m[i] = (float)(mi / nv);
 }
 
 // Sign(Z) into the tile layout: tile = 128 rows x 64 columns, byte 256 g + 16 r + j, bit s = sign of
@@ -402,7 +445,7 @@ inline SvidWorkspace svid_workspace(int rows, int cols) {
     w.u = off;        off = up256(off + 4 * (size_t)rows);
     w.v = off;        off = up256(off + 4 * (size_t)cols);
     w.partial = off;  off = up256(off + 4 * chunks * (size_t)cols);
-    w.scalars = off;  off = up256(off + 4 * (((size_t)cols + 63) / 64));   // squared length of v_raw per 64 columns
+    w.scalars = off;  off = up256(off + 4 * (((size_t)cols + reduce_cols(cols) - 1) / reduce_cols(cols)));   // squared length of v_raw per workgroup of the column reduction
     w.total = off;
     return w;
 }
@@ -435,10 +478,11 @@ extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* 
                         (reinterpret_cast<uintptr_t>(m_dev) & 15) == 0) ? 1 : 0;
     const int chunks = (rows + COL_CHUNK_ROWS - 1) / COL_CHUNK_ROWS;
     const int n_rt = dbf_row_tiles(rows), n_ct = dbf_col_tiles(cols);
-    const int n_ss = (cols + 63) / 64;
+    const int n_ss = (cols + reduce_cols(cols) - 1) / reduce_cols(cols);
 
     // One pass per round wherever rows can be held: up to 24576 columns in 16-byte pieces, 12288 in single values.  8 rounds, us, two
-    // passes / one: 4096 x 4096 247 / 157; before the 64-bit column sums 154, and 2048 x 4096 161 / 93, 8192 x 8192 (one pass before: 548) 472.
+    // passes / one: 4096 x 4096 247 / 157, now 134 (the row sums of a batch reduced together, 15.6 -> 13.7 us a round; 32 columns to a workgroup of
+    // the reduction; the last kernel 6.7 -> 3.8); 2048 x 4096 161 / 93, now 83; 4 rounds of 8192 x 8192 262, now 252.
     const int cpl = (cols + 4095) / 4096;  // float4s per thread and row of a workgroup of 1024
     const bool one_pass = cpl <= (vec_ok ? 6 : 3);
     if (!(one_pass && cpl == 1 && vec_ok))   // (else the first pass writes the signs)
@@ -467,7 +511,7 @@ extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* 
                     default: n_wg = launch_round<16, 3, false>(first, st, ra); break;
                 }
             }
-            hipLaunchKernelGGL(dbf_svid_col_reduce_kernel, dim3(n_ss), dim3(64 * REDUCE_SUMS), 0, st, partial, n_wg, cols, v, ss_part);
+            launch_reduce(cols, st, partial, n_wg, cols, v, ss_part);
             continue;
         }
         if (it == 0)
@@ -478,10 +522,10 @@ extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* 
                                ss_part, n_ss, u, vec_ok);
         hipLaunchKernelGGL(dbf_svid_col_dots_kernel, dim3((cols + COL_BLOCK - 1) / COL_BLOCK, chunks), dim3(256), 0, st,
                            Z, rows, cols, u, partial);
-        hipLaunchKernelGGL(dbf_svid_col_reduce_kernel, dim3(n_ss), dim3(64 * REDUCE_SUMS), 0, st, partial, chunks, cols, v, ss_part);
+        launch_reduce(cols, st, partial, chunks, cols, v, ss_part);
     }
     const int longest = rows > cols ? rows : cols;
-    hipLaunchKernelGGL(dbf_svid_finish_kernel, dim3((longest + 255) / 256), dim3(256), 0, st, u, rows, ss_part, n_ss, v,
+    hipLaunchKernelGGL(dbf_svid_finish_kernel, dim3((longest + FINISH - 1) / FINISH), dim3(FINISH), 0, st, u, rows, ss_part, n_ss, v,
                        cols, static_cast<float*>(a_dev));
     if (hipGetLastError() != hipSuccess) return DBF_EHIP;
     return DBF_OK;

@@ -99,3 +99,17 @@ def test_svid_one_pass_rounds_at_the_edges_of_their_row_lengths(rows, cols):
         assert np.array_equal(words, O.pack_signs(S)), "sign bits differ"
         assert np.max(np.abs(a - a_ref)) <= TOL * np.max(np.abs(a_ref))
         assert np.max(np.abs(m - m_ref)) <= TOL * np.max(np.abs(m_ref))
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 31), (1023, 32), (1025, 33), (4097, 8192), (260, 8193), (4100, 95), (2, 1030)])
+def test_svid_at_the_edges_of_its_reductions(rows, cols):
+    """32 or 64 columns to a workgroup of the column reduction (8192 columns and less, more), 1024 entries of either factor to a workgroup of the last
+    kernel, which takes the rows' lengths 4096 at a time.  Tolerance: as above."""
+    Z = I.make_svid_matrix(rows, cols, I.seed_for(8, 80 + rows + cols))
+    for iters in (1, 2, 5):
+        G.say("start svid %dx%d iters=%d" % (rows, cols, iters))
+        S, a_ref, m_ref = O.svid(Z.astype(np.float64), iters)
+        a, m, words = _run(Z, iters)
+        assert np.array_equal(words, O.pack_signs(S)), "sign bits differ"
+        assert np.max(np.abs(a - a_ref)) <= TOL * np.max(np.abs(a_ref))
+        assert np.max(np.abs(m - m_ref)) <= TOL * np.max(np.abs(m_ref))
