@@ -3,7 +3,7 @@
 //
 //     Minv = (B^T B + rho I)^-1  (q x q),   C = B^T W  (q x r)
 //
-//     R  = C + rho (a . S . m^T - U)           dbf_admm_rhs_kernel     (A = a . S . m^T never exists densely: S is read
+//     R  = C + rho (a . S . m^T - U)           dbf_admm_operands_kernel (A = a . S . m^T never exists densely: S is read
 //                                                                       from the packed tile layout; R only as fp16 planes)
 //     Z  = Minv^T R + U   (= W_hat + U)        dbf_split_gemm_kernel   fp16 matrix cores, operands split in two
 //                                                                       (dbf_split_gemm.h), U added in the epilogue
@@ -12,8 +12,8 @@
 //
 // The contraction is q x q x r in fp32 accuracy (34 GFLOP at q = 2048, r = 4096) and dominates; the elementwise
 // kernels and the projection are bandwidth bound.  Measured at that size: the contraction 331 us on the fp32 matrix cores, 219 on the bf16
-// ones with operands in three parts, 106 on the fp16 ones with operands in two, whose planes cost 7 (Minv) and 16 us (R, with its making); the update with two
-// rounds of SVID 388, 288, 190 us; error against 64 bits 8.1e-6, 5.1e-6, 1.8e-6 (fewer roundings: 16 products enter the accumulator at
+// ones with operands in three parts, 106 on the fp16 ones with operands in two, whose planes, with the making of R, take 18 us in one launch (22 in two); the update
+// with two rounds of SVID 388, 288, now 182 us; error against 64 bits 8.1e-6, 5.1e-6, 1.8e-6 (fewer roundings: 16 products enter the accumulator at
 // once, and half as many of them).
 // The paper gives no kernel design for this step.
 #include "dbf_kernels.h"
@@ -83,13 +83,19 @@ __global__ __launch_bounds__(256) void dbf_admm_dual_kernel(const float* __restr
     }
 }
 
-// R = C + rho (a_k m_j s_kj - U) (q x r; k = its row is the summation index of the contraction), written straight into
-// fp16 planes: R exists nowhere in fp32.  The lane's eight rows are one bit of eight bytes 16 apart of one sign tile.
-__global__ __launch_bounds__(256) void dbf_admm_rhs_kernel(const float* __restrict__ C, const float* __restrict__ U, float rho,
-                                                          const float* __restrict__ a, const float* __restrict__ m,
-                                                          const uint8_t* __restrict__ bits, int q, int r, int n_ct,
-                                                          uint8_t* __restrict__ planes) {
-    const SgSite s = sg_site(q, 2);
+// The operands of the contraction in one launch: the planes of Minv (blockIdx.y below q_blocks), and R = C + rho (a_k m_j s_kj - U) (q x r; k = its
+// row is the summation index of the contraction), written straight into fp16 planes: R exists nowhere in fp32.  A lane's eight rows of R are
+// one bit of eight bytes 16 apart of one sign tile.
+__global__ __launch_bounds__(256) void dbf_admm_operands_kernel(const float* __restrict__ Minv, uint8_t* __restrict__ Minv_planes, int q_blocks,
+                                                               const float* __restrict__ C, const float* __restrict__ U, float rho,
+                                                               const float* __restrict__ a, const float* __restrict__ m,
+                                                               const uint8_t* __restrict__ bits, int q, int r, int n_ct,
+                                                               uint8_t* __restrict__ planes) {
+    if ((int)blockIdx.y < q_blocks) {
+        sg_split_dense(Minv, q, q, q, nullptr, Minv_planes, blockIdx.y);
+        return;
+    }
+    const SgSite s = sg_site(q, 2, blockIdx.y - q_blocks);
     const int j = min(s.i, r - 1);
     const float mj = m[j];
     float x[2][8];
@@ -122,7 +128,7 @@ __global__ __launch_bounds__(256) void dbf_admm_rhs_kernel(const float* __restri
 // contraction read (R's for c > jb, Y's for c <= jb) and nowhere else.
 // What bounds it: the chain.  Per block row 2 launches and 4 x 32 pivots; the update's products take 3 us of it.  Measured at
 // q = 2048 (16 block rows): panel 5.6 us, update 31.6 us of which the pivots 25 while every entry of a pivot row went through a scalar register and
-// the pivot's root stood in the chain; now 6.1 and 23.7.  With p = r = 4096 the constants took 890 us so, now 756.
+// the pivot's root stood in the chain; now 6.1 and 23.7.  With p = r = 4096 the constants took 890 us so, now 740.
 // ---------------------------------------------------------------------------------------------
 constexpr int NB = 128;        // block size: the contraction's tile
 constexpr int CH_LD = NB + 4;  // LDS row length of a diagonal block: rows start on 16 bytes
@@ -596,10 +602,10 @@ extern "C" int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int
     const int n_rt = dbf_row_tiles(q), n_ct = dbf_col_tiles(r);
     const int vec_r = ((r & 3) == 0 && (reinterpret_cast<uintptr_t>(U) & 15) == 0) ? 1 : 0;  // (Z is 256-byte aligned)
 
-    hipLaunchKernelGGL(dbf_split_dense_kernel, sg_plane_grid(q, q), dim3(256), 0, st, static_cast<const float*>(Minv_dev), (size_t)q, q,
-                       q, nullptr, base + w.P);
-    hipLaunchKernelGGL(dbf_admm_rhs_kernel, sg_plane_grid(q, r), dim3(256), 0, st, C, U, rho, static_cast<const float*>(a_dev),
-                       static_cast<const float*>(m_dev), static_cast<const uint8_t*>(bits_dev), q, r, n_ct, base + w.R);
+    const dim3 of_minv = sg_plane_grid(q, q), of_r = sg_plane_grid(q, r);   // (the same summation indices: the same x)
+    hipLaunchKernelGGL(dbf_admm_operands_kernel, dim3(of_r.x, of_minv.y + of_r.y), dim3(256), 0, st, static_cast<const float*>(Minv_dev), base + w.P,
+                       (int)of_minv.y, C, U, rho, static_cast<const float*>(a_dev), static_cast<const float*>(m_dev),
+                       static_cast<const uint8_t*>(bits_dev), q, r, n_ct, base + w.R);
     SplitGemmArgs g = {};
     g.P = base + w.P;  g.Q = base + w.R;
     g.add = U;  g.lda = r;
@@ -637,7 +643,6 @@ inline PrepWorkspace prep_workspace(int p, int q, int r) {
     w.total = off;
     return w;
 }
-__global__ void dbf_admm_clear_flag_kernel(int* flag) { *flag = 0; }
 }  // namespace
 
 extern "C" size_t dbf_admm_prepare_workspace_bytes(int p, int q, int r) {
@@ -667,13 +672,11 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
     const float* b = static_cast<const float*>(b_dev);
     const int n_ct = dbf_col_tiles(p);
 
-    hipLaunchKernelGGL(dbf_admm_clear_flag_kernel, dim3(1), dim3(1), 0, st, fail);
     uint8_t *S = base + w.S, *V = base + w.V;
-    hipLaunchKernelGGL((dbf_split_signs_kernel<false>), sg_plane_grid(p, q), dim3(256), 0, st, bits, n_ct, p, q, nullptr, S);
     // G = B^T B + rho I with B[l][j] = b_l S[j][l] m2_j: the signs against the signs times b^2, m2 by output row and column in
     // the epilogue.  Upper blocks only.
+    hipLaunchKernelGGL(dbf_split_signs_kernel, sg_plane_grid(p, q), dim3(256), 0, st, bits, n_ct, p, q, b, S, V, fail);
     {
-        hipLaunchKernelGGL((dbf_split_signs_kernel<true>), sg_plane_grid(p, q), dim3(256), 0, st, bits, n_ct, p, q, b, V);
         SplitGemmArgs g = {};
         g.P = S;  g.Q = V;  g.out = G;  g.ldo = q;  g.M = q;  g.N = q;  g.K = p;
         g.rs = m2;  g.cs = m2;  g.diag = rho;  g.upper = 1;

@@ -70,11 +70,11 @@ __device__ __forceinline__ void sg_store2(uint8_t* at, const float (&x)[8], floa
 
 // The plane kernels: a workgroup of 256 threads has a chunk of 128 k and 32 lines, a wavefront two fragments of it.
 struct SgSite {
-    int i, k0[2];    // this lane's output index and the first k of its two fragments
+    int i, k0[2];    // this lane's output index (of the ib-th 32) and the first k of its two fragments
     size_t off[2];   // byte offset of the lane's 16 bytes in piece 0 (pieces are 4 fragments apart)
 };
-__device__ inline SgSite sg_site(int K, int pieces) {
-    const int lane = threadIdx.x & 63, n_kb = sg_kblocks(K), ib = blockIdx.y;
+__device__ inline SgSite sg_site(int K, int pieces, int ib) {
+    const int lane = threadIdx.x & 63, n_kb = sg_kblocks(K);
     SgSite s;
     s.i = 32 * ib + (lane & 31);
 #pragma unroll
@@ -109,9 +109,9 @@ __device__ __forceinline__ void sg_split_chunk(uint8_t* planes, int K, int M, co
 
 // Planes of a dense k-major matrix src [K][ld >= M], its rows scaled by kscale (or NULL).  A wavefront's load of one k is two
 // runs of 128 bytes.  Bound by memory: 4 bytes read and 4 written per element.
-__global__ __launch_bounds__(256) void dbf_split_dense_kernel(const float* __restrict__ src, size_t ld, int K, int M,
-                                                             const float* __restrict__ kscale, uint8_t* __restrict__ planes) {
-    const SgSite s = sg_site(K, 2);
+__device__ __forceinline__ void sg_split_dense(const float* __restrict__ src, size_t ld, int K, int M, const float* __restrict__ kscale,
+                                               uint8_t* __restrict__ planes, int ib) {
+    const SgSite s = sg_site(K, 2, ib);
     float x[2][8];
 #pragma unroll
     for (int n = 0; n < 2; ++n)
@@ -124,12 +124,19 @@ __global__ __launch_bounds__(256) void dbf_split_dense_kernel(const float* __res
     sg_split_chunk(planes, K, M, s, x);
 }
 
-// Planes of a packed sign matrix S (rows = output index i, columns = k) in the 128 x 64 tile layout.  SCALED: two planes of
-// +-kscale[k]^2; else one plane of +-1.  A lane's eight signs are bit (i % 128) / 16 of eight consecutive bytes.
-template <bool SCALED>
-__global__ __launch_bounds__(256) void dbf_split_signs_kernel(const uint8_t* __restrict__ bits, int n_ct, int K, int M,
+__global__ __launch_bounds__(256) void dbf_split_dense_kernel(const float* __restrict__ src, size_t ld, int K, int M,
                                                              const float* __restrict__ kscale, uint8_t* __restrict__ planes) {
-    const SgSite s = sg_site(K, SCALED ? 2 : 1);
+    sg_split_dense(src, ld, K, M, kscale, planes, blockIdx.y);
+}
+
+// Planes of a packed sign matrix S (rows = output index i, columns = k) in the 128 x 64 tile layout: `signs`, one plane of +-1, and `scaled`, two
+// planes of +-kscale[k]^2.  A lane's eight signs are bit (i % 128) / 16 of eight consecutive bytes.  (One launch for both, which also clears
+// *flag: as three they took 6.5, 9.3 and 5 us.)
+__global__ __launch_bounds__(256) void dbf_split_signs_kernel(const uint8_t* __restrict__ bits, int n_ct, int K, int M,
+                                                             const float* __restrict__ kscale, uint8_t* __restrict__ signs,
+                                                             uint8_t* __restrict__ scaled, int* __restrict__ flag) {
+    const SgSite s = sg_site(K, 2, blockIdx.y), s1 = sg_site(K, 1, blockIdx.y);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *flag = 0;
     const int i = min(s.i, sg_lines(M) - 1), ir = i & 127;
     float x[2][8];
 #pragma unroll
@@ -138,28 +145,17 @@ __global__ __launch_bounds__(256) void dbf_split_signs_kernel(const uint8_t* __r
         const unsigned* b = reinterpret_cast<const unsigned*>(bits + ((size_t)(i >> 7) * n_ct + (k0 >> 6)) * DBF_TILE_BYTES +
                                                               256 * ((k0 >> 4) & 3) + 16 * (ir & 15) + (k0 & 15));   // (a caller's: 4-byte aligned)
         const unsigned b0 = b[0], b1 = b[1];
+        v8h h;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const unsigned bit = ((e < 4 ? b0 : b1) >> (8 * (e & 3) + (ir >> 4))) & 1u;
-            float v = 1.f;
-            if (SCALED) {
-                const float c = kscale[min(s.k0[n] + e, K - 1)];
-                v = c * c;
-            }
-            x[n][e] = (s.k0[n] + e < K && s.i < M) ? (bit ? v : -v) : 0.f;
+            const float c = kscale[min(s.k0[n] + e, K - 1)], sign = (s.k0[n] + e < K && s.i < M) ? (bit ? 1.f : -1.f) : 0.f;
+            h[e] = (_Float16)sign;
+            x[n][e] = sign != 0.f ? sign * (c * c) : 0.f;   // (a scale past the end may be no number)
         }
+        *reinterpret_cast<v8h*>(signs + s1.off[n]) = h;
     }
-    if (SCALED) {
-        sg_split_chunk(planes, K, M, s, x);
-    } else {
-#pragma unroll
-        for (int n = 0; n < 2; ++n) {
-            v8h h;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) h[e] = (_Float16)x[n][e];
-            *reinterpret_cast<v8h*>(planes + s.off[n]) = h;
-        }
-    }
+    sg_split_chunk(scaled, K, M, s, x);
 }
 
 // ---------------------------------------------------------------------------------------------
