@@ -26,7 +26,7 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 constexpr int FEW_WAVES = 8;
 constexpr int FEW_THREADS = 64 * FEW_WAVES;
 constexpr int FEW_PF = 8;            // tiles in flight per wavefront
-constexpr int FEW_HELD = 10;         // vectors of eight input values a lane can hold
+constexpr int FEW_HELD = 12;         // vectors of eight input values a lane can hold (four rows of 12288; 10: 11008 -> 4096, k = 4477, batch 8 / 16 14.64 / 18.71 us, so 14.21 / 16.85)
 constexpr int FEW_RB = DBF_TILE_ROWS + 1;  // LDS row of a reduction buffer (see RB_STRIDE in dbf_gemv_mfma.hip)
 constexpr float QMAX = 32512.f;
 constexpr unsigned OOB = 0x80000000u;
@@ -619,7 +619,8 @@ hipError_t raise_lds_few() {
 }
 template <int NP>
 hipError_t raise_lds_planes() {
-    for (hipError_t e : {raise_lds_few<2, NP>(), raise_lds_few<4, NP>(), raise_lds_few<6, NP>(), raise_lds_few<8, NP>(), raise_lds_few<FEW_HELD, NP>()})
+    for (hipError_t e : {raise_lds_few<2, NP>(), raise_lds_few<4, NP>(), raise_lds_few<6, NP>(), raise_lds_few<8, NP>(), raise_lds_few<10, NP>(),
+                         raise_lds_few<FEW_HELD, NP>()})
         if (e != hipSuccess) return e;
     return hipSuccess;
 }
@@ -777,6 +778,7 @@ hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y
         else if (held <= 4) launch(std::integral_constant<int, 4>{}, planes);
         else if (held <= 6) launch(std::integral_constant<int, 6>{}, planes);
         else if (held <= 8) launch(std::integral_constant<int, 8>{}, planes);
+        else if (held <= 10) launch(std::integral_constant<int, 10>{}, planes);
         else launch(std::integral_constant<int, FEW_HELD>{}, planes);
     };
     if (np == 2) launch_planes(std::integral_constant<int, 2>{});

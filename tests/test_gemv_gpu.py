@@ -906,10 +906,11 @@ def test_few_workgroups_with_rows_of_several_lds_chunks(shapes, batch):
             l.close()
 
 
-@pytest.mark.parametrize("shape,n", [((260, 3000, 3000), 3), ((300, 4000, 1100), 2), ((700, 130, 4033), 1), ((1000, 9001, 200), 1)])
+@pytest.mark.parametrize("shape,n", [((260, 3000, 3000), 3), ((300, 4000, 1100), 2), ((700, 130, 4033), 1), ((1000, 9001, 200), 1),
+                                     ((11008, 4096, 300), 1), ((12288, 3900, 700), 1), ((12296, 300, 3900), 1)])
 def test_row_tiles_whose_bit_planes_are_shared_by_workgroups(shape, n):
     """Two, four or all of the eight bit planes of a row tile to a workgroup, with one to eight tokens (tests/test_routes_cpu.py has the rule), also
-    of the last row tile, whose planes may hold no row: a layer alone and groups, every batch up to 16, against the kind that
+    of the last row tile, whose planes may hold no row, and of rows of 11 and 12 vectors a lane and more than can be held: a layer alone and groups, every batch up to 16, against the kind that
     cuts nothing.  Integer sums: no tolerance."""
     n_in, n_out, k = shape
     layers = [G.pack(I.make_layer(n_in, n_out, k, seed=I.seed_for(6, 900 + i + k))) for i in range(n)]
