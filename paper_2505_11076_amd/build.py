@@ -95,20 +95,117 @@ def _ring_homes_report(code: str, pf: int, pf_f4: int):
     return seen, bad
 
 
+def _assembly(src: str) -> str:
+    import tempfile
+    with tempfile.TemporaryDirectory() as tmp:
+        asm = os.path.join(tmp, "code.s")
+        cmd = [_hipcc(), *[f for f in FLAGS if f != "-fPIC"], "--cuda-device-only", "-S", "-x", "hip",
+               os.path.join(CSRC, src), "-o", asm]
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc -S failed for %s:\n%s" % (src, res.stderr))
+        return open(asm).read()
+
+
+# The third guard, for vector arithmetic written as inline assembly.  gfx950 wants a number of instructions between some writes and
+# uses of a register and does not wait by itself; the compiler keeps them in its own code, but neither looks into an asm block nor
+# knows what the statement behind one reads.  A missing wait gives an old value now and then, which no test shows reliably.
+WAITS_SRC = "dbf_admm.hip"
+TRANSCENDENTAL = ("v_rcp", "v_rsq", "v_sqrt", "v_exp", "v_log", "v_sin", "v_cos")
+
+
+def _wait_states_report(code: str):
+    """(vector instructions seen, [complaints]) for assembly text, along the order of the lines (a branch is taken to fall through).
+    Wait states between a vector instruction that writes a register and one that uses it: a scalar register as an operand 2, as a lane
+    number 4; a vector register read by v_readlane 1, by a DPP operand 2, by a lane swap 2; the result of a
+    transcendental instruction by another kind 1."""
+    import re
+    seen, bad, kernel, now = 0, [], "?", 0
+    sgpr, vgpr, trans = {}, {}, {}      # register -> when the last vector instruction that wrote it was issued
+
+    def registers(text):
+        out = []
+        for kind, lo, hi, one in re.findall(r"\b([vs])\[(\d+):(\d+)\]|\b([vs]\d+|vcc)\b", text):
+            out += [one] if one else ["%s%d" % (kind, i) for i in range(int(lo), int(hi) + 1)]
+        return out
+
+    for number, line in enumerate(code.splitlines(), 1):
+        label = re.match(r"(_Z\w+):", line)
+        if label:
+            kernel, sgpr, vgpr, trans = label.group(1), {}, {}, {}
+            continue
+        line = line.split(";")[0].strip()
+        if not line or line[0] in ".;" or line.endswith(":"):
+            continue
+        op, _, rest = line.partition(" ")
+        op, _, tail = op.partition("\t")
+        rest = (tail + " " + rest).strip()
+        if op == "s_nop":
+            now += 1 + int(rest, 0)
+            continue
+        now += 1
+        if op in ("s_branch", "s_endpgm", "s_setpc_b64"):
+            sgpr, vgpr, trans = {}, {}, {}
+            continue
+        args = [a.strip() for a in rest.split(",")]
+        if not op.startswith("v_"):     # (whatever else writes a register is waited for in other ways)
+            if not re.match(r"(ds|global|buffer|flat|scratch)_(store|write)|s_(cmp|bitcmp|cbranch|waitcnt|barrier)", op):
+                for r in registers(args[0]):
+                    for t in (sgpr, vgpr, trans):
+                        t.pop(r, None)
+            continue
+        seen += 1
+        swap, mfma = "_swap_" in op, op.startswith("v_mfma")
+        two = op.startswith(("v_add_co", "v_sub_co", "v_subrev_co", "v_addc_co", "v_subb_co", "v_subbrev_co", "v_div_scale", "v_mad_u64", "v_mad_i64"))
+        n_out = 2 if swap or two else 1
+        sources = registers(" ".join(args if swap else args[n_out:]))
+        if op.startswith(("v_fmac", "v_mac", "v_div_fmas")):
+            sources += registers(args[0]) if "fmas" not in op else ["vcc"]
+
+        def want(table, register, n, what):
+            if register in table and now - table[register] - 1 < n:
+                bad.append("%s, line %d: %d of %d wait states before `%s`, which reads %s (%s)"
+                           % (kernel, number, now - table[register] - 1, n, line, register, what))
+
+        dpp = "_dpp" in op or re.search(r"\b(quad_perm|row_\w+|wave_\w+):", rest)
+        for r in sources:
+            want(sgpr, r, 2, "scalar operand")
+            if op.startswith(("v_readlane", "v_readfirstlane")):
+                want(vgpr, r, 1, "lane read")
+            if swap:
+                want(vgpr, r, 2, "lane swap")
+            if not op.startswith(TRANSCENDENTAL):
+                want(trans, r, 1, "transcendental result")
+        if op.startswith(("v_readlane", "v_writelane")):
+            for r in registers(args[2]):
+                want(sgpr, r, 4, "lane number")
+        if dpp:
+            for r in registers(args[n_out]):
+                want(vgpr, r, 2, "DPP operand")
+        for r in registers(" ".join(args[:n_out])):
+            for t in (sgpr, vgpr, trans):
+                t.pop(r, None)
+            if not mfma:
+                (vgpr if r[0] == "v" and r != "vcc" else sgpr)[r] = now
+                if op.startswith(TRANSCENDENTAL):
+                    trans[r] = now
+    return seen, bad
+
+
+def _check_wait_states() -> None:
+    seen, bad = _wait_states_report(_assembly(WAITS_SRC))
+    if not seen:
+        raise RuntimeError("%s: no vector instruction found in the assembly" % WAITS_SRC)
+    if bad:
+        raise RuntimeError("%s: wait states are missing:\n  %s" % (WAITS_SRC, "\n  ".join(bad)))
+
+
 def _check_ring_homes() -> None:
     import re
-    import tempfile
     text = open(os.path.join(CSRC, RING_SRC)).read()
     pf = int(re.search(r"#define DBF_PF (\d+)", text).group(1))
     pf_f4 = int(re.search(r"#define DBF_PF_F4 (\d+)", text).group(1))
-    with tempfile.TemporaryDirectory() as tmp:
-        asm = os.path.join(tmp, "ring.s")
-        cmd = [_hipcc(), *[f for f in FLAGS if f != "-fPIC"], "--cuda-device-only", "-S", "-x", "hip",
-               os.path.join(CSRC, RING_SRC), "-o", asm]
-        res = subprocess.run(cmd, capture_output=True, text=True)
-        if res.returncode != 0:
-            raise RuntimeError("hipcc -S failed for %s:\n%s" % (RING_SRC, res.stderr))
-        code = open(asm).read()
+    code = _assembly(RING_SRC)
     seen, bad = _ring_homes_report(code, pf, pf_f4)
     if not seen:
         raise RuntimeError("%s: no items kernel found in the assembly (has it been renamed?)" % RING_SRC)
@@ -196,10 +293,11 @@ def build_route_recorder(runtime_cpp: str) -> str:
 
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as pool:
-        ring = pool.submit(_check_ring_homes)
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 2)) as pool:
+        checks = [pool.submit(_check_ring_homes), pool.submit(_check_wait_states)]
         objs = list(pool.map(_compile, SOURCES))
-        ring.result()
+        for c in checks:
+            c.result()
     cmd = [_hipcc(), "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:

@@ -174,13 +174,16 @@ __device__ __forceinline__ void chol_rows(float (&x)[32], float v0, float v1, fl
 }
 // Pivot C, its value to lane C of piv: the rows below lose their multiples of row C.  t = x[C] / pivot (reciprocal and one Newton step), and lanes 0-15
 // of x[C] in every 16 lanes of v0, lanes 16-31 in every 16 of v1.  (One block, so that what the instructions want between a write and a
-// use -- two others before a lane swap of a fresh register and before a lane broadcast of one, one behind the reciprocal -- is the work itself.)
+// use is the work itself as far as it goes: one other before a lane read of a fresh register, two between the lane read and a use of its scalar
+// register, two before a lane swap of a fresh register and before a lane broadcast of one, one behind the reciprocal.  The
+// build checks the assembly for them: _wait_states_report in build.py.)
 template <int C>
 __device__ __forceinline__ void chol_pivot(float (&x)[32], float& piv) {
     float v0, v1, t, r, p;
     asm("v_mov_b32 %0, %6\n\t"
-        "v_mov_b32 %1, %6\n\t"
         "v_readlane_b32 %4, %6, %7\n\t"
+        "v_mov_b32 %1, %6\n\t"
+        "s_nop 0\n\t"
         "v_rcp_f32 %3, %4\n\t"
         "v_permlane32_swap_b32 %0, %1\n\t"
         "v_mov_b32 %1, %0\n\t"
@@ -242,7 +245,7 @@ __device__ __forceinline__ int chol_factor32_any(float* H, float* T, int lane) {
 // (lower triangular, zeros above), and T (leading dimension CH_LDT) receives Y^T = R^-1.  Lane l < 32 holds column l of
 // the block, lane 32 + l column l of the identity.  A pivot row's entries reach the other rows through lane broadcasts that are part
 // of the multiplication; the rows are scaled by 1 / sqrt(pivot) at the end, all roots at once.  What bounds it: a wavefront on its own issues one
-// instruction in four cycles, here 11 and one per row below for a pivot.  (With every entry through a scalar register, two
+// instruction in four cycles, here 12 and one per row below for a pivot.  (With every entry through a scalar register, two
 // instructions a row, and the root in the chain from pivot to pivot 8300 cycles, so 4400.)  Returns whether a pivot was not positive.
 __device__ __forceinline__ int chol_factor32(float* H, float* T, int lane) {
     const int l32 = lane & 31;

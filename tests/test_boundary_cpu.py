@@ -325,6 +325,43 @@ def test_build_refuses_spills_in_kernels_with_hand_issued_loads():
     assert set(Bd.NO_SPILL) == {"dbf_gemv_mfma.hip", "dbf_gemm_i8.hip"}
 
 
+PIVOT = ["v_mov_b32 v5, v8", "v_readlane_b32 s10, v8, 0", "v_mov_b32 v9, v8", "s_nop 0", "v_rcp_f32 v3, s10", "v_permlane32_swap_b32 v5, v9",
+         "v_mov_b32 v9, v5", "v_fma_f32 v7, -s10, v3, 1.0", "v_fma_f32 v3, v7, v3, v3", "v_permlane16_swap_b32 v5, v9", "v_mul_f32 v7, v8, v3",
+         "v_writelane_b32 v191, s10, 0", "v_fmac_f32_dpp v160, -v5, v7 row_newbcast:1 row_mask:0xf bank_mask:0xf"]
+
+
+@pytest.mark.parametrize("drop,what", [
+    (None, None), ("s_nop 0", "1 of 2 wait states before `v_rcp_f32 v3, s10`"), ("v_writelane_b32 v191, s10, 0", "1 of 2 wait states before `v_fmac"),
+    ("v_mov_b32 v5, v8", "0 of 1 wait states before `v_readlane"), ("v_fma_f32 v3, v7, v3, v3", "1 of 2 wait states before `v_permlane16")])
+def test_build_refuses_missing_wait_states(drop, what):
+    """The reader of the assembly on a pivot as it is written and on ones that lack an instruction that was a wait."""
+    from paper_2505_11076_amd import build as Bd
+    lines = ["v_add_f32_e32 v8, v1, v2"] + [l for l in PIVOT if l != drop] + ["s_endpgm"]
+    seen, bad = Bd._wait_states_report("_Zkernel:\n" + "\n".join("\t" + l + " ; note" for l in lines))
+    assert seen >= 11
+    if what is None:
+        assert bad == []
+    else:
+        assert any(what in b for b in bad), bad
+    # a reciprocal used at once; an index that a vector instruction has just written, and a wait that is long enough
+    _, bad = Bd._wait_states_report("v_rcp_f32 v3, v1\nv_mul_f32 v4, v3, v2\n")
+    assert len(bad) == 1 and "0 of 1" in bad[0]
+    _, bad = Bd._wait_states_report("v_readfirstlane_b32 s4, v1\ns_nop 2\nv_readlane_b32 s5, v2, s4\n")
+    assert len(bad) == 1 and "3 of 4" in bad[0]
+    assert Bd._wait_states_report("v_readfirstlane_b32 s4, v1\ns_nop 3\nv_readlane_b32 s5, v2, s4\n")[1] == []
+
+
+def test_kernels_with_vector_arithmetic_in_assembly_keep_their_wait_states():
+    """Every source with such a block is one that the build checks, and the check passes."""
+    from paper_2505_11076_amd import build as Bd
+    import re
+    with_blocks = [f for f in os.listdir(Bd.CSRC) if re.search(r'asm(?: volatile)?\(\s*"v_', open(os.path.join(Bd.CSRC, f)).read())]
+    assert with_blocks == [Bd.WAITS_SRC]
+    code = Bd._assembly(Bd.WAITS_SRC)
+    seen, bad = Bd._wait_states_report(code)
+    assert code.count("v_permlane16_swap_b32") >= 64 and seen > 1000 and bad == []
+
+
 def test_bench_read_ceiling_is_measured_as_the_rates_it_is_compared_with():
     """The read probe's rate goes through the protocol of the other figures (a settle phase first) and is the best of several: one
     measurement that falls into the clock's transient after idle must not become the ceiling."""
