@@ -485,7 +485,7 @@ __device__ __forceinline__ void chol_tile(CholTile& lds, const SgOperand P, cons
         }
         __syncthreads();
     }
-    // (scaled by one operand after the other: see dbf_split_gemm.h)
+    // (P's scale first, unlike sg_scaled in dbf_split_gemm.h: P is R, whose entries are below the root of one of G's, 2^64)
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll

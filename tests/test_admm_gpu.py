@@ -384,6 +384,40 @@ def test_admm_contraction_with_operands_of_many_magnitudes(q, r):
     assert np.all(err <= gate)
 
 
+@pytest.mark.parametrize("q,r", [(130, 70), (300, 200), (2048, 2048), (2304, 2304)])
+@pytest.mark.parametrize("exponent", [110, 96, -96])
+def test_admm_contraction_between_a_large_and_a_small_operand(q, r, exponent):
+    """Minv = 2^e D M D and C = 2^-e C0 / D, D from 2^-14 to 2^14 and the same for 128 rows: the products are of ordinary size, though entries of
+    Minv reach 2^124 (or fall to 2^-124, those of C reaching 2^110): no sum may leave the range on its way through the two operands' scales.  D does not vary inside
+    a chunk, so that all terms are met to 2^-22 or better, as in the test above; its gate.  (Sizes: every shape of blocks.)"""
+    rng = np.random.default_rng(I.seed_for(6, 930 + q + exponent))
+    steps = rng.integers(-14, 15, (q + 127) // 128)
+    steps[0] = 14 if exponent > 0 else -14
+    D = np.exp2(np.repeat(steps - (14 if exponent > 96 else 0), 128)[:q].astype(np.float64))
+    M = rng.uniform(0.2, 1.0, (q, q)) * np.where(rng.random((q, q)) < 0.5, -1.0, 1.0)
+    Minv = ((M + M.T) * D[:, None] * D[None, :] * 2.0 ** exponent).astype(np.float32)
+    small = 2.0 ** -exponent / D[:, None]
+    C = (rng.standard_normal((q, r)) * small).astype(np.float32)
+    S = np.where(rng.random((q, r)) < 0.5, 1, -1).astype(np.int8)
+    a = (0.3 * 2.0 ** -(exponent // 2) / D).astype(np.float32)
+    m = (rng.uniform(0.5, 1.5, r) * 2.0 ** -(exponent - exponent // 2)).astype(np.float32)
+    U = (0.1 * rng.standard_normal((q, r)) * np.minimum(small, 1.0)).astype(np.float32)   # (Z has it too, and is of ordinary size)
+    assert np.all(np.isfinite(Minv)) and np.all(np.isfinite(C)) and np.max(np.abs(Minv if exponent > 0 else C)) > 2.0 ** 106
+    dev = DeviceState(Minv, C, S, a, m, U)
+    dev.step(1.0, 2)
+    S1, a1, m1, U1 = dev.host()
+    am = np.abs(a.astype(np.float64)[:, None] * m)
+    R = C.astype(np.float64) + a.astype(np.float64)[:, None] * S * m - U
+    Z = Minv.astype(np.float64) @ R + U
+    terms = np.abs(Minv.astype(np.float64)) @ (np.abs(C).astype(np.float64) + am + np.abs(U)) + np.abs(U)
+    got = U1 + a1[:, None] * S1 * m1[None, :]
+    gate = 2.0 ** -19 * terms + 2.0 ** -22 * np.abs(a1[:, None] * m1[None, :])
+    with np.errstate(invalid="ignore"):
+        err = np.abs(got - Z)
+    G.say("  large and small q=%d r=%d 2^%d: largest error %.2g of the gate" % (q, r, exponent, np.max(err / gate)))
+    assert np.all(np.isfinite(got)) and np.all(err <= gate)
+
+
 @pytest.mark.parametrize("q", [40, 200])
 def test_admm_prepare_with_subnormal_pivots(q):
     """Pivots below 2^-126, where the reciprocal and root instructions take none: G = B^T B + rho I with rho = 9e-39 and B^T B a
