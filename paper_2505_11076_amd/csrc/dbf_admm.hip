@@ -201,8 +201,8 @@ __device__ __forceinline__ void chol_pivots(float (&x)[32], float& piv, std::int
     (chol_pivot<C>(x, piv), ...);
 }
 
-// The same for any pivots, in LDS and at leisure: pivots down to subnormal numbers (the instructions take none: a scaled copy), rows of pivots that are not
-// positive set to zero.  Returns whether there was one of the latter.
+// The same for any pivots, in LDS and at leisure, with roots alone: pivots down to subnormal numbers (the instructions take none: a scaled copy) and up
+// to the largest, rows of pivots that are not positive set to zero.  Returns whether there was one of the latter.
 __device__ __forceinline__ int chol_factor32_any(float* H, float* T, int lane) {
     const int l32 = lane & 31;
     volatile float* X = lane < 32 ? H + l32 : T + l32;   // column l of the block or of the identity
@@ -259,7 +259,8 @@ __device__ __forceinline__ int chol_factor32(float* H, float* T, int lane) {
 #pragma unroll
     for (int r = 0; r < 32; ++r) x[r] = right ? (r == l32 ? 1.f : 0.f) : x[r];
     chol_pivots(x, piv, std::make_integer_sequence<int, 32>());
-    if (__any(__builtin_bit_cast(unsigned, piv) - 0x00800000u >= 0x7f000000u)) return chol_factor32_any(H, T, lane);   // (not a positive normal number)
+    // (below 2^-126, whose reciprocal and root the instructions do not take, 2^126 and more, whose reciprocal they do not return, or not positive)
+    if (__any(__builtin_bit_cast(unsigned, piv) - 0x00800000u >= 0x7e000000u)) return chol_factor32_any(H, T, lane);
     float y = __builtin_amdgcn_rsqf(piv);
     y = fmaf(0.5f * y, fmaf(-piv * y, y, 1.f), y);
 #pragma unroll

@@ -443,3 +443,30 @@ def test_admm_prepare_with_subnormal_pivots(q):
     err = np.max(np.abs(got - want)) / np.max(np.abs(want))
     G.say("  subnormal pivots q=%d: Minv err %.2e of max" % (q, err))
     assert np.all(np.isfinite(got)) and err <= 2e-5
+
+
+@pytest.mark.parametrize("q", [40, 200])
+def test_admm_prepare_with_pivots_at_the_top_of_the_range(q):
+    """Diagonal entries of G = B^T B + rho I from 6e37 to 1.6e38, on both sides of 2^126 = 8.5e37, above which the reciprocal of a pivot is subnormal and
+    the instruction returns zero.  Against 64 bits; Minv is near the bottom of the range (1e-38), whose spacing 2^-149 is 1.4e-7 of it."""
+    p, r, rho = 64, 16, np.float32(6e37)
+    rng = np.random.default_rng(I.seed_for(6, 955 + q))
+    S = np.where(rng.random((q, p)) < 0.5, -1.0, 1.0)
+    m2 = (1.25e18 * rng.uniform(0.1, 1.0, q)).astype(np.float32)
+    b, W = np.ones(p, dtype=np.float32), rng.standard_normal((p, r)).astype(np.float32)
+    bits = torch.from_numpy(B.dbf_tile_host(q, p, O.pack_signs(S)).copy()).cuda()
+    dev = [torch.from_numpy(x.copy()).cuda() for x in (m2, b, W)]
+    Minv, Cm = torch.empty((q, q), device="cuda"), torch.empty((q, r), device="cuda")
+    flag = torch.full((1,), 77, dtype=torch.int32, device="cuda")
+    wsb = B.dbf_admm_prepare_workspace_bytes(p, q, r)
+    ws = torch.full((wsb,), 0xA5, dtype=torch.uint8, device="cuda")
+    B.dbf_admm_prepare(bits.data_ptr(), dev[0].data_ptr(), dev[1].data_ptr(), dev[2].data_ptr(), p, q, r, float(rho), Minv.data_ptr(),
+                       Cm.data_ptr(), ws.data_ptr(), wsb, flag.data_ptr(), G.stream_handle())
+    torch.cuda.synchronize()
+    assert int(flag.item()) == 0
+    Bt = m2.astype(np.float64)[:, None] * S
+    want = np.linalg.inv((Bt @ Bt.T + float(rho) * np.eye(q)) * 1e-38) * 1e-38
+    got = Minv.cpu().numpy().astype(np.float64)
+    err = np.max(np.abs(got - want)) / np.max(np.abs(want))
+    G.say("  pivots up to 1.6e38 q=%d: Minv err %.2e of max" % (q, err))
+    assert np.all(np.isfinite(got)) and err <= 2e-5
