@@ -92,23 +92,35 @@ __global__ __launch_bounds__(256) void dbf_admm_operands_kernel(const float* __r
                                                                const uint8_t* __restrict__ bits, int q, int r, int n_ct,
                                                                uint8_t* __restrict__ planes) {
     if ((int)blockIdx.y < q_blocks) {
-        sg_split_dense(Minv, q, q, q, nullptr, Minv_planes, blockIdx.y);
+        sg_split_dense<true>(Minv, q, q, q, nullptr, Minv_planes, blockIdx.y);
         return;
     }
     const SgSite s = sg_site(q, 2, blockIdx.y - q_blocks);
     const int j = min(s.i, r - 1);
     const float mj = m[j];
-    float x[2][8];
+    float x[2][8], u[2][8], ak[2][8];
+    unsigned sign[2][8];
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
-        const int bit = (s.k0[n] & 127) >> 4;   // (a chunk is a row tile)
-        const uint8_t* sb = bits + ((size_t)blockIdx.x * n_ct + (j >> 6)) * DBF_TILE_BYTES + 256 * ((j >> 4) & 3) + 16 * (s.k0[n] & 15) + (j & 15);
+        const uint8_t* sb = bits + ((size_t)blockIdx.x * n_ct + (j >> 6)) * DBF_TILE_BYTES + 256 * ((j >> 4) & 3) + 16 * (s.k0[n] & 15) + (j & 15);   // (a chunk is a row tile)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int k = min(s.k0[n] + e, q - 1);   // (clamped, not branched around: the loads of all sixteen rows in flight)
+            const int k = min(s.k0[n] + e, q - 1);
             const size_t at = (size_t)k * r + j;
-            const float am = a[k] * mj;
-            const float v = C[at] + rho * (((sb[16 * e] >> bit) & 1 ? am : -am) - U[at]);
+            x[n][e] = C[at];
+            u[n][e] = U[at];
+            ak[n][e] = a[k];
+            sign[n][e] = sb[16 * e];
+        }
+    }
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const int bit = (s.k0[n] & 127) >> 4;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            asm("" : "+v"(x[n][e]), "+v"(u[n][e]), "+v"(ak[n][e]), "+v"(sign[n][e]));   // (as in sg_split_dense: the loads of all sixteen rows in flight)
+            const float am = ak[n][e] * mj;
+            const float v = x[n][e] + rho * (((sign[n][e] >> bit) & 1 ? am : -am) - u[n][e]);
             x[n][e] = (s.k0[n] + e < q && s.i < r) ? v : 0.f;
         }
     }
@@ -417,7 +429,7 @@ __global__ __launch_bounds__(256) void dbf_chol_panel_kernel(const float* __rest
             x[4 + e] = h ? hi : got;
         }
         const int kb = j0 / 16 + 2 * w + t;
-        sg_store2(planes + (((size_t)(c0 / NB) * n_kb + kb) * 8 + ((c0 >> 5) & 3)) * SG_FRAG + lane * 16, x, scale.down);
+        sg_store2(planes + (((size_t)(c0 / NB) * n_kb + kb) * 8 + ((c0 >> 5) & 3)) * SG_FRAG + lane * 16, x, scale);
     }
 }
 

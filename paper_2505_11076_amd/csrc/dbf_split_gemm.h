@@ -2,9 +2,10 @@
 //
 // An fp32 value is taken as (h + l / 2048) 2^e: h the fp16 value nearest to x 2^-e, l the fp16 value nearest to 2048 times the rest.  e belongs
 // to an output line of an operand and a chunk of 128 summation indices: it puts the largest magnitude of those 128 values into
-// [2^14, 2^15).  h and l have 22 significant bits and a sign between them: x is met to 2^-23 of itself, 2^-24.5 on average, and values below 2^-28 of
-// the chunk's largest to 2^-51 of that one.  A product of two such values is taken as h h + (h l + l h) / 2048, the two in sums of their own;
-// l l, left out, is at most 2^-22 of the product (2^-24.5 on average), of either sign.  Products of two fp16 are exact in the matrix cores, the
+// [2^14, 2^15).  (Minv has a factor in place of 2^e that makes it 2^15: sg_scale_largest.)  h and l have 22 significant bits and a sign between them: x is met
+// to 2^-23 of itself, 2^-24.5 on average, down to 2^-27 of the chunk's largest, and smaller values to 2^-50 of that one.  A product of two such values is taken as
+// h h + (h l + l h) / 2048, the two in sums of their own; l l, left out, is at most 2^-22 of the product (2^-24.5 on average), of either sign, but never
+// negative where a line meets itself (the diagonal of Y^T Y).  Products of two fp16 are exact in the matrix cores, the
 // sums of a chunk are kept in fp32, 16 products entering a sum at once, and are scaled and added to the total chunk by chunk.
 // An operand that is a matrix of signs is one fp16 plane of +-1, and two products suffice.
 //
@@ -55,14 +56,29 @@ __device__ __forceinline__ SgScale sg_scale(float mx) {
     return s;
 }
 
-// The two pieces of eight values to a fragment of piece 0 (`at`) and of piece 1.
-__device__ __forceinline__ void sg_store2(uint8_t* at, const float (&x)[8], float down) {
+// The same, but no power of two: up = mx / 2^15, so that the largest value is met exactly, h = 2^15 and l = 0 (a power of two where that would be below
+// 2^-115, which is enough for subnormal numbers).  For Minv, whose diagonal outweighs the rest of a line: an error of that entry would be common to a
+// whole row of the result, and the row's factor keeps all of it (deviation of the factor from 64 bits, over sizes: 7.0e-8 with a power of two, 5.4e-8 so;
+// three bf16 parts left 5.5e-8).
+__device__ __forceinline__ SgScale sg_scale_largest(float mx) {
+    SgScale s;
+    s.up = fmaxf(mx * 0x1p-15f, 0x1p-115f);
+    s.down = __builtin_amdgcn_rcpf(s.up);   // (need not be exact)
+    return s;
+}
+
+// The two pieces of eight values to a fragment of piece 0 (`at`) and of piece 1.  (LARGEST: a scale that is no power of two; the rest is taken
+// before it is scaled, so that only the rounding of l remains.)
+template <bool LARGEST = false>
+__device__ __forceinline__ void sg_store2(uint8_t* at, const float (&x)[8], const SgScale& c) {
     v8h h, l;
+    const float low = c.down * SG_LOW;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const float v = x[e] * down;
+        float v = x[e] * c.down;
+        if (LARGEST) asm("" : "+v"(v));   // (one value: the compiler rounds the product for h and for its use below by different instructions, once and twice)
         h[e] = (_Float16)v;
-        l[e] = (_Float16)((v - (float)h[e]) * SG_LOW);
+        l[e] = (_Float16)(LARGEST ? fmaf(-(float)h[e], c.up, x[e]) * low : (v - (float)h[e]) * SG_LOW);
     }
     *reinterpret_cast<v8h*>(at) = h;
     *reinterpret_cast<v8h*>(at + 4 * SG_FRAG) = l;
@@ -88,6 +104,7 @@ __device__ inline SgSite sg_site(int K, int pieces, int ib) {
 inline dim3 sg_plane_grid(int K, int M) { return dim3((K + SG_CHUNK - 1) / SG_CHUNK, sg_lines(M) / 32); }
 
 // Scales the values of a workgroup's chunk and lines and stores their pieces and scales.  x: zero where k or i is out of range.
+template <bool LARGEST = false>
 __device__ __forceinline__ void sg_split_chunk(uint8_t* planes, int K, int M, const SgSite& s, const float (&x)[2][8]) {
     __shared__ float part[4][32];
     const int lane = threadIdx.x & 63, l32 = lane & 31, w = threadIdx.x >> 6;
@@ -100,15 +117,16 @@ __device__ __forceinline__ void sg_split_chunk(uint8_t* planes, int K, int M, co
     if (lane < 32) part[w][lane] = mx;
     __syncthreads();
     mx = fmaxf(fmaxf(part[0][l32], part[1][l32]), fmaxf(part[2][l32], part[3][l32]));
-    const SgScale c = sg_scale(mx);
+    const SgScale c = LARGEST ? sg_scale_largest(mx) : sg_scale(mx);
 #pragma unroll
     for (int n = 0; n < 2; ++n)
-        sg_store2(planes + s.off[n], x[n], c.down);
+        sg_store2<LARGEST>(planes + s.off[n], x[n], c);
     if (threadIdx.x < 32) reinterpret_cast<float*>(planes + sg_scales_at(2, K, M))[(size_t)blockIdx.x * sg_lines(M) + s.i] = c.up;
 }
 
 // Planes of a dense k-major matrix src [K][ld >= M], its rows scaled by kscale (or NULL).  A wavefront's load of one k is two
 // runs of 128 bytes.  Bound by memory: 4 bytes read and 4 written per element.
+template <bool LARGEST = false>
 __device__ __forceinline__ void sg_split_dense(const float* __restrict__ src, size_t ld, int K, int M, const float* __restrict__ kscale,
                                                uint8_t* __restrict__ planes, int ib) {
     const SgSite s = sg_site(K, 2, ib);
@@ -118,10 +136,16 @@ __device__ __forceinline__ void sg_split_dense(const float* __restrict__ src, si
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const int k = min(s.k0[n] + e, K - 1), i = min(s.i, M - 1);   // (clamped, not branched around: sixteen loads in flight)
-            const float v = src[(size_t)k * ld + i] * (kscale ? kscale[k] : 1.f);
-            x[n][e] = (s.k0[n] + e < K && s.i < M) ? v : 0.f;
+            x[n][e] = src[(size_t)k * ld + i] * (kscale ? kscale[k] : 1.f);
         }
-    sg_split_chunk(planes, K, M, s, x);
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            asm("" : "+v"(x[n][e]));   // (or the compiler puts each load behind a branch and waits for it)
+            x[n][e] = (s.k0[n] + e < K && s.i < M) ? x[n][e] : 0.f;
+        }
+    sg_split_chunk<LARGEST>(planes, K, M, s, x);
 }
 
 __global__ __launch_bounds__(256) void dbf_split_dense_kernel(const float* __restrict__ src, size_t ld, int K, int M,

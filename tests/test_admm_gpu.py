@@ -470,3 +470,25 @@ def test_admm_prepare_with_pivots_at_the_top_of_the_range(q):
     err = np.max(np.abs(got - want)) / np.max(np.abs(want))
     G.say("  pivots up to 1.6e38 q=%d: Minv err %.2e of max" % (q, err))
     assert np.all(np.isfinite(got)) and err <= 2e-5
+
+
+@pytest.mark.parametrize("q,r", [(40, 4096), (300, 4096), (2048, 4096)])
+def test_admm_contraction_meets_the_largest_entry_of_a_line_exactly(q, r):
+    """Minv = D, of 24 significant bits (and, at the larger sizes, a hundredth of its size beside it).  An error of an entry of the diagonal is common to
+    its row of Z, and the row's factor keeps all of it; those of R and of the sums differ from column to column: at most 2^-22 of an entry each, so that their
+    mean over r = 4096 columns has a deviation of at most 2^-22 / sqrt(3 r) = 2^-28.8.  Gate: six of these.  (An entry with two bits less: 2^-24.5.)"""
+    rng = np.random.default_rng(I.seed_for(6, 990 + q))
+    Minv = np.diag(rng.uniform(0.3, 0.7, q))
+    if q > 40:
+        M = 0.002 / np.sqrt(q) * rng.standard_normal((q, q))
+        Minv += M + M.T
+    Minv = Minv.astype(np.float32)
+    C = (np.where(rng.random((q, r)) < 0.5, 1, -1) * rng.uniform(0.5, 1.5, (q, r))).astype(np.float32)
+    S = np.where(rng.random((q, r)) < 0.5, 1, -1).astype(np.int8)
+    dev = DeviceState(Minv, C, S, np.zeros(q, np.float32), np.ones(r, np.float32), np.zeros((q, r), np.float32))
+    dev.step(1.0, 1)
+    S1, a1, m1, U1 = dev.host()
+    Z = Minv.astype(np.float64) @ C.astype(np.float64)
+    err = np.sum((U1 + a1[:, None] * S1 * m1[None, :] - Z) * np.sign(Z), axis=1) / np.sum(np.abs(Z), axis=1)
+    G.say("  rows of Z q=%d r=%d: common error 2^%.2f at most, 2^%.2f on average" % (q, r, np.log2(np.max(np.abs(err))), np.log2(np.mean(np.abs(err)))))
+    assert np.max(np.abs(err)) <= 6 * 2.0 ** -22 / np.sqrt(3 * r)
