@@ -447,17 +447,22 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
 // the chunks are shared by two halves of a workgroup of 512; and the blocks are 64 x 128 where those of 128 x 128 would leave half of
 // the compute units idle.  us, 64 x 128 with 512 threads / 128 x 128 with 512 / with 256 (K = M):  512 x 768 outputs (24 blocks) 12.2 / 17.9 / 19.2,
 // 1024 x 2048 (128) 20.2 / 27.5 / 30.1, 1536 x 1536 (144) 44.7 / 36.2 / 40.7, 2048 x 2048 (256) 62.1 / 55.2 / 57.8, 1792 x 2560 (280) 77.6 / 84.1 / 67.6,
-// 2415 x 2816 (418) 137 / 115 / 102.  Sums of unequal lengths (ktri) in 64 x 128 with 256 threads, so that short ones end early: the upper 136 blocks of
-// Y^T Y, q = 2048, 35 us, in 128 x 128 with 512 threads 45 (B^T B, of equal lengths: 69 and 64).
+// 2415 x 2816 (418) 137 / 115 / 102.
+// Sums of unequal lengths (ktri) go best in 64 x 128 at every size: short ones end early.  With 512 threads until the blocks keep the chip busy by
+// themselves.  us, the constants (p = r = 768), 64 x 128 with 512 threads / with 256 / 128 x 128 with 512 / with 256: q = 1536 (78 blocks) 417 / 424 / 432 / 440,
+// 2048 (136) 557 / 562 / 570 / 582, 2560 (210) 703 / 711 / 718 / 732, 2944 (276) 811 / 816 / 826 / 842, 3328 (351) 940 / 939 / 949 / 969,
+// 3712 (435) 1063 / 1054 / 1062 / 1085, 4096 (528) 1166 / 1149 / 1155 / 1180.
+// (Blocks of the upper triangle go to the compute dies as they come, column by column, not in bands as the full grid's: for B^T B, q = 2048, p = 4096,
+// 29 % of the reads hit L2, where the banded launches have 79 to 84 %.  A banded order of the triangle has not been measured.)
 template <int PA>
 inline void launch_split_gemm(const SplitGemmArgs& g, hipStream_t st) {
     const int mt = (g.M + 127) / 128, nt = (g.N + 127) / 128;
     const long long blocks = g.upper ? (long long)mt * (mt + 1) / 2 : (long long)mt * nt;
     auto grid = [&](int bi) { return g.upper ? dim3((unsigned)(blocks * (2 / bi))) : dim3(bi == 2 ? mt : (g.M + 63) / 64, nt); };
-    if (blocks <= 128)
+    if (blocks <= 128 || (g.ktri && blocks <= 320))
         hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 1, 2>), grid(1), dim3(512), 0, st, g);
-    else if (g.ktri && blocks <= 256)
-        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 1, 1>), grid(1), dim3(256), 0, st, g);
+    else if (PA == 2 && g.ktri)   // (Y^T Y alone)
+        hipLaunchKernelGGL((dbf_split_gemm_kernel<2, 1, 1>), grid(1), dim3(256), 0, st, g);
     else if (blocks <= 256)
         hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 2, 2>), grid(2), dim3(512), 0, st, g);
     else
