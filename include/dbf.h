@@ -259,8 +259,8 @@ int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void
  *          two operands of the contraction as two fp16 planes each -- 4 bytes per entry of a q x q and a q x r
  *          matrix, rounded up to 128 each way, and their scales -- and the SVID workspace).
  * The contraction has fp32 accuracy: its operands are split into two fp16 parts relative to the largest of 128 entries along the
- * summation.  That entry of Minv is met exactly, any other to 2^-23 of itself down to 2^-27 of it, and to 2^-50 of it below.  No entry is too
- * large or too small (results that fp32 holds are not lost on the way).
+ * summation.  That entry of Minv is met exactly, any other to 2^-23 of itself down to 2^-27 of it, and to 2^-50 of it below.  No sum
+ * leaves fp32's range on the way unless its result does.
  * Asynchronous on hip_stream, allocates nothing; results do not depend on scheduling.  NaNs unsupported.
  * Errors: DBF_EINVAL (null or misaligned pointers, sizes out of range, rho <= 0 or not finite,
  * svid_iters < 1), DBF_EWORKSPACE, DBF_EHIP. */

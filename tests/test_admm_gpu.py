@@ -361,8 +361,8 @@ def test_sign_tiles_may_start_at_any_multiple_of_four_bytes(p, q, r):
 @pytest.mark.parametrize("q,r", [(130, 70), (300, 200), (513, 129)])
 def test_admm_contraction_with_operands_of_many_magnitudes(q, r):
     """Minv = D M D and C = C0 / D with D from 2^-12 to 2^12: along a line of either operand entries differ by 2^24 and more, while all terms of
-    a sum count alike.  The operands are split relative to the largest of 128 entries of a line, exactly to 2^-23 down to 2^-28 of it, so that a sum is met
-    to a few 2^-22 of the sum of its terms' magnitudes; 2^-19 leaves room for the fp32 additions (as many roundings as 16-term steps)."""
+    a sum count alike.  The operands are split relative to the largest of 128 entries of a line, exactly to 2^-23 down to 2^-27 of it, and the product of two rests,
+    2^-22, is left out: at worst 2^-21 of the sum of the terms' magnitudes.  As much again is for R's own roundings and the fp32 additions."""
     rng = np.random.default_rng(I.seed_for(6, 970 + q))
     D = np.exp2(rng.uniform(-12, 12, q))
     M = rng.uniform(0.2, 1.0, (q, q)) * np.where(rng.random((q, q)) < 0.5, -1.0, 1.0)
@@ -379,8 +379,43 @@ def test_admm_contraction_with_operands_of_many_magnitudes(q, r):
     terms = np.abs(Minv.astype(np.float64)) @ (np.abs(C).astype(np.float64) + np.abs(a.astype(np.float64)[:, None] * m) + np.abs(U)) + np.abs(U)
     got = U1 + a1[:, None] * S1 * m1[None, :]
     err = np.abs(got - Z)
-    gate = 2.0 ** -19 * terms + 2.0 ** -22 * np.abs(a1[:, None] * m1[None, :])
+    gate = 2.0 ** -20 * terms + 2.0 ** -23 * np.abs(a1[:, None] * m1[None, :])   # (the latter: U' = Z - a' S' m' on the device)
     G.say("  magnitudes q=%d r=%d: largest error %.2g of the gate" % (q, r, np.max(err / gate)))
+    assert np.all(err <= gate)
+
+
+@pytest.mark.parametrize("below", [20, 27, 32, 40])
+@pytest.mark.parametrize("outlier_in", ["Minv", "C"])
+def test_admm_contraction_of_entries_far_below_the_largest_of_their_chunk(outlier_in, below):
+    """One entry of a chunk of a line is 1.5 and meets a zero of the other operand, the one that counts is 2^-below of it: met to 2^-50 of the
+    largest (dbf.h), which is more than its own 2^-23 from 2^-27 on.  Z has one term an entry, so that nothing else is in it but the split
+    (2^-21 of the term at worst) and the roundings of Z, U and this test's sum."""
+    q, r = 256, 200
+    rng = np.random.default_rng(I.seed_for(6, 975 + below))
+    v, C = rng.uniform(0.5, 1.0, q), rng.uniform(0.5, 1.0, (q, r)) * np.where(rng.random((q, r)) < 0.5, -1, 1)
+    heads = np.arange(0, q, 128)                  # the summation index of a chunk that has the large entry
+    if outlier_in == "Minv":
+        Minv = np.diag(v * 2.0 ** -below)
+        for i in range(q):
+            Minv[heads[i // 128], i] = Minv[i, heads[i // 128]] = 1.5
+        C[heads] = 0
+    else:
+        Minv = np.diag(v)
+        C *= 2.0 ** -below
+        C[heads] = 1.5
+    Minv, C = Minv.astype(np.float32), C.astype(np.float32)
+    S = np.where(rng.random((q, r)) < 0.5, 1, -1).astype(np.int8)
+    dev = DeviceState(Minv, C, S, np.zeros(q, np.float32), np.ones(r, np.float32), np.zeros((q, r), np.float32))
+    dev.step(1.0, 1)
+    S1, a1, m1, U1 = dev.host()
+    rest = np.setdiff1d(np.arange(q), heads)
+    Z = (Minv.astype(np.float64) @ C.astype(np.float64))[rest]
+    A1 = (a1[:, None] * S1 * m1[None, :])[rest]
+    floor = 2.0 ** -50 * 1.5 * (np.abs(C[rest]) if outlier_in == "Minv" else v[rest, None])
+    gate = floor + 2.0 ** -21 * np.abs(Z) + 2.0 ** -23 * (np.abs(Z) + np.abs(A1))
+    err = np.abs(U1[rest] + A1 - Z)
+    G.say("  outlier in %s, 2^-%d below: largest error %.2g of the gate, 2^%.1f of the entry" % (outlier_in, below, np.max(err / gate),
+                                                                                                 np.log2(np.max(err / np.abs(Z)))))
     assert np.all(err <= gate)
 
 
@@ -411,7 +446,7 @@ def test_admm_contraction_between_a_large_and_a_small_operand(q, r, exponent):
     Z = Minv.astype(np.float64) @ R + U
     terms = np.abs(Minv.astype(np.float64)) @ (np.abs(C).astype(np.float64) + am + np.abs(U)) + np.abs(U)
     got = U1 + a1[:, None] * S1 * m1[None, :]
-    gate = 2.0 ** -19 * terms + 2.0 ** -22 * np.abs(a1[:, None] * m1[None, :])
+    gate = 2.0 ** -20 * terms + 2.0 ** -23 * np.abs(a1[:, None] * m1[None, :])   # (the latter: U' = Z - a' S' m' on the device)
     with np.errstate(invalid="ignore"):
         err = np.abs(got - Z)
     G.say("  large and small q=%d r=%d 2^%d: largest error %.2g of the gate" % (q, r, exponent, np.max(err / gate)))
