@@ -12,8 +12,8 @@
 //
 // The contraction is q x q x r in fp32 accuracy (34 GFLOP at q = 2048, r = 4096) and dominates; the elementwise
 // kernels and the projection are bandwidth bound.  Measured at that size: the contraction 331 us on the fp32 matrix cores, 219 on the bf16
-// ones with operands in three parts, 106 on the fp16 ones with operands in two, whose planes, with the making of R, take 18 us in one launch (22 in two); the update
-// with two rounds of SVID 388, 288, now 182 us; error against 64 bits 8.1e-6, 5.1e-6, 1.8e-6 (fewer roundings: 16 products enter the accumulator at
+// ones with operands in three parts, 108 on the fp16 ones with operands in two, whose planes, with the making of R, take 22 us in one launch; the update
+// with two rounds of SVID 388, 287, now 184 us; error against 64 bits 8.1e-6, 5.1e-6, 1.6e-6 (fewer roundings: 16 products enter the accumulator at
 // once, and half as many of them).
 // The paper gives no kernel design for this step.
 #include "dbf_kernels.h"
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void dbf_admm_operands_kernel(const float* __r
 // contraction read (R's for c > jb, Y's for c <= jb) and nowhere else.
 // What bounds it: the chain.  Per block row 2 launches and 4 x 32 pivots; the update's products take 3 us of it.  Measured at
 // q = 2048 (16 block rows): panel 5.6 us, update 31.6 us of which the pivots 25 while every entry of a pivot row went through a scalar register and
-// the pivot's root stood in the chain; now 6.1 and 23.7.  With p = r = 4096 the constants took 890 us so, now 740.
+// the pivot's root stood in the chain; now 6.2 and 23.8.  With p = r = 4096 the constants took 890 us so, now 736.
 // ---------------------------------------------------------------------------------------------
 constexpr int NB = 128;        // block size: the contraction's tile
 constexpr int CH_LD = NB + 4;  // LDS row length of a diagonal block: rows start on 16 bytes
@@ -258,7 +258,7 @@ __device__ __forceinline__ int chol_factor32_any(float* H, float* T, int lane) {
 // the block, lane 32 + l column l of the identity.  A pivot row's entries reach the other rows through lane broadcasts that are part
 // of the multiplication; the rows are scaled by 1 / sqrt(pivot) at the end, all roots at once.  What bounds it: a wavefront on its own issues one
 // instruction in four cycles, here 12 and one per row below for a pivot.  (With every entry through a scalar register, two
-// instructions a row, and the root in the chain from pivot to pivot 8300 cycles, so 4400.)  Returns whether a pivot was not positive.
+// instructions a row, and the root in the chain from pivot to pivot 8300 cycles; so 4400 with 11 instructions a pivot.)  Returns whether a pivot was not positive.
 __device__ __forceinline__ int chol_factor32(float* H, float* T, int lane) {
     const int l32 = lane & 31;
     const bool right = lane >= 32;

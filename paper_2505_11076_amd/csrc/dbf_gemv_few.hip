@@ -773,6 +773,9 @@ hipError_t dbf_launch_few(const DbfPlan& p, bool stage_a, const void* x, void* y
         hipLaunchKernelGGL(kernel, grid, dim3(FEW_THREADS), lds, stream, first, t, io, p.d_few_acc, in_off, row_off, s.cols,
                            list ? n_items : s.rows, tokens, cut);
     };
+    // (In steps of two: values held beyond the row's cost requests and rounding of nothing.  us per call with as many as a row needs / 2 / 4 / 12 more: 8192 x 8192,
+    // k = 4096, batch 8 12.80 / 13.25 / 13.78 / 15.00; 11008 -> 4096, k = 4477, batch 1 10.36 / 10.96 / 11.40 / 12.92; 4096 -> 11008, batch 8 11.96 / 12.42 / 13.08 / 14.01;
+    // 2048 x 2048, batch 8 9.9 / 10.1 / 10.1 / 10.6.  Up to twelve in all.)
     auto launch_planes = [&](auto planes) {
         if (held <= 2) launch(std::integral_constant<int, 2>{}, planes);
         else if (held <= 4) launch(std::integral_constant<int, 4>{}, planes);

@@ -107,8 +107,8 @@ def test_admm_step_matches_the_oracle(shape, rho, iters):
 @pytest.mark.parametrize("q,r", [(1, 1), (15, 33), (16, 31), (17, 64), (127, 128), (128, 129), (129, 127), (257, 96)])
 def test_admm_step_at_the_edges_of_the_contraction_tiles(q, r):
     """The contraction works on fragments of 16 summation indices by 32 outputs and tiles of 128 x 128: one less, equal
-    and one more in each.  The gates are those above (what the split operands leave out, at most about 2^-24 of a
-    product, is of the size of fp32's own rounding)."""
+    and one more in each.  The gates are those above (what the split operands leave out, at most 2^-21 of a
+    product and a quarter of that on average, is a few times fp32's own rounding)."""
     p, rho = 2 * q + 40, 0.7
     Bm, W, S, a, m, U = I.make_admm_problem(p, q, r, I.seed_for(9, 300 + q + r))
     Minv, C = _constants(Bm, W, rho)
