@@ -130,432 +130,616 @@ __global__ __launch_bounds__(256) void dbf_admm_operands_kernel(const float* __r
 // ---------------------------------------------------------------------------------------------
 // Inverse of the symmetric positive definite G = B^T B + rho I by a blocked Cholesky factorisation G = R^T R (R upper
 // triangular), blocks of 128: forward elimination of the augmented matrix [G | I] gives [R | Y] with Y = R^-T, and
-// G^-1 = Y^T Y is one more contraction.  Block row jb in two launches:
-//   panel    [R | Y][jb, :] = R_jj^-T [G | Y][jb, :], all columns at once            dbf_chol_panel_kernel
-//   update   [G | Y][i, :] -= R[jb, i]^T [R | Y][jb, :] for the block rows i > jb    dbf_chol_update_kernel
-// and the workgroup of the update that makes diagonal block jb + 1 factors it and inverts its factor right there: that
-// chain of 128 pivots, the longest of the whole, runs beside the other blocks' updates.
-// G and Y share one q x q matrix: block (i, c) is G's for c >= i and Y's for c < i (an update starts it at zero at c = jb), and
-// row jb of R is dead after its own update.  A finished row is written as the fp16 planes that the update and the last
-// contraction read (R's for c > jb, Y's for c <= jb) and nowhere else.
-// What bounds it: the chain.  Per block row 2 launches and 4 x 32 pivots; the update's products take 3 us of it.  Measured at
-// q = 2048 (16 block rows): panel 5.6 us, update 31.6 us of which the pivots 25 while every entry of a pivot row went through a scalar register and
-// the pivot's root stood in the chain; now 6.2 and 23.8.  With p = r = 4096 the constants took 890 us so, now 736.
+// G^-1 = Y^T Y is one more contraction.  Block row j is one launch (dbf_chol_row_kernel), with T = R_jj^-T from the launch before:
+//   [R | Y][j, :] = T [G | Y][j, :]     [G | Y][i, :] -= R[j, i]^T [R | Y][j, :] for the block rows i > j
+// A workgroup has block (i, c) of the second and makes the two blocks of row j that it needs, R[j, i] and [R | Y][j, c], by itself: three
+// products for one, but no launch before it.  The workgroup of diagonal block j + 1 goes on to factor it and to invert its factor: that
+// chain of 128 pivots, the longest of the whole, runs beside the other blocks' products.
+// G and Y share one q x q matrix: block (i, c) is G's for c >= i and Y's for c < i (it starts at zero at j = c); row j is read
+// only.  A finished row of Y is written as the fp16 planes that the last contraction reads; R is kept nowhere.
+// What bounds it: the chain.  Per block row a launch of 22 us at q = 2048: 2 to the loads' arrival, 6 to the diagonal block, four times 2.5 for 32 pivots and
+// 0.4 for the next row's share of them, 0.7 for T.  (As two launches, a panel of 6 us and an update of 24 whose chain held an inverse's product behind each 32
+// pivots, the constants took 744 us with p = r = 4096; so 627.)  Blocks that fill the chip more than once make row j too often: from 256 blocks on
+// dbf_chol_panel_kernel makes it first (q = 3328 870 us without, 819 so; 4096 with p = r = 4096 1681, 1484).
 // ---------------------------------------------------------------------------------------------
 constexpr int NB = 128;        // block size: the contraction's tile
 constexpr int CH_LD = NB + 4;  // LDS row length of a diagonal block: rows start on 16 bytes
-constexpr int CH_LDT = 36;
-constexpr int CH_LDS = 4 * (NB * CH_LD + 32 * CH_LDT);
+constexpr int CH_THREADS = 512;
+constexpr int CH_MADE = 256;    // more blocks than this: row j first, in a launch of its own
+constexpr int CH_PLANES = 64 * SG_FRAG;   // the two pieces of a 128 x 128 operand: [k / 16][piece][line / 32]
+// T's planes leave fragments of k beyond a line empty: the first of these has its lines' scales.
+constexpr int CH_T_UP = (7 * 2 * 4) * SG_FRAG;
 
-// d -= P^T Q (or d = -P^T Q) for 32 x 32 blocks in LDS, 32 values of k: lane l supplies P[k][l % 32] and Q[k][l % 32], k = 2 kk + l / 32.
-// (What is there is read with the operands, but subtracted from at the end: starting the sums from it rounds it 32 times.)
-__device__ __forceinline__ void chol_update32(float* d, const float* P, const float* Q, bool fresh, int lane) {
-    const int l32 = lane & 31, h = lane >> 5;
-    float a[16], b[16];
-    v16f acc, old;
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-        a[kk] = P[(2 * kk + h) * CH_LD + l32];
-        b[kk] = Q[(2 * kk + h) * CH_LD + l32];
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) old[v] = d[(8 * (v >> 2) + 4 * h + (v & 3)) * CH_LD + l32];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kk], b[kk], acc, 0, 0, 0);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) d[(8 * (v >> 2) + 4 * h + (v & 3)) * CH_LD + l32] = (fresh ? 0.f : old[v]) - acc[v];
+struct CholPivot {
+    float v0, v1, t;   // lanes 0-15 of a pivot row in every 16 lanes, lanes 16-31 in every 16; the row over its pivot
+};
+// x -= (entry R of the pivot row) * t
+template <int R>
+__device__ __forceinline__ void chol_sub(float (&x)[32], const CholPivot& p) {
+    asm("v_fmac_f32_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(x[R]) : "v"(R < 16 ? p.v0 : p.v1), "v"(p.t), "n"(R & 15));
 }
-
-// The operand of 16 x 16 outputs for 32 values of k: lane l supplies P[k][l % 16], k = 16 (kk / 4) + 4 (l / 16) + kk % 4 (rows four apart start 16 banks
-// apart); register v of the result is row 4 (l / 16) + v, column l % 16.
-__device__ __forceinline__ void chol_load16(const float* P, int ld, int lane, float (&x)[8]) {
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) x[kk] = P[(16 * (kk >> 2) + 4 * (lane >> 4) + (kk & 3)) * ld + (lane & 15)];
+template <int FROM, int... R>
+__device__ __forceinline__ void chol_subs(float (&x)[32], const CholPivot& p, std::integer_sequence<int, R...>) {
+    (chol_sub<FROM + R>(x, p), ...);
 }
-
-// x -= (lane N of each 16 of v) * t.  (Written out: the compiler makes two instructions of it.)
-template <int N>
-__device__ __forceinline__ void chol_sub(float& x, float v, float t) {
-    asm("v_fmac_f32_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(x) : "v"(v), "v"(t), "n"(N));
-}
-template <int C, int... R>
-__device__ __forceinline__ void chol_rows(float (&x)[32], float v0, float v1, float t, std::integer_sequence<int, R...>) {
-    (chol_sub<(C + 1 + R) & 15>(x[C + 1 + R], C + 1 + R < 16 ? v0 : v1, t), ...);
-}
-// Pivot C, its value to lane C of piv: the rows below lose their multiples of row C.  t = x[C] / pivot (reciprocal and one Newton step), and lanes 0-15
-// of x[C] in every 16 lanes of v0, lanes 16-31 in every 16 of v1.  (One block, so that what the instructions want between a write and a
-// use is the work itself as far as it goes: one other before a lane read of a fresh register, two between the lane read and a use of its scalar
-// register, two before a lane swap of a fresh register and before a lane broadcast of one, one behind the reciprocal.  The
-// build checks the assembly for them: _wait_states_report in build.py.)
+// Pivot C, its value to lane C of piv: t = row C / pivot (reciprocal, product and one correction: met to its last bit or nearly so) and the row's entries for
+// the rows below.  Row C is up to date; `before`, the pivot before it, is still owed to the rows below, and the first six of them get it here, where the chain
+// from row C to row C + 1 would leave the wavefront waiting (eight cycles from a result to its use, four to issue an instruction).  (One block, so that what the
+// instructions want between a write and a use -- one other before a lane read of a fresh register, two between the lane read and a use of its scalar
+// register, two before a lane swap of a fresh register and before a lane broadcast of one, one behind the reciprocal -- is the work itself as
+// far as it goes.  The build checks the assembly for them: _wait_states_report in build.py.)
+#define CHOL_OWED(n) "v_fmac_f32_dpp %" #n ", -%" CHOL_FROM_##n ", %[bt] row_newbcast:%[n" #n "] row_mask:0xf bank_mask:0xf\n\t"
+#define CHOL_FROM_0 "[b0]"
+#define CHOL_FROM_1 "[b1]"
+#define CHOL_FROM_2 "[b2]"
+#define CHOL_FROM_3 "[b3]"
+#define CHOL_FROM_4 "[b4]"
+#define CHOL_FROM_5 "[b5]"
+#define CHOL_PIVOT(o0, o1, o2, o3, o4, o5)                                                                                                        \
+    asm(o0 o1 "v_mov_b32 %[v0], %[xc]\n\t"                                                                                                        \
+        "v_readlane_b32 %[p], %[xc], %[c]\n\t"                                                                                                    \
+        "v_mov_b32 %[v1], %[xc]\n\t" o2 "v_rcp_f32 %[r], %[p]\n\t"                                                                                \
+        "v_permlane32_swap_b32 %[v0], %[v1]\n\t" o3 "v_mul_f32 %[t0], %[xc], %[r]\n\t"                                                            \
+        "v_mov_b32 %[v1], %[v0]\n\t" o4 "v_fma_f32 %[t], -%[t0], %[p], %[xc]\n\t" o5 "v_permlane16_swap_b32 %[v0], %[v1]\n\t"                     \
+        "v_fma_f32 %[t], %[t], %[r], %[t0]\n\t"                                                                                                   \
+        "v_writelane_b32 %[piv], %[p], %[c]"                                                                                                      \
+        : "+v"(x[X(0)]), "+v"(x[X(1)]), "+v"(x[X(2)]), "+v"(x[X(3)]), "+v"(x[X(4)]), "+v"(x[X(5)]), [v0] "=&v"(now.v0), [v1] "=&v"(now.v1),       \
+          [t] "=&v"(now.t), [t0] "=&v"(t0), [r] "=&v"(r), [p] "=&s"(p), [piv] "+v"(piv)                                                           \
+        : [xc] "v"(x[C]), [bt] "v"(before.t), [b0] "v"(from(0)), [b1] "v"(from(1)), [b2] "v"(from(2)), [b3] "v"(from(3)), [b4] "v"(from(4)),      \
+          [b5] "v"(from(5)), [c] "n"(C), [n0] "n"(X(0) & 15), [n1] "n"(X(1) & 15), [n2] "n"(X(2) & 15), [n3] "n"(X(3) & 15), [n4] "n"(X(4) & 15), \
+          [n5] "n"(X(5) & 15))
 template <int C>
-__device__ __forceinline__ void chol_pivot(float (&x)[32], float& piv) {
-    float v0, v1, t, r, p;
-    asm("v_mov_b32 %0, %6\n\t"
-        "v_readlane_b32 %4, %6, %7\n\t"
-        "v_mov_b32 %1, %6\n\t"
-        "s_nop 0\n\t"
-        "v_rcp_f32 %3, %4\n\t"
-        "v_permlane32_swap_b32 %0, %1\n\t"
-        "v_mov_b32 %1, %0\n\t"
-        "v_fma_f32 %2, -%4, %3, 1.0\n\t"
-        "v_fma_f32 %3, %2, %3, %3\n\t"
-        "v_permlane16_swap_b32 %0, %1\n\t"
-        "v_mul_f32 %2, %6, %3\n\t"
-        "v_writelane_b32 %5, %4, %7"
-        : "=&v"(v0), "=&v"(v1), "=&v"(t), "=&v"(r), "=&s"(p), "+v"(piv)
-        : "v"(x[C]), "n"(C));
-    chol_rows<C>(x, v0, v1, t, std::make_integer_sequence<int, 31 - C>());
+__device__ __forceinline__ void chol_pivot(float (&x)[32], float& piv, CholPivot& before) {
+    CholPivot now;
+    float r, t0;
+    int p;
+    constexpr int LEFT = C > 0 ? 31 - C : 0;   // the rows that `before` is owed to
+    // (rows that do not exist: operands of a block that does not use them)
+    constexpr auto X = [](int n) { return n < LEFT ? C + 1 + n : (C + 26 + n) % 32; };
+    auto from = [&](int n) { return X(n) < 16 ? before.v0 : before.v1; };
+    if constexpr (C == 0) before.v0 = before.v1 = before.t = 0.f;
+    if constexpr (LEFT >= 6) CHOL_PIVOT(CHOL_OWED(0), CHOL_OWED(1), CHOL_OWED(2), CHOL_OWED(3), CHOL_OWED(4), CHOL_OWED(5));
+    else if constexpr (LEFT == 5) CHOL_PIVOT(CHOL_OWED(0), "", CHOL_OWED(1), CHOL_OWED(2), CHOL_OWED(3), CHOL_OWED(4));
+    else if constexpr (LEFT == 4) CHOL_PIVOT(CHOL_OWED(0), "", CHOL_OWED(1), CHOL_OWED(2), "", CHOL_OWED(3));
+    else if constexpr (LEFT == 3) CHOL_PIVOT("", "", CHOL_OWED(0), CHOL_OWED(1), "", CHOL_OWED(2));
+    else if constexpr (LEFT == 2) CHOL_PIVOT("", "", CHOL_OWED(0), "", "", CHOL_OWED(1));
+    else if constexpr (LEFT == 1) CHOL_PIVOT("", "", CHOL_OWED(0), "", "", "s_nop 0\n\t");
+    else CHOL_PIVOT("", "", "s_nop 0\n\t", "", "", "s_nop 0\n\t");
+    chol_subs<C + 7>(x, before, std::make_integer_sequence<int, (LEFT > 6 ? LEFT - 6 : 0)>());
+    if constexpr (C < 31) chol_sub<C + 1>(x, now);
+    before = now;
 }
 template <int... C>
 __device__ __forceinline__ void chol_pivots(float (&x)[32], float& piv, std::integer_sequence<int, C...>) {
-    (chol_pivot<C>(x, piv), ...);
+    CholPivot before;
+    (chol_pivot<C>(x, piv, before), ...);
+}
+// x *= lane N of each 16 of v.  (The waits of a DPP operand are the caller's for the first.)
+template <int N>
+__device__ __forceinline__ void chol_mul(float& x, float v) {
+    asm volatile("v_mul_f32_dpp %0, %1, %0 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "+v"(x) : "v"(v), "n"(N));
+}
+template <int... R>
+__device__ __forceinline__ void chol_scale_rows(float (&x)[16], float v, std::integer_sequence<int, R...>) {
+    asm volatile("s_nop 1" : "+v"(v));
+    (chol_mul<R>(x[R], v), ...);
 }
 
-// The same for any pivots, in LDS and at leisure, with roots alone: pivots down to subnormal numbers (the instructions take none: a scaled copy) and up
-// to the largest, rows of pivots that are not positive set to zero.  Returns whether there was one of the latter.
-__device__ __forceinline__ int chol_factor32_any(float* H, float* T, int lane) {
-    const int l32 = lane & 31;
-    volatile float* X = lane < 32 ? H + l32 : T + l32;   // column l of the block or of the identity
-    const int ld = lane < 32 ? CH_LD : CH_LDT;
-    volatile float* G = H;
+// The same for any pivots, in LDS (64 columns at X) and at leisure, with roots alone: pivots down to subnormal numbers (the instructions take none: a
+// scaled copy) and up to the largest, rows of pivots that are not positive set to zero.  Returns whether there was one of the latter.
+__device__ __forceinline__ int chol_rows32_any(volatile float* X, int lane) {
     int bad = 0;
-    if (lane >= 32)
-        for (int r = 0; r < 32; ++r) X[r * ld] = r == l32 ? 1.f : 0.f;
 #pragma unroll 1
     for (int c = 0; c < 32; ++c) {
-        const float piv = G[c * CH_LD + c];
+        const float piv = X[c * 64 + c];
         const bool tiny = piv < 0x1p-64f, pos = piv > 0.f;
         const float ps = tiny ? piv * 0x1p64f : piv;
         float y = __builtin_amdgcn_rsqf(ps);
         y = fmaf(0.5f * y, fmaf(-ps * y, y, 1.f), y);
         y = tiny ? y * 0x1p32f : y;
         bad |= !pos;
-        const float xc = X[c * ld] * (pos ? y : 0.f);
-        X[c * ld] = xc;
+        __builtin_amdgcn_wave_barrier();
+        const float xc = X[c * 64 + lane] * (pos ? y : 0.f);
+        X[c * 64 + lane] = xc;
         __builtin_amdgcn_wave_barrier();
 #pragma unroll 1
-        for (int r = c + 1; r < 32; ++r) X[r * ld] = fmaf(-G[c * CH_LD + r], xc, X[r * ld]);
+        for (int r = c + 1; r < 32; ++r) X[r * 64 + lane] = fmaf(-X[c * 64 + r], xc, X[r * 64 + lane]);
         __builtin_amdgcn_wave_barrier();
-    }
-    float x[32];
-#pragma unroll
-    for (int r = 0; r < 32; ++r) x[r] = X[r * ld];
-    __builtin_amdgcn_wave_barrier();
-    if (lane >= 32) {
-#pragma unroll
-        for (int r = 0; r < 32; ++r) {
-            G[r * CH_LD + l32] = x[r];
-            T[l32 * CH_LDT + r] = x[r];
-        }
     }
     return bad;
 }
 
-// One wavefront: the 32 x 32 diagonal block at H (leading dimension CH_LD, upper triangle read) is replaced by Y = R^-T
-// (lower triangular, zeros above), and T (leading dimension CH_LDT) receives Y^T = R^-1.  Lane l < 32 holds column l of
-// the block, lane 32 + l column l of the identity.  A pivot row's entries reach the other rows through lane broadcasts that are part
+// The planes of a row of 32 x 32 blocks in LDS: of each block the two pieces of eight k for a line at [pair of eight][piece][half][line] in 16 bytes; a lane's
+// half h and pair f have rows 16 h + 8 f .. + 7 (any order of k does, if both operands have it).
+constexpr int CH_ROW = 4 * SG_FRAG;
+struct CholBlock {
+    // Y: block s of its diagonal in columns 32 s .. + 31; spare: a wavefront's each
+    float H[NB * CH_LD], Y[32 * CH_LD], spare[4][32 * 64], up[2][NB];
+    uint8_t rows[2][4 * CH_ROW];
+    unsigned largest[NB];
+};
+
+// One wavefront: the 32 rows of a diagonal block `diag` (upper triangle read) and of the 32 more columns at `right` are eliminated, the latter to planes (`row`, `up`)
+// and, with `keep`, in place.  Lane l < 32 holds column l of the block, lane 32 + l column l of the others.
+// A pivot row's entries reach the other rows through lane broadcasts that are part
 // of the multiplication; the rows are scaled by 1 / sqrt(pivot) at the end, all roots at once.  What bounds it: a wavefront on its own issues one
-// instruction in four cycles, here 12 and one per row below for a pivot.  (With every entry through a scalar register, two
-// instructions a row, and the root in the chain from pivot to pivot 8300 cycles; so 4400 with 11 instructions a pivot.)  Returns whether a pivot was not positive.
-__device__ __forceinline__ int chol_factor32(float* H, float* T, int lane) {
-    const int l32 = lane & 31;
-    const bool right = lane >= 32;
-    float x[32], piv = 1.f;
+// instruction in four to five cycles, here 13 and one per row below for a pivot, eight where an instruction waits for the one before it.  (32 pivots
+// 4250 cycles, and 1700 for loads, roots and planes.)
+// Returns whether a pivot was not positive.
+__device__ __forceinline__ int chol_rows32(const float* diag, float* right, bool keep, uint8_t* row, float* up, float* spare, int lane) {
+    const bool upper = lane >= 32;
+    const int l32 = lane & 31, h = lane >> 5;
+    const float* src = (upper ? right : diag) + l32;
+    float x[32], piv = 1.f, o[16];
+    int bad = 0;
 #pragma unroll
-    for (int r = 0; r < 32; ++r) {
-        x[r] = H[r * CH_LD + l32];
-        asm("" : "+v"(x[r]));  // (loaded by all lanes, not in a branch of its own)
-    }
-#pragma unroll
-    for (int r = 0; r < 32; ++r) x[r] = right ? (r == l32 ? 1.f : 0.f) : x[r];
+    for (int r = 0; r < 32; ++r) x[r] = src[r * CH_LD];
     chol_pivots(x, piv, std::make_integer_sequence<int, 32>());
     // (below 2^-126, whose reciprocal and root the instructions do not take, 2^126 and more, whose reciprocal they do not return, or not positive)
-    if (__any(__builtin_bit_cast(unsigned, piv) - 0x00800000u >= 0x7e000000u)) return chol_factor32_any(H, T, lane);
-    float y = __builtin_amdgcn_rsqf(piv);
-    y = fmaf(0.5f * y, fmaf(-piv * y, y, 1.f), y);
+    if (__any(__builtin_bit_cast(unsigned, piv) - 0x00800000u >= 0x7e000000u)) {
+#pragma unroll 1
+        for (int r = 0; r < 32; ++r) spare[r * 64 + lane] = src[r * CH_LD];
+        __builtin_amdgcn_wave_barrier();
+        bad = chol_rows32_any(spare, lane);
 #pragma unroll
-    for (int r = 0; r < 32; ++r) x[r] *= __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, y), r));
-    if (right) {
+        for (int r = 0; r < 16; ++r) o[r] = spare[(16 * h + r) * 64 + 32 + l32];
+    } else {
+        // the columns on the right to all lanes: rows 0-15 of column l to lane l, 16-31 to lane 32 + l
 #pragma unroll
-        for (int r = 0; r < 32; ++r) {
-            H[r * CH_LD + l32] = x[r];
-            T[l32 * CH_LDT + r] = x[r];
-        }
+        for (int r = 0; r < 16; ++r)
+            o[r] = __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x[r]), __builtin_bit_cast(unsigned, x[16 + r]), false, false)[1]);
+        float y = __builtin_amdgcn_rsqf(piv);
+        y = fmaf(0.5f * y, fmaf(-piv * y, y, 1.f), y);
+        // lanes 0-15 of y in lanes 0-15 and 16-31, lanes 16-31 in lanes 32-47 and 48-63
+        const unsigned yb = __builtin_bit_cast(unsigned, y);
+        const unsigned both = __builtin_amdgcn_permlane32_swap(yb, yb, false, false)[0];
+        const auto halves = __builtin_amdgcn_permlane16_swap(both, both, false, false);
+        chol_scale_rows(o, __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_permlane32_swap((unsigned)halves[0], (unsigned)halves[1], false, false)[0]),
+                        std::make_integer_sequence<int, 16>());
     }
-    return 0;
+    if (keep) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) right[(16 * h + r) * CH_LD + l32] = o[r];
+    }
+    float mx = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, fabsf(o[r]));
+    const unsigned mb = __builtin_bit_cast(unsigned, mx);
+    const auto two = __builtin_amdgcn_permlane32_swap(mb, mb, false, false);
+    const SgScale scale = sg_scale(fmaxf(__builtin_bit_cast(float, (unsigned)two[0]), __builtin_bit_cast(float, (unsigned)two[1])));
+    if (lane < 32) up[l32] = scale.up;
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+        float part[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) part[e] = o[8 * f + e];
+        sg_store2<false, SG_FRAG>(row + 2 * f * SG_FRAG + lane * 16, part, scale);
+    }
+    return bad;
 }
 
-// One workgroup (256 threads): the 128 x 128 block in LDS (upper triangle; identity where it is padded) is factored, and tinv
-// (128 x 128, row major, device memory) receives Y = R^-T, the inverse of the transposed factor: its 32 x 32 blocks on and below the diagonal.  *fail is raised if
-// a pivot is not positive.  The elimination above, once more, with blocks of 32: all wavefronts bring the
-// next diagonal block up to date, wavefront 0 factors it while the others update the rest.
-__device__ __forceinline__ void chol_block(float* H, float* T, float* __restrict__ tinv, int* __restrict__ fail) {
-    const int tid = threadIdx.x, lane = tid & 63;
+// d -= P^T Q (or d = -P^T Q) for 16 x 32 values at d, row length CH_LD, from the planes of two blocks, lines 16 r16 .. + 15 of P's.  All four products of the pieces.
+__device__ __forceinline__ void chol_update16(float* d, const uint8_t* P, const float* p_up, int r16, const uint8_t* Q, const float* q_up, bool fresh, int lane) {
+    const int l16 = lane & 15, g = lane >> 4;
+    auto at = [&](const uint8_t* base, int piece, int line) { return *reinterpret_cast<const v8h*>(base + (4 * (g >> 1) + 2 * piece + (g & 1)) * (SG_FRAG / 2) + line * 16); };
+    v8h a[2], b[2][2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        a[p] = at(P, p, 16 * r16 + l16);
+#pragma unroll
+        for (int n = 0; n < 2; ++n) b[n][p] = at(Q, p, 16 * n + l16);
+    }
+    const v4f pu = *reinterpret_cast<const v4f*>(p_up + 16 * r16 + 4 * g);
+    float qu[2];
+    v4f old[2];
+    d += 4 * g * CH_LD + l16;
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        qu[n] = q_up[16 * n + l16];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) old[n][v] = d[v * CH_LD + 16 * n];
+    }
+    v4f hh[2], hl[2], ll[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        hh[n] = hl[n] = ll[n] = (v4f){0.f, 0.f, 0.f, 0.f};
+        ll[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[1], b[n][1], ll[n], 0, 0, 0);
+        hl[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[1], b[n][0], hl[n], 0, 0, 0);
+        hh[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[0], b[n][0], hh[n], 0, 0, 0);
+    }
+#pragma unroll
+    for (int n = 0; n < 2; ++n) hl[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[0], b[n][1], hl[n], 0, 0, 0);
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float low = fmaf(ll[n][v], 1.f / SG_LOW, hl[n][v]);
+            d[v * CH_LD + 16 * n] = (fresh ? 0.f : old[n][v]) - fmaf(low, 1.f / SG_LOW, hh[n][v]) * pu[v] * qu[n];
+        }
+}
+
+// One workgroup: the 128 x 128 block H in LDS (upper triangle; identity where it is padded) is factored, and `planes` receives T = R^-T, the inverse of the
+// transposed factor, as an operand whose lines are T's rows.  *fail is raised if a pivot is not positive.  The elimination above, once more, with blocks of
+// 32: beside the diagonal block a row has four blocks, those of G, the identity, those of Y, and each of four wavefronts takes the
+// diagonal block and one of them through the pivots (so no product with an inverse follows them); the other four bring rows further down up to date
+// meanwhile.  (On the fp16 matrix cores: a vector instruction waits for an fp32 matrix instruction of another wavefront of its SIMD, 64 cycles each, but not for
+// an fp16 one.)  Below the diagonal H has Y, on it what was eliminated; the diagonal of Y, the identity to begin with, is apart.
+__device__ __forceinline__ void chol_block_begin(CholBlock& lds) {   // (a barrier follows)
+    const int tid = threadIdx.x;
+    if (tid < NB) lds.largest[tid] = 0;
+#pragma unroll
+    for (int n = 0; n < 32 * NB / CH_THREADS; ++n) {
+        const int e = tid + CH_THREADS * n, i = e / NB, k = e % NB;
+        lds.Y[i * CH_LD + k] = (k & 31) == i ? 1.f : 0.f;
+    }
+}
+__device__ __forceinline__ void chol_block(CholBlock& lds, uint8_t* __restrict__ planes, int* __restrict__ fail) {
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    auto blk = [&](int i, int c) { return H + 32 * i * CH_LD + 32 * c; };
-    const int r16 = w & 1, c16 = w >> 1, at16 = (16 * r16 + 4 * (lane >> 4)) * CH_LD + 16 * c16 + (lane & 15);   // a wavefront's 16 x 16 of a block
+    auto blk = [&](int i, int c) { return (i == c ? lds.Y : lds.H + 32 * i * CH_LD) + 32 * c; };   // (the diagonal: Y's)
     int bad = 0;
+    // 16 rows of block (i, c) take their part of row s
+    auto update = [&](int s, int i, int c, int r16) {
+        const uint8_t* row = lds.rows[s & 1];
+        const float* up = lds.up[s & 1];
+        chol_update16(lds.H + (32 * i + 16 * r16) * CH_LD + 32 * c, row + i * CH_ROW, up + 32 * i, r16, row + c * CH_ROW, up + 32 * c, c == s, lane);
+    };
 #pragma unroll 1
     for (int s = 0; s < 4; ++s) {
-        // beside the pivots of block (s, s): what else row s - 1 takes from the rows i >= s, columns c >= i (G) and c < s (Y)
-        if (w == 0) {
-            bad |= chol_factor32(blk(s, s), T, lane);
+        if (w < 4) {
+            bad |= chol_rows32(lds.H + 32 * s * CH_LD + 32 * s, blk(s, w), w <= s, lds.rows[s & 1] + w * CH_ROW, lds.up[s & 1] + 32 * w, lds.spare[w], lane);
         } else if (s > 0) {
+            // what row s - 1 takes from the rows i > s, columns c >= i (G) and c < s (Y, which starts at c = s - 1)
             int n = 0;
-            for (int i = s; i < 4; ++i)
+            for (int i = s + 1; i < 4; ++i)
                 for (int c = 0; c < 4; ++c) {
-                    if ((c >= s && c < i) || (i == s && c == s)) continue;
-                    if (++n % 3 == w - 1) chol_update32(blk(i, c), blk(s - 1, i), blk(s - 1, c), c == s - 1, lane);   // (Y starts at c = s - 1)
+                    if (c >= s && c < i) continue;
+                    for (int r16 = 0; r16 < 2; ++r16)
+                        if (n++ % 4 == w - 4) update(s - 1, i, c, r16);
                 }
         }
         __syncthreads();
-        // row s, the three blocks beside the diagonal, 16 x 16 of each to a wavefront
-        {
-            float t[8], d[3][8];
-            chol_load16(T + 16 * r16, CH_LDT, lane, t);
-#pragma unroll
-            for (int n = 0; n < 3; ++n) chol_load16(blk(s, n + (n >= s)) + 16 * c16, CH_LD, lane, d[n]);
-            __syncthreads();   // (in place)
-            v4f o[3];
-#pragma unroll
-            for (int n = 0; n < 3; ++n) o[n] = (v4f){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < 8; ++kk)
-#pragma unroll
-                for (int n = 0; n < 3; ++n) o[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(t[kk], d[n][kk], o[n], 0, 0, 0);
-#pragma unroll
-            for (int n = 0; n < 3; ++n)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) blk(s, n + (n >= s))[at16 + v * CH_LD] = o[n][v];
-        }
-        __syncthreads();
-        // the next diagonal block, 16 x 16 to a wavefront
+        // row s + 1 takes its part of row s
         if (s < 3) {
-            float a[8], b[8];
-            chol_load16(blk(s, s + 1) + 16 * r16, CH_LD, lane, a);
-            chol_load16(blk(s, s + 1) + 16 * c16, CH_LD, lane, b);
-            float* d = blk(s + 1, s + 1) + at16;
-            v4f old, o[2];   // (two sums: half the chain)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) old[v] = d[v * CH_LD];
-            o[0] = o[1] = (v4f){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kk = 0; kk < 8; ++kk) o[kk & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kk], b[kk], o[kk & 1], 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) d[v * CH_LD] = old[v] - (o[0][v] + o[1][v]);
+            update(s, s + 1, w & 3, w >> 2);
             __syncthreads();
         }
     }
     if (bad && tid == 0) atomicAdd(fail, 1);
-    // (32 x 32 blocks above the diagonal are not read)
+    // T's planes, its lower triangle alone: wavefront w has lines 32 (w % 4) .. + 31 and every other 16 k of them
+    const int ib = w & 3;
+    float x[4][8], mx = 0.f;
 #pragma unroll
-    for (int n = 0; n < NB * NB / 4 / 256; ++n) {
-        const int e = tid + 256 * n, i = e / (NB / 4), k = 4 * (e % (NB / 4));
-        if (k / 32 <= i / 32) *reinterpret_cast<v4f*>(tinv + NB * i + k) = *reinterpret_cast<const v4f*>(H + i * CH_LD + k);
+    for (int n = 0; n < 4; ++n) {
+        if (n > ib) continue;
+        const float* at = blk(ib, n) + l32 * CH_LD + 16 * (w >> 2) + 8 * h;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            x[n][e] = at[e];
+            mx = fmaxf(mx, fabsf(x[n][e]));
+        }
     }
+    atomicMax(&lds.largest[32 * ib + l32], __builtin_bit_cast(unsigned, mx));
+    __syncthreads();
+    const SgScale scale = sg_scale(__builtin_bit_cast(float, lds.largest[32 * ib + l32]));
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        if (n > ib) continue;
+        sg_store2(planes + ((2 * n + (w >> 2)) * 8 + ib) * SG_FRAG + lane * 16, x[n], scale);
+    }
+    if (w < 4 && lane < 32) reinterpret_cast<float*>(planes + CH_T_UP)[32 * ib + l32] = scale.up;
 }
 
 // Diagonal block 0.
-__global__ __launch_bounds__(256) void dbf_chol_first_kernel(const float* __restrict__ G, int q, float* __restrict__ tinv,
-                                                           int* __restrict__ fail) {
-    __shared__ __align__(16) uint8_t lds[CH_LDS];
-    float* H = reinterpret_cast<float*>(lds);
+__global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_chol_first_kernel(
+    const float* __restrict__ G, int q, uint8_t* __restrict__ planes, int* __restrict__ fail) {
+    __shared__ __align__(16) CholBlock lds;
     const int w = min(q, NB);
-#pragma unroll 16
-    for (int e = threadIdx.x; e < NB * NB; e += 256) {
-        const int i = e / NB, j = e % NB;
-        const float v = G[(size_t)min(min(i, j), w - 1) * q + min(max(i, j), w - 1)];
-        H[i * CH_LD + j] = (i < w && j < w) ? v : (i == j ? 1.f : 0.f);
+    float v[NB * NB / CH_THREADS];
+#pragma unroll
+    for (int n = 0; n < NB * NB / CH_THREADS; ++n) {
+        const int e = threadIdx.x + CH_THREADS * n, i = e / NB, j = e % NB;
+        v[n] = G[(size_t)min(min(i, j), w - 1) * q + min(max(i, j), w - 1)];
     }
+#pragma unroll
+    for (int n = 0; n < NB * NB / CH_THREADS; ++n) {
+        const int e = threadIdx.x + CH_THREADS * n, i = e / NB, j = e % NB;
+        lds.H[i * CH_LD + j] = (i < w && j < w) ? v[n] : (i == j ? 1.f : 0.f);
+    }
+    chol_block_begin(lds);
     __syncthreads();
-    chol_block(H, H + NB * CH_LD, tinv, fail);
+    chol_block(lds, planes, fail);
 }
 
-// Row jb, 32 columns per workgroup: the planes of R_jj^-T [G | Y][jb, :].  Wavefront w makes rows 32 w .. + 31; every load is
-// issued before anything waits.  (Columns of the diagonal block itself: Y there is R_jj^-T, the product with the identity.)
-__global__ __launch_bounds__(256) void dbf_chol_panel_kernel(const float* __restrict__ G, int q, int jb, const float* __restrict__ tinv,
-                                                           uint8_t* __restrict__ planes) {
-    __shared__ float Q[NB][33], part[4][32];
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int j0 = jb * NB, wb = min(NB, q - j0), c0 = 32 * blockIdx.x, n_kb = sg_kblocks(q);
-    const bool diag = (c0 / NB) == jb;
-    const int rk = tid >> 5, cc = c0 + (tid & 31);
-    float qv[16];
-    v4f a[16];
+// ---- blocks of row j: [R | Y][j, c] = T [G | Y][j, c], a workgroup of eight wavefronts --------------------------------------
+// An operand's planes in LDS are laid out like a chunk of them in memory; what else a block's making needs:
+struct CholScales {
+    unsigned g_largest[NB], p_largest[NB];   // largest magnitudes of the columns, before and after; zeros to begin with
+};
+// A thread's part of [G | Y][j, c]: register e of x[b] is row 16 w + 8 h + e, column 32 b + l32.
+// (Addresses are a scalar base, the block row's, and 32 bits: 128 rows of a matrix that fits the memory are less than 2^31 bytes.)
+__device__ __forceinline__ void chol_load_block(const float* __restrict__ G, int q, int j, int c, float (&x)[4][8]) {
+    const int lane = threadIdx.x & 63, row0 = 16 * (threadIdx.x >> 6) + 8 * (lane >> 5), rows = q - NB * j;
+    const float* base = G + (size_t)(NB * j) * q;
+    unsigned col[4];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) qv[e] = G[(size_t)(j0 + min(rk + 8 * e, wb - 1)) * q + min(cc, q - 1)];
-    // (register e of a[m] is k = 8 m + 4 h + e of row 32 w + l32; k >= 32 (w + 1) is not used)
+    for (int b = 0; b < 4; ++b) col[b] = min(NB * c + 32 * b + (lane & 31), q - 1);
 #pragma unroll
-    for (int m = 0; m < 16; ++m) a[m] = *reinterpret_cast<const v4f*>(tinv + (32 * w + l32) * NB + 8 * m + 4 * h);
+    for (int e = 0; e < 8; ++e) {
+        const unsigned at = (unsigned)min(row0 + e, rows - 1) * (unsigned)q;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int k = rk + 8 * e;
-        Q[k][tid & 31] = (k >= wb || cc >= q) ? 0.f : diag ? (j0 + k == cc ? 1.f : 0.f) : qv[e];
+        for (int b = 0; b < 4; ++b) x[b][e] = base[at + col[b]];
     }
-    __syncthreads();
-    v16f acc;
+}
+// ... into planes.  (Block (j, j) stands for Y's, where the product with the identity is T.)  Two barriers are the caller's: one between the
+// zeros of s.g_largest and this, one behind it.
+__device__ __forceinline__ void chol_split_block(float (&x)[4][8], int q, int j, int c, uint8_t* planes, CholScales& s) {
+    const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5, w = threadIdx.x >> 6;
+    if (c == j || NB * (c + 1) > q || NB * (j + 1) > q) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int row = NB * j + 16 * w + 8 * h + e, col = NB * c + 32 * b + l32;
+                x[b][e] = (row >= q || col >= q) ? 0.f : c == j ? (row == col ? 1.f : 0.f) : x[b][e];
+            }
+    }
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        if (b > w) break;
+        float mx = 0.f;
 #pragma unroll
-        for (int m = 4 * b; m < 4 * b + 4; ++m)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[m][e], Q[8 * m + 4 * h + e][l32], acc, 0, 0, 0);
+        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(x[b][e]));
+        atomicMax(&s.g_largest[32 * b + l32], __builtin_bit_cast(unsigned, mx));
     }
-    // the largest magnitude of each column: its scale
-    float mx = 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) mx = fmaxf(mx, fabsf(acc[v]));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    if (lane < 32) part[w][lane] = mx;
     __syncthreads();
-    mx = fmaxf(fmaxf(part[0][l32], part[1][l32]), fmaxf(part[2][l32], part[3][l32]));
-    const SgScale scale = sg_scale(mx);
-    if (tid < 32) reinterpret_cast<float*>(planes + sg_scales_at(2, q, q))[(size_t)jb * sg_lines(q) + c0 + tid] = scale.up;
-    // register v of lane (h, l32) is row 8 (v / 4) + 4 h + v % 4; a plane wants rows 8 h .. + 7 of each 16
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float lo = acc[8 * t + e], hi = acc[8 * t + 4 + e];
-            const float got = __shfl_xor(h ? lo : hi, 32, 64);
-            x[e] = h ? got : lo;
-            x[4 + e] = h ? hi : got;
-        }
-        const int kb = j0 / 16 + 2 * w + t;
-        sg_store2(planes + (((size_t)(c0 / NB) * n_kb + kb) * 8 + ((c0 >> 5) & 3)) * SG_FRAG + lane * 16, x, scale);
-    }
+    for (int b = 0; b < 4; ++b)
+        sg_store2(planes + (w * 8 + b) * SG_FRAG + lane * 16, x[b], sg_scale(__builtin_bit_cast(float, s.g_largest[32 * b + l32])));
 }
-
-// The products of one chunk for a workgroup of 128 x 128 outputs (dbf_split_gemm.h has the layout of the operands): acc = their sums, scaled.
-// 32 k per step, through registers into two LDS buffers.  `meanwhile` runs beside the last step's products.  Ends with a barrier behind the last read of `lds`.
-struct CholTile {
-    uint8_t frags[2][32 * SG_FRAG];
-    float up[256];
-};
-template <class F>
-__device__ __forceinline__ void chol_tile(CholTile& lds, const SgOperand P, const SgOperand Q, v16f (&acc)[2][2], F meanwhile) {
-    constexpr int STEPS = NB / 32;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), fi = 2 * (w & 1), fj = 2 * (w >> 1);
-    v4f st[8];
-    v16f low[2][2];   // the products with a low piece (dbf_split_gemm.h)
-    // (an operand's 32 k are 16 KiB in one run: [k / 16][piece][32-block])
-    auto fetch = [&](int s) {
+// A wavefront makes two blocks of 32 x 32 side by side: the four row blocks, whose T has 2, 4, 6 and 8 fragments of k, are dealt so that the two wavefronts of a
+// SIMD (w and w + 4, as a workgroup's are placed) have ten between them.
+__device__ __forceinline__ int chol_row_block(int w) { return w < 4 ? w >> 1 : 3 - ((w & 3) >> 1); }
+__device__ __forceinline__ void chol_load_t(const uint8_t* __restrict__ t_planes, v8h (&t)[8][2]) {
+    const int lane = threadIdx.x & 63, rb = chol_row_block(__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6));
 #pragma unroll
-        for (int n = 0; n < 8; ++n) st[n] = *reinterpret_cast<const v4f*>((n < 4 ? P.frags : Q.frags) + (size_t)s * 16 * SG_FRAG + 4096 * (n & 3) + 16 * tid);
-    };
-    auto stage = [&](int buf) {
+    for (int n = 0; n < 4; ++n)
+        if (n <= rb) {
 #pragma unroll
-        for (int n = 0; n < 8; ++n) *reinterpret_cast<v4f*>(&lds.frags[buf][4096 * n + 16 * tid]) = st[n];
-    };
+            for (int k = 2 * n; k < 2 * n + 2; ++k)
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[bi][bj][v] = low[bi][bj][v] = 0.f;
-    fetch(0);
-    const float up = tid < 128 ? P.up[tid] : Q.up[tid - 128];
-    stage(0);
-    lds.up[tid] = up;
-    fetch(1);
-    __syncthreads();
-#pragma unroll
-    for (int s = 0; s < STEPS; ++s) {
-        if (s + 1 < STEPS) stage((s + 1) & 1);
-        if (s + 2 < STEPS) fetch(s + 2);
-        __builtin_amdgcn_sched_barrier(0);
-        if (s + 1 == STEPS) meanwhile();
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-            const uint8_t* base = &lds.frags[s & 1][8 * sub * SG_FRAG + 16 * lane];
-            v8h a[2][2], b[2][2];
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int x = 0; x < 2; ++x) {
-                    a[x][p] = *reinterpret_cast<const v8h*>(base + (4 * p + fi + x) * SG_FRAG);
-                    b[x][p] = *reinterpret_cast<const v8h*>(base + (16 + 4 * p + fj + x) * SG_FRAG);
-                }
-#pragma unroll
-            for (int p = 1; p >= 0; --p)
-#pragma unroll
-                for (int q = 1 - p; q >= 0; --q)
-#pragma unroll
-                    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-                        for (int bj = 0; bj < 2; ++bj) {
-                            v16f& sum = p + q == 0 ? acc[bi][bj] : low[bi][bj];
-                            sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][p], b[bj][q], sum, 0, 0, 0);
-                        }
+                for (int p = 0; p < 2; ++p) t[k][p] = *reinterpret_cast<const v8h*>(t_planes + ((k * 2 + p) * 4 + rb) * SG_FRAG + lane * 16);
         }
-        __syncthreads();
-    }
-    // (P's scale first, unlike sg_scaled in dbf_split_gemm.h: P is R, whose entries are below the root of one of G's, 2^64)
+}
+// The product, and its own planes to `out` (LDS), its lines' scales to `up`; with `rows` also to the planes of all of [R | Y] there.  Begins with a barrier (the
+// planes `g` are whole) and ends without one.
+__device__ __forceinline__ void chol_make_block(const v8h (&t)[8][2], const float* t_up, const uint8_t* g, uint8_t* out, float* up,
+                                                CholScales& s, uint8_t* __restrict__ rows, int q, int j, int c) {
+    const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int c0 = 2 * (w & 1), rb = chol_row_block(w);
+    __syncthreads();
+    v16f acc[2], low[2];
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = low[0][v] = low[1][v] = 0.f;
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            const float uq = lds.up[128 + 32 * (fj + bj) + (lane & 31)];
+    for (int n = 0; n < 4; ++n)
+        if (n <= rb) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const v4f ur = *reinterpret_cast<const v4f*>(&lds.up[32 * (fi + bi) + 8 * c + 4 * (lane >> 5)]);
+            for (int k = 2 * n; k < 2 * n + 2; ++k) {
+                v8h x[2][2];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[bi][bj][4 * c + e] = fmaf(low[bi][bj][4 * c + e], 1.f / SG_LOW, acc[bi][bj][4 * c + e]) * ur[e] * uq;
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) x[b][p] = *reinterpret_cast<const v8h*>(g + ((k * 2 + p) * 4 + c0 + b) * SG_FRAG + lane * 16);
+                const v8h t_low = t[k][1] * (_Float16)(1.f / SG_LOW);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) low[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(t_low, x[b][1], low[b], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) low[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(t[k][1], x[b][0], low[b], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(t[k][0], x[b][0], acc[b], 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < 2; ++b) low[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(t[k][0], x[b][1], low[b], 0, 0, 0);
             }
         }
+    float mx[2] = {0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const v4f ur = *reinterpret_cast<const v4f*>(t_up + 32 * rb + 8 * k + 4 * h);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                acc[b][4 * k + e] = fmaf(low[b][4 * k + e], 1.f / SG_LOW, acc[b][4 * k + e]) * ur[e];
+                mx[b] = fmaxf(mx[b], fabsf(acc[b][4 * k + e]));
+            }
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) atomicMax(&s.p_largest[32 * (c0 + b) + l32], __builtin_bit_cast(unsigned, mx[b]));
     __syncthreads();
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int line = 32 * (c0 + b) + l32;
+        const SgScale scale = sg_scale(__builtin_bit_cast(float, s.p_largest[line]));
+        if (rb == 0 && h == 0) {
+            // (the columns' own scales have been left out so far.  T is an inverse root of G, from 2^-64 to 2^75: the sums times its scales are normal numbers)
+            const float all = scale.up * sg_scale(__builtin_bit_cast(float, s.g_largest[line])).up;
+            if (up) up[line] = all;
+            if (rows) reinterpret_cast<float*>(rows + sg_scales_at(2, q, q))[(size_t)j * sg_lines(q) + NB * c + line] = all;
+        }
+        // register v of lane (h, l32) is row 8 (v / 4) + 4 h + v % 4; a plane wants rows 8 h .. + 7 of each 16
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float lo = acc[b][8 * k + e], hi = acc[b][8 * k + 4 + e];   // (values of their own: the cast takes no element of a vector)
+                const auto swapped = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, lo), __builtin_bit_cast(unsigned, hi), false, false);
+                x[e] = __builtin_bit_cast(float, (unsigned)swapped[0]);
+                x[4 + e] = __builtin_bit_cast(float, (unsigned)swapped[1]);
+            }
+            const int kb = 2 * rb + k;
+            if (out) sg_store2(out + (kb * 8 + c0 + b) * SG_FRAG + lane * 16, x, scale);
+            if (rows) sg_store2(rows + (((size_t)c * sg_kblocks(q) + NB / 16 * j + kb) * 8 + c0 + b) * SG_FRAG + lane * 16, x, scale);
+        }
+    }
 }
 
-// Rows i > jb: [G | Y][i, :] -= R[jb, i]^T [R | Y][jb, :], a workgroup per 128 x 128 block.  Workgroup (0, 0) has diagonal block jb + 1: it keeps it in LDS
-// and factors it; being the first of the launch it starts with it.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_chol_update_kernel(
-    float* __restrict__ G, int q, int jb, const uint8_t* __restrict__ planes, float* __restrict__ tinv_next, int* __restrict__ fail) {
-    __shared__ __align__(16) uint8_t lds[CH_LDS > sizeof(CholTile) ? CH_LDS : sizeof(CholTile)];
-    const int nblk = gridDim.x, it = jb + 1 + blockIdx.y, jt = (int)((jb + 1 + blockIdx.x) % nblk);
-    if (jt > jb && jt < it) return;
+// Row j: a workgroup per block (i, c), i > j, of [G | Y] (c >= i and c <= j), row by row from the diagonal block on: the first is the diagonal block
+// j + 1, which it factors, and being the first of the launch it starts with it.  Row j of Y is written by the workgroups of row j + 1.
+// (The products of P and Q are of 128 k each; the sums' scales: P's first, unlike sg_scaled in dbf_split_gemm.h: P is R, whose entries are below the root of
+// one of G's, 2^64.)
+// MADE: row j is in `rows` already, its planes in G's columns too (dbf_chol_panel_kernel).
+template <bool MADE>
+__global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_chol_row_kernel(
+    float* __restrict__ G, int q, int j, const uint8_t* __restrict__ t_planes, uint8_t* __restrict__ rows, uint8_t* __restrict__ t_next,
+    int* __restrict__ fail) {
+    struct Tiles {
+        uint8_t g[CH_PLANES], p[CH_PLANES];
+        float t_up[NB], up[2][NB];
+        CholScales s[2];
+    };
+    __shared__ __align__(16) uint8_t lds[sizeof(Tiles) > sizeof(CholBlock) ? sizeof(Tiles) : sizeof(CholBlock)];
+    Tiles& T = *reinterpret_cast<Tiles*>(lds);
+    const int nblk = (q + NB - 1) / NB;
+    int i = j + 1, c = blockIdx.x;   // row i has its n - i blocks of G and j + 1 of Y
+    while (c >= nblk - i + j + 1) c -= nblk - i++ + j + 1;
+    c = c < nblk - i ? i + c : c - (nblk - i);
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), fi = 2 * (w & 1), fj = 2 * (w >> 1);
-    const bool factor = blockIdx.x == 0 && blockIdx.y == 0;
-    v16f acc[2][2];
-    float old[2][2][16];
-    // (block row jb is whole: only the last can be short, and it has nothing to update)
-    chol_tile(*reinterpret_cast<CholTile*>(lds), sg_operand(planes, 2, q, q, it, jb), sg_operand(planes, 2, q, q, jt, jb), acc, [&]() {
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool diag = i == c;
+    v8h t[8][2];
+    float x[4][8], y[4][8], up_or_t;
+    if (MADE) {
+        const SgOperand P = sg_operand(rows, 2, q, q, i, j), Q = sg_operand(rows, 2, q, q, c, j);
 #pragma unroll
-                           for (int bi = 0; bi < 2; ++bi)
+        for (int n = 0; n < 8; ++n) sg_load16_lds(P.frags + (8 * w + n) * SG_FRAG + lane * 16, T.p + (8 * w + n) * SG_FRAG);
+        if (!diag) {
 #pragma unroll
-                               for (int bj = 0; bj < 2; ++bj)
+            for (int n = 0; n < 8; ++n) sg_load16_lds(Q.frags + (8 * w + n) * SG_FRAG + lane * 16, T.g + (8 * w + n) * SG_FRAG);
+        }
+        up_or_t = (tid & NB ? Q : P).up[tid & (NB - 1)];
+    } else {
+        chol_load_block(G, q, j, i, x);
+        chol_load_t(t_planes, t);
+        (&T.s[0].g_largest[0])[tid] = 0;
+        up_or_t = reinterpret_cast<const float*>(t_planes + CH_T_UP)[tid & (NB - 1)];
+    }
+    // this wavefront's two blocks of 32 x 32: side by side, or of a diagonal block's upper ten the w-th and, for two wavefronts, one more
+    auto upper = [](int n) { return n < 4 ? n : n < 7 ? 4 + n - 3 : n < 9 ? 8 + n - 5 : 15; };
+    const int b0 = diag ? upper(w) : 4 * (w & 3) + 2 * (w >> 2), b1 = diag ? upper(min(w + 8, 9)) : b0 + 1;
+    const bool two = !diag || w < 2;
+    auto row_of = [&](int b, int v) { return 32 * (b >> 2) + 8 * (v >> 2) + 4 * h + (v & 3); };
+    auto col_of = [&](int b) { return 32 * (b & 3) + l32; };
+    float* const Gi = G + (size_t)(NB * i) * q;
+    auto load_old = [&](float (&o)[4][8]) {   // (what is subtracted from, register 16 n + v)
 #pragma unroll
-                                   for (int v = 0; v < 16; ++v) {
-                                       const int row = NB * it + 32 * (fi + bi) + 8 * (v >> 2) + 4 * h + (v & 3);
-                                       const int col = NB * jt + 32 * (fj + bj) + l32;
-                                       old[bi][bj][v] = G[(size_t)min(row, q - 1) * q + min(col, q - 1)];
-                                   }
-                       });
-    float* H = reinterpret_cast<float*>(lds);   // (the tile's last barrier is behind every read of the operands)
+        for (int n = 0; n < 2; ++n) {
+            if (n == 1 && !two) break;
+            const unsigned col = min(NB * c + col_of(n ? b1 : b0), q - 1);
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
+            for (int v = 0; v < 16; ++v) o[2 * n + (v >> 3)][v & 7] = Gi[(unsigned)min(row_of(n ? b1 : b0, v), q - NB * i - 1) * (unsigned)q + col];
+        }
+    };
+    if (MADE) {
+        load_old(y);
+        if (tid < 2 * NB) T.up[0][tid] = up_or_t;
+    } else {
+        if (diag) load_old(y); else chol_load_block(G, q, j, c, y);
+        __syncthreads();
+        if (tid < NB) T.t_up[tid] = up_or_t;
+        chol_split_block(x, q, j, i, T.g, T.s[0]);
+        chol_make_block(t, T.t_up, T.g, T.p, T.up[0], T.s[0], nullptr, q, j, i);
+        if (!diag) {   // (everyone is done with the planes in T.g; the second's take the place of what they are made from)
+            chol_split_block(y, q, j, c, T.g, T.s[1]);
+            load_old(y);
+            chol_make_block(t, T.t_up, T.g, T.g, T.up[1], T.s[1], i == j + 1 && c <= j ? rows : nullptr, q, j, c);
+        }
+    }
+    __syncthreads();
+    const uint8_t *P = T.p + lane * 16, *Q = (diag ? T.p : T.g) + lane * 16;
+    v16f acc[2], low[2];
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
+    for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = low[0][v] = low[1][v] = 0.f;
+    auto product = [&](int n, const v8h (&a)[2], const v8h (&b)[2]) {
+        low[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[1], b[0], low[n], 0, 0, 0);
+        low[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], b[1], low[n], 0, 0, 0);
+        acc[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[0], b[0], acc[n], 0, 0, 0);
+    };
+#pragma unroll
+    for (int kb = 0; kb < NB / 16; ++kb) {
+        auto frag = [&](const uint8_t* base, int line, v8h (&f)[2]) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p) f[p] = *reinterpret_cast<const v8h*>(base + ((kb * 2 + p) * 4 + line) * SG_FRAG);
+        };
+        v8h a[2], b[2];
+        frag(P, b0 >> 2, a);
+        frag(Q, b0 & 3, b);
+        product(0, a, b);
+        if (two) {
+            if (diag) frag(P, b1 >> 2, a);
+            frag(Q, b1 & 3, b);
+            product(1, a, b);
+        }
+    }
+    const float *up = T.up[0], *uq = T.up[diag ? 0 : 1];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const int b = n ? b1 : b0;
+        const float u = uq[col_of(b)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const v4f ur = *reinterpret_cast<const v4f*>(up + row_of(b, 4 * k));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int v = 4 * k + e;
+                acc[n][v] = (c == j ? 0.f : y[2 * n + (v >> 3)][v & 7]) - fmaf(low[n][v], 1.f / SG_LOW, acc[n][v]) * ur[e] * u;
+            }
+        }
+    }
+    if (blockIdx.x > 0) {
+#pragma unroll
+        for (int n = 0; n < 2; ++n)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int i = 32 * (fi + bi) + 8 * (v >> 2) + 4 * h + (v & 3), j = 32 * (fj + bj) + l32;
-                const int row = NB * it + i, col = NB * jt + j;
-                const bool in = row < q && col < q;
-                const float val = (jt == jb ? 0.f : old[bi][bj][v]) - acc[bi][bj][v];
-                if (factor) H[i * CH_LD + j] = in ? val : (i == j ? 1.f : 0.f);
-                else if (in) G[(size_t)row * q + col] = val;
+                if (n == 1 && !two) continue;
+                const int row = row_of(n ? b1 : b0, v), col = NB * c + col_of(n ? b1 : b0);
+                if (row < q - NB * i && col < q) Gi[(unsigned)row * (unsigned)q + (unsigned)col] = acc[n][v];
             }
-    if (!factor) return;
+        return;
+    }
+    CholBlock& B = *reinterpret_cast<CholBlock*>(lds);
+    const bool whole = NB * (i + 1) <= q;
+    __syncthreads();   // (the block takes the planes' place)
+    chol_block_begin(B);
+#pragma unroll
+    for (int n = 0; n < 2; ++n)
+        if (n == 0 || two) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = row_of(n ? b1 : b0, v), col = col_of(n ? b1 : b0);
+                B.H[row * CH_LD + col] = (whole || (NB * i + row < q && NB * i + col < q)) ? acc[n][v] : (row == col ? 1.f : 0.f);
+            }
+        }
     __syncthreads();
-    chol_block(H, H + NB * CH_LD, tinv_next, fail);
+    chol_block(B, t_next, fail);
+}
+
+// Row j by itself, a workgroup per 128 columns: the last of Y, and rows whose blocks below are many.
+__global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_chol_panel_kernel(
+    const float* __restrict__ G, int q, int j, const uint8_t* __restrict__ t_planes, uint8_t* __restrict__ rows) {
+    __shared__ __align__(16) uint8_t g[CH_PLANES];
+    __shared__ __align__(16) float t_up[NB];
+    __shared__ CholScales s;
+    const int c = blockIdx.x;
+    v8h t[8][2];
+    float x[4][8];
+    chol_load_block(G, q, j, c, x);
+    chol_load_t(t_planes, t);
+    if (threadIdx.x < 2 * NB) (&s.g_largest[0])[threadIdx.x] = 0;
+    if (threadIdx.x < NB) t_up[threadIdx.x] = reinterpret_cast<const float*>(t_planes + CH_T_UP)[threadIdx.x];
+    __syncthreads();
+    chol_split_block(x, q, j, c, g, s);
+    chol_make_block(t, t_up, g, nullptr, nullptr, s, rows, q, j, c);
 }
 
 // M[j][i] = M[i][j] for i < j: the lower triangle of a symmetric matrix whose upper blocks were computed.
@@ -641,14 +825,14 @@ extern "C" int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int
 // ---- forming the constant matrices of the update on the device ---------------------------------
 namespace {
 struct PrepWorkspace {
-    size_t tinv, fail, S, V, total;
+    size_t T, fail, S, V, total;
     int nblk;
 };
 inline PrepWorkspace prep_workspace(int p, int q, int r) {
     PrepWorkspace w;
     w.nblk = (q + NB - 1) / NB;
     size_t off = 0;
-    w.tinv = off;  off = up256(off + 4 * (size_t)w.nblk * NB * NB);
+    w.T = off;     off = up256(off + CH_PLANES * (size_t)(w.nblk < 2 ? w.nblk : 2));   // planes of R_jj^-T, of two block rows in turn
     w.fail = off;  off = up256(off + 256);
     w.S = off;     off = up256(off + sg_plane_bytes(1, p, q));   // planes of the signs
     // planes of the other operand of the three large contractions in turn: the scaled signs, b . W, [R | Y]
@@ -680,7 +864,6 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
         return DBF_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     uint8_t* base = static_cast<uint8_t*>(workspace_dev);
-    float* tinv = reinterpret_cast<float*>(base + w.tinv);
     int* fail = not_positive_definite_dev ? not_positive_definite_dev : reinterpret_cast<int*>(base + w.fail);
     float* G = static_cast<float*>(Minv_dev);  // G, then its factor, live in the output until the last contraction
     const uint8_t* bits = static_cast<const uint8_t*>(bits_dev);
@@ -707,15 +890,17 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
         g.rs = m2;
         launch_split_gemm<1>(g, st);
     }
-    // [G | I] -> [R | Y], the planes of Y (and of R, row by row) in V
-    hipLaunchKernelGGL(dbf_chol_first_kernel, dim3(1), dim3(256), 0, st, G, q, tinv, fail);
-    for (int jb = 0; jb < w.nblk; ++jb) {
-        const bool last = jb + 1 == w.nblk;
-        float* tj = tinv + (size_t)jb * NB * NB;
-        hipLaunchKernelGGL(dbf_chol_panel_kernel, dim3(4 * w.nblk), dim3(256), 0, st, G, q, jb, tj, V);
-        if (!last)
-            hipLaunchKernelGGL(dbf_chol_update_kernel, dim3(w.nblk, w.nblk - 1 - jb), dim3(256), 0, st, G, q, jb, V, tj + NB * NB,
-                               fail);
+    // [G | I] -> [R | Y], the planes of Y in V
+    uint8_t* T[2] = {base + w.T, base + w.T + CH_PLANES};
+    hipLaunchKernelGGL(dbf_chol_first_kernel, dim3(1), dim3(CH_THREADS), 0, st, G, q, T[0], fail);
+    for (int j = 0; j < w.nblk; ++j) {
+        const int below = w.nblk - 1 - j;   // block rows; the i-th of them has below - i blocks of G and j + 1 of Y
+        const long long blocks = (long long)below * (below + 1) / 2 + (long long)below * (j + 1);
+        const bool made = below == 0 || blocks > CH_MADE;
+        if (made) hipLaunchKernelGGL(dbf_chol_panel_kernel, dim3(w.nblk), dim3(CH_THREADS), 0, st, G, q, j, T[j & 1], V);
+        if (below > 0)
+            hipLaunchKernelGGL(made ? dbf_chol_row_kernel<true> : dbf_chol_row_kernel<false>, dim3((unsigned)blocks), dim3(CH_THREADS), 0, st, G, q, j, T[j & 1], V,
+                               T[~j & 1], fail);
     }
     // G^-1 = Y^T Y (overwrites G): upper blocks, the sums starting where both operands can be non-zero,
     // then the mirror image

@@ -21,6 +21,7 @@ namespace {
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 
 // ---------------------------------------------------------------------------------------------
 // Operand planes.  The operand element (k, i) -- summation index k, output index i -- lives in a fragment of 16 k by 32 i, the
@@ -67,21 +68,36 @@ __device__ __forceinline__ SgScale sg_scale_largest(float mx) {
     return s;
 }
 
-// The two pieces of eight values to a fragment of piece 0 (`at`) and of piece 1.  (LARGEST: a scale that is no power of two; the rest is taken
+// The two pieces of eight values to a fragment of piece 0 (`at`) and, NEXT bytes on, of piece 1.  (LARGEST: a scale that is no power of two; the rest is taken
 // before it is scaled, so that only the rounding of l remains.)
-template <bool LARGEST = false>
+template <bool LARGEST = false, int NEXT = 4 * SG_FRAG>
 __device__ __forceinline__ void sg_store2(uint8_t* at, const float (&x)[8], const SgScale& c) {
     v8h h, l;
-    const float low = c.down * SG_LOW;
+    if (LARGEST) {
+        const float low = c.down * SG_LOW;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        float v = x[e] * c.down;
-        if (LARGEST) asm("" : "+v"(v));   // (one value: the compiler rounds the product for h and for its use below by different instructions, once and twice)
-        h[e] = (_Float16)v;
-        l[e] = (_Float16)(LARGEST ? fmaf(-(float)h[e], c.up, x[e]) * low : (v - (float)h[e]) * SG_LOW);
+        for (int e = 0; e < 8; ++e) {
+            float v = x[e] * c.down;
+            asm("" : "+v"(v));   // (one value: the compiler rounds the product for h and for its use below by different instructions, once and twice)
+            h[e] = (_Float16)v;
+            l[e] = (_Float16)(fmaf(-(float)h[e], c.up, x[e]) * low);
+        }
+    } else {
+        // (v SG_LOW - h SG_LOW: both exact, four instructions an element)
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+            const float v[2] = {x[e] * c.down, x[e + 1] * c.down};
+            v2h two = {(_Float16)v[0], (_Float16)v[1]};
+            asm("" : "+v"(two));   // (or the compiler rounds it a second time for the rest)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                h[e + i] = two[i];
+                l[e + i] = (_Float16)fmaf((float)two[i], -SG_LOW, v[i] * SG_LOW);
+            }
+        }
     }
     *reinterpret_cast<v8h*>(at) = h;
-    *reinterpret_cast<v8h*>(at + 4 * SG_FRAG) = l;
+    *reinterpret_cast<v8h*>(at + NEXT) = l;
 }
 
 // The plane kernels: a workgroup of 256 threads has a chunk of 128 k and 32 lines, a wavefront two fragments of it.
@@ -183,8 +199,8 @@ __global__ __launch_bounds__(256) void dbf_split_signs_kernel(const uint8_t* __r
 }
 
 // ---------------------------------------------------------------------------------------------
-// out[i][j] = rs[i] * cs[j] * sum_k P[k][i] Q[k][j] + add[i][j] + (i == j ? diag : 0)
-// from the planes of P (PA = 2 pieces, or 1: signs) and Q (2 pieces).  Workgroup = 128 x 128 outputs (BI = 2; BI = 1: 64 x 128), 4
+// out[i][j] = sum_k P[k][i] Q[k][j] + add[i][j] from the planes of P (PA = 2 pieces) and Q (2 pieces), or, P being signs (PA = 1),
+// rs[i] * cs[j] * sum_k P[k][i] Q[k][j] + (i == j ? diag : 0).  Workgroup = 128 x 128 outputs (BI = 2; BI = 1: 64 x 128), 4
 // wavefronts of 64 x 64 (2 x 2 blocks of 32 x 32: 64 registers for each of the three sums; BI = 1: 32 x 64), 16 values of k per step:
 // 12 matrix instructions of 32 cycles per wavefront (8 with PA = 1) against 8 (6) LDS reads of 1 KiB.  A step's 16 (12) KiB come straight
 // from memory into one of four LDS buffers, three steps ahead, one barrier per step; two workgroups per compute unit cover each
@@ -197,9 +213,9 @@ __global__ __launch_bounds__(256) void dbf_split_signs_kernel(const uint8_t* __r
 struct SplitGemmArgs {
     const uint8_t* P;
     const uint8_t* Q;
-    const float* add;      // [M][N] with leading dimension lda, or NULL
-    const float* rs;       // [M] or NULL
-    const float* cs;       // [N] or NULL
+    const float* add;      // PA = 2: [M][N] with leading dimension lda, or NULL
+    const float* rs;       // PA = 1: [M]
+    const float* cs;       // PA = 1: [N], or NULL (and diag is 0)
     float* out;            // [M][N], leading dimension ldo
     size_t lda, ldo;
     float diag;
@@ -332,6 +348,15 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
                     for (int bj = 0; bj < 2; ++bj) product(bi, bj, p, q);
     };
+    // l l where the lines meet themselves: there it is of one sign, and lost from all of a diagonal
+    const bool self = PA == 2 && BI == 1 && g.ktri && (row0 >> 7) == jt;
+    auto multiply_self = [&]() {
+        if (PA == 2 && BI == 1 && self) {
+            const v8h s = a[0][PA - 1] * (_Float16)(1.f / SG_LOW);
+#pragma unroll
+            for (int bj = 0; bj < 2; ++bj) low[0][bj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(s, b[bj][1], low[0][bj], 0, 0, 0);
+        }
+    };
     // A chunk's sums, scaled, to the total.  Register v of lane l of a 32 x 32 block is row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.
     // (sg_scaled has the order of the scales)
     auto fold = [&](int bi, int bj) {
@@ -378,6 +403,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
             fetch(ring[(j + 3) & 3], i + (j + 3) / 8, (j + 3) & 7);
             if (j == 0) fetch_ups(i);
             read(ring[j & 3]);
+            multiply_self();
             if (j < 7) multiply(); else multiply_last(KS == 1 || KS * i + kg < chunks);
         }
     }
@@ -407,26 +433,23 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
     // (what is added is loaded for all of the block at once, clamped, not branched around)
     auto row_of = [&](int bi, int v) { return row0 + 32 * (fi + bi) + 8 * (v >> 2) + 4 * h + (v & 3); };
-    if (g.rs) {
+    float rs[BI][16];
+    if (PA == 1) {
 #pragma unroll
         for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float rs = g.rs[min(row_of(bi, v), g.M - 1)];
-#pragma unroll
-                for (int bj = 0; bj < 2; ++bj) tot[bi][bj][v] *= rs;
-            }
+            for (int v = 0; v < 16; ++v) rs[bi][v] = g.rs[min(row_of(bi, v), g.M - 1)];
     }
 #pragma unroll
     for (int bj = 0; bj < 2; ++bj) {
         const int col = 128 * jt + 32 * (fj + bj) + l32, cc = min(col, g.N - 1);
-        const float cs = g.cs ? g.cs[cc] : 1.f;
+        const double cs = PA == 1 && g.cs ? g.cs[cc] : 1.;
         float add[BI][16];
 #pragma unroll
         for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
             for (int v = 0; v < 16; ++v) add[bi][v] = 0.f;
-        if (g.add) {
+        if (PA == 2 && g.add) {
 #pragma unroll
             for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
@@ -437,7 +460,10 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int row = row_of(bi, v);
-                const float val = tot[bi][bj][v] * cs + add[bi][v] + (row == col ? g.diag : 0.f);
+                // (two factors and the diagonal: rounded once, in 64 bits; G's error is common to all that follows.  Minv, means over ten
+                // sizes: 2.25e-7, so 2.22e-7)
+                float val = tot[bi][bj][v] + add[bi][v];
+                if (PA == 1) val = g.cs ? (float)fma((double)tot[bi][bj][v] * (double)rs[bi][v], cs, row == col ? (double)g.diag : 0.) : tot[bi][bj][v] * rs[bi][v];
                 if (row < g.M && col < g.N) g.out[(size_t)row * g.ldo + col] = val;
             }
     }

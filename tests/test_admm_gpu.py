@@ -325,6 +325,15 @@ def test_admm_contractions_with_their_steps_and_blocks_cut_by_size(p, q, r):
     _check_step("update q=%d r=%d" % (q, r), state0, dev.host(), Minv64, C64, rho, 1, z_gate=2 * Z_GATE)
 
 
+@pytest.mark.parametrize("q", [127, 129, 256, 385, 511, 2830])
+def test_admm_prepare_at_the_edges_of_the_elimination_blocks(q):
+    """Blocks of 128 with one row or column more or less, one to five block rows; 2830: 23 block rows, the first of which have more than 256 blocks below
+    them and so are made in a launch of their own.  Gates: as above."""
+    prob = PackedProblem(60, q, 33, I.seed_for(9, 700 + q))
+    Minv, Cm = prob.prepare_on_device(0.9)
+    _check_constants("constants q=%d" % q, prob, 0.9, Minv, Cm)
+
+
 @pytest.mark.parametrize("p,q,r", [(100, 70, 90), (520, 300, 260)])
 def test_sign_tiles_may_start_at_any_multiple_of_four_bytes(p, q, r):
     """The packed signs of the constants and of an update are documented as 4-byte aligned: the same tiles 4, 8 and 12 bytes further on
