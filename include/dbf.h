@@ -283,8 +283,10 @@ int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int r, float r
  *   bits_dev: device, dbf_tiled_bytes(q, p) bytes: S in the tile layout, rows q, columns p (read only).
  *   m2_dev: device fp32 [q];  b_dev: device fp32 [p];  W_dev: device fp32 [p][r] row major (all read only).
  *   rho > 0.   Minv_dev: device fp32 [q][q] out;   C_dev: device fp32 [q][r] out.
- *   workspace_dev: device, 256-byte aligned, >= dbf_admm_prepare_workspace_bytes(p, q, r) bytes (a q x q matrix,
- *          the inverses of the diagonal blocks, S as fp16 and the largest of S, W and the q x q matrix as two fp16 planes).
+ *   workspace_dev: device, 256-byte aligned, >= dbf_admm_prepare_workspace_bytes(p, q, r) bytes (the inverses of two
+ *          diagonal blocks, S as fp16, the largest of S, W and a q x q matrix as two fp16 planes, and that matrix's once more:
+ *          without the last, two planes of whole blocks of 128, a workspace is taken as well, and C is made before the
+ *          factorisation instead of beside it).
  *   not_positive_definite_dev: device int (4-byte aligned) or NULL: set to the number of diagonal blocks whose
  *          factorisation met a non-positive pivot (0 = fine; with rho > 0 the matrix is positive definite and
  *          this only happens when rounding swamps rho).  Read it with an ordinary stream-ordered copy.

@@ -19,6 +19,7 @@
 #include "dbf_kernels.h"
 #include "dbf_split_gemm.h"
 
+#include <algorithm>
 #include <cmath>
 #include <utility>
 
@@ -430,10 +431,114 @@ __device__ __forceinline__ void chol_block(CholBlock& lds, uint8_t* __restrict__
     if (w < 4 && lane < 32) reinterpret_cast<float*>(planes + CH_T_UP)[32 * ib + l32] = scale.up;
 }
 
+// ---- C = B^T W beside the elimination ------------------------------------------------------------------------------------------
+// The elimination keeps a third of the compute units busy, and one of them long.  The others make C meanwhile: each launch of the elimination has further
+// workgroups, one per compute unit left, for parts of C, 128 x 128 outputs and at most CP_CHUNKS chunks of the summation index each.  A block's parts are in
+// launches one after the other, each going on from the sums that the last one left in C; all of a block's first parts come before any second one.
+struct CholBeside {
+    const uint8_t *bits, *Q;   // the signs' tiles, b . W's planes
+    const float* rs;           // of the output rows
+    float* out;
+    int M, N, K, n_ct;
+    int col0, tiles;           // first block column, how many blocks
+    int steps, parts;          // chunks to a part, parts to a block
+    int begin, count;          // of this launch's parts
+};
+constexpr int CP_CHUNKS = 8;
+constexpr int CP_AHEAD = 4;    // steps of 16 k whose operands are on their way
+// A workgroup without LDS (the ring of dbf_split_gemm.h has no place beside the elimination's): a wavefront has 64 x 32 outputs, the fragments of b . W
+// come straight from memory to registers, and those of the signs are made there: eight bytes of a tile are a lane's eight k for all of 128 rows.  The same
+// products, in the same order, as there with 256 threads.
+// Measured at p = r = 4096, q = 2048: a launch of the elimination takes 27 us with 8 chunks beside it for 22 without any (the clock of a busy chip), all sixteen
+// 424 for 360, and C in a launch of its own 130: 627 -> 554 us.  (The signs' fragments from their plane in memory: 571.  Parts of 7 chunks: the same; of 4: not all
+// of C has room.)
+__device__ __forceinline__ void chol_beside(const CholBeside& g, int index) {
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), rp = w & 1, cb = w >> 1;
+    // a compute die works on neighbouring blocks, eight rows of them at a time (dbf_split_gemm.h)
+    const int die = index & 7, per = g.count >> 3, extra = g.count & 7, id = g.begin + die * per + min(die, extra) + (index >> 3);
+    const int part = id / g.tiles, tile = id - part * g.tiles, mt = (g.M + 127) >> 7, nt = g.tiles / mt;
+    const int band = tile / (8 * nt), in_band = tile - band * 8 * nt, rows = min(8, mt - 8 * band);
+    const int it = 8 * band + in_band % rows, jt = g.col0 + in_band / rows;
+    const int chunks = (g.K + SG_CHUNK - 1) / SG_CHUNK, c0 = part * g.steps, c1 = min(chunks, c0 + g.steps);
+    if (c0 >= c1) return;
+    const SgOperand Q = sg_operand(g.Q, 2, g.K, g.N, jt, 0);
+    // (byte 256 (k / 16) + 16 (i % 16) + k % 16 of a row of tiles, bit (i % 128) / 16)
+    const uint8_t *p = g.bits + (size_t)it * g.n_ct * DBF_TILE_BYTES + 16 * (lane & 15) + 8 * h, *q = Q.frags + cb * SG_FRAG + lane * 16;
+    const int s1 = SG_CHUNK_STEPS * c1, shift = 7 - 4 * rp - (l32 >> 4);
+    uint2 a[CP_AHEAD];
+    v8h b[CP_AHEAD][2];
+    auto fetch = [&](int slot, int s) {
+        const int k = min(s, s1 - 1);
+        typedef unsigned v2u4 __attribute__((ext_vector_type(2), aligned(4)));   // (a caller's)
+        const v2u4 t = *reinterpret_cast<const v2u4*>(p + 256 * (size_t)min(k, 4 * g.n_ct - 1));   // (b . W is zero beyond the last tile)
+        a[slot] = make_uint2(t.x, t.y);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) b[slot][x] = *reinterpret_cast<const v8h*>(q + ((size_t)k * 8 + 4 * x) * SG_FRAG);
+    };
+    // a bit of bytes e and e + 1 of eight to the signs of two halves: 1 or, where it is clear, -1
+    auto signs = [&](uint2 w, int x) {
+        typedef unsigned v4u __attribute__((ext_vector_type(4)));
+        v4u o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned word = ~(e < 2 ? w.x : w.y), two = __builtin_amdgcn_perm(word, word, e & 1 ? 0x030c020cu : 0x010c000cu);
+            o[e] = ((two << (shift - 2 * x)) & 0x80008000u) | 0x3c003c00u;
+        }
+        return __builtin_bit_cast(v8h, o);
+    };
+#pragma unroll
+    for (int n = 0; n < CP_AHEAD; ++n) fetch(n, SG_CHUNK_STEPS * c0 + n);
+    const int row0 = 128 * it + 64 * rp, col = 128 * jt + 32 * cb + l32, cc = min(col, g.N - 1);
+    auto row_of = [&](int x, int v) { return row0 + 32 * x + 8 * (v >> 2) + 4 * h + (v & 3); };
+    v16f acc[2], low[2], tot[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            acc[x][v] = low[x][v] = 0.f;
+            tot[x][v] = part == 0 ? 0.f : g.out[(size_t)min(row_of(x, v), g.M - 1) * g.N + cc];
+        }
+#pragma unroll 1
+    for (int c = c0; c < c1; ++c) {
+        const float uq = Q.up[(size_t)c * Q.lines + 32 * cb + l32];
+#pragma unroll
+        for (int n = 0; n < SG_CHUNK_STEPS; ++n) {
+            const int slot = n % CP_AHEAD;
+            const v8h s[2] = {signs(a[slot], 0), signs(a[slot], 1)};
+#pragma unroll
+            for (int x = 0; x < 2; ++x) low[x] = __builtin_amdgcn_mfma_f32_32x32x16_f16(s[x], b[slot][1], low[x], 0, 0, 0);
+#pragma unroll
+            for (int x = 0; x < 2; ++x) acc[x] = __builtin_amdgcn_mfma_f32_32x32x16_f16(s[x], b[slot][0], acc[x], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(slot, SG_CHUNK_STEPS * c + n + CP_AHEAD);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                tot[x][v] = fmaf(fmaf(low[x][v], 1.f / SG_LOW, acc[x][v]), uq, tot[x][v]);
+                acc[x][v] = low[x][v] = 0.f;
+            }
+    }
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int row = row_of(x, v);
+            if (row < g.M && col < g.N) g.out[(size_t)row * g.N + col] = c1 == chunks ? tot[x][v] * g.rs[row] : tot[x][v];
+        }
+}
+
 // Diagonal block 0.
 __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_chol_first_kernel(
-    const float* __restrict__ G, int q, uint8_t* __restrict__ planes, int* __restrict__ fail) {
+    const float* __restrict__ G, int q, uint8_t* __restrict__ planes, int* __restrict__ fail, const CholBeside beside) {
     __shared__ __align__(16) CholBlock lds;
+    if (blockIdx.x > 0) {
+        chol_beside(beside, blockIdx.x - 1);
+        return;
+    }
     const int w = min(q, NB);
     float v[NB * NB / CH_THREADS];
 #pragma unroll
@@ -592,7 +697,7 @@ __device__ __forceinline__ void chol_make_block(const v8h (&t)[8][2], const floa
 template <bool MADE>
 __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_chol_row_kernel(
     float* __restrict__ G, int q, int j, const uint8_t* __restrict__ t_planes, uint8_t* __restrict__ rows, uint8_t* __restrict__ t_next,
-    int* __restrict__ fail) {
+    int* __restrict__ fail, const CholBeside beside) {
     struct Tiles {
         uint8_t g[CH_PLANES], p[CH_PLANES];
         float t_up[NB], up[2][NB];
@@ -600,6 +705,10 @@ __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     };
     __shared__ __align__(16) uint8_t lds[sizeof(Tiles) > sizeof(CholBlock) ? sizeof(Tiles) : sizeof(CholBlock)];
     Tiles& T = *reinterpret_cast<Tiles*>(lds);
+    if (blockIdx.x >= gridDim.x - beside.count) {
+        chol_beside(beside, blockIdx.x - (gridDim.x - beside.count));
+        return;
+    }
     const int nblk = (q + NB - 1) / NB;
     int i = j + 1, c = blockIdx.x;   // row i has its n - i blocks of G and j + 1 of Y
     while (c >= nblk - i + j + 1) c -= nblk - i++ + j + 1;
@@ -825,7 +934,7 @@ extern "C" int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int
 // ---- forming the constant matrices of the update on the device ---------------------------------
 namespace {
 struct PrepWorkspace {
-    size_t T, fail, S, V, total;
+    size_t T, fail, S, V, Y, least, total;   // `least`: what a call can do with: [R | Y]'s planes in the place of b . W's, nothing of C beside the elimination
     int nblk;
 };
 inline PrepWorkspace prep_workspace(int p, int q, int r) {
@@ -840,8 +949,37 @@ inline PrepWorkspace prep_workspace(int p, int q, int r) {
     v = v < sg_plane_bytes(2, p, r) ? sg_plane_bytes(2, p, r) : v;
     v = v < sg_plane_bytes(2, q, q) ? sg_plane_bytes(2, q, q) : v;
     w.V = off;     off = up256(off + v);
+    w.least = off;
+    w.Y = off;
+    if (w.nblk > 1) off = up256(off + sg_plane_bytes(2, q, q));   // those of [R | Y], while b . W's are still wanted
     w.total = off;
     return w;
+}
+// Blocks of row j's launch of the elimination: the i-th block row below has below - i blocks of G and j + 1 of Y.
+inline long long chol_blocks(int nblk, int j) {
+    const int below = nblk - 1 - j;
+    return (long long)below * (below + 1) / 2 + (long long)below * (j + 1);
+}
+// The compute units that a launch of this many workgroups leaves.
+inline long long chol_free(long long blocks) { return blocks < 256 ? 256 - blocks : 0; }
+// How much of C is made beside the elimination: as many block columns, from the last one down, as its launches have room for.
+struct CholPlan {
+    int columns, steps, parts;
+};
+inline CholPlan chol_plan(int p, int q, int r) {
+    const int nblk = (q + NB - 1) / NB, chunks = (p + SG_CHUNK - 1) / SG_CHUNK;
+    CholPlan plan;
+    plan.parts = (chunks + CP_CHUNKS - 1) / CP_CHUNKS;
+    plan.steps = (chunks + plan.parts - 1) / plan.parts;
+    auto room = [&](long long tiles) {   // (a launch has one part of a block at most)
+        long long n = std::min(tiles, chol_free(1));
+        for (int j = 0; j + 1 < nblk; ++j) n += std::min(tiles, chol_free(chol_blocks(nblk, j)));
+        return n;
+    };
+    long long columns = std::min((long long)(r + 127) / 128, room(1 << 30) / ((long long)nblk * plan.parts));
+    while (columns > 0 && room(columns * nblk) < columns * nblk * plan.parts) --columns;
+    plan.columns = (int)columns;
+    return plan;
 }
 }  // namespace
 
@@ -860,7 +998,7 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
     for (const void* ptr : ptrs)
         if (reinterpret_cast<uintptr_t>(ptr) & 3) return DBF_EINVAL;
     const PrepWorkspace w = prep_workspace(p, q, r);
-    if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < w.total)
+    if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < w.least)
         return DBF_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     uint8_t* base = static_cast<uint8_t*>(workspace_dev);
@@ -869,7 +1007,8 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
     const uint8_t* bits = static_cast<const uint8_t*>(bits_dev);
     const float* m2 = static_cast<const float*>(m2_dev);
     const float* b = static_cast<const float*>(b_dev);
-    const int n_ct = dbf_col_tiles(p);
+    const int n_ct = dbf_col_tiles(p), nt = (r + 127) / 128;
+    const CholPlan plan = w.nblk > 1 && workspace_bytes >= w.total ? chol_plan(p, q, r) : CholPlan{0, 0, 0};
 
     uint8_t *S = base + w.S, *V = base + w.V;
     // G = B^T B + rho I with B[l][j] = b_l S[j][l] m2_j: the signs against the signs times b^2, m2 by output row and column in
@@ -888,25 +1027,34 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
         SplitGemmArgs g = {};
         g.P = S;  g.Q = V;  g.out = static_cast<float*>(C_dev);  g.ldo = r;  g.M = q;  g.N = r;  g.K = p;
         g.rs = m2;
-        launch_split_gemm<1>(g, st);
+        if (plan.columns < nt) launch_split_gemm<1>(g, st, nt - plan.columns);
     }
-    // [G | I] -> [R | Y], the planes of Y in V
-    uint8_t* T[2] = {base + w.T, base + w.T + CH_PLANES};
-    hipLaunchKernelGGL(dbf_chol_first_kernel, dim3(1), dim3(CH_THREADS), 0, st, G, q, T[0], fail);
+    // [G | I] -> [R | Y], the planes of Y in V, or beside what the rest of C is made of
+    uint8_t *T[2] = {base + w.T, base + w.T + CH_PLANES}, *Y = plan.columns ? base + w.Y : V;
+    CholBeside beside = {bits, V, m2, static_cast<float*>(C_dev), q, r, p, n_ct, nt - plan.columns, plan.columns * ((q + 127) / 128), plan.steps, plan.parts, 0, 0};
+    auto besides = [&](long long blocks) {   // this launch's parts
+        beside.begin += beside.count;
+        beside.count = (int)std::min((long long)beside.tiles * beside.parts - beside.begin, std::min((long long)beside.tiles, chol_free(blocks)));
+        return beside;
+    };
+    besides(1);
+    hipLaunchKernelGGL(dbf_chol_first_kernel, dim3(1 + beside.count), dim3(CH_THREADS), 0, st, G, q, T[0], fail, beside);
     for (int j = 0; j < w.nblk; ++j) {
-        const int below = w.nblk - 1 - j;   // block rows; the i-th of them has below - i blocks of G and j + 1 of Y
-        const long long blocks = (long long)below * (below + 1) / 2 + (long long)below * (j + 1);
+        const int below = w.nblk - 1 - j;
+        const long long blocks = chol_blocks(w.nblk, j);
         const bool made = below == 0 || blocks > CH_MADE;
-        if (made) hipLaunchKernelGGL(dbf_chol_panel_kernel, dim3(w.nblk), dim3(CH_THREADS), 0, st, G, q, j, T[j & 1], V);
-        if (below > 0)
-            hipLaunchKernelGGL(made ? dbf_chol_row_kernel<true> : dbf_chol_row_kernel<false>, dim3((unsigned)blocks), dim3(CH_THREADS), 0, st, G, q, j, T[j & 1], V,
-                               T[~j & 1], fail);
+        if (made) hipLaunchKernelGGL(dbf_chol_panel_kernel, dim3(w.nblk), dim3(CH_THREADS), 0, st, G, q, j, T[j & 1], Y);
+        if (below > 0) {
+            besides(blocks);
+            hipLaunchKernelGGL(made ? dbf_chol_row_kernel<true> : dbf_chol_row_kernel<false>, dim3((unsigned)(blocks + beside.count)), dim3(CH_THREADS), 0, st, G, q,
+                               j, T[j & 1], Y, T[~j & 1], fail, beside);
+        }
     }
     // G^-1 = Y^T Y (overwrites G): upper blocks, the sums starting where both operands can be non-zero,
     // then the mirror image
     {
         SplitGemmArgs g = {};
-        g.P = V;  g.Q = V;  g.out = G;  g.ldo = q;  g.M = q;  g.N = q;  g.K = q;
+        g.P = Y;  g.Q = Y;  g.out = G;  g.ldo = q;  g.M = q;  g.N = q;  g.K = q;
         g.upper = 1;  g.ktri = 1;
         launch_split_gemm<2>(g, st);
         hipLaunchKernelGGL(dbf_chol_mirror_kernel, dim3((q + 31) / 32, (q + 31) / 32), dim3(256), 0, st, G, q);

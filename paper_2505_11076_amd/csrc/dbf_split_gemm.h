@@ -480,9 +480,10 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
 // 3712 (435) 1063 / 1054 / 1062 / 1085, 4096 (528) 1166 / 1149 / 1155 / 1180.
 // (Blocks of the upper triangle go to the compute dies as they come, column by column, not in bands as the full grid's: for B^T B, q = 2048, p = 4096,
 // 29 % of the reads hit L2, where the banded launches have 79 to 84 %.  A banded order of the triangle has not been measured.)
+// (`columns`: only the first so many blocks of each row.)
 template <int PA>
-inline void launch_split_gemm(const SplitGemmArgs& g, hipStream_t st) {
-    const int mt = (g.M + 127) / 128, nt = (g.N + 127) / 128;
+inline void launch_split_gemm(const SplitGemmArgs& g, hipStream_t st, int columns = 1 << 30) {
+    const int mt = (g.M + 127) / 128, all = (g.N + 127) / 128, nt = columns < all ? columns : all;
     const long long blocks = g.upper ? (long long)mt * (mt + 1) / 2 : (long long)mt * nt;
     auto grid = [&](int bi) { return g.upper ? dim3((unsigned)(blocks * (2 / bi))) : dim3(bi == 2 ? mt : (g.M + 63) / 64, nt); };
     if (blocks <= 128 || (g.ktri && blocks <= 320))

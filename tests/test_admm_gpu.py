@@ -153,7 +153,7 @@ class PackedProblem:
         self.S_B, self.m2, self.b, self.W, self.S, self.a, self.m, self.U = I.make_admm_packed_problem(p, q, r, seed)
         self.B_dense = O.fixed_factor_dense(self.S_B, self.b, self.m2)
 
-    def prepare_on_device(self, rho):
+    def prepare_on_device(self, rho, less=0):
         p, q, r = self.p, self.q, self.r
         tiled = B.dbf_tile_host(q, p, O.pack_signs(self.S_B.astype(np.float64)))
         bits = torch.from_numpy(tiled.copy()).cuda()
@@ -161,7 +161,7 @@ class PackedProblem:
         Minv = torch.full((q, q), float("nan"), dtype=torch.float32, device="cuda")
         Cm = torch.full((q, r), float("nan"), dtype=torch.float32, device="cuda")
         flag = torch.full((1,), 77, dtype=torch.int32, device="cuda")
-        wsb = B.dbf_admm_prepare_workspace_bytes(p, q, r)
+        wsb = B.dbf_admm_prepare_workspace_bytes(p, q, r) - less
         ws = torch.full((wsb,), 0xA5, dtype=torch.uint8, device="cuda")
         B.dbf_admm_prepare(bits.data_ptr(), m2.data_ptr(), b.data_ptr(), W.data_ptr(), p, q, r, rho, Minv.data_ptr(),
                            Cm.data_ptr(), ws.data_ptr(), wsb, flag.data_ptr(), G.stream_handle())
@@ -332,6 +332,19 @@ def test_admm_prepare_at_the_edges_of_the_elimination_blocks(q):
     prob = PackedProblem(60, q, 33, I.seed_for(9, 700 + q))
     Minv, Cm = prob.prepare_on_device(0.9)
     _check_constants("constants q=%d" % q, prob, 0.9, Minv, Cm)
+
+
+@pytest.mark.parametrize("p,q,r", [(2100, 300, 1000), (1100, 200, 16600), (700, 520, 516)])
+def test_admm_prepare_with_parts_of_C_beside_the_elimination(p, q, r):
+    """C in three parts a block, in two with more block columns than there is room for, in one; and with the workspace that a call can do with, without the planes
+    of Y (two pieces of q x q in whole blocks of 128, four bytes a line and block): the same without parts.  Gates: as above."""
+    prob = PackedProblem(p, q, r, I.seed_for(9, 800 + p + q))
+    n = (q + 127) // 128
+    for less in (0, 256, n * n * 65536 + 512 * n * n):
+        Minv, Cm = prob.prepare_on_device(0.9, less)
+        _check_constants("constants p=%d q=%d r=%d, %d bytes less" % (p, q, r, less), prob, 0.9, Minv, Cm)
+    with pytest.raises(B.DbfError):
+        prob.prepare_on_device(0.9, less + 256)
 
 
 @pytest.mark.parametrize("p,q,r", [(100, 70, 90), (520, 300, 260)])
