@@ -901,7 +901,7 @@ extern "C" int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int
     for (const void* p : ptrs)
         if (reinterpret_cast<uintptr_t>(p) & 3) return DBF_EINVAL;
     const AdmmWorkspace w = admm_workspace(q, r);
-    if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < w.total)
+    if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < w.svid + dbf_svid_least_workspace(q, r))
         return DBF_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     uint8_t* base = static_cast<uint8_t*>(workspace_dev);

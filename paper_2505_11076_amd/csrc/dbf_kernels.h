@@ -71,4 +71,7 @@ hipError_t dbf_gemm_i8_launch(const dbf_layer* L, const void* X_dev, void* Y_dev
 // each < src->k).  Queued on `stream`.
 hipError_t dbf_prune_launch(const dbf_layer* src, dbf_layer* dst, const int* keep_dev, int n_keep, hipStream_t stream);
 
+// What dbf_svid can do with (a launch per round); dbf_svid_workspace_bytes is that or more.
+size_t dbf_svid_least_workspace(int rows, int cols);
+
 #endif  // DBF_KERNELS_H

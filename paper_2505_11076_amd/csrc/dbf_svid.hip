@@ -24,8 +24,11 @@
 //                order), partial sums per 64-row chunk, then summed over the chunks in a fixed order;
 //   norms        partial sums of squares per 32 or 64 columns (v) or per thread stride (u), combined in a fixed tree;
 //   signs        one workgroup per 128 x 64 tile, a thread per four bytes of the tile.
+// And where Z has room in the registers of the whole device and the rounds are several, one launch does all of them (dbf_svid_held_kernel).
 #include "dbf_kernels.h"
 #include "dbf_wave.h"
+
+#include <type_traits>
 
 namespace {
 
@@ -413,6 +416,362 @@ __global__ __launch_bounds__(256) void dbf_svid_signs_kernel(const float* __rest
     reinterpret_cast<unsigned*>(bits + ((size_t)blockIdx.y * n_ct + blockIdx.x) * DBF_TILE_BYTES)[t] = out;
 }
 
+// ---- all rounds in one launch -------------------------------------------------------------------------------------------
+// Z held in registers from round to round: 256 compute units have 128 MB of them.  The rows are cut into parts, G groups of eight rows each (the groups of
+// the one-pass round), a part to a workgroup of 512 threads, one workgroup to a compute unit.  A round: every workgroup forms its rows' dots with v and its
+// partial column sums, as there, and writes the sums to memory; each then adds up some columns of all parts, in 64 bits, and publishes
+// their v; when it has every column, a workgroup goes on to the next round.
+// What passes between workgroups is written through to memory and read from there (agent scope).  All of it is sums of magnitudes, so the sign is free to tell
+// a round from the one before: words of round i (from 1) have the sign i % 2, all are +0 to begin with, and a word is written again only
+// when everyone has read it (who writes sums of round i + 1 has all of v of round i, which nobody publishes without all the sums of round i; who publishes v of
+// round i + 1 has everyone's sums of that round, which nobody forms without v of round i).  So a reader polls the values themselves, and a step from
+// workgroup to workgroup is one way to memory and one back.  (With a flag behind the values: 13.6 us a round of 4096 x 4096.)
+// Who is there: a workgroup takes a ticket and clears its words, and goes on when all have; the last ticket closes the door.  If others keep the device busy, the first one closes it
+// after HELD_WAIT_US: workgroups that come later leave at once, and those inside share out the parts among them, reading Z anew for each part and round.  So
+// nobody waits for a workgroup that is not running, and the sums are the same, bit for bit, whoever made them: their order is that of the parts.
+// What bounds it: those steps, two a round.  At 4096 x 4096 7.7 us a round: 1.3 of arithmetic, two
+// steps of 2 to 2.5, the adding up; 24 us besides, 14 of them the one read of Z.  (A launch a round: 13.9 for the read from the last-level cache, 4.1 for the
+// reduction.)
+constexpr int HELD_THREADS = 512, HELD_WAVES = HELD_THREADS / 64;
+constexpr int HELD_PARTS = 256;
+constexpr unsigned HELD_CLOSED = 0x80000000u;
+constexpr int HELD_WAIT_US = 50;                    // (DBF_TUNE_WAIT_LIMIT_US where that is less)
+constexpr int HELD_SPINS = 1 << 21;                 // (seconds: a wait this long is a mistake; it ends, and the factors are no numbers)
+struct HeldSync {                                   // cleared before the launch
+    unsigned state, inside, cleared, pad[61];
+};
+struct HeldArgs {
+    const float* Z;
+    float *u, *partial, *a, *m;
+    HeldSync* sync;
+    float* v;                                       // [cols]: v_raw as published
+    double* ss;                                     // [part]: squared length of its part of u
+    uint8_t* bits;
+    int rows, cols, iters, n_parts, n_ct;
+    int lanes;                                      // a workgroup adds up 4 << lanes columns at a time
+    unsigned wait_ticks;                            // of the constant clock, 100 MHz
+};
+template <class T>
+__device__ __forceinline__ T held_load(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <class T>
+__device__ __forceinline__ void held_store(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+// 16 bytes, written through to memory and read from there (the policy of an agent-scope access)
+constexpr int HELD_MEMORY = 16;   // sc1
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t held_buffer(const void* p, size_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)std::min(bytes, (size_t)0x7fffffff), 0x00020000);
+}
+__device__ __forceinline__ v4f held_load4(__amdgpu_buffer_rsrc_t b, unsigned at) {
+    return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(b, at, 0, HELD_MEMORY));
+}
+__device__ __forceinline__ void held_store4(__amdgpu_buffer_rsrc_t b, unsigned at, v4f v) {
+    typedef unsigned v4u __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), b, at, 0, HELD_MEMORY);
+}
+
+__global__ __launch_bounds__(256) void dbf_svid_clear_kernel(unsigned long long* __restrict__ words, int n) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) words[i] = 0;
+}
+
+// v plus what other lanes hold of it: all whose number is the same modulo 2^LANES, register to register.
+template <int CTRL>
+__device__ __forceinline__ double held_dpp(double v) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    return __builtin_bit_cast(double, (unsigned long long)(unsigned)dbf_dpp_move<CTRL>((int)b) | (unsigned long long)(unsigned)dbf_dpp_move<CTRL>((int)(b >> 32)) << 32);
+}
+template <int LANES>
+__device__ __forceinline__ double held_sum(double v) {
+    if (LANES <= 3) v += held_dpp<0x128>(v);   // row_ror:8
+    if (LANES <= 2) v += held_dpp<0x124>(v);   // row_ror:4
+    auto add = [](auto lo, auto hi) {
+        return __builtin_bit_cast(double, (unsigned)lo[0] | (unsigned long long)(unsigned)hi[0] << 32) +
+               __builtin_bit_cast(double, (unsigned)lo[1] | (unsigned long long)(unsigned)hi[1] << 32);
+    };
+    unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+    v = add(__builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false), __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false));
+    b = __builtin_bit_cast(unsigned long long, v);
+    return add(__builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false), __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false));
+}
+
+template <int CPL, int G>
+__global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_svid_held_kernel(const HeldArgs A) {
+    __shared__ float dots[8 * G][HELD_WAVES];
+    __shared__ float us[8 * G];
+    __shared__ float lengths[HELD_WAVES];
+    __shared__ double sums[HELD_WAVES][64], total[2];
+    __shared__ int enter[2];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rows = A.rows, cols = A.cols, n_parts = A.n_parts;
+    HeldSync* const sync = A.sync;
+    v4f z[8 * G][CPL], v[CPL], acc[CPL];
+    auto col_of = [&](int k) { return 4 * tid + 4 * HELD_THREADS * k; };
+    auto live = [&](int k) { return col_of(k) < cols; };   // (cols is a multiple of 4)
+    auto row_of = [&](int part, int r) {
+        const int g = part * G + (r >> 3);
+        return 128 * (g >> 4) + 16 * (r & 7) + (g & 15);
+    };
+    auto load_part = [&](int part) {   // (rows and columns beyond the matrix: others in their place, no branch around a load)
+#pragma unroll
+        for (int r = 0; r < 8 * G; ++r) {
+            const float* zr = A.Z + (size_t)min(row_of(part, r), rows - 1) * cols;
+#pragma unroll
+            for (int k = 0; k < CPL; ++k) z[r][k] = *reinterpret_cast<const v4f*>(zr + (live(k) ? col_of(k) : 0));
+        }
+    };
+    const int chunk_cols = 4 << A.lanes, n_chunks = (cols + chunk_cols - 1) / chunk_cols;
+    const auto partial_of = [&](int part) { return held_buffer(A.partial + (size_t)part * cols, 4 * (size_t)cols); };
+    const auto v_buffer = held_buffer(A.v, 4 * (size_t)cols);
+    bool lost = false;   // (a wait has not ended)
+    // One wavefront clears a part's words and those of every step-th chunk from there on, and when they are in memory and `times` that many have come from
+    // everyone inside, it has the number of these; 0 if the door was closed before (nothing may be touched then).
+    auto clear = [&](int part, int step) {
+        const v4f zero = {0.f, 0.f, 0.f, 0.f};
+        for (int col = 4 * lane; col < cols; col += 256) held_store4(partial_of(part), 4 * (unsigned)col, zero);
+        for (int chunk = part; chunk < n_chunks; chunk += step)
+            if (4 * lane < chunk_cols) held_store4(v_buffer, 4 * (unsigned)(chunk * chunk_cols + 4 * lane), zero);   // (nothing beyond the last column)
+        if (lane == 0) held_store(reinterpret_cast<unsigned long long*>(A.ss + part), 0ull);
+    };
+    auto all_cleared = [&](int ticket, int times) {
+        __builtin_amdgcn_s_waitcnt(0);
+        int n = 0;
+        if (lane == 0) {
+            auto close = [&] {
+                const unsigned old = __hip_atomic_fetch_or(&sync->state, HELD_CLOSED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!(old & HELD_CLOSED)) held_store(&sync->inside, old);
+            };
+            __hip_atomic_fetch_add(&sync->cleared, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (ticket == (int)gridDim.x - 1) close();
+            const unsigned long long t0 = wall_clock64();
+            for (int spin = 0; spin < HELD_SPINS; ++spin) {
+                n = (int)held_load(&sync->inside);
+                if (n > 0 && held_load(&sync->cleared) >= (unsigned)(n * times)) break;
+                if (n == 0 && ticket == 0 && wall_clock64() - t0 >= A.wait_ticks) close();
+            }
+        }
+        return __builtin_amdgcn_readfirstlane(n);
+    };
+    if (w == 0) {   // (before its loads of Z, or every answer would come behind them)
+        int mine = 0, n = 0;
+        if (lane == 0) mine = (int)__hip_atomic_fetch_add(&sync->state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mine = __builtin_amdgcn_readfirstlane(mine);
+        if (mine >= 0) {   // (HELD_CLOSED is the sign)
+            clear(blockIdx.x, n_parts);
+            n = all_cleared(mine, 1);
+            if (n > 0 && n < n_parts) {   // the parts and columns of those outside
+                for (int part = mine; part < n_parts; part += n) clear(part, n);
+                all_cleared(mine, 2);
+            }
+        }
+        if (lane == 0) {
+            enter[0] = mine;
+            enter[1] = n;
+        }
+    }
+    load_part(blockIdx.x);
+    __syncthreads();
+    const int inside = __builtin_amdgcn_readfirstlane(enter[1]);
+    if (inside == 0) return;   // (too late)
+    const bool held = inside == n_parts;
+    const int ticket = held ? (int)blockIdx.x : __builtin_amdgcn_readfirstlane(enter[0]);   // (all are inside: the part that is in the registers)
+    // 16 bytes of round `it`, once they are there
+    auto await4 = [&](__amdgpu_buffer_rsrc_t b, unsigned at, int it) {
+        v4f x;
+        for (int spin = 0;; ++spin) {
+            asm volatile("" ::: "memory");   // (another load each time)
+            x = held_load4(b, at);
+            bool all = true;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float one = x[e];
+                all = all && __builtin_bit_cast(unsigned, one) >> 31 == (unsigned)(it & 1);
+            }
+            if (all || lost) break;
+            lost = spin > HELD_SPINS;
+        }
+        return (v4f){fabsf(x.x), fabsf(x.y), fabsf(x.z), fabsf(x.w)};
+    };
+    auto of_round = [](float x, int it) { return __builtin_bit_cast(float, (__builtin_bit_cast(unsigned, x) & 0x7fffffffu) | (unsigned)it << 31); };
+    // this thread's columns of v as of round `it` (from 1), and the sum of their squares to lengths[]
+    auto take_v = [&](int it) {
+        float ss = 0.f;
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) v[k] = live(k) ? await4(v_buffer, 4 * (unsigned)col_of(k), it) : (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < CPL; ++k) ss += (v[k].x * v[k].x + v[k].y * v[k].y) + (v[k].z * v[k].z + v[k].w * v[k].w);
+        ss = dbf_wave_sum_f(ss);
+        if (lane == 0) lengths[w] = ss;
+    };
+    for (int it = 0; it < A.iters; ++it) {
+        if (it > 0) take_v(it);
+        for (int part = ticket; part < n_parts; part += inside) {
+            if (!held) load_part(part);
+            if (it == 0) {
+                // the signs: a group of eight rows is a byte column of a tile
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const int group = part * G + g;
+                    if (group >= (rows + DBF_TILE_ROWS - 1) / DBF_TILE_ROWS * 16) break;
+#pragma unroll
+                    for (int k = 0; k < CPL; ++k) {
+                        unsigned out = 0;
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) {
+                            const v4f x = z[8 * g + r][k];
+                            const unsigned four = (unsigned)(x.x >= 0.f) | (unsigned)(x.y >= 0.f) << 8 | (unsigned)(x.z >= 0.f) << 16 | (unsigned)(x.w >= 0.f) << 24;
+                            out |= (live(k) && row_of(part, 8 * g + r) < rows) ? four << r : 0u;
+                        }
+                        const int col = col_of(k);
+                        if (col < A.n_ct * DBF_TILE_COLS)
+                            *reinterpret_cast<unsigned*>(A.bits + ((size_t)(group >> 4) * A.n_ct + (col >> 6)) * DBF_TILE_BYTES + 256 * ((col >> 4) & 3) +
+                                                         16 * (group & 15) + (col & 15)) = out;
+                    }
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                float part_dot[8], sum[2];
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    float d = 0.f;
+#pragma unroll
+                    for (int k = 0; k < CPL; ++k) {
+                        const v4f x = z[8 * g + r][k];
+                        if (it == 0) d += live(k) ? (fabsf(x.x) + fabsf(x.y)) + (fabsf(x.z) + fabsf(x.w)) : 0.f;
+                        else d += (fabsf(x.x) * v[k].x + fabsf(x.y) * v[k].y) + (fabsf(x.z) * v[k].z + fabsf(x.w) * v[k].w);
+                    }
+                    part_dot[r] = d;
+                }
+                wave_sums<8>(part_dot, sum);
+                if ((lane & 15) == 0) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) dots[8 * g + i + 2 * (lane >> 4)][w] = sum[i];
+                }
+            }
+            __syncthreads();
+            if (tid < 8 * G * HELD_WAVES) {
+                static_assert(HELD_WAVES == 8, "eight neighbouring lanes have a row's parts");
+                const float tot = dbf_row8_sum_f((&dots[0][0])[tid]);
+                if ((tid & 7) == 0) {
+                    float inv;
+                    if (it == 0) {
+                        inv = 1.f / sqrtf((float)cols);
+                    } else {
+                        float ss = lengths[0];
+#pragma unroll
+                        for (int i = 1; i < HELD_WAVES; ++i) ss += lengths[i];
+                        const float nrm = sqrtf(ss);
+                        inv = nrm > 0.f ? 1.f / nrm : 0.f;
+                    }
+                    const int row = row_of(part, tid >> 3);
+                    const float ur = row < rows ? tot * inv : 0.f;
+                    us[tid >> 3] = ur;
+                    if (it + 1 == A.iters && row < rows) A.u[row] = ur;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < CPL; ++k) acc[k] = (v4f){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < 8 * G; ++r) {
+                const float ur = us[r];
+#pragma unroll
+                for (int k = 0; k < CPL; ++k) {
+                    const v4f x = z[r][k];
+                    acc[k].x += fabsf(x.x) * ur;  acc[k].y += fabsf(x.y) * ur;  acc[k].z += fabsf(x.z) * ur;  acc[k].w += fabsf(x.w) * ur;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < CPL; ++k) {
+                const v4f out = {of_round(acc[k].x, it + 1), of_round(acc[k].y, it + 1), of_round(acc[k].z, it + 1), of_round(acc[k].w, it + 1)};
+                held_store4(partial_of(part), 4 * (unsigned)col_of(k), out);   // (nothing beyond the last column)
+            }
+            if (it + 1 == A.iters && w == 0) {
+                double ss = 0.;
+                if (lane < 8 * G) ss = (double)us[lane] * (double)us[lane];
+#pragma unroll
+                for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+                if (lane == 0) held_store(reinterpret_cast<unsigned long long*>(A.ss + part), __builtin_bit_cast(unsigned long long, ss) | 1ull << 63);
+            }
+        }
+        // the columns of all parts: four columns to a lane, a part to 2^LANES of them
+        auto add_up = [&](auto lanes) {
+            constexpr int LANES = decltype(lanes)::value, PER = HELD_THREADS >> LANES, COLS = 4 << LANES;
+            const auto all = held_buffer(A.partial, 4 * (size_t)cols * n_parts);
+            const int c4 = 4 * (tid & ((1 << LANES) - 1)), first = tid >> LANES;
+            for (int chunk = ticket; chunk < n_chunks; chunk += inside) {
+                const unsigned at = 4 * min((unsigned)(chunk * COLS + c4), (unsigned)cols - 4);
+                v4f p[HELD_PARTS / PER < 4 ? HELD_PARTS / PER : 4];
+                double s[4] = {0., 0., 0., 0.};
+#pragma unroll
+                for (int i = 0; i < (int)(sizeof(p) / sizeof(p[0])); ++i)
+                    p[i] = await4(all, at + 4 * (unsigned)cols * (unsigned)min(first + PER * i, n_parts - 1), it + 1);
+#pragma unroll
+                for (int i = 0; i < (int)(sizeof(p) / sizeof(p[0])); ++i)
+                    if (first + PER * i < n_parts) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) s[e] += (double)p[i][e];
+                    }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) s[e] = held_sum<LANES>(s[e]);
+                if (lane < 1 << LANES) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sums[w][c4 + e] = s[e];
+                }
+                __syncthreads();
+                if (tid < COLS && chunk * COLS + tid < cols) {
+                    double sum = sums[0][tid];
+#pragma unroll
+                    for (int i = 1; i < HELD_WAVES; ++i) sum += sums[i][tid];
+                    held_store(A.v + chunk * COLS + tid, of_round((float)sum, it + 1));
+                }
+                __syncthreads();
+            }
+        };
+        if (A.lanes == 2) add_up(std::integral_constant<int, 2>());
+        else if (A.lanes == 3) add_up(std::integral_constant<int, 3>());
+        else add_up(std::integral_constant<int, 4>());
+    }
+    // both lengths, in 64 bits; m = v_raw / ||v_raw|| and a = u_raw ||v_raw|| / ||u_raw||^2
+    take_v(A.iters);
+    double s[2] = {0., 0.};
+#pragma unroll
+    for (int k = 0; k < CPL; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[1] += (double)v[k][e] * (double)v[k][e];
+    if (tid < n_parts) {
+        unsigned long long ss = 0;
+        for (int spin = 0; !(ss = held_load(reinterpret_cast<const unsigned long long*>(A.ss + tid))) && !lost; ++spin) lost = spin > HELD_SPINS;
+        s[0] = __builtin_bit_cast(double, ss & ~(1ull << 63));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) s[i] += __shfl_xor(s[i], off, 64);
+        if (lane == 0) sums[w][i] = s[i];
+    }
+    __syncthreads();
+    if (tid < 2) {
+        double sum = sums[0][tid];
+#pragma unroll
+        for (int i = 1; i < HELD_WAVES; ++i) sum += sums[i][tid];
+        total[tid] = sum;
+    }
+    __syncthreads();
+    const double ssu = total[0], nv = lost ? __builtin_nan("") : sqrt(total[1]);
+#pragma unroll
+    for (int k = 0; k < CPL; ++k)
+        if (live(k) && (col_of(k) / chunk_cols) % inside == ticket) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) A.m[col_of(k) + e] = nv != 0. ? (float)(v[k][e] / nv) : v[k][e];
+        }
+    for (int part = ticket; part < n_parts; part += inside)
+        if (tid < 8 * G && row_of(part, tid) < rows) {
+            const int row = row_of(part, tid);
+            A.a[row] = ssu != 0. ? (float)(A.u[row] * (nv / ssu)) : 0.f;   // (written by this workgroup)
+        }
+}
+
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 // Groups of eight rows per workgroup of the one-pass round.
 inline int round_groups_per_wg(int rows) { return (16 * dbf_row_tiles(rows) + ROUND_WGS - 1) / ROUND_WGS; }
@@ -433,8 +792,21 @@ int launch_round(bool first, hipStream_t st, const RoundArgs& a) {
                            a.n_ss, a.u, a.partial, per, n_groups, a.bits, a.n_ct);
     return n_wg;
 }
+// Whether the rounds run in one launch: groups of eight rows per part, or 0.  (16-byte pieces; at most 192 values a thread, 160
+// of long rows.  Less than 64 K entries: too little for a workgroup on each of a few compute units.)
+inline int held_cpl(int cols) { return (cols + 4 * HELD_THREADS - 1) / (4 * HELD_THREADS); }
+inline int held_groups(int rows, int cols) {
+    if ((cols & 3) || (long long)rows * cols < 1 << 16 || cols > 24576 || rows > 1 << 15) return 0;
+    const int per = (16 * dbf_row_tiles(rows) + HELD_PARTS - 1) / HELD_PARTS, cpl = held_cpl(cols);
+    if (per * cpl > (cpl > 3 ? 5 : 6)) return 0;
+    return cpl == 1 && per == 5 ? 6 : per;
+}
+// From how many rounds on one launch is the faster: its head and end cost more than two or three launches, its rounds less.  us, a launch a
+// round / one launch: 4096 x 4096 3 rounds 53.6 / 47.1, 8 134.6 / 84.1; 2048 x 6144 3 52.8 / 47.4; 3072 x 4000 3 41.8 / 42.8; 3000 x 2048 4 33.7 / 36.0; 768 x 768
+// 6 40.0 / 33.0; 1500 x 4000 6 56.9 / 56.0; 4000 x 900 6 45.9 / 42.8.
+inline int held_rounds(int rows, int cols) { return (long long)rows * cols >= 12 << 20 ? 3 : 6; }
 struct SvidWorkspace {
-    size_t u, v, partial, scalars, total;
+    size_t u, v, partial, scalars, least, sync, ss, total;   // `least`: what a call can do with, a launch per round
 };
 inline SvidWorkspace svid_workspace(int rows, int cols) {
     SvidWorkspace w;
@@ -446,8 +818,41 @@ inline SvidWorkspace svid_workspace(int rows, int cols) {
     w.v = off;        off = up256(off + 4 * (size_t)cols);
     w.partial = off;  off = up256(off + 4 * chunks * (size_t)cols);
     w.scalars = off;  off = up256(off + 4 * (((size_t)cols + reduce_cols(cols) - 1) / reduce_cols(cols)));   // squared length of v_raw per workgroup of the column reduction
+    w.least = off;
+    w.sync = w.ss = off;
+    if (held_groups(rows, cols)) {
+        off = up256(off + sizeof(HeldSync));
+        w.ss = off;  off = up256(off + sizeof(double) * HELD_PARTS);
+    }
     w.total = off;
     return w;
+}
+template <int CPL, int G>
+void launch_held(HeldArgs a, hipStream_t st) {
+    a.n_parts = (16 * dbf_row_tiles(a.rows) + G - 1) / G;
+    const int n_words = (int)(sizeof(HeldSync) / 8), limit = dbf_tune(DBF_TUNE_WAIT_LIMIT_US);
+    // 16 or 32 columns to a workgroup at a time, 64 if there are no more than 128 parts: all at once where that does it
+    auto chunks = [&](int lanes) { return (a.cols + (4 << lanes) - 1) / (4 << lanes); };
+    a.lanes = chunks(2) <= a.n_parts ? 2 : chunks(3) <= a.n_parts || a.n_parts > 128 ? 3 : 4;
+    a.wait_ticks = 100u * (unsigned)(limit < HELD_WAIT_US ? limit : HELD_WAIT_US);
+    hipLaunchKernelGGL(dbf_svid_clear_kernel, dim3((n_words + 255) / 256), dim3(256), 0, st, reinterpret_cast<unsigned long long*>(a.sync), n_words);
+    hipLaunchKernelGGL((dbf_svid_held_kernel<CPL, G>), dim3(a.n_parts), dim3(HELD_THREADS), 0, st, a);
+}
+void launch_held_any(int groups, const HeldArgs& a, hipStream_t st) {
+    switch (10 * held_cpl(a.cols) + groups) {
+        case 11: return launch_held<1, 1>(a, st);
+        case 12: return launch_held<1, 2>(a, st);
+        case 13: return launch_held<1, 3>(a, st);
+        case 14: return launch_held<1, 4>(a, st);
+        case 16: return launch_held<1, 6>(a, st);
+        case 21: return launch_held<2, 1>(a, st);
+        case 22: return launch_held<2, 2>(a, st);
+        case 23: return launch_held<2, 3>(a, st);
+        case 31: return launch_held<3, 1>(a, st);
+        case 32: return launch_held<3, 2>(a, st);
+        case 41: return launch_held<4, 1>(a, st);
+        default: return launch_held<5, 1>(a, st);
+    }
 }
 
 }  // namespace
@@ -457,6 +862,8 @@ extern "C" size_t dbf_svid_workspace_bytes(int rows, int cols) {
     return svid_workspace(rows, cols).total;
 }
 
+size_t dbf_svid_least_workspace(int rows, int cols) { return svid_workspace(rows, cols).least; }
+
 extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev,
                         void* workspace_dev, size_t workspace_bytes, void* hip_stream) {
     if (!Z_dev || !a_dev || !m_dev || !bits_dev || rows < 1 || cols < 1 || iters < 1) return DBF_EINVAL;
@@ -465,7 +872,7 @@ extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* 
         (reinterpret_cast<uintptr_t>(m_dev) & 3) || (reinterpret_cast<uintptr_t>(bits_dev) & 3))
         return DBF_EINVAL;
     const SvidWorkspace w = svid_workspace(rows, cols);
-    if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < w.total)
+    if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < w.least)
         return DBF_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const float* Z = static_cast<const float*>(Z_dev);
@@ -483,6 +890,13 @@ extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* 
     // One pass per round wherever rows can be held: up to 24576 columns in 16-byte pieces, 12288 in single values.  8 rounds, us, two
     // passes / one: 4096 x 4096 247 / 157, now 134 (the row sums of a batch reduced together, 15.6 -> 13.7 us a round; 32 columns to a workgroup of
     // the reduction; the last kernel 6.7 -> 3.8); 2048 x 4096 161 / 93, now 83; 4 rounds of 8192 x 8192 262, now 252.
+    if (const int groups = held_groups(rows, cols); groups && vec_ok && iters >= held_rounds(rows, cols) && workspace_bytes >= w.total) {
+        const HeldArgs h = {Z, u, partial, static_cast<float*>(a_dev), v, reinterpret_cast<HeldSync*>(base + w.sync),
+                            reinterpret_cast<float*>(base + w.v), reinterpret_cast<double*>(base + w.ss), static_cast<uint8_t*>(bits_dev),
+                            rows, cols, iters, 0, n_ct, 0, 0};
+        launch_held_any(groups, h, st);
+        return hipGetLastError() == hipSuccess ? DBF_OK : DBF_EHIP;
+    }
     const int cpl = (cols + 4095) / 4096;  // float4s per thread and row of a workgroup of 1024
     const bool one_pass = cpl <= (vec_ok ? 6 : 3);
     if (!(one_pass && cpl == 1 && vec_ok))   // (else the first pass writes the signs)

@@ -57,6 +57,11 @@ __device__ inline float dbf_row16_sum_f(float v) {
     v += __builtin_bit_cast(float, dbf_dpp_move<0x124>(__builtin_bit_cast(int, v)));
     return v + __builtin_bit_cast(float, dbf_dpp_move<0x128>(__builtin_bit_cast(int, v)));
 }
+__device__ inline float dbf_row8_sum_f(float v) {   // of eight neighbouring lanes
+    v += __builtin_bit_cast(float, dbf_dpp_move<0xB1>(__builtin_bit_cast(int, v)));
+    v += __builtin_bit_cast(float, dbf_dpp_move<0x4E>(__builtin_bit_cast(int, v)));
+    return v + __builtin_bit_cast(float, dbf_dpp_move<0x141>(__builtin_bit_cast(int, v)));  // row_half_mirror
+}
 __device__ inline float dbf_wave_sum_f(float v) {
     v = dbf_row16_sum_f(v);
     const int b = __builtin_bit_cast(int, v);

@@ -113,3 +113,26 @@ def test_svid_at_the_edges_of_its_reductions(rows, cols):
         assert np.array_equal(words, O.pack_signs(S)), "sign bits differ"
         assert np.max(np.abs(a - a_ref)) <= TOL * np.max(np.abs(a_ref))
         assert np.max(np.abs(m - m_ref)) <= TOL * np.max(np.abs(m_ref))
+
+
+@pytest.mark.parametrize("rows,cols", [(128, 512), (2049, 2052), (4096, 2048), (6000, 1000), (8000, 900), (12000, 260), (5000, 4096), (2000, 6140),
+                                       (4000, 5000), (1000, 8192), (1500, 10240), (300, 12288)])
+def test_svid_rounds_in_one_launch(rows, cols):
+    """Six rounds and more: Z in registers, 1 to 5 float4s per thread and row, 8 to 48 rows per workgroup, 16, 32 and 64 columns added up at a time, rows too long for
+    it.  With a wait of nothing the first workgroup goes on with those that are there and they take over the others' rows: the same bits.  Tolerance: as
+    above."""
+    Z = I.make_svid_matrix(rows, cols, I.seed_for(8, 120 + rows + cols))
+    for iters in (6, 7):
+        G.say("start svid %dx%d iters=%d" % (rows, cols, iters))
+        S, a_ref, m_ref = O.svid(Z.astype(np.float64), iters)
+        a, m, words = _run(Z, iters)
+        assert np.array_equal(words, O.pack_signs(S)), "sign bits differ"
+        assert np.max(np.abs(a - a_ref)) <= TOL * np.max(np.abs(a_ref))
+        assert np.max(np.abs(m - m_ref)) <= TOL * np.max(np.abs(m_ref))
+        try:
+            B.dbf_tuning_set(B.TUNE_WAIT_LIMIT_US, 0)
+            G.say("  nobody waited for")
+            a0, m0, words0 = _run(Z, iters)
+        finally:
+            B.dbf_tuning_reset()
+        assert np.array_equal(a, a0) and np.array_equal(m, m0) and np.array_equal(words, words0)
