@@ -577,8 +577,9 @@ LayerOffsets layer_offsets(int n_in, int n_out, int k) {
 // Makes a layer of the given shape on the current device: ONE allocation that holds its signs and vectors (left to the caller to fill),
 // the zeroed memory of its launch plan, its scratch, and the plan's tables.  `extra_bytes` from `extra` (4 k at most) go up with the
 // tables, to *extra_dev in the end of the scratch: there until the layer's first call.
-// Everything is queued on the null stream; the rest of the scratch is zeroed there.
-int create_layer(int n_in, int n_out, int k, const LayerOffsets& o, const void* extra, size_t extra_bytes, void** extra_dev, dbf_layer** out) {
+// Everything is queued on the null stream; the rest of the scratch is zeroed there, or, with `clear`, left to the caller: `clear_bytes` from there on.
+int create_layer(int n_in, int n_out, int k, const LayerOffsets& o, const void* extra, size_t extra_bytes, void** extra_dev, void** clear, size_t* clear_bytes,
+                 dbf_layer** out) {
     dbf_layer* L = new (std::nothrow) dbf_layer();
     if (!L) return DBF_ENOMEM;
     DbfStage& sb = L->h_stages[0];
@@ -622,7 +623,12 @@ int create_layer(int n_in, int n_out, int k, const LayerOffsets& o, const void* 
         const std::vector<uint8_t> tables = place_plan(draft, d + o_tables, d + o_zero, shift, shift + draft.zero_bytes, &L->plan);
         image.insert(image.end(), tables.begin(), tables.end());
         if (extra_dev) *extra_dev = d + o_tables - upload;
-        e = hipMemsetAsync(d + o_zero, 0, o_tables - upload - o_zero, nullptr);
+        if (clear) {
+            *clear = d + o_zero;
+            *clear_bytes = o_tables - upload - o_zero;
+        } else {
+            e = hipMemsetAsync(d + o_zero, 0, o_tables - upload - o_zero, nullptr);
+        }
         if (e == hipSuccess) e = hipMemcpy(d + o_tables - upload, image.data(), image.size(), hipMemcpyHostToDevice);
     }
     if (e != hipSuccess) {
@@ -660,7 +666,7 @@ int build_layer(int n_in, int n_out, int k, const uint32_t* A_bits, const uint32
     std::memcpy(image + o.b, b, 2 * (size_t)n_in);
 
     dbf_layer* L = nullptr;
-    rc = create_layer(n_in, n_out, k, o, nullptr, 0, nullptr, &L);
+    rc = create_layer(n_in, n_out, k, o, nullptr, 0, nullptr, nullptr, nullptr, &L);
     if (rc != DBF_OK) {
         std::free(image);
         return rc;
@@ -923,10 +929,11 @@ int dbf_prune_middle(const dbf_layer* L, const int32_t* keep, int n_keep, dbf_la
 
     dbf_layer* N = nullptr;
     const LayerOffsets o = layer_offsets(L->n_in, L->n_out, n_keep);
-    void* keep_dev = nullptr;
-    const int rc = create_layer(L->n_in, L->n_out, n_keep, o, keep, sizeof(int) * (size_t)n_keep, &keep_dev, &N);
+    void *keep_dev = nullptr, *clear = nullptr;
+    size_t clear_bytes = 0;
+    const int rc = create_layer(L->n_in, L->n_out, n_keep, o, keep, sizeof(int) * (size_t)n_keep, &keep_dev, &clear, &clear_bytes, &N);
     if (rc != DBF_OK) return rc;
-    hipError_t e = dbf_prune_launch(L, N, static_cast<const int*>(keep_dev), n_keep, nullptr);
+    hipError_t e = dbf_prune_launch(L, N, static_cast<const int*>(keep_dev), n_keep, clear, clear_bytes, nullptr);
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         (void)hipGetLastError();

@@ -68,8 +68,8 @@ hipError_t dbf_gemm_i8_launch(const dbf_layer* L, const void* X_dev, void* Y_dev
 
 // Middle-channel pruning: fills the sign tiles and vectors of `dst` (a freshly created layer with
 // k = n_keep on the same device) from `src` and the kept middle indices keep_dev (device, increasing,
-// each < src->k).  Queued on `stream`.
-hipError_t dbf_prune_launch(const dbf_layer* src, dbf_layer* dst, const int* keep_dev, int n_keep, hipStream_t stream);
+// each < src->k), and zeroes clear_bytes from `clear` on (multiples of 16).  Queued on `stream`.
+hipError_t dbf_prune_launch(const dbf_layer* src, dbf_layer* dst, const int* keep_dev, int n_keep, void* clear, size_t clear_bytes, hipStream_t stream);
 
 // What dbf_svid can do with (a launch per round); dbf_svid_workspace_bytes is that or more.
 size_t dbf_svid_least_workspace(int rows, int cols);
