@@ -93,7 +93,8 @@ __global__ __launch_bounds__(256) void dbf_admm_operands_kernel(const float* __r
                                                                const uint8_t* __restrict__ bits, int q, int r, int n_ct,
                                                                uint8_t* __restrict__ planes) {
     if ((int)blockIdx.y < q_blocks) {
-        sg_split_dense<true>(Minv, q, q, q, nullptr, Minv_planes, blockIdx.y);
+        __shared__ float part[4][32];
+        sg_split_dense<true>(Minv, q, q, q, nullptr, Minv_planes, blockIdx.y, blockIdx.x, threadIdx.x, part);
         return;
     }
     const SgSite s = sg_site(q, 2, blockIdx.y - q_blocks);
@@ -851,24 +852,6 @@ __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     chol_make_block(t, t_up, g, nullptr, nullptr, s, rows, q, j, c);
 }
 
-// M[j][i] = M[i][j] for i < j: the lower triangle of a symmetric matrix whose upper blocks were computed.
-// One workgroup per 32 x 32 block on or above the diagonal, through LDS so that both sides are coalesced.
-__global__ __launch_bounds__(256) void dbf_chol_mirror_kernel(float* __restrict__ M, int q) {
-    __shared__ float t[32][33];
-    const int bi = blockIdx.y, bj = blockIdx.x;
-    if (bi > bj) return;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int rr = ty; rr < 32; rr += 8) {
-        const int i = 32 * bi + rr, j = 32 * bj + tx;
-        t[rr][tx] = (i < q && j < q) ? M[(size_t)i * q + j] : 0.f;
-    }
-    __syncthreads();
-    for (int rr = ty; rr < 32; rr += 8) {
-        const int j = 32 * bj + rr, i = 32 * bi + tx;   // writes M[j][i] = t[i - 32 bi][j - 32 bj]
-        if (i < q && j < q && i < j) M[(size_t)j * q + i] = t[tx][rr];
-    }
-}
-
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 struct AdmmWorkspace {
     size_t P, R, Z, svid, total;
@@ -934,7 +917,7 @@ extern "C" int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int
 // ---- forming the constant matrices of the update on the device ---------------------------------
 namespace {
 struct PrepWorkspace {
-    size_t T, fail, S, V, Y, least, total;   // `least`: what a call can do with: [R | Y]'s planes in the place of b . W's, nothing of C beside the elimination
+    size_t T, fail, S, V, Y, least, total;   // `least`: what a call can do with: all of V's contents one after the other, nothing of C beside other work
     int nblk;
 };
 inline PrepWorkspace prep_workspace(int p, int q, int r) {
@@ -950,8 +933,8 @@ inline PrepWorkspace prep_workspace(int p, int q, int r) {
     v = v < sg_plane_bytes(2, q, q) ? sg_plane_bytes(2, q, q) : v;
     w.V = off;     off = up256(off + v);
     w.least = off;
-    w.Y = off;
-    if (w.nblk > 1) off = up256(off + sg_plane_bytes(2, q, q));   // those of [R | Y], while b . W's are still wanted
+    w.Y = off;   // those of the scaled signs and then of [R | Y], apart from b . W's
+    if (w.nblk > 1) off = up256(off + std::max(sg_plane_bytes(2, p, q), sg_plane_bytes(2, q, q)));
     w.total = off;
     return w;
 }
@@ -1008,26 +991,28 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
     const float* m2 = static_cast<const float*>(m2_dev);
     const float* b = static_cast<const float*>(b_dev);
     const int n_ct = dbf_col_tiles(p), nt = (r + 127) / 128;
-    const CholPlan plan = w.nblk > 1 && workspace_bytes >= w.total ? chol_plan(p, q, r) : CholPlan{0, 0, 0};
+    const bool roomy = w.nblk > 1 && workspace_bytes >= w.total;
+    const CholPlan plan = roomy ? chol_plan(p, q, r) : CholPlan{0, 0, 0};
 
     uint8_t *S = base + w.S, *V = base + w.V;
     // G = B^T B + rho I with B[l][j] = b_l S[j][l] m2_j: the signs against the signs times b^2, m2 by output row and column in
-    // the epilogue.  Upper blocks only.
-    hipLaunchKernelGGL(dbf_split_signs_kernel, sg_plane_grid(p, q), dim3(256), 0, st, bits, n_ct, p, q, b, S, V, fail);
-    {
-        SplitGemmArgs g = {};
-        g.P = S;  g.Q = V;  g.out = G;  g.ldo = q;  g.M = q;  g.N = q;  g.K = p;
-        g.rs = m2;  g.cs = m2;  g.diag = rho;  g.upper = 1;
-        launch_split_gemm<1>(g, st);
-    }
+    // the epilogue.  Upper blocks only.  Beside them, as far as compute units are idle, b . W's planes.
+    uint8_t* const scaled = roomy ? base + w.Y : V;
+    const SplitBesideArgs dense = {static_cast<const float*>(W_dev), b, V, (size_t)r, p, r, 0};
+    hipLaunchKernelGGL(dbf_split_signs_kernel, sg_plane_grid(p, q), dim3(256), 0, st, bits, n_ct, p, q, b, S, scaled, fail);
+    SplitGemmArgs gram = {};
+    gram.P = S;  gram.Q = scaled;  gram.out = G;  gram.ldo = q;  gram.M = q;  gram.N = q;  gram.K = p;
+    gram.rs = m2;  gram.cs = m2;  gram.diag = rho;  gram.upper = 1;
+    const int made = 2 * launch_split_gemm<1>(gram, st, 1 << 30, roomy ? &dense : nullptr);   // (times 32 lines)
+    const dim3 planes = sg_plane_grid(p, r);
+    if (made < (int)planes.y)
+        hipLaunchKernelGGL(dbf_split_dense_kernel, dim3(planes.x, planes.y - made), dim3(256), 0, st, dense.src, dense.ld, p, r, b, V, made);
     // C = B^T W: the signs against b . W
-    {
-        hipLaunchKernelGGL(dbf_split_dense_kernel, sg_plane_grid(p, r), dim3(256), 0, st, static_cast<const float*>(W_dev), (size_t)r, p, r, b,
-                           V);
+    if (plan.columns < nt) {
         SplitGemmArgs g = {};
         g.P = S;  g.Q = V;  g.out = static_cast<float*>(C_dev);  g.ldo = r;  g.M = q;  g.N = r;  g.K = p;
         g.rs = m2;
-        if (plan.columns < nt) launch_split_gemm<1>(g, st, nt - plan.columns);
+        launch_split_gemm<1>(g, st, nt - plan.columns);
     }
     // [G | I] -> [R | Y], the planes of Y in V, or beside what the rest of C is made of
     uint8_t *T[2] = {base + w.T, base + w.T + CH_PLANES}, *Y = plan.columns ? base + w.Y : V;
@@ -1050,14 +1035,12 @@ extern "C" int dbf_admm_prepare(const void* bits_dev, const void* m2_dev, const 
                                j, T[j & 1], Y, T[~j & 1], fail, beside);
         }
     }
-    // G^-1 = Y^T Y (overwrites G): upper blocks, the sums starting where both operands can be non-zero,
-    // then the mirror image
+    // G^-1 = Y^T Y (overwrites G): upper blocks, the sums starting where both operands can be non-zero, written to both triangles
     {
         SplitGemmArgs g = {};
         g.P = Y;  g.Q = Y;  g.out = G;  g.ldo = q;  g.M = q;  g.N = q;  g.K = q;
-        g.upper = 1;  g.ktri = 1;
+        g.upper = 1;  g.ktri = 1;  g.vec = (q & 3) == 0 && (reinterpret_cast<uintptr_t>(G) & 15) == 0;
         launch_split_gemm<2>(g, st);
-        hipLaunchKernelGGL(dbf_chol_mirror_kernel, dim3((q + 31) / 32, (q + 31) / 32), dim3(256), 0, st, G, q);
     }
     if (hipGetLastError() != hipSuccess) return DBF_EHIP;
     return DBF_OK;

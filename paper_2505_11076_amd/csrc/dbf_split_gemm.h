@@ -16,6 +16,8 @@
 
 #include "dbf_kernels.h"
 
+#include <algorithm>
+
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -100,30 +102,31 @@ __device__ __forceinline__ void sg_store2(uint8_t* at, const float (&x)[8], cons
     *reinterpret_cast<v8h*>(at + NEXT) = l;
 }
 
-// The plane kernels: a workgroup of 256 threads has a chunk of 128 k and 32 lines, a wavefront two fragments of it.
+// The plane kernels: 256 threads have a chunk of 128 k and 32 lines, a wavefront two fragments of it.  (A workgroup of their own, blockIdx.x the chunk;
+// or half of a larger one.)
 struct SgSite {
     int i, k0[2];    // this lane's output index (of the ib-th 32) and the first k of its two fragments
     size_t off[2];   // byte offset of the lane's 16 bytes in piece 0 (pieces are 4 fragments apart)
 };
-__device__ inline SgSite sg_site(int K, int pieces, int ib) {
-    const int lane = threadIdx.x & 63, n_kb = sg_kblocks(K);
+__device__ inline SgSite sg_site(int K, int pieces, int ib, int chunk, int t) {
+    const int lane = t & 63, n_kb = sg_kblocks(K);
     SgSite s;
     s.i = 32 * ib + (lane & 31);
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
-        const int kb = blockIdx.x * (SG_CHUNK / 16) + 2 * (threadIdx.x >> 6) + n;
+        const int kb = chunk * (SG_CHUNK / 16) + 2 * (t >> 6) + n;
         s.k0[n] = 16 * kb + 8 * (lane >> 5);
         s.off[n] = (((size_t)(ib >> 2) * n_kb + kb) * (4 * pieces) + (ib & 3)) * SG_FRAG + lane * 16;
     }
     return s;
 }
+__device__ inline SgSite sg_site(int K, int pieces, int ib) { return sg_site(K, pieces, ib, blockIdx.x, threadIdx.x); }
 inline dim3 sg_plane_grid(int K, int M) { return dim3((K + SG_CHUNK - 1) / SG_CHUNK, sg_lines(M) / 32); }
 
 // Scales the values of a workgroup's chunk and lines and stores their pieces and scales.  x: zero where k or i is out of range.
 template <bool LARGEST = false>
-__device__ __forceinline__ void sg_split_chunk(uint8_t* planes, int K, int M, const SgSite& s, const float (&x)[2][8]) {
-    __shared__ float part[4][32];
-    const int lane = threadIdx.x & 63, l32 = lane & 31, w = threadIdx.x >> 6;
+__device__ __forceinline__ void sg_split_chunk(uint8_t* planes, int K, int M, const SgSite& s, const float (&x)[2][8], int chunk, int t, float (*part)[32]) {
+    const int lane = t & 63, l32 = lane & 31, w = t >> 6;
     float mx = 0.f;
 #pragma unroll
     for (int n = 0; n < 2; ++n)
@@ -137,15 +140,20 @@ __device__ __forceinline__ void sg_split_chunk(uint8_t* planes, int K, int M, co
 #pragma unroll
     for (int n = 0; n < 2; ++n)
         sg_store2<LARGEST>(planes + s.off[n], x[n], c);
-    if (threadIdx.x < 32) reinterpret_cast<float*>(planes + sg_scales_at(2, K, M))[(size_t)blockIdx.x * sg_lines(M) + s.i] = c.up;
+    if (t < 32) reinterpret_cast<float*>(planes + sg_scales_at(2, K, M))[(size_t)chunk * sg_lines(M) + s.i] = c.up;
+}
+template <bool LARGEST = false>
+__device__ __forceinline__ void sg_split_chunk(uint8_t* planes, int K, int M, const SgSite& s, const float (&x)[2][8]) {
+    __shared__ float part[4][32];
+    sg_split_chunk<LARGEST>(planes, K, M, s, x, blockIdx.x, threadIdx.x, part);
 }
 
 // Planes of a dense k-major matrix src [K][ld >= M], its rows scaled by kscale (or NULL).  A wavefront's load of one k is two
 // runs of 128 bytes.  Bound by memory: 4 bytes read and 4 written per element.
 template <bool LARGEST = false>
 __device__ __forceinline__ void sg_split_dense(const float* __restrict__ src, size_t ld, int K, int M, const float* __restrict__ kscale,
-                                               uint8_t* __restrict__ planes, int ib) {
-    const SgSite s = sg_site(K, 2, ib);
+                                               uint8_t* __restrict__ planes, int ib, int chunk, int t, float (*part)[32]) {
+    const SgSite s = sg_site(K, 2, ib, chunk, t);
     float x[2][8];
 #pragma unroll
     for (int n = 0; n < 2; ++n)
@@ -161,12 +169,13 @@ __device__ __forceinline__ void sg_split_dense(const float* __restrict__ src, si
             asm("" : "+v"(x[n][e]));   // (or the compiler puts each load behind a branch and waits for it)
             x[n][e] = (s.k0[n] + e < K && s.i < M) ? x[n][e] : 0.f;
         }
-    sg_split_chunk<LARGEST>(planes, K, M, s, x);
+    sg_split_chunk<LARGEST>(planes, K, M, s, x, chunk, t, part);
 }
-
-__global__ __launch_bounds__(256) void dbf_split_dense_kernel(const float* __restrict__ src, size_t ld, int K, int M,
-                                                             const float* __restrict__ kscale, uint8_t* __restrict__ planes) {
-    sg_split_dense(src, ld, K, M, kscale, planes, blockIdx.y);
+// blockIdx.y: 32 lines.  (Those from `first` on.)
+__global__ __launch_bounds__(256) void dbf_split_dense_kernel(const float* __restrict__ src, size_t ld, int K, int M, const float* __restrict__ kscale,
+                                                             uint8_t* __restrict__ planes, int first) {
+    __shared__ float part[4][32];
+    sg_split_dense(src, ld, K, M, kscale, planes, first + blockIdx.y, blockIdx.x, threadIdx.x, part);
 }
 
 // Planes of a packed sign matrix S (rows = output index i, columns = k) in the 128 x 64 tile layout: `signs`, one plane of +-1, and `scaled`, two
@@ -221,7 +230,8 @@ struct SplitGemmArgs {
     float diag;
     int M, N, K;
     int upper;             // symmetric output (M = N): only the blocks that meet the upper triangle are made, a workgroup in x for each
-    int ktri;              // both operands are zero for k < output index: sums start at the first chunk that can contribute
+    int ktri;              // (upper) both operands are zero for k < output index: sums start at the first chunk that can contribute; both triangles are written
+    int vec;               // ktri: out may be written 16 bytes at a time
 };
 
 // One operand of a workgroup's block: its fragments from a chunk on, its lines' scales from that chunk on (two pieces).
@@ -260,14 +270,32 @@ __device__ __forceinline__ void sg_barrier() {
     asm volatile("" ::: "memory");
 }
 
-template <int PA, int BI, int KS>
-__global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_split_gemm_kernel(const SplitGemmArgs g) {
+// Planes made beside a contraction whose blocks leave compute units idle, by workgroups of 512 threads behind those of the blocks: two times 32 lines of a chunk
+// each, of `pairs` times 64 lines.
+struct SplitBesideArgs {
+    const float* src;
+    const float* kscale;
+    uint8_t* planes;
+    size_t ld;
+    int K, M, pairs;
+};
+
+template <int PA, int BI, int KS, bool BESIDE>
+__global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_split_gemm_kernel(const SplitGemmArgs g, const SplitBesideArgs d) {
     // slots of P and of Q in a buffer; P's loads per wavefront and step (BI = 1, PA = 1: two of its four slots are copies), all of them
     constexpr int NP = BI * PA < 2 ? 4 : 2 * BI * PA, NF = NP + 8, PL = NP / 4, PER = PL + 2;
     constexpr int BUF = NF * SG_FRAG, SUMS = KS == 2 ? 2 * 256 * (int)sizeof(v16f) : 0;
     // (four objects: the compiler then knows that a load into one is not read from another)
     __shared__ __align__(16) uint8_t r0[KS * BUF > SUMS ? KS * BUF : SUMS], r1[KS * BUF], r2[KS * BUF], r3[KS * BUF];
     __shared__ __align__(16) float ups[KS][256];   // the scales of a chunk: P's 128 lines, then Q's
+    if (BESIDE) {
+        const int chunks = (d.K + SG_CHUNK - 1) / SG_CHUNK, index = (int)blockIdx.x - ((int)gridDim.x - chunks * d.pairs), half = threadIdx.x >> 8;
+        if (index >= 0) {
+            sg_split_dense(d.src, d.ld, d.K, d.M, d.kscale, d.planes, 2 * (index / chunks) + half, index % chunks, threadIdx.x & 255,
+                           reinterpret_cast<float (*)[32]>(ups[0]) + 4 * half);
+            return;
+        }
+    }
     const int tid = threadIdx.x & 255, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
     // A compute die (linear id modulo 8) works on neighbouring blocks, eight rows of them at a time: what it reads of both operands stays
@@ -464,8 +492,29 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
                 // sizes: 2.25e-7, so 2.22e-7)
                 float val = tot[bi][bj][v] + add[bi][v];
                 if (PA == 1) val = g.cs ? (float)fma((double)tot[bi][bj][v] * (double)rs[bi][v], cs, row == col ? (double)g.diag : 0.) : tot[bi][bj][v] * rs[bi][v];
-                if (row < g.M && col < g.N) g.out[(size_t)row * g.ldo + col] = val;
+                if (PA == 2 && BI == 1 && g.ktri) {
+                    // (symmetric, both triangles written: a block on the diagonal from its upper half, so that they are the same bits)
+                    tot[bi][bj][v] = val;
+                    if ((!self || row <= col) && row < g.M && col < g.N) g.out[(size_t)row * g.ldo + col] = val;
+                } else if (row < g.M && col < g.N) {
+                    g.out[(size_t)row * g.ldo + col] = val;
+                }
             }
+        if (PA == 2 && BI == 1 && g.ktri && col < g.N) {
+            float* const line = g.out + (size_t)col * g.ldo;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int row = row_of(0, 4 * c);   // and the three behind it: 16 bytes of a line
+                const v4f x = {tot[0][bj][4 * c], tot[0][bj][4 * c + 1], tot[0][bj][4 * c + 2], tot[0][bj][4 * c + 3]};
+                if (g.vec && (!self || row + 3 < col)) {
+                    if (row < g.M) *reinterpret_cast<v4f*>(line + row) = x;   // (M is a multiple of 4)
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (row + e < g.M && (!self || row + e < col)) line[row + e] = x[e];
+                }
+            }
+        }
     }
 }
 
@@ -480,20 +529,35 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
 // 3712 (435) 1063 / 1054 / 1062 / 1085, 4096 (528) 1166 / 1149 / 1155 / 1180.
 // (Blocks of the upper triangle go to the compute dies as they come, column by column, not in bands as the full grid's: for B^T B, q = 2048, p = 4096,
 // 29 % of the reads hit L2, where the banded launches have 79 to 84 %.  A banded order of the triangle has not been measured.)
-// (`columns`: only the first so many blocks of each row.)
+// (`columns`: only the first so many blocks of each row.  `beside`: planes to be made by further workgroups, where there are idle compute units for them; returns
+// how many times 64 lines are.)
 template <int PA>
-inline void launch_split_gemm(const SplitGemmArgs& g, hipStream_t st, int columns = 1 << 30) {
+inline int launch_split_gemm(const SplitGemmArgs& g, hipStream_t st, int columns = 1 << 30, const SplitBesideArgs* beside = nullptr) {
     const int mt = (g.M + 127) / 128, all = (g.N + 127) / 128, nt = columns < all ? columns : all;
     const long long blocks = g.upper ? (long long)mt * (mt + 1) / 2 : (long long)mt * nt;
     auto grid = [&](int bi) { return g.upper ? dim3((unsigned)(blocks * (2 / bi))) : dim3(bi == 2 ? mt : (g.M + 63) / 64, nt); };
-    if (blocks <= 128 || (g.ktri && blocks <= 320))
-        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 1, 2>), grid(1), dim3(512), 0, st, g);
-    else if (PA == 2 && g.ktri)   // (Y^T Y alone)
-        hipLaunchKernelGGL((dbf_split_gemm_kernel<2, 1, 1>), grid(1), dim3(256), 0, st, g);
-    else if (blocks <= 256)
-        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 2, 2>), grid(2), dim3(512), 0, st, g);
-    else
-        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 2, 1>), grid(2), dim3(256), 0, st, g);
+    SplitBesideArgs d = {};
+    auto more = [&](dim3 of) {   // (blocks in x alone)
+        const long long chunks = (beside->K + SG_CHUNK - 1) / SG_CHUNK, most = sg_lines(beside->M) / 64;
+        d = *beside;
+        d.pairs = 0;
+        // (as many as an idle compute unit makes in the contraction's time: 2 us a chunk here, 3 a workgroup there.  The constants, us, none / so / twice that: 4096, 2048,
+        // 4096 539 / 527 / 529; 768, 600, 768 153.0 / 149.7 / 149.8; 4096, 512, 4096 179 / 168 / 168; 11008, 1500, 4096 696 / 703 / 705, where the contraction waits for memory itself)
+        if (g.K <= 8192) d.pairs = (int)std::min(most, std::max(0ll, 256 - (long long)of.x) * ((g.K + SG_CHUNK - 1) / SG_CHUNK) * 2 / 3 / chunks);
+        return dim3((unsigned)(of.x + chunks * d.pairs));
+    };
+    if (blocks <= 128 || (g.ktri && blocks <= 320)) {
+        if (PA == 1 && beside) hipLaunchKernelGGL((dbf_split_gemm_kernel<1, 1, 2, true>), more(grid(1)), dim3(512), 0, st, g, d);
+        else hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 1, 2, false>), grid(1), dim3(512), 0, st, g, d);
+    } else if (PA == 2 && g.ktri) {   // (Y^T Y alone)
+        hipLaunchKernelGGL((dbf_split_gemm_kernel<2, 1, 1, false>), grid(1), dim3(256), 0, st, g, d);
+    } else if (blocks <= 256) {
+        if (PA == 1 && beside) hipLaunchKernelGGL((dbf_split_gemm_kernel<1, 2, 2, true>), more(grid(2)), dim3(512), 0, st, g, d);
+        else hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 2, 2, false>), grid(2), dim3(512), 0, st, g, d);
+    } else {
+        hipLaunchKernelGGL((dbf_split_gemm_kernel<PA, 2, 1, false>), grid(2), dim3(256), 0, st, g, d);
+    }
+    return d.pairs;
 }
 
 }  // namespace

@@ -336,11 +336,11 @@ def test_admm_prepare_at_the_edges_of_the_elimination_blocks(q):
 
 @pytest.mark.parametrize("p,q,r", [(2100, 300, 1000), (1100, 200, 16600), (700, 520, 516)])
 def test_admm_prepare_with_parts_of_C_beside_the_elimination(p, q, r):
-    """C in three parts a block, in two with more block columns than there is room for, in one; and with the workspace that a call can do with, without the planes
-    of Y (two pieces of q x q in whole blocks of 128, four bytes a line and block): the same without parts.  Gates: as above."""
+    """C in three parts a block, in two with more block columns than there is room for, in one; and with the workspace that a call can do with, without the
+    planes that are apart then (two pieces of max(p, q) x q in whole blocks of 128, four bytes a line and block): the same one after the other.  Gates: as above."""
     prob = PackedProblem(p, q, r, I.seed_for(9, 800 + p + q))
-    n = (q + 127) // 128
-    for less in (0, 256, n * n * 65536 + 512 * n * n):
+    n = (q + 127) // 128 * ((max(p, q) + 127) // 128)
+    for less in (0, 256, n * 65536 + 512 * n):
         Minv, Cm = prob.prepare_on_device(0.9, less)
         _check_constants("constants p=%d q=%d r=%d, %d bytes less" % (p, q, r, less), prob, 0.9, Minv, Cm)
     with pytest.raises(B.DbfError):
