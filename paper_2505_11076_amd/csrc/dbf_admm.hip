@@ -8,7 +8,7 @@
 //     Z  = Minv^T R + U   (= W_hat + U)        dbf_split_gemm_kernel   fp16 matrix cores, operands split in two
 //                                                                       (dbf_split_gemm.h), U added in the epilogue
 //     (S', a', m') = SVID(Z)                   dbf_svid (dbf_svid.hip)
-//     U' = Z - a' . S' . m'^T  (= U + W_hat - A')   dbf_admm_dual_kernel
+//     U' = Z - a' . S' . m'^T  (= U + W_hat - A')   dbf_svid_dual (dbf_svid.hip)
 //
 // The contraction is q x q x r in fp32 accuracy (34 GFLOP at q = 2048, r = 4096) and dominates; the elementwise
 // kernels and the projection are bandwidth bound.  Measured at that size: the contraction 331 us on the fp32 matrix cores, 219 on the bf16
@@ -24,65 +24,6 @@
 #include <utility>
 
 namespace {
-
-// ---------------------------------------------------------------------------------------------
-// Elementwise kernels.  One workgroup per 128 x 64 tile of the sign matrix; thread t takes the four
-// columns 4 (t % 16) .. + 3 of rows 16 s + t / 16, s = 0 .. 7.  Their eight sign quadruples are the
-// eight bits of the four bytes of ONE 32-bit word of the tile (byte 256 g + 16 r + j, bit s = sign of
-// row 16 s + r, column 16 g + j), and a wavefront touches four rows of 256 contiguous bytes per pass.
-// ---------------------------------------------------------------------------------------------
-struct TileThread {
-    int row0, col, word;  // first row (s = 0), first column, word index in the tile
-};
-__device__ inline TileThread tile_thread(int t) {
-    const int rr = t >> 4, cq = t & 15;
-    TileThread x;
-    x.row0 = blockIdx.y * DBF_TILE_ROWS + rr;
-    x.col = blockIdx.x * DBF_TILE_COLS + 4 * cq;
-    x.word = 64 * (cq >> 2) + 4 * rr + (cq & 3);
-    return x;
-}
-
-// U' = Z - a_i m_j s_ij
-__global__ __launch_bounds__(256) void dbf_admm_dual_kernel(const float* __restrict__ Z, const float* __restrict__ a,
-                                                           const float* __restrict__ m, const uint8_t* __restrict__ bits,
-                                                           int rows, int cols, int n_ct, int vec_ok, float* __restrict__ out) {
-    const TileThread x = tile_thread(threadIdx.x);
-    if (x.col >= cols) return;
-    const unsigned w =
-        reinterpret_cast<const unsigned*>(bits + ((size_t)blockIdx.y * n_ct + blockIdx.x) * DBF_TILE_BYTES)[x.word];
-    const bool vec = vec_ok && x.col + 4 <= cols;
-    float mj[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) mj[e] = x.col + e < cols ? m[x.col + e] : 0.f;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-        const int row = x.row0 + 16 * s;
-        if (row >= rows) break;
-        const float ai = a[row];
-        const size_t at = (size_t)row * cols + x.col;
-        float v[4], res[4];
-        if (vec) {
-            const v4f p = *reinterpret_cast<const v4f*>(Z + at);
-            v[0] = p.x;  v[1] = p.y;  v[2] = p.z;  v[3] = p.w;
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = x.col + e < cols ? Z[at + e] : 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float am = ai * mj[e];
-            res[e] = v[e] - (((w >> (8 * e + s)) & 1u) ? am : -am);
-        }
-        if (vec) {
-            *reinterpret_cast<v4f*>(out + at) = (v4f){res[0], res[1], res[2], res[3]};
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (x.col + e < cols) out[at + e] = res[e];
-        }
-    }
-}
 
 // The operands of the contraction in one launch: the planes of Minv (blockIdx.y below q_blocks), and R = C + rho (a_k m_j s_kj - U) (q x r; k = its
 // row is the summation index of the contraction), written straight into fp16 planes: R exists nowhere in fp32.  A lane's eight rows of R are
@@ -891,8 +832,7 @@ extern "C" int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int
     float* Z = reinterpret_cast<float*>(base + w.Z);
     float* U = static_cast<float*>(U_dev);
     const float* C = static_cast<const float*>(C_dev);
-    const int n_rt = dbf_row_tiles(q), n_ct = dbf_col_tiles(r);
-    const int vec_r = ((r & 3) == 0 && (reinterpret_cast<uintptr_t>(U) & 15) == 0) ? 1 : 0;  // (Z is 256-byte aligned)
+    const int n_ct = dbf_col_tiles(r);
 
     const dim3 of_minv = sg_plane_grid(q, q), of_r = sg_plane_grid(q, r);   // (the same summation indices: the same x)
     hipLaunchKernelGGL(dbf_admm_operands_kernel, dim3(of_r.x, of_minv.y + of_r.y), dim3(256), 0, st, static_cast<const float*>(Minv_dev), base + w.P,
@@ -905,13 +845,7 @@ extern "C" int dbf_admm_step(const void* Minv_dev, const void* C_dev, int q, int
     g.M = q;  g.N = r;  g.K = q;
     launch_split_gemm<2>(g, st);
     if (hipGetLastError() != hipSuccess) return DBF_EHIP;
-    const int rc = dbf_svid(Z, q, r, svid_iters, a_dev, m_dev, bits_dev, base + w.svid, workspace_bytes - w.svid, st);
-    if (rc != DBF_OK) return rc;
-    hipLaunchKernelGGL(dbf_admm_dual_kernel, dim3(n_ct, n_rt), dim3(256), 0, st, Z, static_cast<const float*>(a_dev),
-                       static_cast<const float*>(m_dev),
-                       static_cast<const uint8_t*>(bits_dev), q, r, n_ct, vec_r, U);
-    if (hipGetLastError() != hipSuccess) return DBF_EHIP;
-    return DBF_OK;
+    return dbf_svid_dual(Z, q, r, svid_iters, a_dev, m_dev, bits_dev, base + w.svid, workspace_bytes - w.svid, U, st);
 }
 
 // ---- forming the constant matrices of the update on the device ---------------------------------

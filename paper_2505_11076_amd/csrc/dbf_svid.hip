@@ -772,6 +772,94 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
         }
 }
 
+// The dual of the ADMM update behind the projection: U = Z - a_i m_j s_ij.  One workgroup per 128 x 64 tile of the sign matrix; thread t takes the four
+// columns 4 (t % 16) .. + 3 of rows 16 s + t / 16, s = 0 .. 7.  Their eight sign quadruples are the
+// eight bits of the four bytes of ONE 32-bit word of the tile (byte 256 g + 16 r + j, bit s = sign of
+// row 16 s + r, column 16 g + j), and a wavefront touches four rows of 256 contiguous bytes per pass.  Bound by memory.
+// FINISH: a and m are made on the way (dbf_svid_finish_kernel; u_raw and v_raw in their place), every workgroup forming both lengths from L2: a
+// launch of 5 us less.  An update of 2048 x 4096 179.5 / 177.1 us, 1024 x 4096 75.5 / 72.3, 512 x 2000 44.5 / 42.7.
+template <bool FINISH>
+__global__ __launch_bounds__(256) void dbf_svid_dual_kernel(const float* __restrict__ Z, const float* __restrict__ a_or_u, const float* __restrict__ m_or_v,
+                                                           const float* __restrict__ ss_part, int n_ss, const uint8_t* __restrict__ bits, int rows, int cols,
+                                                           int n_ct, int vec_ok, float* __restrict__ a, float* __restrict__ m, float* __restrict__ out) {
+    __shared__ double part[2][4];
+    const int tid = threadIdx.x, lane = tid & 63, rr = tid >> 4, cq = tid & 15;
+    const int row0 = blockIdx.y * DBF_TILE_ROWS + rr, col = blockIdx.x * DBF_TILE_COLS + 4 * cq;
+    const unsigned w = reinterpret_cast<const unsigned*>(bits + ((size_t)blockIdx.y * n_ct + blockIdx.x) * DBF_TILE_BYTES)[64 * (cq >> 2) + 4 * rr + (cq & 3)];
+    const bool vec = vec_ok && col + 4 <= cols;
+    float mj[4], ai[8];
+    v4f z[8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) mj[e] = m_or_v[min(col + e, cols - 1)];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        const int row = min(row0 + 16 * s, rows - 1);
+        const float* at = Z + (size_t)row * cols;
+        ai[s] = a_or_u[row];
+        if (vec) {
+            z[s] = *reinterpret_cast<const v4f*>(at + col);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z[s][e] = at[min(col + e, cols - 1)];
+        }
+    }
+    if (FINISH) {
+        double s[2] = {0., 0.};
+        for (int j0 = tid; j0 < rows; j0 += 4 * 256) {
+            float p[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p[e] = a_or_u[min(j0 + 256 * e, rows - 1)];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[0] += j0 + 256 * e < rows ? (double)p[e] * (double)p[e] : 0.;
+        }
+        for (int j = tid; j < n_ss; j += 256) s[1] += (double)ss_part[j];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            s[k] = held_sum<2>(s[k]);   // (lanes equal modulo 4; the rest below)
+            s[k] += held_dpp<0xB1>(s[k]);
+            s[k] += held_dpp<0x4E>(s[k]);
+            if (lane == 0) part[k][tid >> 6] = s[k];
+        }
+        __syncthreads();
+        const double ssu = (part[0][0] + part[0][1]) + (part[0][2] + part[0][3]), ssv = (part[1][0] + part[1][1]) + (part[1][2] + part[1][3]);
+        const double nv = sqrt(ssv), of_u = nv / ssu;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) ai[s] = ssu > 0. ? (float)(ai[s] * of_u) : 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mj[e] = nv > 0. ? (float)(mj[e] / nv) : mj[e];
+        if (blockIdx.x == 0 && cq == 0) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                if (row0 + 16 * s < rows) a[row0 + 16 * s] = ai[s];
+        }
+        if (blockIdx.y == 0 && rr == 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (col + e < cols) m[col + e] = mj[e];
+        }
+    }
+    if (col >= cols) return;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+        const int row = row0 + 16 * s;
+        if (row >= rows) break;
+        const size_t at = (size_t)row * cols + col;
+        v4f res;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float am = ai[s] * mj[e];
+            res[e] = z[s][e] - (((w >> (8 * e + s)) & 1u) ? am : -am);
+        }
+        if (vec) {
+            *reinterpret_cast<v4f*>(out + at) = res;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (col + e < cols) out[at + e] = res[e];
+        }
+    }
+}
+
 inline size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 // Groups of eight rows per workgroup of the one-pass round.
 inline int round_groups_per_wg(int rows) { return (16 * dbf_row_tiles(rows) + ROUND_WGS - 1) / ROUND_WGS; }
@@ -857,44 +945,40 @@ void launch_held_any(int groups, const HeldArgs& a, hipStream_t st) {
 
 }  // namespace
 
-extern "C" size_t dbf_svid_workspace_bytes(int rows, int cols) {
-    if (rows < 1 || cols < 1 || rows > DBF_MAX_DIM || cols > DBF_MAX_DIM) return 0;
-    return svid_workspace(rows, cols).total;
-}
-
-size_t dbf_svid_least_workspace(int rows, int cols) { return svid_workspace(rows, cols).least; }
-
-extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev,
-                        void* workspace_dev, size_t workspace_bytes, void* hip_stream) {
-    if (!Z_dev || !a_dev || !m_dev || !bits_dev || rows < 1 || cols < 1 || iters < 1) return DBF_EINVAL;
-    if (rows > DBF_MAX_DIM || cols > DBF_MAX_DIM) return DBF_EINVAL;
-    if ((reinterpret_cast<uintptr_t>(Z_dev) & 3) || (reinterpret_cast<uintptr_t>(a_dev) & 3) ||
-        (reinterpret_cast<uintptr_t>(m_dev) & 3) || (reinterpret_cast<uintptr_t>(bits_dev) & 3))
-        return DBF_EINVAL;
+namespace {
+// The projection, and with U the dual behind it.
+int svid_run(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev, void* workspace_dev, size_t workspace_bytes, float* U,
+             hipStream_t st) {
     const SvidWorkspace w = svid_workspace(rows, cols);
-    if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < w.least)
-        return DBF_EWORKSPACE;
-    hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const float* Z = static_cast<const float*>(Z_dev);
     uint8_t* base = static_cast<uint8_t*>(workspace_dev);
     float* u = reinterpret_cast<float*>(base + w.u);
-    float* v = static_cast<float*>(m_dev);   // the right factor is iterated in place in the caller's buffer
     float* partial = reinterpret_cast<float*>(base + w.partial);
     float* ss_part = reinterpret_cast<float*>(base + w.scalars);
-    const int vec_ok = ((cols & 3) == 0 && (reinterpret_cast<uintptr_t>(Z_dev) & 15) == 0 &&
-                        (reinterpret_cast<uintptr_t>(m_dev) & 15) == 0) ? 1 : 0;
+    const int n_rt = dbf_row_tiles(rows), n_ct = dbf_col_tiles(cols), n_ss = (cols + reduce_cols(cols) - 1) / reduce_cols(cols);
+    // The last kernel's work in the dual's while every workgroup reading u is little (2048 x 4096: 1024 of 8 KiB).  An update by size, us, apart / in the
+    // dual: 512 x 2000 44.5 / 42.7, 2048 x 4096 179.5 / 177.1, 4096 x 4096 516 / 516, 8192 x 4096 1918 / 1916: nothing left to gain beyond 4096 x 4096.
+    const bool finish_in_dual = U && (size_t)n_rt * n_ct * rows <= 8u << 20;
+    // the right factor is iterated in place in the caller's buffer, or where the dual's workgroups read it while others write m
+    float* const v = finish_in_dual ? reinterpret_cast<float*>(base + w.v) : static_cast<float*>(m_dev);
+    const int vec_ok = ((cols & 3) == 0 && (reinterpret_cast<uintptr_t>(Z_dev) & 15) == 0 && (reinterpret_cast<uintptr_t>(v) & 15) == 0) ? 1 : 0;
+    const int vec_u = ((cols & 3) == 0 && (reinterpret_cast<uintptr_t>(Z_dev) & 15) == 0 && (reinterpret_cast<uintptr_t>(U) & 15) == 0) ? 1 : 0;
+    auto dual = [&](bool finish) {
+        float *a = static_cast<float*>(a_dev), *m = static_cast<float*>(m_dev);
+        hipLaunchKernelGGL(finish ? dbf_svid_dual_kernel<true> : dbf_svid_dual_kernel<false>, dim3(n_ct, n_rt), dim3(256), 0, st, Z, finish ? u : a, finish ? v : m,
+                           ss_part, n_ss, static_cast<const uint8_t*>(bits_dev), rows, cols, n_ct, vec_u, a, m, U);
+    };
     const int chunks = (rows + COL_CHUNK_ROWS - 1) / COL_CHUNK_ROWS;
-    const int n_rt = dbf_row_tiles(rows), n_ct = dbf_col_tiles(cols);
-    const int n_ss = (cols + reduce_cols(cols) - 1) / reduce_cols(cols);
 
     // One pass per round wherever rows can be held: up to 24576 columns in 16-byte pieces, 12288 in single values.  8 rounds, us, two
     // passes / one: 4096 x 4096 247 / 157, now 134 (the row sums of a batch reduced together, 15.6 -> 13.7 us a round; 32 columns to a workgroup of
     // the reduction; the last kernel 6.7 -> 3.8); 2048 x 4096 161 / 93, now 83; 4 rounds of 8192 x 8192 262, now 252.
     if (const int groups = held_groups(rows, cols); groups && vec_ok && iters >= held_rounds(rows, cols) && workspace_bytes >= w.total) {
-        const HeldArgs h = {Z, u, partial, static_cast<float*>(a_dev), v, reinterpret_cast<HeldSync*>(base + w.sync),
+        const HeldArgs h = {Z, u, partial, static_cast<float*>(a_dev), static_cast<float*>(m_dev), reinterpret_cast<HeldSync*>(base + w.sync),
                             reinterpret_cast<float*>(base + w.v), reinterpret_cast<double*>(base + w.ss), static_cast<uint8_t*>(bits_dev),
                             rows, cols, iters, 0, n_ct, 0, 0};
         launch_held_any(groups, h, st);
+        if (U) dual(false);
         return hipGetLastError() == hipSuccess ? DBF_OK : DBF_EHIP;
     }
     const int cpl = (cols + 4095) / 4096;  // float4s per thread and row of a workgroup of 1024
@@ -938,9 +1022,39 @@ extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* 
                            Z, rows, cols, u, partial);
         launch_reduce(cols, st, partial, chunks, cols, v, ss_part);
     }
-    const int longest = rows > cols ? rows : cols;
-    hipLaunchKernelGGL(dbf_svid_finish_kernel, dim3((longest + FINISH - 1) / FINISH), dim3(FINISH), 0, st, u, rows, ss_part, n_ss, v,
-                       cols, static_cast<float*>(a_dev));
+    if (finish_in_dual) {
+        dual(true);
+    } else {
+        const int longest = rows > cols ? rows : cols;
+        hipLaunchKernelGGL(dbf_svid_finish_kernel, dim3((longest + FINISH - 1) / FINISH), dim3(FINISH), 0, st, u, rows, ss_part, n_ss, v,
+                           cols, static_cast<float*>(a_dev));
+        if (U) dual(false);
+    }
     if (hipGetLastError() != hipSuccess) return DBF_EHIP;
     return DBF_OK;
+}
+}  // namespace
+
+extern "C" size_t dbf_svid_workspace_bytes(int rows, int cols) {
+    if (rows < 1 || cols < 1 || rows > DBF_MAX_DIM || cols > DBF_MAX_DIM) return 0;
+    return svid_workspace(rows, cols).total;
+}
+
+size_t dbf_svid_least_workspace(int rows, int cols) { return svid_workspace(rows, cols).least; }
+
+extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev,
+                        void* workspace_dev, size_t workspace_bytes, void* hip_stream) {
+    if (!Z_dev || !a_dev || !m_dev || !bits_dev || rows < 1 || cols < 1 || iters < 1) return DBF_EINVAL;
+    if (rows > DBF_MAX_DIM || cols > DBF_MAX_DIM) return DBF_EINVAL;
+    if ((reinterpret_cast<uintptr_t>(Z_dev) & 3) || (reinterpret_cast<uintptr_t>(a_dev) & 3) ||
+        (reinterpret_cast<uintptr_t>(m_dev) & 3) || (reinterpret_cast<uintptr_t>(bits_dev) & 3))
+        return DBF_EINVAL;
+    if (!workspace_dev || (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < svid_workspace(rows, cols).least)
+        return DBF_EWORKSPACE;
+    return svid_run(Z_dev, rows, cols, iters, a_dev, m_dev, bits_dev, workspace_dev, workspace_bytes, nullptr, static_cast<hipStream_t>(hip_stream));
+}
+
+int dbf_svid_dual(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev, void* workspace_dev, size_t workspace_bytes,
+                  float* U_dev, hipStream_t stream) {
+    return svid_run(Z_dev, rows, cols, iters, a_dev, m_dev, bits_dev, workspace_dev, workspace_bytes, U_dev, stream);
 }

@@ -549,3 +549,49 @@ def test_admm_contraction_meets_the_largest_entry_of_a_line_exactly(q, r):
     err = np.sum((U1 + a1[:, None] * S1 * m1[None, :] - Z) * np.sign(Z), axis=1) / np.sum(np.abs(Z), axis=1)
     G.say("  rows of Z q=%d r=%d: common error 2^%.2f at most, 2^%.2f on average" % (q, r, np.log2(np.max(np.abs(err))), np.log2(np.mean(np.abs(err)))))
     assert np.max(np.abs(err)) <= 6 * 2.0 ** -22 / np.sqrt(3 * r)
+
+
+@pytest.mark.parametrize("q,r,iters", [(1, 1, 1), (129, 65, 1), (300, 200, 2), (127, 2052, 8), (2048, 16388, 1)])
+def test_admm_step_ends_as_the_projection_and_the_dual(q, r, iters):
+    """The last kernel of an update forms a' and m' beside U', or after dbf_svid's own last kernel where it has too many
+    workgroups (2048 x 16388), or after all rounds in one launch (8 rounds of 127 x 2052).  Z lies before the
+    projection's part at the end of the workspace: dbf_svid of it gives the same signs and, but for sums of squares in
+    64 bits in another order, the same a' and m' (rounded to fp32 once or twice: 4 x 2^-24), and U' = Z - a' S' m'^T to
+    its two roundings.  m' may start at any multiple of four bytes.  Where that or the one launch takes the rounds to other
+    kernels, their fp32 sums of positive terms, each through at most 128 additions, are in another order: 2 x 128 x 2^-24."""
+    G.say("start admm ending q=%d r=%d iters=%d" % (q, r, iters))
+    gen = torch.Generator(device="cuda").manual_seed(I.seed_for(31, q + r))
+    rand = lambda *n: torch.randn(*n, generator=gen, device="cuda")  # noqa: E731
+    Minv = torch.eye(q, device="cuda") + 0.01 * rand(q, q) / q ** 0.5
+    C, U0, a0, m0 = rand(q, r), 0.1 * rand(q, r), rand(q).abs(), rand(r).abs()
+    svid_bytes = B.dbf_svid_workspace_bytes(q, r)
+    wsb = B.dbf_admm_workspace_bytes(q, r)
+    end = wsb - svid_bytes
+    up256 = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    tiles = (q + 127) // 128 * ((r + 63) // 64) * 1024
+    results = []
+    for shift in (0, 1):
+        ws = torch.full((wsb,), 0xA5, dtype=torch.uint8, device="cuda")
+        a, U, bits = a0.clone(), U0.clone(), torch.zeros(tiles, dtype=torch.uint8, device="cuda")
+        m = torch.full((r + 2,), -7.0, device="cuda")
+        m[shift:shift + r] = m0
+        B.dbf_admm_step(Minv.data_ptr(), C.data_ptr(), q, r, 1.0, iters, a.data_ptr(), m.data_ptr() + 4 * shift, bits.data_ptr(),
+                        U.data_ptr(), ws.data_ptr(), wsb, G.stream_handle())
+        torch.cuda.synchronize()
+        assert (m[:shift] == -7.0).all() and (m[shift + r:] == -7.0).all()
+        results.append((a, m[shift:shift + r].clone(), bits, U))
+    Z = ws[end - up256(4 * q * r):][:4 * q * r].view(torch.float32).reshape(q, r).clone()
+    a, m, bits, U = results[0]
+    tol = (4 if iters < 3 and r < 16384 else 2 * 128) * 2.0 ** -24
+    for other in results[1:]:
+        assert torch.equal(bits, other[2])
+        for x, y in zip((a, m, U), (other[0], other[1], other[3])):
+            assert (x - y).abs().max() <= tol * x.abs().max()
+    sa, sm, sbits = torch.empty_like(a0), torch.empty_like(m0), torch.zeros_like(bits)
+    sws = torch.empty(svid_bytes, dtype=torch.uint8, device="cuda")
+    B.dbf_svid(Z.data_ptr(), q, r, iters, sa.data_ptr(), sm.data_ptr(), sbits.data_ptr(), sws.data_ptr(), svid_bytes, G.stream_handle())
+    torch.cuda.synchronize()
+    assert torch.equal(bits, sbits)
+    assert ((a - sa).abs() <= tol * sa.abs()).all() and ((m - sm).abs() <= tol * sm.abs()).all()
+    am = a[:, None] * m[None, :]
+    assert ((U - (Z - torch.where(Z >= 0, am, -am))).abs() <= 2.0 ** -23 * (Z.abs() + am)).all()
