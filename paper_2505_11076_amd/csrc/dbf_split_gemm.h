@@ -284,6 +284,7 @@ template <int PA, int BI, int KS, bool BESIDE>
 __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))) void dbf_split_gemm_kernel(const SplitGemmArgs g, const SplitBesideArgs d) {
     // slots of P and of Q in a buffer; P's loads per wavefront and step (BI = 1, PA = 1: two of its four slots are copies), all of them
     constexpr int NP = BI * PA < 2 ? 4 : 2 * BI * PA, NF = NP + 8, PL = NP / 4, PER = PL + 2;
+    constexpr bool AHEAD = KS == 1 && PA == 2;
     constexpr int BUF = NF * SG_FRAG, SUMS = KS == 2 ? 2 * 256 * (int)sizeof(v16f) : 0;
     // (four objects: the compiler then knows that a load into one is not read from another)
     __shared__ __align__(16) uint8_t r0[KS * BUF > SUMS ? KS * BUF : SUMS], r1[KS * BUF], r2[KS * BUF], r3[KS * BUF];
@@ -350,31 +351,25 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
             }
     const int fi = BI * (w & 1), fj = 2 * (w >> 1);           // this wavefront's first 32-blocks
     v8h a[BI][PA], b[2][2];
-    auto read = [&](const uint8_t* buf) {
-        const uint8_t* base = buf + kg * BUF + 16 * lane;
+    auto read_p = [&](const uint8_t* buf, int p) {
 #pragma unroll
-        for (int p = 0; p < PA; ++p)
+        for (int x = 0; x < BI; ++x) a[x][p] = *reinterpret_cast<const v8h*>(buf + kg * BUF + 16 * lane + (2 * BI * p + fi + x) * SG_FRAG);
+    };
+    auto read_q = [&](const uint8_t* buf, int p) {
 #pragma unroll
-            for (int x = 0; x < BI; ++x) a[x][p] = *reinterpret_cast<const v8h*>(base + (2 * BI * p + fi + x) * SG_FRAG);
-#pragma unroll
-        for (int p = 0; p < 2; ++p)
-#pragma unroll
-            for (int x = 0; x < 2; ++x) b[x][p] = *reinterpret_cast<const v8h*>(base + (NP + 4 * p + fj + x) * SG_FRAG);
+        for (int x = 0; x < 2; ++x) b[x][p] = *reinterpret_cast<const v8h*>(buf + kg * BUF + 16 * lane + (NP + 4 * p + fj + x) * SG_FRAG);
     };
     auto product = [&](int bi, int bj, int p, int q) {
         v16f& sum = p + q == 0 ? acc[bi][bj] : low[bi][bj];
         sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[bi][p], b[bj][q], sum, 0, 0, 0);
     };
     // (piece pairs outermost: an accumulator is used again only after the others)
-    auto multiply = [&]() {
+    auto multiply = [&](int p, int q) {
 #pragma unroll
-        for (int p = PA - 1; p >= 0; --p)
+        for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
-            for (int q = 1 - p; q >= 0; --q)
-#pragma unroll
-                for (int bi = 0; bi < BI; ++bi)
-#pragma unroll
-                    for (int bj = 0; bj < 2; ++bj) product(bi, bj, p, q);
+            for (int bj = 0; bj < 2; ++bj) product(bi, bj, p, q);
+        if (AHEAD) __builtin_amdgcn_sched_barrier(0);
     };
     // l l where the lines meet themselves: there it is of one sign, and lost from all of a diagonal
     const bool self = PA == 2 && BI == 1 && g.ktri && (row0 >> 7) == jt;
@@ -403,7 +398,11 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
             }
         }
     };
-    auto multiply_last = [&](bool live) {
+    auto read_early = [&](const uint8_t* buf) {
+        read_p(buf, PA - 1);
+        read_q(buf, 0);
+    };
+    auto multiply_last = [&](bool live, const uint8_t* next) {
 #pragma unroll
         for (int n = 0; n <= 2 * BI; ++n) {
             if (n < 2 * BI) {
@@ -411,6 +410,9 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
                 for (int p = PA - 1; p >= 0; --p)
 #pragma unroll
                     for (int q = 1 - p; q >= 0; --q) product(n >> 1, n & 1, p, q);
+            }
+            if (AHEAD && n == 2 * BI - 1) {
+                read_early(next);
             }
             if (n > 0 && live) fold((n - 1) >> 1, (n - 1) & 1);
             __builtin_amdgcn_sched_barrier(0);
@@ -422,17 +424,38 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
     fetch(r1, 0, 1);
     fetch(r2, 0, 2);
     const int rounds = (chunks + KS - 1) / KS;
+    // Two workgroups to a compute unit wait for each other's LDS reads (of 64 KiB a step for 24 products of a wavefront pair, what the matrix pipe takes): the
+    // next step's l of P and h of Q are read as soon as this step's products with them are done.  An update of 2048 x 4096 178.6 / 176.0 us,
+    // 3000 x 4000 324.2 / 316.8.  With KS = 2, a workgroup alone, the loads' third step of lead is worth more: 1024 x 4096 73.2 / 73.8,
+    // as with signs in one piece, half of whose products could cover the reads: constants of 4096^3 1424 / 1441, 4096 x 2048 x 11008 826 / 841.
+    if (AHEAD) {
+        sg_barrier<2 * PER>();
+        read_early(r0);
+    }
     for (int i = 0; i < rounds; ++i) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            // the loads of this step have arrived, those of the two after it (and, of steps 0 and 1, the scales) may not have; every
-            // wavefront is done with the step before, whose buffer the next loads take
-            if (j == 1 || j == 2) sg_barrier<2 * PER + 1>(); else sg_barrier<2 * PER>();
+            // The loads of this step (AHEAD: and of the next) have arrived, those of the two after it (the one after them; and, of steps 0 and 1, the
+            // scales) may not have; every wavefront is done with the step before, whose buffer the next loads take.
+            constexpr int LEFT = (AHEAD ? 1 : 2) * PER;
+            if (j == 1 || j == 2) sg_barrier<LEFT + 1>(); else sg_barrier<LEFT>();
+            const uint8_t *const now = ring[j & 3], *const next = ring[(j + 1) & 3];
+            if (!AHEAD) read_early(now);
+            if (PA == 2) read_p(now, 0);
+            read_q(now, 1);
             fetch(ring[(j + 3) & 3], i + (j + 3) / 8, (j + 3) & 7);
             if (j == 0) fetch_ups(i);
-            read(ring[j & 3]);
+            if (AHEAD) __builtin_amdgcn_sched_barrier(0);
             multiply_self();
-            if (j < 7) multiply(); else multiply_last(KS == 1 || KS * i + kg < chunks);
+            if (j < 7) {
+                if (PA == 2) multiply(PA - 1, 0);
+                if (AHEAD) read_p(next, PA - 1);
+                multiply(0, PA == 2 && !AHEAD ? 1 : 0);
+                if (AHEAD) read_q(next, 0);
+                multiply(0, PA == 2 && !AHEAD ? 0 : 1);
+            } else {
+                multiply_last(KS == 1 || KS * i + kg < chunks, next);
+            }
         }
     }
     sg_barrier<0>();
