@@ -758,6 +758,8 @@ def svid_bench(B, I, torch, np, stream, proto, iters=8):
         #  signs in the first of them; the algorithmic bytes above keep the two-pass count, so the rate on them can pass the peak)
         one_pass = cols <= 24576 and cols % 4 == 0
         passes = (iters if cols <= 4096 else iters + 1) if one_pass else (2 * iters + 1)
+        if one_pass and rows <= 1 << 15 and rows * cols <= 20 << 20 and iters >= 6:
+            passes = 1   # (Z stays in registers from round to round)
         res["%dx%d_iters%d" % (rows, cols, iters)] = {
             "ms_per_call": round(ms, 4), "algorithmic_bytes": nbytes, "GBps": round(nbytes / (ms * 1e-3) / 1e9, 1),
             "frac_of_hbm_peak": round(nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),

@@ -12,8 +12,8 @@
 //
 // The contraction is q x q x r in fp32 accuracy (34 GFLOP at q = 2048, r = 4096) and dominates; the elementwise
 // kernels and the projection are bandwidth bound.  Measured at that size: the contraction 331 us on the fp32 matrix cores, 219 on the bf16
-// ones with operands in three parts, 108 on the fp16 ones with operands in two, whose planes, with the making of R, take 22 us in one launch; the update
-// with two rounds of SVID 388, 287, now 184 us; error against 64 bits 8.1e-6, 5.1e-6, 1.6e-6 (fewer roundings: 16 products enter the accumulator at
+// ones with operands in three parts, 106-110 on the fp16 ones with operands in two, whose planes, with the making of R, take 22 us in one launch; the update
+// with two rounds of SVID 388, 287, now 178-180 us; error against 64 bits 8.1e-6, 5.1e-6, 1.6e-6 (fewer roundings: 16 products enter the accumulator at
 // once, and half as many of them).
 // The paper gives no kernel design for this step.
 #include "dbf_kernels.h"
