@@ -390,7 +390,7 @@ constexpr int CP_CHUNKS = 8;
 constexpr int CP_AHEAD = 4;    // steps of 16 k whose operands are on their way
 // A workgroup without LDS (the ring of dbf_split_gemm.h has no place beside the elimination's): a wavefront has 64 x 32 outputs, the fragments of b . W
 // come straight from memory to registers, and those of the signs are made there: eight bytes of a tile are a lane's eight k for all of 128 rows.  The same
-// products, in the same order, as there with 256 threads.
+// products as there.
 // Measured at p = r = 4096, q = 2048: a launch of the elimination takes 27 us with 8 chunks beside it for 22 without any (the clock of a busy chip), all sixteen
 // 424 for 360, and C in a launch of its own 130: 627 -> 554 us.  (The signs' fragments from their plane in memory: 571.  Parts of 7 chunks: the same; of 4: not all
 // of C has room.)
@@ -433,16 +433,28 @@ __device__ __forceinline__ void chol_beside(const CholBeside& g, int index) {
     for (int n = 0; n < CP_AHEAD; ++n) fetch(n, SG_CHUNK_STEPS * c0 + n);
     const int row0 = 128 * it + 64 * rp, col = 128 * jt + 32 * cb + l32, cc = min(col, g.N - 1);
     auto row_of = [&](int x, int v) { return row0 + 32 * x + 8 * (v >> 2) + 4 * h + (v & 3); };
-    v16f acc[2], low[2], tot[2];
+    // (a part's halves are sums of their own, added to those before: C is 8.6e-8 from 64 bits, mean over seven sizes; all chunks in one chain 1.00e-7; 512
+    // threads of dbf_split_gemm.h, a sum each, 9.4e-8; no difference in time)
+    const int half = c0 + (c1 - c0) / 2;
+    v16f acc[2], low[2], tot[2], sum[2];
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            acc[x][v] = low[x][v] = 0.f;
-            tot[x][v] = part == 0 ? 0.f : g.out[(size_t)min(row_of(x, v), g.M - 1) * g.N + cc];
+            acc[x][v] = low[x][v] = tot[x][v] = 0.f;
+            sum[x][v] = part == 0 ? 0.f : g.out[(size_t)min(row_of(x, v), g.M - 1) * g.N + cc];
         }
 #pragma unroll 1
     for (int c = c0; c < c1; ++c) {
+        if (c == half) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    sum[x][v] += tot[x][v];
+                    tot[x][v] = 0.f;
+                }
+        }
         const float uq = Q.up[(size_t)c * Q.lines + 32 * cb + l32];
 #pragma unroll
         for (int n = 0; n < SG_CHUNK_STEPS; ++n) {
@@ -469,7 +481,8 @@ __device__ __forceinline__ void chol_beside(const CholBeside& g, int index) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int row = row_of(x, v);
-            if (row < g.M && col < g.N) g.out[(size_t)row * g.N + col] = c1 == chunks ? tot[x][v] * g.rs[row] : tot[x][v];
+            const float all = sum[x][v] + tot[x][v];
+            if (row < g.M && col < g.N) g.out[(size_t)row * g.N + col] = c1 == chunks ? all * g.rs[row] : all;
         }
 }
 
