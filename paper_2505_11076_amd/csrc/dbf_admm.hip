@@ -660,7 +660,7 @@ __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     };
     __shared__ __align__(16) uint8_t lds[sizeof(Tiles) > sizeof(CholBlock) ? sizeof(Tiles) : sizeof(CholBlock)];
     Tiles& T = *reinterpret_cast<Tiles*>(lds);
-    if (blockIdx.x >= gridDim.x - beside.count) {
+    if (!MADE && blockIdx.x >= gridDim.x - beside.count) {   // (launches with room for parts have fewer than 256 blocks)
         chol_beside(beside, blockIdx.x - (gridDim.x - beside.count));
         return;
     }

@@ -302,19 +302,22 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
     // A compute die (linear id modulo 8) works on neighbouring blocks, eight rows of them at a time: what it reads of both operands stays
     // in its own L2.  (2048 x 4096 outputs: whole columns of blocks to a die 97 us, 8 x 8 blocks 92.)
     int it, jt;
+    auto banded = [](unsigned lin, unsigned n_wg) {
+        const unsigned die = lin & 7, slot = lin >> 3, per = n_wg >> 3, extra = n_wg & 7;
+        return (int)(die * per + (die < extra ? die : extra) + slot);
+    };
     if (g.upper) {
-        // column by column of the blocks that meet the upper triangle: (2 / BI) (jt + 1) of column jt
-        const int v = blockIdx.x;
+        // Column by column of the blocks that meet the upper triangle: (2 / BI) (jt + 1) of column jt.  Neighbours to a die here too (constants, p = r = 4096,
+        // q = 2048 521 us / 513; 2048 x 900 x 6000 259.5 / 256.5), but where the sums shorten from column to column: one die would have the longest.
         auto before = [](int c) { return (2 / BI) * (c * (c + 1) / 2); };
+        const int v = g.ktri ? (int)blockIdx.x : banded(blockIdx.x, before((g.N + 127) >> 7));
         jt = (int)((sqrtf(1.f + (float)(4 * BI) * (float)v) - 1.f) * 0.5f);
         while (before(jt) > v) --jt;
         while (before(jt + 1) <= v) ++jt;
         it = v - before(jt);
     } else {
         const int mt = gridDim.x, nt = gridDim.y;
-        const unsigned n_wg = mt * nt, lin = blockIdx.x + mt * blockIdx.y;
-        const unsigned die = lin & 7, slot = lin >> 3, per = n_wg >> 3, extra = n_wg & 7;
-        const int vid = (int)(die * per + (die < extra ? die : extra) + slot), band = vid / (8 * nt), in_band = vid - band * 8 * nt, rows = min(8, mt - 8 * band);
+        const int vid = banded(blockIdx.x + mt * blockIdx.y, mt * nt), band = vid / (8 * nt), in_band = vid - band * 8 * nt, rows = min(8, mt - 8 * band);
         it = 8 * band + in_band % rows;
         jt = in_band / rows;
     }
