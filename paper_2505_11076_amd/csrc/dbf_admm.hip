@@ -705,8 +705,11 @@ __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         }
     };
     if (MADE) {
-        load_old(y);
+        // (the planes' arrival first: at the barrier the compiler cannot tell their loads from these, and waits for all.  q = 8192, p = r = 768: 4795 us, so 4526; 4096 1009 / 992)
         if (tid < 2 * NB) T.up[0][tid] = up_or_t;
+        __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt = 0
+        asm volatile("" ::: "memory");
+        load_old(y);
     } else {
         if (diag) load_old(y); else chol_load_block(G, q, j, c, y);
         __syncthreads();
