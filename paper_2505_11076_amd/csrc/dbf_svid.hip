@@ -436,7 +436,9 @@ constexpr int HELD_THREADS = 512, HELD_WAVES = HELD_THREADS / 64;
 constexpr int HELD_PARTS = 256;
 constexpr unsigned HELD_CLOSED = 0x80000000u;
 constexpr int HELD_WAIT_US = 50;                    // (DBF_TUNE_WAIT_LIMIT_US where that is less)
-constexpr int HELD_SPINS = 1 << 21;                 // (seconds: a wait this long is a mistake; it ends, and the factors are no numbers)
+// Polls of a wait: seconds.  A wait this long is a mistake; it ends, and what it waited for is no number from there on: in all that comes of it, in this
+// workgroup and in those that read its sums.  Every entry of the product a m^T is then no number, or right.
+constexpr int HELD_SPINS = 1 << 21;
 struct HeldSync {                                   // cleared before the launch
     unsigned state, inside, cleared, pad[61];
 };
@@ -450,6 +452,7 @@ struct HeldArgs {
     int rows, cols, iters, n_parts, n_ct;
     int lanes;                                      // a workgroup adds up 4 << lanes columns at a time
     unsigned wait_ticks;                            // of the constant clock, 100 MHz
+    int door_spins, spins;                          // HELD_SPINS: of the wait for all to be in, of the others
 };
 template <class T>
 __device__ __forceinline__ T held_load(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -499,7 +502,7 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
     __shared__ float us[8 * G];
     __shared__ float lengths[HELD_WAVES];
     __shared__ double sums[HELD_WAVES][64], total[2];
-    __shared__ int enter[2];
+    __shared__ int enter[2], any_lost, spins;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rows = A.rows, cols = A.cols, n_parts = A.n_parts;
     HeldSync* const sync = A.sync;
@@ -523,7 +526,7 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
     const auto v_buffer = held_buffer(A.v, 4 * (size_t)cols);
     bool lost = false;   // (a wait has not ended)
     // One wavefront clears a part's words and those of every step-th chunk from there on, and when they are in memory and `times` that many have come from
-    // everyone inside, it has the number of these; 0 if the door was closed before (nothing may be touched then).
+    // everyone inside, it has the number of these, or -1 if they have not come in time; 0 if the door was closed before (nothing may be touched then).
     auto clear = [&](int part, int step) {
         const v4f zero = {0.f, 0.f, 0.f, 0.f};
         for (int col = 4 * lane; col < cols; col += 256) held_store4(partial_of(part), 4 * (unsigned)col, zero);
@@ -542,11 +545,13 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
             __hip_atomic_fetch_add(&sync->cleared, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (ticket == (int)gridDim.x - 1) close();
             const unsigned long long t0 = wall_clock64();
-            for (int spin = 0; spin < HELD_SPINS; ++spin) {
+            bool all = false;
+            for (int spin = 0; spin < A.door_spins && !all; ++spin) {
                 n = (int)held_load(&sync->inside);
-                if (n > 0 && held_load(&sync->cleared) >= (unsigned)(n * times)) break;
+                all = n > 0 && held_load(&sync->cleared) >= (unsigned)(n * times);
                 if (n == 0 && ticket == 0 && wall_clock64() - t0 >= A.wait_ticks) close();
             }
+            if (!all) n = -1;
         }
         return __builtin_amdgcn_readfirstlane(n);
     };
@@ -559,21 +564,28 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
             n = all_cleared(mine, 1);
             if (n > 0 && n < n_parts) {   // the parts and columns of those outside
                 for (int part = mine; part < n_parts; part += n) clear(part, n);
-                all_cleared(mine, 2);
+                n = all_cleared(mine, 2);
             }
         }
         if (lane == 0) {
             enter[0] = mine;
             enter[1] = n;
+            any_lost = 0;
+            spins = A.spins;
         }
     }
     load_part(blockIdx.x);
     __syncthreads();
     const int inside = __builtin_amdgcn_readfirstlane(enter[1]);
     if (inside == 0) return;   // (too late)
+    if (inside < 0) {          // (the others, if they go on, do without its sums: nothing of theirs is a number either)
+        for (int i = tid; i < rows; i += HELD_THREADS) A.a[i] = __builtin_nanf("");
+        for (int j = tid; j < cols; j += HELD_THREADS) A.m[j] = __builtin_nanf("");
+        return;
+    }
     const bool held = inside == n_parts;
     const int ticket = held ? (int)blockIdx.x : __builtin_amdgcn_readfirstlane(enter[0]);   // (all are inside: the part that is in the registers)
-    // 16 bytes of round `it`, once they are there
+    // 16 bytes of round `it`, once they are there; no numbers, of this and all later ones, if they do not come
     auto await4 = [&](__amdgpu_buffer_rsrc_t b, unsigned at, int it) {
         v4f x;
         for (int spin = 0;; ++spin) {
@@ -585,8 +597,12 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
                 const float one = x[e];
                 all = all && __builtin_bit_cast(unsigned, one) >> 31 == (unsigned)(it & 1);
             }
-            if (all || lost) break;
-            lost = spin > HELD_SPINS;
+            if (all) break;
+            lost = lost || spin >= spins;
+            if (lost) {
+                x.x = x.y = x.z = x.w = __builtin_nanf("");
+                break;
+            }
         }
         return (v4f){fabsf(x.x), fabsf(x.y), fabsf(x.z), fabsf(x.w)};
     };
@@ -740,9 +756,10 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
         for (int e = 0; e < 4; ++e) s[1] += (double)v[k][e] * (double)v[k][e];
     if (tid < n_parts) {
         unsigned long long ss = 0;
-        for (int spin = 0; !(ss = held_load(reinterpret_cast<const unsigned long long*>(A.ss + tid))) && !lost; ++spin) lost = spin > HELD_SPINS;
+        for (int spin = 0; !(ss = held_load(reinterpret_cast<const unsigned long long*>(A.ss + tid))) && !lost; ++spin) lost = spin >= spins;
         s[0] = __builtin_bit_cast(double, ss & ~(1ull << 63));
     }
+    if (lost) any_lost = 1;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -758,7 +775,7 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
         total[tid] = sum;
     }
     __syncthreads();
-    const double ssu = total[0], nv = lost ? __builtin_nan("") : sqrt(total[1]);
+    const double ssu = total[0], nv = any_lost ? __builtin_nan("") : sqrt(total[1]);
 #pragma unroll
     for (int k = 0; k < CPL; ++k)
         if (live(k) && (col_of(k) / chunk_cols) % inside == ticket) {
@@ -768,7 +785,7 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
     for (int part = ticket; part < n_parts; part += inside)
         if (tid < 8 * G && row_of(part, tid) < rows) {
             const int row = row_of(part, tid);
-            A.a[row] = ssu != 0. ? (float)(A.u[row] * (nv / ssu)) : 0.f;   // (written by this workgroup)
+            A.a[row] = ssu != 0. || any_lost ? (float)(A.u[row] * (nv / ssu)) : 0.f;   // (written by this workgroup)
         }
 }
 
@@ -946,9 +963,9 @@ void launch_held_any(int groups, const HeldArgs& a, hipStream_t st) {
 }  // namespace
 
 namespace {
-// The projection, and with U the dual behind it.
+// The projection, and with U the dual behind it.  (The polls: of the waits of the one launch.)
 int svid_run(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev, void* workspace_dev, size_t workspace_bytes, float* U,
-             hipStream_t st) {
+             hipStream_t st, int door_spins = HELD_SPINS, int spins = HELD_SPINS) {
     const SvidWorkspace w = svid_workspace(rows, cols);
     const float* Z = static_cast<const float*>(Z_dev);
     uint8_t* base = static_cast<uint8_t*>(workspace_dev);
@@ -976,7 +993,7 @@ int svid_run(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void
     if (const int groups = held_groups(rows, cols); groups && vec_ok && iters >= held_rounds(rows, cols) && workspace_bytes >= w.total) {
         const HeldArgs h = {Z, u, partial, static_cast<float*>(a_dev), static_cast<float*>(m_dev), reinterpret_cast<HeldSync*>(base + w.sync),
                             reinterpret_cast<float*>(base + w.v), reinterpret_cast<double*>(base + w.ss), static_cast<uint8_t*>(bits_dev),
-                            rows, cols, iters, 0, n_ct, 0, 0};
+                            rows, cols, iters, 0, n_ct, 0, 0, door_spins, spins};
         launch_held_any(groups, h, st);
         if (U) dual(false);
         return hipGetLastError() == hipSuccess ? DBF_OK : DBF_EHIP;
@@ -1057,4 +1074,12 @@ extern "C" int dbf_svid(const void* Z_dev, int rows, int cols, int iters, void* 
 int dbf_svid_dual(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev, void* workspace_dev, size_t workspace_bytes,
                   float* U_dev, hipStream_t stream) {
     return svid_run(Z_dev, rows, cols, iters, a_dev, m_dev, bits_dev, workspace_dev, workspace_bytes, U_dev, stream);
+}
+
+int dbf_svid_forced(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev, void* workspace_dev, size_t workspace_bytes,
+                    int door_spins, int spins, void* hip_stream) {
+    if (!held_groups(rows, cols) || iters < held_rounds(rows, cols) || (reinterpret_cast<uintptr_t>(Z_dev) & 15) || (reinterpret_cast<uintptr_t>(m_dev) & 15) ||
+        (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < svid_workspace(rows, cols).total || door_spins < 0 || spins < 0)
+        return DBF_EINVAL;
+    return svid_run(Z_dev, rows, cols, iters, a_dev, m_dev, bits_dev, workspace_dev, workspace_bytes, nullptr, static_cast<hipStream_t>(hip_stream), door_spins, spins);
 }

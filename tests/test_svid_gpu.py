@@ -7,6 +7,8 @@ Tolerance: every entry of a and m is a sum of up to 4096 non-negative fp32 produ
 normalisation; sequential fp32 summation of n positive terms has relative error at most n * 2^-24
 (2.4e-4 at n = 4096), the tree-shaped parts far less, and the errors of one round enter the next
 through well-conditioned positive sums.  The gate is 2e-4 of the largest entry of each vector."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -21,7 +23,7 @@ pytestmark = pytest.mark.gpu
 TOL = 2e-4
 
 
-def _run(Z, iters):
+def _run(Z, iters, **forced):
     rows, cols = Z.shape
     z = torch.from_numpy(Z.copy()).cuda()
     a = torch.full((rows,), float("nan"), dtype=torch.float32, device="cuda")
@@ -30,8 +32,15 @@ def _run(Z, iters):
     bits = torch.full((nb,), 0xA5, dtype=torch.uint8, device="cuda")
     wsb = B.dbf_svid_workspace_bytes(rows, cols)
     ws = torch.full((wsb,), 0xA5, dtype=torch.uint8, device="cuda")
-    B.dbf_svid(z.data_ptr(), rows, cols, iters, a.data_ptr(), m.data_ptr(), bits.data_ptr(), ws.data_ptr(), wsb,
-               G.stream_handle())
+    if forced:
+        p = ctypes.c_void_p
+        fn = B.lib().dbf_svid_forced
+        fn.argtypes = [p, ctypes.c_int, ctypes.c_int, ctypes.c_int, p, p, p, p, ctypes.c_size_t, ctypes.c_int, ctypes.c_int, p]
+        assert fn(z.data_ptr(), rows, cols, iters, a.data_ptr(), m.data_ptr(), bits.data_ptr(), ws.data_ptr(), wsb,
+                  forced.get("door_spins", 1 << 21), forced.get("spins", 1 << 21), G.stream_handle()) == 0
+    else:
+        B.dbf_svid(z.data_ptr(), rows, cols, iters, a.data_ptr(), m.data_ptr(), bits.data_ptr(), ws.data_ptr(), wsb,
+                   G.stream_handle())
     torch.cuda.synchronize()
     words = B.dbf_untile_host(rows, cols, bits.cpu().numpy())
     return a.cpu().numpy().astype(np.float64), m.cpu().numpy().astype(np.float64), words
@@ -136,3 +145,22 @@ def test_svid_rounds_in_one_launch(rows, cols):
         finally:
             B.dbf_tuning_reset()
         assert np.array_equal(a, a0) and np.array_equal(m, m0) and np.array_equal(words, words0)
+
+
+@pytest.mark.parametrize("rows,cols", [(768, 512), (2049, 2052), (1500, 10240)])
+def test_svid_waits_that_run_out_leave_no_wrong_numbers(rows, cols):
+    """All rounds in one launch with a wait of the workgroups, for all to be in or for each other's sums, cut to a few polls (they are seconds long): what was
+    not waited for must not pass for a number.  Every entry of the product of the two factors is right, to the bit, or no number; with no polls at all none is
+    right."""
+    Z = I.make_svid_matrix(rows, cols, I.seed_for(8, 160 + rows + cols))
+    a_ref, m_ref, _ = _run(Z, 6)
+    want = a_ref[:, None] * m_ref[None, :]
+    for wait in ("door_spins", "spins"):
+        for polls in (0, 1, 2, 3, 4, 6, 8, 12, 16, 64):
+            G.say("start svid %dx%d, %s %d" % (rows, cols, wait, polls))
+            a, m, _ = _run(Z, 6, **{wait: polls})
+            got = a[:, None] * m[None, :]
+            none = np.isnan(got)
+            G.say("  %.3f of the entries are no numbers" % np.mean(none))
+            assert np.all(none | (got == want))
+            assert polls > 0 or np.all(none)
