@@ -233,8 +233,8 @@ int dbf_prune_middle(const dbf_layer* layer, const int32_t* keep, int n_keep, db
  *             library (dbf_untile_host turns a host copy into canonical words), padding bits zero.
  *   workspace_dev: device, 256-byte aligned, >= dbf_svid_workspace_bytes(rows, cols) bytes.  (Three, or for less than
  *             12 Mi entries six, rounds and more of a matrix that fits the device's registers are one launch, whose workgroups
- *             exchange sums; it goes on without those that have not started after 50 us, DBF_TUNE_WAIT_LIMIT_US if that is
- *             less.  Without the last 2304 bytes a workspace is taken as well: then every round is a launch.)
+ *             exchange sums; where other work keeps some from starting, the others go on without them once they have waited as
+ *             long as doing their part will take, 100 ms at most.  Without the last 2304 bytes a workspace is taken as well: then every round is a launch.)
  * Asynchronous on hip_stream, allocates nothing; all reductions have a fixed order (results do not
  * depend on scheduling).  Errors: DBF_EINVAL (null / misaligned pointers, sizes out of range,
  * iters < 1), DBF_EWORKSPACE, DBF_EHIP. */
@@ -393,8 +393,7 @@ enum {
     DBF_TUNE_SHARED_MIN_BATCH = 8,    /* smallest batch that takes the once-per-call quantisation, 1..17 (default 2) */
     DBF_TUNE_SHARED_LDS_KB = 9,       /* LDS budget per workgroup for the copied input, 16..64 KiB (default 52)     */
     DBF_TUNE_WAIT_LIMIT_US = 10,      /* bound of the device-side wait in microseconds, 0..10 000 000 (default
-                                         250 000); 0 makes every wait that is not already satisfied give up
-                                         (dbf_svid: goes on without those not waited for, same bits out)             */
+                                         250 000); 0 makes every wait that is not already satisfied give up          */
     /* PLAN knob */
     DBF_TUNE_LONG_ROWS = 11,          /* -1 (default): plans of several layers, most of whose sign bytes are in layers
                                          with one stage input longer than 6144 values and the other longer than 4096,

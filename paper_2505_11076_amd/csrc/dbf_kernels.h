@@ -74,10 +74,10 @@ hipError_t dbf_prune_launch(const dbf_layer* src, dbf_layer* dst, const int* kee
 // What dbf_svid can do with (a launch per round); dbf_svid_workspace_bytes is that or more.
 size_t dbf_svid_least_workspace(int rows, int cols);
 
-// For tests: a call of dbf_svid that is one launch (DBF_EINVAL: it is not), whose workgroups wait `door_spins` polls for
-// all to be in and `spins` for each other's sums.
+// For tests: a call of dbf_svid that is one launch (DBF_EINVAL: it is not), whose first `door` workgroups are let in and
+// wait `door_spins` polls for all of these and `spins` for each other's sums.
 extern "C" int dbf_svid_forced(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev, void* workspace_dev,
-                               size_t workspace_bytes, int door_spins, int spins, void* hip_stream);
+                               size_t workspace_bytes, int door, int door_spins, int spins, void* hip_stream);
 
 // dbf_svid (its arguments checked by the caller) and then the scaled dual of the ADMM update, U = Z - a . Sign(Z) . m^T.
 int dbf_svid_dual(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev, void* workspace_dev, size_t workspace_bytes,

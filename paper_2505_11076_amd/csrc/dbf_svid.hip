@@ -426,16 +426,20 @@ __global__ __launch_bounds__(256) void dbf_svid_signs_kernel(const float* __rest
 // when everyone has read it (who writes sums of round i + 1 has all of v of round i, which nobody publishes without all the sums of round i; who publishes v of
 // round i + 1 has everyone's sums of that round, which nobody forms without v of round i).  So a reader polls the values themselves, and a step from
 // workgroup to workgroup is one way to memory and one back.  (With a flag behind the values: 13.6 us a round of 4096 x 4096.)
-// Who is there: a workgroup takes a ticket and clears its words, and goes on when all have; the last ticket closes the door.  If others keep the device busy, the first one closes it
-// after HELD_WAIT_US: workgroups that come later leave at once, and those inside share out the parts among them, reading Z anew for each part and round.  So
+// Who is there: a workgroup takes a ticket and clears its words, and goes on when all have; the last ticket closes the door.  If others keep the device busy, the first one closes it:
+// workgroups that come later leave at once, and those inside share out the parts among them, reading Z anew for each part and round.  So
 // nobody waits for a workgroup that is not running, and the sums are the same, bit for bit, whoever made them: their order is that of the parts.
+// When: a part of another workgroup takes 1.5 us and its bytes at 75 GB/s, each round.  The door stays open until that, for those inside now, would have been
+// done (HELD_DOOR_US at most): at worst the call takes twice what it would have with the right choice.  4096 x 4096, 8 rounds, with place for 8 at first and for
+// all after 300 us: closed after 50 us 1635 us, so 405, a launch a round 451; with place for 64 throughout 325, 435, 243.  (6 rounds with 1 / 4 / 16 / 64 / 128 / 255
+// inside 9980 / 2270 / 600 / 189 / 140 / 144 us, with all 70.)
 // What bounds it: those steps, two a round.  At 4096 x 4096 7.7 us a round: 1.3 of arithmetic, two
 // steps of 2 to 2.5, the adding up; 24 us besides, 14 of them the one read of Z.  (A launch a round: 13.9 for the read from the last-level cache, 4.1 for the
 // reduction.)
 constexpr int HELD_THREADS = 512, HELD_WAVES = HELD_THREADS / 64;
 constexpr int HELD_PARTS = 256;
 constexpr unsigned HELD_CLOSED = 0x80000000u;
-constexpr int HELD_WAIT_US = 50;                    // (DBF_TUNE_WAIT_LIMIT_US where that is less)
+constexpr int HELD_DOOR_US = 100000;                // (less than HELD_SPINS polls)
 // Polls of a wait: seconds.  A wait this long is a mistake; it ends, and what it waited for is no number from there on: in all that comes of it, in this
 // workgroup and in those that read its sums.  Every entry of the product a m^T is then no number, or right.
 constexpr int HELD_SPINS = 1 << 21;
@@ -451,8 +455,9 @@ struct HeldArgs {
     uint8_t* bits;
     int rows, cols, iters, n_parts, n_ct;
     int lanes;                                      // a workgroup adds up 4 << lanes columns at a time
-    unsigned wait_ticks;                            // of the constant clock, 100 MHz
+    unsigned share_ticks;                           // of the constant clock, 100 MHz: what one part takes those who are without it, all rounds
     int door_spins, spins;                          // HELD_SPINS: of the wait for all to be in, of the others
+    int door;                                       // tickets (n_parts, or fewer in a test: the others are outside)
 };
 template <class T>
 __device__ __forceinline__ T held_load(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -540,16 +545,19 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
         if (lane == 0) {
             auto close = [&] {
                 const unsigned old = __hip_atomic_fetch_or(&sync->state, HELD_CLOSED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (!(old & HELD_CLOSED)) held_store(&sync->inside, old);
+                if (!(old & HELD_CLOSED)) held_store(&sync->inside, std::min(old, (unsigned)A.door));
             };
             __hip_atomic_fetch_add(&sync->cleared, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (ticket == (int)gridDim.x - 1) close();
+            if (ticket == A.door - 1) close();
             const unsigned long long t0 = wall_clock64();
             bool all = false;
             for (int spin = 0; spin < A.door_spins && !all; ++spin) {
                 n = (int)held_load(&sync->inside);
                 all = n > 0 && held_load(&sync->cleared) >= (unsigned)(n * times);
-                if (n == 0 && ticket == 0 && wall_clock64() - t0 >= A.wait_ticks) close();
+                if (n == 0 && ticket == 0) {
+                    const unsigned in = held_load(&sync->state) & ~HELD_CLOSED, share = A.share_ticks * ((n_parts + in - 1) / in);
+                    if (wall_clock64() - t0 >= std::min(share, 100u * HELD_DOOR_US)) close();
+                }
             }
             if (!all) n = -1;
         }
@@ -559,7 +567,7 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
         int mine = 0, n = 0;
         if (lane == 0) mine = (int)__hip_atomic_fetch_add(&sync->state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         mine = __builtin_amdgcn_readfirstlane(mine);
-        if (mine >= 0) {   // (HELD_CLOSED is the sign)
+        if ((unsigned)mine < (unsigned)A.door) {   // (HELD_CLOSED is the sign)
             clear(blockIdx.x, n_parts);
             n = all_cleared(mine, 1);
             if (n > 0 && n < n_parts) {   // the parts and columns of those outside
@@ -935,11 +943,12 @@ inline SvidWorkspace svid_workspace(int rows, int cols) {
 template <int CPL, int G>
 void launch_held(HeldArgs a, hipStream_t st) {
     a.n_parts = (16 * dbf_row_tiles(a.rows) + G - 1) / G;
-    const int n_words = (int)(sizeof(HeldSync) / 8), limit = dbf_tune(DBF_TUNE_WAIT_LIMIT_US);
+    a.door = std::min(a.door, a.n_parts);
+    const int n_words = (int)(sizeof(HeldSync) / 8);
     // 16 or 32 columns to a workgroup at a time, 64 if there are no more than 128 parts: all at once where that does it
     auto chunks = [&](int lanes) { return (a.cols + (4 << lanes) - 1) / (4 << lanes); };
     a.lanes = chunks(2) <= a.n_parts ? 2 : chunks(3) <= a.n_parts || a.n_parts > 128 ? 3 : 4;
-    a.wait_ticks = 100u * (unsigned)(limit < HELD_WAIT_US ? limit : HELD_WAIT_US);
+    a.share_ticks = (unsigned)std::min((long long)a.iters * (150 + 32ll * G * a.cols / 750), 100ll * HELD_DOOR_US);
     hipLaunchKernelGGL(dbf_svid_clear_kernel, dim3((n_words + 255) / 256), dim3(256), 0, st, reinterpret_cast<unsigned long long*>(a.sync), n_words);
     hipLaunchKernelGGL((dbf_svid_held_kernel<CPL, G>), dim3(a.n_parts), dim3(HELD_THREADS), 0, st, a);
 }
@@ -965,7 +974,7 @@ void launch_held_any(int groups, const HeldArgs& a, hipStream_t st) {
 namespace {
 // The projection, and with U the dual behind it.  (The polls: of the waits of the one launch.)
 int svid_run(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev, void* workspace_dev, size_t workspace_bytes, float* U,
-             hipStream_t st, int door_spins = HELD_SPINS, int spins = HELD_SPINS) {
+             hipStream_t st, int door_spins = HELD_SPINS, int spins = HELD_SPINS, int door = HELD_PARTS) {
     const SvidWorkspace w = svid_workspace(rows, cols);
     const float* Z = static_cast<const float*>(Z_dev);
     uint8_t* base = static_cast<uint8_t*>(workspace_dev);
@@ -993,7 +1002,7 @@ int svid_run(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void
     if (const int groups = held_groups(rows, cols); groups && vec_ok && iters >= held_rounds(rows, cols) && workspace_bytes >= w.total) {
         const HeldArgs h = {Z, u, partial, static_cast<float*>(a_dev), static_cast<float*>(m_dev), reinterpret_cast<HeldSync*>(base + w.sync),
                             reinterpret_cast<float*>(base + w.v), reinterpret_cast<double*>(base + w.ss), static_cast<uint8_t*>(bits_dev),
-                            rows, cols, iters, 0, n_ct, 0, 0, door_spins, spins};
+                            rows, cols, iters, 0, n_ct, 0, 0, door_spins, spins, door};
         launch_held_any(groups, h, st);
         if (U) dual(false);
         return hipGetLastError() == hipSuccess ? DBF_OK : DBF_EHIP;
@@ -1077,9 +1086,10 @@ int dbf_svid_dual(const void* Z_dev, int rows, int cols, int iters, void* a_dev,
 }
 
 int dbf_svid_forced(const void* Z_dev, int rows, int cols, int iters, void* a_dev, void* m_dev, void* bits_dev, void* workspace_dev, size_t workspace_bytes,
-                    int door_spins, int spins, void* hip_stream) {
+                    int door, int door_spins, int spins, void* hip_stream) {
     if (!held_groups(rows, cols) || iters < held_rounds(rows, cols) || (reinterpret_cast<uintptr_t>(Z_dev) & 15) || (reinterpret_cast<uintptr_t>(m_dev) & 15) ||
-        (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < svid_workspace(rows, cols).total || door_spins < 0 || spins < 0)
+        (reinterpret_cast<uintptr_t>(workspace_dev) & 255) || workspace_bytes < svid_workspace(rows, cols).total || door < 1 || door_spins < 0 || spins < 0)
         return DBF_EINVAL;
-    return svid_run(Z_dev, rows, cols, iters, a_dev, m_dev, bits_dev, workspace_dev, workspace_bytes, nullptr, static_cast<hipStream_t>(hip_stream), door_spins, spins);
+    return svid_run(Z_dev, rows, cols, iters, a_dev, m_dev, bits_dev, workspace_dev, workspace_bytes, nullptr, static_cast<hipStream_t>(hip_stream), door_spins, spins,
+                    door);
 }

@@ -23,7 +23,25 @@ pytestmark = pytest.mark.gpu
 TOL = 2e-4
 
 
-def _run(Z, iters, **forced):
+def _parts(rows, cols):
+    """Workgroups of the one launch for all rounds; 0: there is none at this size."""
+    wsb = B.dbf_svid_workspace_bytes(rows, cols)
+    up256 = lambda n: (n + 255) // 256 * 256   # noqa: E731
+    groups = 16 * ((rows + 127) // 128)
+    per, cpl = (groups + 255) // 256, (cols + 2047) // 2048
+    chunks = max((rows + 63) // 64, (groups + per - 1) // per)
+    least = up256(4 * rows) + up256(4 * cols) + up256(4 * chunks * cols) + up256(4 * ((cols + 31) // 32 if cols <= 8192 else (cols + 63) // 64))
+    if wsb == least:
+        return 0
+    assert wsb == least + 2304
+    if cpl == 1 and per == 5:
+        per = 6
+    return (groups + per - 1) // per
+
+
+def _run(Z, iters, before=None, **forced):
+    """a, m, sign words; with a wait or the door forced, or something to do `before`, also how many workgroups were inside (the second word of what the
+    one launch keeps in the workspace's last 2304 bytes)."""
     rows, cols = Z.shape
     z = torch.from_numpy(Z.copy()).cuda()
     a = torch.full((rows,), float("nan"), dtype=torch.float32, device="cuda")
@@ -32,18 +50,22 @@ def _run(Z, iters, **forced):
     bits = torch.full((nb,), 0xA5, dtype=torch.uint8, device="cuda")
     wsb = B.dbf_svid_workspace_bytes(rows, cols)
     ws = torch.full((wsb,), 0xA5, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    if before:
+        before()
     if forced:
         p = ctypes.c_void_p
         fn = B.lib().dbf_svid_forced
-        fn.argtypes = [p, ctypes.c_int, ctypes.c_int, ctypes.c_int, p, p, p, p, ctypes.c_size_t, ctypes.c_int, ctypes.c_int, p]
+        fn.argtypes = [p, ctypes.c_int, ctypes.c_int, ctypes.c_int, p, p, p, p, ctypes.c_size_t, ctypes.c_int, ctypes.c_int, ctypes.c_int, p]
         assert fn(z.data_ptr(), rows, cols, iters, a.data_ptr(), m.data_ptr(), bits.data_ptr(), ws.data_ptr(), wsb,
-                  forced.get("door_spins", 1 << 21), forced.get("spins", 1 << 21), G.stream_handle()) == 0
+                  forced.get("door", 256), forced.get("door_spins", 1 << 21), forced.get("spins", 1 << 21), G.stream_handle()) == 0
     else:
         B.dbf_svid(z.data_ptr(), rows, cols, iters, a.data_ptr(), m.data_ptr(), bits.data_ptr(), ws.data_ptr(), wsb,
                    G.stream_handle())
     torch.cuda.synchronize()
     words = B.dbf_untile_host(rows, cols, bits.cpu().numpy())
-    return a.cpu().numpy().astype(np.float64), m.cpu().numpy().astype(np.float64), words
+    out = a.cpu().numpy().astype(np.float64), m.cpu().numpy().astype(np.float64), words
+    return out + (int(ws[-2304:].view(torch.int32)[1]),) if forced or before else out
 
 
 @pytest.mark.parametrize("shape,iters", [(s, i) for s in [(512, 256), (100, 77), (130, 1000), (1000, 129),
@@ -128,8 +150,7 @@ def test_svid_at_the_edges_of_its_reductions(rows, cols):
                                        (4000, 5000), (1000, 8192), (1500, 10240), (300, 12288)])
 def test_svid_rounds_in_one_launch(rows, cols):
     """Six rounds and more: Z in registers, 1 to 5 float4s per thread and row, 8 to 48 rows per workgroup, 16, 32 and 64 columns added up at a time, rows too long for
-    it.  With a wait of nothing the first workgroup goes on with those that are there and they take over the others' rows: the same bits.  Tolerance: as
-    above."""
+    it.  With a door that lets only some of the workgroups in, these take over the others' rows: the same bits.  Tolerance: as above."""
     Z = I.make_svid_matrix(rows, cols, I.seed_for(8, 120 + rows + cols))
     for iters in (6, 7):
         G.say("start svid %dx%d iters=%d" % (rows, cols, iters))
@@ -138,13 +159,37 @@ def test_svid_rounds_in_one_launch(rows, cols):
         assert np.array_equal(words, O.pack_signs(S)), "sign bits differ"
         assert np.max(np.abs(a - a_ref)) <= TOL * np.max(np.abs(a_ref))
         assert np.max(np.abs(m - m_ref)) <= TOL * np.max(np.abs(m_ref))
-        try:
-            B.dbf_tuning_set(B.TUNE_WAIT_LIMIT_US, 0)
-            G.say("  nobody waited for")
-            a0, m0, words0 = _run(Z, iters)
-        finally:
-            B.dbf_tuning_reset()
-        assert np.array_equal(a, a0) and np.array_equal(m, m0) and np.array_equal(words, words0)
+        parts = _parts(rows, cols)
+        assert (parts == 0) == (cols == 12288)
+        for door in [n for n in (1, 3, 60, parts - 1) if 0 < n < parts]:
+            G.say("  %d of %d workgroups inside" % (door, parts))
+            a0, m0, words0, inside = _run(Z, iters, door=door)
+            assert inside == door
+            assert np.array_equal(a, a0) and np.array_equal(m, m0) and np.array_equal(words, words0)
+
+
+def test_svid_waits_for_workgroups_that_a_busy_device_lets_in_late():
+    """248 compute units are busy with another stream's projection, for some 300 us, when a projection of 256 workgroups starts: the eight that find a
+    place would take a millisecond for everyone's rows, so they wait for the others, and all are inside in the end.  (Had they gone on alone, the bits would be
+    the same.)"""
+    rows, cols, iters, busy_rows = 4096, 4096, 8, 3968
+    Z = I.make_svid_matrix(rows, cols, I.seed_for(8, 170))
+    a_ref, m_ref, words_ref = _run(Z, iters)
+    z = torch.from_numpy(Z[:busy_rows].copy()).cuda()
+    f = lambda n: torch.empty(n, dtype=torch.float32, device="cuda")   # noqa: E731
+    a, m, ws = f(busy_rows), f(cols), torch.empty(B.dbf_svid_workspace_bytes(busy_rows, cols), dtype=torch.uint8, device="cuda")
+    bits = torch.empty(B.dbf_tiled_bytes(busy_rows, cols), dtype=torch.uint8, device="cuda")
+    assert _parts(busy_rows, cols) == 248 and _parts(rows, cols) == 256
+    busy = torch.cuda.Stream()
+    G.say("start svid beside a busy device")
+
+    def occupy():
+        B.dbf_svid(z.data_ptr(), busy_rows, cols, 40, a.data_ptr(), m.data_ptr(), bits.data_ptr(), ws.data_ptr(), ws.numel(), busy.cuda_stream)
+
+    a0, m0, words0, inside = _run(Z, iters, before=occupy)
+    G.say("  %d of 256 workgroups inside" % inside)
+    assert np.array_equal(a_ref, a0) and np.array_equal(m_ref, m0) and np.array_equal(words_ref, words0)
+    assert inside == 256
 
 
 @pytest.mark.parametrize("rows,cols", [(768, 512), (2049, 2052), (1500, 10240)])
@@ -158,7 +203,7 @@ def test_svid_waits_that_run_out_leave_no_wrong_numbers(rows, cols):
     for wait in ("door_spins", "spins"):
         for polls in (0, 1, 2, 3, 4, 6, 8, 12, 16, 64):
             G.say("start svid %dx%d, %s %d" % (rows, cols, wait, polls))
-            a, m, _ = _run(Z, 6, **{wait: polls})
+            a, m, _, _ = _run(Z, 6, **{wait: polls})
             got = a[:, None] * m[None, :]
             none = np.isnan(got)
             G.say("  %.3f of the entries are no numbers" % np.mean(none))
