@@ -783,17 +783,19 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
         total[tid] = sum;
     }
     __syncthreads();
-    const double ssu = total[0], nv = any_lost ? __builtin_nan("") : sqrt(total[1]);
+    // (lengths that are no numbers, as in the other last kernels: a is zero and m as it is, no numbers with a Z like that)
+    const double ssu = total[0], nv = sqrt(total[1]);
+    const bool none = any_lost;
 #pragma unroll
     for (int k = 0; k < CPL; ++k)
         if (live(k) && (col_of(k) / chunk_cols) % inside == ticket) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) A.m[col_of(k) + e] = nv != 0. ? (float)(v[k][e] / nv) : v[k][e];
+            for (int e = 0; e < 4; ++e) A.m[col_of(k) + e] = none ? __builtin_nanf("") : nv > 0. ? (float)(v[k][e] / nv) : v[k][e];
         }
     for (int part = ticket; part < n_parts; part += inside)
         if (tid < 8 * G && row_of(part, tid) < rows) {
             const int row = row_of(part, tid);
-            A.a[row] = ssu != 0. || any_lost ? (float)(A.u[row] * (nv / ssu)) : 0.f;   // (written by this workgroup)
+            A.a[row] = none ? __builtin_nanf("") : ssu > 0. ? (float)(A.u[row] * (nv / ssu)) : 0.f;   // (written by this workgroup)
         }
 }
 

@@ -39,7 +39,7 @@ def _parts(rows, cols):
     return (groups + per - 1) // per
 
 
-def _run(Z, iters, before=None, **forced):
+def _run(Z, iters, before=None, less=0, **forced):
     """a, m, sign words; with a wait or the door forced, or something to do `before`, also how many workgroups were inside (the second word of what the
     one launch keeps in the workspace's last 2304 bytes)."""
     rows, cols = Z.shape
@@ -48,7 +48,7 @@ def _run(Z, iters, before=None, **forced):
     m = torch.full((cols,), float("nan"), dtype=torch.float32, device="cuda")
     nb = B.dbf_tiled_bytes(rows, cols)
     bits = torch.full((nb,), 0xA5, dtype=torch.uint8, device="cuda")
-    wsb = B.dbf_svid_workspace_bytes(rows, cols)
+    wsb = B.dbf_svid_workspace_bytes(rows, cols) - less
     ws = torch.full((wsb,), 0xA5, dtype=torch.uint8, device="cuda")
     torch.cuda.synchronize()
     if before:
@@ -166,6 +166,29 @@ def test_svid_rounds_in_one_launch(rows, cols):
             a0, m0, words0, inside = _run(Z, iters, door=door)
             assert inside == door
             assert np.array_equal(a, a0) and np.array_equal(m, m0) and np.array_equal(words, words0)
+
+
+@pytest.mark.parametrize("rows,cols", [(768, 1024), (4096, 3076)])
+@pytest.mark.parametrize("entry", [float("nan"), float("inf"), 0.0, 1e19, 3e-23])
+def test_svid_gives_the_same_outside_the_numbers_whatever_the_launches(rows, cols, entry):
+    """NaN is not supported, but the factors must not depend on how many rounds there are, or on whether these are one launch or, with the
+    workspace's last 2304 bytes left out, a launch each: one entry that is no number or infinite makes a zero and m no numbers; a zero matrix gives zeros; and so on where the
+    squares leave the range.  Tolerance for what are numbers: as above."""
+    Z = I.make_svid_matrix(rows, cols, I.seed_for(8, 175 + rows))
+    if entry == entry and entry < 1e38:
+        Z = (Z * entry).astype(np.float32)
+    else:
+        Z[rows // 2, cols // 3] = entry
+    for iters in (2, 3, 6):
+        G.say("start svid %dx%d %g iters=%d" % (rows, cols, entry, iters))
+        a, m, words = _run(Z, iters)
+        a1, m1, words1 = _run(Z, iters, less=2304)
+        assert np.array_equal(words, words1)
+        for x, y in ((a, a1), (m, m1)):
+            G.say("  %d no numbers, %d zeros of %d" % (np.sum(np.isnan(x)), np.sum(x == 0), x.size))
+            assert np.allclose(x, y, rtol=TOL, atol=0, equal_nan=True)
+        if entry != entry or entry > 1e38:
+            assert np.all(a == 0) and np.all(np.isnan(m))
 
 
 def test_svid_waits_for_workgroups_that_a_busy_device_lets_in_late():
