@@ -28,6 +28,7 @@
 #include "dbf_kernels.h"
 #include "dbf_wave.h"
 
+#include <climits>
 #include <type_traits>
 
 namespace {
@@ -916,10 +917,23 @@ inline int held_groups(int rows, int cols) {
     if (per * cpl > (cpl > 3 ? 5 : 6)) return 0;
     return cpl == 1 && per == 5 ? 6 : per;
 }
+inline int held_parts(int rows, int groups) { return (16 * dbf_row_tiles(rows) + groups - 1) / groups; }
+// 16 or 32 columns to a workgroup at a time, 64 if there are no more than 128 parts: all at once where that does it
+inline int held_chunks(int cols, int lanes) { return (cols + (4 << lanes) - 1) / (4 << lanes); }
+inline int held_lanes(int cols, int parts) { return held_chunks(cols, 2) <= parts ? 2 : held_chunks(cols, 3) <= parts || parts > 128 ? 3 : 4; }
 // From how many rounds on one launch is the faster: its head and end cost more than two or three launches, its rounds less.  us, a launch a
-// round / one launch: 4096 x 4096 3 rounds 53.6 / 47.1, 8 134.6 / 84.1; 2048 x 6144 3 52.8 / 47.4; 3072 x 4000 3 41.8 / 42.8; 3000 x 2048 4 33.7 / 36.0; 768 x 768
-// 6 40.0 / 33.0; 1500 x 4000 6 56.9 / 56.0; 4000 x 900 6 45.9 / 42.8.
-inline int held_rounds(int rows, int cols) { return (long long)rows * cols >= 12 << 20 ? 3 : 6; }
+// round / one launch: 4096 x 4096 3 rounds 54.5 / 47.9, 8 135.6 / 84.9; 2048 x 6144 3 52.7 / 47.6; 1640 x 10240 3 70.7 / 70.0; 1240 x 10240 3 58.4 / 61.7, 4 74.1 / 74.2; 3000 x 2048 6
+// 47.7 / 45.7; 768 x 768 6 37.5 / 32.4; 1500 x 4000 6 56.0 / 56.4, 7 64.6 / 62.9; 4000 x 900 6 45.5 / 41.9.
+// Few parts of long rows have the columns to add up in two or more turns, each as long as the first: two, 256 x 4096 6 46.3 / 47.3, 12 88.7 / 83.9; 384 x 4096 6
+// 46.5 / 50.7, 12 88.9 / 89.8; 512 x 8192 6 60.6 / 64.4, 8 78.5 / 80.9, 12 114.3 / 113.9; 768 x 10240 6 86.0 / 80.7; three, 256 x 6144 6 53.7 / 64.2, 16 133.7 / 149.9; eight,
+// 128 x 8192 6 55.3 / 122.
+inline int held_rounds(int rows, int cols) {
+    const int parts = held_parts(rows, held_groups(rows, cols)), turns = (held_chunks(cols, held_lanes(cols, parts)) + parts - 1) / parts;
+    if (turns > 2) return INT_MAX;
+    if (turns == 2 && parts < 96) return parts < 64 ? 12 : 8;
+    const long long entries = (long long)rows * cols;
+    return entries < 12 << 20 ? 6 : held_cpl(cols) == 5 && entries < 16 << 20 ? 4 : 3;
+}
 struct SvidWorkspace {
     size_t u, v, partial, scalars, least, sync, ss, total;   // `least`: what a call can do with, a launch per round
 };
@@ -944,12 +958,10 @@ inline SvidWorkspace svid_workspace(int rows, int cols) {
 }
 template <int CPL, int G>
 void launch_held(HeldArgs a, hipStream_t st) {
-    a.n_parts = (16 * dbf_row_tiles(a.rows) + G - 1) / G;
+    a.n_parts = held_parts(a.rows, G);
     a.door = std::min(a.door, a.n_parts);
     const int n_words = (int)(sizeof(HeldSync) / 8);
-    // 16 or 32 columns to a workgroup at a time, 64 if there are no more than 128 parts: all at once where that does it
-    auto chunks = [&](int lanes) { return (a.cols + (4 << lanes) - 1) / (4 << lanes); };
-    a.lanes = chunks(2) <= a.n_parts ? 2 : chunks(3) <= a.n_parts || a.n_parts > 128 ? 3 : 4;
+    a.lanes = held_lanes(a.cols, a.n_parts);
     a.share_ticks = (unsigned)std::min((long long)a.iters * (150 + 32ll * G * a.cols / 750), 100ll * HELD_DOOR_US);
     hipLaunchKernelGGL(dbf_svid_clear_kernel, dim3((n_words + 255) / 256), dim3(256), 0, st, reinterpret_cast<unsigned long long*>(a.sync), n_words);
     hipLaunchKernelGGL((dbf_svid_held_kernel<CPL, G>), dim3(a.n_parts), dim3(HELD_THREADS), 0, st, a);

@@ -551,10 +551,10 @@ def test_admm_contraction_meets_the_largest_entry_of_a_line_exactly(q, r):
     assert np.max(np.abs(err)) <= 6 * 2.0 ** -22 / np.sqrt(3 * r)
 
 
-@pytest.mark.parametrize("q,r,iters", [(1, 1, 1), (129, 65, 1), (300, 200, 2), (127, 2052, 8), (2048, 16388, 1)])
+@pytest.mark.parametrize("q,r,iters", [(1, 1, 1), (129, 65, 1), (300, 200, 2), (127, 2052, 8), (300, 2052, 8), (2048, 16388, 1)])
 def test_admm_step_ends_as_the_projection_and_the_dual(q, r, iters):
     """The last kernel of an update forms a' and m' beside U', or after dbf_svid's own last kernel where it has too many
-    workgroups (2048 x 16388), or after all rounds in one launch (8 rounds of 127 x 2052).  Z lies before the
+    workgroups (2048 x 16388), or after all rounds in one launch (8 rounds of 300 x 2052).  Z lies before the
     projection's part at the end of the workspace: dbf_svid of it gives the same signs and, but for sums of squares in
     64 bits in another order, the same a' and m' (rounded to fp32 once or twice: 4 x 2^-24), and U' = Z - a' S' m'^T to
     its two roundings.  m' may start at any multiple of four bytes.  Where that or the one launch takes the rounds to other

@@ -356,3 +356,27 @@ def test_bit_planes_of_a_row_tile_are_dealt_to_idle_compute_units(rec, n, shape,
         rec.lib.dbf_stack_free(stack)
         for l in layers:
             rec.lib.dbf_free(l)
+
+
+@pytest.mark.parametrize("shape,one_launch_from", [
+    ((4096, 4096), 3), ((11008, 4096), None), ((768, 768), 6), ((2048, 10240), 3), ((1240, 10240), 4), ((128, 1024), 6), ((768, 10240), 6),
+    ((512, 8192), 8), ((384, 4096), 12), ((128, 2048), 12), ((256, 6144), None), ((128, 8192), None), ((4096, 4095), None), ((64, 1000), None)])
+def test_the_projection_is_one_launch_where_that_is_the_faster(rec, shape, one_launch_from):
+    """All rounds in one launch from a number of rounds on that depends on the size, never where few workgroups would add up the columns of long rows in
+    more than two turns (128 x 8192: eight); a launch a round with a workspace that has no room for what the one launch needs."""
+    rows, cols = shape
+    rec.lib.dbf_svid_workspace_bytes.restype = C.c_size_t
+    ws = rec.lib.dbf_svid_workspace_bytes(rows, cols)
+
+    def names(iters, less=0):
+        rec.launches()
+        p = C.c_void_p
+        assert rec.lib.dbf_svid(p(4096), rows, cols, iters, p(1 << 30), p(1 << 31), p(1 << 32), p(1 << 20), C.c_size_t(ws - less), None) == 0
+        return _names(rec.launches())
+
+    one = ["dbf_svid_clear", "dbf_svid_held"]
+    for iters in (1, 2, 3, 4, 5, 6, 7, 8, 11, 12, 100):
+        got = names(iters)
+        assert (got == one) == (one_launch_from is not None and iters >= one_launch_from), (iters, got)
+        if got == one:
+            assert "dbf_svid_held" not in names(iters, 2304) and len(names(iters, 2304)) >= 2 * iters + 1
