@@ -90,7 +90,7 @@ constexpr int CH_LD = NB + 4;  // LDS row length of a diagonal block: rows start
 constexpr int CH_THREADS = 512;
 constexpr int CH_MADE = 256;    // more blocks than this: row j first, in a launch of its own
 constexpr int CH_PLANES = 64 * SG_FRAG;   // the two pieces of a 128 x 128 operand: [k / 16][piece][line / 32]
-// T's planes leave fragments of k beyond a line empty: the first of these has its lines' scales.
+// T's planes leave fragments of k beyond a line empty: the first of these has its lines' scales, and behind them what the rows that T's columns meet are multiplied by.
 constexpr int CH_T_UP = (7 * 2 * 4) * SG_FRAG;
 
 struct CholPivot {
@@ -169,7 +169,7 @@ __device__ __forceinline__ void chol_scale_rows(float (&x)[16], float v, std::in
 }
 
 // The same for any pivots, in LDS (64 columns at X) and at leisure, with roots alone: pivots down to subnormal numbers (the instructions take none: a
-// scaled copy) and up to the largest, rows of pivots that are not positive set to zero.  Returns whether there was one of the latter.
+// scaled copy) and up to the largest, rows of pivots that are not positive set to zero.  Returns whether there was one of the latter.  (The diagonal becomes the pivots' roots.)
 __device__ __forceinline__ int chol_rows32_any(volatile float* X, int lane) {
     int bad = 0;
 #pragma unroll 1
@@ -197,7 +197,7 @@ __device__ __forceinline__ int chol_rows32_any(volatile float* X, int lane) {
 constexpr int CH_ROW = 4 * SG_FRAG;
 struct CholBlock {
     // Y: block s of its diagonal in columns 32 s .. + 31; spare: a wavefront's each
-    float H[NB * CH_LD], Y[32 * CH_LD], spare[4][32 * 64], up[2][NB];
+    float H[NB * CH_LD], Y[32 * CH_LD], spare[4][32 * 64], up[2][NB], even[NB];
     uint8_t rows[2][4 * CH_ROW];
     unsigned largest[NB];
 };
@@ -208,8 +208,9 @@ struct CholBlock {
 // of the multiplication; the rows are scaled by 1 / sqrt(pivot) at the end, all roots at once.  What bounds it: a wavefront on its own issues one
 // instruction in four to five cycles, here 13 and one per row below for a pivot, eight where an instruction waits for the one before it.  (32 pivots
 // 4250 cycles, and 1700 for loads, roots and planes.)
+// `even`, unless NULL: the roots of the pivots, rounded down (or up) to powers of two.
 // Returns whether a pivot was not positive.
-__device__ __forceinline__ int chol_rows32(const float* diag, float* right, bool keep, uint8_t* row, float* up, float* spare, int lane) {
+__device__ __forceinline__ int chol_rows32(const float* diag, float* right, bool keep, uint8_t* row, float* up, float* even, float* spare, int lane) {
     const bool upper = lane >= 32;
     const int l32 = lane & 31, h = lane >> 5;
     const float* src = (upper ? right : diag) + l32;
@@ -224,6 +225,8 @@ __device__ __forceinline__ int chol_rows32(const float* diag, float* right, bool
         for (int r = 0; r < 32; ++r) spare[r * 64 + lane] = src[r * CH_LD];
         __builtin_amdgcn_wave_barrier();
         bad = chol_rows32_any(spare, lane);
+        // (zero for a pivot that was not positive, or no number)
+        if (even && lane < 32) even[lane] = __builtin_bit_cast(float, min(max(__builtin_bit_cast(unsigned, spare[65 * lane]) & 0x7f800000u, 27u << 23), 227u << 23));
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[r] = spare[(16 * h + r) * 64 + 32 + l32];
     } else {
@@ -233,6 +236,7 @@ __device__ __forceinline__ int chol_rows32(const float* diag, float* right, bool
             o[r] = __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x[r]), __builtin_bit_cast(unsigned, x[16 + r]), false, false)[1]);
         float y = __builtin_amdgcn_rsqf(piv);
         y = fmaf(0.5f * y, fmaf(-piv * y, y, 1.f), y);
+        if (even && lane < 32) even[lane] = __builtin_bit_cast(float, (254u << 23) - (__builtin_bit_cast(unsigned, y) & 0x7f800000u));
         // lanes 0-15 of y in lanes 0-15 and 16-31, lanes 16-31 in lanes 32-47 and 48-63
         const unsigned yb = __builtin_bit_cast(unsigned, y);
         const unsigned both = __builtin_amdgcn_permlane32_swap(yb, yb, false, false)[0];
@@ -302,7 +306,8 @@ __device__ __forceinline__ void chol_update16(float* d, const uint8_t* P, const 
 }
 
 // One workgroup: the 128 x 128 block H in LDS (upper triangle; identity where it is padded) is factored, and `planes` receives T = R^-T, the inverse of the
-// transposed factor, as an operand whose lines are T's rows.  *fail is raised if a pivot is not positive.  The elimination above, once more, with blocks of
+// transposed factor, as an operand whose lines are T's rows, its columns times powers of two that undo the scales of G's rows: of b_l S m_k a column of T is as large as
+// 1 / m_k, and what is small along a line would have fewer bits (m from 1e-6 to 1e6: Minv met to 9e-5 without, 3e-7 so).  *fail is raised if a pivot is not positive.  The elimination above, once more, with blocks of
 // 32: beside the diagonal block a row has four blocks, those of G, the identity, those of Y, and each of four wavefronts takes the
 // diagonal block and one of them through the pivots (so no product with an inverse follows them); the other four bring rows further down up to date
 // meanwhile.  (On the fp16 matrix cores: a vector instruction waits for an fp32 matrix instruction of another wavefront of its SIMD, 64 cycles each, but not for
@@ -330,7 +335,8 @@ __device__ __forceinline__ void chol_block(CholBlock& lds, uint8_t* __restrict__
 #pragma unroll 1
     for (int s = 0; s < 4; ++s) {
         if (w < 4) {
-            bad |= chol_rows32(lds.H + 32 * s * CH_LD + 32 * s, blk(s, w), w <= s, lds.rows[s & 1] + w * CH_ROW, lds.up[s & 1] + 32 * w, lds.spare[w], lane);
+            bad |= chol_rows32(lds.H + 32 * s * CH_LD + 32 * s, blk(s, w), w <= s, lds.rows[s & 1] + w * CH_ROW, lds.up[s & 1] + 32 * w, w == 0 ? lds.even + 32 * s : nullptr,
+                               lds.spare[w], lane);
         } else if (s > 0) {
             // what row s - 1 takes from the rows i > s, columns c >= i (G) and c < s (Y, which starts at c = s - 1)
             int n = 0;
@@ -355,10 +361,11 @@ __device__ __forceinline__ void chol_block(CholBlock& lds, uint8_t* __restrict__
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
         if (n > ib) continue;
-        const float* at = blk(ib, n) + l32 * CH_LD + 16 * (w >> 2) + 8 * h;
+        const int k = 16 * (w >> 2) + 8 * h;
+        const float *at = blk(ib, n) + l32 * CH_LD + k, *even = lds.even + 32 * n + k;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            x[n][e] = at[e];
+            x[n][e] = at[e] * even[e];
             mx = fmaxf(mx, fabsf(x[n][e]));
         }
     }
@@ -370,7 +377,11 @@ __device__ __forceinline__ void chol_block(CholBlock& lds, uint8_t* __restrict__
         if (n > ib) continue;
         sg_store2(planes + ((2 * n + (w >> 2)) * 8 + ib) * SG_FRAG + lane * 16, x[n], scale);
     }
-    if (w < 4 && lane < 32) reinterpret_cast<float*>(planes + CH_T_UP)[32 * ib + l32] = scale.up;
+    if (w < 4 && lane < 32) {
+        float* const scales = reinterpret_cast<float*>(planes + CH_T_UP) + 32 * ib + l32;
+        scales[0] = scale.up;
+        scales[NB] = __builtin_bit_cast(float, (254u << 23) - __builtin_bit_cast(unsigned, lds.even[32 * ib + l32]));
+    }
 }
 
 // ---- C = B^T W beside the elimination ------------------------------------------------------------------------------------------
@@ -531,9 +542,15 @@ __device__ __forceinline__ void chol_load_block(const float* __restrict__ G, int
         for (int b = 0; b < 4; ++b) x[b][e] = base[at + col[b]];
     }
 }
+// What its rows are multiplied by, as T's columns have been divided.
+__device__ __forceinline__ void chol_load_even(const uint8_t* __restrict__ t_planes, float (&even)[8]) {
+    const float* at = reinterpret_cast<const float*>(t_planes + CH_T_UP) + NB + 16 * (threadIdx.x >> 6) + 8 * ((threadIdx.x & 63) >> 5);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) even[e] = at[e];
+}
 // ... into planes.  (Block (j, j) stands for Y's, where the product with the identity is T.)  Two barriers are the caller's: one between the
 // zeros of s.g_largest and this, one behind it.
-__device__ __forceinline__ void chol_split_block(float (&x)[4][8], int q, int j, int c, uint8_t* planes, CholScales& s) {
+__device__ __forceinline__ void chol_split_block(float (&x)[4][8], const float (&even)[8], int q, int j, int c, uint8_t* planes, CholScales& s) {
     const int lane = threadIdx.x & 63, l32 = lane & 31, h = lane >> 5, w = threadIdx.x >> 6;
     if (c == j || NB * (c + 1) > q || NB * (j + 1) > q) {
 #pragma unroll
@@ -548,7 +565,10 @@ __device__ __forceinline__ void chol_split_block(float (&x)[4][8], int q, int j,
     for (int b = 0; b < 4; ++b) {
         float mx = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(x[b][e]));
+        for (int e = 0; e < 8; ++e) {
+            x[b][e] *= even[e];
+            mx = fmaxf(mx, fabsf(x[b][e]));
+        }
         atomicMax(&s.g_largest[32 * b + l32], __builtin_bit_cast(unsigned, mx));
     }
     __syncthreads();
@@ -621,7 +641,8 @@ __device__ __forceinline__ void chol_make_block(const v8h (&t)[8][2], const floa
         const int line = 32 * (c0 + b) + l32;
         const SgScale scale = sg_scale(__builtin_bit_cast(float, s.p_largest[line]));
         if (rb == 0 && h == 0) {
-            // (the columns' own scales have been left out so far.  T is an inverse root of G, from 2^-64 to 2^75: the sums times its scales are normal numbers)
+            // (the columns' own scales have been left out so far.  A line of T has an entry from 1/2 to 2 on the diagonal, and its largest is not far from
+            // that: the sums times its scales are normal numbers)
             const float all = scale.up * sg_scale(__builtin_bit_cast(float, s.g_largest[line])).up;
             if (up) up[line] = all;
             if (rows) reinterpret_cast<float*>(rows + sg_scales_at(2, q, q))[(size_t)j * sg_lines(q) + NB * c + line] = all;
@@ -672,7 +693,7 @@ __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool diag = i == c;
     v8h t[8][2];
-    float x[4][8], y[4][8], up_or_t;
+    float x[4][8], y[4][8], even[8], up_or_t;
     if (MADE) {
         const SgOperand P = sg_operand(rows, 2, q, q, i, j), Q = sg_operand(rows, 2, q, q, c, j);
 #pragma unroll
@@ -685,6 +706,7 @@ __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     } else {
         chol_load_block(G, q, j, i, x);
         chol_load_t(t_planes, t);
+        chol_load_even(t_planes, even);
         (&T.s[0].g_largest[0])[tid] = 0;
         up_or_t = reinterpret_cast<const float*>(t_planes + CH_T_UP)[tid & (NB - 1)];
     }
@@ -714,10 +736,10 @@ __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         if (diag) load_old(y); else chol_load_block(G, q, j, c, y);
         __syncthreads();
         if (tid < NB) T.t_up[tid] = up_or_t;
-        chol_split_block(x, q, j, i, T.g, T.s[0]);
+        chol_split_block(x, even, q, j, i, T.g, T.s[0]);
         chol_make_block(t, T.t_up, T.g, T.p, T.up[0], T.s[0], nullptr, q, j, i);
         if (!diag) {   // (everyone is done with the planes in T.g; the second's take the place of what they are made from)
-            chol_split_block(y, q, j, c, T.g, T.s[1]);
+            chol_split_block(y, even, q, j, c, T.g, T.s[1]);
             load_old(y);
             chol_make_block(t, T.t_up, T.g, T.g, T.up[1], T.s[1], i == j + 1 && c <= j ? rows : nullptr, q, j, c);
         }
@@ -799,13 +821,14 @@ __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     __shared__ CholScales s;
     const int c = blockIdx.x;
     v8h t[8][2];
-    float x[4][8];
+    float x[4][8], even[8];
     chol_load_block(G, q, j, c, x);
     chol_load_t(t_planes, t);
+    chol_load_even(t_planes, even);
     if (threadIdx.x < 2 * NB) (&s.g_largest[0])[threadIdx.x] = 0;
     if (threadIdx.x < NB) t_up[threadIdx.x] = reinterpret_cast<const float*>(t_planes + CH_T_UP)[threadIdx.x];
     __syncthreads();
-    chol_split_block(x, q, j, c, g, s);
+    chol_split_block(x, even, q, j, c, g, s);
     chol_make_block(t, t_up, g, nullptr, nullptr, s, rows, q, j, c);
 }
 

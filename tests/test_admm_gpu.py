@@ -475,6 +475,47 @@ def test_admm_contraction_between_a_large_and_a_small_operand(q, r, exponent):
     assert np.all(np.isfinite(got)) and np.all(err <= gate)
 
 
+def _scaled_error(p, q, m2, rho, seed):
+    """Minv from the device against 64 bits, entries relative to the roots of their diagonal entries: the largest error, its norm over Minv's, and the condition
+    of B^T B + rho I with its diagonal scaled to one."""
+    rng = np.random.default_rng(seed)
+    S = np.where(rng.random((q, p)) < 0.5, -1.0, 1.0)
+    b, W = (rng.uniform(0.5, 1.5, p) / np.sqrt(p)).astype(np.float32), rng.standard_normal((p, 16)).astype(np.float32)
+    bits = torch.from_numpy(B.dbf_tile_host(q, p, O.pack_signs(S)).copy()).cuda()
+    dev = [torch.from_numpy(x.copy()).cuda() for x in (m2, b, W)]
+    Minv, Cm = torch.empty((q, q), device="cuda"), torch.empty((q, 16), device="cuda")
+    flag = torch.full((1,), 77, dtype=torch.int32, device="cuda")
+    wsb = B.dbf_admm_prepare_workspace_bytes(p, q, 16)
+    ws = torch.full((wsb,), 0xA5, dtype=torch.uint8, device="cuda")
+    B.dbf_admm_prepare(bits.data_ptr(), dev[0].data_ptr(), dev[1].data_ptr(), dev[2].data_ptr(), p, q, 16, rho, Minv.data_ptr(), Cm.data_ptr(),
+                       ws.data_ptr(), wsb, flag.data_ptr(), G.stream_handle())
+    torch.cuda.synchronize()
+    assert int(flag.item()) == 0
+    Bt = m2.astype(np.float64)[:, None] * (S * b.astype(np.float64))
+    A = Bt @ Bt.T + float(np.float32(rho)) * np.eye(q)
+    s = 1 / np.sqrt(np.diag(A))
+    A *= s[:, None] * s
+    values = np.linalg.eigvalsh(A)
+    want = np.linalg.inv(A)
+    got = Minv.cpu().numpy().astype(np.float64) / (s[:, None] * s)
+    d = 1 / np.sqrt(np.diag(want))
+    err = (got - want) * d[:, None] * d
+    return np.max(np.abs(err)), np.linalg.norm(err) / np.linalg.norm(want * d[:, None] * d), values[-1] / values[0]
+
+
+@pytest.mark.parametrize("p,q", [(400, 100), (2000, 500), (5400, 2830)])
+@pytest.mark.parametrize("decades", [2, 6, 8])
+def test_admm_prepare_with_scales_of_many_magnitudes(p, q, decades):
+    """m2 from 10^-d to 10^d and rho far below all of it: an elimination in floating point does not feel the scales of rows and columns, so the error, entries
+    relative to the roots of their diagonal entries, stays that of the problem with its diagonal scaled to one: about its condition times the roundings of
+    q numbers that add up at random, 2^-24 sqrt(q).  (2830: block rows made first.)"""
+    rng = np.random.default_rng(I.seed_for(6, 940 + q + decades))
+    m2 = (10 ** rng.uniform(-decades, decades, q)).astype(np.float32)
+    worst, norm, cond = _scaled_error(p, q, m2, 10.0 ** (-2 * decades - 9), I.seed_for(6, 941 + q + decades))
+    G.say("  scales of %d decades p=%d q=%d: largest error %.2e, of the norm %.2e, condition %.1f" % (2 * decades, p, q, worst, norm, cond))
+    assert worst <= 2.0 ** -24 * np.sqrt(q) * cond
+
+
 @pytest.mark.parametrize("q", [40, 200])
 def test_admm_prepare_with_subnormal_pivots(q):
     """Pivots below 2^-126, where the reciprocal and root instructions take none: G = B^T B + rho I with rho = 9e-39 and B^T B a
