@@ -710,10 +710,10 @@ __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
         (&T.s[0].g_largest[0])[tid] = 0;
         up_or_t = reinterpret_cast<const float*>(t_planes + CH_T_UP)[tid & (NB - 1)];
     }
-    // this wavefront's two blocks of 32 x 32: side by side, or of a diagonal block's upper ten the w-th and, for two wavefronts, one more
-    auto upper = [](int n) { return n < 4 ? n : n < 7 ? 4 + n - 3 : n < 9 ? 8 + n - 5 : 15; };
-    const int b0 = diag ? upper(w) : 4 * (w & 3) + 2 * (w >> 2), b1 = diag ? upper(min(w + 8, 9)) : b0 + 1;
-    const bool two = !diag || w < 2;
+    // this wavefront's two blocks of 32 x 32: side by side; or of a diagonal block's upper ten, whose four on the diagonal have one product more, one or two, so that
+    // the two wavefronts of a SIMD have two of these or three others
+    const int b0 = diag ? 0x62f531a0u >> 4 * w & 15 : 4 * (w & 3) + 2 * (w >> 2), b1 = diag ? (w == 2 ? 7 : 11) : b0 + 1;
+    const bool two = !diag || w == 2 || w == 3;
     auto row_of = [&](int b, int v) { return 32 * (b >> 2) + 8 * (v >> 2) + 4 * h + (v & 3); };
     auto col_of = [&](int b) { return 32 * (b & 3) + l32; };
     float* const Gi = G + (size_t)(NB * i) * q;
@@ -768,6 +768,13 @@ __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
             if (diag) frag(P, b1 >> 2, a);
             frag(Q, b1 & 3, b);
             product(1, a, b);
+        }
+    }
+    if (diag && b0 % 5 == 0) {   // (lines meet themselves: l l is of one sign there, and left out it would be lost from all of a diagonal)
+#pragma unroll
+        for (int kb = 0; kb < NB / 16; ++kb) {
+            const v8h l = *reinterpret_cast<const v8h*>(P + ((kb * 2 + 1) * 4 + (b0 >> 2)) * SG_FRAG);
+            low[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(l * (_Float16)(1.f / SG_LOW), l, low[0], 0, 0, 0);
         }
     }
     const float *up = T.up[0], *uq = T.up[diag ? 0 : 1];
