@@ -82,13 +82,15 @@ __global__ __launch_bounds__(256) void dbf_admm_operands_kernel(const float* __r
 // only.  A finished row of Y is written as the fp16 planes that the last contraction reads; R is kept nowhere.
 // What bounds it: the chain.  Per block row a launch of 22 us at q = 2048: 2 to the loads' arrival, 6 to the diagonal block, four times 2.5 for 32 pivots and
 // 0.4 for the next row's share of them, 0.7 for T.  (As two launches, a panel of 6 us and an update of 24 whose chain held an inverse's product behind each 32
-// pivots, the constants took 744 us with p = r = 4096; so 627.)  Blocks that fill the chip more than once make row j too often: from 256 blocks on
+// pivots, the constants took 744 us with p = r = 4096; so 627.)  Blocks that fill the chip more than once make row j too often: for more than 256 blocks
 // dbf_chol_panel_kernel makes it first (q = 3328 870 us without, 819 so; 4096 with p = r = 4096 1681, 1484).
 // ---------------------------------------------------------------------------------------------
 constexpr int NB = 128;        // block size: the contraction's tile
 constexpr int CH_LD = NB + 4;  // LDS row length of a diagonal block: rows start on 16 bytes
 constexpr int CH_THREADS = 512;
+constexpr int CH_UNITS = 256;   // compute units
 constexpr int CH_MADE = 256;    // more blocks than this: row j first, in a launch of its own
+static_assert(CH_MADE >= CH_UNITS, "a launch with parts of C beside it (chol_free) makes row j itself");
 constexpr int CH_PLANES = 64 * SG_FRAG;   // the two pieces of a 128 x 128 operand: [k / 16][piece][line / 32]
 // T's planes leave fragments of k beyond a line empty: the first of these has its lines' scales, and behind them what the rows that T's columns meet are multiplied by.
 constexpr int CH_T_UP = (7 * 2 * 4) * SG_FRAG;
@@ -681,7 +683,7 @@ __global__ __launch_bounds__(CH_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2
     };
     __shared__ __align__(16) uint8_t lds[sizeof(Tiles) > sizeof(CholBlock) ? sizeof(Tiles) : sizeof(CholBlock)];
     Tiles& T = *reinterpret_cast<Tiles*>(lds);
-    if (!MADE && blockIdx.x >= gridDim.x - beside.count) {   // (launches with room for parts have fewer than 256 blocks)
+    if (!MADE && blockIdx.x >= gridDim.x - beside.count) {   // (launches with room for parts have fewer than CH_UNITS blocks)
         chol_beside(beside, blockIdx.x - (gridDim.x - beside.count));
         return;
     }
@@ -924,7 +926,7 @@ inline long long chol_blocks(int nblk, int j) {
     return (long long)below * (below + 1) / 2 + (long long)below * (j + 1);
 }
 // The compute units that a launch of this many workgroups leaves.
-inline long long chol_free(long long blocks) { return blocks < 256 ? 256 - blocks : 0; }
+inline long long chol_free(long long blocks) { return blocks < CH_UNITS ? CH_UNITS - blocks : 0; }
 // How much of C is made beside the elimination: as many block columns, from the last one down, as its launches have room for.
 struct CholPlan {
     int columns, steps, parts;

@@ -380,3 +380,36 @@ def test_the_projection_is_one_launch_where_that_is_the_faster(rec, shape, one_l
         assert (got == one) == (one_launch_from is not None and iters >= one_launch_from), (iters, got)
         if got == one:
             assert "dbf_svid_held" not in names(iters, 2304) and len(names(iters, 2304)) >= 2 * iters + 1
+
+
+@pytest.mark.parametrize("p,q,r", [(4096, 2048, 4096), (768, 768, 768), (11008, 1500, 4096), (300, 130, 200), (4096, 4096, 4096), (1024, 2830, 9000),
+                                   (2100, 300, 1000), (1100, 200, 16600), (8192, 2880, 16384)])
+def test_all_parts_of_C_are_made_and_none_beside_a_row_that_is_there(rec, p, q, r):
+    """The elimination's launches have a workgroup per block below a row and, up to 256 in all, one per part of C = B^T W; rows of more blocks are made in a launch of
+    their own and have no parts beside them.  All parts of the blocks that the contraction's launch leaves out are among them."""
+    P = C.c_void_p
+    rec.lib.dbf_admm_prepare_workspace_bytes.restype = C.c_size_t
+    ws = rec.lib.dbf_admm_prepare_workspace_bytes(p, q, r)
+    rec.launches()
+    assert rec.lib.dbf_admm_prepare(*[P(n << 32) for n in (1, 2, 3, 4)], p, q, r, C.c_float(1.0), P(5 << 32), P(6 << 32), P(7 << 32), C.c_size_t(ws), P(8 << 32), None) == 0
+    launches = rec.launches()
+    n, columns = (q + 127) // 128, (r + 127) // 128
+    chunks = (p + 127) // 128
+    parts_made = blocks_of_row = 0
+    row = 0
+    for (name, grid, _, _), full in zip(launches, rec.full_names):
+        if name == "dbf_chol_first":
+            parts_made += grid[0] - 1
+            assert grid[0] <= 256
+        elif name == "dbf_chol_row":
+            below = n - 1 - row
+            blocks = below * (below + 1) // 2 + below * (row + 1)
+            made = "ILb1E" in full
+            assert made == (blocks > 256)
+            assert grid[0] == blocks if made else blocks <= grid[0] <= 256
+            parts_made += grid[0] - blocks
+            row += 1
+    assert row == n - 1
+    gemms = [grid for name, grid, _, _ in launches if name == "dbf_split_gemm"]
+    beside = columns - (gemms[1][1] if len(gemms) == 3 else 0)   # (B^T B, C, Y^T Y)
+    assert len(gemms) in (2, 3) and parts_made == beside * n * ((chunks + 7) // 8)
