@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256) void dbf_split_signs_kernel(const uint8_t* __r
 // rs[i] * cs[j] * sum_k P[k][i] Q[k][j] + (i == j ? diag : 0).  Workgroup = 128 x 128 outputs (BI = 2; BI = 1: 64 x 128), 4
 // wavefronts of 64 x 64 (2 x 2 blocks of 32 x 32: 64 registers for each of the three sums; BI = 1: 32 x 64), 16 values of k per step:
 // 12 matrix instructions of 32 cycles per wavefront (8 with PA = 1) against 8 (6) LDS reads of 1 KiB.  A step's 16 (12) KiB come straight
-// from memory into one of four LDS buffers, three steps ahead, one barrier per step; two workgroups per compute unit cover each
+// from memory into one of four LDS buffers, three steps ahead (two where the next step's operands are read early: AHEAD), one barrier per step; two workgroups per compute unit cover each
 // other's barriers.  A chunk's last products are made block by block, each block being scaled and added to the total while the next is multiplied.
 // KS = 2: eight wavefronts, two such halves that take every other chunk and add up through LDS at the end.
 // What bounds it: the matrix pipes, at the rate that a plain bf16 product of 8192^3 reaches on the same card (1.24 PFLOP/s).  2048 x 4096
@@ -553,8 +553,6 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(2, 2))
 // themselves.  us, the constants (p = r = 768), 64 x 128 with 512 threads / with 256 / 128 x 128 with 512 / with 256: q = 1536 (78 blocks) 417 / 424 / 432 / 440,
 // 2048 (136) 557 / 562 / 570 / 582, 2560 (210) 703 / 711 / 718 / 732, 2944 (276) 811 / 816 / 826 / 842, 3328 (351) 940 / 939 / 949 / 969,
 // 3712 (435) 1063 / 1054 / 1062 / 1085, 4096 (528) 1166 / 1149 / 1155 / 1180.
-// (Blocks of the upper triangle go to the compute dies as they come, column by column, not in bands as the full grid's: for B^T B, q = 2048, p = 4096,
-// 29 % of the reads hit L2, where the banded launches have 79 to 84 %.  A banded order of the triangle has not been measured.)
 // (`columns`: only the first so many blocks of each row.  `beside`: planes to be made by further workgroups, where there are idle compute units for them; returns
 // how many times 64 lines are.)
 template <int PA>

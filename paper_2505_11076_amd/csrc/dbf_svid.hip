@@ -909,7 +909,9 @@ int launch_round(bool first, hipStream_t st, const RoundArgs& a) {
     return n_wg;
 }
 // Whether the rounds run in one launch: groups of eight rows per part, or 0.  (16-byte pieces; at most 192 values a thread, 160
-// of long rows.  Less than 64 K entries: too little for a workgroup on each of a few compute units.)
+// of long rows.  Less than 64 K entries: too little for a workgroup on each of a few compute units.  With 160 and more the compiler keeps 9 to 32 registers
+// of a thread in scratch; a launch a round is the slower there too, us, a launch a round / one launch: 12288 x 2048 6 rounds 126.1 / 77.8, 6144 x 4096 3 68.4 / 62.0,
+// 3000 x 6144 3 68.7 / 55.7, 2048 x 10240 3 77.2 / 73.7, 8 177.5 / 145.5.)
 inline int held_cpl(int cols) { return (cols + 4 * HELD_THREADS - 1) / (4 * HELD_THREADS); }
 inline int held_groups(int rows, int cols) {
     if ((cols & 3) || (long long)rows * cols < 1 << 16 || cols > 24576 || rows > 1 << 15) return 0;
