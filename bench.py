@@ -734,6 +734,25 @@ def prune_bench(B, I, torch, np):
     return res
 
 
+def svid_passes(rows, cols, iters):
+    """Passes that the library makes over Z, whose rows start on 16 bytes where cols is a multiple of four: one where all rounds are one launch, else one or
+    two a round by the length of the rows, and one for the signs where the first does not write them."""
+    ceil = lambda a, b: -(-a // b)  # noqa: E731
+    vec, groups, quads = cols % 4 == 0, 16 * ceil(rows, 128), ceil(cols, 2048)
+    per = ceil(groups, 256)
+    if vec and rows * cols >= 1 << 16 and cols <= 24576 and rows <= 1 << 15 and per * quads <= (5 if quads > 3 else 6):
+        parts = ceil(groups, 6 if quads == 1 and per == 5 else per)
+        columns = 16 if ceil(cols, 16) <= parts else 32 if ceil(cols, 32) <= parts or parts > 128 else 64
+        turns = ceil(ceil(cols, columns), parts)
+        if turns == 2 and parts < 96:
+            least = 12 if parts < 64 else 8
+        else:
+            least = 6 if rows * cols < 12 << 20 else 4 if quads == 5 and rows * cols < 16 << 20 else 3
+        if turns <= 2 and iters >= least:
+            return 1
+    return iters * (1 if ceil(cols, 4096) <= (6 if vec else 3) else 2) + (0 if vec and cols <= 4096 else 1)
+
+
 def svid_bench(B, I, torch, np, stream, proto, iters=8):
     """dbf_svid (signs + `iters` rounds of power iteration) on two factor-sized fp32 matrices.  Bytes:
     Z is read once for the signs and twice per round (row dots, column dots); the packed signs and
@@ -754,12 +773,8 @@ def svid_bench(B, I, torch, np, stream, proto, iters=8):
         from oracle import dbf_oracle as O
         O.svid(Z.astype(np.float64), iters)
         cpu_s = time.time() - t0
-        # (the library makes both products of a round in ONE pass over Z for rows of at most 24576 values, and up to 4096 the
-        #  signs in the first of them; the algorithmic bytes above keep the two-pass count, so the rate on them can pass the peak)
-        one_pass = cols <= 24576 and cols % 4 == 0
-        passes = (iters if cols <= 4096 else iters + 1) if one_pass else (2 * iters + 1)
-        if one_pass and rows <= 1 << 15 and rows * cols <= 20 << 20 and iters >= 6:
-            passes = 1   # (Z stays in registers from round to round)
+        # (the algorithmic bytes above keep the two-pass count, so the rate on them can pass the peak)
+        passes = svid_passes(rows, cols, iters)
         res["%dx%d_iters%d" % (rows, cols, iters)] = {
             "ms_per_call": round(ms, 4), "algorithmic_bytes": nbytes, "GBps": round(nbytes / (ms * 1e-3) / 1e9, 1),
             "frac_of_hbm_peak": round(nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),

@@ -382,6 +382,30 @@ def test_the_projection_is_one_launch_where_that_is_the_faster(rec, shape, one_l
             assert "dbf_svid_held" not in names(iters, 2304) and len(names(iters, 2304)) >= 2 * iters + 1
 
 
+def test_the_benchmark_counts_the_passes_over_Z_that_the_projection_makes(rec):
+    """bench.py's own statement of the rules against the launches of the calls: one kernel that reads Z is one pass."""
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("bench_under_test", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    rec.lib.dbf_svid_workspace_bytes.restype = C.c_size_t
+    rng = np.random.default_rng(3)
+    shapes = [(4096, 4096), (11008, 4096), (16384, 1024), (8192, 2500), (6144, 4096), (10240, 2048), (12288, 2048), (77, 24580), (50, 12288), (50, 12289)]
+    shapes += [tuple(int(np.exp(rng.uniform(0, np.log(n)))) for n in (40000, 30000)) for _ in range(150)]
+    shapes += [(128 * int(rng.integers(1, 100)) - int(rng.integers(0, 2)), 4 * int(rng.integers(1, 3000))) for _ in range(300)]
+    one = 0
+    for rows, cols in shapes:
+        ws = rec.lib.dbf_svid_workspace_bytes(rows, cols)
+        for iters in (1, 2, 3, 4, 6, 8, 12):
+            rec.launches()
+            p = C.c_void_p
+            assert rec.lib.dbf_svid(p(4096), rows, cols, iters, p(1 << 40), p(2 << 40), p(3 << 40), p(4 << 40), C.c_size_t(ws), None) == 0
+            reads = [n for n in _names(rec.launches()) if n in ("dbf_svid_held", "dbf_svid_round", "dbf_svid_row_dots", "dbf_svid_col_dots", "dbf_svid_signs")]
+            assert bench.svid_passes(rows, cols, iters) == len(reads), (rows, cols, iters, reads)
+            one += reads == ["dbf_svid_held"]
+    assert one > 300
+
+
 @pytest.mark.parametrize("p,q,r", [(4096, 2048, 4096), (768, 768, 768), (11008, 1500, 4096), (300, 130, 200), (4096, 4096, 4096), (1024, 2830, 9000),
                                    (2100, 300, 1000), (1100, 200, 16600), (8192, 2880, 16384)])
 def test_all_parts_of_C_are_made_and_none_beside_a_row_that_is_there(rec, p, q, r):
