@@ -431,7 +431,8 @@ __global__ __launch_bounds__(256) void dbf_svid_signs_kernel(const float* __rest
 // workgroups that come later leave at once, and those inside share out the parts among them, reading Z anew for each part and round.  So
 // nobody waits for a workgroup that is not running, and the sums are the same, bit for bit, whoever made them: their order is that of the parts.
 // When: a part of another workgroup takes 1.5 us and its bytes at 75 GB/s, each round.  The door stays open until that, for those inside now, would have been
-// done (HELD_DOOR_US at most): at worst the call takes twice what it would have with the right choice.  4096 x 4096, 8 rounds, with place for 8 at first and for
+// done (HELD_DOOR_US at most, twice that in all), and a fourth of it from when the last one came in, for the others may be right behind: unless they come
+// one by one, the call takes about twice what it would have with the right choice at worst.  4096 x 4096, 8 rounds, with place for 8 at first and for
 // all after 300 us: closed after 50 us 1635 us, so 405, a launch a round 451; with place for 64 throughout 325, 435, 243.  (6 rounds with 1 / 4 / 16 / 64 / 128 / 255
 // inside 9980 / 2270 / 600 / 189 / 140 / 144 us, with all 70.)
 // What bounds it: those steps, two a round.  At 4096 x 4096 7.7 us a round: 1.3 of arithmetic, two
@@ -440,7 +441,7 @@ __global__ __launch_bounds__(256) void dbf_svid_signs_kernel(const float* __rest
 constexpr int HELD_THREADS = 512, HELD_WAVES = HELD_THREADS / 64;
 constexpr int HELD_PARTS = 256;
 constexpr unsigned HELD_CLOSED = 0x80000000u;
-constexpr int HELD_DOOR_US = 100000;                // (less than HELD_SPINS polls)
+constexpr int HELD_DOOR_US = 100000;                // (twice this is less than HELD_SPINS polls)
 // Polls of a wait: seconds.  A wait this long is a mistake; it ends, and what it waited for is no number from there on: in all that comes of it, in this
 // workgroup and in those that read its sums.  Every entry of the product a m^T is then no number, or right.
 constexpr int HELD_SPINS = 1 << 21;
@@ -551,13 +552,18 @@ __global__ __launch_bounds__(HELD_THREADS) __attribute__((amdgpu_waves_per_eu(2,
             __hip_atomic_fetch_add(&sync->cleared, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (ticket == A.door - 1) close();
             const unsigned long long t0 = wall_clock64();
+            unsigned long long last = t0;   // when someone came in, and how many that made
+            unsigned seen = 0;
             bool all = false;
             for (int spin = 0; spin < A.door_spins && !all; ++spin) {
                 n = (int)held_load(&sync->inside);
                 all = n > 0 && held_load(&sync->cleared) >= (unsigned)(n * times);
-                if (n == 0 && ticket == 0) {
-                    const unsigned in = held_load(&sync->state) & ~HELD_CLOSED, share = A.share_ticks * ((n_parts + in - 1) / in);
-                    if (wall_clock64() - t0 >= std::min(share, 100u * HELD_DOOR_US)) close();
+                if (n == 0 && ticket == 0 && wall_clock64() - t0 >= A.share_ticks) {   // (not before: a load more a poll)
+                    const unsigned in = held_load(&sync->state) & ~HELD_CLOSED, share = std::min(A.share_ticks * ((n_parts + in - 1) / in), 100u * HELD_DOOR_US);
+                    const unsigned long long now = wall_clock64();
+                    if (in != seen) last = now;
+                    seen = in;
+                    if ((now - t0 >= share && now - last >= share / 4) || now - t0 >= 200u * HELD_DOOR_US) close();
                 }
             }
             if (!all) n = -1;

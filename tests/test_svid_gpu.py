@@ -8,6 +8,7 @@ normalisation; sequential fp32 summation of n positive terms has relative error 
 (2.4e-4 at n = 4096), the tree-shaped parts far less, and the errors of one round enter the next
 through well-conditioned positive sums.  The gate is 2e-4 of the largest entry of each vector."""
 import ctypes
+import time
 
 import numpy as np
 import pytest
@@ -192,7 +193,7 @@ def test_svid_gives_the_same_outside_the_numbers_whatever_the_launches(rows, col
 
 
 def test_svid_waits_for_workgroups_that_a_busy_device_lets_in_late():
-    """248 compute units are busy with another stream's projection, for some 300 us, when a projection of 256 workgroups starts: the eight that find a
+    """248 compute units are busy with another stream's projection, for some 600 us, when a projection of 256 workgroups starts: the eight that find a
     place would take a millisecond for everyone's rows, so they wait for the others, and all are inside in the end.  (Had they gone on alone, the bits would be
     the same.)"""
     rows, cols, iters, busy_rows = 4096, 4096, 8, 3968
@@ -207,7 +208,8 @@ def test_svid_waits_for_workgroups_that_a_busy_device_lets_in_late():
     G.say("start svid beside a busy device")
 
     def occupy():
-        B.dbf_svid(z.data_ptr(), busy_rows, cols, 40, a.data_ptr(), m.data_ptr(), bits.data_ptr(), ws.data_ptr(), ws.numel(), busy.cuda_stream)
+        B.dbf_svid(z.data_ptr(), busy_rows, cols, 80, a.data_ptr(), m.data_ptr(), bits.data_ptr(), ws.data_ptr(), ws.numel(), busy.cuda_stream)
+        time.sleep(2e-4)   # (until it has its places)
 
     a0, m0, words0, inside = _run(Z, iters, before=occupy)
     G.say("  %d of 256 workgroups inside" % inside)
