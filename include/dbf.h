@@ -233,8 +233,10 @@ int dbf_prune_middle(const dbf_layer* layer, const int32_t* keep, int n_keep, db
  *             library (dbf_untile_host turns a host copy into canonical words), padding bits zero.
  *   workspace_dev: device, 256-byte aligned, >= dbf_svid_workspace_bytes(rows, cols) bytes.  (Three, or for less than
  *             12 Mi entries six, rounds and more of a matrix that fits the device's registers are one launch -- of few long
- *             rows only more rounds, or none -- whose workgroups exchange sums; where other work keeps some from starting, the others go on without them once they have waited as
- *             long as doing their part will take, 200 ms at most.  Without the last 2304 bytes a workspace is taken as well: then every round is a launch.)
+ *             rows only more rounds, or none -- whose workgroups exchange sums.  Where other work keeps some from starting,
+ *             the others go on without them once they have waited as long as doing their part will take, 200 ms at most: the
+ *             same bits out.  A wait for sums that lasts seconds is given up, and the factors are no numbers.  Without the
+ *             last 2304 bytes a workspace is taken as well: then every round is a launch.)
  * Asynchronous on hip_stream, allocates nothing; all reductions have a fixed order (results do not
  * depend on scheduling).  Errors: DBF_EINVAL (null / misaligned pointers, sizes out of range,
  * iters < 1), DBF_EWORKSPACE, DBF_EHIP. */
