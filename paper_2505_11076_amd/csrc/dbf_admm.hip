@@ -210,7 +210,7 @@ struct CholBlock {
 // of the multiplication; the rows are scaled by 1 / sqrt(pivot) at the end, all roots at once.  What bounds it: a wavefront on its own issues one
 // instruction in four to five cycles, here 13 and one per row below for a pivot, eight where an instruction waits for the one before it.  (32 pivots
 // 4250 cycles, and 1700 for loads, roots and planes.)
-// `even`, unless NULL: the roots of the pivots, rounded down (or up) to powers of two.
+// `even`, unless NULL: the roots of the pivots, rounded down (or up) to powers of two, zero where there is none.
 // Returns whether a pivot was not positive.
 __device__ __forceinline__ int chol_rows32(const float* diag, float* right, bool keep, uint8_t* row, float* up, float* even, float* spare, int lane) {
     const bool upper = lane >= 32;
@@ -227,8 +227,10 @@ __device__ __forceinline__ int chol_rows32(const float* diag, float* right, bool
         for (int r = 0; r < 32; ++r) spare[r * 64 + lane] = src[r * CH_LD];
         __builtin_amdgcn_wave_barrier();
         bad = chol_rows32_any(spare, lane);
-        // (zero for a pivot that was not positive, or no number)
-        if (even && lane < 32) even[lane] = __builtin_bit_cast(float, min(max(__builtin_bit_cast(unsigned, spare[65 * lane]) & 0x7f800000u, 27u << 23), 227u << 23));
+        if (even && lane < 32) {   // (zero for a pivot that was not positive: T's column is)
+            const unsigned root = __builtin_bit_cast(unsigned, spare[65 * lane]) & 0x7f800000u;
+            even[lane] = __builtin_bit_cast(float, root < 0x7f800000u ? root : 0u);
+        }
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[r] = spare[(16 * h + r) * 64 + 32 + l32];
     } else {
@@ -382,7 +384,8 @@ __device__ __forceinline__ void chol_block(CholBlock& lds, uint8_t* __restrict__
     if (w < 4 && lane < 32) {
         float* const scales = reinterpret_cast<float*>(planes + CH_T_UP) + 32 * ib + l32;
         scales[0] = scale.up;
-        scales[NB] = __builtin_bit_cast(float, (254u << 23) - __builtin_bit_cast(unsigned, lds.even[32 * ib + l32]));
+        const unsigned even = __builtin_bit_cast(unsigned, lds.even[32 * ib + l32]);
+        scales[NB] = __builtin_bit_cast(float, even ? (254u << 23) - even : 0u);   // (a row without a pivot counts as zero)
     }
 }
 

@@ -244,6 +244,28 @@ def test_admm_prepare_argument_errors_and_the_definiteness_flag():
     assert int(flag.item()) >= 1
 
 
+@pytest.mark.parametrize("p,q,rho", [(64, 512, 1e-12), (40, 300, 1e20)])
+def test_admm_prepare_leaves_numbers_behind_pivots_that_are_not_positive(p, q, rho):
+    """G = B^T B + rho I of rank p with rho far below its rounding, or with scales that make it so behind the first block (m2 = 0 in that, 1e18 behind it, rho = 1e20): pivots that are not positive raise the flag, and their rows count as zero.  Minv is not the inverse then, but has no infinities or NaN."""
+    rng = np.random.default_rng(I.seed_for(6, 935 + q))
+    S = np.where(rng.random((q, p)) < 0.5, -1.0, 1.0)
+    m2 = rng.uniform(0.5, 1.5, q).astype(np.float32)
+    if rho > 1:
+        m2 = np.where(np.arange(q) < 128, 0, 1e18 * m2).astype(np.float32)
+    b, W = np.full(p, 0.25, np.float32), rng.standard_normal((p, 16)).astype(np.float32)
+    bits = torch.from_numpy(B.dbf_tile_host(q, p, O.pack_signs(S)).copy()).cuda()
+    dev = [torch.from_numpy(x.copy()).cuda() for x in (m2, b, W)]
+    Minv, Cm = torch.empty((q, q), device="cuda"), torch.empty((q, 16), device="cuda")
+    flag = torch.full((1,), 77, dtype=torch.int32, device="cuda")
+    wsb = B.dbf_admm_prepare_workspace_bytes(p, q, 16)
+    ws = torch.full((wsb,), 0xA5, dtype=torch.uint8, device="cuda")
+    B.dbf_admm_prepare(bits.data_ptr(), dev[0].data_ptr(), dev[1].data_ptr(), dev[2].data_ptr(), p, q, 16, rho, Minv.data_ptr(), Cm.data_ptr(),
+                       ws.data_ptr(), wsb, flag.data_ptr(), G.stream_handle())
+    torch.cuda.synchronize()
+    G.say("  p=%d q=%d: %d blocks with such pivots, largest entry %.2g" % (p, q, int(flag.item()), float(Minv.abs().max())))
+    assert 1 <= int(flag.item()) <= (q + 127) // 128 and bool(torch.isfinite(Minv).all())
+
+
 def test_admm_fixed_point_on_an_exactly_factorisable_target():
     """W = B A* with A* of the SVID form and U = 0: the update must give A* back and leave U at zero
     (to fp32 accuracy)."""
